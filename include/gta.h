@@ -281,7 +281,9 @@ GTA_API const char *gta_strerror(int code);
  * 128), H a multiple of 128; decode in addition needs cache rows of a compiled shape: heads of 128
  * with (n_k, n_q, n_c, d_l) in {(4,4,1,512), (8,8,1,1024), (4,8,1,512), (4,4,2,512), (4,8,2,512),
  * (4,4,4,512)}, or one key of 64 with latents of 128: n_c = 1 with n_q in {3,5,6}, n_c = 2 with n_q in
- * {6,10}.  With GTA_DEBUG set in the environment a bf16 call that takes the generic kernels says so
+ * {6,10}.  fp32 configurations answer 0; stage by stage they run on fp32 MFMA kernels where the shape allows
+ * (widths in units of 64, heads of at most 64; attention: heads of 32, 64 or 128, latents in units of 64;
+ * decode: one key of 64 and one latent of 128 for at most 16 maps).  With GTA_DEBUG set in the environment a bf16 call that takes the generic kernels says so
  * on stderr. */
 GTA_API int gta_uses_tuned_kernels(const gta_config *cfg, int mode);
 

@@ -373,6 +373,9 @@ int gta_prefill_attention(const gta_config *cfg, const void *q, const void *k, c
   hipStream_t st = (hipStream_t)hip_stream;
   if (attn_prefill_supported(d, max_seqlen))
     launch_attn_prefill_bf16(d, q, k, c, cu_seqlens, batch, total_tokens, max_seqlen, l_out, st);
+  else if (f32_attn_ok(d, batch, max_seqlen))
+    launch_attn_prefill_f32(d, (const float *)q, (const float *)k, (const float *)c, cu_seqlens, batch, total_tokens, max_seqlen,
+                            (float *)l_out, st);
   else
     launch_attn_prefill_rowwise(d, q, k, c, cu_seqlens, batch, total_tokens, max_seqlen, l_out, st);
   return check_launch();
@@ -461,7 +464,8 @@ int gta_decode_attention(const gta_config *cfg, const float *q, const gta_cache 
     tuned_decode_attention(d, q, nullptr, ws.oldlen, *cache, slots, batch, ws.splits, ws.part, st);
   } else {
     launch_cached_len(*cache, slots, batch, ws.oldlen, st);
-    generic_decode_attention(d, q, ws.oldlen, *cache, slots, batch, ws.splits, ws.part, st);
+    if (f32_decode_ok(d, *cache, batch)) launch_decode_attn_f32(d, q, ws.oldlen, *cache, slots, batch, ws.splits, ws.part, st);
+    else generic_decode_attention(d, q, ws.oldlen, *cache, slots, batch, ws.splits, ws.part, st);
   }
   return check_launch();
 }
@@ -476,7 +480,7 @@ int gta_decode_combine(const gta_config *cfg, const gta_cache *cache, const int3
   if (!l_out) return GTA_ERR_NULL;
   if (misaligned(l_out)) return GTA_ERR_ALIGN;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (decode_is_tuned(d, *cache)) tuned_decode_combine(d, ws.part, ws.oldlen, ws.splits, batch, l_out, st);
+  if (decode_is_tuned(d, *cache) || f32_decode_ok(d, *cache, batch)) tuned_decode_combine(d, ws.part, ws.oldlen, ws.splits, batch, l_out, st);
   else generic_decode_combine(d, ws.part, ws.oldlen, ws.splits, batch, l_out, st);
   return check_launch();
 }

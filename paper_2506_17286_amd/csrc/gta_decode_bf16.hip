@@ -18,6 +18,15 @@ namespace {
 typedef __bf16 bf16;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) float f32x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// eight consecutive weights
+__device__ __forceinline__ bf16x8 load8(const bf16 *p) { return *reinterpret_cast<const bf16x8 *>(p); }
+__device__ __forceinline__ f32x8 load8(const float *p) {
+  const f32x4 lo = *reinterpret_cast<const f32x4 *>(p), hi = *reinterpret_cast<const f32x4 *>(p + 4);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
@@ -1106,14 +1115,15 @@ __global__ __launch_bounds__(512) void decode_tail1_kernel(Dims d, const float *
 // The tail for the narrow shapes (d_l = 128, d_h = 64, 1 / 2 / 4 heads per map group, at most 32 splits):
 // one workgroup finishes the heads of ONE map group for two sequences, and, like the kernel above, asks
 // for everything it reads -- split statistics, partial accumulators, the group's decoder matrices, the
-// gate partials -- before it uses any of it.
-template <typename TO, int HPQ>
+// gate partials -- before it uses any of it.  TW: element type of the decoder matrices (bf16, or fp32 for the
+// fp32 decode step).
+template <typename TO, typename TW, int HPQ>
 __global__ __launch_bounds__(256) void decode_tail_narrow_kernel(Dims d, const float *__restrict__ pacc,
                                                                  const float *__restrict__ pml,
                                                                  const int32_t *__restrict__ oldlen, int splits,
                                                                  int batch, const float *__restrict__ G, int g_nsum,
                                                                  int64_t g_kstride, int g_ld,
-                                                                 const bf16 *__restrict__ wp, TO *__restrict__ out,
+                                                                 const TW *__restrict__ wp, TO *__restrict__ out,
                                                                  int32_t *seq_lens, int32_t *status,
                                                                  const int32_t *__restrict__ slots, int max_batch) {
   constexpr int DL = 128, DH = 64, MAXS = 32, ROWS = 2;
@@ -1158,11 +1168,11 @@ __global__ __launch_bounds__(256) void decode_tail_narrow_kernel(Dims d, const f
     }
   }
   const int cg = tid % 8, ph = (tid / 8) % NPH, hl = tid / (8 * NPH);   // 8 output columns, latent phase, head
-  bf16x8 w8[APC];
+  decltype(load8(wp)) w8[APC];
   {
-    const bf16 *wb = wp + (int64_t)(g * HPQ + hl) * DL * DH + cg * 8;
+    const TW *wb = wp + (int64_t)(g * HPQ + hl) * DL * DH + cg * 8;
 #pragma unroll
-    for (int i = 0; i < APC; ++i) w8[i] = *reinterpret_cast<const bf16x8 *>(wb + (int64_t)(ph * APC + i) * DH);
+    for (int i = 0; i < APC; ++i) w8[i] = load8(wb + (int64_t)(ph * APC + i) * DH);
   }
   if (g == 0 && tid < ROWS && b0 + tid < batch) {
     const int b = b0 + tid, slot = slots ? slots[b] : b;
@@ -1336,7 +1346,7 @@ void launch_tail_any(const Dims &d, const float *pacc, const float *pml, const D
   if (d.dl == 128 && d.dh == 64 && (d.hpq == 1 || d.hpq == 2 || d.hpq == 4) && ws.splits <= 32) {
     const dim3 grid(d.nq, (batch + 1) / 2);
 #define GTA_TAIL_NARROW(HPQ)                                                                                      \
-    decode_tail_narrow_kernel<TO, HPQ><<<grid, 256, 0, st>>>(d, pacc, pml, ws.oldlen, ws.splits, batch, gs.g, gs.nsum, \
+    decode_tail_narrow_kernel<TO, bf16, HPQ><<<grid, 256, 0, st>>>(d, pacc, pml, ws.oldlen, ws.splits, batch, gs.g, gs.nsum, \
                                                             gs.kstride, gs.ld, wp, out, cache.seq_lens, cache.status, \
                                                             slots, cache.max_batch)
     if (d.hpq == 4) GTA_TAIL_NARROW(4);
@@ -1456,6 +1466,20 @@ void tuned_decode_combine(const Dims &d, const float *part, const int32_t *oldle
   const float *pml = part + (int64_t)batch * splits * d.nq * d.dl;
   decode_combine_kernel<<<dim3((d.dl + 255) / 256, d.nq, batch), 256, splits * sizeof(float), st>>>(
       d, part, pml, oldlen, splits, L);
+}
+
+bool launch_decode_tail_f32(const Dims &d, const DecodeWs &ws, int batch, const float *wp, float *out, const gta_cache &cache,
+                            const int32_t *slots, hipStream_t st) {
+  if (d.dl != 128 || d.dh != 64 || (d.hpq != 1 && d.hpq != 2 && d.hpq != 4) || ws.splits > 32) return false;
+  const float *pml = ws.part + (int64_t)batch * ws.splits * d.nq * d.dl;
+  auto launch = [&](auto kernel) {
+    kernel<<<dim3(d.nq, (batch + 1) / 2), 256, 0, st>>>(d, ws.part, pml, ws.oldlen, ws.splits, batch, ws.g, 1, 0, d.wg_w, wp,
+                                                        out, cache.seq_lens, cache.status, slots, cache.max_batch);
+  };
+  if (d.hpq == 4) launch(decode_tail_narrow_kernel<float, float, 4>);
+  else if (d.hpq == 2) launch(decode_tail_narrow_kernel<float, float, 2>);
+  else launch(decode_tail_narrow_kernel<float, float, 1>);
+  return true;
 }
 
 int tuned_decode(const Dims &d, const gta_weights &w, const void *x_new, int batch, const gta_cache &cache,

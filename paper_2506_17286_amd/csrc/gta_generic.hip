@@ -1,6 +1,7 @@
 // Shape-generic HIP kernels of the GTA attention pass: any dimensions, fp32 or bf16 elements,
-// fp32 arithmetic throughout.  They are the path for the fp32 workloads and for shapes the tuned
-// bf16 kernels do not cover; they favour being obviously right over speed.
+// fp32 arithmetic throughout.  They are the path for shapes that neither the tuned bf16 kernels nor the
+// fp32 MFMA kernels (gta_f32.hip, entered from the drivers below) cover; they favour being obviously right
+// over speed.
 //
 // Pipeline (paper Sec. 3.2-3.3, per-token form App. B.1):
 //   prefill: row map -> RoPE table -> 4 projection GEMMs (raw fp32) -> finalize (RoPE, split into
@@ -10,7 +11,9 @@
 //            partials -> log-sum-exp combine -> decoder GEMM with gate epilogue -> [W_O] -> commit
 #include <math.h>
 
-#include "gta_internal.h"
+#include <type_traits>
+
+#include "gta_tuned.h"
 
 namespace gta {
 namespace {
@@ -659,15 +662,10 @@ CacheView view_of(const gta_cache *c, const int32_t *slots) {
 inline dim3 grid1d(int64_t n, int block = 256) { return dim3((unsigned)((n + block - 1) / block)); }
 
 // ------------------------------------------------------------------------------ drivers
+// Raw fp32 projections into ws.praw, then RoPE, the split into Q | K | C | gate and the cache rows.
 template <typename T>
-int prefill_impl(const Dims &d, const gta_weights &w, const T *x, const int32_t *cu, int batch, int64_t total,
-                 int max_len, const gta_cache *cache, const int32_t *slots, T *out, const PrefillWs &ws,
-                 hipStream_t st) {
-  const int per_seq = (int)(total / batch);
-  const int M = (int)total;
-  launch_rowmap(cu, batch, total, ws.seq_id, ws.pos, st);
-  if (d.rope) launch_rope_table(ws.rope, max_len, d.dh, d.rope_base, st);
-  // Sec. 3.2 projections, raw fp32: [Q | K | C | gate pre-activation]
+void project_raw(const Dims &d, const gta_weights &w, const T *x, int M, const PrefillWs &ws, const gta_cache *cache,
+                 const int32_t *slots, int64_t total, int max_len, int rope_by_token, hipStream_t st) {
   const T *wmat[4] = {(const T *)w.wq, (const T *)w.wk, (const T *)w.wc, (const T *)w.wg};
   const int wn[4] = {d.wq_w, d.wk_w, d.wc_w, d.wg_w};
   int off = 0;
@@ -676,26 +674,50 @@ int prefill_impl(const Dims &d, const gta_weights &w, const T *x, const int32_t 
                 EpiStoreF32{ws.praw, d.wtot, off}, st);
     off += wn[i];
   }
-  CacheView cv = view_of(cache, slots);
   finalize_prefill_kernel<T><<<grid1d(total * d.wtot), 256, 0, st>>>(
-      d, ws.praw, ws.seq_id, ws.pos, ws.rope, max_len, total, (T *)ws.q, (T *)ws.k, (T *)ws.c, (float *)ws.g, cv);
-  if (cache) launch_prefill_commit(*cache, slots, cu, batch, total, st);
+      d, ws.praw, ws.seq_id, ws.pos, ws.rope, max_len, total, (T *)ws.q, (T *)ws.k, (T *)ws.c, (float *)ws.g,
+      view_of(cache, slots), rope_by_token);
+}
+
+// Value decoder with the gate (Sec. 3.2), then the optional output projection (Sec. 3.3), from ws.l and ws.g.
+template <typename T>
+void finish_heads(const Dims &d, const gta_weights &w, int M, const PrefillWs &ws, T *out, hipStream_t st) {
+  constexpr bool F32 = std::is_same<T, float>::value;
+  const float *L = (const float *)ws.l, *G = (const float *)ws.g;
+  float *O = (float *)ws.o;
+  auto decode_heads = [&](auto *dst) {
+    typedef typename std::remove_pointer<decltype(dst)>::type TD;
+    if (F32 && f32_decoder_ok(d, M)) { launch_decoder_f32(d, L, w.wp, G, (float *)dst, M, st); return; }
+    launch_gemm(L, (int64_t)d.nq * d.dl, (int64_t)d.dl, d.hpq, (const T *)w.wp, (int64_t)d.dh, (int64_t)d.dl * d.dh,
+                M, d.dh, d.dl, d.nh, EpiGate<TD>{dst, d.wg_w, G, d.wg_w, d.dh, d.gate}, st);
+  };
+  if (!w.wo) { decode_heads(out); return; }
+  decode_heads(O);
+  if (F32 && f32_gemms_ok(d, M)) launch_out_proj_f32(d, O, w.wo, (float *)out, M, st);
+  else launch_gemm(O, (int64_t)d.wg_w, 0, 1, (const T *)w.wo, (int64_t)d.H, 0, M, d.H, d.wg_w, 1, EpiStoreT<T>{out, d.H}, st);
+}
+
+template <typename T>
+int prefill_impl(const Dims &d, const gta_weights &w, const T *x, const int32_t *cu, int batch, int64_t total,
+                 int max_len, const gta_cache *cache, const int32_t *slots, T *out, const PrefillWs &ws,
+                 hipStream_t st) {
+  const int per_seq = (int)(total / batch);
+  const int M = (int)total;
+  constexpr bool F32 = std::is_same<T, float>::value;   // fp32: MFMA kernels where the shape allows (gta_f32.hip)
+  launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
+  // Sec. 3.2 projections, RoPE, cache rows: [Q | K | C | gate pre-activation]
+  if (F32 && f32_gemms_ok(d, total)) launch_proj_f32(d, w, x, M, ws, cache, slots, max_len, false, st);
+  else project_raw<T>(d, w, x, M, ws, cache, slots, total, max_len, 0, st);
   // shared attention map x latent values, one map per group (Sec. 3.3)
-  dim3 agrid((max_len + 3) / 4, d.nq, batch);
-  attn_prefill_generic_kernel<T, float><<<agrid, 256, 4 * d.dh * sizeof(float), st>>>(
-      d, (const T *)ws.q, (const T *)ws.k, (const T *)ws.c, cu, per_seq, max_len, (float *)ws.l);
-  // value decoder with gate epilogue (Sec. 3.2), then the optional output projection (Sec. 3.3)
-  const float *L = (const float *)ws.l;
-  if (w.wo) {
-    float *O = (float *)ws.o;
-    launch_gemm(L, (int64_t)d.nq * d.dl, (int64_t)d.dl, d.hpq, (const T *)w.wp, (int64_t)d.dh, (int64_t)d.dl * d.dh,
-                M, d.dh, d.dl, d.nh, EpiGate<float>{O, d.wg_w, (const float *)ws.g, d.wg_w, d.dh, d.gate}, st);
-    launch_gemm(O, (int64_t)d.wg_w, 0, 1, (const T *)w.wo, (int64_t)d.H, 0, M, d.H, d.wg_w, 1,
-                EpiStoreT<T>{out, d.H}, st);
+  if (F32 && f32_attn_ok(d, batch, max_len)) {
+    launch_attn_prefill_f32(d, (const float *)ws.q, (const float *)ws.k, (const float *)ws.c, cu, batch, total, max_len,
+                            (float *)ws.l, st);
   } else {
-    launch_gemm(L, (int64_t)d.nq * d.dl, (int64_t)d.dl, d.hpq, (const T *)w.wp, (int64_t)d.dh, (int64_t)d.dl * d.dh,
-                M, d.dh, d.dl, d.nh, EpiGate<T>{out, d.wg_w, (const float *)ws.g, d.wg_w, d.dh, d.gate}, st);
+    dim3 agrid((max_len + 3) / 4, d.nq, batch);
+    attn_prefill_generic_kernel<T, float><<<agrid, 256, 4 * d.dh * sizeof(float), st>>>(
+        d, (const T *)ws.q, (const T *)ws.k, (const T *)ws.c, cu, per_seq, max_len, (float *)ws.l);
   }
+  finish_heads<T>(d, w, M, ws, out, st);
   return check_launch();
 }
 
@@ -708,31 +730,13 @@ int prefill_chunk_impl(const Dims &d, const gta_weights &w, const T *x, const in
   const int per_seq = (int)(total / batch);
   const int M = (int)total;
   launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, st);
-  const T *wmat[4] = {(const T *)w.wq, (const T *)w.wk, (const T *)w.wc, (const T *)w.wg};
-  const int wn[4] = {d.wq_w, d.wk_w, d.wc_w, d.wg_w};
-  int off = 0;
-  for (int i = 0; i < 4; ++i) {
-    launch_gemm(x, (int64_t)d.H, 0, 1, wmat[i], (int64_t)wn[i], 0, M, wn[i], d.H, 1,
-                EpiStoreF32{ws.praw, d.wtot, off}, st);
-    off += wn[i];
-  }
+  if (std::is_same<T, float>::value && f32_gemms_ok(d, total)) launch_proj_f32(d, w, x, M, ws, &cache, slots, max_chunk, true, st);
+  else project_raw<T>(d, w, x, M, ws, &cache, slots, total, max_chunk, 1, st);
   CacheView cv = view_of(&cache, slots);
-  finalize_prefill_kernel<T><<<grid1d(total * d.wtot), 256, 0, st>>>(
-      d, ws.praw, ws.seq_id, ws.pos, ws.rope, max_chunk, total, (T *)ws.q, (T *)ws.k, (T *)ws.c, (float *)ws.g, cv, 1);
   dim3 agrid((max_chunk + 3) / 4, d.nq, batch);
   attn_chunk_generic_kernel<T, float><<<agrid, 256, 4 * d.dh * sizeof(float), st>>>(
       d, (const T *)ws.q, cv, ws.prefix, cu, per_seq, (float *)ws.l);
-  const float *L = (const float *)ws.l;
-  if (w.wo) {
-    float *O = (float *)ws.o;
-    launch_gemm(L, (int64_t)d.nq * d.dl, (int64_t)d.dl, d.hpq, (const T *)w.wp, (int64_t)d.dh, (int64_t)d.dl * d.dh,
-                M, d.dh, d.dl, d.nh, EpiGate<float>{O, d.wg_w, (const float *)ws.g, d.wg_w, d.dh, d.gate}, st);
-    launch_gemm(O, (int64_t)d.wg_w, 0, 1, (const T *)w.wo, (int64_t)d.H, 0, M, d.H, d.wg_w, 1,
-                EpiStoreT<T>{out, d.H}, st);
-  } else {
-    launch_gemm(L, (int64_t)d.nq * d.dl, (int64_t)d.dl, d.hpq, (const T *)w.wp, (int64_t)d.dh, (int64_t)d.dl * d.dh,
-                M, d.dh, d.dl, d.nh, EpiGate<T>{out, d.wg_w, (const float *)ws.g, d.wg_w, d.dh, d.gate}, st);
-  }
+  finish_heads<T>(d, w, M, ws, out, st);
   launch_prefill_chunk_commit(cache, slots, cu, batch, total, ws.prefix, st);
   return check_launch();
 }
@@ -842,6 +846,7 @@ int generic_prefill_chunk(const Dims &d, const gta_weights &w, const void *x, co
 
 int generic_decode(const Dims &d, const gta_weights &w, const void *x_new, int batch, const gta_cache &cache,
                    const int32_t *slots, void *out, const DecodeWs &ws, hipStream_t st) {
+  if (f32_decode_ok(d, cache, batch)) return f32_decode(d, w, x_new, batch, cache, slots, out, ws, st);
   if (d.dtype == GTA_BF16)
     return decode_impl<bf16>(d, w, (const bf16 *)x_new, batch, cache, slots, (bf16 *)out, ws, st);
   return decode_impl<float>(d, w, (const float *)x_new, batch, cache, slots, (float *)out, ws, st);

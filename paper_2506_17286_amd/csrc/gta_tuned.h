@@ -58,4 +58,25 @@ void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
                             void *L, const void *wp, const void *gate, void *out, bool fuse, hipStream_t st);
 
+// fp32 MFMA kernels (gta_f32.hip).  They serve the shape-generic entry path where the shape allows; each condition
+// covers its own kernels.
+bool f32_gemms_ok(const Dims &d, int64_t M);                                  // projection, output projection
+bool f32_decoder_ok(const Dims &d, int64_t M);                                // value decoder
+bool f32_attn_ok(const Dims &d, int batch, int max_len);                      // prefill attention
+bool f32_decode_ok(const Dims &d, const gta_cache &cache, int batch);         // decode step
+void launch_proj_f32(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
+                     const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st);
+void launch_decoder_f32(const Dims &d, const float *L, const void *wp, const float *gate, float *out, int M, hipStream_t st);
+void launch_out_proj_f32(const Dims &d, const float *O, const void *wo, float *out, int M, hipStream_t st);
+void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, const float *c, const int32_t *cu, int batch,
+                             int64_t total, int max_len, float *L, hipStream_t st);
+// partials in the layout of tuned_decode_attention (merged by tuned_decode_combine or the tail)
+void launch_decode_attn_f32(const Dims &d, const float *q, const int32_t *oldlen, const gta_cache &cache, const int32_t *slots,
+                            int batch, int splits, float *part, hipStream_t st);
+int f32_decode(const Dims &d, const gta_weights &w, const void *x_new, int batch, const gta_cache &cache, const int32_t *slots,
+               void *out, const DecodeWs &ws, hipStream_t st);
+// the narrow decode tail on fp32 weights (gta_decode_bf16.hip); false where it does not take the call
+bool launch_decode_tail_f32(const Dims &d, const DecodeWs &ws, int batch, const float *wp, float *out, const gta_cache &cache,
+                            const int32_t *slots, hipStream_t st);
+
 }  // namespace gta

@@ -1,0 +1,95 @@
+"""The fp32 MFMA kernels against the oracle at the edges of their tiles: row tiles of 32 (few rows) and 128 (many),
+32-key blocks dealt to four waves, latent slices of 64 and 128 columns, 16-row decode steps, splits without rows,
+contiguous and block-table caches, full slots.
+
+Bound: the fp32 tolerances of the parity gate (max-abs 1e-5, relative RMS 1e-5); sums of at most 1280 fp32 products
+stay a factor of ten below them."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as U
+from oracle import gta_oracle as orc
+from paper_2506_17286_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+PAPER = dict(d_model=128, n_heads=20, n_qgroups=5, n_kgroups=1, n_cgroups=1, head_dim=64, latent_dim=128)
+SHAPES = {
+    "paper": PAPER,
+    "paper_nq3": dict(PAPER, n_heads=12, n_qgroups=3),
+    "paper_h1": dict(PAPER, n_heads=16, n_qgroups=16),                   # as many maps as a step has columns
+    "heads32": dict(d_model=64, n_heads=8, n_qgroups=2, n_kgroups=2, n_cgroups=1, head_dim=32, latent_dim=64),
+    "heads16": dict(d_model=64, n_heads=8, n_qgroups=4, n_kgroups=4, n_cgroups=2, head_dim=16, latent_dim=32),
+    "latent192": dict(d_model=192, n_heads=4, n_qgroups=2, n_kgroups=1, n_cgroups=1, head_dim=64, latent_dim=192),
+    "latent256": dict(d_model=64, n_heads=4, n_qgroups=4, n_kgroups=2, n_cgroups=2, head_dim=64, latent_dim=256),
+    "heads128": dict(d_model=64, n_heads=2, n_qgroups=2, n_kgroups=1, n_cgroups=1, head_dim=128, latent_dim=128),
+}
+LENS = {"short": [1, 31, 32, 33, 97], "long": [513, 2, 160]}
+
+
+def _wl(shape, **kw):
+    return W.Workload(name=f"f32_{shape}", kind="prefill", batch=1, seqlen=64, dtype="f32", rope=True, seed=4100,
+                      **dict(SHAPES[shape], **kw))
+
+
+def _inputs(wl, tokens, with_wo):
+    rng = W.make_rng(wl)
+    # weights of standard deviation 1/sqrt(H): scores and gates of order one at these small widths
+    w = W.draw_weights(wl, rng, with_wo=with_wo, std=wl.d_model ** -0.5)
+    return w, W.draw_hidden(wl, rng, tokens)
+
+
+def _scale(ref):
+    return max(1.0, float(np.abs(ref).max()))
+
+
+@pytest.mark.parametrize("with_wo", [False, True])
+@pytest.mark.parametrize("lens", list(LENS))
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_prefill(shape, lens, with_wo):
+    wl, lens = _wl(shape), LENS[lens]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    w, x = _inputs(wl, int(cu[-1]), with_wo)
+    cache = U.DeviceCache(wl, len(lens), max(lens) + 3, fill=7.0)
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "f32"), x, cu, cache=cache))
+    for b, n in enumerate(lens):
+        ref, k, c = orc.prefill_sequence(U.oracle_config(wl), U.oracle_weights(w), x[cu[b]:cu[b + 1]])
+        U.assert_close(out[cu[b]:cu[b + 1]], ref, "f32", f"{shape} sequence {b}", _scale(ref))
+        U.assert_close(U.f64(cache.k[b, :n]), k.reshape(n, -1), "f32", "keys", _scale(k))
+        U.assert_close(U.f64(cache.c[b, :n]), c.reshape(n, -1), "f32", "latents", _scale(c))
+        assert bool((cache.k[b, n:] == 7.0).all()) and int(cache.seq_lens[b]) == n
+
+
+@pytest.mark.parametrize("splits", [0, 1, 5, 40])          # 40: more than the one-round-trip tail takes
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("shape", ["paper", "paper_nq3", "paper_h1"])
+def test_decode(shape, paged, splits):
+    """Contexts around the 16-row step, an empty slot, a full slot; two steps in a row."""
+    wl = _wl(shape)
+    ctx = [0, 1, 15, 16, 17, 255, 300, 336]
+    cap = 336                                              # the last slot is full
+    w, x = _inputs(wl, 2 * len(ctx), True)
+    wdev, (kw, cw) = U.upload_weights(w, "f32"), wl.kv_width
+    rng = np.random.default_rng(5)
+    k0 = rng.standard_normal((len(ctx), cap, kw)).astype(np.float32)
+    c0 = rng.standard_normal((len(ctx), cap, cw)).astype(np.float32)
+    if paged:
+        cache = U.PagedDeviceCache(wl, len(ctx), 16, cap // 16, seed=3)
+        cache.store(torch.from_numpy(k0).cuda(), torch.from_numpy(c0).cuda())
+    else:
+        cache = U.DeviceCache(wl, len(ctx), cap, torch.from_numpy(k0).cuda(), torch.from_numpy(c0).cuda())
+    cache.seq_lens.copy_(torch.tensor(ctx, dtype=torch.int32))
+    kr, cr = k0.astype(np.float64), c0.astype(np.float64)
+    lens, status = np.array(ctx, dtype=np.int32), np.zeros(len(ctx), dtype=np.int32)
+    for step in range(2):
+        xs = x[step * len(ctx):(step + 1) * len(ctx)]
+        ref = orc.decode(U.oracle_config(wl), U.oracle_weights(w), xs, kr, cr, lens, status, range(len(ctx)))
+        out = U.f64(U.run_decode(wl, wdev, xs, cache, num_splits=splits))
+        assert not out[-1].any()                           # the full slot
+        U.assert_close(out, ref, "f32", f"{shape} step {step}", _scale(ref))
+        kd, cd = cache.logical() if paged else (cache.k, cache.c)
+        U.assert_close(U.f64(kd), kr, "f32", "keys", _scale(kr))
+        U.assert_close(U.f64(cd), cr, "f32", "latents", _scale(cr))
+        np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
+        np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
