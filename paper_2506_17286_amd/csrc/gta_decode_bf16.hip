@@ -1484,11 +1484,23 @@ bool launch_decode_tail_f32(const Dims &d, const DecodeWs &ws, int batch, const 
 
 int tuned_decode(const Dims &d, const gta_weights &w, const void *x_new, int batch, const gta_cache &cache,
                  const int32_t *slots, void *out, const DecodeWs &ws, hipStream_t st) {
-  // Three launches: split-K projection of the new tokens (Sec. 3.2); attention, whose workgroups sum
-  // the partials, rotate q and k at position seq_len and append the new rows themselves; the tail
-  // (combine, value decoder, gate from the same partials, bookkeeping).
+  // Three launches: projection of the new tokens (Sec. 3.2), as fp32 split-K partials or finished; attention, whose
+  // workgroups in the first case sum the partials, rotate q and k at position seq_len and append the new
+  // rows themselves; the tail (combine, value decoder, gate, bookkeeping).
   GateSrc gs;
-  if (gemm_shapes_supported(d)) {
+  // Few rows against narrow weights: the projection whose workgroups split K themselves hands q, gate and the new
+  // rows over finished, so the attention kernel sums no partials (paper layer, whole step: batch 64 45 -> 42 us,
+  // batch 128 46 -> 42, batch 1 33 -> 31.5).  Wide weights are re-read per 32 rows and its 64-byte pieces of a
+  // weight row stream worse than the 256-byte pieces of the split-K kernel, while a long stream hides the partials'
+  // sums: there only up to 8 sequences and 32K rows in all (1B shape, 8 behind 1000 rows 27.4 -> 26.3 us, 8 behind
+  // 8192 43.8 -> 44.1, 64 behind 8192 190 -> 192; 8 x 128 + 1024 shape, 1 behind 1000 56.7 -> 53.5, 8 behind 8192
+  // 89.3 -> 90.2, 64 behind 2000 141 -> 155).
+  const bool narrow_weights = batch <= 128 && d.H <= 1536;
+  if (rows_gemm_ok(d) && (narrow_weights || (batch <= 8 && (int64_t)batch * cache.max_seq <= 32768))) {
+    launch_rows_proj_decode(d, w, x_new, batch, cache, slots, ws, st);
+    tuned_decode_attention(d, ws.q, ws.oldlen, nullptr, cache, slots, batch, ws.splits, ws.part, st);
+    gs = GateSrc{ws.g, 1, 0, d.wg_w};
+  } else if (gemm_shapes_supported(d)) {
     const int ks = skinny_ksplit(d, batch);
     launch_skinny_proj(d, w, x_new, batch, ws.praw, ks, st);
     RopeFreq rf{};

@@ -1,0 +1,172 @@
+// Epilogues shared by the GEMM kernels that hand out groups of four finished columns (gta_f32.hip,
+// gta_rows_bf16.hip), and the column tiles of the kernels for few rows.
+#pragma once
+#include "gta_internal.h"
+
+namespace gta {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+__device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
+__device__ __forceinline__ void store4(__bf16 *p, f32x4 v) {
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  bf16x4 o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = (__bf16)v[i];
+  *reinterpret_cast<bf16x4 *>(p) = o;
+}
+
+// sin and cos of p * f: the angle is formed and reduced to [-pi/4, pi/4] in fp64 (pi/2 in two parts), then the Taylor
+// series to degree 9 / 10 in fp32 (the first terms left out are below 2e-9 and 2e-10 there) and the quadrant.
+__device__ __forceinline__ void rope_sincos(int p, double f, float &sn, float &cs) {
+  const double ang = (double)p * f;
+  const double k = rint(ang * 0.6366197723675814);
+  double rd = fma(-k, 1.5707963267948966, ang);
+  rd = fma(-k, 6.123233995736766e-17, rd);
+  const float r = (float)rd, r2 = r * r;
+  const float s = fmaf(r * r2, fmaf(r2, fmaf(r2, fmaf(r2, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), r);
+  const float c = fmaf(r2, fmaf(r2, fmaf(r2, fmaf(r2, fmaf(r2, -1.f / 3628800.f, 1.f / 40320.f), -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
+  const int q = (int)(k - 4.0 * floor(k * 0.25));   // quadrant 0 .. 3
+  const float a = q & 1 ? c : s, b = q & 1 ? s : c;
+  sn = q & 2 ? -a : a;
+  cs = (q + 1) & 2 ? -b : b;
+}
+
+// ------------------------------------------------------------------------------ epilogues
+// A GEMM hands its epilogue groups of four columns in three calls: early(row, first column, rotated tile?) requests
+// what the group reads itself, prepare() works out position, cache row and sines, store() takes the values and
+// `partner`, which returns the four values half a head further (used by the rotation only).  The kernels for few
+// rows call early() ahead of their operand loads and prepare() under them: behind them the two cost a decode step
+// 6 us.  Columns are global (all segments).
+
+// Projection (Sec. 3.2) with RoPE on q and k (App. B.1.1) and the cache write (App. B.1.3).
+// TD: element type of the Q | K | C | gate rows (a decode step keeps q and gate in fp32), TC: of the caches.
+template <typename TD, typename TC>
+struct ProjEpi {
+  TD *dst[4]; int width[4];                 // Q | K | C | gate rows (decode: K and C go to the caches only)
+  int dh, rope;
+  // prefill: position and sequence of every packed token and the (cos, sin) table
+  const int32_t *seq_id, *pos; const float2 *table; int max_len, rope_by_token;
+  // decode (seq_lens != NULL): row b is the new token of slot slots[b] at position seq_lens[slot]
+  const int32_t *seq_lens; int32_t *oldlen; double freq[64];
+  TC *kcache, *ccache; const int32_t *slots; int max_batch, max_seq; PageMap pm;   // kcache NULL: no cache write
+
+  __device__ __forceinline__ void locate(int col, int &seg, int &local) const {
+    seg = 0;
+    while (seg < 3 && col >= width[seg]) { col -= width[seg]; ++seg; }
+    local = col;
+  }
+  // does the tile of columns starting at `col` (one segment) hold rotated values?
+  __device__ __forceinline__ bool rotates(int col) const { return rope && col < width[0] + width[1]; }
+  __device__ __forceinline__ int head_dim() const { return dh; }
+  // what a group of four columns reads on its own account, requested before anything else (early), and what follows
+  // from it without the group's values (prepare)
+  struct Early { int slot, p, seq; double f[4]; };
+  struct Ctx { int seg, lc, half; int64_t cr; f32x4 cs, sn; };   // half: distance to the partner (signed), 0 = not rotated
+  __device__ __forceinline__ Early early(int row, int col, bool rot) const {
+    Early e{};
+    if (seq_lens) {
+      e.slot = slots ? slots[row] : row;
+      const bool ok = e.slot >= 0 && e.slot < max_batch;
+      e.p = seq_lens[ok ? e.slot : 0];
+      if (!ok) e.p = -1;
+      if (rot) {
+        const int j = col % (dh / 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e.f[i] = freq[j + i];
+      }
+    } else {
+      e.p = pos[row];
+      if (kcache) e.seq = seq_id[row];
+    }
+    return e;
+  }
+  __device__ __forceinline__ Ctx prepare(const Early &y, int row, int col, bool rot) const {
+    Ctx c;
+    locate(col, c.seg, c.lc);
+    int p = y.p;
+    c.cr = -1;
+    if (seq_lens) {
+      if (p >= 0 && p < max_seq) c.cr = cache_row(pm, max_seq, y.slot, p);
+      if (col == 0) oldlen[row] = c.cr >= 0 ? p : -1;
+      if (c.cr < 0) p = 0;                      // slot full: nothing is appended, the tail zero-fills the sequence
+    } else if (kcache && (c.seg == 1 || c.seg == 2)) {
+      const int slot = slots ? slots[y.seq] : y.seq;
+      if (slot >= 0 && slot < max_batch && p >= 0 && p < max_seq) c.cr = cache_row(pm, max_seq, slot, p);
+    }
+    c.half = 0;
+    if (rot && (seq_lens || rope_by_token || p < max_len)) {
+      const int half = dh / 2, e = c.lc % dh, j = e < half ? e : e - half;
+      c.half = e < half ? half : -half;
+      if (seq_lens) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { float s, t; rope_sincos(p, y.f[i], s, t); c.sn[i] = s; c.cs[i] = t; }
+      } else {
+        const float4 *t = reinterpret_cast<const float4 *>(table + (int64_t)(rope_by_token ? row : p) * half + j);
+        const float4 t0 = t[0], t1 = t[1];
+        c.cs = f32x4{t0.x, t0.z, t1.x, t1.z}; c.sn = f32x4{t0.y, t0.w, t1.y, t1.w};
+      }
+    }
+    return c;
+  }
+  template <class Partner>
+  __device__ __forceinline__ void store(const Ctx &c, int row, f32x4 v, Partner partner) const {
+    if (c.half) {
+      const f32x4 o = partner(c.half);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = c.half > 0 ? v[i] * c.cs[i] - o[i] * c.sn[i] : v[i] * c.cs[i] + o[i] * c.sn[i];
+    }
+    const bool cached = c.seg == 1 || c.seg == 2;
+    if (!(seq_lens && cached)) store4(dst[c.seg] + (int64_t)row * width[c.seg] + c.lc, v);
+    if (c.cr >= 0 && cached) store4((c.seg == 1 ? kcache : ccache) + c.cr * width[c.seg] + c.lc, v);
+  }
+};
+
+// Value decoder (Sec. 3.2): times the gate factor of the same element.
+template <typename T>
+struct GateEpi {
+  T *out; const float *g; int ld, gate;
+  __device__ __forceinline__ bool rotates(int) const { return false; }
+  __device__ __forceinline__ int head_dim() const { return 0; }
+  struct Early {};
+  struct Ctx { int col; };
+  __device__ __forceinline__ Early early(int, int, bool) const { return Early{}; }
+  __device__ __forceinline__ Ctx prepare(const Early &, int, int col, bool) const { return Ctx{col}; }
+  template <class Partner>
+  __device__ __forceinline__ void store(const Ctx &c, int row, f32x4 v, Partner) const {
+    const int64_t o = (int64_t)row * ld + c.col;
+    if (gate) {
+      const f32x4 z = *reinterpret_cast<const f32x4 *>(g + o);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] *= gate == kGateSigmoid ? 1.0f / (1.0f + expf(-z[i])) : gate_factor(gate, z[i]);
+    }
+    store4(out + o, v);
+  }
+};
+
+template <typename T>
+struct StoreEpi {
+  T *out; int ld;
+  __device__ __forceinline__ bool rotates(int) const { return false; }
+  __device__ __forceinline__ int head_dim() const { return 0; }
+  struct Early {};
+  struct Ctx { int col; };
+  __device__ __forceinline__ Early early(int, int, bool) const { return Early{}; }
+  __device__ __forceinline__ Ctx prepare(const Early &, int, int col, bool) const { return Ctx{col}; }
+  template <class Partner>
+  __device__ __forceinline__ void store(const Ctx &c, int row, f32x4 v, Partner) const {
+    store4(out + (int64_t)row * ld + c.col, v);
+  }
+};
+
+// Column tile nt (32 columns) of the kernels for few rows: tile column c is global column col0 + c % 16 +
+// (c / 16) * step.  A rotated tile must hold both halves of its heads: with heads wider than 32 it takes 16
+// columns of one half and the 16 they pair with (`pair`), otherwise whole heads lie in 32 columns in a row.
+struct RowTile { int col0, step; bool pair; };
+__device__ __forceinline__ RowTile row_tile(int nt, bool rot, int dh) {
+  if (!rot || dh <= 32) return RowTile{nt * 32, 16, false};
+  const int tph = dh / 32;
+  return RowTile{nt / tph * dh + nt % tph * 16, dh / 2, true};
+}
+
+}  // namespace gta

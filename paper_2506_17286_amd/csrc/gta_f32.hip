@@ -10,14 +10,13 @@
 // eight, one k per step.
 #include <math.h>
 
+#include "gta_epilogues.h"
 #include "gta_tuned.h"
 
 namespace gta {
 namespace {
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ void zero16(f32x16 &v) {
@@ -33,110 +32,6 @@ __device__ __forceinline__ float pair_sum(float v) {
   const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-
-// RoPE angle of position p and frequency f: reduced mod 2 pi in fp64, then fp32 sincos
-__device__ __forceinline__ void rope_sincos(int p, double f, float &sn, float &cs) {
-  const double ang = (double)p * f;
-  const double k = rint(ang * 0.15915494309189535);
-  double r = fma(-k, 6.283185307179586, ang);
-  r = fma(-k, 2.4492935982947064e-16, r);
-  sincosf((float)r, &sn, &cs);
-}
-
-// ------------------------------------------------------------------------------ epilogues
-// A GEMM hands its epilogue groups of four columns: store(row, first column, values, partner), where `partner`
-// returns the four values half a head further (used by the rotation only).  Columns are global (all segments).
-
-// Projection (Sec. 3.2) with RoPE on q and k (App. B.1.1) and the cache write (App. B.1.3).
-struct ProjEpi {
-  float *dst[4]; int width[4];              // Q | K | C | gate rows
-  int dh, rope;
-  // prefill: position and sequence of every packed token and the (cos, sin) table
-  const int32_t *seq_id, *pos; const float2 *table; int max_len, rope_by_token;
-  // decode (seq_lens != NULL): row b is the new token of slot slots[b] at position seq_lens[slot]
-  const int32_t *seq_lens; int32_t *oldlen; double freq[32];
-  float *kcache, *ccache; const int32_t *slots; int max_batch, max_seq; PageMap pm;   // kcache NULL: no cache write
-
-  __device__ __forceinline__ void locate(int col, int &seg, int &local) const {
-    seg = 0;
-    while (seg < 3 && col >= width[seg]) { col -= width[seg]; ++seg; }
-    local = col;
-  }
-  // does the tile of columns starting at `col` (one segment) hold rotated values?
-  __device__ __forceinline__ bool rotates(int col) const { return rope && col < width[0] + width[1]; }
-  __device__ __forceinline__ int head_dim() const { return dh; }
-  template <class Partner>
-  __device__ __forceinline__ void store(int row, int col, f32x4 v, bool rot, Partner partner) const {
-    int seg, lc;
-    locate(col, seg, lc);
-    int slot, p;
-    int64_t cr = -1;
-    if (seq_lens) {
-      slot = slots ? slots[row] : row;
-      const bool ok = slot >= 0 && slot < max_batch;
-      p = ok ? seq_lens[slot] : -1;
-      if (p >= 0 && p < max_seq) cr = cache_row(pm, max_seq, slot, p);
-      if (col == 0) oldlen[row] = cr >= 0 ? p : -1;
-      if (cr < 0) p = 0;                        // slot full: nothing is appended, the tail zero-fills the sequence
-    } else {
-      p = pos[row];
-      if (kcache && (seg == 1 || seg == 2)) {
-        const int b = seq_id[row];
-        slot = slots ? slots[b] : b;
-        if (slot >= 0 && slot < max_batch && p >= 0 && p < max_seq) cr = cache_row(pm, max_seq, slot, p);
-      }
-    }
-    if (rot) {
-      const int half = dh / 2, e = lc % dh, j = e < half ? e : e - half;
-      const f32x4 o = partner(e < half ? half : -half);
-      f32x4 cs, sn;
-      bool turn = true;
-      if (seq_lens) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { float s, c; rope_sincos(p, freq[j + i], s, c); sn[i] = s; cs[i] = c; }
-      } else {
-        turn = rope_by_token || p < max_len;
-        const float4 *t = reinterpret_cast<const float4 *>(table + (int64_t)(turn ? (rope_by_token ? row : p) : 0) * half + j);
-        const float4 t0 = t[0], t1 = t[1];
-        cs = f32x4{t0.x, t0.z, t1.x, t1.z}; sn = f32x4{t0.y, t0.w, t1.y, t1.w};
-      }
-      if (turn) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = e < half ? v[i] * cs[i] - o[i] * sn[i] : v[i] * cs[i] + o[i] * sn[i];
-      }
-    }
-    if (!(seq_lens && (seg == 1 || seg == 2))) *reinterpret_cast<f32x4 *>(dst[seg] + (int64_t)row * width[seg] + lc) = v;
-    if (cr >= 0 && (seg == 1 || seg == 2))
-      *reinterpret_cast<f32x4 *>((seg == 1 ? kcache : ccache) + cr * width[seg] + lc) = v;
-  }
-};
-
-// Value decoder (Sec. 3.2): times the gate factor of the same element.
-struct GateEpi {
-  float *out; const float *g; int ld, gate;
-  __device__ __forceinline__ bool rotates(int) const { return false; }
-  __device__ __forceinline__ int head_dim() const { return 0; }
-  template <class Partner>
-  __device__ __forceinline__ void store(int row, int col, f32x4 v, bool, Partner) const {
-    const int64_t o = (int64_t)row * ld + col;
-    if (gate) {
-      const f32x4 z = *reinterpret_cast<const f32x4 *>(g + o);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] *= gate == kGateSigmoid ? 1.0f / (1.0f + expf(-z[i])) : gate_factor(gate, z[i]);
-    }
-    *reinterpret_cast<f32x4 *>(out + o) = v;
-  }
-};
-
-struct StoreEpi {
-  float *out; int ld;
-  __device__ __forceinline__ bool rotates(int) const { return false; }
-  __device__ __forceinline__ int head_dim() const { return 0; }
-  template <class Partner>
-  __device__ __forceinline__ void store(int row, int col, f32x4 v, bool, Partner) const {
-    *reinterpret_cast<f32x4 *>(out + (int64_t)row * ld + col) = v;
-  }
-};
 
 // ------------------------------------------------------------------------------ operands
 // Both operands for the columns from `col` on: the segment they lie in (projection), or the head they belong to
@@ -167,17 +62,20 @@ __device__ __forceinline__ void operand_at(const GemmOperands &g, int col, const
 // trip), U groups in flight; the W partial tiles are summed through LDS in a fixed order.  For a decode step's
 // rows and short prompts: what bounds these is the latency of a few loads and how many workgroups pull on the
 // weights, not arithmetic.  A tile that is rotated must hold both halves of its heads: with heads of 64 it takes
-// columns j .. j+15 and j+32 .. j+47 of a head, otherwise (whole heads fit) 32 columns in a row.
+// 16 columns of one half and the 16 they pair with, otherwise (whole heads fit) 32 columns in a row.
 template <int W, class Epi>
-__global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, int ntn, Epi epi) {
+__global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, Epi epi) {
   constexpr int U = 5, PITCH = 32 + 4;
   extern __shared__ __attribute__((aligned(16))) float red[];   // [W][32][PITCH]
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = blockIdx.x % ntn, m0 = blockIdx.x / ntn * 32;
-  const bool rot = epi.rotates(nt * 32), pair = rot && epi.head_dim() == 64;
-  // tile column c is global column col0 + c % 16 + (c / 16) * step
-  const int col0 = pair ? (nt >> 1) * 64 + (nt & 1) * 16 : nt * 32, step = pair ? 32 : 16;
+  // consecutive workgroup ids go to different XCDs; each XCD takes a contiguous eighth of the tiles, row tiles
+  // fastest: neighbouring tiles share the 128-byte lines of the weights, which should reach one L2 only
+  const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  const int ntm = (g.M + 31) / 32, nt = at / ntm, m0 = at % ntm * 32;
+  const bool rot = epi.rotates(nt * 32);
+  const RowTile ct = row_tile(nt, rot, epi.head_dim());
+  const int col0 = ct.col0, step = ct.step;
   const float *A, *B;
   int ldb;
   operand_at(g, col0, A, B, ldb);
@@ -193,16 +91,24 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, i
 #pragma unroll
     for (int j = 0; j < 4; ++j) b[u][j] = bp[(int64_t)(k + j) * ldb];
   };
+  const int row = tid >> 3, c = (tid & 7) * 4, fcol = ct.col0 + (c & 15) + (c >> 4) * ct.step;   // what this thread finishes
+  const bool finisher = tid < 256 && m0 + row < g.M;
+  typename Epi::Early early{};
+  if (finisher) early = epi.early(m0 + row, fcol, rot);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < U; ++u) load(u, wave + u * W);
-  for (int c = wave; c < ng; c += U * W) {
+  __builtin_amdgcn_sched_barrier(0);
+  typename Epi::Ctx ctx{};
+  if (finisher) ctx = epi.prepare(early, m0 + row, fcol, rot);
+  for (int c0 = wave; c0 < ng; c0 += U * W) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (c + u * W < ng) {
+      if (c0 + u * W < ng) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][j], b[u][j], acc, 0, 0, 0);
       }
-      load(u, c + (u + U) * W);
+      load(u, c0 + (u + U) * W);
     }
   }
   float *mine = red + wave * 32 * PITCH;
@@ -216,11 +122,8 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, i
     for (int w = 1; w < W; ++w) v += *reinterpret_cast<const f32x4 *>(p + w * 32 * PITCH);
     return v;
   };
-  if (tid >= 256) return;
-  const int row = tid >> 3, c = (tid & 7) * 4;
-  if (m0 + row >= g.M) return;
-  epi.store(m0 + row, col0 + (c & 15) + (c >> 4) * step, sum4(row, c), rot,
-            [&](int off) { return sum4(row, c + (pair ? (off > 0 ? 16 : -16) : off)); });
+  if (!finisher) return;
+  epi.store(ctx, m0 + row, sum4(row, c), [&](int off) { return sum4(row, c + (ct.pair ? (off > 0 ? 16 : -16) : off)); });
 }
 
 // ------------------------------------------------------------------------------ many rows: LDS tiles
@@ -319,7 +222,7 @@ __global__ __launch_bounds__(256) void gemm_tiles_f32_kernel(GemmOperands g, int
     const int row = i / (BN / 4), col = (i % (BN / 4)) * 4;
     if (m0 + row >= g.M) continue;
     const float *p = sm + row * OP + col;
-    epi.store(m0 + row, nt * BN + col, *reinterpret_cast<const f32x4 *>(p), rot,
+    epi.store(epi.prepare(epi.early(m0 + row, nt * BN + col, rot), m0 + row, nt * BN + col, rot), m0 + row, *reinterpret_cast<const f32x4 *>(p),
               [&](int off) { return *reinterpret_cast<const f32x4 *>(p + off); });
   }
 }
@@ -614,7 +517,7 @@ void launch_gemm_rows_f32(const GemmOperands &g, int cols, const Epi &epi, hipSt
   auto launch = [&](auto kernel, int w) {
     const int smem = w * 32 * (32 + 4) * (int)sizeof(float);
     if (smem > 64 * 1024) allow_dynamic_lds((const void *)kernel, smem);
-    kernel<<<(cols / 32) * ((g.M + 31) / 32), 64 * w, smem, st>>>(g, cols / 32, epi);
+    kernel<<<(cols / 32) * ((g.M + 31) / 32), 64 * w, smem, st>>>(g, epi);
   };
   // two rounds of loads per wave at most: K = 1280 over 16 waves (64 rows of the paper's projection 16 us, 20 us with
   // eight waves of 64 columns), K = 256 over eight (5 us; 16 mostly idle waves 9 us), K = 64 over four
@@ -652,8 +555,8 @@ bool f32_decode_ok(const Dims &d, const gta_cache &cache, int batch) {
   return f32_gemms_ok(d, batch) && d.nk == 1 && d.nc == 1 && d.nq <= 16 && d.dh == 64 && d.dl == 128 && tuned_decode_layout_ok(cache);
 }
 
-static ProjEpi proj_epi(const Dims &d, float *q, float *k, float *c, float *g, const gta_cache *cache, const int32_t *slots) {
-  ProjEpi e{};
+static ProjEpi<float, float> proj_epi(const Dims &d, float *q, float *k, float *c, float *g, const gta_cache *cache, const int32_t *slots) {
+  ProjEpi<float, float> e{};
   e.dst[0] = q; e.dst[1] = k; e.dst[2] = c; e.dst[3] = g;
   e.width[0] = d.wq_w; e.width[1] = d.wk_w; e.width[2] = d.wc_w; e.width[3] = d.wg_w;
   e.dh = d.dh; e.rope = d.rope;
@@ -675,7 +578,7 @@ static GemmOperands proj_operands(const Dims &d, const gta_weights &w, const voi
 
 void launch_proj_f32(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
                      const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st) {
-  ProjEpi e = proj_epi(d, (float *)ws.q, (float *)ws.k, (float *)ws.c, (float *)ws.g, cache, slots);
+  ProjEpi<float, float> e = proj_epi(d, (float *)ws.q, (float *)ws.k, (float *)ws.c, (float *)ws.g, cache, slots);
   e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
   launch_gemm_f32(proj_operands(d, w, x, M), d.wtot, e, st);
 }
@@ -685,7 +588,7 @@ void launch_decoder_f32(const Dims &d, const float *L, const void *wp, const flo
   g.A = L; g.lda = d.nq * d.dl; g.M = M; g.K = d.dl;
   g.B[0] = (const float *)wp; g.seg_cols[0] = d.dh;
   g.heads_per_group = d.hpq; g.a_group_stride = d.dl;
-  const GateEpi e{out, gate, d.wg_w, d.gate};
+  const GateEpi<float> e{out, gate, d.wg_w, d.gate};
   if (d.dh == 64) { launch_gemm_f32(g, d.wg_w, e, st); return; }
   launch_gemm_rows_f32(g, d.wg_w, e, st);   // heads of 32: 32-column tiles
 }
@@ -696,7 +599,7 @@ void launch_out_proj_f32(const Dims &d, const float *O, const void *wo, float *o
   GemmOperands g{};
   g.A = O; g.lda = d.wg_w; g.M = M; g.K = d.wg_w;
   g.B[0] = (const float *)wo; g.ldb[0] = d.H; g.seg_cols[0] = d.H;
-  launch_gemm_f32(g, d.H, StoreEpi{out, d.H}, st);
+  launch_gemm_f32(g, d.H, StoreEpi<float>{out, d.H}, st);
 }
 
 void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, const float *c, const int32_t *cu, int batch,
@@ -735,7 +638,7 @@ void launch_decode_attn_f32(const Dims &d, const float *q, const int32_t *oldlen
 // caches, tail (merge, value decoder, gate, bookkeeping), output projection.
 int f32_decode(const Dims &d, const gta_weights &w, const void *x_new, int batch, const gta_cache &cache, const int32_t *slots,
                void *out, const DecodeWs &ws, hipStream_t st) {
-  ProjEpi e = proj_epi(d, ws.q, nullptr, nullptr, ws.g, &cache, slots);
+  ProjEpi<float, float> e = proj_epi(d, ws.q, nullptr, nullptr, ws.g, &cache, slots);
   e.seq_lens = cache.seq_lens; e.oldlen = ws.oldlen;
   for (int j = 0; j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
   launch_gemm_f32(proj_operands(d, w, x_new, batch), d.wtot, e, st);

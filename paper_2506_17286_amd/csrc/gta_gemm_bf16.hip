@@ -1010,7 +1010,6 @@ typedef GemmTile<32, 128, 64, 1, 4> TileSkinny32;
 typedef GemmTile<64, 128, 64, 1, 4> TileSkinny64;
 typedef GemmTile<32, 64, 64, 1, 2> TileSkinny32N64;   // 64-wide tiles for widths that are not multiples of 128
 typedef GemmTile<64, 64, 64, 2, 2> TileSkinny64N64;
-typedef GemmTile<32, 32, 64, 1, 1> TileSkinny32N32;    // one wave per tile: the output projection of a decode step
 
 typedef GemmTile<256, 256, 64, 2, 2> TileBig;    // wave tile 128 x 128
 typedef GemmTile<256, 128, 64, 4, 1> TileHead;   // one 128-wide head per workgroup, wave tile 64(m) x 128(n)
@@ -1187,10 +1186,10 @@ void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const voi
 
 void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st) {
   PlainArgs a{(const bf16 *)A, lda, M, N, K, (const bf16 *)B, (bf16 *)C};
-  if (M <= 64 && N % 32 == 0) {
-    // a decode step's few rows: 128-column tiles would be N / 128 workgroups (10 at the paper's layer, 14 us);
-    // 32 x 32 tiles of one wave each give 4 to 8 times as many (11 us there, whole step 55 -> 52 us)
-    launch<TileSkinny32N32>(plain_gemm_kernel<TileSkinny32N32>, a, (N / 32) * ((M + 31) / 32), st);
+  if (M <= 128 && N % 32 == 0 && K % 16 == 0) {
+    // a decode step's few rows: K split inside the workgroups (paper layer: 11 -> 6 us, whole step at batch 64
+    // 49 -> 45 us, at batch 128 55 -> 46 us; before that 32 x 32 tiles of one wave each up to 64 rows)
+    launch_rows_plain(A, lda, M, N, K, B, C, st);
     return;
   }
   if (M <= 1024 && N % 128 == 0) {   // short prefill: 64-row tiles

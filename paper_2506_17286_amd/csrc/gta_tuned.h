@@ -58,6 +58,12 @@ void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
                             void *L, const void *wp, const void *gate, void *out, bool fuse, hipStream_t st);
 
+// bf16 GEMMs for few rows, K split inside the workgroup (gta_rows_bf16.hip)
+bool rows_gemm_ok(const Dims &d);
+void launch_rows_proj_decode(const Dims &d, const gta_weights &w, const void *x, int batch, const gta_cache &cache,
+                             const int32_t *slots, const DecodeWs &ws, hipStream_t st);
+void launch_rows_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st);
+
 // fp32 MFMA kernels (gta_f32.hip).  They serve the shape-generic entry path where the shape allows; each condition
 // covers its own kernels.
 bool f32_gemms_ok(const Dims &d, int64_t M);                                  // projection, output projection

@@ -1,0 +1,68 @@
+"""Decode steps through the few-row GEMMs (K split inside the workgroup) and the split counts of short contexts: row
+tiles of 32, K shorter than one round of the 16 waves and longer than two, rotated tiles of heads of 64 and 128, W_O,
+full slots; and the fixed scratch array where the library's own split count would not fit it.
+
+Bounds: the bf16 tolerances of the parity gate, the max-abs one scaled by the largest reference value."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as U
+from oracle import gta_oracle as orc
+from paper_2506_17286_amd import binding as B, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CASES = [("paper", 128, 1), ("paper", 128, 33), ("paper", 1408, 32), ("paper", 1408, 128), ("paper", 128, 129),
+         ("1b", 128, 1), ("1b", 2176, 8), ("1b", 256, 9)]
+
+
+def _wl(family, d_model):
+    base = W.PAPER_WORKLOADS[1] if family == "paper" else W.WORKLOADS[3]
+    return W.scaled(base, d_model=d_model, seed=5200)
+
+
+@pytest.mark.parametrize("with_wo", [False, True])
+@pytest.mark.parametrize("family,d_model,batch", CASES)
+def test_decode_rows(family, d_model, batch, with_wo):
+    wl, cap = _wl(family, d_model), 200
+    rng = W.make_rng(wl)
+    w = W.draw_weights(wl, rng, with_wo=with_wo, std=d_model ** -0.5)
+    x = W.draw_hidden(wl, rng, batch)
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    ctx = rng.integers(0, cap, size=batch).astype(np.int32)
+    ctx[-1] = cap if batch > 1 else 63                      # the last slot is full
+    cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.from_numpy(ctx))
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, "bf16"), x, cache))
+    kr, cr, lens, status = k.astype(np.float64), c.astype(np.float64), ctx.copy(), np.zeros(batch, dtype=np.int32)
+    ref = orc.decode(U.oracle_config(wl), U.oracle_weights(w), x, kr, cr, lens, status, range(batch))
+    U.assert_close(out, ref, "bf16", "out", max(1.0, float(np.abs(ref).max())))
+    U.assert_close(U.f64(cache.k), kr, "bf16", "keys", float(np.abs(kr).max()))
+    U.assert_close(U.f64(cache.c), cr, "bf16", "latents", float(np.abs(cr).max()))
+    np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
+    np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
+
+
+def test_static_scratch_takes_coarser_splits_where_its_own_do_not_fit():
+    wl, batch, cap = W.scaled(W.WORKLOADS[4], kind="decode", d_model=256, seed=5300), 58, 256
+    cfg = B.config_of(wl)
+    assert B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, batch, 0, cap) > B.GTA_STATIC_SCRATCH_BYTES
+    assert B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, batch, 0, cap, 1) <= B.GTA_STATIC_SCRATCH_BYTES
+    rng = W.make_rng(wl)
+    wdev = U.upload_weights(W.draw_weights(wl, rng), "bf16")
+    x = B.to_device(W.draw_hidden(wl, rng, batch), "bf16")
+    k, c = (B.to_device(a, "bf16") for a in W.draw_cache(wl, rng, batch, cap))
+    lens = torch.full((batch,), 200, dtype=torch.int32, device="cuda")
+    outs = []
+    for static in (True, False):
+        cache = U.DeviceCache(wl, batch, cap, k.clone(), c.clone(), lens.clone())
+        out = torch.full((batch, wl.n_heads * wl.head_dim), float("nan"), dtype=torch.bfloat16, device="cuda")
+        if static:
+            B.gta_decode_static(cfg, B.make_weights(wdev), x, batch, cache.struct, None, out, 0)
+        else:
+            ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, batch, 0, cap, 1))
+            B.gta_decode(cfg, B.make_weights(wdev), x, batch, cache.struct, None, out, 1, ws)
+        torch.cuda.synchronize()
+        outs.append((out, cache.k, cache.c, cache.seq_lens))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
