@@ -102,13 +102,12 @@ static double split_launch_cost(int batch, int s, int max_seq) {
   return cost + 0.5 * s;   // partials to write and merge
 }
 
-int choose_splits(const Dims &d, int batch, int max_seq, int requested) {
-  if (requested > 0) return requested > 1024 ? 1024 : requested;
-  // enough (sequence, split) blocks to put one or two on every one of the 256 CUs (the kernel's choice), but
-  // no split shorter than 256 cached rows.
+// min_rows: no split shorter than this many cached rows.
+static int choose_splits_of(const Dims &d, int batch, int max_seq, int min_rows) {
+  // enough (sequence, split) blocks to put one or two on every one of the 256 CUs (the kernel's choice)
   const int target = tuned_decode_target_workgroups(d);
   int want = (target + batch - 1) / batch;
-  int cap = max_seq / 256;
+  int cap = max_seq / min_rows;
   if (cap < 1) cap = 1;
   const bool tuned = tuned_decode_supported(d);
   if (tuned) cap = std::min(cap, tuned_decode_max_splits(d, batch));
@@ -130,6 +129,18 @@ int choose_splits(const Dims &d, int batch, int max_seq, int requested) {
   int s = want < cap ? want : cap;
   if (s < 1) s = 1;
   return s;
+}
+
+// Slices of at least 64 rows: a workgroup's chain of steps over its slice is what a small batch waits for (whole
+// steps with 256-, 128-, 64- and 32-row slices: 1B shape, one sequence behind 2000 rows 33.7 / 28.3 / 25.4 / 24.3 us,
+// 16 behind 1000 36.5 / 31.5 / 30.4 / 30.2; paper layer, one behind 1000 31.4 / 27.8 / 26.1 / 27.6, fp32 8 behind 1000
+// 46 / 43 / 41 / 46).  The one-round-trip tails hold 32 (narrow rows) or 64 splits, though: past those only slices of
+// at least 256 rows pay for the general tail.
+int choose_splits(const Dims &d, int batch, int max_seq, int requested) {
+  if (requested > 0) return requested > 1024 ? 1024 : requested;
+  const int one_trip = d.dl == 128 && d.dh == 64 ? 32 : 64;
+  const int s = choose_splits_of(d, batch, max_seq, 64);
+  return s <= one_trip ? s : std::max(one_trip, choose_splits_of(d, batch, max_seq, 256));
 }
 
 DecodeWs carve_decode(const Dims &d, bool with_wo, int batch, int splits, void *base) {
@@ -346,8 +357,14 @@ int gta_decode(const gta_config *cfg, const gta_weights *weights, const void *x_
 
 int gta_decode_static(const gta_config *cfg, const gta_weights *weights, const void *x_new, int32_t batch,
                       const gta_cache *cache, const int32_t *slots, void *out, int32_t num_splits, void *hip_stream) {
-  // the size check comes first: an oversized call is refused before anything else is touched
-  const size_t need = cache ? gta_workspace_bytes(cfg, GTA_MODE_DECODE, batch, 0, cache->max_seq, num_splits) : 0;
+  // the size check comes first: an oversized call is refused before anything else is touched.  Where the library's
+  // own split count is what makes the call too large, the coarser slices of at least 256 rows are tried.
+  size_t need = cache ? gta_workspace_bytes(cfg, GTA_MODE_DECODE, batch, 0, cache->max_seq, num_splits) : 0;
+  Dims d;
+  if (need > (size_t)GTA_STATIC_SCRATCH_BYTES && num_splits == 0 && make_dims(cfg, &d) == GTA_OK) {
+    num_splits = choose_splits_of(d, batch, cache->max_seq, 256);
+    need = gta_workspace_bytes(cfg, GTA_MODE_DECODE, batch, 0, cache->max_seq, num_splits);
+  }
   if (need > (size_t)GTA_STATIC_SCRATCH_BYTES) return GTA_ERR_WORKSPACE;
   void *ws = nullptr;
   const int rc = static_scratch(&ws);
