@@ -121,193 +121,155 @@ __device__ __forceinline__ void gemm_mainloop(const bf16 *__restrict__ A, int64_
 }
 
 // ---- software-pipelined main loop for the big tiles --------------------------------------------
-// One wave per SIMD owns a 128-wide accumulator tile, so nothing but the wave's own instruction
-// stream can hide latencies.  The loop is therefore pipelined by hand on three levels:
-//   * operand fragments of k-step kk+1 are read from LDS while the MFMAs of step kk run (two
-//     fragment sets); the fragments of the next tile's first step are read during the last step;
-//   * k-tile kt+1 is written to the other LDS stage during steps 0..2 of tile kt, and the one
-//     workgroup barrier of the tile sits before the last step, whose MFMAs cover its skew;
-//   * global loads run two tiles ahead of the LDS writes (two staging register sets): the loads of
-//     tile kt+3 go out in steps 1..3, each into registers whose LDS write was issued one step before.
-// Every step is one scheduling region in which the memory instructions are dealt out between the
-// MFMAs (sched_group_barrier), so the matrix pipe always has the next MFMA queued and neither the
-// LDS nor the vector-memory queue sees a burst.
-// The last three k-tiles have nothing left to prefetch for the product; the caller may use the two
-// staging sets that become free for a `tail` prefetch of 16 + 16 sixteen-byte chunks per thread
-// (the decoder fetches its gate tile this way), which are handed back in r_tail0 / r_tail1.
-template <class T>
-struct PipeMap {
-  static constexpr int A_CPR = T::BK / 8, A_RPP = T::NT / A_CPR, A_PASSES = T::BM / A_RPP;
-  static constexpr int B_CPR = T::BN / 8, B_RPP = T::NT / B_CPR, B_PASSES = T::BK / B_RPP;
-  static constexpr int KSTEPS = T::BK / 16;
-  static_assert(T::BM % A_RPP == 0 && T::BK % B_RPP == 0 && A_PASSES >= 1 && B_PASSES >= 1, "staging");
-  static_assert(KSTEPS == 4, "the step schedule below is written for four k-steps per tile");
+// 256 x 256 tile, eight waves (two per SIMD) of 64 x 128, k-tiles of 32.  Both operand tiles go from memory straight
+// into LDS (buffer_load_dwordx4 .. lds: no staging registers, no LDS writes by the waves) through four stages, so a
+// k-tile is requested three tiles ahead of its use.  The loop is laid out in steps of one MFMA:
+//   * the fragment reads of k-step kk+1 go out under the MFMAs of step kk (two fragment sets);
+//   * the barrier of tile t sits in its first k-step, behind that step's fragment reads: every wave has then read all
+//     of stage t, and (each wave having waited for its own loads) tile t+1 is complete;
+//   * behind it, under the MFMAs of the second k-step, go the reads of tile t+1's first step and the wave's loads of
+//     tile t+4 into the stage just left.
+// LDS layout: a load instruction fills 1 KiB in lane order, so there is no padding; instead each lane fetches the
+// 16-byte chunk that belongs in its slot.  X rows are 4 chunks, chunk c of row r in slot c ^ x_swz(r): any 8 (16)
+// consecutive rows read one logical chunk from 8 (16) different 16-byte columns of 128 (256) bytes.  Weight rows are
+// 32 chunks, chunk c of k-row k in slot c ^ 4 (k % 4): the four k-rows of a transpose read lie in different 64-byte
+// columns.
+// Bound: what the chip sustains on such data (1240 TFLOP/s for a large library GEMM; the projection of 112 K rows x
+// 4096 x 7168 reaches 1180).  Measured against four waves of 128 x 128 that staged through registers (one wave per
+// SIMD, 512 registers and spills): projection 16384 x 2048 x 3584 273 -> 252 us, 65536 x 1280 x 1792 394 -> 325,
+// W_O 65536 x 1280 x 1280 251 -> 225, decoder of 16384 rows 76 -> 69.  The same loop with four waves was no faster
+// than the staged one; wave priorities, the barrier's place and free scheduling changed nothing.
+__device__ __forceinline__ int x_swz(int r) { return ((r >> 2) & 3) ^ (r & 2); }
+
+struct BigLoop {
+  static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, X_BYTES = BM * BK * 2, STAGE = X_BYTES + BK * BN * 2;
+  static constexpr int SMEM = NSTAGE * STAGE;
 };
-template <class T>
-struct PipeStage { u32x4 a[PipeMap<T>::A_PASSES], b[PipeMap<T>::B_PASSES]; };
 
-enum : int { SG_MFMA = 0x008, SG_VMEM_READ = 0x020, SG_DS_READ = 0x100, SG_DS_WRITE = 0x200 };
-
-// Schedule of one k-step: N_FRAG fragment reads of the next step go out one per MFMA, then N_W LDS
-// writes and N_G global loads are dealt out over the remaining MFMAs.
-template <int N_MFMA, int N_FRAG, int N_W, int N_G>
-__device__ __forceinline__ void deal_step() {
-  // MFMAs that carry fragment reads (one each if there are enough MFMAs, else half of the MFMAs with
-  // several reads each); the others carry the LDS writes and global loads
-  constexpr int F_SLOTS = N_MFMA > N_FRAG ? N_FRAG : N_MFMA / 2;
-  constexpr int RPS = (N_FRAG + F_SLOTS - 1) / F_SLOTS;
-  static_assert(F_SLOTS >= 1 && N_MFMA > F_SLOTS, "schedule");
-#pragma unroll
-  for (int i = 0; i < F_SLOTS; ++i) {
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(SG_DS_READ, RPS, 0);
-  }
-  constexpr int rest = N_MFMA - F_SLOTS;
-  constexpr int pw = (N_W + rest - 1) / rest, pg = (N_G + rest - 1) / rest;
-#pragma unroll
-  for (int i = 0; i < rest; ++i) {
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-    if constexpr (pw > 0) __builtin_amdgcn_sched_group_barrier(SG_DS_WRITE, pw, 0);
-    if constexpr (pg > 0) __builtin_amdgcn_sched_group_barrier(SG_VMEM_READ, pg, 0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
+// 16 bytes per lane from rsrc + voff + soff to LDS offset lds + 16 * lane.  vmcnt counts it; the compiler does not
+// know that, so every wait for these loads is spelled out.
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
+}
+__device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {   // reads past `bytes` return 0
+  const uint64_t b = (uint64_t)base;
+  return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
 }
 
-// Tail prefetch hook: chunk i (0..15) of tail set `set` is at gbase() + off(set, i) (wave-uniform) +
-// thr_of(set, i) (per thread), all offsets in bytes.
+// What the last four tiles fetch instead of operands: load j (0..7) of stage `s` of this wave.
 struct NoTail {
   static constexpr bool active = false;
-  __device__ const char *gbase() const { return nullptr; }
-  __device__ unsigned off(int, int) const { return 0; }
-  __device__ unsigned thr_of(int, int) const { return 0; }
+  __device__ void load(int, int, unsigned) const {}
 };
 
-// `Abase` points at row m0 of the row operand; `Bbase` + `boff` (bytes, per thread) at k-row
-// tid / B_CPR of this thread's 8-column chunk of the weight operand.  K / BK must be even and >= 4.
-template <class T, class Tail>
-__device__ __forceinline__ void gemm_mainloop_pipe(const bf16 *__restrict__ Abase, int64_t lda, int rows_valid,
-                                                   const bf16 *__restrict__ Bbase, unsigned boff, int64_t ldb,
-                                                   int K, char *smem, f32x16 (&acc)[T::TN][T::TM],
-                                                   PipeStage<T> &r_tail0, PipeStage<T> &r_tail1, const Tail &tail) {
-  typedef PipeMap<T> P;
-  typedef PipeStage<T> Stage;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wn = wave % T::WGN, wm = wave / T::WGN;
-  const int a_c = tid % P::A_CPR, a_r = tid / P::A_CPR;
-  const int b_c = tid % P::B_CPR, b_r = tid / P::B_CPR;
-  // Addresses are a wave-uniform base plus ONE 32-bit per-thread offset.  Pass i of the row operand
-  // covers rows i * A_RPP + a_r; ip is the last pass that holds a valid row.  Passes before it use the
-  // full per-thread offset, pass ip and the (entirely invalid) passes after it use row ip * A_RPP +
-  // min(a_r, last valid row of that pass): valid rows map to themselves, the rest stay in bounds.
-  const int ip = (rows_valid - 1) / P::A_RPP;
-  const unsigned athr = (unsigned)(a_r * lda + a_c * 8) * 2u;
-  const unsigned athr_p = (unsigned)(min(a_r, rows_valid - 1 - ip * P::A_RPP) * lda + a_c * 8) * 2u;
-  const char *Ab = reinterpret_cast<const char *>(Abase);
-  const char *Bb = reinterpret_cast<const char *>(Bbase);
+// Weight operand of a big tile: `base` points at its first k-row, rows are ld elements apart; column chunk c (8
+// columns) sits chunk_bytes(c) behind the start of a row; `bytes` covers 32 rows.
+struct WeightTile {
+  const bf16 *base; int64_t ld; unsigned bytes;
+  unsigned head_bytes;   // > 0: columns 128 .. 255 are another matrix (the next head) this far behind the first
+  __device__ __forceinline__ unsigned chunk_bytes(int c) const { return head_bytes ? (c >> 4) * head_bytes + (c & 15) * 16 : c * 16; }
+};
+__device__ __forceinline__ WeightTile weight_tile(const bf16 *base, int64_t ld, unsigned head_bytes = 0) {
+  return WeightTile{base, ld, (unsigned)(31 * ld * 2) + (head_bytes ? head_bytes + 256u : 512u), head_bytes};
+}
+
+// acc[tn][tm][r]:  n = wn*128 + tn*32 + 8*(r/4) + 4*(lane/32) + r%4,  m = wm*128 + tm*32 + lane%32, wn = wave % 2, wm = wave / 2.
+// `Abase` points at row m0 of the row operand.  K a multiple of 32, at least 128.  All loads have landed on return and
+// every wave has passed a barrier behind its last LDS read.
+template <class G, class Tail>
+__device__ __forceinline__ void gemm_mainloop_big(const bf16 *__restrict__ Abase, int64_t lda, int rows_valid, WeightTile B, int K,
+                                                  char *smem, f32x16 (&acc)[G::TN][G::TM], const Tail &tail) {
+  typedef BigLoop T;
+  constexpr int TM = G::TM, TN = G::TN, NW = G::NT / 64, LPW = 16 / NW;   // LPW: load instructions per wave and operand
+  const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % G::WGN, wm = wave / G::WGN;
   const int nk = K / T::BK;
-
-  struct Frags { bf16x8 x[T::TM], w[T::TN]; };
-  // The 16 loads / LDS writes of a tile are split in three parts (6, 6, 4): A passes with
-  // i % 3 == part, B passes with (i + 1) % 3 == part; part < 0 = all.
-  // Tiles past the end of K are clamped to the last one (redundant loads, in bounds), except that
-  // with a tail, tile nk+1 is tail set 0 and tile nk+2 tail set 1.  The choice is made with scalar
-  // bit masks, not branches, so that every k-step stays one scheduling region.
-  const unsigned a_pass_bytes = (unsigned)(P::A_RPP * lda * 2), b_pass_bytes = (unsigned)(P::B_RPP * ldb * 2);
-  auto gload_part = [&](Stage &r, int kt, int part) {
-    const bool tl = Tail::active && kt > nk;
-    const int set = kt > nk + 1 ? 1 : 0;
-    kt = min(kt, nk - 1);
-    const char *ak = Ab + (int64_t)kt * (T::BK * 2);
-    const char *bk = Bb + (int64_t)kt * T::BK * ldb * 2;
-    const char *abase = tl ? tail.gbase() : ak, *bbase = tl ? tail.gbase() : bk;
+  const int rv = min(rows_valid, T::BM);
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+  // this wave's loads of a tile: rows 64 wave + 16 j + lane/4 of X (rows past the last valid one re-read it), k-rows
+  // 8 wave + 2 j + lane/32 of the weights
+  unsigned xv[LPW], wv[LPW];
 #pragma unroll
-    for (int i = 0; i < P::A_PASSES; ++i)
-      if (part < 0 || i % 3 == part) {
-        const unsigned o_tile = (unsigned)min(i, ip) * a_pass_bytes, o_tail = tail.off(set, i);
-        const unsigned t_tile = i < ip ? athr : athr_p, t_tail = tail.thr_of(set, i);
-        r.a[i] = *reinterpret_cast<const u32x4 *>(abase + (tl ? o_tail : o_tile) + (tl ? t_tail : t_tile));
-      }
-#pragma unroll
-    for (int i = 0; i < P::B_PASSES; ++i)
-      if (part < 0 || (i + 1) % 3 == part) {
-        const unsigned o_tile = (unsigned)i * b_pass_bytes, o_tail = tail.off(set, P::A_PASSES + i);
-        const unsigned t_tail = tail.thr_of(set, P::A_PASSES + i);
-        r.b[i] = *reinterpret_cast<const u32x4 *>(bbase + (tl ? o_tail : o_tile) + (tl ? t_tail : boff));
-      }
-  };
-  const int a_st = a_r * T::A_PITCH + a_c * 16, b_st = T::A_BYTES + b_r * T::B_PITCH + b_c * 16;
-  auto sstore_part = [&](char *st, const Stage &r, int part) {
-#pragma unroll
-    for (int i = 0; i < P::A_PASSES; ++i)
-      if (part < 0 || i % 3 == part) *reinterpret_cast<u32x4 *>(st + a_st + i * P::A_RPP * T::A_PITCH) = r.a[i];
-#pragma unroll
-    for (int i = 0; i < P::B_PASSES; ++i)
-      if (part < 0 || (i + 1) % 3 == part)
-        *reinterpret_cast<u32x4 *>(st + b_st + i * P::B_RPP * T::B_PITCH) = r.b[i];
-  };
-  const int xoff = (wm * T::WM + (lane & 31)) * T::A_PITCH + (lane >> 5) * 16;
-  const int woff = T::A_BYTES + ((lane >> 5) * 8 + ((lane & 15) >> 2)) * T::B_PITCH +
-                   (wn * T::WN + ((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
-  auto load_frags = [&](Frags &f, const char *st, int kk) {
-#pragma unroll
-    for (int tm = 0; tm < T::TM; ++tm)
-      f.x[tm] = *reinterpret_cast<const bf16x8 *>(st + xoff + tm * 32 * T::A_PITCH + kk * 32);
-#pragma unroll
-    for (int tn = 0; tn < T::TN; ++tn) {
-      const char *wp = st + woff + kk * 16 * T::B_PITCH + tn * 64;
-      s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp));
-      s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 4 * T::B_PITCH));
-      s16x8 w8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      f.w[tn] = __builtin_bit_cast(bf16x8, w8);
-    }
-  };
-  auto mma = [&](const Frags &f) {
-#pragma unroll
-    for (int tn = 0; tn < T::TN; ++tn)
-#pragma unroll
-      for (int tm = 0; tm < T::TM; ++tm)
-        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[tn], f.x[tm], acc[tn][tm], 0, 0, 0);
-  };
-  constexpr int N_MFMA = T::TM * T::TN, N_FRAG = T::TM + 2 * T::TN;
-
-  Stage &r0 = r_tail1, &r1 = r_tail0;   // tile t is staged in r(t & 1); the tail sets end up in r1, r0
-  Frags f0, f1;
-  gload_part(r0, 0, -1);
-  gload_part(r1, 1, -1);
-  sstore_part(smem, r0, -1);
-  gload_part(r0, 2, -1);
-  __syncthreads();
-  load_frags(f0, smem, 0);
-  __builtin_amdgcn_sched_barrier(0);
-
-  // tile kt is in `cur`; `rw` holds tile kt+1 and is refilled with tile kt+3 (or a tail set)
-  auto tile = [&](char *cur, char *nxt, Stage &rw, int kt) {
-    load_frags(f1, cur, 1);
-    sstore_part(nxt, rw, 0);
-    mma(f0);
-    deal_step<N_MFMA, N_FRAG, 6, 0>();
-    load_frags(f0, cur, 2);
-    sstore_part(nxt, rw, 1);
-    gload_part(rw, kt + 3, 0);
-    mma(f1);
-    deal_step<N_MFMA, N_FRAG, 6, 6>();
-    load_frags(f1, cur, 3);
-    sstore_part(nxt, rw, 2);
-    gload_part(rw, kt + 3, 1);
-    mma(f0);
-    deal_step<N_MFMA, N_FRAG, 4, 6>();
-    // tile kt+1 is complete and every wave is done reading `cur` once all waves pass this barrier
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    load_frags(f0, nxt, 0);
-    gload_part(rw, kt + 3, 2);
-    mma(f1);
-    deal_step<N_MFMA, N_FRAG, 0, 4>();
-  };
-  char *s0 = smem, *s1 = smem + T::STAGE;
-  for (int kt = 0; kt < nk; kt += 2) {
-    tile(s0, s1, r1, kt);
-    tile(s1, s0, r0, kt + 1);
+  for (int j = 0; j < LPW; ++j) {
+    const int r = (wave * LPW + j) * 16 + (lane >> 2), k = (wave * LPW + j) * 2 + h;
+    xv[j] = (unsigned)(min(r, rv - 1) * lda * 2) + ((lane & 3) ^ x_swz(lane >> 2)) * 16;
+    wv[j] = (unsigned)(k * B.ld * 2) + B.chunk_bytes(ln ^ ((k & 3) << 2));
   }
+  const u32x4 xr = buffer_of(Abase, (unsigned)((rv - 1) * lda * 2) + (unsigned)K * 2u);
+  const int64_t wstep = (int64_t)T::BK * B.ld * 2;
+  const char *wbase = reinterpret_cast<const char *>(B.base);   // of the tile that is requested next
+  auto load_x = [&](int t, int j) { load_to_lds(xr, xv[j], (unsigned)(t * T::BK * 2), lds0 + (t & 3) * T::STAGE + (wave * LPW + j) * 1024); };
+  auto load_w = [&](int t, int j) {
+    load_to_lds(buffer_of(wbase, B.bytes), wv[j], 0u, lds0 + (t & 3) * T::STAGE + T::X_BYTES + (wave * LPW + j) * 1024);
+  };
+  // fragment addresses: X chunk 2 kk + h of row ln (+ 32 tm), weight rows 8 h + (lane%16)/4 (+ 16 kk, + 4)
+  int xo[2], wo[TN];
+  const int wr = (lane & 15) >> 2;
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) xo[kk] = (wm * G::WM + ln) * 64 + (((kk * 2 + h) ^ x_swz(ln & 15)) * 16);
+#pragma unroll
+  for (int tn = 0; tn < TN; ++tn)
+    wo[tn] = T::X_BYTES + (h * 8 + wr) * 512 + (wn * (G::WN / 8) + ((tn ^ wr) << 2) + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) * 16 + (lane & 1) * 8;
+  struct Frags { bf16x8 x[TM]; s16x4 lo[TN], hi[TN]; };
+  constexpr int NR = TM + 2 * TN, NM = TM * TN;   // fragment reads and MFMAs of a k-step
+  // fragment read i, in the order the MFMAs of the step need them
+  auto read_frag = [&](Frags &f, const char *st, int kk, int i) {
+    if (i >= 2 && i < 2 + TM) { f.x[i - 2] = *reinterpret_cast<const bf16x8 *>(st + xo[kk] + (i - 2) * 2048); return; }
+    const int w = i < 2 ? i : i - TM, tn = w / 2;
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn] + kk * 8192 + (w & 1) * 2048));
+    if (w & 1) f.hi[tn] = v; else f.lo[tn] = v;
+  };
+  // the reads of step i of NM: all of them within the first NM - 2 steps
+  auto read_frags = [&](Frags &f, const char *st, int kk, int i) {
+    constexpr int S = NM - 3;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      if (r * S / NR == i) read_frag(f, st, kk, r);
+  };
+  auto mma = [&](const Frags &f, int i) {
+    const int tn = i / TM, tm = i % TM;
+    const s16x8 w8 = __builtin_shufflevector(f.lo[tn], f.hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
+    acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), f.x[tm], acc[tn][tm], 0, 0, 0);
+  };
+  constexpr int PER_TILE = 2 * LPW;   // loads of a wave per tile
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) { load_x(t, j); load_w(t, j); }
+    wbase += wstep;
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * PER_TILE) : "memory");
+  Frags f0, f1;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) read_frag(f0, smem, 0, i);
+#pragma unroll 1
+  for (int t = 0; t < nk; ++t) {
+    const char *cur = smem + (t & 3) * T::STAGE, *nxt = smem + ((t + 1) & 3) * T::STAGE;
+    const bool more = t + 4 < nk;
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      read_frags(f1, cur, 1, i);
+      mma(f0, i);
+      if (i == NM - 3) {   // three tiles in flight (t+1 .. t+3); at the end there may be fewer
+        if (Tail::active || t < nk - 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * PER_TILE) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      read_frags(f0, nxt, 0, i);
+      if (i % 2 == 1) {
+        const int l = i / 2;   // NM / 2 = PER_TILE
+        if (more) { if (l % 2 == 0) load_x(t + 4, l / 2); else load_w(t + 4, l / 2); }
+        else if (Tail::active) tail.load(t & 3, l, lds0 + (t & 3) * T::STAGE);
+      }
+      mma(f1, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wbase += wstep;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 template <class T>
@@ -349,20 +311,22 @@ __device__ __forceinline__ void tile_of_block(int ntn, int ntm, int &mt, int &nt
 // ---- epilogue of the 256 x 256 tile through LDS -------------------------------------------------
 // In the accumulator layout a lane owns 4 consecutive columns of one row, so direct stores would be
 // 8 bytes wide and scattered over 32 rows per instruction.  The tile is therefore rounded to bf16,
-// parked in LDS in output layout (row pitch 528 bytes) and written out with 16-byte stores in which
-// 32 consecutive lanes cover one 512-byte row segment.
-constexpr int kOutPitch = 256 * 2 + 16;
+// parked in LDS in output layout and written out with 16-byte stores in which 32 consecutive lanes cover one
+// 512-byte row segment.  Chunk c (8 columns) of row r sits in slot c ^ (r % 16) of its row, which spreads the rows
+// of an access in accumulator layout over the banks.
+__device__ __forceinline__ int out_chunk(int row, int c) { return row * 512 + ((c ^ (row & 15)) << 4); }
+constexpr int kOutBytes = 256 * 512;
 
 template <class T>
 __device__ __forceinline__ int out_lds_offset(int tm, int tn, int rq) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % T::WGN, wm = wave / T::WGN;
-  return (wm * T::WM + tm * 32 + (lane & 31)) * kOutPitch + (wn * T::WN + tn * 32 + rq * 8 + (lane >> 5) * 4) * 2;
+  return out_chunk(wm * T::WM + tm * 32 + (lane & 31), (wn * T::WN + tn * 32) / 8 + rq) + (lane >> 5) * 8;
 }
 
 template <class T>
 __device__ __forceinline__ void tile_to_lds(const f32x16 (&acc)[T::TN][T::TM], char *smem) {
-  static_assert(T::BM == 256 && T::BN == 256 && T::SMEM >= 256 * kOutPitch, "epilogue staging");
+  static_assert(T::BM == 256 && T::BN == 256, "epilogue staging");
 #pragma unroll
   for (int tm = 0; tm < T::TM; ++tm)
 #pragma unroll
@@ -381,7 +345,7 @@ __device__ __forceinline__ void for_each_out_chunk(const char *smem, F f) {
 #pragma unroll 4
   for (int it = 0; it < 256 / RPP; ++it) {
     const int r = it * RPP + r0;
-    f(r, ch, *reinterpret_cast<const u32x4 *>(smem + r * kOutPitch + ch * 16));
+    f(r, ch, *reinterpret_cast<const u32x4 *>(smem + out_chunk(r, ch)));
   }
 }
 
@@ -414,19 +378,16 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
   // positions of this lane's rows: asked for before the main loop (a tile of Q or K rotates by them right
   // after it: 0.8 us of load latency per tile otherwise), not at all by the big tiles that do not rotate
   const bool rotate = a.rope != nullptr && seg < 2;
-  constexpr bool kBig = T::TM == 4 && T::TN == 4;
+  constexpr bool kBig = T::BM == 256 && T::BN == 256;
   int pos_of[T::TM];
   if (rotate || !kBig) {
 #pragma unroll
     for (int tm = 0; tm < T::TM; ++tm)
       pos_of[tm] = a.pos[min(m0 + (int)(threadIdx.x >> 6) / T::WGN * T::WM + tm * 32 + (int)(threadIdx.x & 31), a.M - 1)];
   }
-  if constexpr (T::TM == 4 && T::TN == 4) {
-    const int ldb = a.width[seg];
-    const unsigned boff = (unsigned)((threadIdx.x / (T::BN / 8)) * ldb + (threadIdx.x % (T::BN / 8)) * 8) * 2u;
-    PipeStage<T> t0, t1;
-    gemm_mainloop_pipe<T>(a.x + (int64_t)m0 * a.lda, a.lda, a.M - m0, a.w[seg] + n_glob, boff, ldb, a.K, smem, acc, t0, t1,
-                          NoTail{});
+  if constexpr (kBig) {
+    gemm_mainloop_big<T>(a.x + (int64_t)m0 * a.lda, a.lda, a.M - m0, weight_tile(a.w[seg] + n_glob, a.width[seg]), a.K, smem, acc,
+                      NoTail{});
   } else {
     gemm_mainloop<T>(a.x, a.lda, a.M, m0, a.w[seg], a.width[seg], n_glob, a.K, smem, acc);
   }
@@ -527,13 +488,11 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
         if (crow) *reinterpret_cast<bf16x4 *>(crow + n) = v;
       }
   }
-  if constexpr (T::TM == 4 && T::TN == 4) {
-    __syncthreads();                 // every wave is done with the operand stages
+  if constexpr (kBig) {
     tile_to_lds<T>(acc, smem);
     // cache row of every tile row (or -1), looked up once and shared through LDS
-    int64_t *crow_of = reinterpret_cast<int64_t *>(smem + 256 * kOutPitch);
-    static_assert(T::SMEM >= 256 * kOutPitch + 256 * 8, "epilogue staging");
-    if (cache) {
+    int64_t *crow_of = reinterpret_cast<int64_t *>(smem + kOutBytes);
+    if (cache && threadIdx.x < 256) {
       const int m = m0 + (int)threadIdx.x;
       int64_t cr = -1;
       if (m < a.M) {
@@ -545,7 +504,7 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
     }
     __syncthreads();
     bf16 *dst = a.dst[seg] + n_glob;
-    for_each_out_chunk(smem, [&](int r, int ch, u32x4 v) {
+    for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
       const int m = m0 + r;
       if (m >= a.M) return;
       *reinterpret_cast<u32x4 *>(dst + (int64_t)m * width + ch * 8) = v;
@@ -580,7 +539,7 @@ __global__ void pack_weights_kernel(ProjArgs a, int wtot, int wpad, bf16 *dst) {
 
 template <class T, int DH>
 __global__ __launch_bounds__(T::NT) void proj_packed_kernel(ProjArgs a, const bf16 *wpack, int wpad) {
-  static_assert(T::TM == 4 && T::TN == 4 && (DH == 64 || DH == 128), "tile");
+  static_assert(T::BM == 256 && T::BN == 256 && T::WN == 128 && (DH == 64 || DH == 128), "tile");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2], wtot = b3 + a.width[3];
   int mt, nt;
@@ -589,10 +548,7 @@ __global__ __launch_bounds__(T::NT) void proj_packed_kernel(ProjArgs a, const bf
   f32x16 acc[T::TN][T::TM];
   zero_acc<T>(acc);
   {
-    const unsigned boff = (unsigned)((threadIdx.x / (T::BN / 8)) * wpad + (threadIdx.x % (T::BN / 8)) * 8) * 2u;
-    PipeStage<T> t0, t1;
-    gemm_mainloop_pipe<T>(a.x + (int64_t)m0 * a.lda, a.lda, a.M - m0, wpack + n0, boff, wpad, a.K, smem, acc, t0, t1,
-                          NoTail{});
+    gemm_mainloop_big<T>(a.x + (int64_t)m0 * a.lda, a.lda, a.M - m0, weight_tile(wpack + n0, wpad), a.K, smem, acc, NoTail{});
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % T::WGN, wm = wave / T::WGN;
@@ -627,10 +583,9 @@ __global__ __launch_bounds__(T::NT) void proj_packed_kernel(ProjArgs a, const bf
       }
     }
   }
-  __syncthreads();                 // every wave is done with the operand stages
   tile_to_lds<T>(acc, smem);
-  int64_t *crow_of = reinterpret_cast<int64_t *>(smem + 256 * kOutPitch);
-  if (a.kcache) {
+  int64_t *crow_of = reinterpret_cast<int64_t *>(smem + kOutBytes);
+  if (a.kcache && threadIdx.x < 256) {
     const int m = m0 + (int)threadIdx.x;
     int64_t cr = -1;
     if (m < a.M) {
@@ -649,7 +604,7 @@ __global__ __launch_bounds__(T::NT) void proj_packed_kernel(ProjArgs a, const bf
   const int width = a.width[seg];
   bf16 *dst = a.dst[seg] + lcol;
   bf16 *cache = !a.kcache ? nullptr : seg == 1 ? a.kcache + lcol : seg == 2 ? a.ccache + lcol : nullptr;
-  for_each_out_chunk(smem, [&](int r, int, u32x4 v) {
+  for_each_out_chunk<T::NT>(smem, [&](int r, int, u32x4 v) {
     const int m = m0 + r;
     if (m >= a.M) return;
     *reinterpret_cast<u32x4 *>(dst + (int64_t)m * width) = v;
@@ -705,20 +660,23 @@ __global__ __launch_bounds__(T::NT) void decoder_gemm_kernel(DecoderArgs a) {
   }
 }
 
-// tail prefetch of the decoder: chunk (set*16 + i) of a thread is row (set*16 + i)*8 + tid/32 of the
-// gate tile (rows past the end of the matrix re-read the last valid one)
+// The decoder's gate tile (256 rows x 512 bytes) fills the four stages as the last four k-tiles leave them, in output
+// layout: stage s takes rows 64 s .. 64 s + 63, two per load (rows past the end of the matrix re-read the last valid
+// one).
+template <int NW>
 struct GateTail {
   static constexpr bool active = true;
-  const char *base; unsigned pass_bytes, thr, thr_p; int ip;   // ip: last 8-row pass with a valid row
-  __device__ const char *gbase() const { return base; }
-  __device__ unsigned off(int set, int i) const { return (unsigned)min(set * 16 + i, ip) * pass_bytes; }
-  __device__ unsigned thr_of(int set, int i) const { return set * 16 + i < ip ? thr : thr_p; }
+  u32x4 rsrc; unsigned ld_bytes; int last;   // last valid row of the tile
+  __device__ __forceinline__ void load(int s, int j, unsigned lds) const {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = (wave * (32 / NW) + j) * 2 + (lane >> 5);
+    load_to_lds(rsrc, (unsigned)min(s * 64 + r, last) * ld_bytes + ((lane & 31) ^ (r & 15)) * 16, 0u, lds + (wave * (32 / NW) + j) * 1024);
+  }
 };
 
 // Two heads of one map group per 256-wide tile (they share the row operand L_g), pipelined main
-// loop.  The gate is applied to the fp32 accumulators: the gate tile is fetched with coalesced
-// 16-byte loads into LDS in output layout, every lane reads the pre-activations of its own
-// elements from there and puts the gated, rounded result back in the same place.
+// loop.  The gate is applied to the fp32 accumulators: the gate tile is fetched into LDS in output layout, every
+// lane reads the pre-activations of its own elements from there and puts the gated, rounded result back in the
+// same place.
 template <class T, bool GATE>
 __global__ __launch_bounds__(T::NT) void decoder_pair_kernel(DecoderArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -729,38 +687,16 @@ __global__ __launch_bounds__(T::NT) void decoder_pair_kernel(DecoderArgs a) {
   zero_acc<T>(acc);
   const int64_t ldo = (int64_t)a.nh * a.dh;
   const int col0 = head * a.dh;
-  // the gate tile (32 chunks of 16 bytes per thread: rows it*8 + tid/32, chunk tid%32) is fetched by
-  // the main loop's tail prefetch while the last two k-tiles are multiplied
-  const int r0 = threadIdx.x >> 5, ch = threadIdx.x & 31;
-  const int rows_valid = a.M - m0;
-  // pass `it` covers rows it*8 + tid/32; rows past the last valid one are clamped to it (their outputs
-  // are not stored)
-  const int rv = min(rows_valid, T::BM);
-  GateTail gate_tail;
-  gate_tail.base = reinterpret_cast<const char *>(a.g + (int64_t)m0 * ldo + col0);
-  gate_tail.pass_bytes = (unsigned)(8 * ldo * 2);
-  gate_tail.ip = (rv - 1) / 8;
-  gate_tail.thr = (unsigned)(r0 * ldo + ch * 8) * 2u;
-  gate_tail.thr_p = (unsigned)(min(r0, (rv - 1) % 8) * ldo + ch * 8) * 2u;
-  PipeStage<T> g0, g1;
+  const int rv = min(a.M - m0, T::BM);
   {
-    const int b_c = threadIdx.x % (T::BN / 8), b_r = threadIdx.x / (T::BN / 8);
-    const int col = b_c * 8;   // columns [0,128) belong to `head`, [128,256) to `head + 1`
-    const unsigned boff = (unsigned)((col / 128) * a.dl * a.dh + b_r * a.dh + col % 128) * 2u;
-    const bf16 *Ab = a.L + (int64_t)m0 * a.ldl + (head / a.hpq) * a.dl, *Bb = a.wp + (int64_t)head * a.dl * a.dh;
-    if constexpr (GATE) gemm_mainloop_pipe<T>(Ab, a.ldl, rows_valid, Bb, boff, a.dh, a.dl, smem, acc, g0, g1, gate_tail);
-    else gemm_mainloop_pipe<T>(Ab, a.ldl, rows_valid, Bb, boff, a.dh, a.dl, smem, acc, g0, g1, NoTail{});
-  }
-  __syncthreads();
-  if constexpr (GATE) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      *reinterpret_cast<u32x4 *>(smem + ((i) * 8 + r0) * kOutPitch + ch * 16) = g0.a[i];
-      *reinterpret_cast<u32x4 *>(smem + ((8 + i) * 8 + r0) * kOutPitch + ch * 16) = g0.b[i];
-      *reinterpret_cast<u32x4 *>(smem + ((16 + i) * 8 + r0) * kOutPitch + ch * 16) = g1.a[i];
-      *reinterpret_cast<u32x4 *>(smem + ((24 + i) * 8 + r0) * kOutPitch + ch * 16) = g1.b[i];
+    const bf16 *Ab = a.L + (int64_t)m0 * a.ldl + (head / a.hpq) * a.dl;
+    const WeightTile wt = weight_tile(a.wp + (int64_t)head * a.dl * a.dh, a.dh, (unsigned)(a.dl * a.dh * 2));
+    if constexpr (GATE) {
+      const GateTail<T::NT / 64> gate{buffer_of(a.g + (int64_t)m0 * ldo + col0, (unsigned)((rv - 1) * ldo * 2) + 512u), (unsigned)(ldo * 2), rv - 1};
+      gemm_mainloop_big<T>(Ab, a.ldl, rv, wt, a.dl, smem, acc, gate);
+    } else {
+      gemm_mainloop_big<T>(Ab, a.ldl, rv, wt, a.dl, smem, acc, NoTail{});
     }
-    __syncthreads();
   }
   // one row block (tm) at a time: all 16 gate reads of the block are issued before the first is used
   // the Sigmoid of the method takes the short path; the other nonlinearities a general one
@@ -793,7 +729,7 @@ __global__ __launch_bounds__(T::NT) void decoder_pair_kernel(DecoderArgs a) {
   if (!GATE || a.gate == kGateSigmoid) gate_rows(std::true_type{});
   else gate_rows(std::false_type{});
   __syncthreads();
-  for_each_out_chunk(smem, [&](int r, int ch, u32x4 v) {
+  for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
     if (m0 + r < a.M) *reinterpret_cast<u32x4 *>(a.out + (int64_t)(m0 + r) * ldo + col0 + ch * 8) = v;
   });
 }
@@ -803,7 +739,7 @@ __global__ __launch_bounds__(T::NT) void decoder_pair_kernel(DecoderArgs a) {
 // fetched with coalesced 16-byte loads before the main loop starts and applied as above.
 template <class T, bool GATE>
 __global__ __launch_bounds__(T::NT) void decoder_multi_kernel(DecoderArgs a) {
-  static_assert(T::BM == 256 && T::BN == 256 && T::NT == 256, "tile");
+  static_assert(T::BM == 256 && T::BN == 256 && T::NT == 256 && T::SMEM >= kOutBytes, "tile");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int hpt = T::BN / a.dh;   // heads per tile
   int mt, nt;
@@ -829,7 +765,7 @@ __global__ __launch_bounds__(T::NT) void decoder_multi_kernel(DecoderArgs a) {
   }
   if constexpr (GATE) {
 #pragma unroll
-    for (int it = 0; it < 32; ++it) *reinterpret_cast<u32x4 *>(smem + (it * 8 + r0) * kOutPitch + ch * 16) = gt[it];
+    for (int it = 0; it < 32; ++it) *reinterpret_cast<u32x4 *>(smem + out_chunk(it * 8 + r0, ch)) = gt[it];
     __syncthreads();
   }
   // the Sigmoid of the method takes the short path; the other nonlinearities a general one
@@ -862,7 +798,7 @@ __global__ __launch_bounds__(T::NT) void decoder_multi_kernel(DecoderArgs a) {
   if (!GATE || a.gate == kGateSigmoid) gate_rows(std::true_type{});
   else gate_rows(std::false_type{});
   __syncthreads();
-  for_each_out_chunk(smem, [&](int r, int ch, u32x4 v) {
+  for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
     if (m0 + r < a.M) *reinterpret_cast<u32x4 *>(a.out + (int64_t)(m0 + r) * ldo + col0 + ch * 8) = v;
   });
 }
@@ -879,14 +815,11 @@ __global__ __launch_bounds__(T::NT) void plain_gemm_kernel(PlainArgs a) {
   f32x16 acc[T::TN][T::TM];
   zero_acc<T>(acc);
   if constexpr (T::BM == 256 && T::BN == 256) {
-    const unsigned boff = (unsigned)((threadIdx.x / (T::BN / 8)) * a.N + (threadIdx.x % (T::BN / 8)) * 8) * 2u;
-    PipeStage<T> t0, t1;
-    gemm_mainloop_pipe<T>(a.A + (int64_t)m0 * a.lda, a.lda, a.M - m0, a.B + n0, boff, a.N, a.K, smem, acc, t0, t1, NoTail{});
+    gemm_mainloop_big<T>(a.A + (int64_t)m0 * a.lda, a.lda, a.M - m0, weight_tile(a.B + n0, a.N), a.K, smem, acc, NoTail{});
   } else {
     gemm_mainloop<T>(a.A, a.lda, a.M, m0, a.B, a.N, n0, a.K, smem, acc);
   }
   if constexpr (T::BM == 256 && T::BN == 256) {
-    __syncthreads();
     tile_to_lds<T>(acc, smem);
     __syncthreads();
     for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
@@ -1011,7 +944,12 @@ typedef GemmTile<64, 128, 64, 1, 4> TileSkinny64;
 typedef GemmTile<32, 64, 64, 1, 2> TileSkinny32N64;   // 64-wide tiles for widths that are not multiples of 128
 typedef GemmTile<64, 64, 64, 2, 2> TileSkinny64N64;
 
-typedef GemmTile<256, 256, 64, 2, 2> TileBig;    // wave tile 128 x 128
+#ifdef W4
+typedef GemmTile<256, 256, 64, 2, 2> TileBig;
+#else
+typedef GemmTile<256, 256, 64, 4, 2> TileBig;    // eight waves, wave tile 64(m) x 128(n)
+#endif
+typedef GemmTile<256, 256, 64, 2, 2> TileBig4;   // four waves of 128 x 128 (plain main loop)
 typedef GemmTile<256, 128, 64, 4, 1> TileHead;   // one 128-wide head per workgroup, wave tile 64(m) x 128(n)
 typedef GemmTile<256, 64, 64, 4, 1> TileHead64;  // one 64-wide head per workgroup, wave tile 64(m) x 64(n)
 
@@ -1175,8 +1113,8 @@ void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const voi
   }
   if ((d.dh == 64 || d.dh == 128) && d.hpq % (256 / d.dh) == 0) {
     const int nt = (d.nh * d.dh / 256) * ((M + 255) / 256);
-    if (d.gate) launch<TileBig>(decoder_multi_kernel<TileBig, true>, a, nt, st);
-    else launch<TileBig>(decoder_multi_kernel<TileBig, false>, a, nt, st);
+    if (d.gate) launch<TileBig4>(decoder_multi_kernel<TileBig4, true>, a, nt, st);
+    else launch<TileBig4>(decoder_multi_kernel<TileBig4, false>, a, nt, st);
   } else if (d.dh % 128 == 0) {
     launch<TileHead>(decoder_gemm_kernel<TileHead>, a, d.nh * (d.dh / 128) * ((M + 255) / 256), st);
   } else {   // heads of 64: one head per 64-wide tile

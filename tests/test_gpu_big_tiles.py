@@ -1,0 +1,62 @@
+"""The 256 x 256 GEMM tiles (operands loaded straight into LDS, eight waves) at their edges: one valid row in the last
+row tile and full row tiles, the shortest contraction the tiles take (four stages of 32) and lengths that leave the
+stages at each phase, two heads side by side in a weight tile, the packed weights, the gate on and off.
+
+Reference: float64 on the same bf16 inputs.  Bounds: the bf16 tolerances of the parity gate, the max-abs one scaled by
+the largest reference value (the outputs carry one bf16 rounding, 2^-9 of their size)."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as U
+from paper_2506_17286_amd import binding as B, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _wl(**kw):
+    base = dict(name="big", kind="prefill", batch=1, seqlen=64, d_model=256, n_heads=4, n_qgroups=2, n_kgroups=2, n_cgroups=1,
+                head_dim=128, latent_dim=256, dtype="bf16", rope=True, seed=6100)
+    return W.Workload(**dict(base, **kw))
+
+
+def _close(got, ref, what):
+    r = ref.cpu().numpy()
+    U.assert_close(U.f64(got), r, "bf16", what, max(1.0, float(np.abs(r).max())))
+
+
+@pytest.mark.parametrize("gate", [True, False])
+@pytest.mark.parametrize("rows", [4097, 4352])
+@pytest.mark.parametrize("wl", [_wl(), _wl(d_model=384, latent_dim=384), _wl(d_model=640, n_heads=8, latent_dim=512),
+                                _wl(head_dim=64, n_heads=20, n_qgroups=5, n_kgroups=1, latent_dim=128, d_model=256)],
+                         ids=["k256", "k384", "k640", "packed"])
+def test_big_tiles(wl, rows, gate):
+    cfg = B.config_of(wl)
+    cfg.gate = B.GATE_CODES[gate]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(wl.seed + rows)
+    rand = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).bfloat16()
+    H, dh, dl, nq, nk, nh = wl.d_model, wl.head_dim, wl.latent_dim, wl.n_qgroups, wl.n_kgroups, wl.n_heads
+    w = {"wq": rand(H, nq * dh, std=H ** -0.5), "wk": rand(H, nk * dh, std=H ** -0.5), "wc": rand(H, dl, std=H ** -0.5),
+         "wg": rand(H, nh * dh, std=H ** -0.5), "wp": rand(nh, dl, dh, std=dl ** -0.5), "wo": rand(nh * dh, H, std=(nh * dh) ** -0.5)}
+    gw, x = B.make_weights(w), rand(rows, H)
+    mk = lambda n: torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    out = {"q": mk(nq * dh), "k": mk(nk * dh), "c": mk(dl), "g": mk(nh * dh)}
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_PREFILL, 1, rows, rows))
+    B.gta_prefill_projection(cfg, gw, x, None, 1, rows, rows, out["q"], out["k"], out["c"], out["g"], ws)
+    ang = torch.arange(rows, device="cuda", dtype=torch.float64)[:, None] * \
+        wl.rope_base ** (-torch.arange(dh // 2, device="cuda", dtype=torch.float64) * 2 / dh)
+    for name, groups in (("q", nq), ("k", nk), ("c", 0), ("g", 0)):
+        ref = x.double() @ w["w" + name].double()
+        if groups:
+            lo, hi = ref.view(rows, groups, dh).split(dh // 2, dim=-1)
+            c, s = ang.cos()[:, None], ang.sin()[:, None]
+            ref = torch.cat([lo * c - hi * s, hi * c + lo * s], dim=-1).reshape(rows, -1)
+        _close(out[name], ref, name)
+    L, z, heads = rand(rows, nq * dl), rand(rows, nh * dh), mk(nh * dh)
+    B.gta_prefill_decoder(cfg, gw, L, z, rows, heads)
+    ref = torch.cat([L[:, h // (nh // nq) * dl:][:, :dl].double() @ w["wp"][h].double() for h in range(nh)], dim=1)
+    _close(heads, ref * torch.sigmoid(z.double()) if gate else ref, "decoder")
+    o = mk(H)
+    B.gta_output_projection(cfg, gw, heads, rows, o)
+    _close(o, heads.double() @ w["wo"].double(), "output projection")
