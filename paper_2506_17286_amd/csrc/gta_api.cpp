@@ -71,7 +71,8 @@ PrefillWs carve_prefill(const Dims &d, bool tuned, bool with_wo, int batch, int6
   w.rope = cv.take<float2>(d.rope ? (size_t)(chunk ? total : max_len) * (d.dh / 2) * sizeof(float2) : 0);
   // generic path: raw projections of every token; tuned path: split-K partials of a short prefill (the
   // same amount whatever the token count, so that a workspace sized for many tokens also serves few)
-  w.praw = cv.take<float>(tuned ? proj_small_rows_bound(d) * d.wtot * 4 : n * d.wtot * 4);
+  // and, once those are consumed, the partial sums of an attention that splits its keys
+  w.praw = cv.take<float>(tuned ? std::max(proj_small_rows_bound(d) * d.wtot * 4, attn_split_bytes(d)) : n * d.wtot * 4);
   w.q = cv.take<void>(n * d.wq_w * es);
   w.k = cv.take<void>(n * d.wk_w * es);
   w.c = cv.take<void>(n * d.wc_w * es);
@@ -389,7 +390,7 @@ int gta_prefill_attention(const gta_config *cfg, const void *q, const void *k, c
   if (total_tokens == 0 || max_seqlen == 0) return GTA_OK;
   hipStream_t st = (hipStream_t)hip_stream;
   if (attn_prefill_supported(d, max_seqlen))
-    launch_attn_prefill_bf16(d, q, k, c, cu_seqlens, batch, total_tokens, max_seqlen, l_out, st);
+    launch_attn_prefill_bf16(d, q, k, c, cu_seqlens, batch, total_tokens, max_seqlen, l_out, nullptr, st);
   else if (f32_attn_ok(d, batch, max_seqlen))
     launch_attn_prefill_f32(d, (const float *)q, (const float *)k, (const float *)c, cu_seqlens, batch, total_tokens, max_seqlen,
                             (float *)l_out, st);

@@ -149,7 +149,7 @@ struct BigLoop {
 // 16 bytes per lane from rsrc + voff + soff to LDS offset lds + 16 * lane.  vmcnt counts it; the compiler does not
 // know that, so every wait for these loads is spelled out.
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff));
 }
 __device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {   // reads past `bytes` return 0
   const uint64_t b = (uint64_t)base;

@@ -2,7 +2,7 @@
 // for every map group g, L_g = Softmax(Q_g K_{k(g)}^T / sqrt(d_h)) C_{c(g)}, one shared map per
 // group, output width d_l (normalised, bf16).  The value decoder runs afterwards as a GEMM.
 //
-// One workgroup = 256 queries of one (sequence, group) x 256 latent columns; each of its 8 waves
+// One workgroup = 256 queries of one (sequence, group) x up to 256 latent columns; each of its 8 waves
 // (two per SIMD, so one wave's softmax runs in the shadow of the other's MFMAs) owns 32 queries
 // and the whole column slice (128 accumulator registers): the softmax statistics of a query live
 // in one lane pair and nothing is exchanged between waves.  Wider latents are covered by several
@@ -22,11 +22,18 @@
 // with v_cvt_pk_bf16_f32 and summed with v_dot2_f32_bf16 (so the row sum is the sum of the rounded
 // values the MFMA sees).
 //
-// Key/latent tiles of 32 rows go global -> registers -> LDS through three stages: the loads of a
-// tile are issued two tiles ahead and written to LDS one tile ahead of its use, one barrier per
-// tile.  The finished tile is rounded to bf16, parked in LDS in output layout and
-// written with 16-byte stores, 32 lanes per 512-byte row segment.
+// Key/latent tiles of 32 rows go from memory straight into LDS (buffer_load_dwordx4 .. lds) through five stages, four
+// steps ahead of their use, one barrier per step; measured against staging through registers and LDS writes: 7 % of the
+// kernel at latents of 1024 and 3 % at 512 (ragged batch of 112 K tokens 19.6 -> 18.6 ms, 4 x 4096 tokens 238 -> 230
+// us).  Bound: MFMA issue, the LDS reads of the fragments (1 KiB per MFMA) and the softmax arithmetic share the cycles
+// (matrix pipes busy about half of them); latents wider than a tile recompute the scores.  The finished tile is rounded
+// to bf16, parked in LDS in output layout and written with 16-byte stores, 32 lanes per 512-byte row segment.
+//
+// Launches that would leave CUs idle take 128 queries per workgroup and split the keys over the two halves of its waves,
+// and, if that is not enough, over workgroups with a merge kernel (rule and figures at launch_attn).
 #include <math.h>
+
+#include <type_traits>
 
 #include "gta_tuned.h"
 
@@ -44,21 +51,36 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-template <int DH_, int DLW_>
+// KS: key halves.  KS = 1: 256 queries, all eight waves walk the same key tiles.  KS = 2: 128 queries, waves 0-3 take
+// the even key tiles and waves 4-7 the odd ones, each with statistics and accumulators of its own, merged at the end:
+// half the chain of key tiles per workgroup and twice the workgroups, for launches that leave CUs idle.
+template <int DH_, int DLW_, int KS_ = 1>
 struct AttnTile {
-  static constexpr int DH = DH_, DLW = DLW_, BK = 32, BQ = 256, NT = 512, NDLB = DLW / 32, NSTAGE = 3;
-  static constexpr int K_PITCH = DH * 2 + 16;      // 16 * odd: conflict-free 16-byte row reads
-  static constexpr int C_PITCH = DLW * 2 + 64 + (DLW % 128 ? 128 : 0);   // == 64 mod 256: conflict-free transpose reads
-  static constexpr int K_BYTES = BK * K_PITCH, C_BYTES = BK * C_PITCH, STAGE = K_BYTES + C_BYTES;
+  static constexpr int DH = DH_, DLW = DLW_, KS = KS_, BK = 32, NT = 512, QW = 8 / KS, BQ = 32 * QW, NDLB = DLW / 32;
+  // A key / latent tile goes straight into LDS, 1 KiB per load instruction in lane order, so rows that one instruction
+  // fetches cannot be padded apart; each instruction therefore fetches rows that are not read together:
+  //   keys     (16 bytes per lane, 32 rows in a row): instruction a fetches rows a + K_INSTR i and lands 16 bytes
+  //            further per a; every second i has its chunk halves swapped (k_sel).  8 (16) rows in a row then lie in
+  //            different 16-byte columns of 128 (256) bytes.
+  //   latents  (transpose read: four rows r of 64 bytes per half wave): instruction 4 b + r fetches rows 4 a + r and
+  //            lands 64 bytes further per r, which puts the four rows into different 64-byte columns of 256 bytes.
+  // Every fragment of a tile is then at one (keys: two) per-lane addresses plus a constant.
+  static constexpr int K_ROW = DH * 2, C_ROW = DLW * 2, K_CPR = K_ROW / 16, C_CPR = C_ROW / 16;
+  static constexpr int K_INSTR = BK * K_ROW / 1024, C_INSTR = BK * C_ROW / 1024, C_RPI = 1024 / C_ROW;
+  static constexpr int K_PITCH = 1024 + 16, C_PITCH = 1024 + 64, C_GROUP = 4 * C_PITCH;
+  static constexpr int K_BYTES = K_INSTR * K_PITCH, C_BYTES = C_INSTR / 4 * C_GROUP, TILE = K_BYTES + C_BYTES, STAGE = KS * TILE;
+  static constexpr int NSTAGE = KS == 1 ? 5 : 3;
   static constexpr int OUT_PITCH = DLW * 2 + 16;
-  static constexpr int SMEM = BQ * OUT_PITCH > NSTAGE * STAGE ? BQ * OUT_PITCH : NSTAGE * STAGE;
-  // 16-byte chunks per tile row, tile rows one pass of the 512 threads covers, passes per tile
-  static constexpr int K_CPR = DH / 8, C_CPR = DLW / 8, K_CHUNKS = BK * K_CPR;
-  static constexpr int C_RPP = NT / C_CPR < BK ? NT / C_CPR : BK, C_LOADS = BK / C_RPP, C_CHUNKS = C_RPP * C_CPR;
+  static constexpr int cmax(int a, int b) { return a > b ? a : b; }
+  static constexpr int MERGE = KS == 1 ? 0 : QW * (NDLB * 16 + 2) * 256;   // the odd half's accumulators and statistics
+  static constexpr int SMEM = cmax(cmax(BQ * OUT_PITCH, NSTAGE * STAGE), MERGE);
   // the hand-scheduled main loop deals 16 softmax slices over 2 * NDLB steps; others take the plain loop
   static constexpr bool PIPELINED = NDLB == 8 || NDLB == 4;
-  static_assert(DH % 16 == 0 && DLW % 32 == 0 && K_CHUNKS <= NT && BK % C_RPP == 0 && C_LOADS >= 1, "tile");
+  static_assert((DH == 64 || DH == 128) && (DLW == 64 || DLW == 128 || DLW == 256) && (KS == 1 || KS == 2), "tile");
   static_assert(SMEM <= 160 * 1024, "LDS budget");
+  __device__ static constexpr int k_sel(int i) { return K_CPR == 16 ? i & 1 : (i ^ (i >> 1)) & 1; }
+  // LDS offset, inside the latent tile, of row 4 a for column 0
+  __device__ static constexpr int c_row(int a) { return a / C_RPI * C_GROUP + a % C_RPI * C_ROW; }
 };
 
 struct AttnArgs {
@@ -75,6 +97,9 @@ struct AttnArgs {
   // already in them behind the prefix[b] rows cached before (prefix[b] < 0: sequence skipped, zero output)
   const int32_t *prefix, *slots; int max_seq;
   PageMap pm; int ps_shift;   // cache mode on a block-table layout: page_size = 1 << ps_shift, a multiple of BK
+  // key range split over `splits` workgroups (not fused): each writes un-normalised fp32 sums pacc [split, token,
+  // n_q*d_l] and (maximum in log2 units, sum) pml [split, token, n_q, column slice], merged by attn_merge_kernel
+  int splits; float *pacc; float2 *pml; int64_t total;
 };
 
 // LDS of the fused value decoder: the normalised 256 x DLW tile (row operand) and the DLW x 256
@@ -84,6 +109,7 @@ struct FusedDecoder {
   static constexpr int N = 256;                         // heads per group x d_h
   static constexpr int W_PITCH = N * 2 + 64;            // == 64 mod 256 for the transpose reads
   static constexpr int W_OFF = T::BQ * T::OUT_PITCH;    // behind the L tile
+  static constexpr int NTN = N / 32 / T::KS;            // 32-column tiles per wave: KS waves share 32 queries
   static constexpr int G_PITCH = N * 2 + 16;
   static constexpr int SMEM_LW = W_OFF + T::DLW * W_PITCH, SMEM_G = T::BQ * G_PITCH;
   static constexpr int SMEM = SMEM_LW > SMEM_G ? (SMEM_LW > T::SMEM ? SMEM_LW : T::SMEM) : (SMEM_G > T::SMEM ? SMEM_G : T::SMEM);
@@ -103,6 +129,24 @@ __device__ __forceinline__ float pair_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// 16 bytes per lane from rsrc + voff to LDS offset lds + 16 * lane; reads past the buffer's end return 0.  vmcnt counts
+// it; the compiler does not know that, so every wait for these loads is spelled out.  (M0 holds nothing the compiler keeps.)
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc));
+}
+__device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {
+  const uint64_t b = (uint64_t)base;   // wave-uniform, which the compiler does not always see
+  return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)b), (unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32) & 0xffff),
+               (unsigned)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
+}
+
+// A scalar load, waited for in place: a vector load would make the compiler wait for every load in flight.
+__device__ __forceinline__ int load_uniform(const int32_t *p) {
+  int v;
+  asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p));
+  return v;
+}
+
 template <class T, bool FUSE>
 __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -115,19 +159,23 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
   // Ids go to the XCDs round-robin whatever their cost, so with ragged lengths a fixed sequence digit
   // would tie each sequence to one XCD and the longest sequences would bound the launch: the
   // sequence digit is rotated by one per tile level, which spreads every sequence over all XCDs.
-  const int per_qt = a.batch * a.nq * a.ndlc;
+  const int per_qt = a.batch * a.nq * a.ndlc * a.splits;
   const int lvl = (int)blockIdx.x / per_qt;
   const int qt = a.n_qtiles - 1 - lvl;
   const int rest = (int)blockIdx.x % per_qt;
   const int b = a.cu ? (rest % a.batch + lvl) % a.batch : rest % a.batch;
-  const int g = (rest / a.batch) % a.nq, dlc = rest / (a.batch * a.nq);
+  const int g = (rest / a.batch) % a.nq, dlc = rest / (a.batch * a.nq) % a.ndlc, split = rest / (a.batch * a.nq * a.ndlc);
   const int64_t start = a.cu ? a.cu[b] : (int64_t)b * a.per_seq;
   const int Tb = a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq;   // queries of this sequence
   const int q0 = qt * T::BQ;
   if (q0 >= Tb) return;
   const int P = a.prefix ? a.prefix[b] : 0;                  // keys cached before the first query
+  const int kh = wave / T::QW, qw = wave % T::QW;            // key half and query rows of this wave
+  float2 *pml = a.pml + (((int64_t)split * a.total + start + q0) * a.nq + g) * a.ndlc + dlc;   // split keys only
   if (P < 0) {   // skipped sequence: zero rows
-    if constexpr (FUSE) {
+    if (!FUSE && a.splits > 1) {
+      if (tid < T::BQ && q0 + tid < Tb) pml[(int64_t)tid * a.nq * a.ndlc] = make_float2(-INFINITY, 0.f);
+    } else if constexpr (FUSE) {
       const int64_t ldo = (int64_t)a.nh * a.dh;
       bf16 *Ob = a.out + (start + q0) * ldo + g * a.hpq * a.dh;
       for (int i = tid; i < T::BQ * 32; i += T::NT)
@@ -141,10 +189,12 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     return;
   }
   const int Tk = P + Tb;                                     // keys of this sequence
-  const int qw0 = q0 + wave * 32;                            // first query of this wave
+  const int qw0 = q0 + qw * 32;                              // first query of this wave
   const int qa0 = P + qw0;                                   // its position among the keys
   const int kend = P + min(q0 + T::BQ, Tb);                  // keys [0, kend) are visible to this tile
-  const int ntiles = (kend + T::BK - 1) / T::BK;
+  const int ntiles_all = (kend + T::BK - 1) / T::BK;
+  const int tile0 = (int)((int64_t)ntiles_all * split / a.splits), tile1 = (int)((int64_t)ntiles_all * (split + 1) / a.splits);
+  const int nsteps = (tile1 - tile0 + T::KS - 1) / T::KS;    // step t: key tiles tile0 + KS t (+ 1)
   const int kend_w = qw0 < Tb ? P + min(qw0 + 32, Tb) : 0;   // keys [0, kend_w) are visible to this wave
   int64_t krow0 = start;                                     // first key / latent row of the sequence
   int slot = 0;
@@ -152,6 +202,7 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     slot = a.slots ? a.slots[b] : b;
     krow0 = a.pm.table ? 0 : (int64_t)slot * a.max_seq;      // block table: Kb / Cb are the pools, rows per tile
   }
+  const int32_t *table = a.pm.table + (int64_t)__builtin_amdgcn_readfirstlane(slot) * a.pm.pages_per_slot;
   const char *Kb = reinterpret_cast<const char *>(a.k + krow0 * a.wk_w + (g / a.qpk) * T::DH);
   const char *Cb = reinterpret_cast<const char *>(a.c + krow0 * a.wc_w + (g / a.qpc) * a.dl + dlc * T::DLW);
   const unsigned wk2 = a.wk_w * 2, wc2 = a.wc_w * 2;
@@ -160,11 +211,6 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
   // the 16-byte chunk d = ks*16 + h*8 .. +8 of the lane's query (rows past the sequence re-read its
   // last row; their output is never written).
   bf16x8 qf[T::DH / 16];
-  {
-    const bf16 *qg = a.q + (start + min(qw0 + ln, Tb - 1)) * a.wq_w + g * T::DH + h * 8;
-#pragma unroll
-    for (int ks = 0; ks < T::DH / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qg + ks * 16);
-  }
 
   f32x16 acc[T::NDLB];
 #pragma unroll
@@ -173,56 +219,85 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  // cooperative tile staging: global -> registers -> LDS; rows past the sequence re-read its last row
-  // (such keys are in the future of every valid query and are masked)
-  u32x4 rk, rc[T::C_LOADS];
-  const int k_row = tid / T::K_CPR, k_ch = tid % T::K_CPR, c_row = tid / T::C_CPR, c_ch = tid % T::C_CPR;
-  // narrow tiles have fewer chunks than threads (no predicate at all where every thread loads)
-  const bool k_loader = T::K_CHUNKS >= T::NT || tid < T::K_CHUNKS, c_loader = T::C_CHUNKS >= T::NT || tid < T::C_CHUNKS;
-  auto gload = [&](int t) {
-    const int j0 = t * T::BK;
-    const char *Kt = Kb, *Ct = Cb;
-    int sub = 0;
-    if (a.pm.table) {   // the tile's 32 rows sit in one page: rows relative to the tile's first pool row
-      const int jt = min(j0, (Tk - 1) & ~(T::BK - 1));   // tiles past the sequence re-read its last tile
-      const int pi = __builtin_amdgcn_readfirstlane(jt >> a.ps_shift);
-      int pg = a.pm.table[(int64_t)slot * a.pm.pages_per_slot + pi];
-      pg = (unsigned)pg >= (unsigned)a.pm.num_pages ? 0 : pg;
-      const int64_t prow = ((int64_t)pg << a.ps_shift) + (jt & (a.pm.page_size - 1));
-      Kt = Kb + prow * wk2; Ct = Cb + prow * wc2;
-      sub = jt;
-    }
-    if (k_loader) {
-      const unsigned r = min(j0 + k_row, Tk - 1) - sub;
-      rk = *reinterpret_cast<const u32x4 *>(Kt + (r * wk2 + k_ch * 16));
-    }
-    if (c_loader) {
+  // Tile staging: this wave's load instructions of a tile are `wave` (, + 8) of the keys and of the latents; tiles with
+  // fewer than eight share the waves.  Rows past the sequence read as zeros (such keys are in the future of every
+  // valid query and are masked, and 0 x 0 adds nothing).
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+  constexpr int CI = T::C_INSTR >= 8 ? T::C_INSTR / 8 : 1;
+  const int ki = wave % T::K_INSTR, ci = wave % T::C_INSTR;
+  unsigned kv, cv[CI];
+  {
+    const int i = lane / T::K_CPR;
+    kv = (ki + T::K_INSTR * i) * wk2 + ((lane % T::K_CPR) ^ (T::k_sel(i) * (T::K_CPR / 2))) * 16;
 #pragma unroll
-      for (int i = 0; i < T::C_LOADS; ++i) {
-        const unsigned r = min(j0 + c_row + i * T::C_RPP, Tk - 1) - sub;
-        rc[i] = *reinterpret_cast<const u32x4 *>(Ct + (r * wc2 + c_ch * 16));
+    for (int j = 0; j < CI; ++j) {
+      const int q = ci + 8 * j;
+      cv[j] = (4 * (q / 4 * T::C_RPI + lane / T::C_CPR) + q % 4) * wc2 + (lane % T::C_CPR) * 16;
+    }
+  }
+  auto k_loader = [&](int j) { return T::K_INSTR >= 8 || wave / 4 == (T::KS == 2 ? j : 0); };
+  auto c_loader = [&](int j) { return T::C_INSTR >= 8 || wave / 4 == (T::KS == 2 ? 1 - j : 1); };
+  // requests the next step: `fill` is its stage, j_next its first key
+  unsigned fill = lds0;
+  int j_next = tile0 * T::BK;
+  const char *kp = Kb + (int64_t)j_next * wk2, *cp = Cb + (int64_t)j_next * wc2;
+  auto issue = [&]() {
+#pragma unroll
+    for (int j = 0; j < T::KS; ++j) {
+      const int j0 = j_next + j * T::BK, rows = min(Tk - j0, T::BK);   // rows < 1: past the end
+      const char *kt = kp + j * T::BK * (int64_t)wk2, *ct = cp + j * T::BK * (int64_t)wc2;
+      if (a.pm.table) {   // the tile's 32 rows sit in one page
+        const int jt = min(j0, (Tk - 1) & ~(T::BK - 1));
+        int pg = load_uniform(table + __builtin_amdgcn_readfirstlane(jt >> a.ps_shift));
+        pg = (unsigned)pg >= (unsigned)a.pm.num_pages ? 0 : pg;
+        const int64_t row0 = ((int64_t)pg << a.ps_shift) + (jt & (a.pm.page_size - 1));
+        kt = Kb + row0 * wk2; ct = Cb + row0 * wc2;
+      }
+      if (k_loader(j)) load_to_lds(buffer_of(kt, rows > 0 ? (rows - 1) * wk2 + T::K_ROW : 0u), kv, fill + j * T::TILE + ki * T::K_PITCH);
+      if (c_loader(j)) {
+        const u32x4 r = buffer_of(ct, rows > 0 ? (rows - 1) * wc2 + T::C_ROW : 0u);
+#pragma unroll
+        for (int i = 0; i < CI; ++i) load_to_lds(r, cv[i], fill + j * T::TILE + T::K_BYTES + (ci + 8 * i) * T::C_PITCH);
       }
     }
+    j_next += T::KS * T::BK;
+    kp += T::KS * T::BK * (int64_t)wk2; cp += T::KS * T::BK * (int64_t)wc2;
+    fill = fill == lds0 + (T::NSTAGE - 1) * T::STAGE ? lds0 : fill + T::STAGE;
   };
-  auto sstore = [&](char *st) {
-    if (k_loader) *reinterpret_cast<u32x4 *>(st + k_row * T::K_PITCH + k_ch * 16) = rk;
-    if (c_loader) {
-#pragma unroll
-      for (int i = 0; i < T::C_LOADS; ++i)
-        *reinterpret_cast<u32x4 *>(st + T::K_BYTES + (c_row + i * T::C_RPP) * T::C_PITCH + c_ch * 16) = rc[i];
-    }
+  // load instructions of this wave per step; wait until at most `steps` steps of them are in flight, then meet
+  constexpr int PER_STEP = (T::K_INSTR >= 8 ? T::KS : T::KS == 2 ? 1 : 0) + (T::C_INSTR >= 8 ? CI * T::KS : T::KS == 2 ? 1 : 0);
+  constexpr bool UNEVEN = T::KS == 1 && (T::K_INSTR < 8) != (T::C_INSTR < 8);   // keys by waves 0-3 only, one more each
+  constexpr bool SHARED = T::KS == 1 && T::K_INSTR < 8 && T::C_INSTR < 8;        // every wave loads one or the other
+  auto wait_meet = [&](auto steps_tag) {
+    constexpr int N = decltype(steps_tag)::value * (SHARED ? 1 : PER_STEP), N1 = decltype(steps_tag)::value * (PER_STEP + 1);
+    if (UNEVEN && wave < 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N1) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
   };
-  const int koff = ln * T::K_PITCH + h * 16;
-  const int coff = T::K_BYTES + (4 * h + ((lane & 15) >> 2)) * T::C_PITCH + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+  // fragment addresses inside a stage (of this wave's tile)
+  const int ksel = T::k_sel(ln / T::K_INSTR) * (T::K_ROW / 2);
+  const int koff = kh * T::TILE + ln % T::K_INSTR * T::K_PITCH + ln / T::K_INSTR * T::K_ROW + h * 16;
+  const int koff_lo = koff + ksel, koff_hi = koff - ksel;      // first, second half of a key row
+  const int coff = kh * T::TILE + T::K_BYTES + ((lane & 15) >> 2) * T::C_PITCH + T::c_row(0) + h * (T::c_row(1) - T::c_row(0)) +
+                   (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+  auto c_frag = [&](int st, int mm, int dlb) {
+    const char *p = smem + (st + coff) + T::c_row(4 * mm) + dlb * 64;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + T::c_row(2)));
+    const s16x8 c8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, c8);
+  };
+  auto k_frag = [&](int st, int ks) {
+    return *reinterpret_cast<const bf16x8 *>(smem + (st + (ks < T::DH / 32 ? koff_lo : koff_hi)) + ks * 32);
+  };
 
   // scores S^T of one 32-key block (raw, unscaled); all key fragments are requested before the first
   // MFMA so that the chain of MFMAs pays one LDS round trip, not one per fragment
-  auto scores = [&](const char *st, f32x16 &s) {
+  auto scores = [&](int st, f32x16 &s) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
     bf16x8 kf[T::DH / 16];
 #pragma unroll
-    for (int ks = 0; ks < T::DH / 16; ++ks) kf[ks] = *reinterpret_cast<const bf16x8 *>(st + koff + ks * 32);
+    for (int ks = 0; ks < T::DH / 16; ++ks) kf[ks] = k_frag(st, ks);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < T::DH / 16; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
@@ -245,7 +320,9 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     for (int r = 2; r < 16; r += 2) bm = fmaxf(fmaxf(s[r], s[r + 1]), bm);   // v_max3
     const float m_cand = pair_max(bm) * a.scale_log2e;
     const float m_new = m_cand > m_run + kLazyThreshold ? fmaxf(m_run, m_cand) : m_run;
-    corr = __builtin_amdgcn_exp2f(m_run - m_new);
+    // a query may see no key of this wave's first block (a block behind it, another wave's or workgroup's keys before it)
+    const float ref = m_new > -INFINITY ? m_new : 0.f;
+    corr = __builtin_amdgcn_exp2f(m_run - ref);
     m_run = m_new;
     const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
     float ps = 0.f;
@@ -253,8 +330,8 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     for (int mm = 0; mm < 2; ++mm)
 #pragma unroll
       for (int i = 0; i < 8; i += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[mm * 8 + i], a.scale_log2e, -m_new));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[mm * 8 + i + 1], a.scale_log2e, -m_new));
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[mm * 8 + i], a.scale_log2e, -ref));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[mm * 8 + i + 1], a.scale_log2e, -ref));
         bf16x2 pk;
         pk[0] = (bf16)p0; pk[1] = (bf16)p1;
         pn[mm][i] = pk[0]; pn[mm][i + 1] = pk[1];
@@ -263,48 +340,49 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     l_run = fmaf(l_run, corr, ps);
   };
   // L^T += C^T . P^T, latent tile rows read through the transpose load with the same key order
-  auto pv = [&](const char *st, const bf16x8 (&pf)[2]) {
+  auto pv = [&](int st, const bf16x8 (&pf)[2]) {
     // key half outermost: consecutive MFMAs go to different accumulators
 #pragma unroll
-    for (int mm = 0; mm < 2; ++mm) {
+    for (int mm = 0; mm < 2; ++mm)
 #pragma unroll
-      for (int dlb = 0; dlb < T::NDLB; ++dlb) {
-        const char *cp = st + coff + mm * 16 * T::C_PITCH + dlb * 64;
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(cp));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(cp + 8 * T::C_PITCH));
-        s16x8 c8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        acc[dlb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, c8), pf[mm], acc[dlb], 0, 0, 0);
-      }
-    }
+      for (int dlb = 0; dlb < T::NDLB; ++dlb)
+        acc[dlb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c_frag(st, mm, dlb), pf[mm], acc[dlb], 0, 0, 0);
   };
 
   // The waves of a workgroup meet at a barrier every tile and so run in phase: the overlap of softmax
   // arithmetic and MFMAs has to come from each wave's own instruction stream.  Iteration t issues the
   // score MFMAs of block t+1, then the map-times-latent MFMAs of block t with the softmax arithmetic
   // of block t+1 dealt out between them.
-  // Stages: tile t+1 is read (scores) from `nxt`, tile t (latents) from `cur`, tile t+2 (loaded during
-  // iteration t-1) is written to `fre`, tile t+3 is loaded.
-  const int nb_w = (kend_w + 31) >> 5;   // blocks this wave needs: 0 .. nb_w-1
-  bf16x8 pf[2];
+  // Step t reads the latents of its tile from stage t and the keys of the next from stage t + 1; the loads of step
+  // t + NSTAGE - 1 go out at its start, into the stage that step t - 1 left.
+  const int nb_all = (kend_w + 31) >> 5, nb_w = min(nb_all, tile1);   // this wave's blocks: tile0 + KS t + kh < nb_w
+  auto blk = [&](int t) { return tile0 + T::KS * t + kh; };
+  bf16x8 pf[2] = {};
   float corr = 1.f;
-  gload(0);
-  sstore(smem);
-  gload(1);
-  __syncthreads();
-  if (nb_w > 0) {
+  issue();
+  issue();
+  {
+    const bf16 *qg = a.q + (start + min(qw0 + ln, Tb - 1)) * a.wq_w + g * T::DH + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < T::DH / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qg + ks * 16);
+    // the compiler's wait for them belongs here, where it costs nothing, and not in front of their uses in the loops
+#pragma unroll
+    for (int ks = 0; ks < T::DH / 16; ++ks) asm volatile("" : "+v"(qf[ks]));
+  }
+#pragma unroll
+  for (int t = 2; t < T::NSTAGE; ++t) issue();
+  wait_meet(std::integral_constant<int, T::NSTAGE - 2>{});   // steps 0 and 1 have landed
+  if (blk(0) < nb_w) {
     f32x16 s;
-    scores(smem, s);
-    if (31 > qa0) mask(s, 0);
+    scores(0, s);
+    if (blk(0) * 32 + 31 > qa0) mask(s, blk(0) * 32);
     softmax(s, pf, corr);
     corr = 1.f;   // the accumulators are still zero
   }
-  sstore(smem + T::STAGE);
-  gload(2);
-  __syncthreads();
-  int cur = 0, nxt = T::STAGE, fre = 2 * T::STAGE;
+  int cur = 0, nxt = T::STAGE;
   auto rotate = [&]() {
-    const int tmp = cur;
-    cur = nxt; nxt = fre; fre = tmp;
+    cur = nxt;
+    nxt = nxt == (T::NSTAGE - 1) * T::STAGE ? 0 : nxt + T::STAGE;
   };
   auto rescale = [&]() {
     if (__builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {   // rare: the running maximum moved
@@ -314,23 +392,21 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
         for (int r = 0; r < 16; ++r) acc[i][r] *= corr;
     }
   };
-  // main part: blocks t and t+1 both lie entirely below this wave's diagonal
+  // main part: this wave's blocks of steps t and t+1 both lie entirely below its diagonal
   int t = 0;
   if constexpr (T::PIPELINED) {
-  const int t_main = min(nb_w, qa0 >> 5) - 1;   // iterations 0 .. t_main-1
+  const int lim = min(nb_w, qa0 >> 5) - 1 - tile0 - kh, t_main = lim < 0 ? 0 : lim / T::KS;   // steps 0 .. t_main-1
 #pragma unroll 1
   for (; t < t_main; ++t) {
     // The fragment reads of the first score MFMAs and of the first two map-times-latent MFMAs go out
     // before anything else, so that the MFMAs below do not each wait for an LDS round trip; the second
     // half of the key fragments follows behind the first two score MFMAs.
     constexpr int KS = T::DH / 16, KS1 = KS / 2;
-    const char *kst = smem + nxt + koff;
     bf16x8 kf[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS1; ++ks) kf[ks] = *reinterpret_cast<const bf16x8 *>(kst + ks * 32);
+    for (int ks = 0; ks < KS1; ++ks) kf[ks] = k_frag(nxt, ks);
     __builtin_amdgcn_sched_barrier(0);
-    sstore(smem + fre);
-    gload(t + 3);
+    if (t > 0) issue();
     rescale();
     f32x16 s;
 #pragma unroll
@@ -340,7 +416,7 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     for (int ks = 0; ks < KS; ++ks) {
       if (ks == 1) {
 #pragma unroll
-        for (int k2 = KS1; k2 < KS; ++k2) kf[k2] = *reinterpret_cast<const bf16x8 *>(kst + k2 * 32);
+        for (int k2 = KS1; k2 < KS; ++k2) kf[k2] = k_frag(nxt, k2);
       }
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
@@ -349,16 +425,9 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     // transpose reads of fragment i+2 and a slice of the softmax arithmetic of block t+1 (16 slices
     // dealt evenly over the steps); the scheduling barrier after every step pins this order, so each
     // MFMA is followed by arithmetic that runs in its shadow
-    const char *st = smem + cur;
     constexpr int NS = 2 * T::NDLB, SPS = 16 / NS;   // steps, softmax slices per step
-    auto cread = [&](int i) {
-      const char *cp = st + coff + (i / T::NDLB) * 16 * T::C_PITCH + (i % T::NDLB) * 64;
-      s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(cp));
-      s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(cp + 8 * T::C_PITCH));
-      s16x8 c8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8, c8);
-    };
-    constexpr int LA = 2;   // latent fragments in flight ahead of their MFMA (3 measured no better)
+    auto cread = [&](int i) { return c_frag(cur, i / T::NDLB, i % T::NDLB); };
+    constexpr int LA = 3;   // latent fragments in flight ahead of their MFMA
     bf16x8 cf[NS + LA], pn[2];
 #pragma unroll
     for (int i = 0; i < LA; ++i) cf[i] = cread(i);
@@ -396,38 +465,79 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
       corr = 1.f;
     }
     pf[0] = pn[0]; pf[1] = pn[1];
-    __syncthreads();
+    wait_meet(std::integral_constant<int, T::NSTAGE - 3>{});
     rotate();
   }
   }
-  // the blocks around the diagonal, then idle iterations that only keep staging for the other waves
+  // the blocks around the diagonal, then idle steps that only keep staging for the other waves
 #pragma unroll 1
-  for (; t < ntiles; ++t) {
-    sstore(smem + fre);
-    gload(t + 3);
-    if (t < nb_w) {
+  for (; t < nsteps; ++t) {
+    if (t > 0) issue();
+    if (blk(t) < nb_w) {
       rescale();
       f32x16 s;
       bf16x8 pn[2];
-      if (t + 1 < nb_w) {
-        scores(smem + nxt, s);
-        if ((t + 1) * 32 + 31 > qa0) mask(s, (t + 1) * 32);
+      if (blk(t + 1) < nb_w) {
+        scores(nxt, s);
+        if (blk(t + 1) * 32 + 31 > qa0) mask(s, blk(t + 1) * 32);
       } else {   // no further block: all-masked scores leave the statistics unchanged and give P = 0
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = -INFINITY;
       }
       softmax(s, pn, corr);
-      pv(smem + cur, pf);
+      pv(cur, pf);
       pf[0] = pn[0]; pf[1] = pn[1];
     }
-    __syncthreads();
+    wait_meet(std::integral_constant<int, T::NSTAGE - 3>{});
     rotate();
+  }
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // no load may land in what follows
+
+  float l_all = pair_sum(l_run);
+  if constexpr (T::KS == 2) {
+    // ---- the odd half's sums join the even half's: register r of lane i of wave w at (w, r, i).  A query whose keys
+    // all lie in one half gets weight 0 from the other (maximum -inf).
+    float *mg = reinterpret_cast<float *>(smem) + qw * (T::NDLB * 16 + 2) * 64 + lane;
+    if (kh == 1) {
+#pragma unroll
+      for (int dlb = 0; dlb < T::NDLB; ++dlb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mg[(dlb * 16 + r) * 64] = acc[dlb][r];
+      mg[T::NDLB * 16 * 64] = m_run; mg[(T::NDLB * 16 + 1) * 64] = l_all;
+    }
+    __syncthreads();
+    if (kh == 0) {
+      const float mo = mg[T::NDLB * 16 * 64], lo = mg[(T::NDLB * 16 + 1) * 64], mx = fmaxf(m_run, mo);
+      const float ref = mx > -INFINITY ? mx : 0.f;
+      const float se = __builtin_amdgcn_exp2f(m_run - ref), so = __builtin_amdgcn_exp2f(mo - ref);
+      l_all = l_all * se + lo * so;
+      m_run = mx;
+#pragma unroll
+      for (int dlb = 0; dlb < T::NDLB; ++dlb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dlb][r] = acc[dlb][r] * se + mg[(dlb * 16 + r) * 64] * so;
+    }
+    __syncthreads();
+  }
+  if (!FUSE && a.splits > 1) {   // un-normalised sums and statistics for the merge
+    const int row = qw * 32 + ln;
+    if (kh == 0 && q0 + row < Tb) {
+      float *pa = a.pacc + ((int64_t)split * a.total + start + q0 + row) * (a.nq * a.dl) + g * a.dl + dlc * T::DLW + 4 * h;
+#pragma unroll
+      for (int dlb = 0; dlb < T::NDLB; ++dlb)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq)
+          *reinterpret_cast<float4 *>(pa + dlb * 32 + rq * 8) =
+              make_float4(acc[dlb][rq * 4], acc[dlb][rq * 4 + 1], acc[dlb][rq * 4 + 2], acc[dlb][rq * 4 + 3]);
+      if (h == 0) pml[(int64_t)row * a.nq * a.ndlc] = make_float2(m_run, l_all);
+    }
+    return;
   }
 
   // ---- normalise, park the tile in LDS in output layout, write row-contiguous 16-byte chunks
-  {
-    const float inv = 1.0f / pair_sum(l_run);
-    const int row = wave * 32 + ln;
+  if (kh == 0) {
+    const float inv = 1.0f / l_all;
+    const int row = qw * 32 + ln;
 #pragma unroll
     for (int dlb = 0; dlb < T::NDLB; ++dlb)
 #pragma unroll
@@ -469,18 +579,18 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
         gt[i] = *reinterpret_cast<const u32x4 *>(gp + (start + min(q0 + i * GRPP + gr0, Tb - 1)) * ldo);
     }
     __syncthreads();
-    f32x16 z[F::N / 32];
+    f32x16 z[F::NTN];   // this wave's columns: 32 (kh * NTN + tn) ..
 #pragma unroll
-    for (int tn = 0; tn < F::N / 32; ++tn)
+    for (int tn = 0; tn < F::NTN; ++tn)
 #pragma unroll
       for (int r = 0; r < 16; ++r) z[tn][r] = 0.f;
-    const char *lrow = smem + (wave * 32 + ln) * T::OUT_PITCH + h * 16;
-    const char *wfr = smem + F::W_OFF + (h * 8 + ((lane & 15) >> 2)) * F::W_PITCH + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+    const char *lrow = smem + (qw * 32 + ln) * T::OUT_PITCH + h * 16;
+    const char *wfr = smem + F::W_OFF + (h * 8 + ((lane & 15) >> 2)) * F::W_PITCH + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2 + kh * F::NTN * 64;
 #pragma unroll
     for (int ks = 0; ks < T::DLW / 16; ++ks) {
       const bf16x8 xf = *reinterpret_cast<const bf16x8 *>(lrow + ks * 32);
 #pragma unroll
-      for (int tn = 0; tn < F::N / 32; ++tn) {
+      for (int tn = 0; tn < F::NTN; ++tn) {
         const char *wp = wfr + ks * 16 * F::W_PITCH + tn * 64;
         s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp));
         s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 4 * F::W_PITCH));
@@ -495,10 +605,10 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
         *reinterpret_cast<u32x4 *>(smem + (i * GRPP + gr0) * F::G_PITCH + gch * 16) = gt[i];
       __syncthreads();
     }
-    // lane: row wave*32 + ln, columns tn*32 + rq*8 + 4h .. +3
-    char *orow = smem + (wave * 32 + ln) * F::G_PITCH + 4 * h * 2;
+    // lane: row qw*32 + ln, columns (kh*NTN + tn)*32 + rq*8 + 4h .. +3
+    char *orow = smem + (qw * 32 + ln) * F::G_PITCH + 4 * h * 2 + kh * F::NTN * 64;
 #pragma unroll
-    for (int tn = 0; tn < F::N / 32; ++tn)
+    for (int tn = 0; tn < F::NTN; ++tn)
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
         bf16x4 *slot = reinterpret_cast<bf16x4 *>(orow + (tn * 32 + rq * 8) * 2);
@@ -536,24 +646,97 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
   }
 }
 
-typedef AttnTile<128, 256> AttnWide;     // d_h = 128, latent width a multiple of 256
-typedef AttnTile<128, 128> AttnMid;      // d_h = 128, other latent widths that are multiples of 128
-typedef AttnTile<64, 128> AttnNarrow;    // d_h = 64, latent width a multiple of 128
-typedef AttnTile<64, 64> AttnSlim;       // d_h = 64, other latent widths that are multiples of 64 (e.g. the
-                                         // GQA-degenerate setting d_l = d_h used as a comparator)
+// Merge of the key splits of one token (blockIdx.x): thread = 4 columns of one map group; weights exp2(m_s - max) /
+// sum.  A token without any keys (skipped sequence) gets zeros.
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ pacc, const float2 *__restrict__ pml, int splits,
+                                                         int64_t total, int nq, int dl, int ndlc, int dlw, bf16 *__restrict__ L) {
+  const int64_t tok = blockIdx.x;
+  for (int i = threadIdx.x; i < nq * dl / 4; i += 256) {
+    const int col = i * 4, g = col / dl, st = g * ndlc + col % dl / dlw;
+    float mx = -INFINITY;
+    for (int s = 0; s < splits; ++s) mx = fmaxf(mx, pml[(s * total + tok) * (nq * ndlc) + st].x);
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    float ls = 0.f;
+    for (int s = 0; s < splits; ++s) {
+      const float2 ml = pml[(s * total + tok) * (nq * ndlc) + st];
+      if (ml.x > -INFINITY) {
+        const float w = __builtin_amdgcn_exp2f(ml.x - mx);
+        const float4 p = *reinterpret_cast<const float4 *>(pacc + (s * total + tok) * (int64_t)(nq * dl) + col);
+        ls = fmaf(w, ml.y, ls);
+        v.x = fmaf(w, p.x, v.x); v.y = fmaf(w, p.y, v.y); v.z = fmaf(w, p.z, v.z); v.w = fmaf(w, p.w, v.w);
+      }
+    }
+    const float inv = ls > 0.f ? 1.0f / ls : 0.f;
+    bf16x4 o;
+    o[0] = (bf16)(v.x * inv); o[1] = (bf16)(v.y * inv); o[2] = (bf16)(v.z * inv); o[3] = (bf16)(v.w * inv);
+    *reinterpret_cast<bf16x4 *>(L + tok * (nq * dl) + col) = o;
+  }
+}
+
+// latent columns per workgroup
+int latent_tile(const Dims &d) { return d.dh == 128 ? (d.dl % 256 == 0 ? 256 : 128) : (d.dl % 128 == 0 ? 128 : 64); }
 
 template <class T, bool FUSE>
-void launch_attn(const AttnArgs &a0, const Dims &d, int batch, int max_len, hipStream_t st) {
-  AttnArgs a = a0;
+void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t st) {
   a.n_qtiles = (max_len + T::BQ - 1) / T::BQ;
   a.ndlc = d.dl / T::DLW;
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;
   allow_dynamic_lds((const void *)attn_prefill_kernel<T, FUSE>, smem);
-  attn_prefill_kernel<T, FUSE><<<a.n_qtiles * a.ndlc * d.nq * batch, T::NT, smem, st>>>(a);
+  attn_prefill_kernel<T, FUSE><<<a.n_qtiles * a.ndlc * d.nq * batch * a.splits, T::NT, smem, st>>>(a);
+}
+
+constexpr int kSplitTarget = 256;   // workgroups of 128 queries a launch with key splits aims at: one per CU
+
+// max_keys: host bound of a sequence's keys.  part: scratch for key splits (attn_split_bytes) or NULL.
+template <int DH, int DLW, bool FUSE>
+void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys, float *part, hipStream_t st) {
+  // Workgroups of 256 queries.  A workgroup's chain of key tiles (1.3 us each) is what a launch of few workgroups waits
+  // for, so those take 128 queries and two key halves: half the chain, twice the workgroups, at a fifth more per tile
+  // pair and 2 us of merge.  Measured whole calls, 256 against 128 queries, 1B shape: fresh prompts, whose tiles differ
+  // in length, 1 x 500 66 against 60 us, 1 x 4096 231 / 178, 2 x 4096 309 / 272 (256 workgroups), 1 x 128 40.7 / 42.2;
+  // chunks behind cached rows, whose tiles are alike, 8 x 300 behind 4000 228 / 171 (128 workgroups), 8 x 600 behind
+  // 4000 317 / 333 (192: one round against two halves), 8 x 1300 behind 3000 518 / 509; ragged 4 x 1200..2048 behind
+  // 1..3000 343 / 332 (256).  From two rounds on (512) nothing is idle.
+  const int64_t wide = (int64_t)((max_len + 255) / 256) * batch * d.nq * (d.dl / DLW);
+  const bool uneven = !a.prefix || a.total * 10 < (int64_t)batch * max_len * 9;
+  a.splits = 1;
+  if (wide >= (uneven ? 512 : 129) || max_keys <= 256) { launch_tile<AttnTile<DH, DLW, 1>, FUSE>(a, d, batch, max_len, st); return; }
+  const int64_t half = (int64_t)((max_len + 127) / 128) * batch * d.nq * (d.dl / DLW);
+  if (!FUSE && part) {
+    // Still fewer workgroups than CUs: the key range is split over workgroups, too, as long as a split keeps 8 steps
+    // of two tiles (16 for a fresh prompt, whose average tile is half as long).  1 x 40 behind 6000 145 us without,
+    // 80 with up to 23 splits, 67 with 11; 4 x 40 behind 6000 153 / 76; 1 x 2000 fresh 124 / 120.
+    const int64_t most = (int64_t)(max_keys + 31) / 32 / (a.prefix ? 16 : 32);
+    a.splits = (int)(kSplitTarget / half < most ? kSplitTarget / half : most);
+    const int64_t stats = a.total * d.nq * (d.dl / DLW) * 2;   // floats per split
+    while (a.splits > 1 && (size_t)(a.splits * (stats + a.total * d.nq * d.dl) + 64) * 4 > attn_split_bytes(d)) --a.splits;
+    if (a.splits < 1) a.splits = 1;
+    a.pml = reinterpret_cast<float2 *>(part);
+    a.pacc = part + ((a.splits * stats + 63) & ~(int64_t)63);
+  }
+  launch_tile<AttnTile<DH, DLW, 2>, FUSE>(a, d, batch, max_len, st);
+  if (a.splits > 1)
+    attn_merge_kernel<<<(unsigned)a.total, 256, 0, st>>>(a.pacc, a.pml, a.splits, a.total, d.nq, d.dl, d.dl / DLW, DLW, a.L);
+}
+
+template <bool FUSE>
+void launch_attn_any(const AttnArgs &a, const Dims &d, int batch, int max_len, int max_keys, float *part, hipStream_t st) {
+  if constexpr (FUSE) { launch_attn<64, 128, true>(a, d, batch, max_len, max_keys, part, st); return; }
+  const int dlw = latent_tile(d);
+  if (d.dh == 128 && dlw == 256) launch_attn<128, 256, false>(a, d, batch, max_len, max_keys, part, st);
+  else if (d.dh == 128) launch_attn<128, 128, false>(a, d, batch, max_len, max_keys, part, st);
+  else if (dlw == 128) launch_attn<64, 128, false>(a, d, batch, max_len, max_keys, part, st);
+  else launch_attn<64, 64, false>(a, d, batch, max_len, max_keys, part, st);
 }
 
 }  // namespace
+
+// Scratch of the key splits, the same whatever the call's size (so that a workspace sized for many tokens also serves
+// few): kSplitTarget workgroups of 128 rows x one latent tile, and two floats per row and tile.
+size_t attn_split_bytes(const Dims &d) {
+  return (size_t)kSplitTarget * 128 * (latent_tile(d) + 2) * 4 + 4096;
+}
 
 bool attn_prefill_supported(const Dims &d, int max_len) {
   // byte offsets inside one sequence's K / C rows are kept in 32 bits
@@ -569,23 +752,20 @@ static AttnArgs attn_args(const Dims &d, const void *q, const void *k, const voi
   a.cu = cu; a.per_seq = (int)(total / batch);
   a.nq = d.nq; a.qpk = d.qpk; a.qpc = d.qpc; a.wq_w = d.wq_w; a.wk_w = d.wk_w; a.wc_w = d.wc_w; a.dl = d.dl;
   a.scale_log2e = d.scale * 1.4426950408889634f;
-  a.batch = batch;
+  a.batch = batch; a.total = total;
   return a;
 }
 
 void launch_attn_prefill_bf16(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,
-                              int batch, int64_t total, int max_len, void *L, hipStream_t st) {
+                              int batch, int64_t total, int max_len, void *L, float *part, hipStream_t st) {
   AttnArgs a = attn_args(d, q, k, c, cu, batch, total);
   a.L = (bf16 *)L;
-  if (d.dh == 128 && d.dl % 256 == 0) launch_attn<AttnWide, false>(a, d, batch, max_len, st);
-  else if (d.dh == 128) launch_attn<AttnMid, false>(a, d, batch, max_len, st);
-  else if (d.dl % 128 == 0) launch_attn<AttnNarrow, false>(a, d, batch, max_len, st);
-  else launch_attn<AttnSlim, false>(a, d, batch, max_len, st);
+  launch_attn_any<false>(a, d, batch, max_len, max_len, part, st);
 }
 
 // One workgroup covers the whole latent width and the group's heads fill one 256-wide tile
 bool attn_decoder_fusable(const Dims &d, int max_len) {
-  return attn_prefill_supported(d, max_len) && d.dh == 64 && d.dl == AttnNarrow::DLW && d.hpq * d.dh == 256;
+  return attn_prefill_supported(d, max_len) && d.dh == 64 && d.dl == 128 && d.hpq * d.dh == 256;
 }
 
 void launch_attn_decoder_bf16(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,
@@ -594,12 +774,12 @@ void launch_attn_decoder_bf16(const Dims &d, const void *q, const void *k, const
   AttnArgs a = attn_args(d, q, k, c, cu, batch, total);
   a.wp = (const bf16 *)wp; a.gate = d.gate ? (const bf16 *)gate : nullptr; a.out = (bf16 *)out;
   a.hpq = d.hpq; a.dh = d.dh; a.nh = d.nh; a.gate_kind = d.gate;
-  launch_attn<AttnNarrow, true>(a, d, batch, max_len, st);
+  launch_attn_any<true>(a, d, batch, max_len, max_len, nullptr, st);
 }
 
 void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache, const int32_t *slots,
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
-                            void *L, const void *wp, const void *gate, void *out, bool fuse, hipStream_t st) {
+                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part, hipStream_t st) {
   AttnArgs a = attn_args(d, q, cache.k, cache.c, cu, batch, total);
   a.prefix = prefix; a.slots = slots; a.max_seq = cache.max_seq;
   a.pm = page_map_of(cache);
@@ -609,15 +789,9 @@ void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache
   if (fuse) {
     a.wp = (const bf16 *)wp; a.gate = d.gate ? (const bf16 *)gate : nullptr; a.out = (bf16 *)out;
     a.hpq = d.hpq; a.dh = d.dh; a.nh = d.nh; a.gate_kind = d.gate;
-    launch_attn<AttnNarrow, true>(a, d, batch, max_chunk, st);
-  } else if (d.dh == 128 && d.dl % 256 == 0) {
-    launch_attn<AttnWide, false>(a, d, batch, max_chunk, st);
-  } else if (d.dh == 128) {
-    launch_attn<AttnMid, false>(a, d, batch, max_chunk, st);
-  } else if (d.dl % 128 == 0) {
-    launch_attn<AttnNarrow, false>(a, d, batch, max_chunk, st);
+    launch_attn_any<true>(a, d, batch, max_chunk, cache.max_seq, nullptr, st);
   } else {
-    launch_attn<AttnSlim, false>(a, d, batch, max_chunk, st);
+    launch_attn_any<false>(a, d, batch, max_chunk, cache.max_seq, part, st);
   }
 }
 

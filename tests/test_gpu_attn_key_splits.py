@@ -1,0 +1,78 @@
+"""Prefill attention of launches with few workgroups: keys split over the wave halves of a workgroup and over workgroups
+with a merge.  Query tiles of 128 with one row, full and one over; a wave whose first key block lies wholly behind some
+of its queries (cached rows that are no multiple of 32); splits beyond a short sequence's keys; empty, skipped and
+single-token sequences; contiguous and block-table caches; the fused decoder.
+
+Reference: the oracle's functions on the rows the caches hold.  Bounds: the bf16 tolerances of the parity gate, the
+max-abs one scaled by the largest reference value."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as U
+from oracle import gta_oracle as orc
+from paper_2506_17286_amd import binding as B, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {"1b": W.WORKLOADS[1], "paper": W.PAPER_WORKLOADS[0],
+          "mid": W.scaled(W.WORKLOADS[1], n_heads=4, n_qgroups=2, n_kgroups=1, latent_dim=128),
+          "slim": W.scaled(W.PAPER_WORKLOADS[0], n_heads=8, n_qgroups=8, n_kgroups=2, n_cgroups=2, latent_dim=64)}
+
+
+def _setup(shape, tokens):
+    wl = W.scaled(SHAPES[shape], d_model=128, seed=7300)
+    if shape in ("paper", "slim"):
+        wl = W.scaled(wl, d_model=256)
+    rng = W.make_rng(wl)
+    # scores of a few nats, so that the softmax is neither flat nor one-hot
+    w = W.draw_weights(wl, rng, std=wl.d_model ** -0.5)
+    return wl, w, W.draw_hidden(wl, rng, tokens), rng
+
+
+def _check(wl, w, x, k, c, prefix, out, what):
+    """out rows of one sequence against the oracle on its first `prefix` cached rows and its own new rows"""
+    cfg, ow = U.oracle_config(wl), U.oracle_weights(w)
+    n = len(x)
+    pos = np.arange(prefix, prefix + n)
+    Q, K, C, G = orc.project_tokens(cfg, ow, x, pos)
+    K = np.concatenate([k[:prefix].reshape(prefix, wl.n_kgroups, wl.head_dim), K])
+    C = np.concatenate([c[:prefix].reshape(prefix, wl.n_cgroups, wl.latent_dim), C])
+    L = np.empty((n, wl.n_qgroups, wl.latent_dim))
+    for g in range(wl.n_qgroups):
+        L[:, g] = orc.attention_map_rows(cfg, Q[:, g], pos, K[:, cfg.k_of_group(g)]) @ C[:, cfg.c_of_group(g)]
+    ref = orc.decode_heads(cfg, ow, L, G)
+    U.assert_close(out, ref, "bf16", what, max(1.0, float(np.abs(ref).max())))
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("lens", [[129], [128], [1, 300, 31], [257, 0, 160], [2048]], ids=str)
+def test_fresh(shape, lens):
+    wl, w, x, _ = _setup(shape, sum(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "bf16"), x, cu, max_seqlen=max(max(lens), 257)))
+    none = np.zeros((0, 1))
+    for b in range(len(lens)):
+        if lens[b]:
+            _check(wl, w, x[cu[b]:cu[b + 1]], none, none, 0, out[cu[b]:cu[b + 1]], f"{shape} {lens} sequence {b}")
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_chunks_behind_cached_rows(shape, paged):
+    lens, prefix, cap = [1, 33, 128, 70, 129, 40], [1500, 2047, 31, 0, 33, 2300], 2304   # the last one does not fit
+    wl, w, x, rng = _setup(shape, sum(lens))
+    k, c = W.draw_cache(wl, rng, len(lens), cap)
+    if paged:
+        cache = U.PagedDeviceCache(wl, len(lens), 32, cap // 32, seed=4)
+        cache.store(B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    else:
+        cache = U.DeviceCache(wl, len(lens), cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = U.f64(U.run_prefill_chunk(wl, U.upload_weights(w, "bf16"), x, cu, cache))
+    for b in range(len(lens) - 1):
+        _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
+               f"{shape} {lens[b]} behind {prefix[b]}")
+    assert not out[cu[-2]:].any() and cache.status.tolist() == [0] * 5 + [B.GTA_ERR_CACHE_FULL]
+    assert cache.seq_lens.tolist() == [n + p for n, p in zip(lens[:-1], prefix[:-1])] + [prefix[-1]]
