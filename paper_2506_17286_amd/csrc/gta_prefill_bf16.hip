@@ -2,11 +2,15 @@
 // for every map group g, L_g = Softmax(Q_g K_{k(g)}^T / sqrt(d_h)) C_{c(g)}, one shared map per
 // group, output width d_l (normalised, bf16).  The value decoder runs afterwards as a GEMM.
 //
-// One workgroup = 256 queries of one (sequence, group) x up to 256 latent columns; each of its 8 waves
-// (two per SIMD, so one wave's softmax runs in the shadow of the other's MFMAs) owns 32 queries
+// One workgroup = 128 queries of one (sequence, group) x up to 256 latent columns; each of its 4 waves owns 32 queries
 // and the whole column slice (128 accumulator registers): the softmax statistics of a query live
-// in one lane pair and nothing is exchanged between waves.  Wider latents are covered by several
-// workgroups that each recompute the scores.  Both products are computed transposed:
+// in one lane pair and nothing is exchanged between waves.  Two workgroups share a CU (two waves per SIMD, so one
+// wave's softmax runs in the shadow of the other's MFMAs) and are out of step, so that the prologue and the epilogue of
+// one, and the steps in which it waits at its barrier, are filled by the other; measured against one workgroup of
+// eight waves and 256 queries: fused kernel of 4 x 4096 tokens with heads of 64 300 -> 270 us, ragged batch of 112 K
+// tokens 18.9 -> 17.95 ms, 4 x 4096 tokens of the 1B shape 231 -> 225 us (whole calls 780 -> 760, 25.1 -> 24.5 ms, 509
+// -> 503).  Wider latents are covered by several workgroups that each recompute the scores.
+// Both products are computed transposed:
 //   S^T[key][query] = K . Q^T      (row operand: K tile from LDS, column operand: the wave's queries,
 //                                   held in 32 registers for the whole kernel)
 //   L^T[col][query] += C^T . P^T   (row operand: latent tile through the LDS transpose read,
@@ -18,19 +22,19 @@
 // accumulator registers in a rarely taken branch.  In the main loop (blocks entirely below the
 // diagonal) the block maximum is not formed at all: probabilities are taken relative to the maximum
 // the query already has, whatever their size, and only a row sum beyond 2^32 sends the wave through
-// the full step (bf16 probabilities and fp32 sums carry any scale; the final division cancels it).  The lane pair of a query is reduced with v_permlane32_swap, P is packed
-// with v_cvt_pk_bf16_f32 and summed with v_dot2_f32_bf16 (so the row sum is the sum of the rounded
-// values the MFMA sees).
+// the full step (bf16 probabilities and fp32 sums carry any scale; the final division cancels it).  The lane
+// pair of a query is reduced with v_permlane32_swap, P is packed with v_cvt_pk_bf16_f32 and summed with
+// v_dot2_f32_bf16 (so the row sum is the sum of the rounded values the MFMA sees).
 //
-// Key/latent tiles of 32 rows go from memory straight into LDS (buffer_load_dwordx4 .. lds) through five stages, four
-// steps ahead of their use, one barrier per step; measured against staging through registers and LDS writes: 7 % of the
-// kernel at latents of 1024 and 3 % at 512 (ragged batch of 112 K tokens 19.6 -> 18.6 ms, 4 x 4096 tokens 238 -> 230
-// us).  Bound: MFMA issue, the LDS reads of the fragments (1 KiB per MFMA) and the softmax arithmetic share the cycles
+// Key/latent tiles of 32 rows go from memory straight into LDS (buffer_load_dwordx4 .. lds) through five stages (heads of
+// 128: three, what fits twice into the LDS of a CU), all but one of them ahead of their use, one barrier per step;
+// measured against staging through registers and LDS writes: 7 % of the kernel at latents of 1024 and 3 % at 512 (ragged
+// batch of 112 K tokens 19.6 -> 18.6 ms, 4 x 4096 tokens 238 -> 230 us).  Bound: MFMA issue, the LDS reads of the fragments (1 KiB per MFMA) and the softmax arithmetic share the cycles
 // (matrix pipes busy about half of them); latents wider than a tile recompute the scores.  The finished tile is rounded
 // to bf16, parked in LDS in output layout and written with 16-byte stores, 32 lanes per 512-byte row segment.
 //
-// Launches that would leave CUs idle take 128 queries per workgroup and split the keys over the two halves of its waves,
-// and, if that is not enough, over workgroups with a merge kernel (rule and figures at launch_attn).
+// Launches that would leave CUs idle split the keys of a workgroup over two times four waves, and, if that is not
+// enough, over workgroups with a merge kernel (rule and figures at launch_attn).
 #include <math.h>
 
 #include <type_traits>
@@ -51,12 +55,13 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-// KS: key halves.  KS = 1: 256 queries, all eight waves walk the same key tiles.  KS = 2: 128 queries, waves 0-3 take
-// the even key tiles and waves 4-7 the odd ones, each with statistics and accumulators of its own, merged at the end:
-// half the chain of key tiles per workgroup and twice the workgroups, for launches that leave CUs idle.
+// KS: key halves of a workgroup of 128 queries.  KS = 1: four waves walk all key tiles.  KS = 2: waves 0-3 take the even
+// key tiles and waves 4-7 the odd ones, each with statistics and accumulators of its own, merged at the end: half the
+// chain of key tiles per workgroup, for launches that leave CUs idle.
 template <int DH_, int DLW_, int KS_ = 1>
 struct AttnTile {
-  static constexpr int DH = DH_, DLW = DLW_, KS = KS_, BK = 32, NT = 512, QW = 8 / KS, BQ = 32 * QW, NDLB = DLW / 32;
+  static constexpr int DH = DH_, DLW = DLW_, KS = KS_, BK = 32, NDLB = DLW / 32;
+  static constexpr int QW = 4, BQ = 32 * QW, NW = QW * KS, NT = 64 * NW;   // waves per key half, queries, waves, threads
   // A key / latent tile goes straight into LDS, 1 KiB per load instruction in lane order, so rows that one instruction
   // fetches cannot be padded apart; each instruction therefore fetches rows that are not read together:
   //   keys     (16 bytes per lane, 32 rows in a row): instruction a fetches rows a + K_INSTR i and lands 16 bytes
@@ -69,7 +74,7 @@ struct AttnTile {
   static constexpr int K_INSTR = BK * K_ROW / 1024, C_INSTR = BK * C_ROW / 1024, C_RPI = 1024 / C_ROW;
   static constexpr int K_PITCH = 1024 + 16, C_PITCH = 1024 + 64, C_GROUP = 4 * C_PITCH;
   static constexpr int K_BYTES = K_INSTR * K_PITCH, C_BYTES = C_INSTR / 4 * C_GROUP, TILE = K_BYTES + C_BYTES, STAGE = KS * TILE;
-  static constexpr int NSTAGE = KS == 1 ? 5 : 3;
+  static constexpr int NSTAGE = DH == 64 && KS == 1 ? 5 : 3;
   static constexpr int OUT_PITCH = DLW * 2 + 16;
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int MERGE = KS == 1 ? 0 : QW * (NDLB * 16 + 2) * 256;   // the odd half's accumulators and statistics
@@ -77,6 +82,7 @@ struct AttnTile {
   // the hand-scheduled main loop deals 16 softmax slices over 2 * NDLB steps; others take the plain loop
   static constexpr bool PIPELINED = NDLB == 8 || NDLB == 4;
   static_assert((DH == 64 || DH == 128) && (DLW == 64 || DLW == 128 || DLW == 256) && (KS == 1 || KS == 2), "tile");
+  static_assert((K_INSTR >= NW && C_INSTR >= NW) || (KS == 2 && NW == 8), "load instructions of a step divide over the waves");
   static_assert(SMEM <= 160 * 1024, "LDS budget");
   __device__ static constexpr int k_sel(int i) { return K_CPR == 16 ? i & 1 : (i ^ (i >> 1)) & 1; }
   // LDS offset, inside the latent tile, of row 4 a for column 0
@@ -102,8 +108,8 @@ struct AttnArgs {
   int splits; float *pacc; float2 *pml; int64_t total;
 };
 
-// LDS of the fused value decoder: the normalised 256 x DLW tile (row operand) and the DLW x 256
-// decoder matrices of the group's heads side by side; afterwards the 256 x 256 gate / output tile.
+// LDS of the fused value decoder: the normalised BQ x DLW tile (row operand) and the DLW x 256 decoder matrices of the
+// group's heads side by side, in halves where two workgroups share a CU; afterwards the BQ x 256 gate / output tile.
 template <class T>
 struct FusedDecoder {
   static constexpr int N = 256;                         // heads per group x d_h
@@ -111,7 +117,8 @@ struct FusedDecoder {
   static constexpr int W_OFF = T::BQ * T::OUT_PITCH;    // behind the L tile
   static constexpr int NTN = N / 32 / T::KS;            // 32-column tiles per wave: KS waves share 32 queries
   static constexpr int G_PITCH = N * 2 + 16;
-  static constexpr int SMEM_LW = W_OFF + T::DLW * W_PITCH, SMEM_G = T::BQ * G_PITCH;
+  static constexpr int KH = T::KS == 1 ? 2 : 1, KROWS = T::DLW / KH;   // the matrices pass through LDS in KH parts
+  static constexpr int SMEM_LW = W_OFF + KROWS * W_PITCH, SMEM_G = T::BQ * G_PITCH;
   static constexpr int SMEM = SMEM_LW > SMEM_G ? (SMEM_LW > T::SMEM ? SMEM_LW : T::SMEM) : (SMEM_G > T::SMEM ? SMEM_G : T::SMEM);
   static_assert(SMEM <= 160 * 1024, "LDS budget");
 };
@@ -148,7 +155,7 @@ __device__ __forceinline__ int load_uniform(const int32_t *p) {
 }
 
 template <class T, bool FUSE>
-__global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
+__global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
@@ -219,24 +226,26 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  // Tile staging: this wave's load instructions of a tile are `wave` (, + 8) of the keys and of the latents; tiles with
-  // fewer than eight share the waves.  Rows past the sequence read as zeros (such keys are in the future of every
+  // Tile staging: this wave's load instructions of a tile are wave, wave + NW, .. of the keys and of the latents; where
+  // there are fewer than waves (two tiles a step), one half of the waves loads a tile's keys, the other its latents.  Rows past the sequence read as zeros (such keys are in the future of every
   // valid query and are masked, and 0 x 0 adds nothing).
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
-  constexpr int CI = T::C_INSTR >= 8 ? T::C_INSTR / 8 : 1;
+  constexpr int KI = T::K_INSTR >= T::NW ? T::K_INSTR / T::NW : 1, CI = T::C_INSTR >= T::NW ? T::C_INSTR / T::NW : 1;
   const int ki = wave % T::K_INSTR, ci = wave % T::C_INSTR;
-  unsigned kv, cv[CI];
+  unsigned kv[KI], cv[CI];
   {
     const int i = lane / T::K_CPR;
-    kv = (ki + T::K_INSTR * i) * wk2 + ((lane % T::K_CPR) ^ (T::k_sel(i) * (T::K_CPR / 2))) * 16;
+#pragma unroll
+    for (int j = 0; j < KI; ++j)
+      kv[j] = (ki + T::NW * j + T::K_INSTR * i) * wk2 + ((lane % T::K_CPR) ^ (T::k_sel(i) * (T::K_CPR / 2))) * 16;
 #pragma unroll
     for (int j = 0; j < CI; ++j) {
-      const int q = ci + 8 * j;
+      const int q = ci + T::NW * j;
       cv[j] = (4 * (q / 4 * T::C_RPI + lane / T::C_CPR) + q % 4) * wc2 + (lane % T::C_CPR) * 16;
     }
   }
-  auto k_loader = [&](int j) { return T::K_INSTR >= 8 || wave / 4 == (T::KS == 2 ? j : 0); };
-  auto c_loader = [&](int j) { return T::C_INSTR >= 8 || wave / 4 == (T::KS == 2 ? 1 - j : 1); };
+  auto k_loader = [&](int j) { return T::K_INSTR >= T::NW || wave / 4 == j; };        // KS = 2: one tile each
+  auto c_loader = [&](int j) { return T::C_INSTR >= T::NW || wave / 4 == 1 - j; };
   // requests the next step: `fill` is its stage, j_next its first key
   unsigned fill = lds0;
   int j_next = tile0 * T::BK;
@@ -253,11 +262,15 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
         const int64_t row0 = ((int64_t)pg << a.ps_shift) + (jt & (a.pm.page_size - 1));
         kt = Kb + row0 * wk2; ct = Cb + row0 * wc2;
       }
-      if (k_loader(j)) load_to_lds(buffer_of(kt, rows > 0 ? (rows - 1) * wk2 + T::K_ROW : 0u), kv, fill + j * T::TILE + ki * T::K_PITCH);
+      if (k_loader(j)) {
+        const u32x4 r = buffer_of(kt, rows > 0 ? (rows - 1) * wk2 + T::K_ROW : 0u);
+#pragma unroll
+        for (int i = 0; i < KI; ++i) load_to_lds(r, kv[i], fill + j * T::TILE + (ki + T::NW * i) * T::K_PITCH);
+      }
       if (c_loader(j)) {
         const u32x4 r = buffer_of(ct, rows > 0 ? (rows - 1) * wc2 + T::C_ROW : 0u);
 #pragma unroll
-        for (int i = 0; i < CI; ++i) load_to_lds(r, cv[i], fill + j * T::TILE + T::K_BYTES + (ci + 8 * i) * T::C_PITCH);
+        for (int i = 0; i < CI; ++i) load_to_lds(r, cv[i], fill + j * T::TILE + T::K_BYTES + (ci + T::NW * i) * T::C_PITCH);
       }
     }
     j_next += T::KS * T::BK;
@@ -265,13 +278,9 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     fill = fill == lds0 + (T::NSTAGE - 1) * T::STAGE ? lds0 : fill + T::STAGE;
   };
   // load instructions of this wave per step; wait until at most `steps` steps of them are in flight, then meet
-  constexpr int PER_STEP = (T::K_INSTR >= 8 ? T::KS : T::KS == 2 ? 1 : 0) + (T::C_INSTR >= 8 ? CI * T::KS : T::KS == 2 ? 1 : 0);
-  constexpr bool UNEVEN = T::KS == 1 && (T::K_INSTR < 8) != (T::C_INSTR < 8);   // keys by waves 0-3 only, one more each
-  constexpr bool SHARED = T::KS == 1 && T::K_INSTR < 8 && T::C_INSTR < 8;        // every wave loads one or the other
+  constexpr int PER_STEP = (T::K_INSTR >= T::NW ? KI * T::KS : 1) + (T::C_INSTR >= T::NW ? CI * T::KS : 1);
   auto wait_meet = [&](auto steps_tag) {
-    constexpr int N = decltype(steps_tag)::value * (SHARED ? 1 : PER_STEP), N1 = decltype(steps_tag)::value * (PER_STEP + 1);
-    if (UNEVEN && wave < 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N1) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(decltype(steps_tag)::value * PER_STEP) : "memory");
   };
   // fragment addresses inside a stage (of this wave's tile)
   const int ksel = T::k_sel(ln / T::K_INSTR) * (T::K_ROW / 2);
@@ -552,21 +561,28 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     // ---- value decoder on the tile (Sec. 3.2): the workgroup holds the whole latent width of its
     // group, so the heads of the group are finished here and L never goes to memory
     typedef FusedDecoder<T> F;
-    constexpr int WCH = T::DLW * (F::N / 8) / T::NT;     // 16-byte chunks of the decoder matrices per thread
+    constexpr int WCH = F::KROWS * (F::N / 8) / T::NT;   // 16-byte chunks of the decoder matrices per thread and part
     constexpr int GCH = T::BQ * (F::N / 8) / T::NT;      // chunks of the gate / output tile per thread
     const int head0 = g * a.hpq;
     const int64_t ldo = (int64_t)a.nh * a.dh;
     u32x4 wr[WCH];
+    auto w_load = [&](int part) {
 #pragma unroll
-    for (int i = 0; i < WCH; ++i) {
-      const int c = tid + i * T::NT, k = c / (F::N / 8), col = (c % (F::N / 8)) * 8;
-      wr[i] = *reinterpret_cast<const u32x4 *>(a.wp + ((int64_t)(head0 + col / a.dh) * a.dl + k) * a.dh + col % a.dh);
-    }
+      for (int i = 0; i < WCH; ++i) {
+        const int c = tid + i * T::NT, k = part * F::KROWS + c / (F::N / 8), col = (c % (F::N / 8)) * 8;
+        wr[i] = *reinterpret_cast<const u32x4 *>(a.wp + ((int64_t)(head0 + col / a.dh) * a.dl + k) * a.dh + col % a.dh);
+      }
+    };
+    auto w_store = [&]() {
 #pragma unroll
-    for (int i = 0; i < WCH; ++i) {
-      const int c = tid + i * T::NT, k = c / (F::N / 8), col = (c % (F::N / 8)) * 8;
-      *reinterpret_cast<u32x4 *>(smem + F::W_OFF + k * F::W_PITCH + col * 2) = wr[i];
-    }
+      for (int i = 0; i < WCH; ++i) {
+        const int c = tid + i * T::NT, k = c / (F::N / 8), col = (c % (F::N / 8)) * 8;
+        *reinterpret_cast<u32x4 *>(smem + F::W_OFF + k * F::W_PITCH + col * 2) = wr[i];
+      }
+    };
+    w_load(0);
+    w_store();
+    if constexpr (F::KH > 1) w_load(1);
     // gate tile: requested now, parked in LDS once the operands are dead (rows past the sequence
     // re-read its last row; they are not stored)
     const int gr0 = tid / (F::N / 8), gch = tid % (F::N / 8);
@@ -588,10 +604,16 @@ __global__ __launch_bounds__(T::NT) void attn_prefill_kernel(AttnArgs a) {
     const char *wfr = smem + F::W_OFF + (h * 8 + ((lane & 15) >> 2)) * F::W_PITCH + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2 + kh * F::NTN * 64;
 #pragma unroll
     for (int ks = 0; ks < T::DLW / 16; ++ks) {
+      constexpr int KSP = F::KROWS / 16;   // k-steps per part
+      if (F::KH > 1 && ks == KSP) {
+        __syncthreads();
+        w_store();
+        __syncthreads();
+      }
       const bf16x8 xf = *reinterpret_cast<const bf16x8 *>(lrow + ks * 32);
 #pragma unroll
       for (int tn = 0; tn < F::NTN; ++tn) {
-        const char *wp = wfr + ks * 16 * F::W_PITCH + tn * 64;
+        const char *wp = wfr + ks % KSP * 16 * F::W_PITCH + tn * 64;
         s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp));
         s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 4 * F::W_PITCH));
         s16x8 w8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -691,18 +713,20 @@ constexpr int kSplitTarget = 256;   // workgroups of 128 queries a launch with k
 // max_keys: host bound of a sequence's keys.  part: scratch for key splits (attn_split_bytes) or NULL.
 template <int DH, int DLW, bool FUSE>
 void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys, float *part, hipStream_t st) {
-  // Workgroups of 256 queries.  A workgroup's chain of key tiles (1.3 us each) is what a launch of few workgroups waits
-  // for, so those take 128 queries and two key halves: half the chain, twice the workgroups, at a fifth more per tile
-  // pair and 2 us of merge.  Measured whole calls, 256 against 128 queries, 1B shape: fresh prompts, whose tiles differ
-  // in length, 1 x 500 66 against 60 us, 1 x 4096 231 / 178, 2 x 4096 309 / 272 (256 workgroups), 1 x 128 40.7 / 42.2;
-  // chunks behind cached rows, whose tiles are alike, 8 x 300 behind 4000 228 / 171 (128 workgroups), 8 x 600 behind
-  // 4000 317 / 333 (192: one round against two halves), 8 x 1300 behind 3000 518 / 509; ragged 4 x 1200..2048 behind
-  // 1..3000 343 / 332 (256).  From two rounds on (512) nothing is idle.
-  const int64_t wide = (int64_t)((max_len + 255) / 256) * batch * d.nq * (d.dl / DLW);
-  const bool uneven = !a.prefix || a.total * 10 < (int64_t)batch * max_len * 9;
-  a.splits = 1;
-  if (wide >= (uneven ? 512 : 129) || max_keys <= 256) { launch_tile<AttnTile<DH, DLW, 1>, FUSE>(a, d, batch, max_len, st); return; }
+  // Workgroups of 128 queries, all keys walked by four waves, two workgroups per CU.  Launches whose workgroups would
+  // all be on the chip at once (512) only wait for the longest chain of key tiles; there eight waves share a workgroup's
+  // queries in two key halves: half the chain, at 2 us of merge and one workgroup per CU.  Measured whole calls, one
+  // half against two, 1B shape: fresh 1 x 2000 127 against 122 us, 1 x 8192 404 / 360 (512 workgroups), 2 x 4096 281 /
+  // 267 (512), 2 x 3000 ragged 213 / 197 (384), 3 x 4000 373 / 398 (768); chunks 8 x 300 behind 4000 189 / 172 (192),
+  // 8 x 600 behind 4000 290 / 291 (320), 5 x 2000 ragged behind 5000 389 / 421 (640); paper shape 4 x 2048 138 / 125
+  // (256).  Up to 1024 keys the chain is too short for more than one round of the two halves: 8 x 1000 191 / 196 (512),
+  // paper 16 x 700 154 / 160 (384), but 2 x 1000 99 / 91 (64); up to 256 keys it is never worth it: 1 x 128 40.7 / 42.2.
   const int64_t half = (int64_t)((max_len + 127) / 128) * batch * d.nq * (d.dl / DLW);
+  a.splits = 1;
+  if (half > 512 || max_keys <= 256 || (half > 256 && max_keys <= 1024)) {
+    launch_tile<AttnTile<DH, DLW, 1>, FUSE>(a, d, batch, max_len, st);
+    return;
+  }
   if (!FUSE && part) {
     // Still fewer workgroups than CUs: the key range is split over workgroups, too, as long as a split keeps 8 steps
     // of two tiles (16 for a fresh prompt, whose average tile is half as long).  1 x 40 behind 6000 145 us without,

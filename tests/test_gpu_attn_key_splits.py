@@ -1,5 +1,5 @@
-"""Prefill attention of launches with few workgroups: keys split over the wave halves of a workgroup and over workgroups
-with a merge.  Query tiles of 128 with one row, full and one over; a wave whose first key block lies wholly behind some
+"""Prefill attention of launches with few workgroups (keys split over the wave halves of a workgroup and over workgroups
+with a merge) and with many (no split; a loose length bound makes the same sequences such a launch).  Query tiles of 128 with one row, full and one over; a wave whose first key block lies wholly behind some
 of its queries (cached rows that are no multiple of 32); splits beyond a short sequence's keys; empty, skipped and
 single-token sequences; contiguous and block-table caches; the fused decoder.
 
@@ -45,12 +45,13 @@ def _check(wl, w, x, k, c, prefix, out, what):
     U.assert_close(out, ref, "bf16", what, max(1.0, float(np.abs(ref).max())))
 
 
+@pytest.mark.parametrize("bound", [257, 70000])
 @pytest.mark.parametrize("shape", list(SHAPES))
 @pytest.mark.parametrize("lens", [[129], [128], [1, 300, 31], [257, 0, 160], [2048]], ids=str)
-def test_fresh(shape, lens):
+def test_fresh(shape, lens, bound):
     wl, w, x, _ = _setup(shape, sum(lens))
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
-    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "bf16"), x, cu, max_seqlen=max(max(lens), 257)))
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "bf16"), x, cu, max_seqlen=max(max(lens), bound)))
     none = np.zeros((0, 1))
     for b in range(len(lens)):
         if lens[b]:
