@@ -16,6 +16,13 @@ __device__ __forceinline__ void store4(__bf16 *p, f32x4 v) {
   *reinterpret_cast<bf16x4 *>(p) = o;
 }
 
+__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+__device__ __forceinline__ f32x4 load4(const __bf16 *p) {
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  const bf16x4 v = *reinterpret_cast<const bf16x4 *>(p);
+  return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+
 // sin and cos of p * f: the angle is formed and reduced to [-pi/4, pi/4] in fp64 (pi/2 in two parts), then the Taylor
 // series to degree 9 / 10 in fp32 (the first terms left out are below 2e-9 and 2e-10 there) and the quadrant.
 __device__ __forceinline__ void rope_sincos(int p, double f, float &sn, float &cs) {
@@ -41,7 +48,8 @@ __device__ __forceinline__ void rope_sincos(int p, double f, float &sn, float &c
 
 // Projection (Sec. 3.2) with RoPE on q and k (App. B.1.1) and the cache write (App. B.1.3).
 // TD: element type of the Q | K | C | gate rows (a decode step keeps q and gate in fp32), TC: of the caches.
-template <typename TD, typename TC>
+// PREFILL: decode steps do not occur (their sines would be held in registers all the same).
+template <typename TD, typename TC, bool PREFILL = false>
 struct ProjEpi {
   TD *dst[4]; int width[4];                 // Q | K | C | gate rows (decode: K and C go to the caches only)
   int dh, rope;
@@ -51,6 +59,7 @@ struct ProjEpi {
   const int32_t *seq_lens; int32_t *oldlen; double freq[64];
   TC *kcache, *ccache; const int32_t *slots; int max_batch, max_seq; PageMap pm;   // kcache NULL: no cache write
 
+  __device__ __forceinline__ bool decode() const { return !PREFILL && seq_lens; }
   __device__ __forceinline__ void locate(int col, int &seg, int &local) const {
     seg = 0;
     while (seg < 3 && col >= width[seg]) { col -= width[seg]; ++seg; }
@@ -65,7 +74,7 @@ struct ProjEpi {
   struct Ctx { int seg, lc, half; int64_t cr; f32x4 cs, sn; };   // half: distance to the partner (signed), 0 = not rotated
   __device__ __forceinline__ Early early(int row, int col, bool rot) const {
     Early e{};
-    if (seq_lens) {
+    if (decode()) {
       e.slot = slots ? slots[row] : row;
       const bool ok = e.slot >= 0 && e.slot < max_batch;
       e.p = seq_lens[ok ? e.slot : 0];
@@ -86,7 +95,7 @@ struct ProjEpi {
     locate(col, c.seg, c.lc);
     int p = y.p;
     c.cr = -1;
-    if (seq_lens) {
+    if (decode()) {
       if (p >= 0 && p < max_seq) c.cr = cache_row(pm, max_seq, y.slot, p);
       if (col == 0) oldlen[row] = c.cr >= 0 ? p : -1;
       if (c.cr < 0) p = 0;                      // slot full: nothing is appended, the tail zero-fills the sequence
@@ -95,10 +104,10 @@ struct ProjEpi {
       if (slot >= 0 && slot < max_batch && p >= 0 && p < max_seq) c.cr = cache_row(pm, max_seq, slot, p);
     }
     c.half = 0;
-    if (rot && (seq_lens || rope_by_token || p < max_len)) {
+    if (rot && (decode() || rope_by_token || p < max_len)) {
       const int half = dh / 2, e = c.lc % dh, j = e < half ? e : e - half;
       c.half = e < half ? half : -half;
-      if (seq_lens) {
+      if (decode()) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) { float s, t; rope_sincos(p, y.f[i], s, t); c.sn[i] = s; c.cs[i] = t; }
       } else {
@@ -117,15 +126,15 @@ struct ProjEpi {
       for (int i = 0; i < 4; ++i) v[i] = c.half > 0 ? v[i] * c.cs[i] - o[i] * c.sn[i] : v[i] * c.cs[i] + o[i] * c.sn[i];
     }
     const bool cached = c.seg == 1 || c.seg == 2;
-    if (!(seq_lens && cached)) store4(dst[c.seg] + (int64_t)row * width[c.seg] + c.lc, v);
+    if (!(decode() && cached)) store4(dst[c.seg] + (int64_t)row * width[c.seg] + c.lc, v);
     if (c.cr >= 0 && cached) store4((c.seg == 1 ? kcache : ccache) + c.cr * width[c.seg] + c.lc, v);
   }
 };
 
 // Value decoder (Sec. 3.2): times the gate factor of the same element.
-template <typename T>
+template <typename T, typename TG = float>
 struct GateEpi {
-  T *out; const float *g; int ld, gate;
+  T *out; const TG *g; int ld, gate;
   __device__ __forceinline__ bool rotates(int) const { return false; }
   __device__ __forceinline__ int head_dim() const { return 0; }
   struct Early {};
@@ -136,7 +145,7 @@ struct GateEpi {
   __device__ __forceinline__ void store(const Ctx &c, int row, f32x4 v, Partner) const {
     const int64_t o = (int64_t)row * ld + c.col;
     if (gate) {
-      const f32x4 z = *reinterpret_cast<const f32x4 *>(g + o);
+      const f32x4 z = load4(g + o);
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] *= gate == kGateSigmoid ? 1.0f / (1.0f + expf(-z[i])) : gate_factor(gate, z[i]);
     }

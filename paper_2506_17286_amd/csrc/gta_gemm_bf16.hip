@@ -12,11 +12,10 @@
 // output row, which makes the RoPE pairing (j, j + d_h/2) lane-local.
 //
 // Workgroup tile BM x BN x BK with WGM x WGN waves of 32x32x16 MFMA tiles.  The 256 x 256 x 64 tiles
-// (one wave of 128 x 128 per SIMD) run the hand-pipelined main loop below: two LDS stages, global
-// loads two tiles ahead of the LDS writes in two register sets, one barrier per k-tile; their result
+// run the hand-pipelined main loop below (operands straight into LDS, four stages); their result
 // is rounded to bf16, parked in LDS in output layout and written with 16-byte row-contiguous stores.
-// The small tiles (64-row tiles of short prefills and of the decode step) take the plain two-stage
-// loop and store straight from the accumulator layout.
+// The small tiles (split-K projection of the decode step) take the plain two-stage loop and store straight from the
+// accumulator layout.  Short prefills take the kernels for few rows (short_gemm_ok).
 #include <math.h>
 
 #include <type_traits>
@@ -25,7 +24,6 @@
 
 namespace gta {
 namespace {
-
 typedef __bf16 bf16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -885,70 +883,12 @@ __global__ __launch_bounds__(T::NT) void skinny_proj_kernel(SkinnyArgs a) {
   }
 }
 
-// Short prefill (few hundred tokens): the 256 x 256 tiles would leave most CUs idle, so the projection
-// runs as the split-K kernel above and this kernel finishes it: sums the partials, rotates q and k
-// (App. B.1.1), rounds to bf16 and stores Q | K | C | gate rows and the cache rows (App. B.1.3).
-// One thread per (token, 8 columns); a chunk never straddles the two halves of a head.
-__global__ __launch_bounds__(256) void proj_small_finalize_kernel(ProjArgs a, const float *__restrict__ part, int ks) {
-  const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2], wtot = b3 + a.width[3];
-  const int cpr = wtot / 8;
-  const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)a.M * cpr) return;
-  const int m = (int)(idx / cpr), gcol = (int)(idx % cpr) * 8;
-  const int seg = (gcol >= b1) + (gcol >= b2) + (gcol >= b3);
-  const int lcol = gcol - (seg == 0 ? 0 : seg == 1 ? b1 : seg == 2 ? b2 : b3);
-  const int64_t pstride = (int64_t)a.M * wtot;
-  auto sum8 = [&](int col, float (&v)[8]) {
-    const float *p = part + (int64_t)m * wtot + col;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = 0.f;
-    for (int s = 0; s < ks; ++s) {
-      const float4 x0 = *reinterpret_cast<const float4 *>(p + s * pstride), x1 = *reinterpret_cast<const float4 *>(p + s * pstride + 4);
-      v[0] += x0.x; v[1] += x0.y; v[2] += x0.z; v[3] += x0.w; v[4] += x1.x; v[5] += x1.y; v[6] += x1.z; v[7] += x1.w;
-    }
-  };
-  float v[8];
-  sum8(gcol, v);
-  const int p = a.pos[m];
-  if (a.rope && seg < 2) {
-    const int half = a.dh / 2, e = lcol % a.dh, lo = e < half;
-    float o[8];
-    sum8(lo ? gcol + half : gcol - half, o);
-    const int row = a.rope_by_token ? m : max(min(p, a.max_len - 1), 0);
-    const float2 *t = a.rope + (int64_t)row * half + e % half;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = lo ? v[i] * t[i].x - o[i] * t[i].y : v[i] * t[i].x + o[i] * t[i].y;
-  }
-  u32x4 w;
-  {
-    const bf16x4 a0 = pack4(v[0], v[1], v[2], v[3]), a1 = pack4(v[4], v[5], v[6], v[7]);
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    const u32x2 r0 = __builtin_bit_cast(u32x2, a0);
-    const u32x2 r1 = __builtin_bit_cast(u32x2, a1);
-    w = u32x4{r0[0], r0[1], r1[0], r1[1]};
-  }
-  const int width = a.width[seg];
-  *reinterpret_cast<u32x4 *>(a.dst[seg] + (int64_t)m * width + lcol) = w;
-  if (a.kcache && (seg == 1 || seg == 2)) {
-    const int b = a.seq_id[m];
-    const int slot = a.slots ? a.slots[b] : b;
-    if (slot >= 0 && slot < a.max_batch && p >= 0 && p < a.max_seq) {
-      const int64_t cr = cache_row(a.pm, a.max_seq, slot, p);
-      if (cr >= 0) *reinterpret_cast<u32x4 *>((seg == 1 ? a.kcache : a.ccache) + cr * width + lcol) = w;
-    }
-  }
-}
-
 typedef GemmTile<32, 128, 64, 1, 4> TileSkinny32;
 typedef GemmTile<64, 128, 64, 1, 4> TileSkinny64;
 typedef GemmTile<32, 64, 64, 1, 2> TileSkinny32N64;   // 64-wide tiles for widths that are not multiples of 128
 typedef GemmTile<64, 64, 64, 2, 2> TileSkinny64N64;
 
-#ifdef W4
-typedef GemmTile<256, 256, 64, 2, 2> TileBig;
-#else
 typedef GemmTile<256, 256, 64, 4, 2> TileBig;    // eight waves, wave tile 64(m) x 128(n)
-#endif
 typedef GemmTile<256, 256, 64, 2, 2> TileBig4;   // four waves of 128 x 128 (plain main loop)
 typedef GemmTile<256, 128, 64, 4, 1> TileHead;   // one 128-wide head per workgroup, wave tile 64(m) x 128(n)
 typedef GemmTile<256, 64, 64, 4, 1> TileHead64;  // one 64-wide head per workgroup, wave tile 64(m) x 64(n)
@@ -994,32 +934,14 @@ size_t proj_packed_bytes(const Dims &d) {
   return d.dtype == GTA_BF16 && !proj_direct_big(d) && proj_packed_ok(d) ? (size_t)d.H * proj_packed_width(d) * 2 : 0;
 }
 
-static bool skinny_wide_tiles(const Dims &d);
 
-// Short prefill: split-K projection on 64-row tiles plus a finalize kernel, as long as the 256-row tiles
-// would fill at most half of the CUs (and up to 4096 tokens).  Measured, whole calls: 1B shape (20 column
-// tiles) 1280 tokens 125 us against 147 us, 1536 tokens 140 against 158, 3072 tokens 244 against 220;
-// the paper's layer (7 column tiles) 2048 tokens 110 against 127, 4096 tokens equal; the 8 x 128 + 1024
-// shape (28 column tiles) 1500 tokens 256 against 216; the projection alone at the 1B shape: 128 tokens
-// 11 us against 55 us, 1024 tokens 34 against 61.
-static int proj_small_max_tokens(const Dims &d) {
-  const int col_tiles = (d.wtot + 255) / 256;
-  const int m = 128 / col_tiles * 256;
-  return m < 4096 ? m : 4096;
-}
-
-int proj_small_ksplit(const Dims &d, int64_t M) {
-  if (!gemm_shapes_supported(d) || M <= 0 || M > proj_small_max_tokens(d)) return 0;
-  return skinny_ksplit(d, (int)M);
-}
-
-// Rows of fp32 partials [ksplit * M, W_tot] the short path needs at most, whatever M is:
-// ksplit <= 768 / tiles + 1 with tiles = n_tiles * ceil(M / 64).
-size_t proj_small_rows_bound(const Dims &d) {
-  if (!gemm_shapes_supported(d)) return 0;
-  const int ntn = d.wtot / (skinny_wide_tiles(d) ? 128 : 64);
-  return (size_t)(768 * 64 / ntn + proj_small_max_tokens(d));
-}
+// Up to one and a half rounds of 64 x 128 tiles (512 are on the chip at once) the tiles that split K over their waves
+// are ahead of the 256 x 256 ones, which would be too few; measured whole calls, 64-row against 256-row tiles:
+// projection of the 1B shape 1700 tokens 94 against 104 us (756 tiles), 1900 109 / 110 (840), 2300 126 / 124 (1008); the
+// 8 x 128 + 1024 shape 800 tokens 104 / 125 (728), 1000 127 / 130 (896); the paper's layer 3200 tokens 78 / 81 (700),
+// 4000 97 / 90 (882).  Value decoder of the 1B shape 3000 tokens 137.7 / 138.8 (752), 4000 169.8 / 167.4 (1008).  W_O of
+// the paper's layer 4000 tokens 97 / 101 (630), 5600 100.6 / 97.7 (880).
+static bool short_gemm_ok(int M, int N) { return (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= 768; }
 
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
                       const gta_cache *cache, const int32_t *slots, int max_len, hipStream_t st, bool rope_by_token) {
@@ -1037,12 +959,7 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
     a.max_batch = cache->max_batch; a.max_seq = cache->max_seq;
     a.pm = page_map_of(*cache);
   }
-  if (const int ks = proj_small_ksplit(d, M)) {
-    launch_skinny_proj(d, w, x, M, ws.praw, ks, st);
-    const int64_t chunks = (int64_t)M * (d.wtot / 8);
-    proj_small_finalize_kernel<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(a, ws.praw, ks);
-    return;
-  }
+  if (short_gemm_ok(M, d.wtot)) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, st); return; }
   if (proj_direct_big(d)) {
     const int nt = (d.wtot / 256) * ((M + 255) / 256);
     launch<TileBig>(proj_gemm_kernel<TileBig>, a, nt, st);
@@ -1101,11 +1018,7 @@ void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const voi
   a.L = (const bf16 *)L; a.ldl = (int64_t)d.nq * d.dl; a.M = M;
   a.wp = (const bf16 *)wp; a.dl = d.dl; a.dh = d.dh; a.hpq = d.hpq; a.nh = d.nh;
   a.g = (const bf16 *)g; a.gate = d.gate; a.out = (bf16 *)out;
-  if ((M <= 1024 || proj_small_ksplit(d, M)) && (d.dh == 64 || d.dh == 128)) {   // short prefill: 64-row tiles, one head (or half of one) each
-    if (d.dh == 128) launch<TileSkinny64>(decoder_gemm_kernel<TileSkinny64>, a, d.nh * ((M + 63) / 64), st);
-    else launch<TileSkinny64N64>(decoder_gemm_kernel<TileSkinny64N64>, a, d.nh * ((M + 63) / 64), st);
-    return;
-  }
+  if (short_gemm_ok(M, d.nh * d.dh)) { launch_short_decoder(d, L, wp, g, out, M, st); return; }
   if (d.dh == 128 && d.hpq % 2 == 0 && d.dl % 128 == 0 && d.dl >= 256) {
     if (d.gate) launch<TileBig>(decoder_pair_kernel<TileBig, true>, a, (d.nh / 2) * ((M + 255) / 256), st);
     else launch<TileBig>(decoder_pair_kernel<TileBig, false>, a, (d.nh / 2) * ((M + 255) / 256), st);
@@ -1130,10 +1043,7 @@ void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const vo
     launch_rows_plain(A, lda, M, N, K, B, C, st);
     return;
   }
-  if (M <= 1024 && N % 128 == 0) {   // short prefill: 64-row tiles
-    launch<TileSkinny64>(plain_gemm_kernel<TileSkinny64>, a, (N / 128) * ((M + 63) / 64), st);
-    return;
-  }
+  if (short_gemm_ok(M, N)) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
   if (N % 256 == 0 && K % 128 == 0 && K >= 256) launch<TileBig>(plain_gemm_kernel<TileBig>, a, (N / 256) * ((M + 255) / 256), st);
   else launch<TileHead>(plain_gemm_kernel<TileHead>, a, (N / 128) * ((M + 255) / 256), st);
 }

@@ -1,7 +1,7 @@
 // bf16 GEMMs for few rows (a decode step's new tokens, short prompts) for gfx950: K split over the waves of a
-// workgroup.
+// workgroup.  Up to about one 32 x 32 tile per CU gemm_rows_bf16_kernel, beyond that gemm_mid_bf16_kernel below.
 //
-// Tile of 32 rows x 32 columns; each of the W waves takes every W-th chunk of 16 k: the row operand is read
+// gemm_rows: tile of 32 rows x 32 columns; each of the W waves takes every W-th chunk of 16 k: the row operand is read
 // straight into MFMA layout (16 bytes per lane), the weight chunk (16 k x 32 columns, 16 bytes per lane) passes
 // through a slot of LDS that only its wave touches and comes back through the transpose read, so there is no
 // barrier before the sums; the loads of U chunks are in flight at once.  The W partial tiles are summed through LDS
@@ -105,6 +105,173 @@ void launch_rows(const RowsOperands &g, int cols, const Epi &epi, hipStream_t st
   gemm_rows_bf16_kernel<W, Epi><<<(cols / 32) * ((g.M + 31) / 32), 64 * W, SMEM, st>>>(g, epi);
 }
 
+// ---- tiles of 64 rows -----------------------------------------------------------------------------
+// Tile of 64 rows x 128 (64) columns, contraction in stages of 64; wave = 64 x 64 outputs x a quarter of every stage.
+// Both operands go from memory straight into LDS (buffer_load_dwordx4 .. lds) through three stages, two steps ahead of
+// their use, one barrier per step; 72 (48) KiB, so two (three) workgroups share a CU and one's barrier is filled by the
+// other.  The four partial tiles are summed through LDS in a fixed order and go to the epilogue finished, four columns
+// per thread: no fp32 partials in memory and no second kernel.
+// LDS layout (a load fills 1 KiB in lane order, so lanes fetch the 16-byte chunk that belongs in their slot): X rows are
+// 8 chunks, chunk c of row r in slot c ^ (r % 8) ^ (r / 8 % 2), so 8 (16) rows in a row read one logical chunk from
+// different 16-byte columns of 128 (256) bytes; weight rows of 16 (8) chunks, chunk c of k-row k in slot c ^ 4 (k % 4)
+// (c ^ 4 (k / 2 % 2)), so the four k-rows of a transpose read lie in different 64-byte columns.
+// Bound: the loads (786 KiB per tile at K = 2048, of which a CU takes 64 bytes per clock) and, with one tile per CU, the
+// read-MFMA chain of a step.  Measured against a split-K projection with fp32 partials in memory plus a finishing kernel
+// and two-stage 64-row tiles for decoder and W_O, whole calls: 1B shape 500 tokens 60.7 -> 47.9 us, 1000 82 -> 66, 1500
+// 105 -> 88; paper's layer 500 tokens 55 -> 43, 2000 84 -> 67; 8 x 128 + 1024 shape 1000 tokens 169 -> 130 us.  Four
+// stages (one workgroup per CU) gain 1 % up to one tile per CU and lose 10 to 18 % beyond.
+struct MidOperands { RowsOperands g; int hpq; };   // hpq > 0: value decoder, one matrix [K, BN] per head and hpq heads per row operand
+
+template <int BN_>
+struct MidTile {
+  static constexpr int BN = BN_, BM = 64, BK = 64, KG = 4, NH = BN / 64, NW = KG * NH, NT = 64 * NW, NSTAGE = 3;
+  static constexpr int X_BYTES = BM * BK * 2, STAGE = X_BYTES + BK * BN * 2;
+  static constexpr int XL = X_BYTES / 1024 / NW, WL = BK * BN * 2 / 1024 / NW;   // load instructions per wave and stage
+  static constexpr int PITCH = BN + 4, RED = BM * PITCH * 4;                     // a partial tile in LDS (fp32)
+  static constexpr int SMEM = NSTAGE * STAGE > 2 * RED ? NSTAGE * STAGE : 2 * RED;
+};
+
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff));
+}
+__device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {   // reads past `bytes` return 0
+  const uint64_t b = (uint64_t)base;
+  return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+
+template <int BN, class Epi>
+__global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOperands o, Epi epi) {
+  typedef MidTile<BN> T;
+  const RowsOperands &g = o.g;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nh = wave % T::NH, kg = wave / T::NH;
+  const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  const int ntm = (g.M + T::BM - 1) / T::BM, nt = at / ntm, m0 = at % ntm * T::BM;
+  int seg = 0, col = nt * BN;
+  const bf16 *A = g.A + (int64_t)m0 * g.lda, *B;
+  if (o.hpq) { A += (int64_t)(nt / o.hpq) * g.K; B = g.B[0] + (int64_t)nt * g.K * BN; }
+  else {
+    while (seg < 3 && col >= g.cols[seg]) { col -= g.cols[seg]; ++seg; }
+    B = g.B[seg] + col;
+  }
+  const int ldb = o.hpq ? BN : g.cols[seg];
+  const int rv = min(g.M - m0, T::BM);
+  // what this thread finishes: four columns of rows frow + 16 i
+  const int frow = tid / (BN / 4), fc = tid % (BN / 4) * 4, fcol = nt * BN + fc;
+  const bool rot = epi.rotates(nt * BN);
+  typename Epi::Early early[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) early[i] = epi.early(m0 + min(frow + 16 * i, rv - 1), fcol, rot);
+
+  unsigned xv[T::XL], wv[T::WL];
+#pragma unroll
+  for (int j = 0; j < T::XL; ++j) {
+    const int r = (wave + T::NW * j) * 8 + (lane >> 3);
+    xv[j] = (unsigned)(min(r, rv - 1) * g.lda * 2) + ((lane & 7) ^ (r & 7) ^ ((r >> 3) & 1)) * 16;
+  }
+#pragma unroll
+  for (int j = 0; j < T::WL; ++j) {
+    constexpr int CPR = BN / 8;
+    const int k = (wave + T::NW * j) * (64 / CPR) + lane / CPR, sw = BN == 128 ? (k & 3) << 2 : (k & 2) << 1;
+    wv[j] = (unsigned)(k * ldb * 2) + ((lane % CPR) ^ sw) * 16;
+  }
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+  const u32x4 xr = buffer_of(A, (unsigned)((rv - 1) * g.lda * 2) + (unsigned)g.K * 2u);
+  const char *wbase = reinterpret_cast<const char *>(B);   // of the stage that is requested next
+  const unsigned wbytes = (unsigned)((T::BK - 1) * ldb * 2 + BN * 2);
+  const int nk = g.K / T::BK;
+  unsigned fill = 0, xs = 0;   // LDS offset and k offset of the stage that is requested next
+  auto request = [&] {
+#pragma unroll
+    for (int j = 0; j < T::XL; ++j) load_to_lds(xr, xv[j], xs, lds0 + fill + (wave + T::NW * j) * 1024);
+    const u32x4 wr = buffer_of(wbase, wbytes);
+#pragma unroll
+    for (int j = 0; j < T::WL; ++j) load_to_lds(wr, wv[j], 0u, lds0 + fill + T::X_BYTES + (wave + T::NW * j) * 1024);
+    xs += T::BK * 2;
+    wbase += (int64_t)T::BK * ldb * 2;
+    fill = fill == (T::NSTAGE - 1) * T::STAGE ? 0u : fill + T::STAGE;
+  };
+  const int xo = ln * 128 + ((kg * 2 + h) ^ (ln & 7) ^ ((ln >> 3) & 1)) * 16;
+  const int wq = (lane & 15) >> 2, sw = BN == 128 ? wq << 2 : (wq & 2) << 1;
+  int wo[2];
+#pragma unroll
+  for (int tn = 0; tn < 2; ++tn)
+    wo[tn] = T::X_BYTES + (kg * 16 + h * 8 + wq) * BN * 2 +
+             ((nh * 8 + tn * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ sw) * 16 + (lane & 1) * 8;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][0][r] = acc[0][1][r] = acc[1][0][r] = acc[1][1][r] = 0.f;
+  __builtin_amdgcn_sched_barrier(0);
+  for (int t = 0; t < T::NSTAGE - 1 && t < nk; ++t) request();
+  int cur = 0;
+#pragma unroll 1
+  for (int t = 0; t < nk; ++t) {
+    if (t + T::NSTAGE - 1 <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((T::NSTAGE - 2) * (T::XL + T::WL)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const char *st = smem + cur;
+    cur = cur == (T::NSTAGE - 1) * T::STAGE ? 0 : cur + T::STAGE;
+    s16x4 lo[2], hi[2];
+    bf16x8 x[2];
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn) {
+      lo[tn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn]));
+      hi[tn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn] + 4 * BN * 2));
+      x[tn] = *reinterpret_cast<const bf16x8 *>(st + xo + tn * 32 * 128);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + T::NSTAGE - 1 < nk) request();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+      for (int tm = 0; tm < 2; ++tm) {
+        const s16x8 w8 = __builtin_shufflevector(lo[tn], hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
+        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), x[tm], acc[tn][tm], 0, 0, 0);
+      }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every wave is done with the stages
+  float *mine = reinterpret_cast<float *>(smem + (kg >> 1) * T::RED) + ln * T::PITCH + nh * 64 + 4 * h;
+  auto exchange = [&](bool add) {
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+      for (int tm = 0; tm < 2; ++tm)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          f32x4 *q = reinterpret_cast<f32x4 *>(mine + tm * 32 * T::PITCH + tn * 32 + rq * 8);
+          f32x4 v{acc[tn][tm][rq * 4], acc[tn][tm][rq * 4 + 1], acc[tn][tm][rq * 4 + 2], acc[tn][tm][rq * 4 + 3]};
+          if (add) v += *q;
+          *q = v;
+        }
+  };
+  if (kg & 1) exchange(false);
+  __syncthreads();
+  if (!(kg & 1)) exchange(true);
+  __builtin_amdgcn_sched_barrier(0);
+  typename Epi::Ctx ctx[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ctx[i] = epi.prepare(early[i], m0 + min(frow + 16 * i, rv - 1), fcol, rot);
+  __syncthreads();
+  const float *red = reinterpret_cast<const float *>(smem);
+  auto sum4 = [&](int row, int c) {
+    const float *q = red + row * T::PITCH + c;
+    return *reinterpret_cast<const f32x4 *>(q) + *reinterpret_cast<const f32x4 *>(q + T::RED / 4);
+  };
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = frow + 16 * i;
+    if (row < rv) epi.store(ctx[i], m0 + row, sum4(row, fc), [&](int off) { return sum4(row, fc + off); });
+  }
+}
+
+template <int BN, class Epi>
+void launch_mid(const MidOperands &o, int cols, const Epi &epi, hipStream_t st) {
+  typedef MidTile<BN> T;
+  allow_dynamic_lds((const void *)gemm_mid_bf16_kernel<BN, Epi>, T::SMEM);
+  gemm_mid_bf16_kernel<BN, Epi><<<(cols / BN) * ((o.g.M + T::BM - 1) / T::BM), T::NT, T::SMEM, st>>>(o, epi);
+}
+
 }  // namespace
 
 // Widths in units of 32 (a tile lies in one of Q, K, C, gate), heads of 64 or 128.
@@ -126,6 +293,54 @@ void launch_rows_proj_decode(const Dims &d, const gta_weights &w, const void *x,
   e.kcache = (bf16 *)cache.k; e.ccache = (bf16 *)cache.c; e.slots = slots;
   e.max_batch = cache.max_batch; e.max_seq = cache.max_seq; e.pm = page_map_of(cache);
   launch_rows(g, d.wtot, e, st);
+}
+
+static ProjEpi<bf16, bf16, true> prefill_epi(const Dims &d, const PrefillWs &ws, const gta_cache *cache, const int32_t *slots,
+                                             int max_len, bool rope_by_token) {
+  ProjEpi<bf16, bf16, true> e{};
+  void *dst[4] = {ws.q, ws.k, ws.c, ws.g};
+  const int width[4] = {d.wq_w, d.wk_w, d.wc_w, d.wg_w};
+  for (int i = 0; i < 4; ++i) { e.dst[i] = (bf16 *)dst[i]; e.width[i] = width[i]; }
+  e.dh = d.dh; e.rope = d.rope;
+  e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
+  if (cache) {
+    e.kcache = (bf16 *)cache->k; e.ccache = (bf16 *)cache->c; e.slots = slots;
+    e.max_batch = cache->max_batch; e.max_seq = cache->max_seq; e.pm = page_map_of(*cache);
+  }
+  return e;
+}
+
+// 128 columns per tile once such tiles give every CU one (paper's layer, W_O alone: 3000 tokens 83 -> 77 us at 470 tiles,
+// equal at 320; with 160 and 80 tiles 64 and 128 columns are the same)
+static bool wide_tiles_fill(int M, int N) { return N / 128 * ((M + 63) / 64) >= 256; }
+
+// Prefill of few rows: q (rotated), k (rotated), latents and gate rows in bf16, key and latent rows to the caches.  Widths
+// in units of 64 (heads of 128: of 128), H a multiple of 64.
+void launch_short_proj(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
+                       const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st) {
+  const RowsOperands g{(const bf16 *)x, d.H, M, d.H, {(const bf16 *)w.wq, (const bf16 *)w.wk, (const bf16 *)w.wc, (const bf16 *)w.wg},
+                       {d.wq_w, d.wk_w, d.wc_w, d.wg_w}};
+  const ProjEpi<bf16, bf16, true> e = prefill_epi(d, ws, cache, slots, max_len, rope_by_token);
+  const bool wide = !(d.wq_w % 128 || d.wk_w % 128 || d.wc_w % 128 || d.wg_w % 128);
+  // Measured whole calls, 32-row against 64-row tiles: 1B shape 33 tokens 28.6 / 33.4 us (224 tiles of 32 x 32), 65 38.4
+  // / 36.5 (336); paper's layer 128 tokens 37.2 / 40.4 (224), 256 47.2 / 44.8 (448); 8 x 128 + 1024 48 tokens 54 / 45 (448)
+  if (d.wtot / 32 * ((M + 31) / 32) <= 256) launch_rows(g, d.wtot, e, st);
+  else if (wide && (d.dh == 128 || wide_tiles_fill(M, d.wtot))) launch_mid<128>(MidOperands{g, 0}, d.wtot, e, st);
+  else launch_mid<64>(MidOperands{g, 0}, d.wtot, e, st);
+}
+
+void launch_short_decoder(const Dims &d, const void *L, const void *wp, const void *g, void *out, int M, hipStream_t st) {
+  const MidOperands o{{(const bf16 *)L, (int64_t)d.nq * d.dl, M, d.dl, {(const bf16 *)wp}, {}}, d.hpq};
+  const GateEpi<bf16, bf16> e{(bf16 *)out, (const bf16 *)g, d.nh * d.dh, d.gate};
+  if (d.dh == 128) launch_mid<128>(o, d.nh * 128, e, st);
+  else launch_mid<64>(o, d.nh * 64, e, st);
+}
+
+void launch_short_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st) {
+  const MidOperands o{{(const bf16 *)A, lda, M, K, {(const bf16 *)B}, {N}}, 0};
+  const StoreEpi<bf16> e{(bf16 *)C, N};
+  if (N % 128 == 0 && wide_tiles_fill(M, N)) launch_mid<128>(o, N, e, st);
+  else launch_mid<64>(o, N, e, st);
 }
 
 void launch_rows_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st) {

@@ -31,8 +31,6 @@ void tuned_decode_combine(const Dims &d, const float *part, const int32_t *oldle
 // bf16 MFMA GEMMs (gta_gemm_bf16.hip)
 bool gemm_shapes_supported(const Dims &d);
 size_t proj_packed_bytes(const Dims &d);   // workspace for the packed [H, Wtot] weights, 0 if not used
-int proj_small_ksplit(const Dims &d, int64_t M);   // > 0: M tokens take the short-prefill projection with this split
-size_t proj_small_rows_bound(const Dims &d);       // rows of [.., W_tot] fp32 partials that path needs at most
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
                       const gta_cache *cache, const int32_t *slots, int max_len, hipStream_t st,
                       bool rope_by_token = false);
@@ -63,6 +61,10 @@ void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache
 bool rows_gemm_ok(const Dims &d);
 void launch_rows_proj_decode(const Dims &d, const gta_weights &w, const void *x, int batch, const gta_cache &cache,
                              const int32_t *slots, const DecodeWs &ws, hipStream_t st);
+void launch_short_proj(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
+                       const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st);
+void launch_short_decoder(const Dims &d, const void *L, const void *wp, const void *g, void *out, int M, hipStream_t st);
+void launch_short_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st);
 void launch_rows_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st);
 
 // fp32 MFMA kernels (gta_f32.hip).  They serve the shape-generic entry path where the shape allows; each condition

@@ -1,6 +1,7 @@
-"""The 256 x 256 GEMM tiles (operands loaded straight into LDS, eight waves) at their edges: one valid row in the last
-row tile and full row tiles, the shortest contraction the tiles take (four stages of 32) and lengths that leave the
-stages at each phase, two heads side by side in a weight tile, the packed weights, the gate on and off.
+"""The prefill's GEMMs at the edges of their tiles: the few-row kernel, the 64-row tiles that split K over their waves
+(three stages of 64: contractions of one, two and more) and the 256 x 256 tiles (operands loaded straight into LDS, eight
+waves, four stages of 32).  One valid row in the last row tile and full row tiles, contractions that leave the stages at
+each phase, two heads side by side in a weight tile, the packed weights, the gate on and off.
 
 Reference: float64 on the same bf16 inputs.  Bounds: the bf16 tolerances of the parity gate, the max-abs one scaled by
 the largest reference value (the outputs carry one bf16 rounding, 2^-9 of their size)."""
@@ -26,11 +27,12 @@ def _close(got, ref, what):
 
 
 @pytest.mark.parametrize("gate", [True, False])
-@pytest.mark.parametrize("rows", [4097, 4352])
+@pytest.mark.parametrize("rows", [33, 64, 65, 449, 24832, 24833])
 @pytest.mark.parametrize("wl", [_wl(), _wl(d_model=384, latent_dim=384), _wl(d_model=640, n_heads=8, latent_dim=512),
+                                _wl(d_model=128), _wl(head_dim=64, n_heads=8, n_qgroups=4, latent_dim=64),
                                 _wl(head_dim=64, n_heads=20, n_qgroups=5, n_kgroups=1, latent_dim=128, d_model=256)],
-                         ids=["k256", "k384", "k640", "packed"])
-def test_big_tiles(wl, rows, gate):
+                         ids=["k256", "k384", "k640", "k128", "slim", "packed"])
+def test_prefill_gemms(wl, rows, gate):
     cfg = B.config_of(wl)
     cfg.gate = B.GATE_CODES[gate]
     g = torch.Generator(device="cuda")
