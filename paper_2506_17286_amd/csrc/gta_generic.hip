@@ -37,40 +37,44 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // ------------------------------------------------------------------------------ small kernels
-__device__ __forceinline__ void rowmap_row(const int32_t *cu, int batch, int per_seq, int64_t t, int32_t *seq_id,
-                                           int32_t *pos) {
-  if (!cu) {
-    seq_id[t] = (int32_t)(t / per_seq);
-    pos[t] = (int32_t)(t % per_seq);
-    return;
-  }
+// sequence and place in it of packed token t
+__device__ __forceinline__ void locate_token(const int32_t *cu, int batch, int per_seq, int64_t t, int &b, int &i) {
+  if (!cu) { b = (int)(t / per_seq); i = (int)(t % per_seq); return; }
   int lo = 0, hi = batch;  // largest b with cu[b] <= t
   while (hi - lo > 1) {
     int mid = (lo + hi) >> 1;
     if (cu[mid] <= t) lo = mid; else hi = mid;
   }
-  seq_id[t] = lo;
-  pos[t] = (int32_t)(t - cu[lo]);
+  b = lo; i = (int)(t - cu[lo]);
 }
 
-__global__ void rowmap_kernel(const int32_t *cu, int batch, int64_t total, int per_seq,
-                              int32_t *seq_id, int32_t *pos) {
-  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < total) rowmap_row(cu, batch, per_seq, t, seq_id, pos);
+__device__ __forceinline__ void rowmap_row(const int32_t *cu, int batch, int per_seq, int64_t t, int32_t *seq_id,
+                                           int32_t *pos) {
+  int b, i;
+  locate_token(cu, batch, per_seq, t, b, i);
+  seq_id[t] = b;
+  pos[t] = i;
 }
 
-// (cos, sin) of pos * base^(-2j/d_h), evaluated in fp64 and rounded once to fp32 (App. B.1.1).
-__device__ __forceinline__ void rope_table_entry(float2 *tab, int half, int dh, double base, int64_t i) {
-  int p = (int)(i / half), j = (int)(i % half);
-  double ang = (double)p * pow(base, -2.0 * (double)j / (double)dh);
-  double s, c;
-  sincos(ang, &s, &c);
-  tab[i] = make_float2((float)c, (float)s);
+// (cos, sin) of p * f, evaluated in fp64 and rounded once to fp32 (App. B.1.1): the angle reduced to [-pi/4, pi/4] (pi/2
+// in two parts), then the Taylor series to degree 11 / 12 (the first terms left out are below 1e-11 there) and the quadrant.
+__device__ __forceinline__ float2 rope_cos_sin(int p, double f) {
+  const double ang = (double)p * f, k = rint(ang * 0.6366197723675814);
+  double x = fma(-k, 1.5707963267948966, ang);
+  x = fma(-k, 6.123233995736766e-17, x);
+  const double y = x * x;
+  const double s = fma(x * y, fma(y, fma(y, fma(y, fma(y, -1. / 39916800., 1. / 362880.), -1. / 5040.), 1. / 120.), -1. / 6.), x);
+  const double c = fma(y, fma(y, fma(y, fma(y, fma(y, fma(y, 1. / 479001600., -1. / 3628800.), 1. / 40320.), -1. / 720.), 1. / 24.), -0.5), 1.);
+  const int q = (int)(k - 4.0 * floor(k * 0.25));   // quadrant 0 .. 3
+  const float a = (float)(q & 1 ? c : s), b = (float)(q & 1 ? s : c);
+  return make_float2((q + 1) & 2 ? -b : b, q & 2 ? -a : a);
 }
 
-__global__ void rope_table_kernel(float2 *tab, int max_pos, int half, int dh, double base) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < (int64_t)max_pos * half) rope_table_entry(tab, half, dh, base, i);
+// Frequencies base^(-2j/d_h) of the RoPE table's columns in LDS: one power per column and workgroup instead of one per
+// entry.
+__device__ __forceinline__ void rope_freqs(double *f, int half, int dh, double base) {
+  for (int j = threadIdx.x; j < half; j += blockDim.x) f[j] = pow(base, -2.0 * (double)j / (double)dh);
+  __syncthreads();
 }
 
 // ------------------------------------------------------------------------------ generic GEMM
@@ -197,17 +201,25 @@ __global__ void finalize_prefill_kernel(Dims d, const float *praw, const int32_t
   }
 }
 
+// Do rows [r0, r1) of a slot all have pages?  A wave looks at 64 table entries at a time (one thread walking them waits
+// for each: 32 pages of 64 rows took 10 us).
+__device__ __forceinline__ bool rows_backed_wave(const PageMap &pm, int slot, int r0, int r1) {
+  if (!pm.table || r1 <= r0) return true;
+  const int32_t *t = pm.table + (int64_t)slot * pm.pages_per_slot;
+  bool bad = false;
+  for (int i = r0 / pm.page_size + (int)(threadIdx.x & 63); i <= (r1 - 1) / pm.page_size; i += 64) bad |= t[i] < 0 || t[i] >= pm.num_pages;
+  return !__any(bad);
+}
+
+// one wave per sequence
 __device__ __forceinline__ void prefill_commit_seq(const CacheView &cv, const int32_t *cu, int per_seq, int b) {
   int n = cu ? cu[b + 1] - cu[b] : per_seq;
   int slot = cv.slots ? cv.slots[b] : b;
   if (slot < 0 || slot >= cv.max_batch) return;
-  if (n <= cv.max_seq && rows_backed(cv.pm, slot, 0, n)) cv.seq_lens[slot] = n;
+  const bool ok = n <= cv.max_seq && rows_backed_wave(cv.pm, slot, 0, n);
+  if (threadIdx.x & 63) return;
+  if (ok) cv.seq_lens[slot] = n;
   else cv.status[slot] = GTA_ERR_CACHE_FULL;
-}
-
-__global__ void prefill_commit_kernel(CacheView cv, const int32_t *cu, int batch, int per_seq) {
-  int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < batch) prefill_commit_seq(cv, cu, per_seq, b);
 }
 
 // Everything a prefill call derives from the sequence offsets alone, in one launch: blocks
@@ -215,7 +227,7 @@ __global__ void prefill_commit_kernel(CacheView cv, const int32_t *cu, int batch
 // rest set the cached lengths (nothing below reads the lengths back during the call).
 __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total, int per_seq, int32_t *seq_id,
                                      int32_t *pos, int nb_row, float2 *tab, int max_pos, int half, int dh,
-                                     double base, int nb_rope, CacheView cv) {
+                                     double base, int nb_rope, int rope_rows, CacheView cv) {
   int blk = blockIdx.x;
   if (blk < nb_row) {
     int64_t t = blk * (int64_t)blockDim.x + threadIdx.x;
@@ -224,12 +236,14 @@ __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total
   }
   blk -= nb_row;
   if (blk < nb_rope) {
-    int64_t i = blk * (int64_t)blockDim.x + threadIdx.x;
-    if (i < (int64_t)max_pos * half) rope_table_entry(tab, half, dh, base, i);
+    extern __shared__ double freq[];
+    rope_freqs(freq, half, dh, base);
+    const int p0 = blk * rope_rows, n = min(rope_rows, max_pos - p0) * half;
+    for (int i = threadIdx.x; i < n; i += 256) tab[(int64_t)p0 * half + i] = rope_cos_sin(p0 + i / half, freq[i % half]);
     return;
   }
   blk -= nb_rope;
-  int b = blk * blockDim.x + threadIdx.x;
+  int b = blk * 4 + (threadIdx.x >> 6);
   if (b < batch) prefill_commit_seq(cv, cu, per_seq, b);
 }
 
@@ -238,54 +252,39 @@ __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total
 // the chunk does not fit (the sequence is then skipped: nothing stored, zero output, status flagged at
 // commit).  Token t of sequence b gets position prefix[b] + (t - cu[b]); the RoPE table is per packed
 // token here (row t), since positions of different sequences no longer coincide.  Blocks [0, nb_row):
-// row map, then nb_rope blocks: RoPE rows, last blocks: prefix[].  Nothing in this launch writes the
-// cached lengths, so every block may read them.
+// row map and RoPE rows, tpw tokens per wave; last blocks: prefix[], a wave per sequence.  Nothing
+// in this launch writes the cached lengths, so every wave may read them.  Against a power and a walk of
+// the page table per entry (whole calls): 4 x 1200..2048 behind 3000 on pages of 64 346 -> 337 us, 4 x 900
+// 144.7 -> 140.7; fresh 1 x 8000 on pages of 64 357 -> 345.
 __device__ __forceinline__ int chunk_prefix(const CacheView &cv, const int32_t *cu, int per_seq, int b) {
   const int slot = cv.slots ? cv.slots[b] : b;
   if (slot < 0 || slot >= cv.max_batch) return -1;
   const int old = cv.seq_lens[slot], n = cu ? cu[b + 1] - cu[b] : per_seq;
-  return (old >= 0 && old + n <= cv.max_seq && rows_backed(cv.pm, slot, old, old + n)) ? old : -1;
+  return (old >= 0 && old + n <= cv.max_seq && rows_backed_wave(cv.pm, slot, old, old + n)) ? old : -1;
 }
 
 __global__ void prefill_chunk_setup_kernel(const int32_t *cu, int batch, int64_t total, int per_seq, int32_t *seq_id,
-                                           int32_t *pos, int nb_row, float2 *tab, int half, int dh, double base,
-                                           int nb_rope, CacheView cv, int32_t *prefix) {
+                                           int32_t *pos, int nb_row, int tpw, float2 *tab, int half, int dh,
+                                           double base, CacheView cv, int32_t *prefix) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int blk = blockIdx.x;
-  auto locate = [&](int64_t t, int &b, int &i) {
-    if (!cu) { b = (int)(t / per_seq); i = (int)(t % per_seq); return; }
-    int lo = 0, hi = batch;
-    while (hi - lo > 1) {
-      int mid = (lo + hi) >> 1;
-      if (cu[mid] <= t) lo = mid; else hi = mid;
-    }
-    b = lo; i = (int)(t - cu[lo]);
-  };
   if (blk < nb_row) {
-    int64_t t = blk * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    int b, i;
-    locate(t, b, i);
-    const int pre = chunk_prefix(cv, cu, per_seq, b);
-    seq_id[t] = b;
-    pos[t] = pre < 0 ? -1 : pre + i;
+    extern __shared__ double freq[];
+    rope_freqs(freq, half, dh, base);   // half = 0: no RoPE
+    int b = -1, pre = -1;
+    for (int64_t t = ((int64_t)blk * 4 + wave) * tpw, end = min(t + tpw, total); t < end; ++t) {
+      int now, i;
+      locate_token(cu, batch, per_seq, t, now, i);
+      if (now != b) { b = now; pre = chunk_prefix(cv, cu, per_seq, b); }
+      if (lane == 0) { seq_id[t] = b; pos[t] = pre < 0 ? -1 : pre + i; }
+      for (int j = lane; j < half; j += 64) tab[t * half + j] = rope_cos_sin(pre < 0 ? 0 : pre + i, freq[j]);
+    }
     return;
   }
-  blk -= nb_row;
-  if (blk < nb_rope) {
-    int64_t e = blk * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= total * half) return;
-    int b, i;
-    locate(e / half, b, i);
-    const int pre = chunk_prefix(cv, cu, per_seq, b), j = (int)(e % half);
-    double ang = (double)(pre < 0 ? 0 : pre + i) * pow(base, -2.0 * (double)j / (double)dh);
-    double sn, cs;
-    sincos(ang, &sn, &cs);
-    tab[e] = make_float2((float)cs, (float)sn);
-    return;
-  }
-  blk -= nb_rope;
-  int b = blk * blockDim.x + threadIdx.x;
-  if (b < batch) prefix[b] = chunk_prefix(cv, cu, per_seq, b);
+  const int b = (blk - nb_row) * 4 + wave;
+  if (b >= batch) return;
+  const int pre = chunk_prefix(cv, cu, per_seq, b);
+  if (lane == 0) prefix[b] = pre;
 }
 
 __global__ void prefill_chunk_commit_kernel(CacheView cv, const int32_t *cu, int batch, int per_seq,
@@ -782,31 +781,19 @@ int decode_impl(const Dims &d, const gta_weights &w, const T *x, int batch, cons
 }  // namespace
 
 // ------------------------------------------------------------------------------ exported helpers
-void launch_rowmap(const int32_t *cu, int batch, int64_t total, int32_t *seq_id, int32_t *pos, hipStream_t st) {
-  if (total <= 0) return;
-  rowmap_kernel<<<grid1d(total), 256, 0, st>>>(cu, batch, total, (int)(total / batch), seq_id, pos);
-}
-
-void launch_rope_table(float2 *tab, int max_pos, int dh, double base, hipStream_t st) {
-  const int half = dh / 2;
-  if (max_pos <= 0 || half <= 0) return;
-  rope_table_kernel<<<grid1d((int64_t)max_pos * half), 256, 0, st>>>(tab, max_pos, half, dh, base);
-}
-
-void launch_prefill_commit(const gta_cache &cache, const int32_t *slots, const int32_t *cu, int batch,
-                           int64_t total, hipStream_t st) {
-  prefill_commit_kernel<<<grid1d(batch), 256, 0, st>>>(view_of(&cache, slots), cu, batch, (int)(total / batch));
-}
-
 void launch_prefill_setup(const Dims &d, const int32_t *cu, int batch, int64_t total, int max_len, int32_t *seq_id,
                           int32_t *pos, float2 *tab, const gta_cache *cache, const int32_t *slots, hipStream_t st) {
   if (total <= 0) return;
   const int half = d.dh / 2;
   const int nb_row = (int)((total + 255) / 256);
-  const int nb_rope = d.rope && max_len > 0 && half > 0 ? (int)(((int64_t)max_len * half + 255) / 256) : 0;
-  const int nb_commit = cache ? (batch + 255) / 256 : 0;
-  prefill_setup_kernel<<<nb_row + nb_rope + nb_commit, 256, 0, st>>>(
-      cu, batch, total, (int)(total / batch), seq_id, pos, nb_row, tab, max_len, half, d.dh, d.rope_base, nb_rope,
+  // One table entry per thread up to 256 workgroups, four beyond: a short prompt waits for one chain, a long one for the
+  // powers (fresh prompts of 500 tokens, heads of 128, whole calls: one entry 47.7 us, four 48.4).
+  const bool rope = d.rope && max_len > 0 && half > 0;
+  const int per_row = half > 256 || !rope ? 1 : 256 / half, rows = per_row * ((int64_t)max_len > 256 * per_row ? 4 : 1);
+  const int nb_rope = rope ? (int)(((int64_t)max_len + rows - 1) / rows) : 0;
+  const int nb_commit = cache ? (batch + 3) / 4 : 0;
+  prefill_setup_kernel<<<nb_row + nb_rope + nb_commit, 256, nb_rope ? half * sizeof(double) : 0, st>>>(
+      cu, batch, total, (int)(total / batch), seq_id, pos, nb_row, tab, max_len, half, d.dh, d.rope_base, nb_rope, rows,
       cache ? view_of(cache, slots) : CacheView{});
 }
 
@@ -814,12 +801,10 @@ void launch_prefill_chunk_setup(const Dims &d, const int32_t *cu, int batch, int
                                 int32_t *pos, float2 *tab, int32_t *prefix, const gta_cache &cache,
                                 const int32_t *slots, hipStream_t st) {
   if (total <= 0) return;
-  const int half = d.dh / 2;
-  const int nb_row = (int)((total + 255) / 256);
-  const int nb_rope = d.rope && half > 0 ? (int)((total * half + 255) / 256) : 0;
-  prefill_chunk_setup_kernel<<<nb_row + nb_rope + (batch + 255) / 256, 256, 0, st>>>(
-      cu, batch, total, (int)(total / batch), seq_id, pos, nb_row, tab, half, d.dh, d.rope_base, nb_rope,
-      view_of(&cache, slots), prefix);
+  const int half = d.rope ? d.dh / 2 : 0, tpw = total > 4096 ? 4 : 1, nb_row = (int)((total + 4 * tpw - 1) / (4 * tpw));
+  prefill_chunk_setup_kernel<<<nb_row + (batch + 3) / 4, 256, half * sizeof(double), st>>>(
+      cu, batch, total, (int)(total / batch), seq_id, pos, nb_row, tpw, tab, half, d.dh, d.rope_base, view_of(&cache, slots),
+      prefix);
 }
 
 void launch_prefill_chunk_commit(const gta_cache &cache, const int32_t *slots, const int32_t *cu, int batch,

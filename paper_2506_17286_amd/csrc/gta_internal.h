@@ -159,11 +159,6 @@ void generic_decode_combine(const Dims &d, const float *part, const int32_t *old
 int launch_calibration_copy(const void *src, void *dst, int64_t bytes, hipStream_t st);
 int launch_calibration_read(const void *src, int64_t bytes, int workgroups, void *sink, hipStream_t st);
 int launch_calibration_mfma(int workgroups, int iters, bool random_operands, void *sink, hipStream_t st);
-void launch_rowmap(const int32_t *cu, int batch, int64_t total, int32_t *seq_id, int32_t *pos,
-                   hipStream_t st);
-void launch_rope_table(float2 *tab, int max_pos, int dh, double base, hipStream_t st);
-void launch_prefill_commit(const gta_cache &cache, const int32_t *slots, const int32_t *cu,
-                           int batch, int64_t total, hipStream_t st);
 // chunked prefill: row map with positions behind the cached rows, per-token RoPE rows, prefix[]; commit
 void launch_prefill_chunk_setup(const Dims &d, const int32_t *cu, int batch, int64_t total, int32_t *seq_id,
                                 int32_t *pos, float2 *tab, int32_t *prefix, const gta_cache &cache,

@@ -1,0 +1,29 @@
+"""What a prefill call derives from offsets, lengths and page tables before its GEMMs: sequences of more than 64 pages (a
+wave looks at 64 table entries at a time), a missing page behind the first 64, several tokens per wave.
+
+Reference: the same tokens as a fresh prompt into contiguous caches.  Both calls run the same projection on the same
+bf16 inputs with the same angles, so the cached rows are equal bit by bit."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as U
+from paper_2506_17286_amd import binding as B, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lens,page,chunk", [([2201, 2198, 7], 32, True), ([2201, 2198, 7], 32, False), ([1030, 1030, 7], 16, False)])
+def test_sequences_of_many_pages(lens, page, chunk):
+    wl = W.scaled(W.WORKLOADS[1], d_model=128, n_heads=4, n_qgroups=2, n_kgroups=1, latent_dim=128, seed=9100)
+    rng = W.make_rng(wl)
+    w, x = W.draw_weights(wl, rng, std=wl.d_model ** -0.5), W.draw_hidden(wl, rng, sum(lens))
+    wdev, cu = U.upload_weights(w, "bf16"), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    plain = U.DeviceCache(wl, 3, 2560)
+    U.run_prefill(wl, wdev, x, cu, cache=plain)
+    paged = U.PagedDeviceCache(wl, 3, page, 2560 // page, seed=1, missing=[(1, lens[1] // page)])
+    (U.run_prefill_chunk if chunk else U.run_prefill)(wl, wdev, x, cu, cache=paged)
+    assert paged.seq_lens.tolist() == [lens[0], 0, lens[2]] and paged.status.tolist() == [0, B.GTA_ERR_CACHE_FULL, 0]
+    k, c = paged.logical()
+    for s in (0, 2):
+        assert torch.equal(k[s, :lens[s]], plain.k[s, :lens[s]]) and torch.equal(c[s, :lens[s]], plain.c[s, :lens[s]])
