@@ -48,7 +48,7 @@ TRAFFIC_SOURCE = {
     ("varlen_prefill_bf16", "attn_prefill_kernel"): ("bench_varlen.txt", "attn_prefill_kernel"),
     ("varlen_prefill_bf16", "projection"): ("bench_varlen.txt", "proj_gemm_kernel"),
     ("varlen_prefill_bf16", "decoder"): ("bench_varlen.txt", "decoder_pair_kernel"),
-    ("gta1b_prefill_b32_t2048", "attn_prefill_kernel"): ("bench_paper.txt", "AttnTile<64, 128>"),
+    ("gta1b_prefill_b32_t2048", "attn_prefill_kernel"): ("bench_paper.txt", "AttnTile<64, 128, 1> plain"),
     ("gta1b_decode_b64_t2048", "decode_attn_kernel"): ("bench_paper.txt", "decode_narrow_kernel"),
 }
 
