@@ -27,7 +27,7 @@
 // v_dot2_f32_bf16 (so the row sum is the sum of the rounded values the MFMA sees).
 //
 // Key/latent tiles of 32 rows go from memory straight into LDS (buffer_load_dwordx4 .. lds) through five stages (heads of
-// 128: three, what fits twice into the LDS of a CU), all but one of them ahead of their use, one barrier per step;
+// 128 and latent tiles of 64: three), all but one of them ahead of their use, one barrier per step;
 // measured against staging through registers and LDS writes: 7 % of the kernel at latents of 1024 and 3 % at 512 (ragged
 // batch of 112 K tokens 19.6 -> 18.6 ms, 4 x 4096 tokens 238 -> 230 us).  Bound: MFMA issue, the LDS reads of the fragments (1 KiB per MFMA) and the softmax arithmetic share the cycles
 // (matrix pipes busy about half of them); latents wider than a tile recompute the scores.  The finished tile is rounded
@@ -74,7 +74,9 @@ struct AttnTile {
   static constexpr int K_INSTR = BK * K_ROW / 1024, C_INSTR = BK * C_ROW / 1024, C_RPI = 1024 / C_ROW;
   static constexpr int K_PITCH = 1024 + 16, C_PITCH = 1024 + 64, C_GROUP = 4 * C_PITCH;
   static constexpr int K_BYTES = K_INSTR * K_PITCH, C_BYTES = C_INSTR / 4 * C_GROUP, TILE = K_BYTES + C_BYTES, STAGE = KS * TILE;
-  static constexpr int NSTAGE = DH == 64 && KS == 1 ? 5 : 3;
+  // as many stages as leave room for the workgroups the registers allow on a CU: two (five stages), with latent tiles of
+  // 64 four (three: 32 x 2048 tokens, 20 maps, heads and latents of 64: 509 us with five stages, 482 with three)
+  static constexpr int NSTAGE = DH == 64 && DLW == 128 && KS == 1 ? 5 : 3;
   static constexpr int OUT_PITCH = DLW * 2 + 16;
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int MERGE = KS == 1 ? 0 : QW * (NDLB * 16 + 2) * 256;   // the odd half's accumulators and statistics
