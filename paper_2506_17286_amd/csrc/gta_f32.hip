@@ -235,7 +235,10 @@ __global__ __launch_bounds__(256) void gemm_tiles_f32_kernel(GemmOperands g, int
 // are transposed (S^T = K Q^T, L^T += C^T P^T), so a lane holds one query: the statistics are per lane pair, and
 // the probabilities are the second product's operand as they stand.  Operands come straight from memory: a key
 // row is read 16 bytes per lane, a latent row as 32 lanes x 16 (or 8) bytes, each requested one block ahead into the
-// registers its predecessor has just left.
+// registers its predecessor has just left.  Later tokens never reach earlier rows, whatever they hold: in the block on
+// the diagonal their probability of 0 turns a latent that is not finite into NaN, so a wave whose sums over that block
+// are not finite forms its part again key by key.  (Looked at behind the loop: a test of the block's latents
+// inside it keeps softmax and products from overlapping, 61 us instead of 57 at 4 x 1024 tokens of the paper's layer.)
 struct AttnF32 {
   const float *q, *k, *c; float *L;
   const int32_t *cu; int per_seq, max_len;
@@ -244,7 +247,7 @@ struct AttnF32 {
 };
 
 template <int DH, int DLW>
-__global__ __launch_bounds__(256, DH < 128 ? 2 : 1) void attn_prefill_f32_kernel(AttnF32 a) {
+__global__ __launch_bounds__(256, DH + DLW < 256 ? 2 : 1) void attn_prefill_f32_kernel(AttnF32 a) {
   constexpr int NT = DLW / 32, OP = DLW + 4;
   typedef float cvec __attribute__((ext_vector_type(NT)));
   extern __shared__ __attribute__((aligned(16))) float dyn[];
@@ -329,6 +332,45 @@ __global__ __launch_bounds__(256, DH < 128 ? 2 : 1) void attn_prefill_f32_kernel
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[r][t], s[r], acc[t], 0, 0, 0);
       cload(blk + 4, r);
+    }
+  }
+  // sums of the wave that holds the diagonal not finite: its blocks again, every query on the keys it sees (registers are
+  // scarce here, not time: 24 tokens of NaN behind 1000 in four sequences of the paper's layer 60 -> 400 us)
+  bool finite = true;
+  if (wave == (nblk - 1) % 4) {
+    float z[4] = {};
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z[r % 4] = fmaf(acc[t][r], 0.f, z[r % 4]);
+    finite = __builtin_amdgcn_ballot_w64((z[0] + z[1]) + (z[2] + z[3]) != 0.f) == 0;
+  }
+  if (__builtin_expect(!finite, 0)) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) zero16(acc[t]);
+    m = -INFINITY;
+    l = 0.f;
+    const float *qr = a.q + (start + min(q0 + ln, Tb - 1)) * a.wq_w + g * DH + h * 4;
+#pragma unroll 1
+    for (int j = wave * 32; j < min(q0 + ln + 1, nkeys); j += (j & 31) == 31 ? 97 : 1) {
+      const float *kr = K + (int64_t)j * a.wk_w, *cr = C + (4 * h - ln) * NT + (int64_t)j * a.wc_w;
+      float d = 0.f;
+#pragma unroll 1
+      for (int c = 0; c < DH; c += 8) {
+        const f32x4 k = *reinterpret_cast<const f32x4 *>(kr + c), q = *reinterpret_cast<const f32x4 *>(qr + c);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d = fmaf(k[i], q[i], d);
+      }
+      const float sc = pair_sum(d) * a.scale_log2e, mn = fmaxf(m, sc), ref = mn > -INFINITY ? mn : 0.f;
+      const float corr = __builtin_amdgcn_exp2f(m - ref), p = __builtin_amdgcn_exp2f(sc - ref);
+      m = mn;
+      l = fmaf(l, corr, h == 0 ? p : 0.f);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const cvec c = *reinterpret_cast<const cvec *>(cr + (8 * (r >> 2) + (r & 3)) * NT);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t][r] = fmaf(p, c[t], acc[t][r] * corr);
+      }
     }
   }
   // merge the waves: tile t, register r of a lane is column (8 (r/4) + 4 h + r % 4) * NT + t of its query
