@@ -310,14 +310,14 @@ __global__ __launch_bounds__(256, DH + DLW < 256 ? 2 : 1) void attn_prefill_f32_
 #pragma unroll
     for (int r = 1; r < 16; ++r) bm = fmaxf(bm, s[r]);
     // the running maximum moves only when a block passes it by 2^8 (fp32 probabilities carry any such scale); it
-    // is finite from the first block on: key 0 of a block is never masked for it
-    const float mc = pair_max(bm) * a.scale_log2e, mn = mc > m + 8.f ? mc : m;
-    const float corr = __builtin_amdgcn_exp2f(m - mn);
+    // stays -inf over blocks whose scores have all overflowed to -inf
+    const float mc = pair_max(bm) * a.scale_log2e, mn = mc > m + 8.f ? mc : m, ref = mn > -INFINITY ? mn : 0.f;
+    const float corr = __builtin_amdgcn_exp2f(m - ref);
     m = mn;
     float ps = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], a.scale_log2e, -mn));
+      s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], a.scale_log2e, -ref));
       ps += s[r];
     }
     l = fmaf(l, corr, ps);
@@ -482,13 +482,14 @@ __global__ __launch_bounds__(256, 2) void decode_attn_f32_kernel(DecF32 a) {
     float bm = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
     bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
     bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
-    const float mn = fmaxf(m, bm * a.scale_log2e);   // finite: a step holds at least one valid row
-    const float corr = __builtin_amdgcn_exp2f(m - mn);
+    // -inf as long as all scores have overflowed to -inf
+    const float mn = fmaxf(m, bm * a.scale_log2e), ref = mn > -INFINITY ? mn : 0.f;
+    const float corr = __builtin_amdgcn_exp2f(m - ref);
     m = mn;
     float ps = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], a.scale_log2e, -mn));
+      sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], a.scale_log2e, -ref));
       ps += sc[r];
     }
     l = fmaf(l, corr, ps);                       // this lane's rows only; summed over the lane groups at the end

@@ -1,5 +1,6 @@
 """fp32 prefill and decode on values that are not finite: a token that holds NaN or infinities (uninitialised padding at the
-tail of equal-length sequences) reaches the rows that see it and no earlier one.
+tail of equal-length sequences) reaches the rows that see it and no earlier one; keys whose score overflows to -inf have
+weight 0, also where they fill a whole block.
 
 Reference: float64, every row on the keys it sees only.  Bounds: the fp32 tolerances of the parity gate on what is
 finite there; what is not finite there has to be the same infinity or a NaN."""
@@ -72,3 +73,56 @@ def test_infinite_latents(shape, row):
         with np.errstate(invalid="ignore"):
             ref = np.stack([m[i, :i + 1] @ cg[:i + 1] for i in range(n)])
         _same(got[:, g], ref, f"{shape} group {g}")
+
+
+def _overflowing(groups, width, rows, bad):
+    """q [1, 1, width] and keys [rows, groups, width] whose products are below -FLT_MAX for the rows `bad`, small elsewhere"""
+    rng = np.random.default_rng(rows)
+    k = rng.standard_normal((rows, groups, width)).astype(np.float32) * np.float32(1e-20)
+    k[bad] = -1e20
+    return np.full((1, 1, width), 1e20, dtype=np.float32), k
+
+
+@pytest.mark.parametrize("block", [0, 1, 2, 3])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_prefill_block_of_overflowed_scores(shape, block):
+    wl, n = _wl(shape), 150
+    q, k = _overflowing(wl.n_kgroups, wl.head_dim, n, slice(32 * block, 32 * block + 32))
+    q = np.broadcast_to(q, (n, wl.n_qgroups, wl.head_dim))
+    c = np.random.default_rng(1).standard_normal((n, wl.n_cgroups, wl.latent_dim)).astype(np.float32)
+    cfg, dev = U.oracle_config(wl), [torch.from_numpy(a.reshape(n, -1).copy()).cuda() for a in (q, k, c)]
+    out = torch.empty((n, wl.n_qgroups * wl.latent_dim), device="cuda")
+    B.gta_prefill_attention(B.config_of(wl), *dev, None, 1, n, n, out)
+    got = U.f64(out).reshape(n, wl.n_qgroups, wl.latent_dim)
+    first = 32 if block == 0 else 0                   # rows without any other key are 0 / 0
+    for g in range(wl.n_qgroups):
+        kg, cg = k[:, cfg.k_of_group(g)].astype(np.float64), c[:, cfg.c_of_group(g)].astype(np.float64)
+        ref = orc.attention_map_rows(cfg, q[first:, g].astype(np.float64), np.arange(first, n), kg) @ cg
+        U.assert_close(got[first:, g], ref, "f32", f"{shape} group {g}", max(1.0, float(np.abs(ref).max())))
+
+
+def _decode_stage(wl, q, k, c, splits):
+    """gta_decode_attention and gta_decode_combine on caches that hold k, c [batch, rows, width]"""
+    batch, rows = k.shape[:2]
+    cache = U.DeviceCache(wl, batch, rows, torch.from_numpy(k).cuda(), torch.from_numpy(c).cuda())
+    cache.seq_lens.fill_(rows)
+    cfg = B.config_of(wl)
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, batch, 0, rows, splits))
+    out = torch.empty((batch, wl.n_qgroups, wl.latent_dim), device="cuda")
+    B.gta_decode_attention(cfg, torch.from_numpy(q.reshape(batch, -1).copy()).cuda(), cache.struct, None, batch, splits, ws)
+    B.gta_decode_combine(cfg, cache.struct, None, batch, splits, ws, out)
+    return U.f64(out)
+
+
+@pytest.mark.parametrize("splits", [1, 5, 40])
+@pytest.mark.parametrize("step", [0, 1, 3])
+def test_decode_step_of_overflowed_scores(step, splits):
+    wl, n = _wl("paper"), 300
+    q, k = _overflowing(1, wl.head_dim, n, slice(16 * step, 16 * step + 16))
+    q = np.broadcast_to(q, (1, wl.n_qgroups, wl.head_dim))
+    c = np.random.default_rng(2).standard_normal((n, wl.latent_dim)).astype(np.float32)
+    got = _decode_stage(wl, q, k.reshape(1, n, -1), c[None], splits)
+    cfg = U.oracle_config(wl)
+    for g in range(wl.n_qgroups):
+        ref = orc.attention_map_rows(cfg, q[:, g].astype(np.float64), np.array([n - 1]), k[:, 0].astype(np.float64)) @ c.astype(np.float64)
+        U.assert_close(got[:, g], ref, "f32", f"group {g}", max(1.0, float(np.abs(ref).max())))
