@@ -470,7 +470,7 @@ __global__ __launch_bounds__(256, 2) void decode_attn_f32_kernel(DecF32 a) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[v][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
-  auto compute = [&](const Step &st, int u) {
+  auto compute = [&](Step &st, int u) {
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < KC; ++c)
@@ -479,6 +479,12 @@ __global__ __launch_bounds__(256, 2) void decode_attn_f32_kernel(DecF32 a) {
     const int left = n - u * 16 - 4 * kq;        // valid rows of this lane's four
 #pragma unroll
     for (int r = 0; r < 4; ++r) sc[r] = r < left ? sc[r] : -INFINITY;
+    if (n - u * 16 < 16) {                       // 0 times the last row's infinity would be NaN
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int v = 0; v < NU; ++v) st.c[r][v] = r < left ? st.c[r][v] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     float bm = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
     bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
     bm = fmaxf(bm, __shfl_xor(bm, 32, 64));

@@ -126,3 +126,17 @@ def test_decode_step_of_overflowed_scores(step, splits):
     for g in range(wl.n_qgroups):
         ref = orc.attention_map_rows(cfg, q[:, g].astype(np.float64), np.array([n - 1]), k[:, 0].astype(np.float64)) @ c.astype(np.float64)
         U.assert_close(got[:, g], ref, "f32", f"group {g}", max(1.0, float(np.abs(ref).max())))
+
+
+@pytest.mark.parametrize("splits", [1, 5, 40])
+@pytest.mark.parametrize("n", [1, 15, 16, 33, 300])
+def test_decode_infinite_latent_in_the_newest_row(n, splits):
+    """Rows past the end re-read the newest one with weight 0."""
+    wl, rng = _wl("paper"), np.random.default_rng(n)
+    q, k, c = (rng.standard_normal(s).astype(np.float32) for s in
+               ((1, wl.n_qgroups, wl.head_dim), (1, n, wl.head_dim), (1, n, wl.latent_dim)))
+    c[0, -1, 7], c[0, -1, 100], c[0, 0, 50] = np.inf, -np.inf, np.nan
+    got = _decode_stage(wl, q, k, c, splits)
+    for g in range(wl.n_qgroups):
+        m = orc.attention_map_rows(U.oracle_config(wl), q[:, g].astype(np.float64), np.array([n - 1]), k[0].astype(np.float64))
+        _same(got[:, g], m @ c[0].astype(np.float64), f"{n} rows, group {g}")
