@@ -1190,7 +1190,7 @@ __global__ __launch_bounds__(256) void decode_tail_narrow_kernel(Dims d, const f
     float ls = e * l_s;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);
-    wt[lane / MAXS][lane % MAXS] = ls > 0.f ? e / ls : 0.f;
+    wt[lane / MAXS][lane % MAXS] = e / ls;   // NaN for a sequence without rows, whose output is 0 whatever follows
   }
   __syncthreads();
   {

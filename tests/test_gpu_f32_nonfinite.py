@@ -1,4 +1,4 @@
-"""fp32 prefill and decode on values that are not finite: a token that holds NaN or infinities (uninitialised padding at the
+"""Prefill and decode in fp32 on values that are not finite: a token that holds NaN or infinities (uninitialised padding at the
 tail of equal-length sequences) reaches the rows that see it and no earlier one; keys whose score overflows to -inf have
 weight 0, also where they fill a whole block.
 
@@ -140,3 +140,23 @@ def test_decode_infinite_latent_in_the_newest_row(n, splits):
     for g in range(wl.n_qgroups):
         m = orc.attention_map_rows(U.oracle_config(wl), q[:, g].astype(np.float64), np.array([n - 1]), k[0].astype(np.float64))
         _same(got[:, g], m @ c[0].astype(np.float64), f"{n} rows, group {g}")
+
+
+@pytest.mark.parametrize("splits", [1, 5, 40])          # 40: more than the one-round-trip tail takes
+@pytest.mark.parametrize("dtype,gate", [("f32", True), ("f32", False), ("bf16", True)])
+def test_decode_step_with_a_nan_key(dtype, gate, splits):
+    """A sequence with a NaN among its keys has no result, the others (and a full slot) are not affected."""
+    wl = W.scaled(_wl("paper"), dtype=dtype)
+    rng, cap, batch = W.make_rng(wl), 300, 4
+    w, x = W.draw_weights(wl, rng, std=wl.d_model ** -0.5), W.draw_hidden(wl, rng, batch)
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    k[1, 20] = np.nan
+    cache = U.DeviceCache(wl, batch, cap, *(torch.from_numpy(a).to("cuda", torch.float32 if dtype == "f32" else torch.bfloat16) for a in (k, c)))
+    cache.seq_lens.copy_(torch.tensor([250, 250, 17, cap], dtype=torch.int32))
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, dtype), x, cache, num_splits=splits, gate=gate))
+    assert np.isnan(out[1]).all() and not out[3].any()
+    lens, status = np.array([250, 250, 17, cap], dtype=np.int32), np.zeros(batch, dtype=np.int32)
+    with np.errstate(invalid="ignore"):
+        ref = orc.decode(U.oracle_config(wl, gate), U.oracle_weights(w), x, k.astype(np.float64), c.astype(np.float64), lens, status, range(batch))
+    for b in (0, 2):
+        U.assert_close(out[b], ref[b], dtype, f"sequence {b}", max(1.0, float(np.abs(ref[b]).max())))
