@@ -10,6 +10,8 @@
 // softmax in the log2 domain, and p * c accumulated with the weight broadcast from a scalar.
 #include <math.h>
 
+#include <type_traits>
+
 #include "gta_tuned.h"
 
 namespace gta {
@@ -1237,7 +1239,8 @@ __global__ __launch_bounds__(256) void decode_tail_narrow_kernel(Dims d, const f
     float acc = 0.f;
 #pragma unroll
     for (int q = 0; q < NPH; ++q) acc += redz[q][r][c];
-    if (d.gate == kGateSigmoid) acc *= 1.0f / (1.0f + __expf(-gz[o]));
+    // fp32 weights: the exponential to the last bit or two, as in the other fp32 gates (the short one loses a digit at |z| = 30)
+    if (d.gate == kGateSigmoid) acc *= 1.0f / (1.0f + (std::is_same<TW, float>::value ? expf(-gz[o]) : __expf(-gz[o])));
     else if (d.gate) acc *= gate_factor(d.gate, gz[o]);
     out[(int64_t)(b0 + r) * d.wg_w + g * HPQ * DH + c] = live(r) ? (TO)acc : (TO)0.f;
   }

@@ -93,3 +93,24 @@ def test_decode(shape, paged, splits):
         U.assert_close(U.f64(cd), cr, "f32", "latents", _scale(cr))
         np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
         np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
+
+
+@pytest.mark.parametrize("splits", [1, 5, 40])
+@pytest.mark.parametrize("shape", ["paper", "paper_nq3", "paper_h1"])
+def test_decode_gate_of_large_pre_activations(shape, splits):
+    """The Sigmoid alone, as the ratio of a gated and an ungated step, on pre-activations up to 40 that are exact (one-hot
+    tokens pick rows of W_G).  Bound: exponential, sum, quotient and two products of at most one unit in the last place
+    each, 6 x 2^-24."""
+    wl, batch = _wl(shape), 5
+    rng = W.make_rng(wl)
+    w = W.draw_weights(wl, rng, std=wl.d_model ** -0.5)
+    w["wg"] = rng.uniform(-40., 40., w["wg"].shape).astype(np.float32)
+    x = np.eye(batch, wl.d_model, dtype=np.float32)
+    k, c = W.draw_cache(wl, rng, batch, 200)
+    outs = []
+    for gate in (True, False):
+        cache = U.DeviceCache(wl, batch, 200, torch.from_numpy(k).cuda(), torch.from_numpy(c).cuda())
+        cache.seq_lens.copy_(torch.tensor([0, 15, 64, 100, 199], dtype=torch.int32))
+        outs.append(U.f64(U.run_decode(wl, U.upload_weights(w, "f32"), x, cache, num_splits=splits, gate=gate)))
+    got, ref = outs[0] / outs[1], orc.sigmoid(w["wg"][:batch])
+    assert np.abs(got / ref - 1.).max() <= 6 * 2. ** -24
