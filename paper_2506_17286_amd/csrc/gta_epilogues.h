@@ -1,7 +1,10 @@
 // Epilogues shared by the GEMM kernels that hand out groups of four finished columns (gta_f32.hip,
 // gta_rows_bf16.hip), and the column tiles of the kernels for few rows.
 #pragma once
+#include <type_traits>
+
 #include "gta_internal.h"
+#include "gta_rope.h"
 
 namespace gta {
 
@@ -21,22 +24,6 @@ __device__ __forceinline__ f32x4 load4(const __bf16 *p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
   const bf16x4 v = *reinterpret_cast<const bf16x4 *>(p);
   return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-}
-
-// sin and cos of p * f: the angle is formed and reduced to [-pi/4, pi/4] in fp64 (pi/2 in two parts), then the Taylor
-// series to degree 9 / 10 in fp32 (the first terms left out are below 2e-9 and 2e-10 there) and the quadrant.
-__device__ __forceinline__ void rope_sincos(int p, double f, float &sn, float &cs) {
-  const double ang = (double)p * f;
-  const double k = rint(ang * 0.6366197723675814);
-  double rd = fma(-k, 1.5707963267948966, ang);
-  rd = fma(-k, 6.123233995736766e-17, rd);
-  const float r = (float)rd, r2 = r * r;
-  const float s = fmaf(r * r2, fmaf(r2, fmaf(r2, fmaf(r2, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), r);
-  const float c = fmaf(r2, fmaf(r2, fmaf(r2, fmaf(r2, fmaf(r2, -1.f / 3628800.f, 1.f / 40320.f), -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
-  const int q = (int)(k - 4.0 * floor(k * 0.25));   // quadrant 0 .. 3
-  const float a = q & 1 ? c : s, b = q & 1 ? s : c;
-  sn = q & 2 ? -a : a;
-  cs = (q + 1) & 2 ? -b : b;
 }
 
 // ------------------------------------------------------------------------------ epilogues
@@ -109,7 +96,10 @@ struct ProjEpi {
       c.half = e < half ? half : -half;
       if (decode()) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { float s, t; rope_sincos(p, y.f[i], s, t); c.sn[i] = s; c.cs[i] = t; }
+        for (int i = 0; i < 4; ++i) {   // fp32 rows: the same values as a prefill's table
+          const float2 t = std::is_same<TC, float>::value ? rope_cos_sin(p, y.f[i]) : rope_cos_sin_short(p, y.f[i]);
+          c.cs[i] = t.x; c.sn[i] = t.y;
+        }
       } else {
         const float4 *t = reinterpret_cast<const float4 *>(table + (int64_t)(rope_by_token ? row : p) * half + j);
         const float4 t0 = t[0], t1 = t[1];

@@ -13,6 +13,7 @@
 
 #include <type_traits>
 
+#include "gta_rope.h"
 #include "gta_tuned.h"
 
 namespace gta {
@@ -54,20 +55,6 @@ __device__ __forceinline__ void rowmap_row(const int32_t *cu, int batch, int per
   locate_token(cu, batch, per_seq, t, b, i);
   seq_id[t] = b;
   pos[t] = i;
-}
-
-// (cos, sin) of p * f, evaluated in fp64 and rounded once to fp32 (App. B.1.1): the angle reduced to [-pi/4, pi/4] (pi/2
-// in two parts), then the Taylor series to degree 11 / 12 (the first terms left out are below 1e-11 there) and the quadrant.
-__device__ __forceinline__ float2 rope_cos_sin(int p, double f) {
-  const double ang = (double)p * f, k = rint(ang * 0.6366197723675814);
-  double x = fma(-k, 1.5707963267948966, ang);
-  x = fma(-k, 6.123233995736766e-17, x);
-  const double y = x * x;
-  const double s = fma(x * y, fma(y, fma(y, fma(y, fma(y, -1. / 39916800., 1. / 362880.), -1. / 5040.), 1. / 120.), -1. / 6.), x);
-  const double c = fma(y, fma(y, fma(y, fma(y, fma(y, fma(y, 1. / 479001600., -1. / 3628800.), 1. / 40320.), -1. / 720.), 1. / 24.), -0.5), 1.);
-  const int q = (int)(k - 4.0 * floor(k * 0.25));   // quadrant 0 .. 3
-  const float a = (float)(q & 1 ? c : s), b = (float)(q & 1 ? s : c);
-  return make_float2((q + 1) & 2 ? -b : b, q & 2 ? -a : a);
 }
 
 // Frequencies base^(-2j/d_h) of the RoPE table's columns in LDS: one power per column and workgroup instead of one per

@@ -114,3 +114,24 @@ def test_decode_gate_of_large_pre_activations(shape, splits):
         outs.append(U.f64(U.run_decode(wl, U.upload_weights(w, "f32"), x, cache, num_splits=splits, gate=gate)))
     got, ref = outs[0] / outs[1], orc.sigmoid(w["wg"][:batch])
     assert np.abs(got / ref - 1.).max() <= 6 * 2. ** -24
+
+
+@pytest.mark.parametrize("shape", ["paper", "paper_nq3"])
+def test_decode_and_chunk_store_the_same_keys(shape):
+    """A token's key row does not depend on the call that stored it: one new token behind 64 prefixes, as a decode step and
+    as a chunk, both on the projection that splits K.  Sums and angles are the same in both and the sines are rounded once
+    from fp64, so that rows may differ only where the two frequencies (a power on the host, one on the device) round apart
+    and the sine lies at the edge of a rounding: by one unit of the larger term, in less than one value in a thousand."""
+    wl, batch, cap = _wl(shape), 64, 6000
+    w, x = _inputs(wl, batch, False)
+    wdev, prefix = U.upload_weights(w, "f32"), np.random.default_rng(8).integers(0, cap, batch)
+    keys = []
+    for chunk in (True, False):
+        cache = U.DeviceCache(wl, batch, cap)
+        cache.seq_lens.copy_(torch.from_numpy(prefix.astype(np.int32)))
+        if chunk:
+            U.run_prefill_chunk(wl, wdev, x, np.arange(batch + 1), cache)
+        else:
+            U.run_decode(wl, wdev, x, cache)
+        keys.append(U.f64(cache.k[torch.arange(batch), torch.from_numpy(prefix)]))
+    assert (keys[0] != keys[1]).mean() < 1e-3 and np.abs(keys[0] - keys[1]).max() <= 2 ** -23 * np.abs(keys[0]).max()
