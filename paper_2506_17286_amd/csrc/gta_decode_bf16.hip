@@ -12,6 +12,7 @@
 
 #include <type_traits>
 
+#include "gta_rope.h"
 #include "gta_tuned.h"
 
 namespace gta {
@@ -1499,7 +1500,7 @@ int tuned_decode(const Dims &d, const gta_weights &w, const void *x_new, int bat
   // 8192 43.8 -> 44.1, 64 behind 8192 190 -> 192; 8 x 128 + 1024 shape, 1 behind 1000 56.7 -> 53.5, 8 behind 8192
   // 89.3 -> 90.2, 64 behind 2000 141 -> 155).
   const bool narrow_weights = batch <= 128 && d.H <= 1536;
-  if (rows_gemm_ok(d) && (narrow_weights || (batch <= 8 && (int64_t)batch * cache.max_seq <= 32768))) {
+  if (rows_gemm_ok(d) && rope_angles_small(d.rope, d.rope_base) && (narrow_weights || (batch <= 8 && (int64_t)batch * cache.max_seq <= 32768))) {
     launch_rows_proj_decode(d, w, x_new, batch, cache, slots, ws, st);
     tuned_decode_attention(d, ws.q, ws.oldlen, nullptr, cache, slots, batch, ws.splits, ws.part, st);
     gs = GateSrc{ws.g, 1, 0, d.wg_w};

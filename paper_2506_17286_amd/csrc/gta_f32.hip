@@ -601,7 +601,8 @@ bool f32_attn_ok(const Dims &d, int batch, int max_len) {
 
 // one key and one latent for all maps, pages that hold whole steps of 16 rows
 bool f32_decode_ok(const Dims &d, const gta_cache &cache, int batch) {
-  return f32_gemms_ok(d, batch) && d.nk == 1 && d.nc == 1 && d.nq <= 16 && d.dh == 64 && d.dl == 128 && tuned_decode_layout_ok(cache);
+  return f32_gemms_ok(d, batch) && d.nk == 1 && d.nc == 1 && d.nq <= 16 && d.dh == 64 && d.dl == 128 &&
+         tuned_decode_layout_ok(cache) && rope_angles_small(d.rope, d.rope_base);
 }
 
 static ProjEpi<float, float> proj_epi(const Dims &d, float *q, float *k, float *c, float *g, const gta_cache *cache, const int32_t *slots) {

@@ -226,7 +226,7 @@ __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total
     extern __shared__ double freq[];
     rope_freqs(freq, half, dh, base);
     const int p0 = blk * rope_rows, n = min(rope_rows, max_pos - p0) * half;
-    for (int i = threadIdx.x; i < n; i += 256) tab[(int64_t)p0 * half + i] = rope_cos_sin(p0 + i / half, freq[i % half]);
+    for (int i = threadIdx.x; i < n; i += 256) tab[(int64_t)p0 * half + i] = rope_cos_sin_any(p0 + i / half, freq[i % half]);
     return;
   }
   blk -= nb_rope;
@@ -264,7 +264,7 @@ __global__ void prefill_chunk_setup_kernel(const int32_t *cu, int batch, int64_t
       locate_token(cu, batch, per_seq, t, now, i);
       if (now != b) { b = now; pre = chunk_prefix(cv, cu, per_seq, b); }
       if (lane == 0) { seq_id[t] = b; pos[t] = pre < 0 ? -1 : pre + i; }
-      for (int j = lane; j < half; j += 64) tab[t * half + j] = rope_cos_sin(pre < 0 ? 0 : pre + i, freq[j]);
+      for (int j = lane; j < half; j += 64) tab[t * half + j] = rope_cos_sin_any(pre < 0 ? 0 : pre + i, freq[j]);
     }
     return;
   }

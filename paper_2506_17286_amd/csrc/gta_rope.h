@@ -1,9 +1,14 @@
 // Sines and cosines of RoPE angles p * base^(-2j/d_h) (App. B.1.1).  The angle is formed and reduced to [-pi/4, pi/4] in
-// fp64 (pi/2 in two parts), then comes a Taylor series and the quadrant.
+// fp64 (pi/2 in two parts), then comes a Taylor series and the quadrant.  Good for angles up to 2^40: every position at a
+// base of 1 or more (rope_angles_small).
 #pragma once
 #include <hip/hip_runtime.h>
 
 namespace gta {
+
+// Frequencies are at most 1.  A smaller base is accepted, but its frequencies grow up to base^-1 and leave the range of
+// the reduction: such calls keep to kernels that call the library's sine.
+inline bool rope_angles_small(int rope, double base) { return !rope || base >= 1.0; }
 
 // p * f = x + quadrant * pi/2
 __device__ __forceinline__ double rope_reduce(int p, double f, int &quadrant) {
@@ -12,8 +17,8 @@ __device__ __forceinline__ double rope_reduce(int p, double f, int &quadrant) {
   return fma(-k, 6.123233995736766e-17, fma(-k, 1.5707963267948966, ang));
 }
 
-// (cos, sin) rounded once from fp64: the series to degree 11 / 12 (the first terms left out are below 1e-11).  For tables
-// and fp32 rows.
+// (cos, sin) rounded once from fp64: the series to degree 11 / 12 (the first terms left out are below 1e-11).  For fp32
+// rows and tables.
 __device__ __forceinline__ float2 rope_cos_sin(int p, double f) {
   int q;
   const double x = rope_reduce(p, f, q), y = x * x;
@@ -23,7 +28,16 @@ __device__ __forceinline__ float2 rope_cos_sin(int p, double f) {
   return make_float2((q + 1) & 2 ? -b : b, q & 2 ? -a : a);
 }
 
-// The same with the series in fp32, to degree 9 / 10 (the first terms left out are below 2e-9 and 2e-10): largest error
+// the same for any angle (tables)
+__device__ __forceinline__ float2 rope_cos_sin_any(int p, double f) {
+  const double ang = (double)p * f;
+  if (fabs(ang) < 0x1p40) return rope_cos_sin(p, f);
+  double s, c;
+  sincos(ang, &s, &c);
+  return make_float2((float)c, (float)s);
+}
+
+// rope_cos_sin with the series in fp32, to degree 9 / 10 (the first terms left out are below 2e-9 and 2e-10): largest error
 // 5.8e-8 against 3.0e-8.  For rows that are rounded to bf16.
 __device__ __forceinline__ float2 rope_cos_sin_short(int p, double f) {
   int q;

@@ -27,3 +27,28 @@ def test_sequences_of_many_pages(lens, page, chunk):
     k, c = paged.logical()
     for s in (0, 2):
         assert torch.equal(k[s, :lens[s]], plain.k[s, :lens[s]]) and torch.equal(c[s, :lens[s]], plain.c[s, :lens[s]])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("call", ["prefill", "chunk", "decode"])
+def test_rope_base_below_one(dtype, call):
+    """A base of 2^-64 makes frequencies up to 2^62, far outside what a two-part reduction by pi/2 takes.  At such angles one
+    unit in the last place of a frequency is many turns, so no two implementations rotate alike; but every one rotates:
+    the lengths of the pairs (j, j + d_h/2) of the stored keys are those of the unrotated projection (bounds of the parity
+    gate)."""
+    wl = W.scaled(W.PAPER_WORKLOADS[1], d_model=128, dtype=dtype, rope_base=2. ** -64, seed=9200)
+    rng, n = W.make_rng(wl), 100
+    w, x = W.draw_weights(wl, rng, std=wl.d_model ** -0.5), W.draw_hidden(wl, rng, n)
+    wdev, cu = U.upload_weights(w, dtype), np.array([0, n], dtype=np.int32)
+    if call == "decode":     # token b behind b rows, one slot each
+        cache = U.DeviceCache(wl, n, n)
+        cache.seq_lens.copy_(torch.arange(n))
+        U.run_decode(wl, wdev, x, cache)
+        rows = cache.k[torch.arange(n), torch.arange(n)]
+    else:
+        cache = U.DeviceCache(wl, 1, n)
+        (U.run_prefill if call == "prefill" else U.run_prefill_chunk)(wl, wdev, x, cu, cache=cache)
+        rows = cache.k[0]
+    pairs = lambda k: np.hypot(k[:, :wl.head_dim // 2], k[:, wl.head_dim // 2:])
+    ref = pairs(x.astype(np.float64) @ w["wk"].astype(np.float64))
+    U.assert_close(pairs(U.f64(rows)), ref, dtype, call, max(1.0, float(ref.max())))
