@@ -105,10 +105,12 @@ struct AttnArgs {
   // already in them behind the prefix[b] rows cached before (prefix[b] < 0: sequence skipped, zero output)
   const int32_t *prefix, *slots; int max_seq;
   PageMap pm; int ps_shift;   // cache mode on a block-table layout: page_size = 1 << ps_shift, a multiple of BK
-  // key range split over `splits` workgroups (not fused): each writes un-normalised fp32 sums pacc [split, token,
-  // n_q*d_l] and (maximum in log2 units, sum) pml [split, token, n_q, column slice], merged by attn_merge_kernel
-  int splits; float *pacc; float2 *pml; int64_t total;
+  // key range split over up to `splits` workgroups (not fused), a sequence's over as many as keep split_tiles key tiles
+  // each: they write un-normalised fp32 sums pacc [split, token, n_q*d_l] and (maximum in log2 units, sum) pml [split,
+  // token, n_q, column slice], merged by attn_merge_kernel.  A sequence that is not split writes its rows itself.
+  int splits, split_tiles; float *pacc; float2 *pml; int64_t total; const int32_t *seq_id;
 };
+__device__ __forceinline__ int splits_of(const AttnArgs &a, int keys) { return max(min((keys + 31) / 32 / a.split_tiles, a.splits), 1); }
 
 // LDS of the fused value decoder: the normalised BQ x DLW tile (row operand) and the DLW x 256 decoder matrices of the
 // group's heads side by side, in halves where two workgroups share a CU; afterwards the BQ x 256 gate / output tile.
@@ -180,11 +182,10 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   if (q0 >= Tb) return;
   const int P = a.prefix ? a.prefix[b] : 0;                  // keys cached before the first query
   const int kh = wave / T::QW, qw = wave % T::QW;            // key half and query rows of this wave
-  float2 *pml = a.pml + (((int64_t)split * a.total + start + q0) * a.nq + g) * a.ndlc + dlc;   // split keys only
+  const int splits = FUSE || a.splits == 1 || P < 0 ? 1 : splits_of(a, P + Tb);
+  if (split >= splits) return;
   if (P < 0) {   // skipped sequence: zero rows
-    if (!FUSE && a.splits > 1) {
-      if (tid < T::BQ && q0 + tid < Tb) pml[(int64_t)tid * a.nq * a.ndlc] = make_float2(-INFINITY, 0.f);
-    } else if constexpr (FUSE) {
+    if constexpr (FUSE) {
       const int64_t ldo = (int64_t)a.nh * a.dh;
       bf16 *Ob = a.out + (start + q0) * ldo + g * a.hpq * a.dh;
       for (int i = tid; i < T::BQ * 32; i += T::NT)
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   const int qa0 = P + qw0;                                   // its position among the keys
   const int kend = P + min(q0 + T::BQ, Tb);                  // keys [0, kend) are visible to this tile
   const int ntiles_all = (kend + T::BK - 1) / T::BK;
-  const int tile0 = (int)((int64_t)ntiles_all * split / a.splits), tile1 = (int)((int64_t)ntiles_all * (split + 1) / a.splits);
+  const int tile0 = (int)((int64_t)ntiles_all * split / splits), tile1 = (int)((int64_t)ntiles_all * (split + 1) / splits);
   const int nsteps = (tile1 - tile0 + T::KS - 1) / T::KS;    // step t: key tiles tile0 + KS t (+ 1)
   const int kend_w = qw0 < Tb ? P + min(qw0 + 32, Tb) : 0;   // keys [0, kend_w) are visible to this wave
   int64_t krow0 = start;                                     // first key / latent row of the sequence
@@ -530,8 +531,9 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
     }
     __syncthreads();
   }
-  if (!FUSE && a.splits > 1) {   // un-normalised sums and statistics for the merge
+  if (!FUSE && splits > 1) {   // un-normalised sums and statistics for the merge
     const int row = qw * 32 + ln;
+    float2 *pml = a.pml + (((int64_t)split * a.total + start + q0) * a.nq + g) * a.ndlc + dlc;
     if (kh == 0 && q0 + row < Tb) {
       float *pa = a.pacc + ((int64_t)split * a.total + start + q0 + row) * (a.nq * a.dl) + g * a.dl + dlc * T::DLW + 4 * h;
 #pragma unroll
@@ -670,22 +672,23 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   }
 }
 
-// Merge of the key splits of one token (blockIdx.x): thread = 4 columns of one map group; weights exp2(m_s - max) /
-// sum.  A token without any keys (skipped sequence) gets zeros.
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ pacc, const float2 *__restrict__ pml, int splits,
-                                                         int64_t total, int nq, int dl, int ndlc, int dlw, bf16 *__restrict__ L) {
+// Merge of the key splits of one token (blockIdx.x): thread = 4 columns of one map group; weights exp2(m_s - max) / sum.
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int dlw) {
   const int64_t tok = blockIdx.x;
+  const int b = a.seq_id[tok], P = a.prefix ? a.prefix[b] : 0, nq = a.nq, dl = a.dl;
+  const int splits = P < 0 ? 1 : splits_of(a, P + (a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq));
+  if (splits == 1) return;
   for (int i = threadIdx.x; i < nq * dl / 4; i += 256) {
-    const int col = i * 4, g = col / dl, st = g * ndlc + col % dl / dlw;
+    const int col = i * 4, st = col / dl * a.ndlc + col % dl / dlw;
     float mx = -INFINITY;
-    for (int s = 0; s < splits; ++s) mx = fmaxf(mx, pml[(s * total + tok) * (nq * ndlc) + st].x);
+    for (int s = 0; s < splits; ++s) mx = fmaxf(mx, a.pml[(s * a.total + tok) * (nq * a.ndlc) + st].x);
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     float ls = 0.f;
     for (int s = 0; s < splits; ++s) {
-      const float2 ml = pml[(s * total + tok) * (nq * ndlc) + st];
+      const float2 ml = a.pml[(s * a.total + tok) * (nq * a.ndlc) + st];
       if (ml.x > -INFINITY) {
         const float w = __builtin_amdgcn_exp2f(ml.x - mx);
-        const float4 p = *reinterpret_cast<const float4 *>(pacc + (s * total + tok) * (int64_t)(nq * dl) + col);
+        const float4 p = *reinterpret_cast<const float4 *>(a.pacc + (s * a.total + tok) * (int64_t)(nq * dl) + col);
         ls = fmaf(w, ml.y, ls);
         v.x = fmaf(w, p.x, v.x); v.y = fmaf(w, p.y, v.y); v.z = fmaf(w, p.z, v.z); v.w = fmaf(w, p.w, v.w);
       }
@@ -693,7 +696,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
     const float inv = ls > 0.f ? 1.0f / ls : 0.f;
     bf16x4 o;
     o[0] = (bf16)(v.x * inv); o[1] = (bf16)(v.y * inv); o[2] = (bf16)(v.z * inv); o[3] = (bf16)(v.w * inv);
-    *reinterpret_cast<bf16x4 *>(L + tok * (nq * dl) + col) = o;
+    *reinterpret_cast<bf16x4 *>(a.L + tok * (nq * dl) + col) = o;
   }
 }
 
@@ -732,8 +735,10 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
   if (!FUSE && part) {
     // Still fewer workgroups than CUs: the key range is split over workgroups, too, as long as a split keeps 8 steps
     // of two tiles (16 for a fresh prompt, whose average tile is half as long).  1 x 40 behind 6000 145 us without,
-    // 80 with up to 23 splits, 67 with 11; 4 x 40 behind 6000 153 / 76; 1 x 2000 fresh 124 / 120.
-    const int64_t most = (int64_t)(max_keys + 31) / 32 / (a.prefix ? 16 : 32);
+    // 80 with up to 23 splits, 67 with 11; 4 x 40 behind 6000 153 / 76; 1 x 2000 fresh 124 / 120.  max_keys is only the
+    // capacity of the slots: the kernels apply the same rule to the keys a sequence has.
+    a.split_tiles = a.prefix ? 16 : 32;
+    const int64_t most = (int64_t)(max_keys + 31) / 32 / a.split_tiles;
     a.splits = (int)(kSplitTarget / half < most ? kSplitTarget / half : most);
     const int64_t stats = a.total * d.nq * (d.dl / DLW) * 2;   // floats per split
     while (a.splits > 1 && (size_t)(a.splits * (stats + a.total * d.nq * d.dl) + 64) * 4 > attn_split_bytes(d)) --a.splits;
@@ -741,9 +746,10 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
     a.pml = reinterpret_cast<float2 *>(part);
     a.pacc = part + ((a.splits * stats + 63) & ~(int64_t)63);
   }
+  a.ndlc = d.dl / DLW;
   launch_tile<AttnTile<DH, DLW, 2>, FUSE>(a, d, batch, max_len, st);
   if (a.splits > 1)
-    attn_merge_kernel<<<(unsigned)a.total, 256, 0, st>>>(a.pacc, a.pml, a.splits, a.total, d.nq, d.dl, d.dl / DLW, DLW, a.L);
+    attn_merge_kernel<<<(unsigned)a.total, 256, 0, st>>>(a, DLW);
 }
 
 template <bool FUSE>
@@ -783,9 +789,10 @@ static AttnArgs attn_args(const Dims &d, const void *q, const void *k, const voi
 }
 
 void launch_attn_prefill_bf16(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,
-                              int batch, int64_t total, int max_len, void *L, float *part, hipStream_t st) {
+                              int batch, int64_t total, int max_len, void *L, float *part, const int32_t *seq_id,
+                              hipStream_t st) {
   AttnArgs a = attn_args(d, q, k, c, cu, batch, total);
-  a.L = (bf16 *)L;
+  a.L = (bf16 *)L; a.seq_id = seq_id;
   launch_attn_any<false>(a, d, batch, max_len, max_len, part, st);
 }
 
@@ -805,9 +812,10 @@ void launch_attn_decoder_bf16(const Dims &d, const void *q, const void *k, const
 
 void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache, const int32_t *slots,
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
-                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part, hipStream_t st) {
+                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part,
+                            const int32_t *seq_id, hipStream_t st) {
   AttnArgs a = attn_args(d, q, cache.k, cache.c, cu, batch, total);
-  a.prefix = prefix; a.slots = slots; a.max_seq = cache.max_seq;
+  a.prefix = prefix; a.slots = slots; a.max_seq = cache.max_seq; a.seq_id = seq_id;
   a.pm = page_map_of(cache);
   a.ps_shift = 0;
   while (a.pm.table && (1 << a.ps_shift) < a.pm.page_size) ++a.ps_shift;
