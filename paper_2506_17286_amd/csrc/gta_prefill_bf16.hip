@@ -682,18 +682,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int dlw) {
     const int col = i * 4, st = col / dl * a.ndlc + col % dl / dlw;
     float mx = -INFINITY;
     for (int s = 0; s < splits; ++s) mx = fmaxf(mx, a.pml[(s * a.total + tok) * (nq * a.ndlc) + st].x);
+    const float ref = mx > -INFINITY ? mx : 0.f;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     float ls = 0.f;
     for (int s = 0; s < splits; ++s) {
       const float2 ml = a.pml[(s * a.total + tok) * (nq * a.ndlc) + st];
-      if (ml.x > -INFINITY) {
-        const float w = __builtin_amdgcn_exp2f(ml.x - mx);
+      if (ml.y != 0.f) {   // a split without visible keys has the sum 0; one of nothing but NaN has no maximum either
+        const float w = __builtin_amdgcn_exp2f(ml.x - ref);
         const float4 p = *reinterpret_cast<const float4 *>(a.pacc + (s * a.total + tok) * (int64_t)(nq * dl) + col);
         ls = fmaf(w, ml.y, ls);
         v.x = fmaf(w, p.x, v.x); v.y = fmaf(w, p.y, v.y); v.z = fmaf(w, p.z, v.z); v.w = fmaf(w, p.w, v.w);
       }
     }
-    const float inv = ls > 0.f ? 1.0f / ls : 0.f;
+    const float inv = 1.0f / ls;
     bf16x4 o;
     o[0] = (bf16)(v.x * inv); o[1] = (bf16)(v.y * inv); o[2] = (bf16)(v.z * inv); o[3] = (bf16)(v.w * inv);
     *reinterpret_cast<bf16x4 *>(a.L + tok * (nq * dl) + col) = o;

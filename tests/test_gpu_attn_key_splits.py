@@ -77,3 +77,23 @@ def test_chunks_behind_cached_rows(shape, paged):
                f"{shape} {lens[b]} behind {prefix[b]}")
     assert not out[cu[-2]:].any() and cache.status.tolist() == [0] * 5 + [B.GTA_ERR_CACHE_FULL]
     assert cache.seq_lens.tolist() == [n + p for n, p in zip(lens[:-1], prefix[:-1])] + [prefix[-1]]
+
+
+@pytest.mark.parametrize("n", [1, 40])
+@pytest.mark.parametrize("where", ["query", "keys"])
+def test_nan_passes_the_merge(where, n):
+    """Scores that are all NaN (a NaN in W_Q or in every cached key of a group) leave no maximum in any split; the heads of
+    that group have no result all the same, the others keep theirs.  Without the gate, which would be NaN of itself."""
+    wl, w, x, rng = _setup("1b", n)
+    cap, prefix = 2304, 2200
+    k, c = W.draw_cache(wl, rng, 1, cap)
+    if where == "query":
+        w["wq"][0, 5] = np.nan
+    else:
+        k[0, :prefix, 5] = np.nan
+        w["wk"][:, 5] = np.nan
+    cache = U.DeviceCache(wl, 1, cap, *(torch.from_numpy(a).to("cuda", torch.bfloat16) for a in (k, c)))
+    cache.seq_lens.fill_(prefix)
+    dev = {name: torch.from_numpy(a).to("cuda", torch.bfloat16) for name, a in w.items() if a is not None}
+    out = U.f64(U.run_prefill_chunk(wl, dev, x, np.array([0, n]), cache, gate=False)).reshape(n, wl.n_qgroups, -1)
+    assert np.isnan(out[:, 0]).all() and np.isfinite(out[:, 1:]).all()
