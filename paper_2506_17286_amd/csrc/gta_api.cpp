@@ -134,13 +134,15 @@ static int choose_splits_of(const Dims &d, int batch, int max_seq, int min_rows)
 // Slices of at least 64 rows: a workgroup's chain of steps over its slice is what a small batch waits for (whole
 // steps with 256-, 128-, 64- and 32-row slices: 1B shape, one sequence behind 2000 rows 33.7 / 28.3 / 25.4 / 24.3 us,
 // 16 behind 1000 36.5 / 31.5 / 30.4 / 30.2; paper layer, one behind 1000 31.4 / 27.8 / 26.1 / 27.6, fp32 8 behind 1000
-// 46 / 43 / 41 / 46).  The one-round-trip tails hold 32 (narrow rows) or 64 splits, though: past those only slices of
-// at least 256 rows pay for the general tail.
+// 46 / 43 / 41 / 46).  The one-round-trip tails hold 32 (narrow rows) or 64 splits (latents of 512), though: past those
+// only slices of at least 256 rows pay for the general tail.  Latents of 1024 and the shape-generic kernels have no such
+// tail; there 64 is where finer slices stop paying (steps with 32 / 64 / 128 splits: 8 x 128 + 1024 shape, one behind
+// 8000 rows 73 / 63.5 / 62.4 us, 4 behind 4000 63.1 / 63.6 / 80.5; fp32 1B shape, one behind 4000 1505 / 1386 / 1362).
 int choose_splits(const Dims &d, int batch, int max_seq, int requested) {
   if (requested > 0) return requested > 1024 ? 1024 : requested;
-  const int one_trip = d.dl == 128 && d.dh == 64 ? 32 : 64;
+  const int fine = d.dl == 128 && d.dh == 64 ? 32 : 64;
   const int s = choose_splits_of(d, batch, max_seq, 64);
-  return s <= one_trip ? s : std::max(one_trip, choose_splits_of(d, batch, max_seq, 256));
+  return s <= fine ? s : std::max(fine, choose_splits_of(d, batch, max_seq, 256));
 }
 
 DecodeWs carve_decode(const Dims &d, bool with_wo, int batch, int splits, void *base) {

@@ -493,8 +493,11 @@ __global__ __launch_bounds__(64) void attn_decode_generic_kernel(Dims d, const f
   }
 }
 
-// Merge the splits of one (sequence, group) by their log-sum-exp weights; L = sum acc / sum l.
+// Merge the splits of one (sequence, group) by their log-sum-exp weights; L = sum acc / sum l.  One wave forms the weights
+// side by side (every thread walking the splits three times cost 0.5 us a split: tiny layer, one sequence behind 4000 rows in 64
+// splits 203 us, 172 now).
 __global__ void decode_combine_kernel(Dims d, const float *part, const int32_t *oldlen, int splits, float *L) {
+  extern __shared__ float wt[];   // [splits]
   const int g = blockIdx.x, b = blockIdx.y;
   const float *pb = part + ((int64_t)b * splits * d.nq + g) * (d.dl + 2);
   const int64_t sstride = (int64_t)d.nq * (d.dl + 2);
@@ -503,21 +506,24 @@ __global__ void decode_combine_kernel(Dims d, const float *part, const int32_t *
     for (int c = threadIdx.x; c < d.dl; c += blockDim.x) Lr[c] = 0.f;
     return;
   }
-  float mx = -INFINITY;
-  for (int s = 0; s < splits; ++s) mx = fmaxf(mx, pb[s * sstride + d.dl]);
-  float lsum = 0.f;
-  for (int s = 0; s < splits; ++s) {
-    float ms = pb[s * sstride + d.dl];
-    if (ms > -INFINITY) lsum += expf(ms - mx) * pb[s * sstride + d.dl + 1];
+  if (threadIdx.x < 64) {
+    float mx = -INFINITY, lsum = 0.f;
+    for (int s = threadIdx.x; s < splits; s += 64) mx = fmaxf(mx, pb[s * sstride + d.dl]);
+    mx = wave_max(mx);
+    for (int s = threadIdx.x; s < splits; s += 64) {
+      const float ms = pb[s * sstride + d.dl];
+      wt[s] = ms > -INFINITY ? expf(ms - mx) : 0.f;
+      if (ms > -INFINITY) lsum += wt[s] * pb[s * sstride + d.dl + 1];
+    }
+    const float inv = 1.0f / wave_sum(lsum);
+    for (int s = threadIdx.x; s < splits; s += 64) wt[s] *= inv;
   }
-  const float inv = 1.0f / lsum;
+  __syncthreads();
   for (int c = threadIdx.x; c < d.dl; c += blockDim.x) {
     float a = 0.f;
-    for (int s = 0; s < splits; ++s) {
-      float ms = pb[s * sstride + d.dl];
-      if (ms > -INFINITY) a += expf(ms - mx) * pb[s * sstride + c];
-    }
-    Lr[c] = a * inv;
+    for (int s = 0; s < splits; ++s)
+      if (wt[s] != 0.f) a = fmaf(wt[s], pb[s * sstride + c], a);
+    Lr[c] = a;
   }
 }
 
@@ -749,7 +755,7 @@ int decode_impl(const Dims &d, const gta_weights &w, const T *x, int batch, cons
   CacheView cv = view_of(&cache, slots);
   dim3 agrid(ws.splits, d.nq, batch);
   attn_decode_generic_kernel<T><<<agrid, 64, d.dh * sizeof(float), st>>>(d, ws.q, ws.oldlen, cv, ws.splits, ws.part);
-  decode_combine_kernel<<<dim3(d.nq, batch), 256, 0, st>>>(d, ws.part, ws.oldlen, ws.splits, ws.l);
+  decode_combine_kernel<<<dim3(d.nq, batch), 256, ws.splits * sizeof(float), st>>>(d, ws.part, ws.oldlen, ws.splits, ws.l);
   if (w.wo) {
     launch_gemm(ws.l, (int64_t)d.nq * d.dl, (int64_t)d.dl, d.hpq, (const T *)w.wp, (int64_t)d.dh,
                 (int64_t)d.dl * d.dh, batch, d.dh, d.dl, d.nh,
@@ -852,7 +858,7 @@ void generic_decode_attention(const Dims &d, const float *q, const int32_t *oldl
 
 void generic_decode_combine(const Dims &d, const float *part, const int32_t *oldlen, int splits, int batch, float *L,
                             hipStream_t st) {
-  decode_combine_kernel<<<dim3(d.nq, batch), 256, 0, st>>>(d, part, oldlen, splits, L);
+  decode_combine_kernel<<<dim3(d.nq, batch), 256, splits * sizeof(float), st>>>(d, part, oldlen, splits, L);
 }
 
 void launch_attn_prefill_rowwise(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,

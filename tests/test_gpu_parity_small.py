@@ -190,3 +190,19 @@ def test_cache_append_bit_exact(dtype):
     np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), seq_ref)
     np.testing.assert_array_equal(cache.status.cpu().numpy(), st_ref)
     assert st_ref[2] == B.GTA_ERR_CACHE_FULL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("splits", [2, 63, 64, 65, 200, 1000])
+def test_generic_decode_split_counts(dtype, splits):
+    """The merge of the shape-generic step around one and several rounds of its wave over the splits, most of them empty."""
+    wl = W.Workload("g", "decode", 3, 90, 48, 6, 3, 3, 1, 12, 20, dtype, True, seed=31)
+    rng, ctx = W.make_rng(wl), np.array([0, 63, 90], dtype=np.int32)
+    w, x = W.draw_weights(wl, rng, std=wl.d_model ** -0.5), W.draw_hidden(wl, rng, 3)
+    k, c = W.draw_cache(wl, rng, 3, 91)
+    cache = U.DeviceCache(wl, 3, 91, B.to_device(k, dtype), B.to_device(c, dtype))
+    cache.seq_lens.copy_(torch.from_numpy(ctx))
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, dtype), x, cache, num_splits=splits))
+    ref = orc.decode(U.oracle_config(wl), U.oracle_weights(w), x, k.astype(np.float64), c.astype(np.float64), ctx,
+                     np.zeros(3, dtype=np.int32), range(3))
+    U.assert_close(out, ref, dtype, f"{splits} splits", max(1.0, float(np.abs(ref).max())))
