@@ -122,7 +122,8 @@ typedef struct {
 /* Bytes of device workspace the call described by the arguments needs.
  *   mode PREFILL: batch sequences, total_tokens packed tokens, longest sequence <= max_len.
  *   mode DECODE : batch sequences, max_len = cache->max_seq, num_splits as passed to gta_decode
- *                 (0 = library's choice).
+ *                 (0 = library's choice; a call with a smaller workspace that still holds context
+ *                 slices of at least 256 rows runs with those).
  *   mode PREFILL_CHUNK: as PREFILL, for gta_prefill_chunk (max_len = max_chunk).
  * Returns 0 if cfg is NULL or invalid. */
 GTA_API size_t gta_workspace_bytes(const gta_config *cfg, int mode, int32_t batch, int64_t total_tokens,

@@ -161,6 +161,15 @@ DecodeWs carve_decode(const Dims &d, bool with_wo, int batch, int splits, void *
   return w;
 }
 
+// The workspace of a decode call in the `bytes` at `base`.  The library's own split count does not grow steadily with the
+// batch (512 / 64 = 8 slices of 64 sequences, 9 of 63), so a workspace sized for a full batch may be too small for a few
+// sequences less; slices of at least 256 rows are taken there.
+static DecodeWs fit_decode(const Dims &d, bool with_wo, int batch, int max_seq, int requested, void *base, size_t bytes) {
+  const DecodeWs ws = carve_decode(d, with_wo, batch, choose_splits(d, batch, max_seq, requested), base);
+  if (requested > 0 || ws.bytes <= bytes) return ws;
+  return carve_decode(d, with_wo, batch, choose_splits_of(d, batch, max_seq, 256), base);
+}
+
 static int check_weights(const gta_weights *w) {
   if (!w || !w->wq || !w->wk || !w->wc || !w->wg || !w->wp) return GTA_ERR_NULL;
   if (misaligned(w->wq) || misaligned(w->wk) || misaligned(w->wc) || misaligned(w->wg) || misaligned(w->wp) ||
@@ -348,8 +357,7 @@ int gta_decode(const gta_config *cfg, const gta_weights *weights, const void *x_
   if (batch <= 0 || batch > kMaxBatch || num_splits < 0 || (!slots && batch > cache->max_batch)) return GTA_ERR_SHAPE;
   if (misaligned(x_new) || misaligned(out) || ((uintptr_t)slots & 3u)) return GTA_ERR_ALIGN;
   if (!workspace || misaligned(workspace)) return GTA_ERR_WORKSPACE;
-  const int splits = choose_splits(d, batch, cache->max_seq, num_splits);
-  DecodeWs ws = carve_decode(d, weights->wo != nullptr, batch, splits, workspace);
+  const DecodeWs ws = fit_decode(d, weights->wo != nullptr, batch, cache->max_seq, num_splits, workspace, workspace_bytes);
   if (ws.bytes > workspace_bytes) return GTA_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   if (decode_is_tuned(d, *cache)) return tuned_decode(d, *weights, x_new, batch, *cache, slots, out, ws, st);
@@ -465,7 +473,7 @@ static int decode_stage_args(const gta_config *cfg, const gta_cache *cache, cons
   if (batch <= 0 || batch > kMaxBatch || num_splits < 0 || (!slots && batch > cache->max_batch)) return GTA_ERR_SHAPE;
   if ((uintptr_t)slots & 3u) return GTA_ERR_ALIGN;
   if (!workspace || misaligned(workspace)) return GTA_ERR_WORKSPACE;
-  *ws = carve_decode(*d, true, batch, choose_splits(*d, batch, cache->max_seq, num_splits), workspace);
+  *ws = fit_decode(*d, true, batch, cache->max_seq, num_splits, workspace, workspace_bytes);
   return ws->bytes > workspace_bytes ? GTA_ERR_WORKSPACE : GTA_OK;
 }
 

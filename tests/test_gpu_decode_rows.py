@@ -66,3 +66,25 @@ def test_static_scratch_takes_coarser_splits_where_its_own_do_not_fit():
         torch.cuda.synchronize()
         outs.append((out, cache.k, cache.c, cache.seq_lens))
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("most,cap", [(64, 2048), (128, 512), (256, 256)])
+def test_workspace_of_a_full_batch_serves_fewer_sequences(most, cap):
+    """fp32 steps: 63 sequences take more splits each than 64; slices of at least 256 rows fit the workspace of 64 all the
+    same."""
+    wl = W.scaled(_wl("paper", 128), dtype="f32")
+    cfg = B.config_of(wl)
+    rng = W.make_rng(wl)
+    w, x = W.draw_weights(wl, rng, std=wl.d_model ** -0.5, with_wo=True), W.draw_hidden(wl, rng, most)
+    wdev, lens = U.upload_weights(w, "f32"), torch.from_numpy(rng.integers(0, cap, most).astype(np.int32)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    k, c = (torch.randn((most, cap, width), device="cuda", generator=gen) for width in wl.kv_width)
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, most, 0, cap))
+    assert any(B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, n, 0, cap) > ws.numel() for n in range(1, most))
+    for batch in (most, most - 1, most // 2 + 1, 2):
+        cache = U.DeviceCache(wl, most, cap, k.clone(), c.clone(), lens.clone())
+        out = torch.empty((batch, wl.d_model), device="cuda")
+        B.gta_decode(cfg, B.make_weights(wdev), B.to_device(x[:batch], "f32"), batch, cache.struct, None, out, 0, ws)
+        again = U.DeviceCache(wl, most, cap, k, c, lens.clone())
+        ref = U.f64(U.run_decode(wl, wdev, x[:batch], again))
+        U.assert_close(U.f64(out), ref, "f32", f"{batch} sequences", max(1.0, float(np.abs(ref).max())))
