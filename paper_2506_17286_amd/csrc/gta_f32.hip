@@ -589,7 +589,9 @@ void launch_gemm_f32(const GemmOperands &g, int cols, const Epi &epi, hipStream_
 // Shapes of the fp32 MFMA GEMMs: every output width in units of 64 columns (a tile lies in one of Q, K, C, gate
 // and holds whole heads), contraction lengths in units of 16.
 bool f32_gemms_ok(const Dims &d, int64_t M) {
-  if (d.dtype != GTA_F32 || (M / 32 + 1) * (d.wtot / 32) >= (1 << 22)) return false;   // (a launch holds at most 2^32 threads)
+  // a launch holds at most 2^32 threads, up to 1024 per 32 x 32 tile (of the output projection only for few rows)
+  const int64_t nrt = M / 32 + 1, most = 1 << 22;
+  if (d.dtype != GTA_F32 || nrt * (d.wtot / 32) >= most || (M <= kRowsMax && nrt * (d.H / 32) >= most)) return false;
   if (d.dh % 8 || 64 % d.dh) return false;
   return !(d.wq_w % 64 || d.wk_w % 64 || d.wc_w % 64 || d.wg_w % 64 || d.H % 64 || d.dl % 16);
 }
