@@ -79,6 +79,29 @@ def test_chunks_behind_cached_rows(shape, paged):
     assert cache.seq_lens.tolist() == [n + p for n, p in zip(lens[:-1], prefix[:-1])] + [prefix[-1]]
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_chunks_of_many_workgroups(shape, paged):
+    """A loose bound on the chunks' lengths and enough sequences that no key halves or splits are taken: every tile shape
+    walks more key tiles than it has stages in cache mode."""
+    lens, prefix, cap = [1, 33, 128, 70, 129, 2, 300] * 2 + [40], [1500, 2047, 31, 0, 33, 700, 1000] * 2 + [2300], 2304
+    wl, w, x, rng = _setup(shape, sum(lens))
+    assert cap // 128 * len(lens) * wl.n_qgroups > 512
+    k, c = W.draw_cache(wl, rng, len(lens), cap)
+    if paged:
+        cache = U.PagedDeviceCache(wl, len(lens), 64, cap // 64, seed=4)
+        cache.store(B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    else:
+        cache = U.DeviceCache(wl, len(lens), cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = U.f64(U.run_prefill_chunk(wl, U.upload_weights(w, "bf16"), x, cu, cache, max_chunk=cap))
+    for b in range(len(lens) - 1):
+        _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
+               f"{shape} {lens[b]} behind {prefix[b]}")
+    assert not out[cu[-2]:].any() and cache.status.tolist() == [0] * 14 + [B.GTA_ERR_CACHE_FULL]
+
+
 @pytest.mark.parametrize("n", [1, 40])
 @pytest.mark.parametrize("where", ["query", "keys"])
 def test_nan_passes_the_merge(where, n):

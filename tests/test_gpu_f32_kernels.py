@@ -1,4 +1,4 @@
-"""The fp32 MFMA kernels against the oracle at the edges of their tiles: row tiles of 32 (few rows) and 128 (many),
+"""The fp32 MFMA kernels against the oracle at the edges of their tiles: row tiles of 32 (few rows) and 64 (many),
 32-key blocks dealt to four waves, latent slices of 64 and 128 columns, 16-row decode steps, splits without rows,
 contiguous and block-table caches, full slots.
 
@@ -135,3 +135,80 @@ def test_decode_and_chunk_store_the_same_keys(shape):
             U.run_decode(wl, wdev, x, cache)
         keys.append(U.f64(cache.k[torch.arange(batch), torch.from_numpy(prefix)]))
     assert (keys[0] != keys[1]).mean() < 1e-3 and np.abs(keys[0] - keys[1]).max() <= 2 ** -23 * np.abs(keys[0]).max()
+
+
+@pytest.mark.parametrize("batch", [33, 256, 257, 300])
+def test_decode_of_many_sequences(batch):
+    """Several row tiles of the kernel for few rows, and the decode epilogue in the one for many."""
+    wl, cap = _wl("paper"), 80
+    w, x = _inputs(wl, batch, True)
+    k, c = W.draw_cache(wl, W.make_rng(wl), batch, cap)
+    ctx = np.random.default_rng(batch).integers(0, cap, batch).astype(np.int32)
+    ctx[batch // 2] = cap                                  # full
+    cache = U.DeviceCache(wl, batch, cap, torch.from_numpy(k).cuda(), torch.from_numpy(c).cuda())
+    cache.seq_lens.copy_(torch.from_numpy(ctx))
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, "f32"), x, cache))
+    kr, cr, lens, status = k.astype(np.float64), c.astype(np.float64), ctx.copy(), np.zeros(batch, dtype=np.int32)
+    ref = orc.decode(U.oracle_config(wl), U.oracle_weights(w), x, kr, cr, lens, status, range(batch))
+    U.assert_close(out, ref, "f32", "out", _scale(ref))
+    U.assert_close(U.f64(cache.k), kr, "f32", "keys", _scale(kr))
+    U.assert_close(U.f64(cache.c), cr, "f32", "latents", _scale(cr))
+    np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
+    np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("lens", [[33, 1, 64, 5, 20], [33, 300, 1, 64, 20]], ids=str)   # projection of few, of many rows
+@pytest.mark.parametrize("shape", ["paper", "heads32", "heads16"])
+def test_chunk(shape, lens, paged):
+    """Per-token RoPE rows behind uneven prefixes; the last chunk does not fit."""
+    wl, prefix, cap = _wl(shape), [0, 37, 100, 255, 390], 400
+    cfg, cu = U.oracle_config(wl), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    w, x = _inputs(wl, int(cu[-1]), False)
+    k, c = W.draw_cache(wl, W.make_rng(wl), len(lens), cap)
+    if paged:
+        cache = U.PagedDeviceCache(wl, len(lens), 16, cap // 16, seed=3)
+        cache.store(torch.from_numpy(k).cuda(), torch.from_numpy(c).cuda())
+    else:
+        cache = U.DeviceCache(wl, len(lens), cap, torch.from_numpy(k).cuda(), torch.from_numpy(c).cuda())
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    out = U.f64(U.run_prefill_chunk(wl, U.upload_weights(w, "f32"), x, cu, cache))
+    kd, cd = (U.f64(t) for t in (cache.logical() if paged else (cache.k, cache.c)))
+    ow = U.oracle_weights(w)
+    for b, (n, p) in enumerate(zip(lens, prefix)):
+        rows, pos = slice(cu[b], cu[b + 1]), np.arange(p, p + n)
+        if p + n > cap:
+            assert not out[rows].any() and int(cache.seq_lens[b]) == p
+            continue
+        Q, K, C, G = orc.project_tokens(cfg, ow, x[rows], pos)
+        K = np.concatenate([k[b, :p].reshape(p, wl.n_kgroups, wl.head_dim), K])
+        C = np.concatenate([c[b, :p].reshape(p, wl.n_cgroups, wl.latent_dim), C])
+        L = np.stack([orc.attention_map_rows(cfg, Q[:, g], pos, K[:, cfg.k_of_group(g)]) @ C[:, cfg.c_of_group(g)]
+                      for g in range(wl.n_qgroups)], axis=1)
+        ref = orc.decode_heads(cfg, ow, L, G)
+        U.assert_close(out[rows], ref, "f32", f"{shape} {n} behind {p}", _scale(ref))
+        U.assert_close(kd[b, :p + n], K.reshape(p + n, -1), "f32", "keys", _scale(K))
+        U.assert_close(cd[b, :p + n], C.reshape(p + n, -1), "f32", "latents", _scale(C))
+        assert int(cache.seq_lens[b]) == p + n
+
+
+@pytest.mark.parametrize("gate", ["silu", "relu2", False])
+@pytest.mark.parametrize("shape", ["paper", "heads32"])
+def test_gates(shape, gate):
+    """The other gates in the decoder epilogues (few and many rows) and in the decode tails (5 and 40 splits)."""
+    wl = _wl(shape)
+    for lens in LENS.values():
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        w, x = _inputs(wl, int(cu[-1]), False)
+        ref, _, _ = orc.prefill(U.oracle_config(wl, gate), U.oracle_weights(w), x, cu)
+        U.assert_close(U.f64(U.run_prefill(wl, U.upload_weights(w, "f32"), x, cu, gate=gate)), ref, "f32", f"{lens}", _scale(ref))
+    ctx = np.array([0, 20, 130], dtype=np.int32)
+    w, x = _inputs(wl, 3, False)
+    k, c = W.draw_cache(wl, W.make_rng(wl), 3, 160)
+    ref = orc.decode(U.oracle_config(wl, gate), U.oracle_weights(w), x, k.astype(np.float64), c.astype(np.float64), ctx.copy(),
+                     np.zeros(3, dtype=np.int32), range(3))
+    for splits in (5, 40):
+        cache = U.DeviceCache(wl, 3, 160, torch.from_numpy(k).cuda(), torch.from_numpy(c).cuda())
+        cache.seq_lens.copy_(torch.from_numpy(ctx))
+        out = U.f64(U.run_decode(wl, U.upload_weights(w, "f32"), x, cache, num_splits=splits, gate=gate))
+        U.assert_close(out, ref, "f32", f"{splits} splits", _scale(ref))
