@@ -149,8 +149,6 @@ void generic_out_proj_f32in(const Dims &d, const gta_weights &w, const float *O,
 
 void launch_attn_prefill_rowwise(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,
                                  int batch, int64_t total, int max_len, void *L, hipStream_t st);
-void launch_finalize_decode_bf16(const Dims &d, const float *part, int nsum, int batch, const gta_cache &cache,
-                                 const int32_t *slots, const DecodeWs &ws, hipStream_t st);
 void launch_cached_len(const gta_cache &cache, const int32_t *slots, int batch, int32_t *oldlen, hipStream_t st);
 void generic_decode_attention(const Dims &d, const float *q, const int32_t *oldlen, const gta_cache &cache,
                               const int32_t *slots, int batch, int splits, float *part, hipStream_t st);
