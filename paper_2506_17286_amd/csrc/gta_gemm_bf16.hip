@@ -20,6 +20,7 @@
 
 #include <type_traits>
 
+#include "gta_lds_load.h"
 #include "gta_tuned.h"
 
 namespace gta {
@@ -30,7 +31,6 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 template <int BM_, int BN_, int BK_, int WGM_, int WGN_>
@@ -143,16 +143,6 @@ struct BigLoop {
   static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, X_BYTES = BM * BK * 2, STAGE = X_BYTES + BK * BN * 2;
   static constexpr int SMEM = NSTAGE * STAGE;
 };
-
-// 16 bytes per lane from rsrc + voff + soff to LDS offset lds + 16 * lane.  vmcnt counts it; the compiler does not
-// know that, so every wait for these loads is spelled out.
-__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff));
-}
-__device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {   // reads past `bytes` return 0
-  const uint64_t b = (uint64_t)base;
-  return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
-}
 
 // What the last four tiles fetch instead of operands: load j (0..7) of stage `s` of this wave.
 struct NoTail {

@@ -39,6 +39,7 @@
 
 #include <type_traits>
 
+#include "gta_lds_load.h"
 #include "gta_tuned.h"
 
 namespace gta {
@@ -51,7 +52,6 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -138,17 +138,6 @@ __device__ __forceinline__ float pair_max(float v) {
 __device__ __forceinline__ float pair_sum(float v) {
   const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// 16 bytes per lane from rsrc + voff to LDS offset lds + 16 * lane; reads past the buffer's end return 0.  vmcnt counts
-// it; the compiler does not know that, so every wait for these loads is spelled out.  (M0 holds nothing the compiler keeps.)
-__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc));
-}
-__device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {
-  const uint64_t b = (uint64_t)base;   // wave-uniform, which the compiler does not always see
-  return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)b), (unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32) & 0xffff),
-               (unsigned)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
 }
 
 // A scalar load, waited for in place: a vector load would make the compiler wait for every load in flight.
@@ -266,12 +255,12 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
         kt = Kb + row0 * wk2; ct = Cb + row0 * wc2;
       }
       if (k_loader(j)) {
-        const u32x4 r = buffer_of(kt, rows > 0 ? (rows - 1) * wk2 + T::K_ROW : 0u);
+        const u32x4 r = uniform_buffer_of(kt, rows > 0 ? (rows - 1) * wk2 + T::K_ROW : 0u);
 #pragma unroll
         for (int i = 0; i < KI; ++i) load_to_lds(r, kv[i], fill + j * T::TILE + (ki + T::NW * i) * T::K_PITCH);
       }
       if (c_loader(j)) {
-        const u32x4 r = buffer_of(ct, rows > 0 ? (rows - 1) * wc2 + T::C_ROW : 0u);
+        const u32x4 r = uniform_buffer_of(ct, rows > 0 ? (rows - 1) * wc2 + T::C_ROW : 0u);
 #pragma unroll
         for (int i = 0; i < CI; ++i) load_to_lds(r, cv[i], fill + j * T::TILE + T::K_BYTES + (ci + T::NW * i) * T::C_PITCH);
       }

@@ -11,6 +11,7 @@
 #include <math.h>
 
 #include "gta_epilogues.h"
+#include "gta_lds_load.h"
 #include "gta_tuned.h"
 
 namespace gta {
@@ -21,7 +22,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // weights side by side: W_Q | W_K | W_C | W_G, or one matrix
@@ -130,14 +130,6 @@ struct MidTile {
   static constexpr int PITCH = BN + 4, RED = BM * PITCH * 4;                     // a partial tile in LDS (fp32)
   static constexpr int SMEM = NSTAGE * STAGE > 2 * RED ? NSTAGE * STAGE : 2 * RED;
 };
-
-__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff));
-}
-__device__ __forceinline__ u32x4 buffer_of(const void *base, unsigned bytes) {   // reads past `bytes` return 0
-  const uint64_t b = (uint64_t)base;
-  return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
-}
 
 template <int BN, class Epi>
 __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOperands o, Epi epi) {
