@@ -94,7 +94,8 @@ struct DecAttnArgs {
   float *pacc, *pml;
 };
 
-// RoPE angle of position p and frequency f: reduced mod 2 pi in fp64, then fp32 sincos
+// RoPE angle of position p and frequency f, reduced mod 2 pi in fp64, then fp32 sincos: any base (rope_cos_sin_short needs
+// one of at least 1)
 __device__ __forceinline__ void rope_sincos(int p, double f, float &sn, float &cs) {
   const double ang = (double)p * f;
   const double k = rint(ang * 0.15915494309189535);
@@ -1498,7 +1499,9 @@ int tuned_decode(const Dims &d, const gta_weights &w, const void *x_new, int bat
   // weight row stream worse than the 256-byte pieces of the split-K kernel, while a long stream hides the partials'
   // sums: there only up to 8 sequences and 32K rows in all (1B shape, 8 behind 1000 rows 27.4 -> 26.3 us, 8 behind
   // 8192 43.8 -> 44.1, 64 behind 8192 190 -> 192; 8 x 128 + 1024 shape, 1 behind 1000 56.7 -> 53.5, 8 behind 8192
-  // 89.3 -> 90.2, 64 behind 2000 141 -> 155).
+  // 89.3 -> 90.2, 64 behind 2000 141 -> 155).  The line at a width of 1536 is a cautious one: with the paper layer's 1792
+  // columns the few-row kernel is ahead at every width tried (64 behind 2000: 768 36.2 -> 32.0, 1536 39.0 -> 34.0, 2048
+  // 39.8 -> 35.1, 3072 41.2 -> 37.5).
   const bool narrow_weights = batch <= 128 && d.H <= 1536;
   if (rows_gemm_ok(d) && rope_angles_small(d.rope, d.rope_base) && (narrow_weights || (batch <= 8 && (int64_t)batch * cache.max_seq <= 32768))) {
     launch_rows_proj_decode(d, w, x_new, batch, cache, slots, ws, st);

@@ -2,7 +2,7 @@
 // and sums in fp32, twice the rate of the vector ALU), for the shapes the conditions at the end of this file
 // name; everything else stays on the shape-generic kernels.
 //
-// The fp32 matrix instructions are slow next to everything that feeds them (64 cycles for 4096 products), so
+// The fp32 matrix instructions are slow next to everything that feeds them (64 cycles for 2048 products), so
 // the kernels here need no elaborate schedule: what decides is that every SIMD has work and that operands are
 // requested early.  The contraction index of an MFMA step is only a label: as long as both operands use the
 // same assignment of k to (step, lane half), any assignment computes the same sum.  Operands that are
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void gemm_tiles_f32_kernel(GemmOperands g, int
         for (int t = 0; t < TM; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[t][j], xb[j], acc[t], 0, 0, 0);
     }
   };
-  // loads run two tiles ahead of the LDS writes: a tile's 1024 cycles of MFMA do not cover a trip to memory
+  // loads run two tiles ahead of the LDS writes: a tile's 512 cycles of MFMA do not cover a trip to memory
   Regs r0, r1;
   gload(r0, 0);
   gload(r1, 1);

@@ -161,7 +161,7 @@ __device__ __forceinline__ WeightTile weight_tile(const bf16 *base, int64_t ld, 
   return WeightTile{base, ld, (unsigned)(31 * ld * 2) + (head_bytes ? head_bytes + 256u : 512u), head_bytes};
 }
 
-// acc[tn][tm][r]:  n = wn*128 + tn*32 + 8*(r/4) + 4*(lane/32) + r%4,  m = wm*128 + tm*32 + lane%32, wn = wave % 2, wm = wave / 2.
+// acc[tn][tm][r]:  n = wn*128 + tn*32 + 8*(r/4) + 4*(lane/32) + r%4,  m = wm*64 + tm*32 + lane%32, wn = wave % 2, wm = wave / 2.
 // `Abase` points at row m0 of the row operand.  K a multiple of 32, at least 128.  All loads have landed on return and
 // every wave has passed a barrier behind its last LDS read.
 template <class G, class Tail>
@@ -174,8 +174,8 @@ __device__ __forceinline__ void gemm_mainloop_big(const bf16 *__restrict__ Abase
   const int nk = K / T::BK;
   const int rv = min(rows_valid, T::BM);
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
-  // this wave's loads of a tile: rows 64 wave + 16 j + lane/4 of X (rows past the last valid one re-read it), k-rows
-  // 8 wave + 2 j + lane/32 of the weights
+  // this wave's loads of a tile: rows 32 wave + 16 j + lane/4 of X (rows past the last valid one re-read it), k-rows
+  // 4 wave + 2 j + lane/32 of the weights
   unsigned xv[LPW], wv[LPW];
 #pragma unroll
   for (int j = 0; j < LPW; ++j) {
@@ -388,9 +388,10 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
   const int width = a.width[seg];
   if constexpr (kBig) {
     if (rotate) {
-      // wave tile = one head: column j pairs with j + d_h/2.  32 groups of 4 pairs per lane (4 row blocks x
+      // wave tile = one head: column j pairs with j + d_h/2.  16 groups of 4 pairs per lane (2 row blocks x
       // 2 column blocks x 4 register quads); the table values of a group are asked for two groups ahead of
-      // their use (one after the other, every group would wait out a whole memory round trip: 9 us per tile)
+      // their use (one after the other, every group would wait out a whole memory round trip: 9 us per tile with
+      // four row blocks)
       constexpr int tiles_half = kHeadDim / 64;
       static_assert(T::TN == 2 * tiles_half, "a wave tile of the rotating segments is one head wide");
       constexpr int G = T::TM * tiles_half * 4, AHEAD = 2;
@@ -892,7 +893,7 @@ void launch(K kernel, const Args &a, int ntiles, hipStream_t st) {
 }  // namespace
 
 // The pipelined 256 x 256 tile against packed weights: widths in units of a 64-column group that
-// holds whole heads, an even number (>= 4) of k-tiles.
+// holds whole heads, at least four k-tiles of 32 (H in units of 128 like everything on this path).
 static bool proj_packed_ok(const Dims &d) {
   if (d.dh != 64 && d.dh != 128) return false;
   if (d.wq_w % d.dh || d.wk_w % d.dh || d.wc_w % 64 || d.wg_w % 64 || d.wq_w % 64 || d.wk_w % 64) return false;
@@ -906,7 +907,7 @@ static bool proj_direct_ok(const Dims &d) {
   return !(d.H % 64 || d.dl % 64 || d.wq_w % 128 || d.wk_w % 128 || d.wc_w % 128 || d.wg_w % 128);
 }
 static bool proj_direct_big(const Dims &d) {
-  // the pipelined loop takes an even number (>= 4) of k-tiles
+  // the pipelined loop takes at least four k-tiles of 32
   return proj_direct_ok(d) && !(d.wq_w % 256 || d.wk_w % 256 || d.wc_w % 256 || d.wg_w % 256) && d.H % 128 == 0 && d.H >= 256;
 }
 

@@ -8,7 +8,7 @@
 // wave's softmax runs in the shadow of the other's MFMAs) and are out of step, so that the prologue and the epilogue of
 // one, and the steps in which it waits at its barrier, are filled by the other; measured against one workgroup of
 // eight waves and 256 queries: fused kernel of 4 x 4096 tokens with heads of 64 300 -> 270 us, ragged batch of 112 K
-// tokens 18.9 -> 17.95 ms, 4 x 4096 tokens of the 1B shape 231 -> 225 us (whole calls 780 -> 760, 25.1 -> 24.5 ms, 509
+// tokens 18.9 -> 17.95 ms, 4 x 4096 tokens of the 1B shape 231 -> 225 us (whole calls 780 -> 760, 25.1 -> 24.0 ms, 509
 // -> 503).  Wider latents are covered by several workgroups that each recompute the scores.
 // Both products are computed transposed:
 //   S^T[key][query] = K . Q^T      (row operand: K tile from LDS, column operand: the wave's queries,
@@ -761,7 +761,7 @@ size_t attn_split_bytes(const Dims &d) {
 }
 
 bool attn_prefill_supported(const Dims &d, int max_len) {
-  // byte offsets inside one sequence's K / C rows are kept in 32 bits
+  // a sequence's K / C rows stay below 2 GiB: the limit the interface names for these kernels
   if ((int64_t)max_len * d.wc_w * 2 >= ((int64_t)1 << 31) || (int64_t)max_len * d.wk_w * 2 >= ((int64_t)1 << 31)) return false;
   if (d.dtype != GTA_BF16 || d.wq_w % 8 || d.wk_w % 8 || d.wc_w % 8) return false;
   return (d.dh == 128 && d.dl % 128 == 0) || (d.dh == 64 && d.dl % 64 == 0);

@@ -115,7 +115,7 @@ void launch_rows(const RowsOperands &g, int cols, const Epi &epi, hipStream_t st
 // 8 chunks, chunk c of row r in slot c ^ (r % 8) ^ (r / 8 % 2), so 8 (16) rows in a row read one logical chunk from
 // different 16-byte columns of 128 (256) bytes; weight rows of 16 (8) chunks, chunk c of k-row k in slot c ^ 4 (k % 4)
 // (c ^ 4 (k / 2 % 2)), so the four k-rows of a transpose read lie in different 64-byte columns.
-// Bound: the loads (786 KiB per tile at K = 2048, of which a CU takes 64 bytes per clock) and, with one tile per CU, the
+// Bound: the loads (768 KiB per tile at K = 2048, of which a CU takes 64 bytes per clock) and, with one tile per CU, the
 // read-MFMA chain of a step.  Measured against a split-K projection with fp32 partials in memory plus a finishing kernel
 // and two-stage 64-row tiles for decoder and W_O, whole calls: 1B shape 500 tokens 60.7 -> 47.9 us, 1000 82 -> 66, 1500
 // 105 -> 88; paper's layer 500 tokens 55 -> 43, 2000 84 -> 67; 8 x 128 + 1024 shape 1000 tokens 169 -> 130 us.  Four
