@@ -24,8 +24,12 @@
  *     gta_prefill_chunk and gta_cache_append then leave the slot as it was (no row stored, length
  *     unchanged) and the first two zero-fill the sequence's output rows.  (gta_prefill refuses
  *     max_seqlen > cache->max_seq on the host; a slot whose block table lacks a page for some row
- *     is flagged, its length is still set, rows without a page are not stored and the output rows
- *     are computed as usual.)
+ *     is flagged and its length left as it was, rows without a page are not stored and the output
+ *     rows are computed as usual.)
+ *   - Values that are not finite reach the rows that attend to them.  A token's NaN or infinity
+ *     reaches no earlier row in fp32 and on the shape-generic kernels; the bf16 MFMA prefill kernels
+ *     work on blocks of 32 keys and may turn up to 31 rows before it into NaN, too.  Padding inside
+ *     a sequence should be finite there.  No sequence reaches another.
  *   - Re-entrant.  Two calls that touch the same cache slot, output or workspace must be ordered
  *     by the caller (same stream or events).  The only process state is a table of "this kernel may
  *     use more than 64 KiB of LDS on this device" attributes, set idempotently on the first launch of
@@ -179,7 +183,9 @@ GTA_API int gta_decode(const gta_config *cfg, const gta_weights *weights, const 
  * ends).  The call allocates and frees nothing.
  *   - A call whose gta_workspace_bytes(cfg, GTA_MODE_DECODE, batch, 0, cache->max_seq, num_splits)
  *     exceeds GTA_STATIC_SCRATCH_BYTES returns GTA_ERR_WORKSPACE and does nothing (32 MiB covers, e.g.,
- *     64 sequences at the 1B layer shape with any context length; use gta_decode beyond that).
+ *     64 sequences at the 1B layer shape with any context length; use gta_decode beyond that).  With
+ *     num_splits 0 the library falls back to context slices of at least 256 rows where its own count does
+ *     not fit: such a call runs if the formula fits for num_splits = max(1, cache->max_seq / 256).
  *   - All calls on one GPU share that GPU's array: calls that may overlap in time (different streams,
  *     different host threads) race; order them.  The array keeps the last call's contents and nothing
  *     in it needs clearing between calls.
@@ -231,7 +237,9 @@ GTA_API int gta_output_projection(const gta_config *cfg, const gta_weights *weig
 /* Attention stage of the prefill (Sec. 3.3, reformulated form): for every map group g and token t,
  * l_out[t, g*d_l : (g+1)*d_l] = sum_{j<=t} Softmax_j(q_g[t].k_{k(g)}[j] / sqrt(d_h)) c_{c(g)}[j].
  *   q [total, n_q*d_h], k [total, n_k*d_h] (both already rotated), c [total, n_c*d_l],
- *   l_out [total, n_q*d_l]; all device, element type = cfg->dtype; cu_seqlens as in gta_prefill. */
+ *   l_out [total, n_q*d_l]; all device, element type = cfg->dtype; cu_seqlens as in gta_prefill.
+ * (Without scratch memory: a launch of few workgroups whose keys gta_prefill splits over several of them runs
+ * unsplit here.) */
 GTA_API int gta_prefill_attention(const gta_config *cfg, const void *q, const void *k, const void *c,
                                   const int32_t *cu_seqlens, int32_t batch, int64_t total_tokens,
                                   int32_t max_seqlen, void *l_out, void *hip_stream);
@@ -282,10 +290,10 @@ GTA_API const char *gta_strerror(int code);
  * 128), H a multiple of 128; decode in addition needs cache rows of a compiled shape: heads of 128
  * with (n_k, n_q, n_c, d_l) in {(4,4,1,512), (8,8,1,1024), (4,8,1,512), (4,4,2,512), (4,8,2,512),
  * (4,4,4,512)}, or one key of 64 with latents of 128: n_c = 1 with n_q in {3,5,6}, n_c = 2 with n_q in
- * {6,10}.  fp32 configurations answer 0; stage by stage they run on fp32 MFMA kernels where the shape allows
- * (widths in units of 64, heads of at most 64; attention: heads of 32, 64 or 128, latents in units of 64;
- * decode: one key of 64 and one latent of 128 for at most 16 maps).  With GTA_DEBUG set in the environment a bf16 call that takes the generic kernels says so
- * on stderr. */
+ * {6,10}.  fp32 configurations answer 0; stage by stage they run on fp32 MFMA kernels where the shape
+ * allows (widths in units of 64, heads of at most 64; attention: heads of 32, 64 or 128, latents in units
+ * of 64; decode: one key of 64 and one latent of 128 for at most 16 maps, rope_base at least 1).  With
+ * GTA_DEBUG set in the environment a bf16 call that takes the generic kernels says so on stderr. */
 GTA_API int gta_uses_tuned_kernels(const gta_config *cfg, int mode);
 
 #ifdef __cplusplus
