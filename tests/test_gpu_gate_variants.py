@@ -1,7 +1,7 @@
 """GPU parity of the gate nonlinearities other than Sigmoid (Silu, ReLU^2: the ablation on the choice of
 nonlinearity) and of the gate switched off, on every kernel that applies the gate: the shape-generic
-path, the MFMA value-decoder kernels (pairs of heads, several heads per tile, one head per tile), the
-decoder fused into the attention kernel, and both decode tails."""
+path, the value-decoder kernel of short prefills, the decoder fused into the attention kernel, and the decode
+tails.  (The 256-row value-decoder kernels: test_gpu_prefill_gemms.py; the fp32 ones: test_gpu_f32_kernels.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = {
     "generic_f32": W.Workload("g", "prefill", 1, 64, 64, 4, 2, 2, 1, 16, 32, "f32", True, seed=21),
-    "1b": W.WORKLOADS[1],                       # decoder_pair_kernel, decode_tail1_kernel
-    "paper": W.PAPER_WORKLOADS[0],              # decoder fused into the attention kernel, decode_tail_kernel
-    "paper_nq6": W.scaled(W.PAPER_WORKLOADS[0], d_model=768, n_heads=12, n_qgroups=6),   # decoder_gemm_kernel, 64-wide tile
+    "1b": W.WORKLOADS[1],                       # decode_tail1_kernel, decode_tail_kernel
+    "paper": W.PAPER_WORKLOADS[0],              # decoder fused into the attention kernel, decode_tail_narrow_kernel
+    "paper_nq6": W.scaled(W.PAPER_WORKLOADS[0], d_model=768, n_heads=12, n_qgroups=6),   # heads of 64
     "multi": W.scaled(W.WORKLOADS[1], d_model=512, n_heads=4, n_qgroups=2, n_kgroups=1, n_cgroups=1, latent_dim=128),
 }
 

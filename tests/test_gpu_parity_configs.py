@@ -1,7 +1,7 @@
 """GPU parity at the full sizes of the five benchmark workloads, in the launch configuration
 bench.py times.  Configs 1-4 compare every output element of every sequence with the fp64 oracle.
 Config 5 (135k packed tokens at d_model 4096) compares every row of its two shortest sequences and,
-on each of the 16 sequences, the rows around every 256-query tile boundary plus at least 256 random
+on each of the 16 sequences, the rows around every 128-query tile boundary plus at least 256 random
 rows; the sample is stated in the test."""
 import numpy as np
 import pytest
@@ -103,12 +103,12 @@ def test_config4_decode_b8_ctx32k_bf16():
 def test_config5_varlen_prefill_bf16():
     """16 ragged sequences (lengths uniform in [512, 16384]), d_model 4096, 32 heads, 8 maps,
     d_l 1024.  Oracle: every row of the two shortest sequences; on each of the other 14 the first and
-    last rows, the rows around every multiple of the 256-query tile and around the small block edges,
-    and 256 further random rows (320 to 450 rows per sequence); every cached key / latent row of all 16."""
+    last rows, the rows around every multiple of the 128-query tile and around the small block edges,
+    and 256 further random rows (320 to 640 rows per sequence); every cached key / latent row of all 16."""
     wl = W.WORKLOADS[4]
     lens = W.draw_seqlens(wl, W.make_rng(wl))
     order = [int(i) for i in np.argsort(lens)]
-    _check_prefill_workload(wl, full_seqs=order[:2], sampled_seqs=order[2:], n_random=256, tile=256)
+    _check_prefill_workload(wl, full_seqs=order[:2], sampled_seqs=order[2:], n_random=256, tile=128)
 
 
 def test_paper_layer_prefill_b32_t2048_bf16():
@@ -205,8 +205,8 @@ def test_tuned_decode_batches_that_do_not_fill_the_last_workgroup(shape, batch):
 @pytest.mark.parametrize("shape,batch,with_wo", [("1b", 300, False), ("1b", 257, True), ("paper", 300, False),
                                                  ("paper", 1100, True), ("wide", 256, False)])
 def test_tuned_decode_large_batches(shape, batch, with_wo):
-    """From 256 sequences on the decode tail runs as a GEMM on bf16 operands (beyond 1024 on the 256-row
-    tiles): short ragged contexts incl. empty ones and a full slot, every output element against the oracle."""
+    """From 256 sequences on the decode tail runs as a GEMM on bf16 operands (on the 64-row tiles that split K,
+    up to 768 of them): short ragged contexts incl. empty ones and a full slot, every output element against the oracle."""
     if shape == "1b":
         base = W.WORKLOADS[2]
     elif shape == "paper":
@@ -269,8 +269,10 @@ def test_tuned_prefill_ragged_small(shape, with_wo, tokens):
         base = W.scaled(W.WORKLOADS[1], **WIDE_ROW_GROUPINGS[shape])
     else:
         base = W.WORKLOADS[1] if shape == "1b" else W.WORKLOADS[4]
-    # calls of few tokens take the short-prefill kernels (split-K projection on 64-row tiles; the limit
-    # depends on the shape and is at most 4096 tokens), longer ones the 256-row tiles: both on a ragged mix
+    # calls of few tokens take the kernels for few rows and the 64-row tiles that split K (up to 768 tiles of 64 x
+    # 128), longer ones the 256-row tiles, on a ragged mix: with many tokens the projections of at least 1472 columns
+    # (1b, wide, paper, paper_nc2, packed128_pad, q8k4c2, c4) take the latter.  Every GEMM of every shape on its 256-row
+    # tiles is checked stage by stage in test_gpu_prefill_gemms.py
     lens = [1, 37, 256, 300, 129, 64]
     slots = [5, 0, 3, 1, 6, 2]
     if tokens == "many":

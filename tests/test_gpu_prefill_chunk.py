@@ -64,7 +64,7 @@ def test_prefix_then_chunk_equals_one_pass(shape, with_wo):
 
 @pytest.mark.parametrize("shape", ["1b", "paper"])
 def test_chunk_beyond_the_short_prefill_limit(shape):
-    """A chunk call with more tokens than the short-prefill kernels take (1536 at the 1B shape, 4096 at the
+    """A chunk call with more tokens than the short-prefill projection takes (1728 at the 1B shape, 3456 at the
     paper's): 256-row projection tiles with per-token RoPE rows.  A long and a short chunk behind 100 and
     650 cached rows."""
     long_len = 1900 if shape == "1b" else 4500

@@ -1,7 +1,7 @@
 """The prefill's GEMMs at the edges of their tiles: the few-row kernel, the 64-row tiles that split K over their waves
 (three stages of 64: contractions of one, two and more) and the 256 x 256 tiles (operands loaded straight into LDS, eight
 waves, four stages of 32).  One valid row in the last row tile and full row tiles, contractions that leave the stages at
-each phase, two heads side by side in a weight tile, the packed weights, the gate on and off.
+each phase, two heads side by side in a weight tile, several heads and one, the packed weights, every gate.
 
 Reference: float64 on the same bf16 inputs.  Bounds: the bf16 tolerances of the parity gate, the max-abs one scaled by
 the largest reference value (the outputs carry one bf16 rounding, 2^-9 of their size)."""
@@ -26,13 +26,29 @@ def _close(got, ref, what):
     U.assert_close(U.f64(got), r, "bf16", what, max(1.0, float(np.abs(r).max())))
 
 
+LAYERS = {
+    "k256": _wl(), "k384": _wl(d_model=384, latent_dim=384), "k640": _wl(d_model=640, n_heads=8, latent_dim=512),
+    "k128": _wl(d_model=128), "slim": _wl(head_dim=64, n_heads=8, n_qgroups=4, latent_dim=64),
+    "packed": _wl(head_dim=64, n_heads=20, n_qgroups=5, n_kgroups=1, latent_dim=128, d_model=256),
+    "multi128": _wl(latent_dim=128), "single128": _wl(n_qgroups=4, latent_dim=128),   # several heads of 128 per tile, one
+}
+
+
 @pytest.mark.parametrize("gate", [True, False])
 @pytest.mark.parametrize("rows", [33, 64, 65, 449, 24832, 24833])
-@pytest.mark.parametrize("wl", [_wl(), _wl(d_model=384, latent_dim=384), _wl(d_model=640, n_heads=8, latent_dim=512),
-                                _wl(d_model=128), _wl(head_dim=64, n_heads=8, n_qgroups=4, latent_dim=64),
-                                _wl(head_dim=64, n_heads=20, n_qgroups=5, n_kgroups=1, latent_dim=128, d_model=256)],
-                         ids=["k256", "k384", "k640", "k128", "slim", "packed"])
-def test_prefill_gemms(wl, rows, gate):
+@pytest.mark.parametrize("layer", list(LAYERS))
+def test_prefill_gemms(layer, rows, gate):
+    _check(LAYERS[layer], rows, gate)
+
+
+@pytest.mark.parametrize("gate", ["silu", "relu2"])
+@pytest.mark.parametrize("rows", [65, 24833])
+@pytest.mark.parametrize("layer", list(LAYERS))
+def test_other_gates(layer, rows, gate):
+    _check(LAYERS[layer], rows, gate)
+
+
+def _check(wl, rows, gate):
     cfg = B.config_of(wl)
     cfg.gate = B.GATE_CODES[gate]
     g = torch.Generator(device="cuda")
@@ -58,7 +74,9 @@ def test_prefill_gemms(wl, rows, gate):
     L, z, heads = rand(rows, nq * dl), rand(rows, nh * dh), mk(nh * dh)
     B.gta_prefill_decoder(cfg, gw, L, z, rows, heads)
     ref = torch.cat([L[:, h // (nh // nq) * dl:][:, :dl].double() @ w["wp"][h].double() for h in range(nh)], dim=1)
-    _close(heads, ref * torch.sigmoid(z.double()) if gate else ref, "decoder")
+    zd = z.double()
+    _close(heads, ref * {True: torch.sigmoid(zd), False: 1., "silu": zd * torch.sigmoid(zd), "relu2": zd.clamp(min=0.) ** 2}[gate],
+           "decoder")
     o = mk(H)
     B.gta_output_projection(cfg, gw, heads, rows, o)
     _close(o, heads.double() @ w["wo"].double(), "output projection")
