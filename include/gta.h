@@ -28,8 +28,8 @@
  *     rows are computed as usual.)
  *   - Values that are not finite reach the rows that attend to them.  A token's NaN or infinity
  *     reaches no earlier row in fp32 and on the shape-generic kernels; the bf16 MFMA prefill kernels
- *     work on blocks of 32 keys and may turn up to 31 rows before it into NaN, too.  Padding inside
- *     a sequence should be finite there.  No sequence reaches another.
+ *     work on blocks of 32 queries and 32 keys and may turn rows less than 64 tokens before it into
+ *     NaN, too.  Padding inside a sequence should be finite there.  No sequence reaches another.
  *   - Re-entrant.  Two calls that touch the same cache slot, output or workspace must be ordered
  *     by the caller (same stream or events).  The only process state is a table of "this kernel may
  *     use more than 64 KiB of LDS on this device" attributes, set idempotently on the first launch of

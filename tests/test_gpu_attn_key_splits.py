@@ -120,3 +120,27 @@ def test_nan_passes_the_merge(where, n):
     dev = {name: torch.from_numpy(a).to("cuda", torch.bfloat16) for name, a in w.items() if a is not None}
     out = U.f64(U.run_prefill_chunk(wl, dev, x, np.array([0, n]), cache, gate=False)).reshape(n, wl.n_qgroups, -1)
     assert np.isnan(out[:, 0]).all() and np.isfinite(out[:, 1:]).all()
+
+
+@pytest.mark.parametrize("bound", [None, 2304])          # key splits, one key half
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_how_far_a_nan_token_reaches_back(shape, bound):
+    """A NaN token behind a prefix that is no multiple of 32: rows at least 64 tokens before it, and the other sequences of
+    the call, are not affected."""
+    lens, prefix, bad, cap = [150, 40] + [1] * 13, [1500, 41] + [9] * 13, 120, 2304
+    wl, w, x, rng = _setup(shape, sum(lens))
+    k, c = W.draw_cache(wl, rng, len(lens), cap)
+    cache = U.DeviceCache(wl, len(lens), cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    cu, xd = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), B.to_device(x, "bf16")
+    xd[bad] = float("nan")
+    cfg, cut = B.config_of(wl), torch.from_numpy(cu).cuda()
+    most = max(lens) if bound is None else bound
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_PREFILL_CHUNK, len(lens), len(x), most))
+    out = torch.empty((len(x), wl.n_heads * wl.head_dim), dtype=torch.bfloat16, device="cuda")
+    weights = U.upload_weights(w, "bf16")
+    B.gta_prefill_chunk(cfg, B.make_weights(weights), xd, cut, len(lens), len(x), most, cache.struct, None, out, ws)
+    got = U.f64(out)
+    _check(wl, w, x[:bad - 63], k[0].astype(np.float64), c[0].astype(np.float64), prefix[0], got[:bad - 63], f"{shape} before")
+    assert np.isnan(got[bad:lens[0]]).all()
+    _check(wl, w, x[cu[1]:cu[2]], k[1].astype(np.float64), c[1].astype(np.float64), prefix[1], got[cu[1]:cu[2]], f"{shape} beside")
