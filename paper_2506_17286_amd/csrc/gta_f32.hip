@@ -10,6 +10,8 @@
 // eight, one k per step.
 #include <math.h>
 
+#include <algorithm>
+
 #include "gta_epilogues.h"
 #include "gta_tuned.h"
 
@@ -596,9 +598,22 @@ bool f32_gemms_ok(const Dims &d, int64_t M) {
   return !(d.wq_w % 64 || d.wk_w % 64 || d.wc_w % 64 || d.wg_w % 64 || d.H % 64 || d.dl % 16);
 }
 
+// Latent columns of a workgroup of the attention kernel and how many such slices there are.
+static int attn_slice(const Dims &d) { return d.dl % 128 == 0 ? 128 : 64; }
+
 bool f32_attn_ok(const Dims &d, int batch, int max_len) {
   if (((int64_t)max_len / 32 + 1) * batch * d.nq * (d.dl / 64 + 1) >= (1 << 24)) return false;
-  return d.dtype == GTA_F32 && (d.dh == 32 || d.dh == 64 || d.dh == 128) && d.dl % 64 == 0;
+  if (d.dtype != GTA_F32 || (d.dh != 32 && d.dh != 64 && d.dh != 128) || d.dl % 64) return false;
+  // Many sequences of a few tokens: a workgroup costs what 32 queries cost, 5 to 7 us a round of the chip, and every latent
+  // slice forms the scores again, where the shape-generic kernel has a wave per row.  MFMA / shape-generic, 400 sequences:
+  // heads of 64, 5 maps, latent of 128 4 tokens 26 / 19 us, 5 26 / 33; heads of 128 (one workgroup per CU), 4 maps, latent of
+  // 128 6 tokens 52 / 42, 8 53 / 64; latent of 512 (4 slices) 8 tokens 187 / 104, 13 197 / 251; 8 maps, latent of 1024 (8
+  // slices) 12 tokens 774 / 493, 16 786 / 911.  Launches that the chip holds at once keep the MFMA kernel (8 x 8 tokens of
+  // the last shape, 512 workgroups: 17 / 25).
+  const int nslice = d.dl / attn_slice(d);
+  const bool one_per_cu = d.dh + attn_slice(d) >= 256;
+  const int few = std::min(12, std::max(one_per_cu ? 6 : 4, 2 * nslice));
+  return !(max_len <= few && (int64_t)batch * d.nq * nslice > (one_per_cu && max_len <= 4 ? 256 : 512));
 }
 
 // one key and one latent for all maps, pages that hold whole steps of 16 rows
@@ -660,8 +675,8 @@ void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, cons
   a.q = q; a.k = k; a.c = c; a.L = L; a.cu = cu; a.per_seq = (int)(total / batch); a.max_len = max_len;
   a.nq = d.nq; a.qpk = d.qpk; a.qpc = d.qpc; a.wq_w = d.wq_w; a.wk_w = d.wk_w; a.wc_w = d.wc_w; a.dl = d.dl;
   a.n_qtiles = (max_len + 31) / 32; a.batch = batch; a.scale_log2e = d.scale * 1.4426950408889634f;
-  const bool wide = d.dl % 128 == 0;
-  a.nslice = d.dl / (wide ? 128 : 64);
+  const bool wide = attn_slice(d) == 128;
+  a.nslice = d.dl / attn_slice(d);
   const unsigned grid = (unsigned)a.n_qtiles * batch * d.nq * a.nslice;
   auto launch = [&](auto kernel, int dlw) {
     const int smem = 4 * 32 * (dlw + 4) * (int)sizeof(float);

@@ -212,3 +212,15 @@ def test_gates(shape, gate):
         cache.seq_lens.copy_(torch.from_numpy(ctx))
         out = U.f64(U.run_decode(wl, U.upload_weights(w, "f32"), x, cache, num_splits=splits, gate=gate))
         U.assert_close(out, ref, "f32", f"{splits} splits", _scale(ref))
+
+
+@pytest.mark.parametrize("longest", [4, 5, 6, 7])
+@pytest.mark.parametrize("shape", ["paper", "heads32", "latent256", "heads128"])
+def test_prefill_of_many_tiny_prompts(shape, longest):
+    """Both sides of the lengths up to which such a batch stays on the kernel with a wave per row."""
+    wl, lens = _wl(shape), [longest] + list(np.random.default_rng(longest).integers(1, longest + 1, 599))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    w, x = _inputs(wl, int(cu[-1]), False)
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "f32"), x, cu))
+    ref, _, _ = orc.prefill(U.oracle_config(wl), U.oracle_weights(w), x, cu)
+    U.assert_close(out, ref, "f32", shape, _scale(ref))
