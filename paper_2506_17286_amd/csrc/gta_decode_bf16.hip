@@ -458,8 +458,8 @@ __global__ __launch_bounds__(256, S::OCC) void decode_attn_kernel(DecAttnArgs a,
     float mx = sm[0][g];
     for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sm[w][g]);
     float ls = 0.f;
-    for (int w = 0; w < kWaves; ++w)
-      if (sm[w][g] > -INFINITY) ls += sl[w][g] * fast_exp2(sm[w][g] - mx);
+    for (int w = 0; w < kWaves; ++w)   // no maximum: a wave without rows (sum 0) or with nothing but NaN (sum NaN)
+      ls = fmaf(sl[w][g], sm[w][g] > -INFINITY ? fast_exp2(sm[w][g] - mx) : 1.f, ls);
     pm[2 * g] = mx;
     pm[2 * g + 1] = ls;
   }
@@ -782,8 +782,8 @@ __global__ __launch_bounds__(256) void decode_narrow_kernel(DecAttnArgs a, RopeF
     float mx = sm[0][g];
     for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sm[w][g]);
     float ls = 0.f;
-    for (int w = 0; w < kWaves; ++w)
-      if (sm[w][g] > -INFINITY) ls += sl[w][g] * fast_exp2(sm[w][g] - mx);
+    for (int w = 0; w < kWaves; ++w)   // no maximum: a wave without rows (sum 0) or with nothing but NaN (sum NaN)
+      ls = fmaf(sl[w][g], sm[w][g] > -INFINITY ? fast_exp2(sm[w][g] - mx) : 1.f, ls);
     pm[2 * g] = mx;
     pm[2 * g + 1] = ls;
   }
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(Dims d, const float
     float ls = 0.f;
     for (int s = lane; s < splits; s += 64) {
       const float m = pm[s * ms];
-      if (m > -INFINITY) ls += exp2f(m - mx) * pm[s * ms + 1];
+      ls = fmaf(pm[s * ms + 1], m > -INFINITY ? exp2f(m - mx) : 1.f, ls);   // no maximum: no rows (sum 0) or nothing but NaN (sum NaN)
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(512) void decode_tail_kernel(Dims d, const float *_
     if (live)
       for (int s = lane; s < splits; s += 64) {
         const float m = pm[s * ms];
-        if (m > -INFINITY) ls += exp2f(m - mx) * pm[s * ms + 1];
+        ls = fmaf(pm[s * ms + 1], m > -INFINITY ? exp2f(m - mx) : 1.f, ls);   // no maximum: no rows (sum 0) or nothing but NaN (sum NaN)
       }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(512) void decode_tail_kernel(Dims d, const float *_
       float w = 0.f;
       if (live) {
         const float m = pm[s * ms];
-        if (m > -INFINITY) w = exp2f(m - mx) * inv;
+        w = (m > -INFINITY ? exp2f(m - mx) : 0.f) * inv;   // NaN everywhere if the sum is
       }
       wt[r * splits + s] = w;
     }
@@ -1301,7 +1301,7 @@ __global__ __launch_bounds__(256) void decode_combine_gate_kernel(Dims d, const 
     float ls = 0.f;
     for (int s = lane; s < splits; s += 64) {
       const float m = pm[s * ms];
-      if (m > -INFINITY) ls += exp2f(m - mx) * pm[s * ms + 1];
+      ls = fmaf(pm[s * ms + 1], m > -INFINITY ? exp2f(m - mx) : 1.f, ls);   // no maximum: no rows (sum 0) or nothing but NaN (sum NaN)
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);

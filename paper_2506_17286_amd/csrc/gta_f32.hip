@@ -555,7 +555,8 @@ __global__ __launch_bounds__(256, 2) void decode_attn_f32_kernel(DecF32 a) {
     for (int w = 1; w < 4; ++w) rm = fmaxf(rm, sm[w][tid]);
     float ls = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) ls += sm[w][tid] > -INFINITY ? sl[w][tid] * __builtin_amdgcn_exp2f(sm[w][tid] - rm) : 0.f;
+    for (int w = 0; w < 4; ++w)   // no maximum: a wave without rows (sum 0) or with nothing but NaN (sum NaN)
+      ls = fmaf(sl[w][tid], sm[w][tid] > -INFINITY ? __builtin_amdgcn_exp2f(sm[w][tid] - rm) : 1.f, ls);
     pml[2 * tid] = rm;
     pml[2 * tid + 1] = ls;
   }

@@ -358,9 +358,10 @@ __device__ void wave_attend(const float *qw, const T *Kb, int64_t kstride, const
       for (int e = 0; e < dh; ++e) a += qw[e] * ldf(kr, e);
       s = a;
     }
-    const float m_new = fmaxf(m, wave_max(s));
-    const float corr = expf(m - m_new);
-    const float p = valid ? expf(s - m_new) : 0.f;
+    // no maximum as long as all scores are NaN or have overflowed to -inf
+    const float m_new = fmaxf(m, wave_max(s)), ref = m_new > -INFINITY ? m_new : 0.f;
+    const float corr = expf(m - ref);
+    const float p = valid ? expf(s - ref) : 0.f;
     l = l * corr + wave_sum(p);
 #pragma unroll
     for (int i = 0; i < NACC; ++i) acc[i] *= corr;
@@ -506,7 +507,7 @@ __global__ void decode_combine_kernel(Dims d, const float *part, const int32_t *
     for (int s = threadIdx.x; s < splits; s += 64) {
       const float ms = pb[s * sstride + d.dl];
       wt[s] = ms > -INFINITY ? expf(ms - mx) : 0.f;
-      if (ms > -INFINITY) lsum += wt[s] * pb[s * sstride + d.dl + 1];
+      lsum = fmaf(pb[s * sstride + d.dl + 1], ms > -INFINITY ? wt[s] : 1.f, lsum);   // no maximum: no rows (sum 0) or nothing but NaN (sum NaN)
     }
     const float inv = 1.0f / wave_sum(lsum);
     for (int s = threadIdx.x; s < splits; s += 64) wt[s] *= inv;

@@ -88,3 +88,29 @@ def test_workspace_of_a_full_batch_serves_fewer_sequences(most, cap):
         again = U.DeviceCache(wl, most, cap, k, c, lens.clone())
         ref = U.f64(U.run_decode(wl, wdev, x[:batch], again))
         U.assert_close(U.f64(out), ref, "f32", f"{batch} sequences", max(1.0, float(np.abs(ref).max())))
+
+
+@pytest.mark.parametrize("splits", [4, 80])             # 80: more than the one-round-trip tails take
+@pytest.mark.parametrize("family,dtype,batch", [("paper", "f32", 5), ("tiny", "f32", 5), ("paper", "bf16", 5), ("1b", "bf16", 5),
+                                                ("1b", "bf16", 64), ("1b", "bf16", 256), ("wide", "bf16", 5)])
+def test_a_context_split_of_nothing_but_nan(family, dtype, batch, splits):
+    """NaN keys that fill whole splits (256 rows in 4, 1280 in 80) and a NaN query leave their sequence without a result,
+    whichever merge follows, and no other sequence is affected."""
+    base = {"paper": W.PAPER_WORKLOADS[1], "1b": W.WORKLOADS[3], "wide": W.WORKLOADS[4], "tiny": W.WORKLOADS[0]}[family]
+    wl = W.scaled(base, kind="decode", d_model=256, dtype=dtype, seed=5400)
+    rng, cap = W.make_rng(wl), 256 if splits == 4 else 1280
+    wdev = U.upload_weights(W.draw_weights(wl, rng, std=wl.d_model ** -0.5), dtype)
+    x, gen = W.draw_hidden(wl, rng, batch), torch.Generator(device="cuda").manual_seed(1)
+    k, c = (torch.randn((batch, cap, width), device="cuda", generator=gen).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+            for width in wl.kv_width)
+    lens = torch.full((batch,), cap - 1, dtype=torch.int32, device="cuda")
+
+    def step(x):
+        return U.run_decode(wl, wdev, x, U.DeviceCache(wl, batch, cap, k.clone(), c.clone(), lens.clone()), num_splits=splits, gate=False)
+    clean = step(x)
+    k[1, 64:128 if splits == 4 else 96] = float("nan")
+    x[3] = np.nan
+    out = step(x)
+    assert torch.isfinite(clean).all() and torch.isnan(out[1]).all() and torch.isnan(out[3]).all()
+    others = [b for b in range(batch) if b not in (1, 3)]
+    assert torch.equal(out[others], clean[others])

@@ -115,16 +115,17 @@ def _decode_stage(wl, q, k, c, splits):
 
 
 @pytest.mark.parametrize("splits", [1, 5, 40])
-@pytest.mark.parametrize("step", [0, 1, 3])
-def test_decode_step_of_overflowed_scores(step, splits):
-    wl, n = _wl("paper"), 300
-    q, k = _overflowing(1, wl.head_dim, n, slice(16 * step, 16 * step + 16))
+@pytest.mark.parametrize("shape,first,last", [("paper", 0, 16), ("paper", 16, 32), ("paper", 48, 64), ("heads32", 0, 64)])   # blocks of 16, 64
+def test_decode_step_of_overflowed_scores(shape, first, last, splits):
+    wl, n = _wl(shape), 300
+    q, k = _overflowing(wl.n_kgroups, wl.head_dim, n, slice(first, last))
     q = np.broadcast_to(q, (1, wl.n_qgroups, wl.head_dim))
     c = np.random.default_rng(2).standard_normal((n, wl.latent_dim)).astype(np.float32)
     got = _decode_stage(wl, q, k.reshape(1, n, -1), c[None], splits)
     cfg = U.oracle_config(wl)
     for g in range(wl.n_qgroups):
-        ref = orc.attention_map_rows(cfg, q[:, g].astype(np.float64), np.array([n - 1]), k[:, 0].astype(np.float64)) @ c.astype(np.float64)
+        kg = k[:, cfg.k_of_group(g)].astype(np.float64)
+        ref = orc.attention_map_rows(cfg, q[:, g].astype(np.float64), np.array([n - 1]), kg) @ c.astype(np.float64)
         U.assert_close(got[:, g], ref, "f32", f"group {g}", max(1.0, float(np.abs(ref).max())))
 
 
