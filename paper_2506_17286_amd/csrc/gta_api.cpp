@@ -399,7 +399,7 @@ int gta_prefill_attention(const gta_config *cfg, const void *q, const void *k, c
   if (total_tokens == 0 || max_seqlen == 0) return GTA_OK;
   hipStream_t st = (hipStream_t)hip_stream;
   if (attn_prefill_supported(d, max_seqlen))
-    launch_attn_prefill_bf16(d, q, k, c, cu_seqlens, batch, total_tokens, max_seqlen, l_out, nullptr, nullptr, st);
+    launch_attn_prefill_bf16(d, q, k, c, cu_seqlens, batch, total_tokens, max_seqlen, l_out, nullptr, st);
   else if (f32_attn_ok(d, batch, max_seqlen))
     launch_attn_prefill_f32(d, (const float *)q, (const float *)k, (const float *)c, cu_seqlens, batch, total_tokens, max_seqlen,
                             (float *)l_out, st);

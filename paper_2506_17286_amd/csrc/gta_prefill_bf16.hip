@@ -105,12 +105,15 @@ struct AttnArgs {
   // already in them behind the prefix[b] rows cached before (prefix[b] < 0: sequence skipped, zero output)
   const int32_t *prefix, *slots; int max_seq;
   PageMap pm; int ps_shift;   // cache mode on a block-table layout: page_size = 1 << ps_shift, a multiple of BK
-  // key range split over up to `splits` workgroups (not fused), a sequence's over as many as keep split_tiles key tiles
-  // each: they write un-normalised fp32 sums pacc [split, token, n_q*d_l] and (maximum in log2 units, sum) pml [split,
+  // key range split over up to `splits` workgroups (not fused), a sequence's over as many as keep up to 2^split_shift key
+  // tiles each: they write un-normalised fp32 sums pacc [split, token, n_q*d_l] and (maximum in log2 units, sum) pml [split,
   // token, n_q, column slice], merged by attn_merge_kernel.  A sequence that is not split writes its rows itself.
-  int splits, split_tiles; float *pacc; float2 *pml; int64_t total; const int32_t *seq_id;
+  // Where fewer than `splits` are used, their number is in the last one's entry, negated, in place of the sum.
+  int splits, split_shift; float *pacc; float2 *pml; int64_t total;
 };
-__device__ __forceinline__ int splits_of(const AttnArgs &a, int keys) { return max(min((keys + 31) / 32 / a.split_tiles, a.splits), 1); }
+// rounded up: a split of 9 tiles is ahead of a chain of 17 (1B shape, 40 tokens behind 700 rows of a slot of 4096 51.8 -> 48.3
+// us, 4 x 40 60.2 -> 57.2, 40 behind 1100 of 8192 52.2 -> 50.1, 200 behind 900 of 2048 64.1 -> 62.1)
+__device__ __forceinline__ int splits_of(const AttnArgs &a, int keys) { return max(min((keys + (32 << a.split_shift) - 1) >> (5 + a.split_shift), a.splits), 1); }
 
 // LDS of the fused value decoder: the normalised BQ x DLW tile (row operand) and the DLW x 256 decoder matrices of the
 // group's heads side by side, in halves where two workgroups share a CU; afterwards the BQ x 256 gate / output tile.
@@ -171,8 +174,12 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   if (q0 >= Tb) return;
   const int P = a.prefix ? a.prefix[b] : 0;                  // keys cached before the first query
   const int kh = wave / T::QW, qw = wave % T::QW;            // key half and query rows of this wave
-  const int splits = FUSE || a.splits == 1 || P < 0 ? 1 : splits_of(a, P + Tb);
-  if (split >= splits) return;
+  const int splits = FUSE ? a.splits : a.splits == 1 || P < 0 ? 1 : splits_of(a, P + Tb);   // fused: 1
+  auto stats = [&](int row) { return a.pml + (((int64_t)split * a.total + start + q0 + row) * a.nq + g) * a.ndlc + dlc; };
+  if (!FUSE && split >= splits) {   // no share in the keys
+    if (split == a.splits - 1 && tid < T::BQ && q0 + tid < Tb) *stats(tid) = make_float2(0.f, -(float)splits);
+    return;
+  }
   if (P < 0) {   // skipped sequence: zero rows
     if constexpr (FUSE) {
       const int64_t ldo = (int64_t)a.nh * a.dh;
@@ -522,7 +529,6 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   }
   if (!FUSE && splits > 1) {   // un-normalised sums and statistics for the merge
     const int row = qw * 32 + ln;
-    float2 *pml = a.pml + (((int64_t)split * a.total + start + q0) * a.nq + g) * a.ndlc + dlc;
     if (kh == 0 && q0 + row < Tb) {
       float *pa = a.pacc + ((int64_t)split * a.total + start + q0 + row) * (a.nq * a.dl) + g * a.dl + dlc * T::DLW + 4 * h;
 #pragma unroll
@@ -531,7 +537,7 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
         for (int rq = 0; rq < 4; ++rq)
           *reinterpret_cast<float4 *>(pa + dlb * 32 + rq * 8) =
               make_float4(acc[dlb][rq * 4], acc[dlb][rq * 4 + 1], acc[dlb][rq * 4 + 2], acc[dlb][rq * 4 + 3]);
-      if (h == 0) pml[(int64_t)row * a.nq * a.ndlc] = make_float2(m_run, l_all);
+      if (h == 0) *stats(row) = make_float2(m_run, l_all);
     }
     return;
   }
@@ -664,18 +670,26 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
 // Merge of the key splits of one token (blockIdx.x): thread = 4 columns of one map group; weights exp2(m_s - max) / sum.
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int dlw) {
   const int64_t tok = blockIdx.x;
-  const int b = a.seq_id[tok], P = a.prefix ? a.prefix[b] : 0, nq = a.nq, dl = a.dl;
-  const int splits = P < 0 ? 1 : splits_of(a, P + (a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq));
-  if (splits == 1) return;
+  const int nq = a.nq, dl = a.dl;
   for (int i = threadIdx.x; i < nq * dl / 4; i += 256) {
     const int col = i * 4, st = col / dl * a.ndlc + col % dl / dlw;
+    auto stats = [&](int s) { return a.pml[(s * a.total + tok) * (nq * a.ndlc) + st]; };
+    constexpr int U = 4;   // requested beside the last, before it is known whether they are used
+    const float2 last = stats(a.splits - 1);
+    float2 first[U];
+#pragma unroll
+    for (int s = 0; s < U; ++s) first[s] = stats(min(s, a.splits - 1));
+    const int splits = last.y < 0.f ? (int)-last.y : a.splits;
+    if (splits == 1) continue;   // written already
     float mx = -INFINITY;
-    for (int s = 0; s < splits; ++s) mx = fmaxf(mx, a.pml[(s * a.total + tok) * (nq * a.ndlc) + st].x);
+#pragma unroll
+    for (int s = 0; s < U; ++s) mx = s < splits ? fmaxf(mx, first[s].x) : mx;
+    for (int s = U; s < splits; ++s) mx = fmaxf(mx, stats(s).x);
     const float ref = mx > -INFINITY ? mx : 0.f;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     float ls = 0.f;
     for (int s = 0; s < splits; ++s) {
-      const float2 ml = a.pml[(s * a.total + tok) * (nq * a.ndlc) + st];
+      const float2 ml = stats(s);
       if (ml.y != 0.f) {   // a split without visible keys has the sum 0; one of nothing but NaN has no maximum either
         const float w = __builtin_amdgcn_exp2f(ml.x - ref);
         const float4 p = *reinterpret_cast<const float4 *>(a.pacc + (s * a.total + tok) * (int64_t)(nq * dl) + col);
@@ -726,9 +740,9 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
     // Still fewer workgroups than CUs: the key range is split over workgroups, too, as long as a split keeps 8 steps
     // of two tiles (16 for a fresh prompt, whose average tile is half as long).  1 x 40 behind 6000 145 us without,
     // 80 with up to 23 splits, 67 with 11; 4 x 40 behind 6000 153 / 76; 1 x 2000 fresh 124 / 120.  max_keys is only the
-    // capacity of the slots: the kernels apply the same rule to the keys a sequence has.
-    a.split_tiles = a.prefix ? 16 : 32;
-    const int64_t most = (int64_t)(max_keys + 31) / 32 / a.split_tiles;
+    // capacity of the slots: the kernels count a sequence's own keys (splits_of).
+    a.split_shift = a.prefix ? 4 : 5;
+    const int64_t most = (int64_t)(max_keys + 31) / 32 >> a.split_shift;
     a.splits = (int)(kSplitTarget / half < most ? kSplitTarget / half : most);
     const int64_t stats = a.total * d.nq * (d.dl / DLW) * 2;   // floats per split
     while (a.splits > 1 && (size_t)(a.splits * (stats + a.total * d.nq * d.dl) + 64) * 4 > attn_split_bytes(d)) --a.splits;
@@ -779,10 +793,9 @@ static AttnArgs attn_args(const Dims &d, const void *q, const void *k, const voi
 }
 
 void launch_attn_prefill_bf16(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,
-                              int batch, int64_t total, int max_len, void *L, float *part, const int32_t *seq_id,
-                              hipStream_t st) {
+                              int batch, int64_t total, int max_len, void *L, float *part, hipStream_t st) {
   AttnArgs a = attn_args(d, q, k, c, cu, batch, total);
-  a.L = (bf16 *)L; a.seq_id = seq_id;
+  a.L = (bf16 *)L;
   launch_attn_any<false>(a, d, batch, max_len, max_len, part, st);
 }
 
@@ -802,10 +815,9 @@ void launch_attn_decoder_bf16(const Dims &d, const void *q, const void *k, const
 
 void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache, const int32_t *slots,
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
-                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part,
-                            const int32_t *seq_id, hipStream_t st) {
+                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part, hipStream_t st) {
   AttnArgs a = attn_args(d, q, cache.k, cache.c, cu, batch, total);
-  a.prefix = prefix; a.slots = slots; a.max_seq = cache.max_seq; a.seq_id = seq_id;
+  a.prefix = prefix; a.slots = slots; a.max_seq = cache.max_seq;
   a.pm = page_map_of(cache);
   a.ps_shift = 0;
   while (a.pm.table && (1 << a.ps_shift) < a.pm.page_size) ++a.ps_shift;

@@ -44,9 +44,8 @@ void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const vo
 // bf16 MFMA causal prefill attention (gta_prefill_bf16.hip)
 bool attn_prefill_supported(const Dims &d, int max_len);
 void launch_attn_prefill_bf16(const Dims &d, const void *q, const void *k, const void *c, const int32_t *cu,
-                              int batch, int64_t total, int max_len, void *L, float *part, const int32_t *seq_id,
-                              hipStream_t st);
-// scratch `part` of the two that can split the key range (NULL: no splits), which need the sequence of every token, too
+                              int batch, int64_t total, int max_len, void *L, float *part, hipStream_t st);
+// scratch `part` of the two that can split the key range (NULL: no splits)
 size_t attn_split_bytes(const Dims &d);
 // attention with the value decoder and gate fused into its epilogue (narrow shapes): writes the heads
 bool attn_decoder_fusable(const Dims &d, int max_len);
@@ -57,8 +56,7 @@ void launch_attn_decoder_bf16(const Dims &d, const void *q, const void *k, const
 // slot, its queries sit at positions prefix[b] .. (prefix[b] < 0: zero rows).  L may be NULL when fused.
 void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache, const int32_t *slots,
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
-                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part,
-                            const int32_t *seq_id, hipStream_t st);
+                            void *L, const void *wp, const void *gate, void *out, bool fuse, float *part, hipStream_t st);
 
 // bf16 GEMMs for few rows, K split inside the workgroup (gta_rows_bf16.hip)
 bool rows_gemm_ok(const Dims &d);

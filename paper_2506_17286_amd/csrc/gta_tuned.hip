@@ -18,7 +18,7 @@ int tuned_prefill(const Dims &d, const gta_weights &w, const void *x, const int3
     launch_attn_decoder_bf16(d, ws.q, ws.k, ws.c, cu, batch, total, max_len, w.wp, ws.g, heads, st);
   } else {
     // Sec. 3.3: one causal softmax map per group applied to the latent values
-    if (attn_prefill_supported(d, max_len)) launch_attn_prefill_bf16(d, ws.q, ws.k, ws.c, cu, batch, total, max_len, ws.l, ws.praw, ws.seq_id, st);
+    if (attn_prefill_supported(d, max_len)) launch_attn_prefill_bf16(d, ws.q, ws.k, ws.c, cu, batch, total, max_len, ws.l, ws.praw, st);
     else launch_attn_prefill_rowwise(d, ws.q, ws.k, ws.c, cu, batch, total, max_len, ws.l, st);
     // Sec. 3.2 value decoder with the gate in the epilogue
     launch_decoder_gemm(d, ws.l, w.wp, ws.g, heads, M, st);
@@ -48,7 +48,7 @@ int tuned_prefill_chunk(const Dims &d, const gta_weights &w, const void *x, cons
   launch_proj_gemm(d, w, x, M, ws, &cache, slots, max_chunk, st, true);
   void *heads = w.wo ? ws.o : out;
   const bool fuse = attn_decoder_fusable(d, cache.max_seq);
-  launch_attn_chunk_bf16(d, ws.q, cache, slots, ws.prefix, cu, batch, total, max_chunk, ws.l, w.wp, ws.g, heads, fuse, ws.praw, ws.seq_id, st);
+  launch_attn_chunk_bf16(d, ws.q, cache, slots, ws.prefix, cu, batch, total, max_chunk, ws.l, w.wp, ws.g, heads, fuse, ws.praw, st);
   if (!fuse) launch_decoder_gemm(d, ws.l, w.wp, ws.g, heads, M, st);
   if (w.wo) launch_plain_gemm(ws.o, d.wg_w, M, d.H, d.wg_w, w.wo, out, st);
   launch_prefill_chunk_commit(cache, slots, cu, batch, total, ws.prefix, st);

@@ -79,6 +79,21 @@ def test_chunks_behind_cached_rows(shape, paged):
     assert cache.seq_lens.tolist() == [n + p for n, p in zip(lens[:-1], prefix[:-1])] + [prefix[-1]]
 
 
+@pytest.mark.parametrize("prefix", [(472, 473), (2000, 10), (7900, 1100), (8100, 3000)], ids=str)   # 16 tiles, 17; 4 splits, none; most and fewer
+@pytest.mark.parametrize("shape", ["1b", "mid", "slim"])
+def test_chunks_in_large_slots(shape, prefix):
+    """Sequences that use fewer splits than the launch has room for, and none."""
+    lens, cap = [40, 40], 8192
+    wl, w, x, rng = _setup(shape, sum(lens))
+    k, c = W.draw_cache(wl, rng, 2, cap)
+    cache = U.DeviceCache(wl, 2, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    out = U.f64(U.run_prefill_chunk(wl, U.upload_weights(w, "bf16"), x, np.array([0, 40, 80]), cache))
+    for b in range(2):
+        _check(wl, w, x[40 * b:40 * b + 40], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[40 * b:40 * b + 40],
+               f"{shape} behind {prefix[b]}")
+
+
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("shape", list(SHAPES))
 def test_chunks_of_many_workgroups(shape, paged):
