@@ -47,16 +47,16 @@ def _check_prefill(wl, lens, with_wo=False, gate=True, with_cache=True, slots=No
 
 
 def test_config1_tiny_prefill_fp32():
-    """BASELINE config 1 as stated: B=1, T=128, d_model=256, 8 heads of 32 in 2 groups, d_l=64."""
+    """The tiny fp32 layer: B=1, T=128, d_model=256, 8 heads of 32 in 2 groups, d_l=64."""
     wl = W.WORKLOADS[0]
     lens, cu, w, x = W.prefill_inputs(wl)
     wdev = U.upload_weights(w, wl.dtype)
     cache = U.DeviceCache(wl, 1, 128)
     out = U.run_prefill(wl, wdev, x, None, batch=1, cache=cache)
     ref, Kref, Cref = orc.prefill_sequence(U.oracle_config(wl), U.oracle_weights(w), x)
-    ma, rr = U.assert_close(U.f64(out), ref, "f32", "config 1")
-    U.assert_close(U.f64(cache.k)[0], Kref, "f32", "config 1 K cache")
-    U.assert_close(U.f64(cache.c)[0], Cref, "f32", "config 1 C cache")
+    ma, rr = U.assert_close(U.f64(out), ref, "f32", "tiny layer")
+    U.assert_close(U.f64(cache.k)[0], Kref, "f32", "tiny layer, K cache")
+    U.assert_close(U.f64(cache.c)[0], Cref, "f32", "tiny layer, C cache")
     assert int(cache.seq_lens[0]) == 128
     assert B.gta_uses_tuned_kernels(B.config_of(wl), B.GTA_MODE_PREFILL) == 0
 
