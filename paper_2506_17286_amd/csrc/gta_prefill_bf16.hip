@@ -37,6 +37,7 @@
 // enough, over workgroups with a merge kernel (rule and figures at launch_attn).
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gta_lds_load.h"
@@ -95,7 +96,8 @@ struct AttnArgs {
   const bf16 *q, *k, *c;     // packed [total, n_q*d_h], [total, n_k*d_h], [total, n_c*d_l]
   bf16 *L;                   // [total, n_q*d_l]
   const int32_t *cu; int per_seq;
-  int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, n_qtiles, ndlc, batch;
+  int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, ndlc, batch;
+  int n_qtiles, levels, spread;   // query tiles of the longest sequence; bound of the levels, order of the tiles (tile_of_rank)
   float scale_log2e;
   // fused value decoder (kernel template flag): O_i = (L_g W_{P,i}) * Sigmoid(gate) for the heads of g
   const bf16 *wp, *gate;     // [n_h, d_l, d_h]; gate pre-activations [total, n_h*d_h] or NULL (gate off)
@@ -150,29 +152,103 @@ __device__ __forceinline__ int load_uniform(const int32_t *p) {
   return v;
 }
 
+__device__ __forceinline__ int wave_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);    // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);    // row_bcast:15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Query tile `u` of all sequences' tiles in the order they are started: most keys first (list scheduling needs that to
+// balance the CUs), sequences in turn inside a level.  Level of tile qt: qt + tiles cached before the chunk, of which a
+// sequence with n tiles behind p has p .. p + n - 1.  False: there are no more.  All lanes of the wave call this with the
+// same arguments; lane i counts sequences i, i + 64, ..
+// The host knows no lengths.  With an id for every (level, sequence) up to the longest, the ids of the shorter ones'
+// missing tiles fell to the same places again and again, and as ids are dealt to the XCDs and their shader engines in a
+// fixed turn, some had no work: ragged batch of 112 K tokens, 16 sequences, CUs busy 0.57 of the time, 18.2 ms; with the
+// tiles that exist numbered here 0.96, 13.0 ms (whole call 24.6 -> 19.6 ms; ragged chunks of 4 sequences 329 -> 306 us,
+// 16 x 100..1000 tokens of the 1B shape 265 -> 257 us; sequences of one length as before).
+struct QueryTile { int b, qt, start, len, prefix; };   // sequence, tile, first token, tokens, keys cached before
+__device__ __forceinline__ bool tile_of_rank(const AttnArgs &a, int bq, int u, QueryTile &t) {
+  const int lane = threadIdx.x & 63;
+  struct Seq { int start, len, prefix, p, n; };
+  auto sequence = [&](int i) {
+    Seq s{};
+    if (i < a.batch) {
+      s.start = a.cu ? a.cu[i] : i * a.per_seq;
+      s.len = a.cu ? a.cu[i + 1] - s.start : a.per_seq;
+      s.prefix = a.prefix ? a.prefix[i] : 0;
+      s.n = max(min((s.len + bq - 1) / bq, a.n_qtiles), 0);
+      s.p = max(s.prefix, 0) / bq;
+    }
+    return s;
+  };
+  auto found = [&](const Seq &s, int base, int at, int level) {
+    t.b = base + at;
+    t.qt = level - __builtin_amdgcn_readlane(s.p, at);
+    t.start = __builtin_amdgcn_readlane(s.start, at);
+    t.len = __builtin_amdgcn_readlane(s.len, at);
+    t.prefix = __builtin_amdgcn_readlane(s.prefix, at);
+    return true;
+  };
+  const Seq s0 = sequence(lane);
+  const int pf = __builtin_amdgcn_readfirstlane(s0.p), nf = __builtin_amdgcn_readfirstlane(s0.n);
+  if (a.batch <= 64 && __builtin_amdgcn_ballot_w64(lane < a.batch && (s0.p != pf || s0.n != nf)) == 0) {   // all alike
+    const int lvl = u / a.batch;
+    return lvl < nf && found(s0, 0, u - lvl * a.batch, pf + nf - 1 - lvl);
+  }
+  auto from_level = [&](int c) {   // tiles of level c and above
+    int n = max(min(s0.p + s0.n - c, s0.n), 0);
+    for (int i = lane + 64; i < a.batch; i += 64) {
+      const Seq s = sequence(i);
+      n += max(min(s.p + s.n - c, s.n), 0);
+    }
+    return wave_sum(n);
+  };
+  if (from_level(0) <= u) return false;
+  int c = 0, above = a.levels, n_above = 0;   // from_level(c) > u >= from_level(above) = n_above
+  while (above - c > 1) {
+    const int mid = (c + above) >> 1, n = from_level(mid);
+    if (n > u) c = mid;
+    else { above = mid; n_above = n; }
+  }
+  int left = u - n_above;   // which of the sequences that have a tile of level c
+  for (int base = 0; base < a.batch; base += 64) {
+    const Seq s = base ? sequence(base + lane) : s0;
+    const bool has = s.p <= c && c < s.p + s.n;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(has);
+    const int count = __builtin_popcountll(mask);
+    if (left < count) {
+      const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+      return found(s, base, __builtin_ctzll(__builtin_amdgcn_ballot_w64(has && before == left)), c);
+    }
+    left -= count;
+  }
+  return false;
+}
+
 template <class T, bool FUSE>
 __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
-  // Workgroups are dispatched in id order and a query tile costs (tile index + 1) key tiles, so the
-  // tile index is the slowest digit of the id, longest first (list scheduling needs that to balance
-  // the CUs); the sequence is the fastest digit, so the 8 XCDs (ids round-robin) each work on few
-  // sequences and the workgroups of one XCD stream the same key range through its L2 in step.
-  // Ids go to the XCDs round-robin whatever their cost, so with ragged lengths a fixed sequence digit
-  // would tie each sequence to one XCD and the longest sequences would bound the launch: the
-  // sequence digit is rotated by one per tile level, which spreads every sequence over all XCDs.
-  const int per_qt = a.batch * a.nq * a.ndlc * a.splits;
-  const int lvl = (int)blockIdx.x / per_qt;
-  const int qt = a.n_qtiles - 1 - lvl;
-  const int rest = (int)blockIdx.x % per_qt;
-  const int b = a.cu ? (rest % a.batch + lvl) % a.batch : rest % a.batch;
-  const int g = (rest / a.batch) % a.nq, dlc = rest / (a.batch * a.nq) % a.ndlc, split = rest / (a.batch * a.nq * a.ndlc);
-  const int64_t start = a.cu ? a.cu[b] : (int64_t)b * a.per_seq;
-  const int Tb = a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq;   // queries of this sequence
-  const int q0 = qt * T::BQ;
-  if (q0 >= Tb) return;
-  const int P = a.prefix ? a.prefix[b] : 0;                  // keys cached before the first query
+  const int per = a.nq * a.ndlc * a.splits;                  // workgroups of a query tile
+  int u, r;                                                  // rank of the tile, workgroup of the tile
+  if (a.spread) { u = (int)blockIdx.x / per; r = (int)blockIdx.x % per; }
+  else {   // eight tiles at a time, one per XCD, in turn from either end
+    const int x = (int)blockIdx.x & 7, at = (int)blockIdx.x >> 3, round = at / per;
+    r = at % per;
+    u = round * 8 + (round & 1 ? 7 - x : x);
+  }
+  QueryTile tile;
+  if (!tile_of_rank(a, T::BQ, u, tile)) return;
+  const int g = r % a.nq, dlc = r / a.nq % a.ndlc, split = r / (a.nq * a.ndlc);
+  const int64_t start = tile.start;
+  const int Tb = tile.len, q0 = tile.qt * T::BQ;             // queries of this sequence, first of this tile
+  const int P = tile.prefix;                                 // keys cached before the first query
   const int kh = wave / T::QW, qw = wave % T::QW;            // key half and query rows of this wave
   const int splits = FUSE ? a.splits : a.splits == 1 || P < 0 ? 1 : splits_of(a, P + Tb);   // fused: 1
   auto stats = [&](int row) { return a.pml + (((int64_t)split * a.total + start + q0 + row) * a.nq + g) * a.ndlc + dlc; };
@@ -205,7 +281,7 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   int64_t krow0 = start;                                     // first key / latent row of the sequence
   int slot = 0;
   if (a.prefix) {
-    slot = a.slots ? a.slots[b] : b;
+    slot = a.slots ? a.slots[tile.b] : tile.b;
     krow0 = a.pm.table ? 0 : (int64_t)slot * a.max_seq;      // block table: Kb / Cb are the pools, rows per tile
   }
   const int32_t *table = a.pm.table + (int64_t)__builtin_amdgcn_readfirstlane(slot) * a.pm.pages_per_slot;
@@ -707,14 +783,24 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int dlw) {
 // latent columns per workgroup
 int latent_tile(const Dims &d) { return d.dh == 128 ? (d.dl % 256 == 0 ? 256 : 128) : (d.dl % 128 == 0 ? 128 : 64); }
 
+// From this many query tiles on a tile's workgroups stay on one XCD (they read the same keys and latents); fewer would
+// leave XCDs idle or unevenly loaded, and their workgroups go to the XCDs in turn: 1 x 4000 tokens of 8 maps and 4 column
+// slices (32 tiles) 454 us on one XCD each, 447 in turn; 1 x 500 of the 1B shape (4) 48.6 / 48.3; from 64 tiles on equal.
+constexpr int kSpreadTiles = 64;
+
 template <class T, bool FUSE>
 void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t st) {
   a.n_qtiles = (max_len + T::BQ - 1) / T::BQ;
   a.ndlc = d.dl / T::DLW;
+  a.levels = a.n_qtiles + (a.prefix ? a.max_seq / T::BQ : 0) + 1;
+  // no more than this many query tiles whatever the lengths are
+  int64_t tiles = std::min((int64_t)a.n_qtiles * batch, a.total / T::BQ + batch);
+  a.spread = tiles < kSpreadTiles;
+  if (!a.spread) tiles = (tiles + 7) / 8 * 8;
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;
   allow_dynamic_lds((const void *)attn_prefill_kernel<T, FUSE>, smem);
-  attn_prefill_kernel<T, FUSE><<<a.n_qtiles * a.ndlc * d.nq * batch * a.splits, T::NT, smem, st>>>(a);
+  attn_prefill_kernel<T, FUSE><<<(unsigned)(tiles * a.ndlc * d.nq * a.splits), T::NT, smem, st>>>(a);
 }
 
 constexpr int kSplitTarget = 256;   // workgroups of 128 queries a launch with key splits aims at: one per CU

@@ -58,6 +58,32 @@ def test_fresh(shape, lens, bound):
             _check(wl, w, x[cu[b]:cu[b + 1]], none, none, 0, out[cu[b]:cu[b + 1]], f"{shape} {lens} sequence {b}")
 
 
+@pytest.mark.parametrize("chunk", [False, True])
+@pytest.mark.parametrize("batch", [3, 63, 64, 65, 130])
+@pytest.mark.parametrize("shape", ["1b", "paper"])
+def test_every_tile_is_found(shape, batch, chunk):
+    """The kernels number the query tiles of ragged sequences themselves, 64 sequences at a time: one tile more or less,
+    empty sequences, levels that only a few or only late sequences reach, cached rows that lift a sequence's tiles."""
+    rng = np.random.default_rng(batch)
+    lens = [int(n) for n in rng.choice([0, 1, 2, 40, 127, 128, 129, 200], batch)]
+    lens[-1], lens[batch // 2] = 390, 257
+    prefix = [int(n) for n in rng.choice([0, 1, 127, 128, 500], batch)] if chunk else [0] * batch
+    cap = 896
+    wl, w, x, r2 = _setup(shape, sum(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    k, c = W.draw_cache(wl, r2, batch, cap)
+    cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    if chunk:
+        cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+        out = U.f64(U.run_prefill_chunk(wl, U.upload_weights(w, "bf16"), x, cu, cache))
+    else:
+        out = U.f64(U.run_prefill(wl, U.upload_weights(w, "bf16"), x, cu, cache=cache))
+    for b in range(batch):
+        if lens[b]:
+            _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
+                   f"{shape} sequence {b}: {lens[b]} behind {prefix[b]}")
+
+
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("shape", list(SHAPES))
 def test_chunks_behind_cached_rows(shape, paged):
