@@ -158,14 +158,15 @@ struct StoreEpi {
   }
 };
 
-// Column tile nt (32 columns) of the kernels for few rows: tile column c is global column col0 + c % 16 +
-// (c / 16) * step.  A rotated tile must hold both halves of its heads: with heads wider than 32 it takes 16
-// columns of one half and the 16 they pair with (`pair`), otherwise whole heads lie in 32 columns in a row.
+// Column tile nt (BN columns) of the kernels for few rows: tile column c is global column col0 + c % (BN / 2) +
+// (c / (BN / 2)) * step.  A rotated tile must hold both halves of its heads: with heads wider than BN it takes BN / 2
+// columns of one half and those they pair with (`pair`), otherwise whole heads lie in BN columns in a row.
 struct RowTile { int col0, step; bool pair; };
+template <int BN = 32>
 __device__ __forceinline__ RowTile row_tile(int nt, bool rot, int dh) {
-  if (!rot || dh <= 32) return RowTile{nt * 32, 16, false};
-  const int tph = dh / 32;
-  return RowTile{nt / tph * dh + nt % tph * 16, dh / 2, true};
+  if (!rot || dh <= BN) return RowTile{nt * BN, BN / 2, false};
+  const int tph = dh / BN;
+  return RowTile{nt / tph * dh + nt % tph * (BN / 2), dh / 2, true};
 }
 
 }  // namespace gta

@@ -59,42 +59,52 @@ __device__ __forceinline__ void operand_at(const GemmOperands &g, int col, const
 }
 
 // ------------------------------------------------------------------------------ few rows: K split over waves
-// Tile of 32 rows x 32 columns; the W waves of the workgroup each take every W-th group of eight k and read their
-// operand fragments straight from memory (nothing is shared between the waves, so LDS would only add a round
+// Tile of 32 rows x BN columns (or 16 x 16); the W waves of the workgroup each take every W-th group of KG k and read
+// their operand fragments straight from memory (nothing is shared between the waves, so LDS would only add a round
 // trip), U groups in flight; the W partial tiles are summed through LDS in a fixed order.  For a decode step's
 // rows and short prompts: what bounds these is the latency of a few loads and how many workgroups pull on the
-// weights, not arithmetic.  A tile that is rotated must hold both halves of its heads: with heads of 64 it takes
-// 16 columns of one half and the 16 they pair with, otherwise (whole heads fit) 32 columns in a row.
-template <int W, class Epi>
+// weights, not arithmetic.  A tile that is rotated must hold both halves of its heads: with heads wider than the tile it
+// takes half its columns of one half and those they pair with, otherwise (whole heads fit) columns in a row.
+template <int W, int BM, int BN, class Epi>
 __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, Epi epi) {
-  constexpr int U = 5, PITCH = 32 + 4;
-  extern __shared__ __attribute__((aligned(16))) float red[];   // [W][32][PITCH]
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
+  constexpr int MT = BN == 32 ? 32 : 16, NSUB = BM / MT;   // MFMA tile, tiles of rows
+  constexpr int U = 5, PITCH = BN + 4, KG = 256 / MT, HB = BN / 2, GR = BN / 4;   // GR: groups of four columns a row
+  extern __shared__ __attribute__((aligned(16))) float red[];   // [W][BM][PITCH]
+  const int tid = threadIdx.x, lane = tid & 63, h = lane / MT, ln = lane % MT;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workgroup ids go to different XCDs; each XCD takes a contiguous eighth of the tiles, row tiles
   // fastest: neighbouring tiles share the 128-byte lines of the weights, which should reach one L2 only
   const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
-  const int ntm = (g.M + 31) / 32, nt = at / ntm, m0 = at % ntm * 32;
-  const bool rot = epi.rotates(nt * 32);
-  const RowTile ct = row_tile(nt, rot, epi.head_dim());
+  const int ntm = (g.M + BM - 1) / BM, nt = at / ntm, m0 = at % ntm * BM;
+  const bool rot = epi.rotates(nt * BN);
+  const RowTile ct = row_tile<BN>(nt, rot, epi.head_dim());
   const int col0 = ct.col0, step = ct.step;
   const float *A, *B;
   int ldb;
   operand_at(g, col0, A, B, ldb);
-  const float *ap = A + (int64_t)min(m0 + ln, g.M - 1) * g.lda + h * 4;
-  const float *bp = B + (int64_t)(h * 4) * ldb + (ln & 15) + (ln >> 4) * step;
-  f32x16 acc;
-  zero16(acc);
-  const int ng = g.K / 8;
-  f32x4 a[U], b[U];
-  auto load = [&](int u, int c) {   // groups past the end re-read the last one; they are not used
-    const int k = min(c, ng - 1) * 8;
-    a[u] = *reinterpret_cast<const f32x4 *>(ap + k);
+  const float *ap[NSUB];
+#pragma unroll
+  for (int i = 0; i < NSUB; ++i) ap[i] = A + (int64_t)min(m0 + i * MT + ln, g.M - 1) * g.lda + h * 4;
+  const float *bp = B + (int64_t)(h * 4) * ldb + ln % HB + ln / HB * step;
+  typedef float accvec __attribute__((ext_vector_type(MT * MT / 64)));
+  accvec acc[NSUB];
+#pragma unroll
+  for (int i = 0; i < NSUB; ++i)
+#pragma unroll
+    for (int r = 0; r < MT * MT / 64; ++r) acc[i][r] = 0.f;
+  const int ng = g.K / KG;
+  f32x4 a[U][NSUB], b[U];
+  // groups past the end re-read the last one; they are not used (a branch around the loads instead: 64 rows of the paper's
+  // layer 54 us a step, not 50)
+  auto load = [&](int u, int c) {
+    const int k = min(c, ng - 1) * KG;
+#pragma unroll
+    for (int i = 0; i < NSUB; ++i) a[u][i] = *reinterpret_cast<const f32x4 *>(ap[i] + k);
 #pragma unroll
     for (int j = 0; j < 4; ++j) b[u][j] = bp[(int64_t)(k + j) * ldb];
   };
-  const int row = tid >> 3, c = (tid & 7) * 4, fcol = ct.col0 + (c & 15) + (c >> 4) * ct.step;   // what this thread finishes
-  const bool finisher = tid < 256 && m0 + row < g.M;
+  const int row = tid / GR, c = tid % GR * 4, fcol = col0 + c % HB + c / HB * step;   // what this thread finishes
+  const bool finisher = tid < BM * GR && m0 + row < g.M;
   typename Epi::Early early{};
   if (finisher) early = epi.early(m0 + row, fcol, rot);
   __builtin_amdgcn_sched_barrier(0);
@@ -108,24 +118,32 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, E
     for (int u = 0; u < U; ++u) {
       if (c0 + u * W < ng) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][j], b[u][j], acc, 0, 0, 0);
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < NSUB; ++i) {
+            if constexpr (MT == 32) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i][j], b[u][j], acc[i], 0, 0, 0);
+            else acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][j], b[u][j], acc[i], 0, 0, 0);
+          }
       }
-      load(u, c0 + (u + U) * W);
+      if (c0 + U * W < ng) load(u, c0 + (u + U) * W);
     }
   }
-  float *mine = red + wave * 32 * PITCH;
+  float *mine = red + wave * BM * PITCH;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) mine[(8 * (r >> 2) + 4 * h + (r & 3)) * PITCH + ln] = acc[r];
+  for (int i = 0; i < NSUB; ++i)
+#pragma unroll
+    for (int r = 0; r < MT * MT / 64; ++r)
+      mine[(i * MT + 256 / MT * (r >> 2) + 4 * h + (r & 3)) * PITCH + ln] = acc[i][r];
   __syncthreads();
   auto sum4 = [&](int row, int col) {
     const float *p = red + row * PITCH + col;
     f32x4 v = *reinterpret_cast<const f32x4 *>(p);
 #pragma unroll
-    for (int w = 1; w < W; ++w) v += *reinterpret_cast<const f32x4 *>(p + w * 32 * PITCH);
+    for (int w = 1; w < W; ++w) v += *reinterpret_cast<const f32x4 *>(p + w * BM * PITCH);
     return v;
   };
   if (!finisher) return;
-  epi.store(ctx, m0 + row, sum4(row, c), [&](int off) { return sum4(row, c + (ct.pair ? (off > 0 ? 16 : -16) : off)); });
+  epi.store(ctx, m0 + row, sum4(row, c), [&](int off) { return sum4(row, c + (ct.pair ? (off > 0 ? HB : -HB) : off)); });
 }
 
 // ------------------------------------------------------------------------------ many rows: LDS tiles
@@ -564,18 +582,30 @@ __global__ __launch_bounds__(256, 2) void decode_attn_f32_kernel(DecF32 a) {
 
 // ------------------------------------------------------------------------------ launches
 // Columns in units of 32.
-template <class Epi>
+template <int BM, int BN, class Epi>
 void launch_gemm_rows_f32(const GemmOperands &g, int cols, const Epi &epi, hipStream_t st) {
   auto launch = [&](auto kernel, int w) {
-    const int smem = w * 32 * (32 + 4) * (int)sizeof(float);
+    const int smem = w * BM * (BN + 4) * (int)sizeof(float);
     if (smem > 64 * 1024) allow_dynamic_lds((const void *)kernel, smem);
-    kernel<<<(cols / 32) * ((g.M + 31) / 32), 64 * w, smem, st>>>(g, epi);
+    kernel<<<(cols / BN) * ((g.M + BM - 1) / BM), 64 * w, smem, st>>>(g, epi);
   };
   // two rounds of loads per wave at most: K = 1280 over 16 waves (64 rows of the paper's projection 16 us, 20 us with
   // eight waves of 64 columns), K = 256 over eight (5 us; 16 mostly idle waves 9 us), K = 64 over four
-  if (g.K >= 640) launch(gemm_rows_f32_kernel<16, Epi>, 16);
-  else if (g.K >= 192) launch(gemm_rows_f32_kernel<8, Epi>, 8);
-  else launch(gemm_rows_f32_kernel<4, Epi>, 4);
+  if (g.K >= 640) launch(gemm_rows_f32_kernel<16, BM, BN, Epi>, 16);
+  else if (g.K >= 192) launch(gemm_rows_f32_kernel<8, BM, BN, Epi>, 8);
+  else launch(gemm_rows_f32_kernel<4, BM, BN, Epi>, 4);
+}
+// The smallest tile of which every CU gets at most one: a tile's time is its own loads and its matrix instructions, 4.4 us of
+// them for 32 x 32 at K = 1280, and a CU without a tile is idle.  Whole calls with 32 x 32 / 32 x 16 / 16 x 16 tiles, paper's
+// layer (56 column tiles of 32 in the projection, 40 in W_O): decode of 1 sequence behind 1000 rows 37.1 / 28.2 / 24.7 us, 16
+// 41.3 / 33.3 / 30.2, 32 43.9 / 36.4 / 30.9 (224 tiles of 16 x 16), 48 49.8 / 42.3 / 42.4 (336; 168 of 32 x 16), 64 behind
+// 2048 57.0 / 50.0 / 52.8 (448; 224); prompts of 100 tokens 44.2 / 53.1 / 49.6 (224 of 32 x 32, 448 of 32 x 16).
+template <class Epi>
+void launch_gemm_rows_f32(const GemmOperands &g, int cols, const Epi &epi, hipStream_t st) {
+  const int64_t tiles16 = (int64_t)(cols / 16) * ((g.M + 15) / 16), tiles32 = (int64_t)(cols / 16) * ((g.M + 31) / 32);
+  if (tiles16 <= 256) launch_gemm_rows_f32<16, 16>(g, cols, epi, st);
+  else if (tiles32 <= 256) launch_gemm_rows_f32<32, 16>(g, cols, epi, st);
+  else launch_gemm_rows_f32<32, 32>(g, cols, epi, st);
 }
 // Up to 256 rows the kernel that splits K inside the workgroup is the faster one (the paper's layer, whole prefill
 // of one sequence: 128 tokens 50 us against 82 with 64 x 64 tiles, 256 tokens 82 against 86, 512 tokens 131 against

@@ -224,3 +224,19 @@ def test_prefill_of_many_tiny_prompts(shape, longest):
     out = U.f64(U.run_prefill(wl, U.upload_weights(w, "f32"), x, cu))
     ref, _, _ = orc.prefill(U.oracle_config(wl), U.oracle_weights(w), x, cu)
     U.assert_close(out, ref, "f32", shape, _scale(ref))
+
+
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 64, 65, 145, 256])
+@pytest.mark.parametrize("shape", ["paper", "heads32", "heads16"])
+def test_gemms_of_few_rows(shape, rows):
+    """Row counts around the three tiles of the few-row GEMMs (paper: 16 x 16 up to 32 rows, 32 x 16 up to 64, 32 x 32 behind;
+    the narrow shapes change over at 144): rotated tiles narrower than a head, as wide, and wider, and partial row tiles."""
+    wl = _wl(shape)
+    w, x = _inputs(wl, rows, True)
+    cache = U.DeviceCache(wl, 1, rows + 3, fill=7.0)
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "f32"), x, [0, rows], cache=cache))
+    ref, k, c = orc.prefill_sequence(U.oracle_config(wl), U.oracle_weights(w), x)
+    U.assert_close(out, ref, "f32", f"{shape} {rows} rows", _scale(ref))
+    U.assert_close(U.f64(cache.k[0, :rows]), k.reshape(rows, -1), "f32", "keys", _scale(k))
+    U.assert_close(U.f64(cache.c[0, :rows]), c.reshape(rows, -1), "f32", "latents", _scale(c))
+    assert bool((cache.k[0, rows:] == 7.0).all())
