@@ -429,8 +429,7 @@ int gta_prefill_projection(const gta_config *cfg, const gta_weights *weights, co
   if (ws.bytes > workspace_bytes) return GTA_ERR_WORKSPACE;
   ws.q = q_out; ws.k = k_out; ws.c = c_out; ws.g = g_out;
   hipStream_t st = (hipStream_t)hip_stream;
-  launch_prefill_setup(d, cu_seqlens, batch, total_tokens, max_seqlen, ws.seq_id, ws.pos, ws.rope, nullptr, nullptr, st);
-  launch_proj_gemm(d, *weights, x, (int)total_tokens, ws, nullptr, nullptr, max_seqlen, st);
+  tuned_project(d, *weights, x, cu_seqlens, batch, total_tokens, max_seqlen, nullptr, nullptr, ws, st);
   return check_launch();
 }
 

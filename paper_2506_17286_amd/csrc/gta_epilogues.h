@@ -19,24 +19,22 @@ __device__ __forceinline__ void store4(__bf16 *p, f32x4 v) {
   *reinterpret_cast<bf16x4 *>(p) = o;
 }
 
-__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
-__device__ __forceinline__ f32x4 load4(const __bf16 *p) {
-  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-  const bf16x4 v = *reinterpret_cast<const bf16x4 *>(p);
-  return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-}
+template <typename T>
+struct Quad { typedef T type __attribute__((ext_vector_type(4))); };
 
 // ------------------------------------------------------------------------------ epilogues
 // A GEMM hands its epilogue groups of four columns in three calls: early(row, first column, rotated tile?) requests
 // what the group reads itself, prepare() works out position, cache row and sines, store() takes the values and
 // `partner`, which returns the four values half a head further (used by the rotation only).  The kernels for few
 // rows call early() ahead of their operand loads and prepare() under them: behind them the two cost a decode step
-// 6 us.  Columns are global (all segments).
+// 6 us.  Columns are global (all segments).  Workgroups behind the tiles are for commit(): side_waves() waves of them.
 
 // Projection (Sec. 3.2) with RoPE on q and k (App. B.1.1) and the cache write (App. B.1.3).
 // TD: element type of the Q | K | C | gate rows (a decode step keeps q and gate in fp32), TC: of the caches.
-// PREFILL: decode steps do not occur (their sines would be held in registers all the same).
-template <typename TD, typename TC, bool PREFILL = false>
+// PREFILL: decode steps do not occur, FOLD false: nor does fold.batch > 0 (their sines would be held in registers all the same).
+// With fold.batch > 0 a group of columns finds its token among the offsets, which are all requested at once, and takes the
+// sines of its angles itself (the same values as the table's), and waves of their own set the lengths.
+template <typename TD, typename TC, bool PREFILL = false, bool FOLD = true>
 struct ProjEpi {
   TD *dst[4]; int width[4];                 // Q | K | C | gate rows (decode: K and C go to the caches only)
   int dh, rope;
@@ -45,7 +43,13 @@ struct ProjEpi {
   // decode (seq_lens != NULL): row b is the new token of slot slots[b] at position seq_lens[slot]
   const int32_t *seq_lens; int32_t *oldlen; double freq[64];
   TC *kcache, *ccache; const int32_t *slots; int max_batch, max_seq; PageMap pm;   // kcache NULL: no cache write
+  Fold fold; CacheView commit_to;
 
+  int side_waves() const { return commit_to.k ? fold.batch : 0; }
+  __device__ __forceinline__ void commit(int wave) const {
+    if (FOLD && wave < fold.batch) prefill_commit_seq(commit_to, fold.cu, fold.per_seq, wave);
+  }
+  __device__ __forceinline__ bool folded() const { return FOLD && fold.batch; }
   __device__ __forceinline__ bool decode() const { return !PREFILL && seq_lens; }
   __device__ __forceinline__ void locate(int col, int &seg, int &local) const {
     seg = 0;
@@ -66,6 +70,24 @@ struct ProjEpi {
       const bool ok = e.slot >= 0 && e.slot < max_batch;
       e.p = seq_lens[ok ? e.slot : 0];
       if (!ok) e.p = -1;
+      if (rot) {
+        const int j = col % (dh / 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e.f[i] = freq[j + i];
+      }
+    } else if (folded()) {
+      if (fold.cu) {
+        int s[kFoldBatch], start = 0;
+#pragma unroll
+        for (int b = 0; b < kFoldBatch; ++b) s[b] = fold.cu[min(b, fold.batch - 1)];
+#pragma unroll
+        for (int b = 0; b < kFoldBatch; ++b)
+          if (b < fold.batch && s[b] <= row) { e.seq = b; start = s[b]; }
+        e.p = row - start;
+      } else {
+        e.seq = row / fold.per_seq;
+        e.p = row - e.seq * fold.per_seq;
+      }
       if (rot) {
         const int j = col % (dh / 2);
 #pragma unroll
@@ -94,10 +116,10 @@ struct ProjEpi {
     if (rot && (decode() || rope_by_token || p < max_len)) {
       const int half = dh / 2, e = c.lc % dh, j = e < half ? e : e - half;
       c.half = e < half ? half : -half;
-      if (decode()) {
+      if (decode() || folded()) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {   // fp32 rows: the same values as a prefill's table
-          const float2 t = std::is_same<TC, float>::value ? rope_cos_sin(p, y.f[i]) : rope_cos_sin_short(p, y.f[i]);
+        for (int i = 0; i < 4; ++i) {   // fp32 rows and prompts: the same values as a prefill's table
+          const float2 t = PREFILL || std::is_same<TC, float>::value ? rope_cos_sin(p, y.f[i]) : rope_cos_sin_short(p, y.f[i]);
           c.cs[i] = t.x; c.sn[i] = t.y;
         }
       } else {
@@ -125,17 +147,23 @@ struct ProjEpi {
 template <typename T, typename TG = float>
 struct GateEpi {
   T *out; const TG *g; int ld, gate;
+  int side_waves() const { return 0; }
+  __device__ __forceinline__ void commit(int) const {}
   __device__ __forceinline__ bool rotates(int) const { return false; }
   __device__ __forceinline__ int head_dim() const { return 0; }
-  struct Early {};
-  struct Ctx { int col; };
-  __device__ __forceinline__ Early early(int, int, bool) const { return Early{}; }
-  __device__ __forceinline__ Ctx prepare(const Early &, int, int col, bool) const { return Ctx{col}; }
+  struct Early { typename Quad<TG>::type z; };
+  struct Ctx { int col; typename Quad<TG>::type z; };
+  __device__ __forceinline__ Early early(int row, int col, bool) const {
+    Early e{};
+    if (gate) e.z = *reinterpret_cast<const typename Quad<TG>::type *>(g + (int64_t)row * ld + col);
+    return e;
+  }
+  __device__ __forceinline__ Ctx prepare(const Early &e, int, int col, bool) const { return Ctx{col, e.z}; }
   template <class Partner>
   __device__ __forceinline__ void store(const Ctx &c, int row, f32x4 v, Partner) const {
     const int64_t o = (int64_t)row * ld + c.col;
     if (gate) {
-      const f32x4 z = load4(g + o);
+      const f32x4 z{(float)c.z[0], (float)c.z[1], (float)c.z[2], (float)c.z[3]};
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] *= gate == kGateSigmoid ? 1.0f / (1.0f + expf(-z[i])) : gate_factor(gate, z[i]);
     }
@@ -146,6 +174,8 @@ struct GateEpi {
 template <typename T>
 struct StoreEpi {
   T *out; int ld;
+  int side_waves() const { return 0; }
+  __device__ __forceinline__ void commit(int) const {}
   __device__ __forceinline__ bool rotates(int) const { return false; }
   __device__ __forceinline__ int head_dim() const { return 0; }
   struct Early {};

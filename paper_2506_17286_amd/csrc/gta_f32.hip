@@ -42,6 +42,7 @@ struct GemmOperands {
   const float *A; int lda, M, K;
   const float *B[4]; int ldb[4], seg_cols[4];   // segments side by side (unused ones have 0 columns)
   int heads_per_group, a_group_stride;          // decoder: > 0; B[0] is [n_h, K, seg_cols[0]]
+  int tiles;                                    // of the launch
 };
 __device__ __forceinline__ void operand_at(const GemmOperands &g, int col, const float *&A, const float *&B, int &ldb) {
   A = g.A;
@@ -74,7 +75,8 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, E
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workgroup ids go to different XCDs; each XCD takes a contiguous eighth of the tiles, row tiles
   // fastest: neighbouring tiles share the 128-byte lines of the weights, which should reach one L2 only
-  const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  const int id = blockIdx.x, per = g.tiles / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  if (id >= g.tiles) { epi.commit((id - g.tiles) * W + wave); return; }
   const int ntm = (g.M + BM - 1) / BM, nt = at / ntm, m0 = at % ntm * BM;
   const bool rot = epi.rotates(nt * BN);
   const RowTile ct = row_tile<BN>(nt, rot, epi.head_dim());
@@ -162,7 +164,8 @@ __global__ __launch_bounds__(256) void gemm_tiles_f32_kernel(GemmOperands g, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   // consecutive workgroup ids go to different XCDs; each XCD takes a contiguous eighth of the tiles, columns
   // fastest, so that the workgroups of an XCD share row strips in its L2
-  const int id = blockIdx.x, per = gridDim.x / 8;
+  const int id = blockIdx.x, per = g.tiles / 8;
+  if (id >= g.tiles) { epi.commit((id - g.tiles) * 4 + wave); return; }
   const int at = id < per * 8 ? (id % 8) * per + id / 8 : id;
   const int nt = at % ntn, m0 = (at / ntn) * BM;
   const float *A, *B;
@@ -583,11 +586,12 @@ __global__ __launch_bounds__(256, 2) void decode_attn_f32_kernel(DecF32 a) {
 // ------------------------------------------------------------------------------ launches
 // Columns in units of 32.
 template <int BM, int BN, class Epi>
-void launch_gemm_rows_f32(const GemmOperands &g, int cols, const Epi &epi, hipStream_t st) {
+void launch_gemm_rows_f32(GemmOperands g, int cols, const Epi &epi, hipStream_t st) {
+  g.tiles = (cols / BN) * ((g.M + BM - 1) / BM);
   auto launch = [&](auto kernel, int w) {
     const int smem = w * BM * (BN + 4) * (int)sizeof(float);
     if (smem > 64 * 1024) allow_dynamic_lds((const void *)kernel, smem);
-    kernel<<<(cols / BN) * ((g.M + BM - 1) / BM), 64 * w, smem, st>>>(g, epi);
+    kernel<<<g.tiles + (epi.side_waves() + w - 1) / w, 64 * w, smem, st>>>(g, epi);
   };
   // two rounds of loads per wave at most: K = 1280 over 16 waves (64 rows of the paper's projection 16 us, 20 us with
   // eight waves of 64 columns), K = 256 over eight (5 us; 16 mostly idle waves 9 us), K = 64 over four
@@ -612,9 +616,10 @@ void launch_gemm_rows_f32(const GemmOperands &g, int cols, const Epi &epi, hipSt
 // 88; a decode step of 128 sequences 57 against 91).
 constexpr int kRowsMax = 256;
 template <class Epi>
-void launch_gemm_f32(const GemmOperands &g, int cols, const Epi &epi, hipStream_t st) {
-  if (g.M <= kRowsMax) launch_gemm_rows_f32(g, cols, epi, st);
-  else gemm_tiles_f32_kernel<Epi><<<(cols / 64) * ((g.M + 63) / 64), 256, 0, st>>>(g, cols / 64, epi);
+void launch_gemm_f32(GemmOperands g, int cols, const Epi &epi, hipStream_t st) {
+  if (g.M <= kRowsMax) { launch_gemm_rows_f32(g, cols, epi, st); return; }
+  g.tiles = (cols / 64) * ((g.M + 63) / 64);
+  gemm_tiles_f32_kernel<Epi><<<g.tiles + (epi.side_waves() + 3) / 4, 256, 0, st>>>(g, cols / 64, epi);
 }
 
 }  // namespace
@@ -674,9 +679,19 @@ static GemmOperands proj_operands(const Dims &d, const gta_weights &w, const voi
   return g;
 }
 
+// Sines worked out in the epilogue pay for few rows only: 64 x 64 tiles of 4096 rows take more time for them than a launch.
+bool f32_proj_folds(const Dims &d, int batch, int64_t M) {
+  return batch <= kFoldBatch && (!d.rope || (M <= kRowsMax && rope_angles_small(d.rope, d.rope_base)));
+}
+
 void launch_proj_f32(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
-                     const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st) {
+                     const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold, hipStream_t st) {
   ProjEpi<float, float> e = proj_epi(d, (float *)ws.q, (float *)ws.k, (float *)ws.c, (float *)ws.g, cache, slots);
+  if (fold.batch) {
+    e.fold = fold;
+    e.commit_to = view_of(cache, slots);
+    for (int j = 0; d.rope && j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
+  }
   e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
   launch_gemm_f32(proj_operands(d, w, x, M), d.wtot, e, st);
 }

@@ -934,8 +934,13 @@ size_t proj_packed_bytes(const Dims &d) {
 // the paper's layer 4000 tokens 97 / 101 (630), 5600 100.6 / 97.7 (880).
 static bool short_gemm_ok(int M, int N) { return (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= 768; }
 
+bool proj_folds(const Dims &d, int batch, int64_t M) {
+  return batch <= kFoldBatch && short_gemm_ok((int)M, d.wtot) && short_proj_folds(d, M);
+}
+
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
-                      const gta_cache *cache, const int32_t *slots, int max_len, hipStream_t st, bool rope_by_token) {
+                      const gta_cache *cache, const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold,
+                      hipStream_t st) {
   ProjArgs a{};
   a.rope_by_token = rope_by_token ? 1 : 0;
   a.x = (const bf16 *)x; a.lda = d.H; a.M = M; a.K = d.H;
@@ -950,7 +955,7 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
     a.max_batch = cache->max_batch; a.max_seq = cache->max_seq;
     a.pm = page_map_of(*cache);
   }
-  if (short_gemm_ok(M, d.wtot)) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, st); return; }
+  if (short_gemm_ok(M, d.wtot)) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
   if (proj_direct_big(d)) {
     const int nt = (d.wtot / 256) * ((M + 255) / 256);
     launch<TileBig>(proj_gemm_kernel<TileBig>, a, nt, st);

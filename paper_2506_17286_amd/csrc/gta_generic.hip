@@ -137,14 +137,6 @@ void launch_gemm(const TA *A, int64_t lda, int64_t a_bstride, int a_bdiv, const 
 }
 
 // ------------------------------------------------------------------------------ finalize
-struct CacheView {
-  void *k, *c;
-  int32_t *seq_lens, *status;
-  const int32_t *slots;
-  int max_batch, max_seq;
-  PageMap pm;
-};
-
 // Splits the raw projections into Q | K | C | gate, rotates q and k (App. B.1.1) and stores the
 // key / latent rows into the caches at row = position.  rope_by_token: the RoPE table has one row per
 // packed token (chunked prefill) instead of one per position; a position < 0 marks a skipped sequence.
@@ -186,27 +178,6 @@ __global__ void finalize_prefill_kernel(Dims d, const float *praw, const int32_t
   } else {
     G[t * d.wg_w + (col - qk_w - d.wc_w)] = v;
   }
-}
-
-// Do rows [r0, r1) of a slot all have pages?  A wave looks at 64 table entries at a time (one thread walking them waits
-// for each: 32 pages of 64 rows took 10 us).
-__device__ __forceinline__ bool rows_backed_wave(const PageMap &pm, int slot, int r0, int r1) {
-  if (!pm.table || r1 <= r0) return true;
-  const int32_t *t = pm.table + (int64_t)slot * pm.pages_per_slot;
-  bool bad = false;
-  for (int i = r0 / pm.page_size + (int)(threadIdx.x & 63); i <= (r1 - 1) / pm.page_size; i += 64) bad |= t[i] < 0 || t[i] >= pm.num_pages;
-  return !__any(bad);
-}
-
-// one wave per sequence
-__device__ __forceinline__ void prefill_commit_seq(const CacheView &cv, const int32_t *cu, int per_seq, int b) {
-  int n = cu ? cu[b + 1] - cu[b] : per_seq;
-  int slot = cv.slots ? cv.slots[b] : b;
-  if (slot < 0 || slot >= cv.max_batch) return;
-  const bool ok = n <= cv.max_seq && rows_backed_wave(cv.pm, slot, 0, n);
-  if (threadIdx.x & 63) return;
-  if (ok) cv.seq_lens[slot] = n;
-  else cv.status[slot] = GTA_ERR_CACHE_FULL;
 }
 
 // Everything a prefill call derives from the sequence offsets alone, in one launch: blocks
@@ -634,17 +605,6 @@ __global__ __launch_bounds__(256) void calibration_mfma_kernel(int iters, float 
   if (v == 123.456f) sink[threadIdx.x] = v;
 }
 
-CacheView view_of(const gta_cache *c, const int32_t *slots) {
-  CacheView v{};
-  if (c) {
-    v.k = c->k; v.c = c->c; v.seq_lens = c->seq_lens; v.status = c->status;
-    v.max_batch = c->max_batch; v.max_seq = c->max_seq;
-    v.pm = page_map_of(*c);
-  }
-  v.slots = slots;
-  return v;
-}
-
 inline dim3 grid1d(int64_t n, int block = 256) { return dim3((unsigned)((n + block - 1) / block)); }
 
 // ------------------------------------------------------------------------------ drivers
@@ -690,9 +650,12 @@ int prefill_impl(const Dims &d, const gta_weights &w, const T *x, const int32_t 
   const int per_seq = (int)(total / batch);
   const int M = (int)total;
   constexpr bool F32 = std::is_same<T, float>::value;   // fp32: MFMA kernels where the shape allows (gta_f32.hip)
-  launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
+  const bool mfma = F32 && f32_gemms_ok(d, total);
+  Fold fold{};
+  if (mfma && f32_proj_folds(d, batch, total)) fold = Fold{cu, batch, per_seq};
+  else launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
   // Sec. 3.2 projections, RoPE, cache rows: [Q | K | C | gate pre-activation]
-  if (F32 && f32_gemms_ok(d, total)) launch_proj_f32(d, w, x, M, ws, cache, slots, max_len, false, st);
+  if (mfma) launch_proj_f32(d, w, x, M, ws, cache, slots, max_len, false, fold, st);
   else project_raw<T>(d, w, x, M, ws, cache, slots, total, max_len, 0, st);
   // shared attention map x latent values, one map per group (Sec. 3.3)
   if (F32 && f32_attn_ok(d, batch, max_len)) {
@@ -716,7 +679,7 @@ int prefill_chunk_impl(const Dims &d, const gta_weights &w, const T *x, const in
   const int per_seq = (int)(total / batch);
   const int M = (int)total;
   launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, st);
-  if (std::is_same<T, float>::value && f32_gemms_ok(d, total)) launch_proj_f32(d, w, x, M, ws, &cache, slots, max_chunk, true, st);
+  if (std::is_same<T, float>::value && f32_gemms_ok(d, total)) launch_proj_f32(d, w, x, M, ws, &cache, slots, max_chunk, true, Fold{}, st);
   else project_raw<T>(d, w, x, M, ws, &cache, slots, total, max_chunk, 1, st);
   CacheView cv = view_of(&cache, slots);
   dim3 agrid((max_chunk + 3) / 4, d.nq, batch);

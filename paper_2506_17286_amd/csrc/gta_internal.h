@@ -96,6 +96,52 @@ __device__ __forceinline__ bool rows_backed(const PageMap &pm, int slot, int r0,
   return true;
 }
 
+// A cache as the kernels that look rows up see it (k NULL: none).
+struct CacheView {
+  void *k, *c;
+  int32_t *seq_lens, *status;
+  const int32_t *slots;
+  int max_batch, max_seq;
+  PageMap pm;
+};
+
+inline CacheView view_of(const gta_cache *c, const int32_t *slots) {
+  CacheView v{};
+  if (c) {
+    v.k = c->k; v.c = c->c; v.seq_lens = c->seq_lens; v.status = c->status;
+    v.max_batch = c->max_batch; v.max_seq = c->max_seq;
+    v.pm = page_map_of(*c);
+  }
+  v.slots = slots;
+  return v;
+}
+
+// Do rows [r0, r1) of a slot all have pages?  A wave looks at 64 table entries at a time (one thread walking them waits
+// for each: 32 pages of 64 rows took 10 us).
+__device__ __forceinline__ bool rows_backed_wave(const PageMap &pm, int slot, int r0, int r1) {
+  if (!pm.table || r1 <= r0) return true;
+  const int32_t *t = pm.table + (int64_t)slot * pm.pages_per_slot;
+  bool bad = false;
+  for (int i = r0 / pm.page_size + (int)(threadIdx.x & 63); i <= (r1 - 1) / pm.page_size; i += 64) bad |= t[i] < 0 || t[i] >= pm.num_pages;
+  return !__any(bad);
+}
+
+// one wave per sequence
+__device__ __forceinline__ void prefill_commit_seq(const CacheView &cv, const int32_t *cu, int per_seq, int b) {
+  int n = cu ? cu[b + 1] - cu[b] : per_seq;
+  int slot = cv.slots ? cv.slots[b] : b;
+  if (slot < 0 || slot >= cv.max_batch) return;
+  const bool ok = n <= cv.max_seq && rows_backed_wave(cv.pm, slot, 0, n);
+  if (threadIdx.x & 63) return;
+  if (ok) cv.seq_lens[slot] = n;
+  else cv.status[slot] = GTA_ERR_CACHE_FULL;
+}
+
+// A fresh prompt batch of at most kFoldBatch sequences needs no launch in front of the projection that works out positions,
+// sines and the cached lengths: with batch > 0 the projection does it.
+constexpr int kFoldBatch = 16;
+struct Fold { const int32_t *cu; int batch, per_seq; };
+
 // ---- workspace carve-up (one function per mode so sizing and use cannot disagree) ----------
 struct PrefillWs {
   int32_t *seq_id, *pos;   // [total] sequence index and position of each packed token

@@ -25,7 +25,7 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // weights side by side: W_Q | W_K | W_C | W_G, or one matrix
-struct RowsOperands { const bf16 *A; int64_t lda; int M, K; const bf16 *B[4]; int cols[4]; };
+struct RowsOperands { const bf16 *A; int64_t lda; int M, K; const bf16 *B[4]; int cols[4]; int tiles; };   // tiles: of the launch
 
 template <int W, class Epi>
 __global__ __launch_bounds__(64 * W) void gemm_rows_bf16_kernel(RowsOperands g, Epi epi) {
@@ -35,7 +35,8 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_bf16_kernel(RowsOperands g, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workgroup ids go to different XCDs; each XCD takes a contiguous eighth of the tiles, row tiles
   // fastest: neighbouring tiles share the 128-byte lines of the weights, which should reach one L2 only
-  const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  const int id = blockIdx.x, per = g.tiles / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  if (id >= g.tiles) { epi.commit((id - g.tiles) * W + wave); return; }
   const int ntm = (g.M + 31) / 32, nt = at / ntm, m0 = at % ntm * 32;
   const bool rot = epi.rotates(nt * 32);
   const RowTile ct = row_tile(nt, rot, epi.head_dim());
@@ -99,10 +100,11 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_bf16_kernel(RowsOperands g, 
 }
 
 template <class Epi>
-void launch_rows(const RowsOperands &g, int cols, const Epi &epi, hipStream_t st) {
+void launch_rows(RowsOperands g, int cols, const Epi &epi, hipStream_t st) {
   constexpr int W = 16, SMEM = W * 32 * (32 + 4) * 4;
   allow_dynamic_lds((const void *)gemm_rows_bf16_kernel<W, Epi>, SMEM);
-  gemm_rows_bf16_kernel<W, Epi><<<(cols / 32) * ((g.M + 31) / 32), 64 * W, SMEM, st>>>(g, epi);
+  g.tiles = (cols / 32) * ((g.M + 31) / 32);
+  gemm_rows_bf16_kernel<W, Epi><<<g.tiles + (epi.side_waves() + W - 1) / W, 64 * W, SMEM, st>>>(g, epi);
 }
 
 // ---- tiles of 64 rows -----------------------------------------------------------------------------
@@ -138,7 +140,8 @@ __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOp
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nh = wave % T::NH, kg = wave / T::NH;
-  const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  const int id = blockIdx.x, per = g.tiles / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
+  if (id >= g.tiles) { epi.commit((id - g.tiles) * T::NW + wave); return; }
   const int ntm = (g.M + T::BM - 1) / T::BM, nt = at / ntm, m0 = at % ntm * T::BM;
   int seg = 0, col = nt * BN;
   const bf16 *A = g.A + (int64_t)m0 * g.lda, *B;
@@ -258,10 +261,11 @@ __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOp
 }
 
 template <int BN, class Epi>
-void launch_mid(const MidOperands &o, int cols, const Epi &epi, hipStream_t st) {
+void launch_mid(MidOperands o, int cols, const Epi &epi, hipStream_t st) {
   typedef MidTile<BN> T;
   allow_dynamic_lds((const void *)gemm_mid_bf16_kernel<BN, Epi>, T::SMEM);
-  gemm_mid_bf16_kernel<BN, Epi><<<(cols / BN) * ((o.g.M + T::BM - 1) / T::BM), T::NT, T::SMEM, st>>>(o, epi);
+  o.g.tiles = (cols / BN) * ((o.g.M + T::BM - 1) / T::BM);
+  gemm_mid_bf16_kernel<BN, Epi><<<o.g.tiles + (epi.side_waves() + T::NW - 1) / T::NW, T::NT, T::SMEM, st>>>(o, epi);
 }
 
 }  // namespace
@@ -287,9 +291,10 @@ void launch_rows_proj_decode(const Dims &d, const gta_weights &w, const void *x,
   launch_rows(g, d.wtot, e, st);
 }
 
-static ProjEpi<bf16, bf16, true> prefill_epi(const Dims &d, const PrefillWs &ws, const gta_cache *cache, const int32_t *slots,
-                                             int max_len, bool rope_by_token) {
-  ProjEpi<bf16, bf16, true> e{};
+template <bool FOLD>
+static ProjEpi<bf16, bf16, true, FOLD> prefill_epi(const Dims &d, const PrefillWs &ws, const gta_cache *cache, const int32_t *slots,
+                                             int max_len, bool rope_by_token, const Fold &fold) {
+  ProjEpi<bf16, bf16, true, FOLD> e{};
   void *dst[4] = {ws.q, ws.k, ws.c, ws.g};
   const int width[4] = {d.wq_w, d.wk_w, d.wc_w, d.wg_w};
   for (int i = 0; i < 4; ++i) { e.dst[i] = (bf16 *)dst[i]; e.width[i] = width[i]; }
@@ -299,6 +304,11 @@ static ProjEpi<bf16, bf16, true> prefill_epi(const Dims &d, const PrefillWs &ws,
     e.kcache = (bf16 *)cache->k; e.ccache = (bf16 *)cache->c; e.slots = slots;
     e.max_batch = cache->max_batch; e.max_seq = cache->max_seq; e.pm = page_map_of(*cache);
   }
+  if (fold.batch) {
+    e.fold = fold;
+    e.commit_to = view_of(cache, slots);
+    for (int j = 0; d.rope && j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
+  }
   return e;
 }
 
@@ -306,18 +316,27 @@ static ProjEpi<bf16, bf16, true> prefill_epi(const Dims &d, const PrefillWs &ws,
 // equal at 320; with 160 and 80 tiles 64 and 128 columns are the same)
 static bool wide_tiles_fill(int M, int N) { return N / 128 * ((M + 63) / 64) >= 256; }
 
+// Measured whole calls, 32-row against 64-row tiles: 1B shape 33 tokens 28.6 / 33.4 us (224 tiles of 32 x 32), 65 38.4
+// / 36.5 (336); paper's layer 128 tokens 37.2 / 40.4 (224), 256 47.2 / 44.8 (448); 8 x 128 + 1024 48 tokens 54 / 45 (448)
+static bool short_rows(const Dims &d, int64_t M) { return (int64_t)(d.wtot / 32) * ((M + 31) / 32) <= 256; }
+
+// A thread of the 64-row tiles finishes 16 rotated values and would work out as many sines behind its main loop (1B shape,
+// 1000 tokens 64.4 -> 66.8 us, 1700 94 -> 104); they keep the table.  32-row tiles: paper's layer, 100 tokens 36.7 -> 33.3.
+bool short_proj_folds(const Dims &d, int64_t M) { return short_rows(d, M) && rope_angles_small(d.rope, d.rope_base); }
+
 // Prefill of few rows: q (rotated), k (rotated), latents and gate rows in bf16, key and latent rows to the caches.  Widths
 // in units of 64 (heads of 128: of 128), H a multiple of 64.
 void launch_short_proj(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
-                       const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st) {
+                       const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold, hipStream_t st) {
   const RowsOperands g{(const bf16 *)x, d.H, M, d.H, {(const bf16 *)w.wq, (const bf16 *)w.wk, (const bf16 *)w.wc, (const bf16 *)w.wg},
                        {d.wq_w, d.wk_w, d.wc_w, d.wg_w}};
-  const ProjEpi<bf16, bf16, true> e = prefill_epi(d, ws, cache, slots, max_len, rope_by_token);
   const bool wide = !(d.wq_w % 128 || d.wk_w % 128 || d.wc_w % 128 || d.wg_w % 128);
-  // Measured whole calls, 32-row against 64-row tiles: 1B shape 33 tokens 28.6 / 33.4 us (224 tiles of 32 x 32), 65 38.4
-  // / 36.5 (336); paper's layer 128 tokens 37.2 / 40.4 (224), 256 47.2 / 44.8 (448); 8 x 128 + 1024 48 tokens 54 / 45 (448)
-  if (d.wtot / 32 * ((M + 31) / 32) <= 256) launch_rows(g, d.wtot, e, st);
-  else if (wide && (d.dh == 128 || wide_tiles_fill(M, d.wtot))) launch_mid<128>(MidOperands{g, 0}, d.wtot, e, st);
+  if (short_rows(d, M)) {
+    launch_rows(g, d.wtot, prefill_epi<true>(d, ws, cache, slots, max_len, rope_by_token, fold), st);
+    return;
+  }
+  const auto e = prefill_epi<false>(d, ws, cache, slots, max_len, rope_by_token, Fold{});
+  if (wide && (d.dh == 128 || wide_tiles_fill(M, d.wtot))) launch_mid<128>(MidOperands{g, 0}, d.wtot, e, st);
   else launch_mid<64>(MidOperands{g, 0}, d.wtot, e, st);
 }
 

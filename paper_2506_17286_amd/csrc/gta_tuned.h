@@ -14,6 +14,9 @@ bool tuned_chunk_layout_ok(const gta_cache &cache);    // ... and the MFMA atten
 int tuned_prefill(const Dims &d, const gta_weights &w, const void *x, const int32_t *cu, int batch,
                   int64_t total, int max_len, const gta_cache *cache, const int32_t *slots, void *out,
                   const PrefillWs &ws, hipStream_t st);
+// setup and projection of a fresh prefill: Q, K, C and gate rows to ws, cache rows and lengths
+void tuned_project(const Dims &d, const gta_weights &w, const void *x, const int32_t *cu, int batch, int64_t total, int max_len,
+                   const gta_cache *cache, const int32_t *slots, const PrefillWs &ws, hipStream_t st);
 // chunked prefill: the chunk's tokens follow the rows the slots already hold (needs the MFMA attention kernel)
 bool tuned_prefill_chunk_supported(const Dims &d, int max_seq);
 int tuned_prefill_chunk(const Dims &d, const gta_weights &w, const void *x, const int32_t *cu, int batch,
@@ -32,8 +35,9 @@ void tuned_decode_combine(const Dims &d, const float *part, const int32_t *oldle
 bool gemm_shapes_supported(const Dims &d);
 size_t proj_packed_bytes(const Dims &d);   // workspace for the packed [H, Wtot] weights, 0 if not used
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
-                      const gta_cache *cache, const int32_t *slots, int max_len, hipStream_t st,
-                      bool rope_by_token = false);
+                      const gta_cache *cache, const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold,
+                      hipStream_t st);
+bool proj_folds(const Dims &d, int batch, int64_t M);   // may launch_proj_gemm do without the setup launch?
 void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const void *g, void *out, int M,
                          hipStream_t st);
 int skinny_ksplit(const Dims &d, int M);
@@ -63,7 +67,8 @@ bool rows_gemm_ok(const Dims &d);
 void launch_rows_proj_decode(const Dims &d, const gta_weights &w, const void *x, int batch, const gta_cache &cache,
                              const int32_t *slots, const DecodeWs &ws, hipStream_t st);
 void launch_short_proj(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
-                       const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st);
+                       const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold, hipStream_t st);
+bool short_proj_folds(const Dims &d, int64_t M);
 void launch_short_decoder(const Dims &d, const void *L, const void *wp, const void *g, void *out, int M, hipStream_t st);
 void launch_short_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st);
 void launch_rows_plain(const void *A, int64_t lda, int M, int N, int K, const void *B, void *C, hipStream_t st);
@@ -75,7 +80,8 @@ bool f32_decoder_ok(const Dims &d, int64_t M);                                //
 bool f32_attn_ok(const Dims &d, int batch, int max_len);                      // prefill attention
 bool f32_decode_ok(const Dims &d, const gta_cache &cache, int batch);         // decode step
 void launch_proj_f32(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
-                     const int32_t *slots, int max_len, bool rope_by_token, hipStream_t st);
+                     const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold, hipStream_t st);
+bool f32_proj_folds(const Dims &d, int batch, int64_t M);                     // may it do without the setup launch?
 void launch_decoder_f32(const Dims &d, const float *L, const void *wp, const float *gate, float *out, int M, hipStream_t st);
 void launch_out_proj_f32(const Dims &d, const float *O, const void *wo, float *out, int M, hipStream_t st);
 void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, const float *c, const int32_t *cu, int batch,

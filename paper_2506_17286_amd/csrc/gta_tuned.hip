@@ -5,13 +5,20 @@ namespace gta {
 
 bool tuned_prefill_supported(const Dims &d) { return gemm_shapes_supported(d); }
 
+void tuned_project(const Dims &d, const gta_weights &w, const void *x, const int32_t *cu, int batch, int64_t total, int max_len,
+                   const gta_cache *cache, const int32_t *slots, const PrefillWs &ws, hipStream_t st) {
+  Fold fold{};
+  if (proj_folds(d, batch, total)) fold = Fold{cu, batch, (int)(total / batch)};
+  else launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
+  launch_proj_gemm(d, w, x, (int)total, ws, cache, slots, max_len, false, fold, st);
+}
+
 int tuned_prefill(const Dims &d, const gta_weights &w, const void *x, const int32_t *cu, int batch, int64_t total,
                   int max_len, const gta_cache *cache, const int32_t *slots, void *out, const PrefillWs &ws,
                   hipStream_t st) {
   const int M = (int)total;
-  launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
   // Sec. 3.2 projections + App. B.1.1 RoPE + cache write, one MFMA GEMM
-  launch_proj_gemm(d, w, x, M, ws, cache, slots, max_len, st);
+  tuned_project(d, w, x, cu, batch, total, max_len, cache, slots, ws, st);
   void *heads = w.wo ? ws.o : out;   // gated heads [M, n_h*d_h]
   if (attn_decoder_fusable(d, max_len)) {
     // Sec. 3.3 with the Sec. 3.2 value decoder and gate in the attention kernel's epilogue
@@ -45,7 +52,7 @@ int tuned_prefill_chunk(const Dims &d, const gta_weights &w, const void *x, cons
                         const PrefillWs &ws, hipStream_t st) {
   const int M = (int)total;
   launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, st);
-  launch_proj_gemm(d, w, x, M, ws, &cache, slots, max_chunk, st, true);
+  launch_proj_gemm(d, w, x, M, ws, &cache, slots, max_chunk, true, Fold{}, st);
   void *heads = w.wo ? ws.o : out;
   const bool fuse = attn_decoder_fusable(d, cache.max_seq);
   launch_attn_chunk_bf16(d, ws.q, cache, slots, ws.prefix, cu, batch, total, max_chunk, ws.l, w.wp, ws.g, heads, fuse, ws.praw, st);

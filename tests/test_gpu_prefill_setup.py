@@ -52,3 +52,32 @@ def test_rope_base_below_one(dtype, call):
     pairs = lambda k: np.hypot(k[:, :wl.head_dim // 2], k[:, wl.head_dim // 2:])
     ref = pairs(x.astype(np.float64) @ w["wk"].astype(np.float64))
     U.assert_close(pairs(U.f64(rows)), ref, dtype, call, max(1.0, float(ref.max())))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("lens", [[5], [33, 64], [0, 7, 0, 0, 3, 0], [3, 1, 4, 1, 5, 9, 2, 6, 5, 3, 5, 8, 9, 7, 9, 3], [4] * 17, [6, 6]],
+                         ids=["one", "two", "empty", "sixteen", "seventeen", "no_offsets"])
+def test_prompts_without_a_setup_launch(dtype, lens):
+    """Up to 16 short prompts (of 17 a launch in front works out rows, sines and lengths): sequences without tokens at either
+    end, a missing page, no offsets.  Chunks behind nothing take the table; their rows are equal bit by bit, and so are
+    lengths and flags."""
+    wl = W.scaled(W.PAPER_WORKLOADS[1], d_model=128, dtype=dtype, seed=9300)
+    rng = W.make_rng(wl)
+    w, x = W.draw_weights(wl, rng, std=wl.d_model ** -0.5), W.draw_hidden(wl, rng, sum(lens))
+    wdev, cu = U.upload_weights(w, dtype), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    last, page = len(lens) - 1, 32
+    plain, paged, chunk = (U.DeviceCache(wl, len(lens), 128), U.PagedDeviceCache(wl, len(lens), page, 4, seed=1, missing=[(last, 0)]),
+                           U.DeviceCache(wl, len(lens), 128))
+    out = U.run_prefill(wl, wdev, x, None if lens == [6, 6] else cu, cache=plain, batch=len(lens))
+    U.run_prefill(wl, wdev, x, cu, cache=paged)
+    ref = U.run_prefill_chunk(wl, wdev, x, cu, cache=chunk)
+    assert plain.seq_lens.tolist() == lens and plain.status.tolist() == [0] * len(lens)
+    full = lens[last] > 0                                  # a sequence without tokens needs no page
+    assert paged.seq_lens.tolist() == lens[:-1] + [0 if full else lens[last]]
+    assert paged.status.tolist() == [0] * last + [B.GTA_ERR_CACHE_FULL if full else 0]
+    k, c = paged.logical()
+    for s, n in enumerate(lens):
+        assert torch.equal(plain.k[s, :n], chunk.k[s, :n]) and torch.equal(plain.c[s, :n], chunk.c[s, :n])
+        if s != last:
+            assert torch.equal(k[s, :n], chunk.k[s, :n]) and torch.equal(c[s, :n], chunk.c[s, :n])
+    U.assert_close(U.f64(out), U.f64(ref), dtype, "outputs")
