@@ -805,6 +805,13 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
 
 constexpr int kSplitTarget = 256;   // workgroups of 128 queries a launch with key splits aims at: one per CU
 
+// Key splits of a launch of `half` workgroups in key halves (rule and figures at launch_attn).
+int key_splits(const AttnArgs &a, int64_t half, int max_keys) {
+  const int64_t most = (int64_t)(max_keys + 31) / 32 >> (a.prefix ? 4 : 5), n = std::min(kSplitTarget / half, most);
+  return n < 1 ? 1 : (int)n;
+}
+int64_t half_workgroups(const Dims &d, int batch, int max_len, int dlw) { return (int64_t)((max_len + 127) / 128) * batch * d.nq * (d.dl / dlw); }
+
 // max_keys: host bound of a sequence's keys.  part: scratch for key splits (attn_split_bytes) or NULL.
 template <int DH, int DLW, bool FUSE>
 void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys, float *part, hipStream_t st) {
@@ -816,7 +823,7 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
   // 8 x 600 behind 4000 290 / 291 (320), 5 x 2000 ragged behind 5000 389 / 421 (640); paper shape 4 x 2048 138 / 125
   // (256).  Up to 1024 keys the chain is too short for more than one round of the two halves: 8 x 1000 191 / 196 (512),
   // paper 16 x 700 154 / 160 (384), but 2 x 1000 99 / 91 (64); up to 256 keys it is never worth it: 1 x 128 40.7 / 42.2.
-  const int64_t half = (int64_t)((max_len + 127) / 128) * batch * d.nq * (d.dl / DLW);
+  const int64_t half = half_workgroups(d, batch, max_len, DLW);
   a.splits = 1;
   if (half > 512 || max_keys <= 256 || (half > 256 && max_keys <= 1024)) {
     launch_tile<AttnTile<DH, DLW, 1>, FUSE>(a, d, batch, max_len, st);
@@ -828,11 +835,9 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
     // 80 with up to 23 splits, 67 with 11; 4 x 40 behind 6000 153 / 76; 1 x 2000 fresh 124 / 120.  max_keys is only the
     // capacity of the slots: the kernels count a sequence's own keys (splits_of).
     a.split_shift = a.prefix ? 4 : 5;
-    const int64_t most = (int64_t)(max_keys + 31) / 32 >> a.split_shift;
-    a.splits = (int)(kSplitTarget / half < most ? kSplitTarget / half : most);
+    a.splits = key_splits(a, half, max_keys);
     const int64_t stats = a.total * d.nq * (d.dl / DLW) * 2;   // floats per split
     while (a.splits > 1 && (size_t)(a.splits * (stats + a.total * d.nq * d.dl) + 64) * 4 > attn_split_bytes(d)) --a.splits;
-    if (a.splits < 1) a.splits = 1;
     a.pml = reinterpret_cast<float2 *>(part);
     a.pacc = part + ((a.splits * stats + 63) & ~(int64_t)63);
   }
@@ -846,7 +851,16 @@ template <bool FUSE>
 void launch_attn_any(const AttnArgs &a, const Dims &d, int batch, int max_len, int max_keys, float *part, hipStream_t st) {
   if constexpr (FUSE) { launch_attn<64, 128, true>(a, d, batch, max_len, max_keys, part, st); return; }
   const int dlw = latent_tile(d);
-  if (d.dh == 128 && dlw == 256) launch_attn<128, 256, false>(a, d, batch, max_len, max_keys, part, st);
+  // Tiles of 128 latent columns recompute the scores twice as often as tiles of 256, a third more matrix work at latents of
+  // 512, but where the chip has room for twice the workgroups the chain of key steps that the call waits for has a third less
+  // in it.  Whole calls, 256 against 128 columns (workgroups of 256): 1B shape fresh 1 x 500 47.2 / 43.7 us (32), 1 x 1000
+  // 64.0 / 58.4 (64), 1 x 2000 110.6 / 100.7 (128), 1 x 3000 136 / 126 (192), 2 x 1500 ragged 121 / 115 (192), 1 x 4000 167.9 /
+  // 165.9 (256), 24 x 128 97.0 / 97.5 (192); 8 x 128 + 1024 shape 1 x 512 76.5 / 72.6 (128), 1 x 1000 129.2 / 130.3 (256).
+  // Chunks, whose chains are alike: 40 behind 6000 62.0 / 57.6 (88), 300 behind 1000 63.1 / 57.1, 2 x 500 behind 4000 91.1 /
+  // 95.0 (256), 3 x 700 behind 4000 167 / 211 (144).
+  const int64_t wide = dlw == 256 ? half_workgroups(d, batch, max_len, 256) : 0;
+  if (wide && (!part || wide * key_splits(a, wide, max_keys) > (a.prefix ? 128 : 255)))
+    launch_attn<128, 256, false>(a, d, batch, max_len, max_keys, part, st);
   else if (d.dh == 128) launch_attn<128, 128, false>(a, d, batch, max_len, max_keys, part, st);
   else if (dlw == 128) launch_attn<64, 128, false>(a, d, batch, max_len, max_keys, part, st);
   else launch_attn<64, 64, false>(a, d, batch, max_len, max_keys, part, st);

@@ -121,21 +121,21 @@ void launch_rows(RowsOperands g, int cols, const Epi &epi, hipStream_t st) {
 // read-MFMA chain of a step.  Measured against a split-K projection with fp32 partials in memory plus a finishing kernel
 // and two-stage 64-row tiles for decoder and W_O, whole calls: 1B shape 500 tokens 60.7 -> 47.9 us, 1000 82 -> 66, 1500
 // 105 -> 88; paper's layer 500 tokens 55 -> 43, 2000 84 -> 67; 8 x 128 + 1024 shape 1000 tokens 169 -> 130 us.  Four
-// stages (one workgroup per CU) gain 1 % up to one tile per CU and lose 10 to 18 % beyond.
+// stages (one workgroup per CU) lose 10 to 18 % beyond one tile per CU; up to there SUB = 2 stages make a step.
 struct MidOperands { RowsOperands g; int hpq; };   // hpq > 0: value decoder, one matrix [K, BN] per head and hpq heads per row operand
 
-template <int BN_>
+template <int BN_, int SUB_ = 1>
 struct MidTile {
-  static constexpr int BN = BN_, BM = 64, BK = 64, KG = 4, NH = BN / 64, NW = KG * NH, NT = 64 * NW, NSTAGE = 3;
+  static constexpr int SUB = SUB_, BN = BN_, BM = 64, BK = 64, KG = 4, NH = BN / 64, NW = KG * NH, NT = 64 * NW, NSTAGE = 3;
   static constexpr int X_BYTES = BM * BK * 2, STAGE = X_BYTES + BK * BN * 2;
   static constexpr int XL = X_BYTES / 1024 / NW, WL = BK * BN * 2 / 1024 / NW;   // load instructions per wave and stage
   static constexpr int PITCH = BN + 4, RED = BM * PITCH * 4;                     // a partial tile in LDS (fp32)
-  static constexpr int SMEM = NSTAGE * STAGE > 2 * RED ? NSTAGE * STAGE : 2 * RED;
+  static constexpr int RING = NSTAGE * SUB * STAGE, SMEM = RING > 2 * RED ? RING : 2 * RED;
 };
 
-template <int BN, class Epi>
-__global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOperands o, Epi epi) {
-  typedef MidTile<BN> T;
+template <int BN, int SUB, class Epi>
+__global__ __launch_bounds__(MidTile<BN>::NT, SUB == 1 ? 4 : 2) void gemm_mid_bf16_kernel(MidOperands o, Epi epi) {
+  typedef MidTile<BN, SUB> T;
   const RowsOperands &g = o.g;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
@@ -175,9 +175,9 @@ __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOp
   const u32x4 xr = buffer_of(A, (unsigned)((rv - 1) * g.lda * 2) + (unsigned)g.K * 2u);
   const char *wbase = reinterpret_cast<const char *>(B);   // of the stage that is requested next
   const unsigned wbytes = (unsigned)((T::BK - 1) * ldb * 2 + BN * 2);
-  const int nk = g.K / T::BK;
+  const int nk = g.K / T::BK / SUB;   // steps
   unsigned fill = 0, xs = 0;   // LDS offset and k offset of the stage that is requested next
-  auto request = [&] {
+  auto request_stage = [&] {
 #pragma unroll
     for (int j = 0; j < T::XL; ++j) load_to_lds(xr, xv[j], xs, lds0 + fill + (wave + T::NW * j) * 1024);
     const u32x4 wr = buffer_of(wbase, wbytes);
@@ -185,7 +185,11 @@ __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOp
     for (int j = 0; j < T::WL; ++j) load_to_lds(wr, wv[j], 0u, lds0 + fill + T::X_BYTES + (wave + T::NW * j) * 1024);
     xs += T::BK * 2;
     wbase += (int64_t)T::BK * ldb * 2;
-    fill = fill == (T::NSTAGE - 1) * T::STAGE ? 0u : fill + T::STAGE;
+    fill = fill == T::RING - T::STAGE ? 0u : fill + T::STAGE;
+  };
+  auto request = [&] {
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) request_stage();
   };
   const int xo = ln * 128 + ((kg * 2 + h) ^ (ln & 7) ^ ((ln >> 3) & 1)) * 16;
   const int wq = (lane & 15) >> 2, sw = BN == 128 ? wq << 2 : (wq & 2) << 1;
@@ -202,28 +206,33 @@ __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOp
   int cur = 0;
 #pragma unroll 1
   for (int t = 0; t < nk; ++t) {
-    if (t + T::NSTAGE - 1 <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((T::NSTAGE - 2) * (T::XL + T::WL)) : "memory");
+    if (t + T::NSTAGE - 1 <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((T::NSTAGE - 2) * SUB * (T::XL + T::WL)) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const char *st = smem + cur;
-    cur = cur == (T::NSTAGE - 1) * T::STAGE ? 0 : cur + T::STAGE;
-    s16x4 lo[2], hi[2];
-    bf16x8 x[2];
+    s16x4 lo[SUB][2], hi[SUB][2];
+    bf16x8 x[SUB][2];
 #pragma unroll
-    for (int tn = 0; tn < 2; ++tn) {
-      lo[tn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn]));
-      hi[tn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn] + 4 * BN * 2));
-      x[tn] = *reinterpret_cast<const bf16x8 *>(st + xo + tn * 32 * 128);
+    for (int u = 0; u < SUB; ++u) {
+      const char *st = smem + cur + u * T::STAGE;
+#pragma unroll
+      for (int tn = 0; tn < 2; ++tn) {
+        lo[u][tn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn]));
+        hi[u][tn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn] + 4 * BN * 2));
+        x[u][tn] = *reinterpret_cast<const bf16x8 *>(st + xo + tn * 32 * 128);
+      }
     }
+    cur = cur == T::RING - SUB * T::STAGE ? 0 : cur + SUB * T::STAGE;
     __builtin_amdgcn_sched_barrier(0);
     if (t + T::NSTAGE - 1 < nk) request();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int tn = 0; tn < 2; ++tn)
+    for (int u = 0; u < SUB; ++u)
 #pragma unroll
-      for (int tm = 0; tm < 2; ++tm) {
-        const s16x8 w8 = __builtin_shufflevector(lo[tn], hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
-        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), x[tm], acc[tn][tm], 0, 0, 0);
-      }
+      for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+          const s16x8 w8 = __builtin_shufflevector(lo[u][tn], hi[u][tn], 0, 1, 2, 3, 4, 5, 6, 7);
+          acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), x[u][tm], acc[tn][tm], 0, 0, 0);
+        }
   }
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every wave is done with the stages
   float *mine = reinterpret_cast<float *>(smem + (kg >> 1) * T::RED) + ln * T::PITCH + nh * 64 + 4 * h;
@@ -260,12 +269,19 @@ __global__ __launch_bounds__(MidTile<BN>::NT, 4) void gemm_mid_bf16_kernel(MidOp
   }
 }
 
+template <int BN, int SUB, class Epi>
+void launch_mid_tiles(const MidOperands &o, const Epi &epi, hipStream_t st) {
+  typedef MidTile<BN, SUB> T;
+  allow_dynamic_lds((const void *)gemm_mid_bf16_kernel<BN, SUB, Epi>, T::SMEM);
+  gemm_mid_bf16_kernel<BN, SUB, Epi><<<o.g.tiles + (epi.side_waves() + T::NW - 1) / T::NW, T::NT, T::SMEM, st>>>(o, epi);
+}
+// Where no CU gets a second tile a step takes two stages, so that it has half the barriers and more loads in flight (1B shape,
+// whole call of 500 tokens 43.7 -> 42.9 us, 256 39.2 -> 38.2; paper's layer 500 tokens 44.0 -> 42.8).
 template <int BN, class Epi>
 void launch_mid(MidOperands o, int cols, const Epi &epi, hipStream_t st) {
-  typedef MidTile<BN> T;
-  allow_dynamic_lds((const void *)gemm_mid_bf16_kernel<BN, Epi>, T::SMEM);
-  o.g.tiles = (cols / BN) * ((o.g.M + T::BM - 1) / T::BM);
-  gemm_mid_bf16_kernel<BN, Epi><<<o.g.tiles + (epi.side_waves() + T::NW - 1) / T::NW, T::NT, T::SMEM, st>>>(o, epi);
+  o.g.tiles = (cols / BN) * ((o.g.M + 63) / 64);
+  if (o.g.tiles <= 256 && o.g.K % 128 == 0) launch_mid_tiles<BN, 2>(o, epi, st);
+  else launch_mid_tiles<BN, 1>(o, epi, st);
 }
 
 }  // namespace
@@ -321,7 +337,8 @@ static bool wide_tiles_fill(int M, int N) { return N / 128 * ((M + 63) / 64) >= 
 static bool short_rows(const Dims &d, int64_t M) { return (int64_t)(d.wtot / 32) * ((M + 31) / 32) <= 256; }
 
 // A thread of the 64-row tiles finishes 16 rotated values and would work out as many sines behind its main loop (1B shape,
-// 1000 tokens 64.4 -> 66.8 us, 1700 94 -> 104); they keep the table.  32-row tiles: paper's layer, 100 tokens 36.7 -> 33.3.
+// 1000 tokens 64.4 -> 66.8 us, 1700 94 -> 104), or 8 under its first loads (500 tokens 42.9 -> 44.2, one tile per CU); they
+// keep the table.  32-row tiles: paper's layer, 100 tokens 36.7 -> 33.3.
 bool short_proj_folds(const Dims &d, int64_t M) { return short_rows(d, M) && rope_angles_small(d.rope, d.rope_base); }
 
 // Prefill of few rows: q (rotated), k (rotated), latents and gate rows in bf16, key and latent rows to the caches.  Widths

@@ -185,3 +185,25 @@ def test_how_far_a_nan_token_reaches_back(shape, bound):
     _check(wl, w, x[:bad - 63], k[0].astype(np.float64), c[0].astype(np.float64), prefix[0], got[:bad - 63], f"{shape} before")
     assert np.isnan(got[bad:lens[0]]).all()
     _check(wl, w, x[cu[1]:cu[2]], k[1].astype(np.float64), c[1].astype(np.float64), prefix[1], got[cu[1]:cu[2]], f"{shape} beside")
+
+
+@pytest.mark.parametrize("chunk,batch", [(False, 15), (False, 16), (True, 16), (True, 17)])
+def test_latent_tile_changes_over(chunk, batch):
+    """Either side of the rule that gives launches of few workgroups latent tiles of 128 columns: 15 (240 workgroups of 256
+    columns) and 16 prompts of two query tiles, 16 and 17 chunks of one, with full, partial and single-row tiles."""
+    lens = [40 if chunk else 129] * batch
+    lens[1], lens[2] = 1, 128
+    prefix, cap = [7 * b for b in range(batch)] if chunk else [0] * batch, 320
+    wl, w, x, rng = _setup("1b", sum(lens))
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    wdev = U.upload_weights(w, "bf16")
+    if chunk:
+        cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+        out = U.f64(U.run_prefill_chunk(wl, wdev, x, cu, cache, max_chunk=128))
+    else:
+        out = U.f64(U.run_prefill(wl, wdev, x, cu, cache=cache))
+    for b in range(batch):
+        _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
+               f"sequence {b}: {lens[b]} behind {prefix[b]}")

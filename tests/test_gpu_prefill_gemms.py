@@ -48,6 +48,12 @@ def test_other_gates(layer, rows, gate):
     _check(LAYERS[layer], rows, gate)
 
 
+@pytest.mark.parametrize("layer,rows", [("packed", 576), ("packed", 577), ("k256", 1600), ("k256", 1601)])
+def test_second_tile_on_a_cu(layer, rows):
+    """252 and 280 tiles of 64 x 64, 250 and 260 of 64 x 128 in the projection: two stages a step or one."""
+    _check(LAYERS[layer], rows, True)
+
+
 def _check(wl, rows, gate):
     cfg = B.config_of(wl)
     cfg.gate = B.GATE_CODES[gate]
