@@ -97,7 +97,7 @@ struct AttnArgs {
   bf16 *L;                   // [total, n_q*d_l]
   const int32_t *cu; int per_seq;
   int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, ndlc, batch;
-  int n_qtiles, levels, spread;   // query tiles of the longest sequence; bound of the levels, order of the tiles (tile_of_rank)
+  int n_qtiles, levels, spread, every;   // query tiles of the longest sequence; bound of the levels, order of the tiles (tile_of_rank)
   float scale_log2e;
   // fused value decoder (kernel template flag): O_i = (L_g W_{P,i}) * Sigmoid(gate) for the heads of g
   const bf16 *wp, *gate;     // [n_h, d_l, d_h]; gate pre-activations [total, n_h*d_h] or NULL (gate off)
@@ -244,7 +244,15 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
     u = round * 8 + (round & 1 ? 7 - x : x);
   }
   QueryTile tile;
-  if (!tile_of_rank(a, T::BQ, u, tile)) return;
+  if (a.every) {   // an id for every (level, sequence)
+    const int lvl = u / a.batch;
+    tile.b = u - lvl * a.batch;
+    tile.qt = a.n_qtiles - 1 - lvl;
+    tile.start = a.cu ? a.cu[tile.b] : tile.b * a.per_seq;
+    tile.len = a.cu ? a.cu[tile.b + 1] - tile.start : a.per_seq;
+    tile.prefix = a.prefix ? a.prefix[tile.b] : 0;
+    if (tile.qt * T::BQ >= tile.len) return;
+  } else if (!tile_of_rank(a, T::BQ, u, tile)) return;
   const int g = r % a.nq, dlc = r / a.nq % a.ndlc, split = r / (a.nq * a.ndlc);
   const int64_t start = tile.start;
   const int Tb = tile.len, q0 = tile.qt * T::BQ;             // queries of this sequence, first of this tile
@@ -795,7 +803,12 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   a.levels = a.n_qtiles + (a.prefix ? a.max_seq / T::BQ : 0) + 1;
   // no more than this many query tiles whatever the lengths are
   int64_t tiles = std::min((int64_t)a.n_qtiles * batch, a.total / T::BQ + batch);
-  a.spread = tiles < kSpreadTiles;
+  // Where the chip holds every (level, sequence) at once the order means nothing and tiles need no ranks (two workgroups
+  // of four waves on a CU, one of eight): ragged calls, with and without ranks, paper's layers 7 x 41..331 tokens 41.4 / 40.8
+  // us, 8 x 10..80 42.2 / 41.5, 32 x 20..100 67.7 / 66.8, 1B shape 4 x 10..40 behind 6000 70.0 / 68.8.
+  a.every = batch > 1 && (int64_t)a.n_qtiles * batch * a.nq * a.ndlc * a.splits <= 512 / T::KS;
+  if (a.every) tiles = (int64_t)a.n_qtiles * batch;
+  a.spread = a.every || tiles < kSpreadTiles;
   if (!a.spread) tiles = (tiles + 7) / 8 * 8;
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;
