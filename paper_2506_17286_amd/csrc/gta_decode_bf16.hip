@@ -465,33 +465,53 @@ __global__ __launch_bounds__(256, S::OCC) void decode_attn_kernel(DecAttnArgs a,
   }
 }
 
-// ---- narrow rows: one shared key of 64 and one latent of 128 (the paper's own model shapes) --------
-// A cache row is only 128 + 256 bytes, so one 1 KiB wave load covers 8 key rows (8 lanes each) or 4
-// latent rows (16 lanes each).  A wave takes 8 rows per step: one key load and two latent loads.
-// Scores are formed in the key layout (lane l: row l/8), the latent accumulators live in the latent
-// layout (lane l: rows l/16 and 4 + l/16 of the step), so a wave runs four independent online-softmax
-// streams (rows c and c+4 of every step, c = 0..3): the two key-layout lane groups of a stream are 32
-// lanes apart and agree on its statistics with one exchange, and the latent-layout lanes of stream c
-// fetch its two probabilities (one bf16 pair) and its rescale factor from lane 8c.  Scores and the
-// probability-times-latent update are bf16 dot products with fp32 sums (v_dot2_f32_bf16, two rows per
-// instruction), which is what keeps the kernel from being bound by VALU issue.  Streams, waves and
-// splits are merged with the usual log-sum-exp weights.  Same three call modes as the kernel above.
-// NC = 2 is the variant with two latents of 128 per row (a wave load covers 2 latent rows): two
-// streams of four rows a step, each lane accumulating the maps of its own latent.
-template <int NQ, int NC = 1>
-__global__ __launch_bounds__(256) void decode_narrow_kernel(DecAttnArgs a, RopeFreq rf) {
-  constexpr int DH = 64, DL = 128, WQ = NQ * DH, WK = DH, WC = NC * DL, half = DH / 2, R = 8;
+// maximum / sum over the four lanes that differ in lane / 16; every lane gets it
+typedef unsigned int dec_u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float rows_max(float v) {
+  dec_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float rows_sum(float v) {
+  dec_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Streaming decode attention for the paper's narrow cache rows: ONE key of 64 and NC latents of 128 per row (384 or 640
+// bytes), NQ <= 16 maps.  A wave takes 16 rows per step.  Scores S[row][map] = K Q^T are two MFMAs of 16 x 16 x 32 (the
+// maps padded to 16 columns), whose result leaves a lane with four rows of one map: softmax statistics are per lane, and the
+// four probabilities are, as they stand, the column operand of the second product L^T[column][map] += C^T P^T.  Its
+// row operand wants four rows of one latent column per lane; a lane loads 16 bytes of each of its four rows (16 lanes cover
+// a row) and pairs them up with v_perm_b32, two MFMAs of 16 x 16 x 16 for each of the eight columns it holds: probabilities
+// are bf16 pairs, the rounded value and what it lacks.  (Rounded once, a step's error against 64 bits was 2.8e-3 to 3.0e-3
+// where the vector kernel before it, with more and shorter streams whose largest probability is exactly 1, had 2.5e-3 to
+// 2.9e-3; with the pair 2.6e-3 to 2.7e-3, at the same time.)  Queries are rounded to bf16, sums are fp32.
+// Bound: at 50 MB a step the launch, a workgroup's chain of loads and the merge (HBM from about 100 MB on); a step of 16 rows
+// is about 65 vector and 18 (34) matrix instructions.  With scores, softmax and latents on the vector ALU, where each lane
+// worked out the softmax of a row that eight of them share, 8 rows took about 200, and the waves of a CU took longer over them
+// than the memory over their rows.  Whole steps, before and now: 5 maps 64 x 2048 40.1 -> 31.8 us, 1 x 1000 26.2 -> 21.5, 32 x
+// 8192 49.4 -> 38.8, 128 x 250..2000 47.1 -> 36.3, 3 maps 64 x 2048 33.2 -> 29.2; two latents, 10 maps 64 x 2048 61.5 -> 37.6,
+// 16 x 4000 43.0 -> 29.6.  Two, three or four steps in flight per wave: 31.8 / 32.1 / 32.7 us at 64 x 2048.  Same three call
+// modes as the kernel above.
+template <int NQ, int NC>
+__global__ __launch_bounds__(256, 2) void decode_narrow_kernel(DecAttnArgs a, RopeFreq rf) {
+  constexpr int DH = 64, DL = 128, WQ = NQ * DH, WK = DH, WC = NC * DL, half = DH / 2, R = 16;
   constexpr int KROW = WK / 8, CROW = WC / 8;   // 16-byte words per cache row
   constexpr int QPC = NQ / NC;                  // maps per latent
-  constexpr int NCL = 2 * NC, RPL = R / NCL;    // latent loads per step, rows per latent load
-  static_assert((NC == 1 || NC == 2) && NQ % NC == 0, "one or two latents");
+  constexpr int PITCH = DL + 4, NBUF = 2;   // steps in flight per wave
+  static_assert((NC == 1 || NC == 2) && NQ % NC == 0 && NQ <= 16, "one or two latents");
   static_assert(WQ / 2 <= 512 && WC <= 256, "prologue mapping");
-  __shared__ float sm[kWaves][NQ], sl[kWaves][NQ];
-  __shared__ float lacc[kWaves * NQ * DL];   // one copy per wave: they merge in one pass
-  __shared__ float qs[WQ];                                       // rotated queries * scale * log2(e)
-  __shared__ __attribute__((aligned(16))) bf16 newrow[WK + WC];  // fused step: the new token's k | c row
+  typedef __attribute__((ext_vector_type(4))) short s16x4;
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  __shared__ float sm[kWaves][16], sl[kWaves][16];
+  __shared__ __attribute__((aligned(16))) float lacc[kWaves][NQ][PITCH];   // one copy per wave: they merge in one pass
+  __shared__ __attribute__((aligned(16))) float qs[WQ];                    // fused step: rotated queries * scale * log2(e)
+  __shared__ __attribute__((aligned(16))) bf16 newrow[WK + WC];            // fused step: the new token's k | c row
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ln = lane & 15, kq = lane >> 4;
   const int s = blockIdx.x, b = blockIdx.y, splits = a.splits;
   float *pa = a.pacc + (int64_t)(b * splits + s) * NQ * DL;
   float *pm = a.pml + (int64_t)(b * splits + s) * NQ * 2;
@@ -526,27 +546,25 @@ __global__ __launch_bounds__(256) void decode_narrow_kernel(DecAttnArgs a, RopeF
     return ((int64_t)pg << a.ps_shift) + (jb & (a.pm.page_size - 1));
   };
 
-  float m[NQ], l[NQ], acc[QPC][8];   // a latent-layout lane accumulates the maps of its own latent
-#pragma unroll
-  for (int g = 0; g < NQ; ++g) { m[g] = -INFINITY; l[g] = 0.f; }
-#pragma unroll
-  for (int v = 0; v < QPC; ++v)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[v][e] = 0.f;
   const int nblk = (j1 - j0 + R - 1) / R;   // j1 - j0 may be 0 (only the new row)
-  struct Blk { u32x4 k, c[NCL]; };
-  Blk bA, bB, bC, bD;   // four steps (3 or 5 KiB each) in flight per wave
+  struct Blk { u32x4 k[2], c[NC][4]; };
+  Blk buf[NBUF];
   auto load = [&](Blk &bk, int blk) {   // rows past the slice re-read its last row; weight 0
     const int jb = j0 + blk * R, last = j1 - 1 - jb;
     const int64_t rb = row0(jb);
-    bk.k = __builtin_nontemporal_load(Kp + (rb + min(lane >> 3, last)) * KROW + (lane & 7));
+    const u32x4 *kp = Kp + (rb + min(ln, last)) * KROW + kq;
 #pragma unroll
-    for (int i = 0; i < NCL; ++i)
-      bk.c[i] = __builtin_nontemporal_load(Cp + (rb + min(i * RPL + lane / CROW, last)) * CROW + lane % CROW);
+    for (int i = 0; i < 2; ++i) bk.k[i] = __builtin_nontemporal_load(kp + 4 * i);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const u32x4 *cp = Cp + (rb + min(4 * kq + r, last)) * CROW + ln;
+#pragma unroll
+      for (int i = 0; i < NC; ++i) bk.c[i][r] = __builtin_nontemporal_load(cp + 16 * i);
+    }
   };
 
-  // ---- queries (and the new row) into LDS; the first cache blocks are requested right behind the
-  // partial sums so that the stream is in flight while the queries are reduced and rotated
+  // ---- queries (and the new row); the first cache blocks are requested right behind their operands so that the stream
+  // is in flight while the queries are reduced and rotated
   const int64_t pstride = (int64_t)a.batch * a.wtot;
   const float *pb = a.praw ? a.praw + (int64_t)b * a.wtot : nullptr;
   auto col_sum = [&](int c) {
@@ -567,225 +585,168 @@ __global__ __launch_bounds__(256) void decode_narrow_kernel(DecAttnArgs a, RopeF
   };
   constexpr int QPT = (WQ / 2 + 255) / 256;   // rotation pairs (qc0, qc0 + d_h/2) per thread
   float q_lo[QPT], q_hi[QPT];
+  f32x4 qd[2][2];                             // finished queries: this lane's operand (map ln, elements 32 i + 8 kq ..)
+  if (a.praw) {
 #pragma unroll
-  for (int i = 0; i < QPT; ++i) {
-    const int pi = tid + i * 256, qc0 = (pi / half) * DH + pi % half;
-    q_lo[i] = q_hi[i] = 0.f;
-    if (pi < WQ / 2) {
-      if (a.praw) { q_lo[i] = col_sum(qc0); q_hi[i] = col_sum(qc0 + half); }
-      else { q_lo[i] = a.q_direct[(int64_t)b * WQ + qc0]; q_hi[i] = a.q_direct[(int64_t)b * WQ + qc0 + half]; }
+    for (int i = 0; i < QPT; ++i) {
+      const int pi = tid + i * 256, qc0 = (pi / half) * DH + pi % half;
+      q_lo[i] = q_hi[i] = 0.f;
+      if (pi < WQ / 2) { q_lo[i] = col_sum(qc0); q_hi[i] = col_sum(qc0 + half); }
     }
+  } else {
+    const f32x4 *qp = reinterpret_cast<const f32x4 *>(a.q_direct + (int64_t)b * WQ + min(ln, NQ - 1) * DH + 8 * kq);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { qd[i][0] = qp[8 * i]; qd[i][1] = qp[8 * i + 1]; }
   }
   __builtin_amdgcn_sched_barrier(0);
-  if (wave < nblk) load(bA, wave);
-  if (wave + kWaves < nblk) load(bB, wave + kWaves);
-  if (wave + 2 * kWaves < nblk) load(bC, wave + 2 * kWaves);
-  if (wave + 3 * kWaves < nblk) load(bD, wave + 3 * kWaves);
-  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < QPT; ++i) {
-    const int pi = tid + i * 256, qc0 = (pi / half) * DH + pi % half;
-    if (pi < WQ / 2) {
-      if (a.praw) rotate(q_lo[i], q_hi[i], pi % half);
-      qs[qc0] = q_lo[i] * a.scale_log2e;
-      qs[qc0 + half] = q_hi[i] * a.scale_log2e;
+  for (int u = 0; u < NBUF; ++u)
+    if (wave + u * kWaves < nblk) load(buf[u], wave + u * kWaves);
+  __builtin_amdgcn_sched_barrier(0);
+  if (a.praw) {
+#pragma unroll
+    for (int i = 0; i < QPT; ++i) {
+      const int pi = tid + i * 256, qc0 = (pi / half) * DH + pi % half;
+      if (pi < WQ / 2) {
+        rotate(q_lo[i], q_hi[i], pi % half);
+        qs[qc0] = q_lo[i] * a.scale_log2e;
+        qs[qc0 + half] = q_hi[i] * a.scale_log2e;
+      }
     }
+    if (has_new) {   // the new token's key row (rotated) and latent row: LDS for this workgroup, cache for the rest
+      const int64_t nr = cache_row(a.pm, a.max_seq, slot, old);   // >= 0: checked where old was set
+      bf16 *krow = a.kc + nr * WK, *crow = a.cc + nr * WC;
+      if (tid < half) {
+        float k_lo = col_sum(WQ + tid), k_hi = col_sum(WQ + tid + half);
+        rotate(k_lo, k_hi, tid);
+        const bf16 rl = (bf16)k_lo, rh = (bf16)k_hi;
+        newrow[tid] = rl; newrow[tid + half] = rh;
+        krow[tid] = rl; krow[tid + half] = rh;
+      }
+      const int c = NC == 1 ? tid - 64 : tid;   // one latent: waves 1 and 2, beside the key row's wave
+      if (c >= 0 && c < WC) {
+        const bf16 r = (bf16)col_sum(WQ + WK + c);
+        newrow[WK + c] = r;
+        crow[c] = r;
+      }
+    }
+    __syncthreads();
+    const f32x4 *qp = reinterpret_cast<const f32x4 *>(qs + min(ln, NQ - 1) * DH + 8 * kq);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { qd[i][0] = qp[8 * i]; qd[i][1] = qp[8 * i + 1]; }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { qd[i][0] *= a.scale_log2e; qd[i][1] *= a.scale_log2e; }
   }
-  if (has_new) {   // the new token's key row (rotated) and latent row: LDS for this workgroup, cache for the rest
-    const int64_t nr = cache_row(a.pm, a.max_seq, slot, old);   // >= 0: checked where old was set
-    bf16 *krow = a.kc + nr * WK, *crow = a.cc + nr * WC;
-    if (tid < half) {
-      float k_lo = col_sum(WQ + tid), k_hi = col_sum(WQ + tid + half);
-      rotate(k_lo, k_hi, tid);
-      const bf16 rl = (bf16)k_lo, rh = (bf16)k_hi;
-      newrow[tid] = rl; newrow[tid + half] = rh;
-      krow[tid] = rl; krow[tid + half] = rh;
-    }
-    const int c = NC == 1 ? tid - 64 : tid;   // one latent: waves 1 and 2, beside the key row's wave
-    if (c >= 0 && c < WC) {
-      const bf16 r = (bf16)col_sum(WQ + WK + c);
-      newrow[WK + c] = r;
-      crow[c] = r;
-    }
-  }
-  __syncthreads();
+  bf16x8 qf[2];   // columns past the last map repeat it; their results are not stored
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qf[i][e] = (bf16)qd[i][e / 4][e % 4];
 
-  // this lane's eighth of every query as bf16 pairs: the scores are bf16 dot products with fp32 sums
-  // (v_dot2_f32_bf16), the precision the prefill kernels give the same product
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-  bf16x2 qh[NQ][4];
+  f32x4 acc[NC][8];   // element r of acc[c][e]: column 8 (4 kq + r) + e of latent c, map ln
 #pragma unroll
-  for (int g = 0; g < NQ; ++g)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      bf16x2 t;
-      t[0] = (bf16)qs[g * DH + (lane & 7) * 8 + 2 * w];
-      t[1] = (bf16)qs[g * DH + (lane & 7) * 8 + 2 * w + 1];
-      qh[g][w] = t;
-    }
-  const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
-  // Key layout: lane l holds row l/8 of the step.  Latent layout: lane l holds rows i*RPL + l/CROW of
-  // the step (i = 0 .. NCL-1), i.e. stream c = l/CROW takes rows c, c+RPL, ..., and the maps of latent
-  // (l%CROW)/16.  One latent: 4 streams of 2 rows a step; two latents: 2 streams of 4 rows a step,
-  // taken as two row pairs (c, c+2) and (c+4, c+6).  src = the key-layout lane on row c that hands
-  // this lane its probabilities: with two latents, the odd lanes of a key row hold the second latent's maps.
-  const int strm = lane / CROW, cgl = (lane % CROW) >> 4;
-  const int src = strm * 8 + cgl;
-  constexpr int PAIR_X = NC == 1 ? 32 : 16;   // lane distance to the other row of a pair (row ^ 4 or row ^ 2)
-  auto compute = [&](const Blk &bk, int nv) {
-    float corr[NQ];
-    bf16x2 pk[NQ];   // (probability of this lane's row, of its pair's other row), rounded as the MFMA paths do
-    const unsigned kw[4] = {bk.k.x, bk.k.y, bk.k.z, bk.k.w};
-    const bool valid = (lane >> 3) < nv;
-    bool changed = false;
+    for (int e = 0; e < 8; ++e) acc[c][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  auto compute = [&](Blk &bk, int nv) {   // nv: valid rows
+    f32x4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int g = 0; g < NQ; ++g) {
-      float sc = 0.f;
+    for (int i = 0; i < 2; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bk.k[i]), qf[i], sc, 0, 0, 0);
+    if (nv < R) {   // wave-uniform; 0 times a repeated row's infinity would be NaN
 #pragma unroll
-      for (int w = 0; w < 4; ++w) sc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kw[w]), qh[g][w], sc, false);
-      sc = group_sum<8>(sc);
-      sc = valid ? sc : -INFINITY;
-      const float sc2 = __shfl_xor(sc, PAIR_X, 64);          // the pair's other row
-      float mx = fmaxf(sc, sc2);
-      if constexpr (NC == 2) mx = fmaxf(mx, __shfl_xor(mx, 32, 64));   // the stream's other pair
-      const float mn = fmaxf(m[g], mx);
-      const float ref = mn > -INFINITY ? mn : 0.f;            // a stream that has seen no row yet
-      corr[g] = fast_exp2(m[g] - ref);
-      changed |= mn != m[g];
-      bf16x2 t;
-      t[0] = (bf16)fast_exp2(sc - ref);
-      t[1] = (bf16)fast_exp2(sc2 - ref);
-      pk[g] = t;
-      l[g] = __builtin_amdgcn_fdot2_f32_bf16(t, ones, l[g] * corr[g], false);   // the sum of the rounded values (of this pair)
-      m[g] = mn;
-    }
-    // latent elements of a pair's two rows side by side: word e = (row A's element e, row B's element e)
-    bf16x2 cx[NC][8];
+      for (int r = 0; r < 4; ++r) {
+        const bool ok = 4 * kq + r < nv;
+        sc[r] = ok ? sc[r] : -INFINITY;
 #pragma unroll
-    for (int pr = 0; pr < NC; ++pr) {
-      const u32x4 &va = bk.c[2 * pr], &vb = bk.c[2 * pr + 1];
-      const unsigned ca[4] = {va.x, va.y, va.z, va.w}, cb[4] = {vb.x, vb.y, vb.z, vb.w};
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        cx[pr][2 * w] = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(cb[w], ca[w], 0x05040100u));
-        cx[pr][2 * w + 1] = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(cb[w], ca[w], 0x07060302u));
+        for (int c = 0; c < NC; ++c) bk.c[c][r] = ok ? bk.c[c][r] : u32x4{0u, 0u, 0u, 0u};
       }
     }
-    const bool any_changed = __any(changed);
+    const float mx = rows_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+    const float mn = fmaxf(m, mx), ref = mn > -INFINITY ? mn : 0.f;   // no row yet, or scores that overflowed to -inf
+    const float corr = fast_exp2(m - ref);
+    m = mn;
+    bf16x4 hi, lo;
+    float ps = 0.f;
 #pragma unroll
-    for (int v = 0; v < QPC; ++v) {
-      // what this key-layout lane hands out: the odd lanes of a row serve the second latent's maps
-      int give = __builtin_bit_cast(int, pk[v]);
-      float give_corr = corr[v];
-      if constexpr (NC == 2) {
-        if (lane & 1) { give = __builtin_bit_cast(int, pk[QPC + v]); give_corr = corr[QPC + v]; }
-      }
-      // lane src sits in the key layout on the first row of the stream's first pair: its pair is
-      // (first latent load's probability, second's); the second pair's lane is four rows further
-      bf16x2 pp[NC];
-      pp[0] = __builtin_bit_cast(bf16x2, __shfl(give, src, 64));
-      if constexpr (NC == 2) pp[1] = __builtin_bit_cast(bf16x2, __shfl(give, src + 32, 64));
-      if (any_changed) {   // wave-uniform
-        const float cr = __shfl(give_corr, src, 64);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[v][e] *= cr;
-      }
-#pragma unroll
-      for (int pr = 0; pr < NC; ++pr)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[v][e] = __builtin_amdgcn_fdot2_f32_bf16(cx[pr][e], pp[pr], acc[v][e], false);
+    for (int r = 0; r < 4; ++r) {
+      const float p = fast_exp2(sc[r] - ref);
+      ps += p;
+      hi[r] = (bf16)p;
+      lo[r] = (bf16)(p - (float)hi[r]);
     }
+    l = fmaf(l, corr, ps);   // of this lane's rows
+    if (__builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[c][e] *= corr;
+    }
+    const s16x4 ph = __builtin_bit_cast(s16x4, hi), pl = __builtin_bit_cast(s16x4, lo);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const unsigned sel = e & 1 ? 0x07060302u : 0x05040100u;
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 col = {__builtin_amdgcn_perm(bk.c[c][1][e / 2], bk.c[c][0][e / 2], sel),
+                           __builtin_amdgcn_perm(bk.c[c][3][e / 2], bk.c[c][2][e / 2], sel)};
+        acc[c][e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, col), ph, acc[c][e], 0, 0, 0);
+        acc[c][e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, col), pl, acc[c][e], 0, 0, 0);
+      }
   };
-  int blk = wave;
-  auto step = [&](Blk &bk) {   // consume a buffer, then refill it with the step four rounds ahead
-    compute(bk, min(R, j1 - (j0 + blk * R)));
-    if (blk + 4 * kWaves < nblk) load(bk, blk + 4 * kWaves);
-    blk += kWaves;
-  };
-  while (blk < nblk) {
-    step(bA);
-    if (blk >= nblk) break;
-    step(bB);
-    if (blk >= nblk) break;
-    step(bC);
-    if (blk >= nblk) break;
-    step(bD);
+  for (int blk = wave; blk < nblk; blk += NBUF * kWaves) {
+#pragma unroll
+    for (int u = 0; u < NBUF; ++u) {   // consume a buffer, then refill it with the step NBUF rounds ahead
+      const int at = blk + u * kWaves;
+      if (at < nblk) {
+        compute(buf[u], min(R, j1 - (j0 + at * R)));
+        if (at + NBUF * kWaves < nblk) load(buf[u], at + NBUF * kWaves);
+      }
+    }
   }
   if (has_new && wave == 0) {   // the new token's own row, from LDS: one more step with a single valid row
     const u32x4 *nr = reinterpret_cast<const u32x4 *>(newrow);
-    bA.k = nr[lane & 7];
 #pragma unroll
-    for (int i = 0; i < NCL; ++i) bA.c[i] = nr[KROW + lane % CROW];
-    compute(bA, 1);
+    for (int i = 0; i < 2; ++i) buf[0].k[i] = nr[kq + 4 * i];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) buf[0].c[c][r] = nr[KROW + 16 * c + ln];
+    compute(buf[0], 1);
   }
 
-  // ---- merge the streams of the wave, then the four waves (fixed order), write the partial.
-  // One latent: streams 0..3 sit on key rows 0..3 (lanes l, l^8, l^16, l^24); each of a stream's two
-  // key rows holds the stream's whole sum.  Two latents: streams 0 and 1 on rows 0 and 1 (lanes l,
-  // l^8); key rows r and r^4 hold the sums of the stream's two pairs (lanes l, l^32).
-  float mw[NQ], lw[NQ];
+  // ---- merge the four waves (fixed order), write the partial
+  l = rows_sum(l);
+  if (kq == 0) { sm[wave][ln] = m; sl[wave][ln] = l; }
 #pragma unroll
-  for (int g = 0; g < NQ; ++g) {
-    float mx = fmaxf(m[g], __shfl_xor(m[g], 8, 64));
-    if constexpr (NC == 1) mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    const float ref = mx > -INFINITY ? mx : 0.f;
-    float lv = l[g] * fast_exp2(m[g] - ref);     // 0 for a stream without rows
-    lv += __shfl_xor(lv, 8, 64);
-    lv += __shfl_xor(lv, NC == 1 ? 16 : 32, 64);
-    mw[g] = mx; lw[g] = lv;
-  }
+  for (int c = 0; c < NC; ++c)
+    if (ln / QPC == c && ln < NQ) {
 #pragma unroll
-  for (int v = 0; v < QPC; ++v) {
-    float give = m[v], mref = mw[v];             // mw is the same in every lane
-    if constexpr (NC == 2) {
-      if (lane & 1) give = m[QPC + v];
-      if (cgl) mref = mw[QPC + v];
+      for (int r = 0; r < 4; ++r) {
+        f32x4 *dst = reinterpret_cast<f32x4 *>(&lacc[wave][ln][8 * (4 * kq + r)]);
+        dst[0] = f32x4{acc[c][0][r], acc[c][1][r], acc[c][2][r], acc[c][3][r]};
+        dst[1] = f32x4{acc[c][4][r], acc[c][5][r], acc[c][6][r], acc[c][7][r]};
+      }
     }
-    const float ms = __shfl(give, src, 64);      // this latent-layout lane's stream and map
-    const float sc = fast_exp2(ms - (mref > -INFINITY ? mref : 0.f));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float val = acc[v][e] * sc;
-      if constexpr (NC == 1) val += __shfl_xor(val, 16, 64);
-      val += __shfl_xor(val, 32, 64);
-      acc[v][e] = val;
-    }
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int g = 0; g < NQ; ++g) { sm[wave][g] = mw[g]; sl[wave][g] = lw[g]; }
-  }
   __syncthreads();
-  if (lane < CROW) {   // lanes of stream 0 hold the wave's sums: latent cgl, elements (lane % 16) * 8 ..
-#pragma unroll
-    for (int v = 0; v < QPC; ++v) {
-      const int g = cgl * QPC + v;
-      float mx = sm[0][g];
-#pragma unroll
-      for (int x = 1; x < kWaves; ++x) mx = fmaxf(mx, sm[x][g]);
-      const float mine = sm[wave][g];
-      const float ws = mine > -INFINITY ? fast_exp2(mine - mx) : 0.f;
-      float *dst = lacc + wave * NQ * DL + g * DL + (lane & 15) * 8;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dst[e] = acc[v][e] * ws;
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < NQ * DL; i += 256) {
-    float v = lacc[i];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) v += lacc[w * NQ * DL + i];   // fixed order
-    pa[i] = v;
-  }
-  if (tid < NQ) {
-    const int g = tid;
+  for (int i = tid; i < NQ * (DL / 4); i += 256) {
+    const int g = i / (DL / 4), col = i % (DL / 4) * 4;
     float mx = sm[0][g];
+#pragma unroll
     for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sm[w][g]);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
     float ls = 0.f;
-    for (int w = 0; w < kWaves; ++w)   // no maximum: a wave without rows (sum 0) or with nothing but NaN (sum NaN)
-      ls = fmaf(sl[w][g], sm[w][g] > -INFINITY ? fast_exp2(sm[w][g] - mx) : 1.f, ls);
-    pm[2 * g] = mx;
-    pm[2 * g + 1] = ls;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float mw = sm[w][g];
+      v += *reinterpret_cast<const f32x4 *>(&lacc[w][g][col]) * (mw > -INFINITY ? fast_exp2(mw - mx) : 0.f);
+      // no maximum: a wave without rows (sum 0) or with nothing but NaN (sum NaN)
+      ls = fmaf(sl[w][g], mw > -INFINITY ? fast_exp2(mw - mx) : 1.f, ls);
+    }
+    *reinterpret_cast<f32x4 *>(pa + g * DL + col) = v;
+    if (col == 0) { pm[2 * g] = mx; pm[2 * g + 1] = ls; }
   }
 }
 
@@ -1408,9 +1369,9 @@ bool tuned_decode_supported(const Dims &d) {
 // narrow kernel: measured at the 1B shape with slot strides as the benchmark has them, 256 against 512
 // workgroups: batch 8 at 32K rows 102 against 105 us per step, batch 16 at 8K 64 against 66, batch 32
 // at 8K 110 against 111, batch 64 at 8K 197 against 199 (fewer partials to write and merge, longer
-// slices per workgroup); the 8 x 128 + 1024 kernel and the two-latent narrow kernel keep only one
-// workgroup per CU resident, so 512 would run in two rounds (163 -> 137 us, 82 -> 65 us).  The
-// one-latent narrow kernel (384-byte rows, 50 MB per step) prefers two per CU: 41 against 44 us.
+// slices per workgroup); the 8 x 128 + 1024 kernel keeps only one workgroup per CU resident, so 512
+// would run in two rounds (163 -> 137 us).  The one-latent narrow kernel prefers two per CU: 64 x 2048 rows
+// 31.8 against 32.4 us, 16 x 4000 27.8 / 29.2, 160 x 1000 42.1 / 45.2; with two latents both are alike.
 int tuned_decode_target_workgroups(const Dims &d) {
   if (d.dtype != GTA_BF16) return 512;
   return narrow_shape(d) && d.nc == 1 ? 512 : 256;
@@ -1451,9 +1412,9 @@ static void launch_attn_any(const Dims &d, const DecAttnArgs &a, const RopeFreq 
 #undef GTA_X
   if (d.nc == 2 && d.nq == 10) decode_narrow_kernel<10, 2><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
   else if (d.nc == 2) decode_narrow_kernel<6, 2><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
-  else if (d.nq == 3) decode_narrow_kernel<3><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
-  else if (d.nq == 5) decode_narrow_kernel<5><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
-  else decode_narrow_kernel<6><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
+  else if (d.nq == 3) decode_narrow_kernel<3, 1><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
+  else if (d.nq == 5) decode_narrow_kernel<5, 1><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
+  else decode_narrow_kernel<6, 1><<<dim3(a.splits, batch), 256, 0, st>>>(a, rf);
 }
 
 // q already rotated.  oldlen_in NULL: attend over the rows the caches hold now (stage call); otherwise

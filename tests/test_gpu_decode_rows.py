@@ -114,3 +114,36 @@ def test_a_context_split_of_nothing_but_nan(family, dtype, batch, splits):
     assert torch.isfinite(clean).all() and torch.isnan(out[1]).all() and torch.isnan(out[3]).all()
     others = [b for b in range(batch) if b not in (1, 3)]
     assert torch.equal(out[others], clean[others])
+
+
+@pytest.mark.parametrize("splits", [0, 1, 3])
+@pytest.mark.parametrize("d_model", [128, 1664])          # queries and new rows finished by the projection, by the stream
+@pytest.mark.parametrize("maps,latents,paged", [(3, 1, False), (5, 1, True), (6, 1, False), (6, 2, True), (10, 2, False)])
+def test_narrow_rows_around_a_step(maps, latents, paged, d_model, splits):
+    """The stream over narrow rows takes 16 rows a step, two steps in flight in each of four waves: contexts around one step,
+    one round and two rounds of the waves, an empty and a full slot, slices without rows; what lies behind a context is NaN."""
+    wl = W.scaled(_wl("paper", d_model), n_heads=2 * maps, n_qgroups=maps, n_cgroups=latents)
+    ctx = np.array([0, 1, 14, 15, 16, 17, 62, 63, 64, 65, 127, 128, 129, 200, 272], dtype=np.int32)   # the last slot is full
+    batch, cap = len(ctx), 272
+    rng = W.make_rng(wl)
+    w = W.draw_weights(wl, rng, with_wo=True, std=d_model ** -0.5)
+    x = W.draw_hidden(wl, rng, batch)
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    for b, n in enumerate(ctx):
+        k[b, n:] = c[b, n:] = np.nan
+    if paged:
+        cache = U.PagedDeviceCache(wl, batch, 16, cap // 16, seed=2)
+        cache.store(B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    else:
+        cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.from_numpy(ctx))
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, "bf16"), x, cache, num_splits=splits))
+    kr, cr, lens, status = k.astype(np.float64), c.astype(np.float64), ctx.copy(), np.zeros(batch, dtype=np.int32)
+    ref = orc.decode(U.oracle_config(wl), U.oracle_weights(w), x, kr, cr, lens, status, range(batch))
+    U.assert_close(out, ref, "bf16", "out", max(1.0, float(np.abs(ref).max())))
+    np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
+    np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
+    k2, c2 = cache.logical() if paged else (cache.k, cache.c)
+    for b in range(batch - 1):
+        U.assert_close(U.f64(k2[b, ctx[b]]), kr[b, ctx[b]], "bf16", "new key", max(1.0, float(np.abs(kr[b, ctx[b]]).max())))
+        U.assert_close(U.f64(c2[b, ctx[b]]), cr[b, ctx[b]], "bf16", "new latent", max(1.0, float(np.abs(cr[b, ctx[b]]).max())))
