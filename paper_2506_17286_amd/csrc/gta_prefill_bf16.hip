@@ -97,7 +97,7 @@ struct AttnArgs {
   bf16 *L;                   // [total, n_q*d_l]
   const int32_t *cu; int per_seq;
   int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, ndlc, batch;
-  int n_qtiles, levels, spread, every;   // query tiles of the longest sequence; bound of the levels, order of the tiles (tile_of_rank)
+  int n_qtiles, levels, spread, every, eighth;   // query tiles of the longest sequence; bound of the levels, order of the tiles (tile_of_rank)
   float scale_log2e;
   // fused value decoder (kernel template flag): O_i = (L_g W_{P,i}) * Sigmoid(gate) for the heads of g
   const bf16 *wp, *gate;     // [n_h, d_l, d_h]; gate pre-activations [total, n_h*d_h] or NULL (gate off)
@@ -237,7 +237,11 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
   const int per = a.nq * a.ndlc * a.splits;                  // workgroups of a query tile
   int u, r;                                                  // rank of the tile, workgroup of the tile
-  if (a.spread) { u = (int)blockIdx.x / per; r = (int)blockIdx.x % per; }
+  if (a.spread) {
+    int id = (int)blockIdx.x;
+    if (a.eighth && id < 8 * a.eighth) id = (id & 7) * a.eighth + (id >> 3);
+    u = id / per; r = id % per;
+  }
   else {   // eight tiles at a time, one per XCD, in turn from either end
     const int x = (int)blockIdx.x & 7, at = (int)blockIdx.x >> 3, round = at / per;
     r = at % per;
@@ -809,6 +813,11 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   a.every = batch > 1 && (int64_t)a.n_qtiles * batch * a.nq * a.ndlc * a.splits <= 512 / T::KS;
   if (a.every) tiles = (int64_t)a.n_qtiles * batch;
   a.spread = a.every || tiles < kSpreadTiles;
+  // Chunks of one tile each cost about the same, and the workgroups of a tile read the same cached rows: there an XCD takes an
+  // eighth of the workgroups in a row (1B shape, 8 x 100 behind 4000 92.1 -> 86.6 us,
+  // 16 x 100 behind 1000 101.4 -> 98.2, 4 x 100 behind 4000 76.7 -> 72.1).  With several tiles a sequence the longest would fall
+  // to one XCD (6 x 1000 ragged behind 3000 183 -> 251).
+  a.eighth = a.prefix && a.n_qtiles == 1 ? (int)(tiles * a.nq * a.ndlc * a.splits / 8) : 0;
   if (!a.spread) tiles = (tiles + 7) / 8 * 8;
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;

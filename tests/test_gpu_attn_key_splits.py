@@ -207,3 +207,22 @@ def test_latent_tile_changes_over(chunk, batch):
     for b in range(batch):
         _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
                f"sequence {b}: {lens[b]} behind {prefix[b]}")
+
+
+@pytest.mark.parametrize("batch", [3, 9])
+@pytest.mark.parametrize("shape", ["paper", "mid"])
+def test_chunks_of_one_tile(shape, batch):
+    """Chunks of at most 128 tokens: the XCDs take workgroups in a row, 15 and 45 (paper) do not divide by eight; one chunk
+    is empty, one full."""
+    lens, cap = [128, 0, 1, 40, 77, 2, 127, 33, 64][:batch], 1216
+    prefix = [int(p) for p in np.random.default_rng(3).integers(0, cap - 128, batch)]
+    wl, w, x, rng = _setup(shape, sum(lens))
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = U.f64(U.run_prefill_chunk(wl, U.upload_weights(w, "bf16"), x, cu, cache))
+    for b in range(batch):
+        if lens[b]:
+            _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
+                   f"{shape} {lens[b]} behind {prefix[b]}")
