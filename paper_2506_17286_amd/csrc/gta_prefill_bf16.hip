@@ -106,6 +106,7 @@ struct AttnArgs {
   // chunk mode (prefix != NULL): k, c are the caches [slot, max_seq, width]; the chunk's own rows are
   // already in them behind the prefix[b] rows cached before (prefix[b] < 0: sequence skipped, zero output)
   const int32_t *prefix, *slots; int max_seq;
+  int32_t *seq_lens, *status; int max_batch, workgroups;   // the lengths, set by one workgroup behind the others
   PageMap pm; int ps_shift;   // cache mode on a block-table layout: page_size = 1 << ps_shift, a multiple of BK
   // key range split over up to `splits` workgroups (not fused), a sequence's over as many as keep up to 2^split_shift key
   // tiles each: they write un-normalised fp32 sums pacc [split, token, n_q*d_l] and (maximum in log2 units, sum) pml [split,
@@ -230,11 +231,23 @@ __device__ __forceinline__ bool tile_of_rank(const AttnArgs &a, int bq, int u, Q
   return false;
 }
 
+// Chunk mode: cached lengths, or the flags of skipped sequences (nothing in this or a later launch of the call reads them).
+// By a workgroup of its own: in the tiles' workgroups the arguments push scalars out of the registers of the main loop.
+__device__ __forceinline__ void commit_chunks(const AttnArgs &a) {
+  for (int b = threadIdx.x; b < a.batch; b += blockDim.x) {
+    const int slot = a.slots ? a.slots[b] : b, pre = a.prefix[b];
+    if (slot < 0 || slot >= a.max_batch) continue;
+    if (pre >= 0) a.seq_lens[slot] = pre + (a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq);
+    else a.status[slot] = GTA_ERR_CACHE_FULL;
+  }
+}
+
 template <class T, bool FUSE>
 __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
+  if ((int)blockIdx.x >= a.workgroups) { commit_chunks(a); return; }
   const int per = a.nq * a.ndlc * a.splits;                  // workgroups of a query tile
   int u, r;                                                  // rank of the tile, workgroup of the tile
   if (a.spread) {
@@ -822,7 +835,8 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;
   allow_dynamic_lds((const void *)attn_prefill_kernel<T, FUSE>, smem);
-  attn_prefill_kernel<T, FUSE><<<(unsigned)(tiles * a.ndlc * d.nq * a.splits), T::NT, smem, st>>>(a);
+  a.workgroups = (int)(tiles * a.ndlc * d.nq * a.splits);
+  attn_prefill_kernel<T, FUSE><<<(unsigned)a.workgroups + (a.prefix ? 1 : 0), T::NT, smem, st>>>(a);
 }
 
 constexpr int kSplitTarget = 256;   // workgroups of 128 queries a launch with key splits aims at: one per CU
@@ -940,6 +954,7 @@ void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache
                             void *L, const void *wp, const void *gate, void *out, bool fuse, float *part, hipStream_t st) {
   AttnArgs a = attn_args(d, q, cache.k, cache.c, cu, batch, total);
   a.prefix = prefix; a.slots = slots; a.max_seq = cache.max_seq;
+  a.seq_lens = cache.seq_lens; a.status = cache.status; a.max_batch = cache.max_batch;
   a.pm = page_map_of(cache);
   a.ps_shift = 0;
   while (a.pm.table && (1 << a.ps_shift) < a.pm.page_size) ++a.ps_shift;

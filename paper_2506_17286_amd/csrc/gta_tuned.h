@@ -57,7 +57,8 @@ void launch_attn_decoder_bf16(const Dims &d, const void *q, const void *k, const
                               int batch, int64_t total, int max_len, const void *wp, const void *gate, void *out,
                               hipStream_t st);
 // The same two against the caches: sequence b's keys / latents are rows 0 .. prefix[b] + T_b - 1 of its
-// slot, its queries sit at positions prefix[b] .. (prefix[b] < 0: zero rows).  L may be NULL when fused.
+// slot, its queries sit at positions prefix[b] .. (prefix[b] < 0: zero rows).  L may be NULL when fused.  Sets the
+// cached lengths, and the flags of skipped sequences (a launch of its own for that took 4 us).
 void launch_attn_chunk_bf16(const Dims &d, const void *q, const gta_cache &cache, const int32_t *slots,
                             const int32_t *prefix, const int32_t *cu, int batch, int64_t total, int max_chunk,
                             void *L, const void *wp, const void *gate, void *out, bool fuse, float *part, hipStream_t st);

@@ -58,7 +58,6 @@ int tuned_prefill_chunk(const Dims &d, const gta_weights &w, const void *x, cons
   launch_attn_chunk_bf16(d, ws.q, cache, slots, ws.prefix, cu, batch, total, max_chunk, ws.l, w.wp, ws.g, heads, fuse, ws.praw, st);
   if (!fuse) launch_decoder_gemm(d, ws.l, w.wp, ws.g, heads, M, st);
   if (w.wo) launch_plain_gemm(ws.o, d.wg_w, M, d.H, d.wg_w, w.wo, out, st);
-  launch_prefill_chunk_commit(cache, slots, cu, batch, total, ws.prefix, st);
   return check_launch();
 }
 

@@ -199,3 +199,27 @@ def test_chunked_prefill_on_the_shape_generic_kernels(shape):
         assert np.all(kc[s_, lens[b]:] == -3.0) and np.all(cc[s_, lens[b]:] == -3.0)
     assert cache.seq_lens.cpu().tolist() == [17, 40, 45, 33]
     assert cache.status.cpu().tolist() == [0, B.GTA_ERR_CACHE_FULL, 0, 0]
+
+
+@pytest.mark.parametrize("shape", ["1b", "paper"])
+@pytest.mark.parametrize("copies,bound", [(1, 64), (9, 64), (9, 96)], ids=["held_at_once", "many_sequences", "loose_bound"])
+def test_lengths_and_flags_of_every_kind_of_sequence(shape, copies, bound):
+    """A workgroup behind those of the attention sets lengths and flags: sequences with and without tokens that fit,
+    do not fit, whose slot holds a negative length, is full, or does not exist."""
+    kinds = [(5, 10, True), (0, 10, True), (33, 90, True), (0, -1, True), (7, -1, True), (0, 96, True), (1, 96, True), (0, 97, True),
+             (64, 32, True), (3, 0, False), (0, 0, False)]                       # tokens, rows cached, slot exists
+    kinds, cap = kinds * copies, 96
+    wl = W.scaled(_base(shape), batch=len(kinds), seqlen=64, min_seqlen=None, d_model=256)
+    lens = [n for n, _, _ in kinds]
+    w, cu, x = _inputs(wl, lens)
+    cache = U.DeviceCache(wl, len(kinds), cap)
+    old = [p for _, p, _ in kinds]
+    cache.seq_lens.copy_(torch.tensor(old, dtype=torch.int32))
+    slots = [b if ok else (-1 if b % 2 else len(kinds)) for b, (_, _, ok) in enumerate(kinds)]
+    out = U.run_prefill_chunk(wl, U.upload_weights(w, wl.dtype), x, cu, cache, slots=slots, max_chunk=bound)
+    fits = [ok and p >= 0 and p + n <= cap for n, p, ok in kinds]
+    assert cache.seq_lens.tolist() == [p + n if f else p for (n, p, _), f in zip(kinds, fits)]
+    assert cache.status.tolist() == [B.GTA_ERR_CACHE_FULL if ok and not f else 0 for (_, _, ok), f in zip(kinds, fits)]
+    for b, f in enumerate(fits):
+        rows = out[cu[b]:cu[b + 1]]
+        assert bool(torch.isfinite(rows).all()) and (f or not rows.any())
