@@ -1077,6 +1077,142 @@ __global__ __launch_bounds__(512) void decode_tail1_kernel(Dims d, const float *
   }
 }
 
+// The tail for 16 sequences per workgroup and one head (d_l = 512, d_h = 128, at most 32 splits; taken up to 8), the decoder on matrix
+// instructions.  Statistics, the first four splits' accumulators, the head's matrix and the gate terms are requested up
+// front; a thread merges four times four columns of one sequence.  The merged outputs become bf16 pairs, the rounded value
+// and what it lacks (16 bits: the vector kernels keep 24, the result is rounded to 8), row operand of two 32 x 32 x 16
+// MFMAs; the matrix passes through slots of LDS that only their wave touches and comes back through the transpose read.
+// Wave = 32 columns and half of the contraction.  Bound: one round trip to memory for 128 KiB of weights and 32 KiB a split.
+// With vector arithmetic and two sequences per workgroup every 128 KiB matrix was read 32 times at 64 sequences: 16 us, now 9.
+template <typename TO>
+__global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float *__restrict__ pacc,
+                                                            const float *__restrict__ pml,
+                                                            const int32_t *__restrict__ oldlen, int splits, int batch,
+                                                            const float *__restrict__ G, int g_nsum, int64_t g_kstride,
+                                                            int g_ld, const bf16 *__restrict__ wp, TO *__restrict__ out,
+                                                            int32_t *seq_lens, int32_t *status,
+                                                            const int32_t *__restrict__ slots, int max_batch) {
+  constexpr int DL = 512, DH = 128, ROWS = 16, LP = DL + 8, KC = DL / 2 / 16, SLOT = 16 * 64;   // KC: chunks of 16 k per wave
+  typedef __attribute__((ext_vector_type(16))) float f32x16;
+  typedef __attribute__((ext_vector_type(4))) short s16x4;
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  __shared__ float wt[ROWS][32];
+  __shared__ __attribute__((aligned(16))) bf16 L[2][ROWS][LP];        // rounded, what it lacks
+  __shared__ __attribute__((aligned(16))) char slot_lds[8][2][SLOT];
+  __shared__ __attribute__((aligned(16))) float redz[2][ROWS][DH + 4];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), cq = wave & 3, kh = wave >> 2;
+  const int head = blockIdx.x, g = head / d.hpq, b0 = blockIdx.y * ROWS;
+  const int row = tid >> 5, c = tid & 31, b = b0 + row;
+  const int old = b < batch ? oldlen[b] : -1;
+  const bool live = old >= 0;
+  // ---- all loads
+  const int64_t sb = live ? (int64_t)b * splits : 0;
+  float m_s = -INFINITY, l_s = 0.f;
+  if (live && c < splits) {
+    const float *pm = pml + ((sb + c) * d.nq + g) * 2;
+    m_s = pm[0]; l_s = pm[1];
+  }
+  const f32x4 *pa = reinterpret_cast<const f32x4 *>(pacc + (sb * d.nq + g) * DL) + c;
+  const int64_t as4 = (int64_t)d.nq * DL / 4;
+  f32x4 v[4][4];
+  auto load = [&](int s0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[s][j] = live && s0 + s < splits ? pa[(s0 + s) * as4 + 32 * j] : f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  load(0);
+  u32x4 w[KC];
+  {
+    const bf16 *wb = wp + ((int64_t)head * DL + kh * (DL / 2) + (lane >> 2)) * DH + cq * 32 + (lane & 3) * 8;
+#pragma unroll
+    for (int u = 0; u < KC; ++u) w[u] = *reinterpret_cast<const u32x4 *>(wb + (int64_t)u * 16 * DH);
+  }
+  f32x4 gz = {0.f, 0.f, 0.f, 0.f};
+  if (d.gate && live)
+    for (int k = 0; k < g_nsum; ++k) gz += *reinterpret_cast<const f32x4 *>(G + k * g_kstride + (int64_t)b * g_ld + head * DH + 4 * c);
+  if (head == 0 && c == 0 && b < batch) {
+    const int slot = slots ? slots[b] : b;
+    if (slot >= 0 && slot < max_batch) {
+      if (live) seq_lens[slot] = old + 1;
+      else status[slot] = GTA_ERR_CACHE_FULL;
+    }
+  }
+  // ---- log-sum-exp weights of the splits: 32 lanes per sequence
+  {
+    float mx = m_s;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    const float e = m_s > -INFINITY ? exp2f(m_s - mx) : 0.f;
+    float ls = e * l_s;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);
+    wt[row][c] = e / ls;   // NaN for a sequence without rows, whose output is 0 whatever follows
+  }
+  __syncthreads();
+  // ---- merged, normalised group output
+  {
+    f32x4 a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < splits; s0 += 4) {
+      if (s0) load(s0);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float ws = s0 + s < splits ? wt[row][s0 + s] : 0.f;
+        if (ws != 0.f) {   // a split without rows has weight 0 and an unwritten accumulator
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[j][i] = fmaf(ws, v[s][j][i], a[j][i]);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bf16x4 hi, lo;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { hi[i] = (bf16)a[j][i]; lo[i] = (bf16)(a[j][i] - (float)hi[i]); }
+      *reinterpret_cast<bf16x4 *>(&L[0][row][(c + 32 * j) * 4]) = hi;
+      *reinterpret_cast<bf16x4 *>(&L[1][row][(c + 32 * j) * 4]) = lo;
+    }
+  }
+  __syncthreads();
+  // ---- value decoder (Sec. 3.2); rows 16 .. 31 of the MFMAs repeat rows 0 .. 15 and are dropped
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const int wr = (lane >> 2) * 64 + (lane & 3) * 16;
+  const int rd = (h * 8 + ((lane & 15) >> 2)) * 64 + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+#pragma unroll
+  for (int u = 0; u < KC; ++u) {
+    char *s = slot_lds[wave][u & 1];
+    *reinterpret_cast<u32x4 *>(s + wr) = w[u];
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(s + rd));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(s + rd + 4 * 64));
+    const bf16x8 w8 = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    const int k = kh * (DL / 2) + u * 16 + h * 8;
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&L[1][lane & 15][k]), w8, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&L[0][lane & 15][k]), w8, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) redz[kh][8 * (r >> 2) + 4 * h + (r & 3)][cq * 32 + ln] = acc[r];
+  __syncthreads();
+  if (b >= batch) return;
+  f32x4 o = *reinterpret_cast<const f32x4 *>(&redz[0][row][4 * c]) + *reinterpret_cast<const f32x4 *>(&redz[1][row][4 * c]);
+  typedef __attribute__((ext_vector_type(4))) TO TO4;
+  TO4 res;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (d.gate == kGateSigmoid) o[i] *= 1.0f / (1.0f + __expf(-gz[i]));
+    else if (d.gate) o[i] *= gate_factor(d.gate, gz[i]);
+    res[i] = live ? (TO)o[i] : (TO)0.f;
+  }
+  *reinterpret_cast<TO4 *>(out + (int64_t)b * d.wg_w + head * DH + 4 * c) = res;
+}
+
 // The tail for the narrow shapes (d_l = 128, d_h = 64, 1 / 2 / 4 heads per map group, at most 32 splits):
 // one workgroup finishes the heads of ONE map group for two sequences, and, like the kernel above, asks
 // for everything it reads -- split statistics, partial accumulators, the group's decoder matrices, the
@@ -1295,14 +1431,28 @@ void launch_tail(const Dims &d, const float *pacc, const float *pml, const Decod
                                                         slots, cache.max_batch);
 }
 
+// More workgroups than two per CU would finish one sequence and head each: 16 sequences per workgroup instead, up to eight
+// splits (two rounds of loads).  Whole steps of the 1B shape, without and with: 33 behind 1000 47.4 / 41.0 us, 63 62.1 / 48.4, 64
+// 54.1 / 49.5, 100 behind 100..1000 71.4 / 56.6, 255 behind 500 99.4 / 72.6, 48 behind 4000 93.5 / 85.8, 64 behind 8192 189.1 /
+// 184.5; where one sequence a workgroup is enough, 16 behind 1000 29.4 / 36.7 and 16 behind 4000 (16 splits) 43.1 / 51.3.  From 256
+// sequences on the GEMM is ahead (320 behind 500 98.7 / 102.5, 1024 behind 256 152 / 162).
+bool tail16_ok(const Dims &d, int batch, int splits) {
+  return d.dl == 512 && d.dh == 128 && batch < kGemmTailBatch && batch * d.nh > 512 && splits <= 8;
+}
+
 template <typename TO>
 void launch_tail_any(const Dims &d, const float *pacc, const float *pml, const DecodeWs &ws, int batch, GateSrc gs,
                      const bf16 *wp, TO *out, const gta_cache &cache, const int32_t *slots, hipStream_t st) {
-  // about 512 workgroups (two per CU): one sequence per workgroup up to batch * n_h = 512, then 2, 4, 8.
+  // about 512 workgroups (two per CU): one sequence per workgroup up to batch * n_h = 512, then 16 (tail16_ok) or 2, 4, 8.
   // Measured at the 1B shape, 8K context: batch 16 one-sequence kernel 9 us against 16 us with two rows;
-  // batch 64 two rows 18 us against 31 us with eight (and a whole step of 205 us against 214 us with the
-  // one-sequence kernel); batch 128 four rows 24 us against 30 us with two.
+  // batch 64 two rows 18 us against 31 us with eight; batch 128 four rows 24 us against 30 us with two.
   const int rows = batch * d.nh / 512;
+  if (tail16_ok(d, batch, ws.splits)) {
+    decode_tail16_kernel<TO><<<dim3(d.nh, (batch + 15) / 16), 512, 0, st>>>(d, pacc, pml, ws.oldlen, ws.splits, batch, gs.g, gs.nsum,
+                                                                            gs.kstride, gs.ld, wp, out, cache.seq_lens,
+                                                                            cache.status, slots, cache.max_batch);
+    return;
+  }
   if (rows < 2 && d.dl == 512 && d.dh == 128 && ws.splits <= 64) {
     decode_tail1_kernel<TO><<<dim3(d.nh, batch), 512, 0, st>>>(d, pacc, pml, ws.oldlen, ws.splits, gs.g, gs.nsum,
                                                                gs.kstride, gs.ld, wp, out, cache.seq_lens,

@@ -147,3 +147,25 @@ def test_narrow_rows_around_a_step(maps, latents, paged, d_model, splits):
     for b in range(batch - 1):
         U.assert_close(U.f64(k2[b, ctx[b]]), kr[b, ctx[b]], "bf16", "new key", max(1.0, float(np.abs(kr[b, ctx[b]]).max())))
         U.assert_close(U.f64(c2[b, ctx[b]]), cr[b, ctx[b]], "bf16", "new latent", max(1.0, float(np.abs(cr[b, ctx[b]]).max())))
+
+
+@pytest.mark.parametrize("with_wo", [False, True])
+@pytest.mark.parametrize("splits", [0, 1, 5, 8, 9])        # 4 at a time; 9: another tail
+@pytest.mark.parametrize("batch", [32, 33, 64, 255])      # 32: another tail; one row in the last tile, full tiles, 15 rows
+def test_tail_of_sixteen_sequences(batch, splits, with_wo):
+    """Contexts from none to full, among them ones that leave splits without rows."""
+    wl, cap = _wl("1b", 256), 640
+    rng = W.make_rng(wl)
+    w = W.draw_weights(wl, rng, with_wo=with_wo, std=wl.d_model ** -0.5)
+    x = W.draw_hidden(wl, rng, batch)
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    ctx = rng.integers(0, cap, size=batch).astype(np.int32)
+    ctx[:4] = 0, 1, 3, cap
+    cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.from_numpy(ctx))
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, "bf16"), x, cache, num_splits=splits))
+    kr, cr, lens, status = k.astype(np.float64), c.astype(np.float64), ctx.copy(), np.zeros(batch, dtype=np.int32)
+    ref = orc.decode(U.oracle_config(wl), U.oracle_weights(w), x, kr, cr, lens, status, range(batch))
+    U.assert_close(out, ref, "bf16", "out", max(1.0, float(np.abs(ref).max())))
+    np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
+    np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
