@@ -123,8 +123,8 @@ static int choose_splits_of(const Dims &d, int batch, int max_seq, int min_rows)
     return best;
   }
   // two workgroups per CU: a launch of just over 512 workgroups runs a second round for the few left over
-  // (paper layer, 2K rows, whole step: batch 72 54 us with 8 splits, 42.5 us with 7; batch 96 57 -> 47;
-  // batch 160 73 -> 60), so the count is rounded down to what fits
+  // (paper layer, 2K rows, whole step on an earlier, slower stream: batch 72 54 us with 8 splits, 42.5 us with 7; batch 96
+  // 57 -> 47; batch 160 73 -> 60), so the count is rounded down to what fits
   if (tuned && batch <= target && (int64_t)batch * want > target) want = target / batch;
   int s = want < cap ? want : cap;
   if (s < 1) s = 1;
@@ -133,7 +133,7 @@ static int choose_splits_of(const Dims &d, int batch, int max_seq, int min_rows)
 
 // Slices of at least 64 rows: a workgroup's chain of steps over its slice is what a small batch waits for (whole
 // steps with 256-, 128-, 64- and 32-row slices: 1B shape, one sequence behind 2000 rows 33.7 / 28.3 / 25.4 / 24.3 us,
-// 16 behind 1000 36.5 / 31.5 / 30.4 / 30.2; paper layer, one behind 1000 31.4 / 27.8 / 26.1 / 27.6, fp32 8 behind 1000
+// 16 behind 1000 36.5 / 31.5 / 30.4 / 30.2; paper layer, one behind 1000 - / 21.9 / 21.6 / 21.7, fp32 8 behind 1000
 // 46 / 43 / 41 / 46).  The one-round-trip tails hold 32 (narrow rows) or 64 splits (latents of 512), though: past those
 // only slices of at least 256 rows pay for the general tail.  Latents of 1024 and the shape-generic kernels have no such
 // tail; there 64 is where finer slices stop paying (steps with 32 / 64 / 128 splits: 8 x 128 + 1024 shape, one behind

@@ -5,9 +5,10 @@
 // The step is HBM-bound (about 2.5 flop per cached byte), so the attention kernel is built around
 // the stream: one workgroup per (sequence, context split) reads every key row and latent row of
 // its slice exactly once, with one 16-byte load per lane covering a whole 1 KiB row per wave
-// instruction, and serves ALL map groups from that single read.  Arithmetic is plain fp32 VALU:
-// a per-lane partial dot product reduced inside the 8/16 lanes of a key group with DPP, online
-// softmax in the log2 domain, and p * c accumulated with the weight broadcast from a scalar.
+// instruction, and serves ALL map groups from that single read.  Rows of 1 KiB and more run on the
+// vector ALU: a per-lane partial dot product reduced inside the 16 lanes of a key group with DPP,
+// online softmax in the log2 domain, and p * c accumulated with the weight broadcast from a scalar;
+// narrow rows, of which memory delivers more per microsecond, on matrix instructions.
 #include <math.h>
 
 #include <type_traits>
@@ -1535,7 +1536,7 @@ int tuned_decode_max_splits(const Dims &d, int batch) {
   return one_seq_tail && batch >= 4 ? 64 : 1024;
 }
 
-// The streaming kernels take a page per scalar lookup: a step of up to 8 rows must not straddle pages.
+// The streaming kernels take a page per scalar lookup: a step of up to 16 rows must not straddle pages.
 bool tuned_decode_layout_ok(const gta_cache &cache) {
   if (!cache.block_table) return true;
   const int ps = cache.page_size;

@@ -658,8 +658,9 @@ bool f32_decode_ok(const Dims &d, const gta_cache &cache, int batch) {
          tuned_decode_layout_ok(cache) && rope_angles_small(d.rope, d.rope_base);
 }
 
-static ProjEpi<float, float> proj_epi(const Dims &d, float *q, float *k, float *c, float *g, const gta_cache *cache, const int32_t *slots) {
-  ProjEpi<float, float> e{};
+template <bool FOLD>
+static ProjEpi<float, float, false, FOLD> proj_epi(const Dims &d, float *q, float *k, float *c, float *g, const gta_cache *cache, const int32_t *slots) {
+  ProjEpi<float, float, false, FOLD> e{};
   e.dst[0] = q; e.dst[1] = k; e.dst[2] = c; e.dst[3] = g;
   e.width[0] = d.wq_w; e.width[1] = d.wk_w; e.width[2] = d.wc_w; e.width[3] = d.wg_w;
   e.dh = d.dh; e.rope = d.rope;
@@ -679,21 +680,25 @@ static GemmOperands proj_operands(const Dims &d, const gta_weights &w, const voi
   return g;
 }
 
-// Sines worked out in the epilogue pay for few rows only: 64 x 64 tiles of 4096 rows take more time for them than a launch.
+// 64 x 64 tiles keep the setup launch: they find the tokens of 16 groups of columns a thread and would work out as many sines
+// (toy layer, 7 x 20..82 tokens 23.4 us with it, 23.7 without).
 bool f32_proj_folds(const Dims &d, int batch, int64_t M) {
-  return batch <= kFoldBatch && (!d.rope || (M <= kRowsMax && rope_angles_small(d.rope, d.rope_base)));
+  return batch <= kFoldBatch && M <= kRowsMax && rope_angles_small(d.rope, d.rope_base);
 }
 
 void launch_proj_f32(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
                      const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold, hipStream_t st) {
-  ProjEpi<float, float> e = proj_epi(d, (float *)ws.q, (float *)ws.k, (float *)ws.c, (float *)ws.g, cache, slots);
-  if (fold.batch) {
-    e.fold = fold;
-    e.commit_to = view_of(cache, slots);
-    for (int j = 0; d.rope && j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
-  }
-  e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
-  launch_gemm_f32(proj_operands(d, w, x, M), d.wtot, e, st);
+  auto launch = [&](auto e) {
+    e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
+    launch_gemm_f32(proj_operands(d, w, x, M), d.wtot, e, st);
+  };
+  float *q = (float *)ws.q, *k = (float *)ws.k, *c = (float *)ws.c, *g = (float *)ws.g;
+  if (!fold.batch) { launch(proj_epi<false>(d, q, k, c, g, cache, slots)); return; }
+  auto e = proj_epi<true>(d, q, k, c, g, cache, slots);
+  e.fold = fold;
+  e.commit_to = view_of(cache, slots);
+  for (int j = 0; d.rope && j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
+  launch(e);
 }
 
 void launch_decoder_f32(const Dims &d, const float *L, const void *wp, const float *gate, float *out, int M, hipStream_t st) {
@@ -751,7 +756,7 @@ void launch_decode_attn_f32(const Dims &d, const float *q, const int32_t *oldlen
 // caches, tail (merge, value decoder, gate, bookkeeping), output projection.
 int f32_decode(const Dims &d, const gta_weights &w, const void *x_new, int batch, const gta_cache &cache, const int32_t *slots,
                void *out, const DecodeWs &ws, hipStream_t st) {
-  ProjEpi<float, float> e = proj_epi(d, ws.q, nullptr, nullptr, ws.g, &cache, slots);
+  auto e = proj_epi<false>(d, ws.q, nullptr, nullptr, ws.g, &cache, slots);
   e.seq_lens = cache.seq_lens; e.oldlen = ws.oldlen;
   for (int j = 0; j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
   launch_gemm_f32(proj_operands(d, w, x_new, batch), d.wtot, e, st);
