@@ -242,12 +242,16 @@ __device__ __forceinline__ void commit_chunks(const AttnArgs &a) {
   }
 }
 
-template <class T, bool FUSE>
+// CHUNK: keys and latents in the caches.  Fresh prompts have a kernel without that code: in one for both they paid for it (calls of
+// the paper's layers, both and now, 7 x 41..331 tokens 41.8 / 40.1 us, 32 x 20..100 68.6 / 66.0, 19 x 295 101.6 / 99.0).
+template <class T, bool FUSE, bool CHUNK>
 __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
+  if constexpr (!CHUNK) { a.prefix = nullptr; a.slots = nullptr; a.pm.table = nullptr; a.eighth = 0; }
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
-  if ((int)blockIdx.x >= a.workgroups) { commit_chunks(a); return; }
+  if constexpr (CHUNK)
+    if ((int)blockIdx.x >= a.workgroups) { commit_chunks(a); return; }
   const int per = a.nq * a.ndlc * a.splits;                  // workgroups of a query tile
   int u, r;                                                  // rank of the tile, workgroup of the tile
   if (a.spread) {
@@ -265,15 +269,15 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
     const int lvl = u / a.batch;
     tile.b = u - lvl * a.batch;
     tile.qt = a.n_qtiles - 1 - lvl;
-    tile.start = a.cu ? a.cu[tile.b] : tile.b * a.per_seq;
-    tile.len = a.cu ? a.cu[tile.b + 1] - tile.start : a.per_seq;
-    tile.prefix = a.prefix ? a.prefix[tile.b] : 0;
+    tile.start = a.cu ? load_uniform(a.cu + tile.b) : tile.b * a.per_seq;
+    tile.len = a.cu ? load_uniform(a.cu + tile.b + 1) - tile.start : a.per_seq;
+    tile.prefix = a.prefix ? load_uniform(a.prefix + tile.b) : 0;
     if (tile.qt * T::BQ >= tile.len) return;
   } else if (!tile_of_rank(a, T::BQ, u, tile)) return;
   const int g = r % a.nq, dlc = r / a.nq % a.ndlc, split = r / (a.nq * a.ndlc);
   const int64_t start = tile.start;
   const int Tb = tile.len, q0 = tile.qt * T::BQ;             // queries of this sequence, first of this tile
-  const int P = tile.prefix;                                 // keys cached before the first query
+  const int P = CHUNK ? tile.prefix : 0;                     // keys cached before the first query
   const int kh = wave / T::QW, qw = wave % T::QW;            // key half and query rows of this wave
   const int splits = FUSE ? a.splits : a.splits == 1 || P < 0 ? 1 : splits_of(a, P + Tb);   // fused: 1
   auto stats = [&](int row) { return a.pml + (((int64_t)split * a.total + start + q0 + row) * a.nq + g) * a.ndlc + dlc; };
@@ -834,9 +838,13 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   if (!a.spread) tiles = (tiles + 7) / 8 * 8;
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;
-  allow_dynamic_lds((const void *)attn_prefill_kernel<T, FUSE>, smem);
   a.workgroups = (int)(tiles * a.ndlc * d.nq * a.splits);
-  attn_prefill_kernel<T, FUSE><<<(unsigned)a.workgroups + (a.prefix ? 1 : 0), T::NT, smem, st>>>(a);
+  auto launch = [&](auto kernel, int more) {
+    allow_dynamic_lds((const void *)kernel, smem);
+    kernel<<<(unsigned)(a.workgroups + more), T::NT, smem, st>>>(a);
+  };
+  if (a.prefix) launch(attn_prefill_kernel<T, FUSE, true>, 1);
+  else launch(attn_prefill_kernel<T, FUSE, false>, 0);
 }
 
 constexpr int kSplitTarget = 256;   // workgroups of 128 queries a launch with key splits aims at: one per CU
