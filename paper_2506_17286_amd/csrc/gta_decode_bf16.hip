@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(512) void decode_tail1_kernel(Dims d, const float *
 // and what it lacks (16 bits: the vector kernels keep 24, the result is rounded to 8), row operand of two 32 x 32 x 16
 // MFMAs; the matrix passes through slots of LDS that only their wave touches and comes back through the transpose read.
 // Wave = 32 columns and half of the contraction.  Bound: one round trip to memory for 128 KiB of weights and 32 KiB a split.
-// With vector arithmetic and two sequences per workgroup every 128 KiB matrix was read 32 times at 64 sequences: 16 us, now 9.
+// With vector arithmetic and two sequences per workgroup every 128 KiB matrix was read 32 times at 64 sequences: 16 us, now 11.
 template <typename TO>
 __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float *__restrict__ pacc,
                                                             const float *__restrict__ pml,
