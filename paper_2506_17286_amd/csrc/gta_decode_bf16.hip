@@ -1080,11 +1080,15 @@ __global__ __launch_bounds__(512) void decode_tail1_kernel(Dims d, const float *
 
 // The tail for 16 sequences per workgroup and one head (d_l = 512, d_h = 128, at most 32 splits; taken up to 8), the decoder on matrix
 // instructions.  Statistics, the first four splits' accumulators, the head's matrix and the gate terms are requested up
-// front; a thread merges four times four columns of one sequence.  The merged outputs become bf16 pairs, the rounded value
-// and what it lacks (16 bits: the vector kernels keep 24, the result is rounded to 8), row operand of two 32 x 32 x 16
-// MFMAs; the matrix passes through slots of LDS that only their wave touches and comes back through the transpose read.
+// front; a thread merges four times four columns of one sequence.  The merged outputs become three bf16 parts, which hold all
+// 24 bits that the vector kernels multiply with: row operand of two 32 x 32 x 16 MFMAs, the first two parts above each other;
+// the matrix passes through slots of LDS that only their wave touches and comes back through the transpose read.
 // Wave = 32 columns and half of the contraction.  Bound: one round trip to memory for 128 KiB of weights and 32 KiB a split.
 // With vector arithmetic and two sequences per workgroup every 128 KiB matrix was read 32 times at 64 sequences: 16 us, now 11.
+// (Whole steps with two parts and with three: 64 behind 8192 184.8 / 184.9 us, 33 behind 1000 41.3 / 40.8, 255 behind 500 73.1 / 73.4.)
+// v without the lower half of its bits: a bf16 value
+__device__ __forceinline__ float high_half(float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); }
+
 template <typename TO>
 __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float *__restrict__ pacc,
                                                             const float *__restrict__ pml,
@@ -1099,7 +1103,7 @@ __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float 
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   __shared__ float wt[ROWS][32];
-  __shared__ __attribute__((aligned(16))) bf16 L[2][ROWS][LP];        // rounded, what it lacks
+  __shared__ __attribute__((aligned(16))) bf16 L[3][ROWS][LP];        // parts of 8 bits each, highest first
   __shared__ __attribute__((aligned(16))) char slot_lds[8][2][SLOT];
   __shared__ __attribute__((aligned(16))) float redz[2][ROWS][DH + 4];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
@@ -1173,18 +1177,22 @@ __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float 
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      bf16x4 hi, lo;
+      bf16x4 part[3];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { hi[i] = (bf16)a[j][i]; lo[i] = (bf16)(a[j][i] - (float)hi[i]); }
-      *reinterpret_cast<bf16x4 *>(&L[0][row][(c + 32 * j) * 4]) = hi;
-      *reinterpret_cast<bf16x4 *>(&L[1][row][(c + 32 * j) * 4]) = lo;
+      for (int i = 0; i < 4; ++i) {
+        const float hi = high_half(a[j][i]), rest = a[j][i] - hi, mid = high_half(rest);
+        part[0][i] = (bf16)hi; part[1][i] = (bf16)mid; part[2][i] = (bf16)(rest - mid);
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x4 *>(&L[p][row][(c + 32 * j) * 4]) = part[p];
     }
   }
   __syncthreads();
-  // ---- value decoder (Sec. 3.2); rows 16 .. 31 of the MFMAs repeat rows 0 .. 15 and are dropped
-  f32x16 acc;
+  // ---- value decoder (Sec. 3.2): rows 0 .. 15 are the highest parts, 16 .. 31 the middle ones; of the lowest parts, which
+  // stand in both, the second half is dropped
+  f32x16 acc, low;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int r = 0; r < 16; ++r) acc[r] = low[r] = 0.f;
   const int wr = (lane >> 2) * 64 + (lane & 3) * 16;
   const int rd = (h * 8 + ((lane & 15) >> 2)) * 64 + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
 #pragma unroll
@@ -1195,11 +1203,11 @@ __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float 
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(s + rd + 4 * 64));
     const bf16x8 w8 = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     const int k = kh * (DL / 2) + u * 16 + h * 8;
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&L[1][lane & 15][k]), w8, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&L[0][lane & 15][k]), w8, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&L[ln >> 4][lane & 15][k]), w8, acc, 0, 0, 0);
+    low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&L[2][lane & 15][k]), w8, low, 0, 0, 0);
   }
 #pragma unroll
-  for (int r = 0; r < 8; ++r) redz[kh][8 * (r >> 2) + 4 * h + (r & 3)][cq * 32 + ln] = acc[r];
+  for (int r = 0; r < 8; ++r) redz[kh][8 * (r >> 2) + 4 * h + (r & 3)][cq * 32 + ln] = low[r] + acc[r + 8] + acc[r];
   __syncthreads();
   if (b >= batch) return;
   f32x4 o = *reinterpret_cast<const f32x4 *>(&redz[0][row][4 * c]) + *reinterpret_cast<const f32x4 *>(&redz[1][row][4 * c]);

@@ -169,3 +169,25 @@ def test_tail_of_sixteen_sequences(batch, splits, with_wo):
     U.assert_close(out, ref, "bf16", "out", max(1.0, float(np.abs(ref).max())))
     np.testing.assert_array_equal(cache.seq_lens.cpu().numpy(), lens)
     np.testing.assert_array_equal(cache.status.cpu().numpy(), status)
+
+
+@pytest.mark.parametrize("splits", [1, 5])
+@pytest.mark.parametrize("batch", [32, 33])                # one sequence a workgroup, sixteen
+def test_merged_outputs_keep_fp32(batch, splits):
+    """Two latent columns whose means over 1024 rows of equal weight, exact in fp32, differ by 2^-19 at a value of 1.001; the
+    decoder subtracts them.  An error of one in 2^23 of either is one in 16 of the difference."""
+    wl, n = _wl("1b", 256), 1024
+    rng = W.make_rng(wl)
+    w = W.draw_weights(wl, rng)
+    w["wp"][:] = 0.0
+    w["wp"][:, 0, 0], w["wp"][:, 1, 0] = -1.0, 1.0
+    k, c = np.zeros((batch, n, wl.kv_width[0]), dtype=np.float32), np.zeros((batch, n, wl.kv_width[1]), dtype=np.float32)
+    c[:, :, :2], c[:, 0, :2], c[:, 1, :2] = 1.0, 4.0, 0.25
+    c[:, 1, 1] += 2.0 ** -9
+    cache = U.DeviceCache(wl, batch, n, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.fill_(n - 1)                             # the new row is 0, as are all scores
+    x = np.zeros((batch, wl.d_model), dtype=np.float32)
+    out = U.f64(U.run_decode(wl, U.upload_weights(w, "bf16"), x, cache, num_splits=splits, gate=False))
+    heads = out.reshape(batch, wl.n_heads, wl.head_dim)
+    np.testing.assert_allclose(heads[:, :, 0], 2.0 ** -19, rtol=2.0 ** -4)
+    assert not heads[:, :, 1:].any()
