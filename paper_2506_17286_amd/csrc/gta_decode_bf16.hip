@@ -1088,6 +1088,8 @@ __global__ __launch_bounds__(512) void decode_tail1_kernel(Dims d, const float *
 // (Whole steps with two parts and with three: 64 behind 8192 184.8 / 184.9 us, 33 behind 1000 41.3 / 40.8, 255 behind 500 73.1 / 73.4.)
 // v without the lower half of its bits: a bf16 value
 __device__ __forceinline__ float high_half(float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); }
+// v with its last bit set: what its upper half lacks is then not 0
+__device__ __forceinline__ float odd_bits(float v) { return __uint_as_float(__float_as_uint(v) | 1u); }
 
 template <typename TO>
 __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float *__restrict__ pacc,
@@ -1180,8 +1182,14 @@ __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float 
       bf16x4 part[3];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float hi = high_half(a[j][i]), rest = a[j][i] - hi, mid = high_half(rest);
-        part[0][i] = (bf16)hi; part[1][i] = (bf16)mid; part[2][i] = (bf16)(rest - mid);
+        // every part has the value's sign and is 0 only if the value is (an error of 2^-31 at most): 0 times an infinite weight, or
+        // infinities of either sign, would make NaN of an infinity
+        const float hi = high_half(a[j][i]);
+        float rest = a[j][i] - hi;
+        if (rest == 0.f) rest = a[j][i] * 0x1p-32f;
+        float mid = high_half(rest), low = odd_bits(rest) - mid;
+        if (rest != rest) mid = low = hi;   // an infinity (or NaN)
+        part[0][i] = (bf16)hi; part[1][i] = (bf16)mid; part[2][i] = (bf16)low;
       }
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x4 *>(&L[p][row][(c + 32 * j) * 4]) = part[p];

@@ -191,3 +191,33 @@ def test_merged_outputs_keep_fp32(batch, splits):
     heads = out.reshape(batch, wl.n_heads, wl.head_dim)
     np.testing.assert_allclose(heads[:, :, 0], 2.0 ** -19, rtol=2.0 ** -4)
     assert not heads[:, :, 1:].any()
+
+
+@pytest.mark.parametrize("where", ["latents", "matrix"])
+@pytest.mark.parametrize("splits", [1, 5])
+@pytest.mark.parametrize("batch", [32, 33])                # one sequence a workgroup, sixteen
+def test_infinities_in_the_tail(batch, splits, where):
+    """An infinite latent or decoder weight gives the infinities of the float64 reference, and nothing else changes."""
+    wl, n = _wl("1b", 256), 200
+    rng = W.make_rng(wl)
+    w, x = W.draw_weights(wl, rng), W.draw_hidden(wl, rng, batch)
+    k, c = W.draw_cache(wl, rng, batch, n)
+    lens = rng.integers(50, n, size=batch).astype(np.int32)
+
+    def step():
+        cache = U.DeviceCache(wl, batch, n, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+        cache.seq_lens.copy_(torch.from_numpy(lens))
+        return U.f64(U.run_decode(wl, U.upload_weights(w, "bf16"), x, cache, num_splits=splits, gate=False))
+    clean = step()
+    if where == "latents":
+        c[1, 7, 3], c[batch - 1, 40, 500] = np.inf, -np.inf
+    else:
+        w["wp"][0, 3, 5], w["wp"][15, 500, 100] = np.inf, -np.inf
+    got = step()
+    with np.errstate(invalid="ignore"):
+        ref = orc.decode(U.oracle_config(wl, False), U.oracle_weights(w), x, k.astype(np.float64), c.astype(np.float64), lens.copy(),
+                         np.zeros(batch, dtype=np.int32), range(batch))
+    bad = ~np.isfinite(ref)
+    assert bad.sum() == (2 * wl.n_heads * wl.head_dim if where == "latents" else 2 * batch) and not np.isnan(ref).any()
+    np.testing.assert_array_equal(got[bad], ref[bad])
+    np.testing.assert_array_equal(got[~bad], clean[~bad])
