@@ -56,6 +56,11 @@ __device__ __forceinline__ void unpack8(const u32x4 &w, float (&f)[8]) {
 }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// v without the lower half of its bits: a bf16 value
+__device__ __forceinline__ float high_half(float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); }
+// v with its last bit set: what its upper half lacks is then not 0
+__device__ __forceinline__ float odd_bits(float v) { return __uint_as_float(__float_as_uint(v) | 1u); }
+
 // Compile-time shape of one instantiation.  A key row is NK*DH elements = KCH chunks of 512
 // (1 KiB, one 16-byte load per lane); a latent row is NC*DLC chunks of 512.
 template <int DH_, int NK_, int QPK_, int NC_, int DLC_, int R_, int OCC_>
@@ -487,7 +492,7 @@ __device__ __forceinline__ float rows_sum(float v) {
 // four probabilities are, as they stand, the column operand of the second product L^T[column][map] += C^T P^T.  Its
 // row operand wants four rows of one latent column per lane; a lane loads 16 bytes of each of its four rows (16 lanes cover
 // a row) and pairs them up with v_perm_b32, two MFMAs of 16 x 16 x 16 for each of the eight columns it holds: probabilities
-// are bf16 pairs, the rounded value and what it lacks.  (Rounded once, a step's error against 64 bits was 2.8e-3 to 3.0e-3
+// are bf16 pairs, their upper half and what it lacks.  (Rounded once, a step's error against 64 bits was 2.8e-3 to 3.0e-3
 // where the vector kernel before it, with more and shorter streams whose largest probability is exactly 1, had 2.5e-3 to
 // 2.9e-3; with the pair 2.6e-3 to 2.7e-3, at the same time.)  Queries are rounded to bf16, sums are fp32.
 // Bound: at 50 MB a step the launch, a workgroup's chain of loads and the merge (HBM from about 100 MB on); a step of 16 rows
@@ -668,14 +673,13 @@ __global__ __launch_bounds__(256, 2) void decode_narrow_kernel(DecAttnArgs a, Ro
     const float mn = fmaxf(m, mx), ref = mn > -INFINITY ? mn : 0.f;   // no row yet, or scores that overflowed to -inf
     const float corr = fast_exp2(m - ref);
     m = mn;
-    bf16x4 hi, lo;
-    float ps = 0.f;
+    float p[4], ps = 0.f;
+    bf16x4 lo;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float p = fast_exp2(sc[r] - ref);
-      ps += p;
-      hi[r] = (bf16)p;
-      lo[r] = (bf16)(p - (float)hi[r]);
+      p[r] = fast_exp2(sc[r] - ref);
+      ps += p[r];
+      lo[r] = (bf16)(odd_bits(p[r]) - high_half(p[r]));   // above 0 unless p is: an infinite latent stays an infinity
     }
     l = fmaf(l, corr, ps);   // of this lane's rows
     if (__builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
@@ -684,13 +688,14 @@ __global__ __launch_bounds__(256, 2) void decode_narrow_kernel(DecAttnArgs a, Ro
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[c][e] *= corr;
     }
-    const s16x4 ph = __builtin_bit_cast(s16x4, hi), pl = __builtin_bit_cast(s16x4, lo);
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    auto upper = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
+    const s16x4 ph = __builtin_bit_cast(s16x4, (u32x2{upper(p[0], p[1]), upper(p[2], p[3])})), pl = __builtin_bit_cast(s16x4, lo);
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const unsigned sel = e & 1 ? 0x07060302u : 0x05040100u;
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
         const u32x2 col = {__builtin_amdgcn_perm(bk.c[c][1][e / 2], bk.c[c][0][e / 2], sel),
                            __builtin_amdgcn_perm(bk.c[c][3][e / 2], bk.c[c][2][e / 2], sel)};
         acc[c][e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, col), ph, acc[c][e], 0, 0, 0);
@@ -1086,11 +1091,6 @@ __global__ __launch_bounds__(512) void decode_tail1_kernel(Dims d, const float *
 // Wave = 32 columns and half of the contraction.  Bound: one round trip to memory for 128 KiB of weights and 32 KiB a split.
 // With vector arithmetic and two sequences per workgroup every 128 KiB matrix was read 32 times at 64 sequences: 16 us, now 11.
 // (Whole steps with two parts and with three: 64 behind 8192 184.8 / 184.9 us, 33 behind 1000 41.3 / 40.8, 255 behind 500 73.1 / 73.4.)
-// v without the lower half of its bits: a bf16 value
-__device__ __forceinline__ float high_half(float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); }
-// v with its last bit set: what its upper half lacks is then not 0
-__device__ __forceinline__ float odd_bits(float v) { return __uint_as_float(__float_as_uint(v) | 1u); }
-
 template <typename TO>
 __global__ __launch_bounds__(512) void decode_tail16_kernel(Dims d, const float *__restrict__ pacc,
                                                             const float *__restrict__ pml,

@@ -221,3 +221,62 @@ def test_infinities_in_the_tail(batch, splits, where):
     assert bad.sum() == (2 * wl.n_heads * wl.head_dim if where == "latents" else 2 * batch) and not np.isnan(ref).any()
     np.testing.assert_array_equal(got[bad], ref[bad])
     np.testing.assert_array_equal(got[~bad], clean[~bad])
+
+
+NARROW = [(3, 1), (5, 1), (6, 1), (6, 2), (10, 2)]         # maps, latents
+
+
+@pytest.mark.parametrize("splits", [1, 5])
+@pytest.mark.parametrize("n", [1, 15, 16, 33, 300])
+@pytest.mark.parametrize("maps,latents", NARROW)
+def test_infinite_latents_of_narrow_rows(maps, latents, n, splits):
+    """The stream and the merge alone; with one row the weight is exactly 1."""
+    wl = W.scaled(_wl("paper", 128), n_heads=2 * maps, n_qgroups=maps, n_cgroups=latents)
+    rng = np.random.default_rng(n)
+    q, k, c = (W.round_to_dtype(rng.standard_normal(s).astype(np.float32), "bf16") for s in
+               ((1, maps, wl.head_dim), (1, n, wl.head_dim), (1, n, latents * wl.latent_dim)))
+    c[0, -1, 7], c[0, n // 2, -1] = np.inf, -np.inf
+    cache = U.DeviceCache(wl, 1, n, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.fill_(n)
+    cfg = B.config_of(wl)
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_DECODE, 1, 0, n, splits))
+    out = torch.empty((maps, wl.latent_dim), device="cuda")
+    B.gta_decode_attention(cfg, torch.from_numpy(q.reshape(1, -1).copy()).cuda(), cache.struct, None, 1, splits, ws)
+    B.gta_decode_combine(cfg, cache.struct, None, 1, splits, ws, out)
+    got, oc = U.f64(out), U.oracle_config(wl)
+    c64 = c[0].astype(np.float64).reshape(n, latents, -1)
+    ref = np.stack([(orc.attention_map_rows(oc, q[:, g].astype(np.float64), np.array([n - 1]), k[0].astype(np.float64)) @ c64[:, oc.c_of_group(g)])[0]
+                    for g in range(maps)])
+    bad = ~np.isfinite(ref)
+    assert bad.any() and not np.isnan(ref).any()
+    np.testing.assert_array_equal(got[bad], ref[bad])
+    U.assert_close(got[~bad], ref[~bad], "bf16", "finite columns", max(1.0, float(np.abs(ref[~bad]).max())))
+
+
+@pytest.mark.parametrize("d_model", [128, 1664])          # new rows finished by the projection, by the stream
+@pytest.mark.parametrize("maps,latents", [(5, 1), (10, 2)])
+def test_new_latent_that_overflows(maps, latents, d_model):
+    """Into an empty slot and behind 20 rows: 1e10 times 1e30 is an infinity in 16 bits, and so are the outputs that it reaches."""
+    wl = W.scaled(_wl("paper", d_model), n_heads=2 * maps, n_qgroups=maps, n_cgroups=latents)
+    rng, batch, cap = W.make_rng(wl), 3, 64
+    w, x = W.draw_weights(wl, rng, std=d_model ** -0.5), W.draw_hidden(wl, rng, batch)
+    k, c = W.draw_cache(wl, rng, batch, cap)
+    for name in ("wq", "wk", "wc", "wg"):
+        w[name][0] = 0.0
+    w["wc"][0, 7], w["wc"][0, -1] = W.round_to_dtype(np.array([1e30, -1e30], dtype=np.float32), "bf16")
+    x[:, 0] = W.round_to_dtype(np.array([1e10, 1e10, 0.0], dtype=np.float32), "bf16")
+    lens = np.array([0, 20, 20], dtype=np.int32)
+    cache = U.DeviceCache(wl, batch, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.from_numpy(lens))
+    got = U.f64(U.run_decode(wl, U.upload_weights(w, "bf16"), x, cache, gate=False))
+    ref = orc.decode(U.oracle_config(wl, False), U.oracle_weights(w), x, k.astype(np.float64), c.astype(np.float64), lens.copy(),
+                     np.zeros(batch, dtype=np.int32), range(batch))
+    assert (np.abs(ref[:2]) > 1e30).all()
+    if latents == 2:                                        # one infinity in each latent
+        np.testing.assert_array_equal(got[:2], np.sign(ref[:2]) * np.inf)
+    else:                                                   # both in one: the sum of two infinities
+        w7, w_last = (np.sign(w["wp"][:, i].reshape(-1)) for i in (7, -1))
+        same = w7 == -w_last
+        np.testing.assert_array_equal(got[:2, same], np.broadcast_to(w7[same] * np.inf, (2, same.sum())))
+        assert np.isnan(got[:2, ~same]).all()
+    U.assert_close(got[2], ref[2], "bf16", "without", max(1.0, float(np.abs(ref[2]).max())))
