@@ -92,12 +92,15 @@ struct AttnTile {
   __device__ static constexpr int c_row(int a) { return a / C_RPI * C_GROUP + a % C_RPI * C_ROW; }
 };
 
+enum { kRanked, kEvery, kSearched };   // AttnArgs.numbering
+
 struct AttnArgs {
   const bf16 *q, *k, *c;     // packed [total, n_q*d_h], [total, n_k*d_h], [total, n_c*d_l]
   bf16 *L;                   // [total, n_q*d_l]
   const int32_t *cu; int per_seq;
   int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, ndlc, batch;
-  int n_qtiles, levels, spread, every, eighth;   // query tiles of the longest sequence; bound of the levels, order of the tiles (tile_of_rank)
+  // query tiles of the longest sequence; bound of the levels (tile_of_rank); how workgroups get theirs (launch_tile)
+  int n_qtiles, levels, numbering, spread, eighth;
   float scale_log2e;
   // fused value decoder (kernel template flag): O_i = (L_g W_{P,i}) * Sigmoid(gate) for the heads of g
   const bf16 *wp, *gate;     // [n_h, d_l, d_h]; gate pre-activations [total, n_h*d_h] or NULL (gate off)
@@ -163,72 +166,108 @@ __device__ __forceinline__ int wave_sum(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
-// Query tile `u` of all sequences' tiles in the order they are started: most keys first (list scheduling needs that to
+struct QueryTile { int b, qt, start, len, prefix; };   // sequence, tile, first token, tokens, keys cached before
+__device__ __forceinline__ void set_sequence(const AttnArgs &a, int b, QueryTile &t) {
+  t.b = __builtin_amdgcn_readfirstlane(b);
+  t.start = t.b * a.per_seq;
+  t.len = a.per_seq;
+  t.prefix = 0;
+  if (a.cu) {   // both loads on their way at once
+    u32x2 ends;
+    if (a.prefix)
+      asm volatile("s_load_dwordx2 %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&s"(ends), "=&s"(t.prefix) : "s"(a.cu + t.b), "s"(a.prefix + t.b));
+    else asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=&s"(ends) : "s"(a.cu + t.b));
+    t.start = (int)ends[0];
+    t.len = (int)ends[1] - t.start;
+  } else if (a.prefix) t.prefix = load_uniform(a.prefix + t.b);
+}
+
+// Query tile `u` of all sequences' tiles in the order they are started, most keys first (list scheduling needs that to
 // balance the CUs), sequences in turn inside a level.  Level of tile qt: qt + tiles cached before the chunk, of which a
 // sequence with n tiles behind p has p .. p + n - 1.  False: there are no more.  All lanes of the wave call this with the
-// same arguments; lane i counts sequences i, i + 64, ..
+// same arguments; lane i counts sequences i, i + 64, .. : G of them.
 // The host knows no lengths.  With an id for every (level, sequence) up to the longest, the ids of the shorter ones'
 // missing tiles fell to the same places again and again, and as ids are dealt to the XCDs and their shader engines in a
 // fixed turn, some had no work: ragged batch of 112 K tokens, 16 sequences, CUs busy 0.57 of the time, 18.2 ms; with the
 // tiles that exist numbered here 0.96, 13.0 ms (whole call 24.6 -> 19.6 ms; ragged chunks of 4 sequences 329 -> 306 us,
 // 16 x 100..1000 tokens of the 1B shape 265 -> 257 us; sequences of one length as before).
-struct QueryTile { int b, qt, start, len, prefix; };   // sequence, tile, first token, tokens, keys cached before
+// A lane holds its sequences in registers, so there is an end to the batch.  Beyond it tile_of_search costs a workgroup two or
+// three loads; the order is worth more to chunks than the search saves (1B shape, ranked / searched: 250 x 16..150 behind
+// 1..4000 770 / 848 us, 128 x 16..300 behind 1..1000 501 / 524; fresh 70 x 50..4000 3.95 / 3.99 ms, 250 x 50..1500 4.10 / 4.05).
+constexpr int kRankedBatch = 256;
+template <int G>
 __device__ __forceinline__ bool tile_of_rank(const AttnArgs &a, int bq, int u, QueryTile &t) {
   const int lane = threadIdx.x & 63;
-  struct Seq { int start, len, prefix, p, n; };
-  auto sequence = [&](int i) {
-    Seq s{};
+  int start[G], len[G], prefix[G], p[G], n[G];
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    const int i = 64 * j + lane;
+    start[j] = len[j] = prefix[j] = p[j] = n[j] = 0;
     if (i < a.batch) {
-      s.start = a.cu ? a.cu[i] : i * a.per_seq;
-      s.len = a.cu ? a.cu[i + 1] - s.start : a.per_seq;
-      s.prefix = a.prefix ? a.prefix[i] : 0;
-      s.n = max(min((s.len + bq - 1) / bq, a.n_qtiles), 0);
-      s.p = max(s.prefix, 0) / bq;
+      start[j] = a.cu ? a.cu[i] : i * a.per_seq;
+      len[j] = a.cu ? a.cu[i + 1] - start[j] : a.per_seq;
+      prefix[j] = a.prefix ? a.prefix[i] : 0;
+      n[j] = max(min((len[j] + bq - 1) / bq, a.n_qtiles), 0);
+      p[j] = max(prefix[j], 0) / bq;
     }
-    return s;
+  }
+  auto found = [&](int j, int at, int level) {
+    t.b = 64 * j + at;
+    t.qt = level - __builtin_amdgcn_readlane(p[j], at);
+    t.start = __builtin_amdgcn_readlane(start[j], at);
+    t.len = __builtin_amdgcn_readlane(len[j], at);
+    t.prefix = __builtin_amdgcn_readlane(prefix[j], at);
   };
-  auto found = [&](const Seq &s, int base, int at, int level) {
-    t.b = base + at;
-    t.qt = level - __builtin_amdgcn_readlane(s.p, at);
-    t.start = __builtin_amdgcn_readlane(s.start, at);
-    t.len = __builtin_amdgcn_readlane(s.len, at);
-    t.prefix = __builtin_amdgcn_readlane(s.prefix, at);
-    return true;
-  };
-  const Seq s0 = sequence(lane);
-  const int pf = __builtin_amdgcn_readfirstlane(s0.p), nf = __builtin_amdgcn_readfirstlane(s0.n);
-  if (a.batch <= 64 && __builtin_amdgcn_ballot_w64(lane < a.batch && (s0.p != pf || s0.n != nf)) == 0) {   // all alike
+  const int pf = __builtin_amdgcn_readfirstlane(p[0]), nf = __builtin_amdgcn_readfirstlane(n[0]);
+  if (G == 1 && __builtin_amdgcn_ballot_w64(lane < a.batch && (p[0] != pf || n[0] != nf)) == 0) {   // all alike
     const int lvl = u / a.batch;
-    return lvl < nf && found(s0, 0, u - lvl * a.batch, pf + nf - 1 - lvl);
+    if (lvl >= nf) return false;
+    found(0, u - lvl * a.batch, pf + nf - 1 - lvl);
+    return true;
   }
   auto from_level = [&](int c) {   // tiles of level c and above
-    int n = max(min(s0.p + s0.n - c, s0.n), 0);
-    for (int i = lane + 64; i < a.batch; i += 64) {
-      const Seq s = sequence(i);
-      n += max(min(s.p + s.n - c, s.n), 0);
-    }
-    return wave_sum(n);
+    int sum = 0;
+#pragma unroll
+    for (int j = 0; j < G; ++j) sum += max(min(p[j] + n[j] - c, n[j]), 0);
+    return wave_sum(sum);
   };
   if (from_level(0) <= u) return false;
-  int c = 0, above = a.levels, n_above = 0;   // from_level(c) > u >= from_level(above) = n_above
-  while (above - c > 1) {
-    const int mid = (c + above) >> 1, n = from_level(mid);
-    if (n > u) c = mid;
-    else { above = mid; n_above = n; }
+  int level = 0, above = a.levels, left = u;   // from_level(level) > u >= from_level(above) = u - left
+  while (above - level > 1) {
+    const int mid = (level + above) >> 1, m = from_level(mid);
+    if (m > u) level = mid;
+    else { above = mid; left = u - m; }
   }
-  int left = u - n_above;   // which of the sequences that have a tile of level c
-  for (int base = 0; base < a.batch; base += 64) {
-    const Seq s = base ? sequence(base + lane) : s0;
-    const bool has = s.p <= c && c < s.p + s.n;
+#pragma unroll
+  for (int j = 0; j < G; ++j) {   // which of the sequences that have a tile of this level
+    const bool has = p[j] <= level && level < p[j] + n[j];
     const uint64_t mask = __builtin_amdgcn_ballot_w64(has);
-    const int count = __builtin_popcountll(mask);
-    if (left < count) {
-      const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
-      return found(s, base, __builtin_ctzll(__builtin_amdgcn_ballot_w64(has && before == left)), c);
-    }
-    left -= count;
+    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+    const uint64_t it = __builtin_amdgcn_ballot_w64(has && before == left);
+    if (it) found(j, __builtin_ctzll(it), level);
+    left -= __builtin_popcountll(mask);
   }
-  return false;
+  return true;
+}
+
+// Any number of ragged sequences: sequence b owns the ids from cu[b] / bq + b on, at least as many as it has tiles, longest
+// first.  The wave narrows the batch down to the owner of `u` by a factor of 64 with every load.  False: an id too many.
+// (Ranking with a walk over all offsets in each step: paper's layer 2048 x 20..200 tokens 2.82 ms, now 2.38.)
+__device__ __forceinline__ bool tile_of_search(const AttnArgs &a, int bq, int u, QueryTile &t) {
+  const int lane = threadIdx.x & 63;
+  int b = 0;
+  for (int count = a.batch; count > 1;) {
+    const int step = (count + 63) >> 6, i = lane * step;
+    const bool reached = i < count && a.cu[b + i] / bq + b + i <= u;
+    const int k = max(__builtin_popcountll(__builtin_amdgcn_ballot_w64(reached)) - 1, 0) * step;
+    b += k;
+    count = min(step, count - k);
+  }
+  set_sequence(a, b, t);
+  b = t.b;
+  t.qt = min((t.len + bq - 1) / bq, a.n_qtiles) - 1 - (u - t.start / bq - b);
+  return t.qt >= 0;
 }
 
 // Chunk mode: cached lengths, or the flags of skipped sequences (nothing in this or a later launch of the call reads them).
@@ -252,7 +291,7 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
   if constexpr (CHUNK)
     if ((int)blockIdx.x >= a.workgroups) { commit_chunks(a); return; }
-  const int per = a.nq * a.ndlc * a.splits;                  // workgroups of a query tile
+  const int per = FUSE ? a.nq : a.nq * a.ndlc * a.splits;    // workgroups of a query tile
   int u, r;                                                  // rank of the tile, workgroup of the tile
   if (a.spread) {
     int id = (int)blockIdx.x;
@@ -265,16 +304,16 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
     u = round * 8 + (round & 1 ? 7 - x : x);
   }
   QueryTile tile;
-  if (a.every) {   // an id for every (level, sequence)
-    const int lvl = u / a.batch;
-    tile.b = u - lvl * a.batch;
+  if (a.numbering == kEvery) {   // an id for every (level, sequence)
+    const int lvl = u < a.batch ? 0 : u / a.batch;
     tile.qt = a.n_qtiles - 1 - lvl;
-    tile.start = a.cu ? load_uniform(a.cu + tile.b) : tile.b * a.per_seq;
-    tile.len = a.cu ? load_uniform(a.cu + tile.b + 1) - tile.start : a.per_seq;
-    tile.prefix = a.prefix ? load_uniform(a.prefix + tile.b) : 0;
+    if (tile.qt < 0) return;
+    set_sequence(a, u - lvl * a.batch, tile);
     if (tile.qt * T::BQ >= tile.len) return;
-  } else if (!tile_of_rank(a, T::BQ, u, tile)) return;
-  const int g = r % a.nq, dlc = r / a.nq % a.ndlc, split = r / (a.nq * a.ndlc);
+  } else if (a.numbering == kSearched) {
+    if (!tile_of_search(a, T::BQ, u, tile)) return;
+  } else if (!(a.batch <= 64 ? tile_of_rank<1>(a, T::BQ, u, tile) : tile_of_rank<kRankedBatch / 64>(a, T::BQ, u, tile))) return;
+  const int g = FUSE ? r : r % a.nq, dlc = FUSE ? 0 : r / a.nq % a.ndlc, split = FUSE ? 0 : r / (a.nq * a.ndlc);
   const int64_t start = tile.start;
   const int Tb = tile.len, q0 = tile.qt * T::BQ;             // queries of this sequence, first of this tile
   const int P = CHUNK ? tile.prefix : 0;                     // keys cached before the first query
@@ -819,17 +858,24 @@ constexpr int kSpreadTiles = 64;
 
 template <class T, bool FUSE>
 void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t st) {
-  a.n_qtiles = (max_len + T::BQ - 1) / T::BQ;
+  a.n_qtiles = ((a.cu ? max_len : std::min(max_len, a.per_seq)) + T::BQ - 1) / T::BQ;
   a.ndlc = d.dl / T::DLW;
   a.levels = a.n_qtiles + (a.prefix ? a.max_seq / T::BQ : 0) + 1;
-  // no more than this many query tiles whatever the lengths are
-  int64_t tiles = std::min((int64_t)a.n_qtiles * batch, a.total / T::BQ + batch);
+  // ids for every (level, sequence), and no more than this many query tiles whatever the lengths are
+  const int64_t every = (int64_t)a.n_qtiles * batch;
+  int64_t tiles = std::min(every, a.total / T::BQ + batch);
   // Where the chip holds every (level, sequence) at once the order means nothing and tiles need no ranks (two workgroups
   // of four waves on a CU, one of eight): ragged calls, with and without ranks, paper's layers 7 x 41..331 tokens 41.4 / 40.8
   // us, 8 x 10..80 42.2 / 41.5, 32 x 20..100 67.7 / 66.8, 1B shape 4 x 10..40 behind 6000 70.0 / 68.8.
-  a.every = batch > 1 && (int64_t)a.n_qtiles * batch * a.nq * a.ndlc * a.splits <= 512 / T::KS;
-  if (a.every) tiles = (int64_t)a.n_qtiles * batch;
-  a.spread = a.every || tiles < kSpreadTiles;
+  const bool at_once = batch > 1 && every * a.nq * a.ndlc * a.splits <= 512 / T::KS;
+  // Nor do fresh prompts of one length or of one tile each, nor, where a batch is too large to rank, lengths so alike that
+  // these ids are the fewer: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100 rows, paper's layer,
+  // 2.57 -> 1.12 (ranked with a walk over all offsets).
+  if (at_once || (!a.prefix && (!a.cu || a.n_qtiles == 1)) || (batch > kRankedBatch && every == tiles)) {
+    a.numbering = kEvery;
+    tiles = every;
+  } else a.numbering = batch <= kRankedBatch ? kRanked : kSearched;
+  a.spread = at_once || tiles < kSpreadTiles;
   // Chunks of one tile each cost about the same, and the workgroups of a tile read the same cached rows: there an XCD takes an
   // eighth of the workgroups in a row (1B shape, 8 x 100 behind 4000 92.1 -> 86.6 us,
   // 16 x 100 behind 1000 101.4 -> 98.2, 4 x 100 behind 4000 76.7 -> 72.1).  With several tiles a sequence the longest would fall

@@ -163,14 +163,14 @@ def run_decode(wl, wdev, x_np, cache: DeviceCache, slots=None, num_splits=0, gat
     return out
 
 
-def run_prefill_chunk(wl, wdev, x_np, cu_np, cache: DeviceCache, slots=None, gate=True, max_chunk=None):
+def run_prefill_chunk(wl, wdev, x_np, cu_np, cache: DeviceCache, slots=None, gate=True, max_chunk=None, batch=None):
     """gta_prefill_chunk through the C ABI: the chunks follow whatever the slots already hold."""
     cfg = B.config_of(wl)
     cfg.gate = B.GATE_CODES[gate]
     total = x_np.shape[0]
     x = B.to_device(x_np, wl.dtype)
-    cu = torch.from_numpy(np.asarray(cu_np, dtype=np.int32)).cuda()
-    batch = len(cu_np) - 1
+    cu = None if cu_np is None else torch.from_numpy(np.asarray(cu_np, dtype=np.int32)).cuda()
+    batch = batch if cu_np is None else len(cu_np) - 1
     max_chunk = int(np.diff(cu_np).max()) if max_chunk is None else max_chunk
     width = wl.d_model if wdev.get("wo") is not None else wl.n_heads * wl.head_dim
     out = torch.full((total, width), float("nan"), dtype=x.dtype, device="cuda")

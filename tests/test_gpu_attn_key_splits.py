@@ -84,6 +84,39 @@ def test_every_tile_is_found(shape, batch, chunk):
                    f"{shape} sequence {b}: {lens[b]} behind {prefix[b]}")
 
 
+@pytest.mark.parametrize("chunk", [False, True])
+@pytest.mark.parametrize("lengths", ["ragged", "alike", "one_tile", "equal", "no_offsets", "loose_bound"])
+@pytest.mark.parametrize("shape,batch", [("1b", 65), ("paper", 256), ("paper", 257), ("1b", 1000), ("paper", 4097)])
+def test_tiles_of_many_sequences(shape, batch, lengths, chunk):
+    """More sequences than a wave has lanes: ranked four to a lane (to 256), two and three rounds of the search for a tile's
+    sequence, or an id for every (level, sequence).  Every row is written; some sequences are compared with the oracle."""
+    rng = np.random.default_rng(batch)
+    some = lambda *choices: [int(n) for n in rng.choice(choices, batch)]
+    lens = {"ragged": some(0, 1, 2, 17, 40, 127, 128, 129), "alike": some(130, 140, 150), "one_tile": some(0, 1, 33, 127, 128),
+            "loose_bound": some(0, 1, 2, 17, 40, 127, 128, 129)}.get(lengths, [129] * batch)
+    if lengths == "ragged":
+        lens[-1], lens[batch // 2] = 390, 257
+    prefix, cap = some(0, 1, 127, 128, 200) if chunk else [0] * batch, 592
+    wl, w, x, r2 = _setup(shape, sum(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    wdev, bound = U.upload_weights(w, "bf16"), 500 if lengths == "loose_bound" else max(lens)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k, c = (torch.randn((batch, cap, width), device="cuda", generator=gen, dtype=torch.bfloat16) for width in wl.kv_width)
+    cache = U.DeviceCache(wl, batch, cap, k.clone(), c.clone())
+    offsets = None if lengths == "no_offsets" else cu
+    if chunk:
+        cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+        out = U.run_prefill_chunk(wl, wdev, x, offsets, cache, max_chunk=bound, batch=batch)
+    else:
+        out = U.run_prefill(wl, wdev, x, offsets, batch=batch, max_seqlen=bound, cache=cache)
+    assert bool(torch.isfinite(out).all()) and bool(out.any(dim=1).all())
+    assert cache.seq_lens.tolist() == [p + n for p, n in zip(prefix, lens)]
+    for b in sorted({0, batch - 1, batch // 2, 63, 64, *(int(i) for i in rng.integers(0, batch, 24))}):
+        if lens[b]:
+            _check(wl, w, x[cu[b]:cu[b + 1]], U.f64(k[b]), U.f64(c[b]), prefix[b], U.f64(out[cu[b]:cu[b + 1]]),
+                   f"{shape} {lengths} sequence {b}: {lens[b]} behind {prefix[b]}")
+
+
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("shape", list(SHAPES))
 def test_chunks_behind_cached_rows(shape, paged):
