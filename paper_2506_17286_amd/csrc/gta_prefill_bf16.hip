@@ -109,7 +109,7 @@ struct AttnArgs {
   // chunk mode (prefix != NULL): k, c are the caches [slot, max_seq, width]; the chunk's own rows are
   // already in them behind the prefix[b] rows cached before (prefix[b] < 0: sequence skipped, zero output)
   const int32_t *prefix, *slots; int max_seq;
-  int32_t *seq_lens, *status; int max_batch, workgroups;   // the lengths, set by one workgroup behind the others
+  int32_t *seq_lens, *status; int max_batch, workgroups;   // the lengths, set by workgroups behind the others
   PageMap pm; int ps_shift;   // cache mode on a block-table layout: page_size = 1 << ps_shift, a multiple of BK
   // key range split over up to `splits` workgroups (not fused), a sequence's over as many as keep up to 2^split_shift key
   // tiles each: they write un-normalised fp32 sums pacc [split, token, n_q*d_l] and (maximum in log2 units, sum) pml [split,
@@ -271,14 +271,14 @@ __device__ __forceinline__ bool tile_of_search(const AttnArgs &a, int bq, int u,
 }
 
 // Chunk mode: cached lengths, or the flags of skipped sequences (nothing in this or a later launch of the call reads them).
-// By a workgroup of its own: in the tiles' workgroups the arguments push scalars out of the registers of the main loop.
-__device__ __forceinline__ void commit_chunks(const AttnArgs &a) {
-  for (int b = threadIdx.x; b < a.batch; b += blockDim.x) {
-    const int slot = a.slots ? a.slots[b] : b, pre = a.prefix[b];
-    if (slot < 0 || slot >= a.max_batch) continue;
-    if (pre >= 0) a.seq_lens[slot] = pre + (a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq);
-    else a.status[slot] = GTA_ERR_CACHE_FULL;
-  }
+// By workgroups of their own: in the tiles' workgroups the arguments push scalars out of the registers of the main loop.  As many
+// as have a thread per sequence: one for all took the launch 9 us longer at 4096 sequences (1B shape, chunks of 1 or 2 behind 30).
+__device__ __forceinline__ void commit_chunk(const AttnArgs &a, int b) {
+  if (b >= a.batch) return;
+  const int slot = a.slots ? a.slots[b] : b, pre = a.prefix[b];
+  if (slot < 0 || slot >= a.max_batch) return;
+  if (pre >= 0) a.seq_lens[slot] = pre + (a.cu ? a.cu[b + 1] - a.cu[b] : a.per_seq);
+  else a.status[slot] = GTA_ERR_CACHE_FULL;
 }
 
 // CHUNK: keys and latents in the caches.  Fresh prompts have a kernel without that code: in one for both they paid for it (calls of
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
   if constexpr (CHUNK)
-    if ((int)blockIdx.x >= a.workgroups) { commit_chunks(a); return; }
+    if ((int)blockIdx.x >= a.workgroups) { commit_chunk(a, ((int)blockIdx.x - a.workgroups) * T::NT + tid); return; }
   const int per = FUSE ? a.nq : a.nq * a.ndlc * a.splits;    // workgroups of a query tile
   int u, r;                                                  // rank of the tile, workgroup of the tile
   if (a.spread) {
@@ -889,7 +889,7 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
     allow_dynamic_lds((const void *)kernel, smem);
     kernel<<<(unsigned)(a.workgroups + more), T::NT, smem, st>>>(a);
   };
-  if (a.prefix) launch(attn_prefill_kernel<T, FUSE, true>, 1);
+  if (a.prefix) launch(attn_prefill_kernel<T, FUSE, true>, (batch + T::NT - 1) / T::NT);
   else launch(attn_prefill_kernel<T, FUSE, false>, 0);
 }
 

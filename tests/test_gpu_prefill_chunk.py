@@ -202,9 +202,10 @@ def test_chunked_prefill_on_the_shape_generic_kernels(shape):
 
 
 @pytest.mark.parametrize("shape", ["1b", "paper"])
-@pytest.mark.parametrize("copies,bound", [(1, 64), (9, 64), (9, 96)], ids=["held_at_once", "many_sequences", "loose_bound"])
+@pytest.mark.parametrize("copies,bound", [(1, 64), (9, 64), (9, 96), (50, 64)],
+                         ids=["held_at_once", "many_sequences", "loose_bound", "several_workgroups"])
 def test_lengths_and_flags_of_every_kind_of_sequence(shape, copies, bound):
-    """A workgroup behind those of the attention sets lengths and flags: sequences with and without tokens that fit,
+    """Workgroups behind those of the attention set lengths and flags: sequences with and without tokens that fit,
     do not fit, whose slot holds a negative length, is full, or does not exist."""
     kinds = [(5, 10, True), (0, 10, True), (33, 90, True), (0, -1, True), (7, -1, True), (0, 96, True), (1, 96, True), (0, 97, True),
              (64, 32, True), (3, 0, False), (0, 0, False)]                       # tokens, rows cached, slot exists
