@@ -34,7 +34,7 @@ struct Quad { typedef T type __attribute__((ext_vector_type(4))); };
 // PREFILL: decode steps do not occur, FOLD false: nor does fold.batch > 0 (their sines would be held in registers all the same).
 // With fold.batch > 0 a group of columns finds its token among the offsets, which are all requested at once, and takes the
 // sines of its angles itself (the same values as the table's), and waves of their own set the lengths.
-template <typename TD, typename TC, bool PREFILL = false, bool FOLD = true>
+template <typename TD, typename TC, bool PREFILL = false, bool FOLD = false>
 struct ProjEpi {
   TD *dst[4]; int width[4];                 // Q | K | C | gate rows (decode: K and C go to the caches only)
   int dh, rope;
