@@ -36,13 +36,12 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
-// Sum over the LPG (8 or 16) consecutive lanes that hold one key group; every lane gets the sum.
-template <int LPG>
+// Sum over the 16 consecutive lanes that hold one key group; every lane gets the sum.
 __device__ __forceinline__ float group_sum(float v) {
   v += dpp_mov<0xB1>(v);    // quad_perm [1,0,3,2]
   v += dpp_mov<0x4E>(v);    // quad_perm [2,3,0,1]
   v += dpp_mov<0x141>(v);   // row_half_mirror: lane i <-> 7-i of each 8
-  if (LPG == 16) v += dpp_mov<0x140>(v);  // row_mirror: lane i <-> 15-i of each 16
+  v += dpp_mov<0x140>(v);   // row_mirror: lane i <-> 15-i of each 16
   return v;
 }
 __device__ __forceinline__ float lane_bcast(float v, int src_lane) {
@@ -73,7 +72,7 @@ struct DecShape {
   static constexpr int CCH = NC * DLC;
   static constexpr int GPL = 512 / DH;   // key groups per chunk
   static constexpr int LPG = DH / 8;     // lanes per key group
-  static_assert(NK * DH % 512 == 0 && NQ % NC == 0, "shape");
+  static_assert(NK * DH % 512 == 0 && NQ % NC == 0 && LPG == 16, "shape");
 };
 
 constexpr int kWaves = 4;
@@ -309,7 +308,7 @@ __global__ __launch_bounds__(256, S::OCC) void decode_attn_kernel(DecAttnArgs a,
           float a = 0.f;
 #pragma unroll
           for (int w = 0; w < 4; ++w) a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kw[w]), qh[i][u][w], a, false);
-          a = group_sum<LPG>(a);
+          a = group_sum(a);
           p[r][i][u] = r < nv ? a : -INFINITY;
         }
       }

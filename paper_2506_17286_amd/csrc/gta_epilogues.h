@@ -27,7 +27,8 @@ struct Quad { typedef T type __attribute__((ext_vector_type(4))); };
 // what the group reads itself, prepare() works out position, cache row and sines, store() takes the values and
 // `partner`, which returns the four values half a head further (used by the rotation only).  The kernels for few
 // rows call early() ahead of their operand loads and prepare() under them: behind them the two cost a decode step
-// 6 us.  Columns are global (all segments).  Workgroups behind the tiles are for commit(): side_waves() waves of them.
+// 6 us.  Columns are global (all segments).  In the launches for few rows, workgroups behind the tiles are
+// for commit(): side_waves() waves of them.
 
 // Projection (Sec. 3.2) with RoPE on q and k (App. B.1.1) and the cache write (App. B.1.3).
 // TD: element type of the Q | K | C | gate rows (a decode step keeps q and gate in fp32), TC: of the caches.

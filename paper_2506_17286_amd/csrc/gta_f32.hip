@@ -42,7 +42,7 @@ struct GemmOperands {
   const float *A; int lda, M, K;
   const float *B[4]; int ldb[4], seg_cols[4];   // segments side by side (unused ones have 0 columns)
   int heads_per_group, a_group_stride;          // decoder: > 0; B[0] is [n_h, K, seg_cols[0]]
-  int tiles;                                    // of the launch
+  int tiles;                                    // of the launch (few rows)
 };
 __device__ __forceinline__ void operand_at(const GemmOperands &g, int col, const float *&A, const float *&B, int &ldb) {
   A = g.A;
@@ -164,8 +164,7 @@ __global__ __launch_bounds__(256) void gemm_tiles_f32_kernel(GemmOperands g, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   // consecutive workgroup ids go to different XCDs; each XCD takes a contiguous eighth of the tiles, columns
   // fastest, so that the workgroups of an XCD share row strips in its L2
-  const int id = blockIdx.x, per = g.tiles / 8;
-  if (id >= g.tiles) { epi.commit((id - g.tiles) * 4 + wave); return; }
+  const int id = blockIdx.x, per = gridDim.x / 8;
   const int at = id < per * 8 ? (id % 8) * per + id / 8 : id;
   const int nt = at % ntn, m0 = (at / ntn) * BM;
   const float *A, *B;
@@ -616,10 +615,9 @@ void launch_gemm_rows_f32(const GemmOperands &g, int cols, const Epi &epi, hipSt
 // 88; a decode step of 128 sequences 57 against 91).
 constexpr int kRowsMax = 256;
 template <class Epi>
-void launch_gemm_f32(GemmOperands g, int cols, const Epi &epi, hipStream_t st) {
-  if (g.M <= kRowsMax) { launch_gemm_rows_f32(g, cols, epi, st); return; }
-  g.tiles = (cols / 64) * ((g.M + 63) / 64);
-  gemm_tiles_f32_kernel<Epi><<<g.tiles + (epi.side_waves() + 3) / 4, 256, 0, st>>>(g, cols / 64, epi);
+void launch_gemm_f32(const GemmOperands &g, int cols, const Epi &epi, hipStream_t st) {
+  if (g.M <= kRowsMax) launch_gemm_rows_f32(g, cols, epi, st);
+  else gemm_tiles_f32_kernel<Epi><<<(cols / 64) * ((g.M + 63) / 64), 256, 0, st>>>(g, cols / 64, epi);
 }
 
 }  // namespace
@@ -688,17 +686,19 @@ bool f32_proj_folds(const Dims &d, int batch, int64_t M) {
 
 void launch_proj_f32(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws, const gta_cache *cache,
                      const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold, hipStream_t st) {
-  auto launch = [&](auto e) {
-    e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
-    launch_gemm_f32(proj_operands(d, w, x, M), d.wtot, e, st);
-  };
   float *q = (float *)ws.q, *k = (float *)ws.k, *c = (float *)ws.c, *g = (float *)ws.g;
-  if (!fold.batch) { launch(proj_epi<false>(d, q, k, c, g, cache, slots)); return; }
-  auto e = proj_epi<true>(d, q, k, c, g, cache, slots);
-  e.fold = fold;
-  e.commit_to = view_of(cache, slots);
-  for (int j = 0; d.rope && j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
-  launch(e);
+  if (fold.batch) {   // few rows (f32_proj_folds)
+    auto e = proj_epi<true>(d, q, k, c, g, cache, slots);
+    e.max_len = max_len;
+    e.fold = fold;
+    e.commit_to = view_of(cache, slots);
+    for (int j = 0; d.rope && j < d.dh / 2; ++j) e.freq[j] = pow(d.rope_base, -2.0 * (double)j / (double)d.dh);
+    launch_gemm_rows_f32(proj_operands(d, w, x, M), d.wtot, e, st);
+    return;
+  }
+  auto e = proj_epi<false>(d, q, k, c, g, cache, slots);
+  e.seq_id = ws.seq_id; e.pos = ws.pos; e.table = ws.rope; e.max_len = max_len; e.rope_by_token = rope_by_token;
+  launch_gemm_f32(proj_operands(d, w, x, M), d.wtot, e, st);
 }
 
 void launch_decoder_f32(const Dims &d, const float *L, const void *wp, const float *gate, float *out, int M, hipStream_t st) {

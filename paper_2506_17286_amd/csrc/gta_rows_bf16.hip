@@ -25,7 +25,7 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // weights side by side: W_Q | W_K | W_C | W_G, or one matrix
-struct RowsOperands { const bf16 *A; int64_t lda; int M, K; const bf16 *B[4]; int cols[4]; int tiles; };   // tiles: of the launch
+struct RowsOperands { const bf16 *A; int64_t lda; int M, K; const bf16 *B[4]; int cols[4]; int tiles; };   // tiles: of the launch (32-row tiles)
 
 template <int W, class Epi>
 __global__ __launch_bounds__(64 * W) void gemm_rows_bf16_kernel(RowsOperands g, Epi epi) {
@@ -140,8 +140,7 @@ __global__ __launch_bounds__(MidTile<BN>::NT, SUB == 1 ? 4 : 2) void gemm_mid_bf
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nh = wave % T::NH, kg = wave / T::NH;
-  const int id = blockIdx.x, per = g.tiles / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
-  if (id >= g.tiles) { epi.commit((id - g.tiles) * T::NW + wave); return; }
+  const int id = blockIdx.x, per = gridDim.x / 8, at = id < per * 8 ? (id % 8) * per + id / 8 : id;
   const int ntm = (g.M + T::BM - 1) / T::BM, nt = at / ntm, m0 = at % ntm * T::BM;
   int seg = 0, col = nt * BN;
   const bf16 *A = g.A + (int64_t)m0 * g.lda, *B;
@@ -270,18 +269,18 @@ __global__ __launch_bounds__(MidTile<BN>::NT, SUB == 1 ? 4 : 2) void gemm_mid_bf
 }
 
 template <int BN, int SUB, class Epi>
-void launch_mid_tiles(const MidOperands &o, const Epi &epi, hipStream_t st) {
+void launch_mid_tiles(const MidOperands &o, int tiles, const Epi &epi, hipStream_t st) {
   typedef MidTile<BN, SUB> T;
   allow_dynamic_lds((const void *)gemm_mid_bf16_kernel<BN, SUB, Epi>, T::SMEM);
-  gemm_mid_bf16_kernel<BN, SUB, Epi><<<o.g.tiles + (epi.side_waves() + T::NW - 1) / T::NW, T::NT, T::SMEM, st>>>(o, epi);
+  gemm_mid_bf16_kernel<BN, SUB, Epi><<<tiles, T::NT, T::SMEM, st>>>(o, epi);
 }
 // Where no CU gets a second tile a step takes two stages, so that it has half the barriers and more loads in flight (1B shape,
 // whole call of 500 tokens 43.7 -> 42.9 us, 256 39.2 -> 38.2; paper's layer 500 tokens 44.0 -> 42.8).
 template <int BN, class Epi>
-void launch_mid(MidOperands o, int cols, const Epi &epi, hipStream_t st) {
-  o.g.tiles = (cols / BN) * ((o.g.M + 63) / 64);
-  if (o.g.tiles <= 256 && o.g.K % 128 == 0) launch_mid_tiles<BN, 2>(o, epi, st);
-  else launch_mid_tiles<BN, 1>(o, epi, st);
+void launch_mid(const MidOperands &o, int cols, const Epi &epi, hipStream_t st) {
+  const int tiles = (cols / BN) * ((o.g.M + 63) / 64);
+  if (tiles <= 256 && o.g.K % 128 == 0) launch_mid_tiles<BN, 2>(o, tiles, epi, st);
+  else launch_mid_tiles<BN, 1>(o, tiles, epi, st);
 }
 
 }  // namespace
