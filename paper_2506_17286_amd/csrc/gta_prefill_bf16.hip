@@ -285,7 +285,7 @@ __device__ __forceinline__ void commit_chunk(const AttnArgs &a, int b) {
 // the paper's layers, both and now, 7 x 41..331 tokens 41.8 / 40.1 us, 32 x 20..100 68.6 / 66.0, 19 x 295 101.6 / 99.0).
 template <class T, bool FUSE, bool CHUNK>
 __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
-  if constexpr (!CHUNK) { a.prefix = nullptr; a.slots = nullptr; a.pm.table = nullptr; a.eighth = 0; }
+  if constexpr (!CHUNK) { a.prefix = nullptr; a.slots = nullptr; a.pm.table = nullptr; }
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
@@ -867,7 +867,7 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   // Where the chip holds every (level, sequence) at once the order means nothing and tiles need no ranks (two workgroups
   // of four waves on a CU, one of eight): ragged calls, with and without ranks, paper's layers 7 x 41..331 tokens 41.4 / 40.8
   // us, 8 x 10..80 42.2 / 41.5, 32 x 20..100 67.7 / 66.8, 1B shape 4 x 10..40 behind 6000 70.0 / 68.8.
-  const bool at_once = batch > 1 && every * a.nq * a.ndlc * a.splits <= 512 / T::KS;
+  const bool fits = every * a.nq * a.ndlc * a.splits <= 512 / T::KS, at_once = batch > 1 && fits;
   // Nor do fresh prompts of one length or of one tile each, nor, where a batch is too large to rank, lengths so alike that
   // these ids are the fewer: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100 rows, paper's layer,
   // 2.57 -> 1.12 (ranked with a walk over all offsets).
@@ -875,12 +875,14 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
     a.numbering = kEvery;
     tiles = every;
   } else a.numbering = batch <= kRankedBatch ? kRanked : kSearched;
-  a.spread = at_once || tiles < kSpreadTiles;
-  // Chunks of one tile each cost about the same, and the workgroups of a tile read the same cached rows: there an XCD takes an
-  // eighth of the workgroups in a row (1B shape, 8 x 100 behind 4000 92.1 -> 86.6 us,
-  // 16 x 100 behind 1000 101.4 -> 98.2, 4 x 100 behind 4000 76.7 -> 72.1).  With several tiles a sequence the longest would fall
-  // to one XCD (6 x 1000 ragged behind 3000 183 -> 251).
-  a.eighth = a.prefix && a.n_qtiles == 1 ? (int)(tiles * a.nq * a.ndlc * a.splits / 8) : 0;
+  // One tile per sequence: the workgroups of a tile read the same rows.  Where the chip holds them all, an XCD takes an eighth of
+  // the workgroups in a row (1B shape, in turn / eighths: 8 x 100 behind 4000 89.8 / 84.1 us, 3 x 100 70.3 / 68.1, 64 x 128 fresh 169.7
+  // / 165.8).  Chunks beyond that are ranked by the rows they read, and eighths would give one XCD the longest: from 16 tiles on they are
+  // dealt like many tiles (eighths / in turn / dealt: 1B shape 40 x 10..100 behind 1..3000 202 / 154 / 148 us, of one length 244 / 256 /
+  // 240; 8 x 128 + 1024 shape 20 x 10..100 behind 1..4000 347 / 260 / 239, of one length 303 / 306 / 307), fewer in turn (12 x 10..100
+  // behind 1..4000 249 / 181 / 180, of one length 225 / 228 / 233).
+  a.spread = at_once || tiles < (a.prefix && a.n_qtiles == 1 ? 16 : kSpreadTiles);
+  a.eighth = fits && a.n_qtiles == 1 ? (int)(tiles * a.nq * a.ndlc * a.splits / 8) : 0;
   if (!a.spread) tiles = (tiles + 7) / 8 * 8;
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;

@@ -19,9 +19,10 @@ SHAPES = {"1b": W.WORKLOADS[1], "paper": W.PAPER_WORKLOADS[0],
           "mid": W.scaled(W.WORKLOADS[1], n_heads=4, n_qgroups=2, n_kgroups=1, latent_dim=128),
           "slim": W.scaled(W.PAPER_WORKLOADS[0], n_heads=8, n_qgroups=8, n_kgroups=2, n_cgroups=2, latent_dim=64)}
 
+WIDE = W.WORKLOADS[4]
 
 def _setup(shape, tokens):
-    wl = W.scaled(SHAPES[shape], d_model=128, seed=7300)
+    wl = W.scaled(SHAPES.get(shape, WIDE), d_model=128, seed=7300)
     if shape in ("paper", "slim"):
         wl = W.scaled(wl, d_model=256)
     rng = W.make_rng(wl)
@@ -242,12 +243,12 @@ def test_latent_tile_changes_over(chunk, batch):
                f"sequence {b}: {lens[b]} behind {prefix[b]}")
 
 
-@pytest.mark.parametrize("batch", [3, 9])
-@pytest.mark.parametrize("shape", ["paper", "mid"])
+@pytest.mark.parametrize("shape,batch", [("paper", 3), ("paper", 9), ("mid", 3), ("mid", 9), ("1b", 32), ("1b", 33), ("wide", 9), ("wide", 17)])
 def test_chunks_of_one_tile(shape, batch):
-    """Chunks of at most 128 tokens: the XCDs take workgroups in a row, 15 and 45 (paper) do not divide by eight; one chunk
-    is empty, one full."""
-    lens, cap = [128, 0, 1, 40, 77, 2, 127, 33, 64][:batch], 1216
+    """Chunks of at most 128 tokens: the XCDs take workgroups in a row, 15 and 45 (paper) do not divide by eight; more than the
+    chip holds at once (1b 33, wide) are ranked and dealt to the XCDs by tile, below 16 by workgroup; some chunks are empty,
+    some full."""
+    lens, cap = ([128, 0, 1, 40, 77, 2, 127, 33, 64] * 4)[:batch], 1216
     prefix = [int(p) for p in np.random.default_rng(3).integers(0, cap - 128, batch)]
     wl, w, x, rng = _setup(shape, sum(lens))
     k, c = W.draw_cache(wl, rng, batch, cap)
