@@ -115,19 +115,38 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, E
   __builtin_amdgcn_sched_barrier(0);
   typename Epi::Ctx ctx{};
   if (finisher) ctx = epi.prepare(early, m0 + row, fcol, rot);
-  for (int c0 = wave; c0 < ng; c0 += U * W) {
+  auto multiply = [&](int u) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (c0 + u * W < ng) {
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int i = 0; i < NSUB; ++i) {
-            if constexpr (MT == 32) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i][j], b[u][j], acc[i], 0, 0, 0);
-            else acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][j], b[u][j], acc[i], 0, 0, 0);
-          }
+      for (int i = 0; i < NSUB; ++i) {
+        if constexpr (MT == 32) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i][j], b[u][j], acc[i], 0, 0, 0);
+        else acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][j], b[u][j], acc[i], 0, 0, 0);
       }
-      if (c0 + U * W < ng) load(u, c0 + (u + U) * W);
+  };
+  // Requests behind the last round are left out (they took 3 to 6 us of 40 to 90 at K = 1280).  A branch around each in the loop
+  // costs long contractions of 32 x 32 tiles more than that (K = 4096, 60 heads: 128 rows 128 us, unconditional 124, last round apart
+  // 111; K = 8192, 200 rows 148, 138, 123); of the smaller tiles, whose contraction is mostly one round, the branch is the faster
+  // form (64 x 2048 rows of the paper's layer 49.3 us, last round apart 51.8).
+  int c0 = wave;
+  if constexpr (MT == 32) {
+    for (; c0 + U * W < ng; c0 += U * W) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        multiply(u);
+        load(u, c0 + (u + U) * W);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c0 + u * W < ng) multiply(u);
+  } else {
+    for (; c0 < ng; c0 += U * W) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (c0 + u * W < ng) multiply(u);
+        if (c0 + U * W < ng) load(u, c0 + (u + U) * W);
+      }
     }
   }
   float *mine = red + wave * BM * PITCH;

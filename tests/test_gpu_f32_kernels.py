@@ -3,7 +3,7 @@
 contiguous and block-table caches, full slots.
 
 Bound: the fp32 tolerances of the parity gate (max-abs 1e-5, relative RMS 1e-5); sums of at most 1280 fp32 products
-stay a factor of ten below them."""
+stay a factor of ten below them, of 3904 in 16 partial sums a factor of five."""
 import numpy as np
 import pytest
 import torch
@@ -240,3 +240,18 @@ def test_gemms_of_few_rows(shape, rows):
     U.assert_close(U.f64(cache.k[0, :rows]), k.reshape(rows, -1), "f32", "keys", _scale(k))
     U.assert_close(U.f64(cache.c[0, :rows]), c.reshape(rows, -1), "f32", "latents", _scale(c))
     assert bool((cache.k[0, rows:] == 7.0).all())
+
+
+@pytest.mark.parametrize("rows", [16, 64, 70])            # 16 x 16, 32 x 16 and 32 x 32 tiles
+@pytest.mark.parametrize("d_model", [640, 1216, 1280, 1344, 2560, 2624, 3904])
+def test_rounds_of_a_contraction(d_model, rows):
+    """16 waves take five groups of the contraction each before they ask for more: part of a round, one, two and more, and some
+    groups over."""
+    wl = W.scaled(_wl("paper"), d_model=d_model)
+    w, x = _inputs(wl, rows, True)
+    cache = U.DeviceCache(wl, 1, rows)
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "f32"), x, [0, rows], cache=cache))
+    ref, k, c = orc.prefill_sequence(U.oracle_config(wl), U.oracle_weights(w), x)
+    U.assert_close(out, ref, "f32", f"{d_model} wide, {rows} rows", _scale(ref))
+    U.assert_close(U.f64(cache.k[0, :rows]), k.reshape(rows, -1), "f32", "keys", _scale(k))
+    U.assert_close(U.f64(cache.c[0, :rows]), c.reshape(rows, -1), "f32", "latents", _scale(c))
