@@ -66,10 +66,11 @@ __device__ __forceinline__ void operand_at(const GemmOperands &g, int col, const
 // rows and short prompts: what bounds these is the latency of a few loads and how many workgroups pull on the
 // weights, not arithmetic.  A tile that is rotated must hold both halves of its heads: with heads wider than the tile it
 // takes half its columns of one half and those they pair with, otherwise (whole heads fit) columns in a row.
-template <int W, int BM, int BN, class Epi>
+constexpr int kRowsInFlight = 5;   // U
+template <int W, int BM, int BN, bool LONG, class Epi>
 __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, Epi epi) {
   constexpr int MT = BN == 32 ? 32 : 16, NSUB = BM / MT;   // MFMA tile, tiles of rows
-  constexpr int U = 5, PITCH = BN + 4, KG = 256 / MT, HB = BN / 2, GR = BN / 4;   // GR: groups of four columns a row
+  constexpr int U = kRowsInFlight, PITCH = BN + 4, KG = 256 / MT, HB = BN / 2, GR = BN / 4;   // GR: groups of four columns a row
   extern __shared__ __attribute__((aligned(16))) float red[];   // [W][BM][PITCH]
   const int tid = threadIdx.x, lane = tid & 63, h = lane / MT, ln = lane % MT;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -125,11 +126,11 @@ __global__ __launch_bounds__(64 * W) void gemm_rows_f32_kernel(GemmOperands g, E
       }
   };
   // Requests behind the last round are left out (they took 3 to 6 us of 40 to 90 at K = 1280).  A branch around each in the loop
-  // costs long contractions of 32 x 32 tiles more than that (K = 4096, 60 heads: 128 rows 128 us, unconditional 124, last round apart
-  // 111; K = 8192, 200 rows 148, 138, 123); of the smaller tiles, whose contraction is mostly one round, the branch is the faster
-  // form (64 x 2048 rows of the paper's layer 49.3 us, last round apart 51.8).
+  // costs a contraction of more than one round (LONG) more than that: 32 x 32 tiles at K = 4096, 60 heads, 128 rows 128 us,
+  // unconditional 124, last round apart 111; K = 8192, 200 rows 148, 138, 123; 16-column tiles, 20 rows 43.8, 44.0, 41.6.  Of a single
+  // round it is the faster form: 64 x 2048 rows of the paper's layer 49.3 us, last round apart 51.8; K = 640, 256 rows 31.5, 32.8.
   int c0 = wave;
-  if constexpr (MT == 32) {
+  if constexpr (LONG) {
     for (; c0 + U * W < ng; c0 += U * W) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -613,9 +614,14 @@ void launch_gemm_rows_f32(GemmOperands g, int cols, const Epi &epi, hipStream_t 
   };
   // two rounds of loads per wave at most: K = 1280 over 16 waves (64 rows of the paper's projection 16 us, 20 us with
   // eight waves of 64 columns), K = 256 over eight (5 us; 16 mostly idle waves 9 us), K = 64 over four
-  if (g.K >= 640) launch(gemm_rows_f32_kernel<16, BM, BN, Epi>, 16);
-  else if (g.K >= 192) launch(gemm_rows_f32_kernel<8, BM, BN, Epi>, 8);
-  else launch(gemm_rows_f32_kernel<4, BM, BN, Epi>, 4);
+  auto launch_waves = [&](auto waves) {
+    constexpr int W = decltype(waves)::value;
+    if (g.K / (BN == 32 ? 8 : 16) > kRowsInFlight * W) launch(gemm_rows_f32_kernel<W, BM, BN, true, Epi>, W);
+    else launch(gemm_rows_f32_kernel<W, BM, BN, false, Epi>, W);
+  };
+  if (g.K >= 640) launch_waves(std::integral_constant<int, 16>{});
+  else if (g.K >= 192) launch_waves(std::integral_constant<int, 8>{});
+  else launch_waves(std::integral_constant<int, 4>{});
 }
 // The smallest tile of which every CU gets at most one: a tile's time is its own loads and its matrix instructions, 4.4 us of
 // them for 32 x 32 at K = 1280, and a CU without a tile is idle.  Whole calls with 32 x 32 / 32 x 16 / 16 x 16 tiles, paper's
