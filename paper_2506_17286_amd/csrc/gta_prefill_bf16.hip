@@ -313,7 +313,8 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
   } else if (a.numbering == kSearched) {
     if (!tile_of_search(a, T::BQ, u, tile)) return;
   } else if (!(a.batch <= 64 ? tile_of_rank<1>(a, T::BQ, u, tile) : tile_of_rank<kRankedBatch / 64>(a, T::BQ, u, tile))) return;
-  const int g = FUSE ? r : r % a.nq, dlc = FUSE ? 0 : r / a.nq % a.ndlc, split = FUSE ? 0 : r / (a.nq * a.ndlc);
+  constexpr bool ONE = FUSE && (!CHUNK || T::KS == 1);       // a workgroup per map (the main loop of the other kernel is slower with it)
+  const int g = ONE ? r : r % a.nq, dlc = ONE ? 0 : r / a.nq % a.ndlc, split = ONE ? 0 : r / (a.nq * a.ndlc);
   const int64_t start = tile.start;
   const int Tb = tile.len, q0 = tile.qt * T::BQ;             // queries of this sequence, first of this tile
   const int P = CHUNK ? tile.prefix : 0;                     // keys cached before the first query
@@ -868,10 +869,11 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   // of four waves on a CU, one of eight): ragged calls, with and without ranks, paper's layers 7 x 41..331 tokens 41.4 / 40.8
   // us, 8 x 10..80 42.2 / 41.5, 32 x 20..100 67.7 / 66.8, 1B shape 4 x 10..40 behind 6000 70.0 / 68.8.
   const bool fits = every * a.nq * a.ndlc * a.splits <= 512 / T::KS, at_once = batch > 1 && fits;
-  // Nor do fresh prompts of one length or of one tile each, nor, where a batch is too large to rank, lengths so alike that
-  // these ids are the fewer: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100 rows, paper's layer,
-  // 2.57 -> 1.12 (ranked with a walk over all offsets).
-  if (at_once || (!a.prefix && (!a.cu || a.n_qtiles == 1)) || (batch > kRankedBatch && every == tiles)) {
+  // Nor do fresh prompts of one length or of one tile each: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100
+  // rows, paper's layer, 2.57 -> 1.12 (ranked with a walk over all offsets).  Where a batch is too large to rank, ids that few tiles
+  // are missing from cost less than the search: 768 wide layer 300 x 20..200 (600 ids, bound 558) 224.8 / 214.2 us, paper's layer 512
+  // chunks of 20..200 (1.14 times the bound) 799 / 782, 300 x 20..130 (1.26) 287 / 273, equal at 260 x 100..1000 (1.6).
+  if (at_once || (!a.prefix && (!a.cu || a.n_qtiles == 1)) || (batch > kRankedBatch && 5 * every <= 8 * tiles)) {
     a.numbering = kEvery;
     tiles = every;
   } else a.numbering = batch <= kRankedBatch ? kRanked : kSearched;

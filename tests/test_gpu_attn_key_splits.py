@@ -86,14 +86,14 @@ def test_every_tile_is_found(shape, batch, chunk):
 
 
 @pytest.mark.parametrize("chunk", [False, True])
-@pytest.mark.parametrize("lengths", ["ragged", "alike", "one_tile", "equal", "no_offsets", "loose_bound"])
+@pytest.mark.parametrize("lengths", ["ragged", "alike", "one_tile", "two_tiles", "equal", "no_offsets", "loose_bound"])
 @pytest.mark.parametrize("shape,batch", [("1b", 65), ("paper", 256), ("paper", 257), ("1b", 1000), ("paper", 4097)])
 def test_tiles_of_many_sequences(shape, batch, lengths, chunk):
     """More sequences than a wave has lanes: ranked four to a lane (to 256), two and three rounds of the search for a tile's
     sequence, or an id for every (level, sequence).  Every row is written; some sequences are compared with the oracle."""
     rng = np.random.default_rng(batch)
     some = lambda *choices: [int(n) for n in rng.choice(choices, batch)]
-    lens = {"ragged": some(0, 1, 2, 17, 40, 127, 128, 129), "alike": some(130, 140, 150), "one_tile": some(0, 1, 33, 127, 128),
+    lens = {"ragged": some(0, 1, 2, 17, 40, 127, 128, 129), "alike": some(130, 140, 150), "one_tile": some(0, 1, 33, 127, 128), "two_tiles": some(0, 1, 100, 129, 200),
             "loose_bound": some(0, 1, 2, 17, 40, 127, 128, 129)}.get(lengths, [129] * batch)
     if lengths == "ragged":
         lens[-1], lens[batch // 2] = 390, 257
