@@ -238,8 +238,8 @@ GTA_API int gta_output_projection(const gta_config *cfg, const gta_weights *weig
  * l_out[t, g*d_l : (g+1)*d_l] = sum_{j<=t} Softmax_j(q_g[t].k_{k(g)}[j] / sqrt(d_h)) c_{c(g)}[j].
  *   q [total, n_q*d_h], k [total, n_k*d_h] (both already rotated), c [total, n_c*d_l],
  *   l_out [total, n_q*d_l]; all device, element type = cfg->dtype; cu_seqlens as in gta_prefill.
- * (Without scratch memory: a launch of few workgroups whose keys gta_prefill splits over several of them runs
- * unsplit here.) */
+ * (Without scratch memory: a launch of few workgroups, whose keys gta_prefill splits over several of them or whose
+ * latents it takes in narrower tiles, runs unsplit on the wider ones here.) */
 GTA_API int gta_prefill_attention(const gta_config *cfg, const void *q, const void *k, const void *c,
                                   const int32_t *cu_seqlens, int32_t batch, int64_t total_tokens,
                                   int32_t max_seqlen, void *l_out, void *hip_stream);

@@ -492,13 +492,14 @@ __device__ __forceinline__ float rows_sum(float v) {
 // row operand wants four rows of one latent column per lane; a lane loads 16 bytes of each of its four rows (16 lanes cover
 // a row) and pairs them up with v_perm_b32, two MFMAs of 16 x 16 x 16 for each of the eight columns it holds: probabilities
 // are bf16 pairs, their upper half and what it lacks.  (Rounded once, a step's error against 64 bits was 2.8e-3 to 3.0e-3
-// where the vector kernel before it, with more and shorter streams whose largest probability is exactly 1, had 2.5e-3 to
-// 2.9e-3; with the pair 2.6e-3 to 2.7e-3, at the same time.)  Queries are rounded to bf16, sums are fp32.
+// where the vector kernel before it, with more and shorter streams whose largest probability is exactly 1, had 2.7e-3 to
+// 3.0e-3; with the pair 2.5e-3 to 2.7e-3, means over eight inputs, at the same time.)  Queries are rounded to bf16, sums are fp32.
 // Bound: at 50 MB a step the launch, a workgroup's chain of loads and the merge (HBM from about 100 MB on); a step of 16 rows
 // is about 65 vector and 18 (34) matrix instructions.  With scores, softmax and latents on the vector ALU, where each lane
 // worked out the softmax of a row that eight of them share, 8 rows took about 200, and the waves of a CU took longer over them
-// than the memory over their rows.  Whole steps, before and now: 5 maps 64 x 2048 40.1 -> 31.8 us, 1 x 1000 26.2 -> 21.5, 32 x
-// 8192 49.4 -> 38.8, 128 x 250..2000 47.1 -> 36.3, 3 maps 64 x 2048 33.2 -> 29.2; two latents, 10 maps 64 x 2048 61.5 -> 37.6,
+// than the memory over their rows.  Whole steps, before and now, on the same buffers every time (with buffers that change from
+// call to call 64 x 2048 41.7 -> 33.5 us, 1 x 1000 27.0 -> 23.5): 5 maps 64 x 2048 39.7 -> 31.7, 1 x 1000 25.4 -> 21.5, 32 x 8192
+// 49.3 -> 39.1, 128 x 250..2000 47.5 -> 36.5, 3 maps 64 x 2048 33.2 -> 29.2; two latents, 10 maps 64 x 2048 61.5 -> 37.6,
 // 16 x 4000 43.0 -> 29.6.  Two, three or four steps in flight per wave: 31.8 / 32.1 / 32.7 us at 64 x 2048.  Same three call
 // modes as the kernel above.
 template <int NQ, int NC>
@@ -1450,7 +1451,7 @@ void launch_tail(const Dims &d, const float *pacc, const float *pml, const Decod
 // More workgroups than two per CU would finish one sequence and head each: 16 sequences per workgroup instead, up to eight
 // splits (two rounds of loads).  Whole steps of the 1B shape, without and with: 33 behind 1000 47.4 / 41.0 us, 63 62.1 / 48.4, 64
 // 54.1 / 49.5, 100 behind 100..1000 71.4 / 56.6, 255 behind 500 99.4 / 72.6, 48 behind 4000 93.5 / 85.8, 64 behind 8192 189.1 /
-// 184.5; where one sequence a workgroup is enough, 16 behind 1000 29.4 / 36.7 and 16 behind 4000 (16 splits) 43.1 / 51.3.  From 256
+// 184.5; 32 heads 17 behind 300 39.6 / 31.9, 64 heads 9 behind 300 41.3 / 34.0, 8 heads 65 behind 1000 58.0 / 50.1; where one sequence a workgroup is enough, 16 behind 1000 29.4 / 36.7 and 16 behind 4000 (16 splits) 43.1 / 51.3.  From 256
 // sequences on the GEMM is ahead (320 behind 500 98.7 / 102.5, 1024 behind 256 152 / 162).
 bool tail16_ok(const Dims &d, int batch, int splits) {
   return d.dl == 512 && d.dh == 128 && batch < kGemmTailBatch && batch * d.nh > 512 && splits <= 8;
