@@ -869,11 +869,14 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   // of four waves on a CU, one of eight): ragged calls, with and without ranks, paper's layers 7 x 41..331 tokens 41.4 / 40.8
   // us, 8 x 10..80 42.2 / 41.5, 32 x 20..100 67.7 / 66.8, 1B shape 4 x 10..40 behind 6000 70.0 / 68.8.
   const bool fits = every * a.nq * a.ndlc * a.splits <= 512 / T::KS, at_once = batch > 1 && fits;
-  // Nor do fresh prompts of one length or of one tile each: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100
-  // rows, paper's layer, 2.57 -> 1.12 (ranked with a walk over all offsets).  Where a batch is too large to rank, ids that few tiles
-  // are missing from cost less than the search: 768 wide layer 300 x 20..200 (600 ids, bound 558) 224.8 / 214.2 us, paper's layer 512
-  // chunks of 20..200 (1.14 times the bound) 799 / 782, 300 x 20..130 (1.26) 287 / 273, equal at 260 x 100..1000 (1.6).
-  if (at_once || (!a.prefix && (!a.cu || a.n_qtiles == 1)) || (batch > kRankedBatch && 5 * every <= 8 * tiles)) {
+  // Nor do fresh prompts of one tile each or of one length: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100
+  // rows, paper's layer, 2.57 -> 1.12 (ranked with a walk over all offsets).  With offsets the lengths show in ids that are no more than
+  // the bound (256 x 129 of the paper's layer with two latents 535 -> 525 us; a batch of one wave's lanes looks at them itself).  Where a
+  // batch is too large to rank, ids that few tiles are missing from cost less than the search: 768 wide layer 300 x 20..200 (600 ids, bound
+  // 558) 224.8 / 214.2 us, paper's layer 512 chunks of 20..200 (1.14 times the bound) 799 / 782, 300 x 20..130 (1.26) 287 / 273, equal
+  // at 260 x 100..1000 (1.6).
+  if (at_once || (!a.prefix && (!a.cu || a.n_qtiles == 1 || (batch > 64 && every == tiles))) ||
+      (batch > kRankedBatch && 5 * every <= 8 * tiles)) {
     a.numbering = kEvery;
     tiles = every;
   } else a.numbering = batch <= kRankedBatch ? kRanked : kSearched;
