@@ -11,13 +11,15 @@
 // a plain 16-byte LDS read of an X row.  Each lane then owns 4 consecutive output columns of one
 // output row, which makes the RoPE pairing (j, j + d_h/2) lane-local.
 //
-// Workgroup tile BM x BN x BK with WGM x WGN waves of 32x32x16 MFMA tiles.  The 256 x 256 x 64 tiles
-// run the hand-pipelined main loop below (operands straight into LDS, four stages); their result
-// is rounded to bf16, parked in LDS in output layout and written with 16-byte row-contiguous stores.
+// Workgroup tile BM x BN x BK with WGM x WGN waves of 32x32x16 MFMA tiles.  Projection and output projection of many rows
+// run as a stream of 256 x 256 tiles through one workgroup per CU (gemm_stream), the value decoder as one such tile per
+// workgroup (gemm_mainloop_big): operands straight into LDS, results rounded to bf16, passed through LDS and written with
+// 16-byte row-contiguous stores.
 // The small tiles (split-K projection of the decode step) take the plain two-stage loop and store straight from the
 // accumulator layout.  Short prefills take the kernels for few rows (short_gemm_ok).
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gta_lds_load.h"
@@ -132,11 +134,9 @@ __device__ __forceinline__ void gemm_mainloop(const bf16 *__restrict__ A, int64_
 // consecutive rows read one logical chunk from 8 (16) different 16-byte columns of 128 (256) bytes.  Weight rows are
 // 32 chunks, chunk c of k-row k in slot c ^ 4 (k % 4): the four k-rows of a transpose read lie in different 64-byte
 // columns.
-// Bound: what the chip sustains on such data (1240 TFLOP/s for a large library GEMM; the projection of 112 K rows x
-// 4096 x 7168 reaches 1180).  Measured against four waves of 128 x 128 that staged through registers (one wave per
-// SIMD, 512 registers and spills): projection 16384 x 2048 x 3584 273 -> 252 us, 65536 x 1280 x 1792 394 -> 325,
-// W_O 65536 x 1280 x 1280 251 -> 225, decoder of 16384 rows 76 -> 69.  The same loop with four waves was no faster
-// than the staged one; wave priorities, the barrier's place and free scheduling changed nothing.
+// Measured against four waves of 128 x 128 that staged through registers (one wave per SIMD, 512 registers and spills):
+// decoder of 16384 rows 76 -> 69.  The same loop with four waves was no faster than the staged one; wave priorities, the
+// barrier's place and free scheduling changed nothing.
 __device__ __forceinline__ int x_swz(int r) { return ((r >> 2) & 3) ^ (r & 2); }
 
 struct BigLoop {
@@ -260,6 +260,232 @@ __device__ __forceinline__ void gemm_mainloop_big(const bf16 *__restrict__ Abase
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Order of a stream's tiles, of which XCD x (workgroup ids x mod 8) takes the x-th eighth: bands of 8 row strips, a band in
+// panels of 4 columns (5, if there are no more), a panel row strip by row strip.  The 32 workgroups of an XCD then work on
+// one block of 8 strips of X x 4 of the weights.  Panels of 7 where 7 divides the columns were slower (projections
+// 16384 x 2048 x 3584 224 -> 228 us, 121600 x 4096 x 7168 5.96 -> 6.23 ms), 3 + 2 columns of 5 too (65536 x 1280 x 1280 196
+// -> 199).  The divisors are known to the host.
+struct Divisor { unsigned magic; int d; };
+inline Divisor divisor(int d) { return Divisor{d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u, d}; }
+__device__ __forceinline__ int quotient(int x, const Divisor &v) {   // x >= 0; the product is at most one too many
+  const int q = v.magic ? (int)__umulhi((unsigned)x, v.magic) : x;
+  return q * v.d > x ? q - 1 : q;
+}
+struct StreamOrder {
+  static constexpr int kBand = 8, kPanel = 4;
+  int ntn, ntm, w;
+  Divisor band, panel, panel_end, width, width_end;   // tiles of a band, of a panel (and in the last band), columns of a panel (and of the last)
+  int tiles() const { return ntn * ntm; }
+};
+inline StreamOrder stream_order(int ntn, int ntm) {
+  StreamOrder o;
+  o.ntn = ntn; o.ntm = ntm;
+  const int np = ntn <= StreamOrder::kPanel + 1 ? 1 : (ntn + StreamOrder::kPanel - 1) / StreamOrder::kPanel;
+  o.w = (ntn + np - 1) / np;
+  const int end = ntm % StreamOrder::kBand ? ntm % StreamOrder::kBand : StreamOrder::kBand, last = ntn - (ntn - 1) / o.w * o.w;
+  o.band = divisor(StreamOrder::kBand * ntn);
+  o.panel = divisor(StreamOrder::kBand * o.w);
+  o.panel_end = divisor(end * o.w);
+  o.width = divisor(o.w);
+  o.width_end = divisor(last);
+  return o;
+}
+struct TileAt { int m, n; };
+__device__ __forceinline__ TileAt tile_at(const StreamOrder &o, int id) {
+  const int nblk = o.ntn * o.ntm, per = nblk >> 3;
+  const int pos = id < per * 8 ? (id & 7) * per + (id >> 3) : id;   // the last nblk % 8 tiles keep their place
+  const int band = quotient(pos, o.band), row0 = band * StreamOrder::kBand;
+  int rem = pos - band * o.band.d;
+  const bool end = o.ntm - row0 < StreamOrder::kBand;
+  const int panel = end ? quotient(rem, o.panel_end) : quotient(rem, o.panel), col0 = panel * o.w;
+  rem -= panel * (end ? o.panel_end.d : o.panel.d);
+  const bool narrow = o.ntn - col0 < o.w;
+  const int row = narrow ? quotient(rem, o.width_end) : quotient(rem, o.width);
+  return TileAt{row0 + row, col0 + rem - row * (narrow ? o.width_end.d : o.w)};
+}
+
+// ---- main loop over a stream of tiles ----------------------------------------------------------
+// A workgroup works through the tiles blockIdx.x, + gridDim.x, .. of a launch of one workgroup per CU; the loads of a tile
+// start under the last k-steps of the tile before it, and what is behind its epilogue's stores does not wait for them.
+// 256 x 256 tile, eight waves (two per SIMD) of 64 x 128.  X comes in rows of 64 k (128 bytes: with 64 bytes of a row per
+// load, the L2 moved every line twice and the loads alone took longer than the matrix instructions, 0.52 against 0.38 us
+// per 32 k at K = 1280), three stages of 32 KiB; weights in four stages of 32 k, 16 KiB each.  The unit of the loop is a
+// half step of 32 k (two k-steps of eight MFMAs per wave); half step u
+//   * reads the fragments of its second k-step under the MFMAs of the first;
+//   * waits at a barrier: every wave has then read all of weight stage u (u odd: and of X stage u / 2), and the loads of
+//     half step u - 3 have landed, which brought weights u + 1 and, if u is odd, the rest of X stage (u + 1) / 2;
+//   * reads the fragments of half step u + 1 under the MFMAs of the second k-step, and requests weights u + 4 and half of an
+//     X stage: the first half of stage s + 3 with u = 2 s + 1, the second with u = 2 s + 2.
+// The epilogue gets the X stage the tile has left as scratch: 4 KiB that belong to the wave until it has the same rows of
+// that stage loaded.  It issues kStores stores at least, always (rows past the end are left to the buffer's bounds), so
+// that the first half steps of the next tile can wait for loads that are older.
+// LDS layout: a load instruction fills 1 KiB in lane order, so there is no padding; each lane fetches the 16-byte chunk that
+// belongs in its slot.  X rows are 8 chunks, chunk c of row r in slot c ^ xs_swz(r): any 8 (16) consecutive rows read one
+// logical chunk from 8 (16) different 16-byte columns of 128 (256) bytes.  Weights as in the loop above.
+// Bound: power.  Without loads a half step takes 0.73 us on such data and 0.54 on zeros, the loads alone 0.38; together 0.8 and
+// 0.6 (0.87 and 0.77 in the loop above), of which the matrix instructions are 0.43 at 2.4 GHz.  Against a workgroup per tile on that
+// loop (kernels inside the calls): projection 65536 x 1280 x 1792 334 -> 293 us, W_O 65536 x 1280 x 1280 234 -> 195,
+// projection 16384 x 2048 x 3584 243 -> 221, 6500 x 2048 x 3584 114 -> 110, 121600 x 4096 x 7168 6.10 -> 5.96 ms.
+struct StreamTile { const bf16 *A; int rows; WeightTile B; };   // row m0 of the row operand, rows from there, weight columns
+
+struct StreamLoop {
+  static constexpr int BM = 256, BN = 256, X_BYTES = BM * 64 * 2, W_BYTES = 32 * BN * 2, W_OFF = 3 * X_BYTES, SMEM = W_OFF + 4 * W_BYTES;
+  static constexpr int WGM = 4, WGN = 2, NT = 512, WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
+};
+__device__ __forceinline__ int xs_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
+// acc[tn][tm][r]:  n = wn*128 + tn*32 + 8*(r/4) + 4*(lane/32) + r%4,  m = wm*64 + tm*32 + lane%32, wn = wave % 2, wm = wave / 2.
+// K a multiple of 128, at least 256.
+template <class Src, class Epi>
+__device__ __forceinline__ void gemm_stream(const StreamOrder &order, int64_t lda, int K, char *smem, const Src &src, const Epi &epi) {
+  typedef StreamLoop T;
+  constexpr int TM = T::TM, TN = T::TN, kSet = 4;   // load instructions of a wave per half step
+  const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % T::WGN, wm = wave / T::WGN;
+  const int nk = K / 64, ntiles = order.ntn * order.ntm;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+  // what is requested next.  Rows past the last valid one read as 0, and so does everything behind the last tile.
+  // This wave's loads: rows 32 wave + 8 j + lane/8 of an X stage, k-rows 4 wave + 2 j + lane/32 of a weight stage.
+  unsigned xv[4], wv[2], xbytes = 0, wbytes = 0;
+  int64_t wstep = 0;
+  const char *xbase = nullptr, *wbase = nullptr;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = wave * 32 + j * 8 + (lane >> 3);
+    xv[j] = (unsigned)(r * lda * 2) + ((lane & 7) ^ xs_swz(r)) * 16;
+  }
+  TileAt now{}, next{};   // the tile that is worked on and the one that is requested
+  auto request_x = [&](int id) {
+    xbytes = 0;
+    if (id >= ntiles) return;
+    next = tile_at(order, id);
+    const StreamTile s = src(next);
+    xbase = reinterpret_cast<const char *>(s.A);
+    xbytes = (unsigned)((min(s.rows, T::BM) - 1) * lda * 2) + 128u;
+  };
+  auto request_w = [&](int id) {
+    wbytes = 0;
+    if (id >= ntiles) return;
+    const StreamTile s = src(next);
+    wbase = reinterpret_cast<const char *>(s.B.base);
+    wbytes = s.B.bytes;
+    wstep = (int64_t)32 * s.B.ld * 2;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int k = (wave * 2 + j) * 2 + h;
+      wv[j] = (unsigned)(k * s.B.ld * 2) + s.B.chunk_bytes(ln ^ ((k & 3) << 2));
+    }
+  };
+  // LDS offsets of X stages s, s + 1, s + 2 and weight stages u .. u + 3
+  int xs[3] = {0, T::X_BYTES, 2 * T::X_BYTES}, ws[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ws[i] = T::W_OFF + i * T::W_BYTES;
+  auto load_x = [&](int at, int j) { load_to_lds(buffer_of(xbase, xbytes), xv[j], lds0 + at + (wave * 4 + j) * 1024); };
+  auto load_w = [&](int at, int j) { load_to_lds(buffer_of(wbase, wbytes), wv[j], lds0 + at + (wave * 2 + j) * 1024); };
+  // fragment addresses: X chunk 2 kk + h of row ln (+ 32 tm), weight rows 8 h + (lane%16)/4 (+ 16 kk, + 4)
+  const int wr = (lane & 15) >> 2;
+  const int xo = (wm * T::WM + ln) * 128 + ((h ^ xs_swz(ln)) << 4);
+  const int wo = (h * 8 + wr) * 512 + (wn * 16 + (wr << 2) + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) * 16 + (lane & 1) * 8;
+  struct Frags { bf16x8 x[TM]; s16x4 lo[TN], hi[TN]; };
+  constexpr int NR = TM + 2 * TN, NM = TM * TN;   // fragment reads and MFMAs of a k-step
+  // fragment read i, in the order the MFMAs of the step need them: k-step xkk of the X stage at xat, wkk of the weights at wat
+  auto read_frag = [&](Frags &f, int xat, int xkk, int wat, int wkk, int i) {
+    if (i >= 2 && i < 2 + TM) {
+      f.x[i - 2] = *reinterpret_cast<const bf16x8 *>(smem + ((xat + xo) ^ (xkk << 5)) + (i - 2) * 4096);
+      return;
+    }
+    const int w = i < 2 ? i : i - TM, tn = w / 2;
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + ((wat + wo) ^ (tn << 6)) + wkk * 8192 + (w & 1) * 2048));
+    if (w & 1) f.hi[tn] = v; else f.lo[tn] = v;
+  };
+  // the reads of MFMA step i of NM: all of them within the first NM - 2 steps
+  auto read_frags = [&](Frags &f, int xat, int xkk, int wat, int wkk, int i) {
+    constexpr int S = NM - 3;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      if (r * S / NR == i) read_frag(f, xat, xkk, wat, wkk, r);
+  };
+  f32x16 acc[TN][TM];
+  auto mma = [&](const Frags &f, int i) {
+    const int tn = i / TM, tm = i % TM;
+    const s16x8 w8 = __builtin_shufflevector(f.lo[tn], f.hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
+    acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), f.x[tm], acc[tn][tm], 0, 0, 0);
+  };
+  int id = blockIdx.x;
+  request_x(id);
+  request_w(id);
+  load_x(xs[0], 0); load_x(xs[0], 1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {   // X 0b W 0 | X 1a W 1 | X 1b W 2 | X 2a W 3
+    if (i & 1) xbase += 128;
+    load_x(xs[(i + 1) / 2], i & 1 ? 0 : 2); load_x(xs[(i + 1) / 2], i & 1 ? 1 : 3);
+    load_w(ws[i], 0); load_w(ws[i], 1);
+    wbase += wstep;
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kSet) : "memory");
+  Frags f0, f1;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) read_frag(f0, xs[0], 0, ws[0], 0, i);
+  int loose = 0;   // half steps of this tile that wait for loads older than the stores of the tile before
+  for (;;) {
+    now = next;
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[tn][tm][r] = 0.f;
+#pragma unroll 1
+    for (int s = 0; s < nk; ++s) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {   // half step 2 s + p
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+          read_frags(f1, xs[0], 2 * p + 1, ws[0], 1, i);
+          mma(f0, i);
+          if (i == NM - 3) {
+            if (2 * s + p < loose) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * kSet + Epi::kStores) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * kSet) : "memory");
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (p == 0) { if (s == nk - 2) request_w(id + gridDim.x); }
+        else if (s == nk - 3) request_x(id + gridDim.x);
+        else xbase += 128;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+          read_frags(f0, p ? xs[1] : xs[0], p ? 0 : 2, ws[1], 0, i);
+          if (i % 2 == 1) {
+            const int l = i / 2;
+            if (l >= 2) load_w(ws[0], l - 2);
+            else if (p == 0) load_x(xs[2], 2 + l);
+            else if (s + 1 < nk) load_x(xs[0], l);   // the last one: behind the epilogue
+          }
+          mma(f1, i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        wbase += wstep;
+        const int w0 = ws[0];
+        ws[0] = ws[1]; ws[1] = ws[2]; ws[2] = ws[3]; ws[3] = w0;
+      }
+      const int x0 = xs[0];
+      xs[0] = xs[1]; xs[1] = xs[2]; xs[2] = x0;
+    }
+    asm volatile("" ::: "memory");
+    epi(now, acc, smem + xs[2] + wave * 4096);
+    id += gridDim.x;
+    if (id >= ntiles) break;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    load_x(xs[2], 0); load_x(xs[2], 1);
+    loose = 3;
+    if constexpr (Epi::kReread) {   // the fragments that the last half step has read gave their registers to the epilogue
+#pragma unroll
+      for (int i = 0; i < NR; ++i) read_frag(f0, xs[0], 0, ws[0], 0, i);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // what was requested behind the last tile still writes LDS
+}
+
 template <class T>
 __device__ __forceinline__ void zero_acc(f32x16 (&acc)[T::TN][T::TM]) {
 #pragma unroll
@@ -283,9 +509,9 @@ __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d) {
 // the x-th eighth of that order: the 32 workgroups that run together on an XCD then form one block,
 // share 8 X strips and 4 weight strips (every operand slice fetched into the L2 is used 4 or 8 times),
 // whatever the numbers of row strips and column tiles are.  Edge blocks are simply smaller.
-__device__ __forceinline__ void tile_of_block(int ntn, int ntm, int &mt, int &nt) {
+__device__ __forceinline__ void tile_of_id(int id, int ntn, int ntm, int &mt, int &nt) {
   constexpr int RB = 8, PW = 4;
-  const int nblk = ntn * ntm, id = blockIdx.x, per = nblk / 8;
+  const int nblk = ntn * ntm, per = nblk / 8;
   const int pos = id < per * 8 ? (id % 8) * per + id / 8 : id;   // the last nblk % 8 tiles keep their place
   const int band = pos / (RB * ntn);
   int rem = pos - band * RB * ntn;
@@ -294,6 +520,48 @@ __device__ __forceinline__ void tile_of_block(int ntn, int ntm, int &mt, int &nt
   rem -= panel * h * PW;
   mt = band * RB + rem % h;
   nt = panel * PW + rem / h;
+}
+__device__ __forceinline__ void tile_of_block(int ntn, int ntm, int &mt, int &nt) { tile_of_id(blockIdx.x, ntn, ntm, mt, nt); }
+
+// ---- epilogue of a stream's tile ----------------------------------------------------------------
+// A wave rounds its 64 x 128 part to bf16 and writes it through its 4 KiB of scratch, 32 rows x 64 columns at a time (in the
+// accumulator layout a lane owns 4 consecutive columns of one row: stores would be 8 bytes wide): 16-byte stores, eight
+// lanes per 128 bytes of a row.  Chunk c of row r sits in slot c ^ (r % 8).  Rows past the end are beyond `bytes`.
+constexpr int kStreamStores = 16;
+// The lane, in a form that keeps what the compiler derives from it inside the epilogue: hoisted out of the loop over tiles,
+// addresses of a few instructions each took the registers of the main loop (30 spills).
+__device__ __forceinline__ int epilogue_lane() {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+// columns 64 tp .. of the wave to `base` (row 0 of the tile, first of the 64 columns); also(r, v) gets row r of the tile's wave
+template <class Also>
+__device__ __forceinline__ void store_columns(const f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], int tp, char *st, bf16 *base, unsigned bytes,
+                                              int ld, const Also &also) {
+  typedef StreamLoop T;
+  const int lane = epilogue_lane(), ln = lane & 31, h = lane >> 5;
+  const int wm = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / T::WGN;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
+  const unsigned voff = (unsigned)((wm * T::WM + (lane >> 3)) * ld + (lane & 7) * 8) * 2;
+#pragma unroll
+  for (int tm = 0; tm < T::TM; ++tm) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        const f32x16 &v = acc[tp * 2 + q][tm];
+        *reinterpret_cast<bf16x4 *>(st + ln * 128 + (((q * 4 + rq) ^ (ln & 7)) << 4) + h * 8) = pack4(v[rq * 4], v[rq * 4 + 1], v[rq * 4 + 2], v[rq * 4 + 3]);
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = i * 8 + (lane >> 3);
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(st + r * 128 + (((lane & 7) ^ (r & 7)) << 4));
+      __builtin_amdgcn_raw_buffer_store_b128(v, rs, voff + (tm * 32 + i * 8) * ld * 2, 0, 0);
+      also(tm * 32 + r, v);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // ---- epilogue of the 256 x 256 tile through LDS -------------------------------------------------
@@ -310,19 +578,6 @@ __device__ __forceinline__ int out_lds_offset(int tm, int tn, int rq) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % T::WGN, wm = wave / T::WGN;
   return out_chunk(wm * T::WM + tm * 32 + (lane & 31), (wn * T::WN + tn * 32) / 8 + rq) + (lane >> 5) * 8;
-}
-
-template <class T>
-__device__ __forceinline__ void tile_to_lds(const f32x16 (&acc)[T::TN][T::TM], char *smem) {
-  static_assert(T::BM == 256 && T::BN == 256, "epilogue staging");
-#pragma unroll
-  for (int tm = 0; tm < T::TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < T::TN; ++tn)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq)
-        *reinterpret_cast<bf16x4 *>(smem + out_lds_offset<T>(tm, tn, rq)) =
-            pack4(acc[tn][tm][rq * 4], acc[tn][tm][rq * 4 + 1], acc[tn][tm][rq * 4 + 2], acc[tn][tm][rq * 4 + 3]);
 }
 
 // calls f(row, chunk, value) for every 16-byte chunk (8 columns) of the staged tile: 32 lanes per row
@@ -363,22 +618,13 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
   const int m0 = mt * T::BM;
   f32x16 acc[T::TN][T::TM];
   zero_acc<T>(acc);
-  // positions of this lane's rows: asked for before the main loop (a tile of Q or K rotates by them right
-  // after it: 0.8 us of load latency per tile otherwise), not at all by the big tiles that do not rotate
+  // positions of this lane's rows: asked for before the main loop (0.8 us of load latency per tile otherwise)
   const bool rotate = a.rope != nullptr && seg < 2;
-  constexpr bool kBig = T::BM == 256 && T::BN == 256;
   int pos_of[T::TM];
-  if (rotate || !kBig) {
 #pragma unroll
-    for (int tm = 0; tm < T::TM; ++tm)
-      pos_of[tm] = a.pos[min(m0 + (int)(threadIdx.x >> 6) / T::WGN * T::WM + tm * 32 + (int)(threadIdx.x & 31), a.M - 1)];
-  }
-  if constexpr (kBig) {
-    gemm_mainloop_big<T>(a.x + (int64_t)m0 * a.lda, a.lda, a.M - m0, weight_tile(a.w[seg] + n_glob, a.width[seg]), a.K, smem, acc,
-                      NoTail{});
-  } else {
-    gemm_mainloop<T>(a.x, a.lda, a.M, m0, a.w[seg], a.width[seg], n_glob, a.K, smem, acc);
-  }
+  for (int tm = 0; tm < T::TM; ++tm)
+    pos_of[tm] = a.pos[min(m0 + (int)(threadIdx.x >> 6) / T::WGN * T::WM + tm * 32 + (int)(threadIdx.x & 31), a.M - 1)];
+  gemm_mainloop<T>(a.x, a.lda, a.M, m0, a.w[seg], a.width[seg], n_glob, a.K, smem, acc);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % T::WGN, wm = wave / T::WGN;
@@ -386,48 +632,6 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
   const int half = a.dh / 2;
   bf16 *cache = seg == 1 ? a.kcache : (seg == 2 ? a.ccache : nullptr);
   const int width = a.width[seg];
-  if constexpr (kBig) {
-    if (rotate) {
-      // wave tile = one head: column j pairs with j + d_h/2.  16 groups of 4 pairs per lane (2 row blocks x
-      // 2 column blocks x 4 register quads); the table values of a group are asked for two groups ahead of
-      // their use (one after the other, every group would wait out a whole memory round trip: 9 us per tile with
-      // four row blocks)
-      constexpr int tiles_half = kHeadDim / 64;
-      static_assert(T::TN == 2 * tiles_half, "a wave tile of the rotating segments is one head wide");
-      constexpr int G = T::TM * tiles_half * 4, AHEAD = 2;
-      bool rot[T::TM];
-      const float2 *trow[T::TM];
-#pragma unroll
-      for (int tm = 0; tm < T::TM; ++tm) {
-        const int m = m0 + wm * T::WM + tm * 32 + (lane & 31), p = pos_of[tm];
-        rot[tm] = m < a.M && (a.rope_by_token || p < a.max_len);
-        // rows that do not rotate read row 0 of the table and keep their values
-        trow[tm] = a.rope + (int64_t)(rot[tm] ? (a.rope_by_token ? m : p) : 0) * half + (lane >> 5) * 4;
-      }
-      float4 tv[AHEAD + 1][2];
-      auto ask = [&](int g) {
-        const int tm = g / (tiles_half * 4), tn = (g / 4) % tiles_half, rq = g % 4;
-        const float4 *tp = reinterpret_cast<const float4 *>(trow[tm] + tn * 32 + rq * 8);
-        tv[g % (AHEAD + 1)][0] = tp[0]; tv[g % (AHEAD + 1)][1] = tp[1];
-      };
-#pragma unroll
-      for (int g = 0; g < AHEAD; ++g) ask(g);
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        if (g + AHEAD < G) ask(g + AHEAD);
-        const int tm = g / (tiles_half * 4), tn = (g / 4) % tiles_half, rq = g % 4, tn_hi = tn + tiles_half;
-        const float4 t0 = tv[g % (AHEAD + 1)][0], t1 = tv[g % (AHEAD + 1)][1];
-        const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float lo = acc[tn][tm][rq * 4 + i], hi = acc[tn_hi][tm][rq * 4 + i];
-          acc[tn][tm][rq * 4 + i] = rot[tm] ? lo * cs[i] - hi * sn[i] : lo;
-          acc[tn_hi][tm][rq * 4 + i] = rot[tm] ? hi * cs[i] + lo * sn[i] : hi;
-        }
-      }
-    }
-  }
-  if constexpr (!kBig)
 #pragma unroll
   for (int tm = 0; tm < T::TM; ++tm) {
     const int m = m0 + wm * T::WM + tm * 32 + (lane & 31);
@@ -477,39 +681,13 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
         if (crow) *reinterpret_cast<bf16x4 *>(crow + n) = v;
       }
   }
-  if constexpr (kBig) {
-    tile_to_lds<T>(acc, smem);
-    // cache row of every tile row (or -1), looked up once and shared through LDS
-    int64_t *crow_of = reinterpret_cast<int64_t *>(smem + kOutBytes);
-    if (cache && threadIdx.x < 256) {
-      const int m = m0 + (int)threadIdx.x;
-      int64_t cr = -1;
-      if (m < a.M) {
-        const int p = a.pos[m], b = a.seq_id[m];
-        const int slot = a.slots ? a.slots[b] : b;
-        if (slot >= 0 && slot < a.max_batch && p >= 0 && p < a.max_seq) cr = cache_row(a.pm, a.max_seq, slot, p);
-      }
-      crow_of[threadIdx.x] = cr;
-    }
-    __syncthreads();
-    bf16 *dst = a.dst[seg] + n_glob;
-    for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
-      const int m = m0 + r;
-      if (m >= a.M) return;
-      *reinterpret_cast<u32x4 *>(dst + (int64_t)m * width + ch * 8) = v;
-      if (cache) {
-        const int64_t cr = crow_of[r];
-        if (cr >= 0) *reinterpret_cast<u32x4 *>(cache + cr * width + n_glob + ch * 8) = v;
-      }
-    });
-  }
 }
 
 // ---- projection against packed weights -----------------------------------------------------------
 // The four weight matrices are first copied side by side into one [H, Wtot] matrix, so that a
 // 256-column tile may straddle Q | K | C | gate: this serves output widths that are multiples of 64
 // but not of 256 (heads of 64, a single shared key).  Columns are routed to their outputs per
-// 64-column group for RoPE (a head never straddles a group) and per 16-byte chunk for the stores.
+// 64-column group (a head never straddles one).
 // The packed row is padded with zero columns to a multiple of 256 (wpad); the last tile computes
 // them and stores nothing for them.
 __global__ void pack_weights_kernel(ProjArgs a, int wtot, int wpad, bf16 *dst) {
@@ -526,82 +704,107 @@ __global__ void pack_weights_kernel(ProjArgs a, int wtot, int wpad, bf16 *dst) {
   *reinterpret_cast<u32x4 *>(dst + i * 8) = v;
 }
 
-template <class T, int DH>
-__global__ __launch_bounds__(T::NT) void proj_packed_kernel(ProjArgs a, const bf16 *wpack, int wpad) {
-  static_assert(T::BM == 256 && T::BN == 256 && T::WN == 128 && (DH == 64 || DH == 128), "tile");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2], wtot = b3 + a.width[3];
-  int mt, nt;
-  tile_of_block(wpad / T::BN, (a.M + T::BM - 1) / T::BM, mt, nt);
-  const int m0 = mt * T::BM, n0 = nt * T::BN;
-  f32x16 acc[T::TN][T::TM];
-  zero_acc<T>(acc);
-  {
-    gemm_mainloop_big<T>(a.x + (int64_t)m0 * a.lda, a.lda, a.M - m0, weight_tile(wpack + n0, wpad), a.K, smem, acc, NoTail{});
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wn = wave % T::WGN, wm = wave / T::WGN;
-  if (a.rope && n0 < b2) {   // the tile holds q or k columns
-    constexpr int half = DH / 2, tiles_half = DH / 64, tiles_head = DH / 32;
+// ---- both projections as streams of tiles --------------------------------------------------------
+// PACKED: weights from wpack (rows of wpad columns), else from the four matrices (widths multiples of 256).  A group of 64
+// columns lies in one of Q | K | C | gate, whole heads in a wave's 128 columns.
+template <int DH, bool PACKED>
+struct ProjStreamEpi {
+  static constexpr int kStores = kStreamStores;
+  static constexpr bool kReread = true;
+  __device__ __forceinline__ void operator()(TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
+    typedef StreamLoop T;
+    // the kernel's first argument, read where it is used: held over the main loop it takes more scalar registers than there are
+    typedef const __attribute__((address_space(4))) ProjArgs KernelArgs;
+    KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const KernelArgs &a = *args;
+    const int lane = epilogue_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % T::WGN, wm = wave / T::WGN;
+    const int m0 = t.m * T::BM, n0 = t.n * T::BN + wn * T::WN;   // first row of the tile, first column of the wave
+    const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2], wtot = b3 + a.width[3];
+    if (a.rope && n0 < b2) {   // q or k columns: column j of a head pairs with j + DH/2
+      constexpr int half = DH / 2, tiles_half = DH / 64, tiles_head = DH / 32, heads = T::WN / DH;
+      constexpr int G = T::TM * tiles_half * 4, AHEAD = 2;   // groups of 4 columns; table values asked for AHEAD groups early
+      bool rot[T::TM];
+      const float2 *trow[T::TM];
 #pragma unroll
-    for (int tm = 0; tm < T::TM; ++tm) {
-      const int m = m0 + wm * T::WM + tm * 32 + (lane & 31);
-      const int p = a.rope_by_token ? min(m, a.M - 1) : max(min(a.pos[min(m, a.M - 1)], a.max_len - 1), 0);   // RoPE table row
+      for (int tm = 0; tm < T::TM; ++tm) {
+        const int m = m0 + wm * T::WM + tm * 32 + (lane & 31), mc = min(m, a.M - 1);
+        const int p = a.rope_by_token ? mc : a.pos[mc];
+        // a row that does not rotate takes row 0 of the table and keeps its values
+        rot[tm] = PACKED || a.rope_by_token || p < a.max_len;
+        trow[tm] = a.rope + (int64_t)(a.rope_by_token ? p : PACKED ? max(min(p, a.max_len - 1), 0) : rot[tm] ? p : 0) * half + (lane >> 5) * 4;
+      }
+      float4 tv[AHEAD + 1][2];
+      auto ask = [&](int g) {
+        const float4 *tp = reinterpret_cast<const float4 *>(trow[g / (tiles_half * 4)] + (g / 4) % tiles_half * 32 + g % 4 * 8);
+        tv[g % (AHEAD + 1)][0] = tp[0]; tv[g % (AHEAD + 1)][1] = tp[1];
+      };
 #pragma unroll
-      for (int tn = 0; tn < T::TN; ++tn) {
-        if ((tn % tiles_head) >= tiles_half) continue;
-        const int tn_hi = tn + tiles_half;
-        if (tn_hi >= T::TN) continue;
-        // latent and gate columns of a straddling tile take the identity rotation (no branch: the
-        // accumulators stay where they are)
-        const bool rot = n0 + wn * T::WN + tn * 32 < b2;
+      for (int g = 0; g < AHEAD; ++g) ask(g);
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-          const int j = (tn % tiles_head) * 32 + rq * 8 + (lane >> 5) * 4;
-          const float4 *tp = reinterpret_cast<const float4 *>(a.rope + (int64_t)p * half + j);
-          const float4 t0 = tp[0], t1 = tp[1];
-          const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+      for (int g = 0; g < G; ++g) {
+        if (g + AHEAD < G) ask(g + AHEAD);
+        const int tm = g / (tiles_half * 4), rq = g % 4;
+        const float4 t0 = tv[g % (AHEAD + 1)][0], t1 = tv[g % (AHEAD + 1)][1];
+        const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+        for (int hd = 0; hd < heads; ++hd) {
+          const int tn = hd * tiles_head + (g / 4) % tiles_half, tn_hi = tn + tiles_half;
+          const bool turn = n0 + hd * DH < b2 && rot[tm];   // columns behind q and k take the identity
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float c = rot ? cs[i] : 1.f, sv = rot ? sn[i] : 0.f;
+            const float c = turn ? cs[i] : 1.f, sv = turn ? sn[i] : 0.f;
             const float lo = acc[tn][tm][rq * 4 + i], hi = acc[tn_hi][tm][rq * 4 + i];
             acc[tn][tm][rq * 4 + i] = lo * c - hi * sv;
             acc[tn_hi][tm][rq * 4 + i] = hi * c + lo * sv;
           }
         }
+        __builtin_amdgcn_sched_barrier(0);   // else the values of all groups are asked for at once: spills
+      }
+    }
+    // cache rows of the wave's 64 rows, one per lane
+    const bool caches = a.kcache && n0 < b3 && n0 + T::WN > b1;
+    int64_t crow = -1;
+    if (caches) {
+      const int m = m0 + wm * T::WM + lane;
+      if (m < a.M) {
+        const int p = a.pos[m], b = a.seq_id[m];
+        const int slot = a.slots ? a.slots[b] : b;
+        if (slot >= 0 && slot < a.max_batch && p >= 0 && p < a.max_seq) crow = cache_row(PageMap{a.pm.table, a.pm.page_size, a.pm.pages_per_slot, a.pm.num_pages}, a.max_seq, slot, p);
+      }
+    }
+#pragma unroll
+    for (int tp = 0; tp < 2; ++tp) {
+      const int col = n0 + tp * 64;
+      const bool s1 = col >= b1, s2 = col >= b2, s3 = col >= b3;
+      const int lcol = col - (s3 ? b3 : s2 ? b2 : s1 ? b1 : 0), width = s3 ? a.width[3] : s2 ? a.width[2] : s1 ? a.width[1] : a.width[0];
+      bf16 *dst = (s3 ? a.dst[3] : s2 ? a.dst[2] : s1 ? a.dst[1] : a.dst[0]) + (int64_t)m0 * width + lcol;
+      const unsigned bytes = PACKED && col >= wtot ? 0u : (unsigned)((min(a.M - m0, T::BM) - 1) * width * 2) + 128u;   // padding: none
+      if (caches && s1 && !s3) {
+        bf16 *cache = (s2 ? a.ccache : a.kcache) + lcol + (lane & 7) * 8;
+        store_columns(acc, tp, st, dst, bytes, width, [&](int r, u32x4 v) {
+          const int64_t cr = ((int64_t)__shfl((int)(crow >> 32), r) << 32) | (unsigned)__shfl((int)crow, r);
+          if (cr >= 0) *reinterpret_cast<u32x4 *>(cache + cr * width) = v;
+        });
+      } else {
+        store_columns(acc, tp, st, dst, bytes, width, [](int, u32x4) {});
       }
     }
   }
-  tile_to_lds<T>(acc, smem);
-  int64_t *crow_of = reinterpret_cast<int64_t *>(smem + kOutBytes);
-  if (a.kcache && threadIdx.x < 256) {
-    const int m = m0 + (int)threadIdx.x;
-    int64_t cr = -1;
-    if (m < a.M) {
-      const int p = a.pos[m], b = a.seq_id[m];
-      const int slot = a.slots ? a.slots[b] : b;
-      if (slot >= 0 && slot < a.max_batch && p >= 0 && p < a.max_seq) cr = cache_row(a.pm, a.max_seq, slot, p);
-    }
-    crow_of[threadIdx.x] = cr;
-  }
-  __syncthreads();
-  // a thread stores the same 16-byte chunk column of every row: its destination is fixed
-  const int gcol = n0 + (threadIdx.x & 31) * 8;
-  if (gcol >= wtot) return;        // zero padding of the packed row; no barrier follows
-  const int seg = (gcol >= b1) + (gcol >= b2) + (gcol >= b3);
-  const int lcol = gcol - (seg == 0 ? 0 : seg == 1 ? b1 : seg == 2 ? b2 : b3);
-  const int width = a.width[seg];
-  bf16 *dst = a.dst[seg] + lcol;
-  bf16 *cache = !a.kcache ? nullptr : seg == 1 ? a.kcache + lcol : seg == 2 ? a.ccache + lcol : nullptr;
-  for_each_out_chunk<T::NT>(smem, [&](int r, int, u32x4 v) {
-    const int m = m0 + r;
-    if (m >= a.M) return;
-    *reinterpret_cast<u32x4 *>(dst + (int64_t)m * width) = v;
-    if (cache) {
-      const int64_t cr = crow_of[r];
-      if (cr >= 0) *reinterpret_cast<u32x4 *>(cache + cr * width) = v;
-    }
-  });
+};
+
+template <int DH, bool PACKED>
+__global__ __launch_bounds__(StreamLoop::NT) void proj_stream_kernel(ProjArgs a, const bf16 *wpack, int wpad, StreamOrder order) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  typedef StreamLoop T;
+  gemm_stream(order, a.lda, a.K, smem, [&](TileAt t) {
+    const int m0 = t.m * T::BM, n0 = t.n * T::BN;
+    if constexpr (PACKED) return StreamTile{a.x + (int64_t)m0 * a.lda, a.M - m0, weight_tile(wpack + n0, wpad)};
+    const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2];
+    const bool s1 = n0 >= b1, s2 = n0 >= b2, s3 = n0 >= b3;
+    const int lcol = n0 - (s3 ? b3 : s2 ? b2 : s1 ? b1 : 0), width = s3 ? a.width[3] : s2 ? a.width[2] : s1 ? a.width[1] : a.width[0];
+    return StreamTile{a.x + (int64_t)m0 * a.lda, a.M - m0, weight_tile((s3 ? a.w[3] : s2 ? a.w[2] : s1 ? a.w[1] : a.w[0]) + lcol, width)};
+  }, ProjStreamEpi<DH, PACKED>{});
 }
 
 // ------------------------------------------------------------------------------ value decoder
@@ -803,19 +1006,7 @@ __global__ __launch_bounds__(T::NT) void plain_gemm_kernel(PlainArgs a) {
   const int m0 = mt * T::BM, n0 = nt * T::BN;
   f32x16 acc[T::TN][T::TM];
   zero_acc<T>(acc);
-  if constexpr (T::BM == 256 && T::BN == 256) {
-    gemm_mainloop_big<T>(a.A + (int64_t)m0 * a.lda, a.lda, a.M - m0, weight_tile(a.B + n0, a.N), a.K, smem, acc, NoTail{});
-  } else {
-    gemm_mainloop<T>(a.A, a.lda, a.M, m0, a.B, a.N, n0, a.K, smem, acc);
-  }
-  if constexpr (T::BM == 256 && T::BN == 256) {
-    tile_to_lds<T>(acc, smem);
-    __syncthreads();
-    for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
-      if (m0 + r < a.M) *reinterpret_cast<u32x4 *>(a.C + (int64_t)(m0 + r) * a.N + n0 + ch * 8) = v;
-    });
-    return;
-  }
+  gemm_mainloop<T>(a.A, a.lda, a.M, m0, a.B, a.N, n0, a.K, smem, acc);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % T::WGN, wm = wave / T::WGN;
 #pragma unroll
@@ -831,6 +1022,28 @@ __global__ __launch_bounds__(T::NT) void plain_gemm_kernel(PlainArgs a) {
             pack4(acc[tn][tm][rq * 4], acc[tn][tm][rq * 4 + 1], acc[tn][tm][rq * 4 + 2], acc[tn][tm][rq * 4 + 3]);
       }
   }
+}
+
+struct PlainStreamEpi {
+  static constexpr int kStores = kStreamStores;
+  static constexpr bool kReread = false;
+  const PlainArgs &a;
+  __device__ __forceinline__ void operator()(TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
+    typedef StreamLoop T;
+    const int wn = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % T::WGN;
+    bf16 *base = a.C + (int64_t)t.m * T::BM * a.N + t.n * T::BN + wn * T::WN;
+    const unsigned bytes = (unsigned)((min(a.M - t.m * T::BM, T::BM) - 1) * a.N * 2) + 128u;
+    store_columns(acc, 0, st, base, bytes, a.N, [](int, u32x4) {});
+    store_columns(acc, 1, st, base + 64, bytes, a.N, [](int, u32x4) {});
+  }
+};
+
+__global__ __launch_bounds__(StreamLoop::NT) void plain_stream_kernel(PlainArgs a, StreamOrder order) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  typedef StreamLoop T;
+  gemm_stream(order, a.lda, a.K, smem, [&](TileAt t) {
+    return StreamTile{a.A + (int64_t)t.m * T::BM * a.lda, a.M - t.m * T::BM, weight_tile(a.B + t.n * T::BN, a.N)};
+  }, PlainStreamEpi{a});
 }
 
 // ------------------------------------------------------------------------------ decode projection
@@ -883,6 +1096,14 @@ typedef GemmTile<256, 256, 64, 4, 2> TileBig;    // eight waves, wave tile 64(m)
 typedef GemmTile<256, 256, 64, 2, 2> TileBig4;   // four waves of 128 x 128 (plain main loop)
 typedef GemmTile<256, 128, 64, 4, 1> TileHead;   // one 128-wide head per workgroup, wave tile 64(m) x 128(n)
 typedef GemmTile<256, 64, 64, 4, 1> TileHead64;  // one 64-wide head per workgroup, wave tile 64(m) x 64(n)
+
+// one workgroup per CU, or per tile where there are fewer
+template <class K, class... Args>
+void launch_stream(K kernel, int M, int N, hipStream_t st, const Args &...args) {
+  const StreamOrder o = stream_order(N / StreamLoop::BN, (M + StreamLoop::BM - 1) / StreamLoop::BM);
+  allow_dynamic_lds((const void *)kernel, StreamLoop::SMEM);
+  kernel<<<std::min(o.tiles(), 256), StreamLoop::NT, StreamLoop::SMEM, st>>>(args..., o);
+}
 
 template <class T, class K, class Args>
 void launch(K kernel, const Args &a, int ntiles, hipStream_t st) {
@@ -957,19 +1178,14 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
   }
   if (short_gemm_ok(M, d.wtot)) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
   if (proj_direct_big(d)) {
-    const int nt = (d.wtot / 256) * ((M + 255) / 256);
-    launch<TileBig>(proj_gemm_kernel<TileBig>, a, nt, st);
+    launch_stream(proj_stream_kernel<128, false>, M, d.wtot, st, a, (const bf16 *)nullptr, 0);
   } else if (proj_packed_ok(d)) {
     bf16 *wpack = (bf16 *)ws.wpack;
     const int wpad = proj_packed_width(d);
     const int64_t chunks = (int64_t)d.H * (wpad / 8);
     pack_weights_kernel<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(a, d.wtot, wpad, wpack);
-    const int nt = (wpad / 256) * ((M + 255) / 256);
-    const int which = d.dh == 64 ? 0 : 1;
-    allow_dynamic_lds(which == 0 ? (const void *)proj_packed_kernel<TileBig, 64> : (const void *)proj_packed_kernel<TileBig, 128>,
-                      TileBig::SMEM);
-    if (which == 0) proj_packed_kernel<TileBig, 64><<<nt, TileBig::NT, TileBig::SMEM, st>>>(a, wpack, wpad);
-    else proj_packed_kernel<TileBig, 128><<<nt, TileBig::NT, TileBig::SMEM, st>>>(a, wpack, wpad);
+    if (d.dh == 64) launch_stream(proj_stream_kernel<64, true>, M, wpad, st, a, (const bf16 *)wpack, wpad);
+    else launch_stream(proj_stream_kernel<128, true>, M, wpad, st, a, (const bf16 *)wpack, wpad);
   } else {
     const int nt = (d.wtot / 128) * ((M + 255) / 256);
     launch<TileHead>(proj_gemm_kernel<TileHead>, a, nt, st);
@@ -1040,7 +1256,9 @@ void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const vo
     return;
   }
   if (short_gemm_ok(M, N)) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
-  if (N % 256 == 0 && K % 128 == 0 && K >= 256) launch<TileBig>(plain_gemm_kernel<TileBig>, a, (N / 256) * ((M + 255) / 256), st);
+  if (N % 256 == 0 && K % 128 == 0 && K >= 256) {
+    launch_stream(plain_stream_kernel, M, N, st, a);
+  }
   else launch<TileHead>(plain_gemm_kernel<TileHead>, a, (N / 128) * ((M + 255) / 256), st);
 }
 
