@@ -265,43 +265,66 @@ __device__ __forceinline__ void gemm_mainloop_big(const bf16 *__restrict__ Abase
 // one block of 8 strips of X x 4 of the weights.  Panels of 7 where 7 divides the columns were slower (projections
 // 16384 x 2048 x 3584 224 -> 228 us, 121600 x 4096 x 7168 5.96 -> 6.23 ms), 3 + 2 columns of 5 too (65536 x 1280 x 1280 196
 // -> 199).  The divisors are known to the host.
+// Up to 128 tiles behind the last whole round of 256 are shared by two workgroups of the XCD, 128 rows each: half a tile takes
+// about 0.7 of the time of a whole one, and the CUs that would have had none take part (projections 16384 x 2048 x 3584, three and
+// a half rounds, 211 -> 203 us; 6500 x 2048 x 3584, 1.4, 99 -> 91; W_O 16384 x 1280 x 1280, 1.25, 59 -> 54).
+constexpr int kStreamGroups = 256;   // workgroups of a launch: one per CU
 struct Divisor { unsigned magic; int d; };
-inline Divisor divisor(int d) { return Divisor{d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u, d}; }
-__device__ __forceinline__ int quotient(int x, const Divisor &v) {   // x >= 0; the product is at most one too many
-  const int q = v.magic ? (int)__umulhi((unsigned)x, v.magic) : x;
-  return q * v.d > x ? q - 1 : q;
+inline Divisor divisor(int d) { return Divisor{0xffffffffu / (unsigned)d, d}; }
+__device__ __forceinline__ int quotient(int x, Divisor v) {   // x >= 0; the product is at most one too few
+  const int q = (int)__umulhi((unsigned)x, v.magic);
+  return x - q * v.d >= v.d ? q + 1 : q;
 }
 struct StreamOrder {
   static constexpr int kBand = 8, kPanel = 4;
-  int ntn, ntm, w;
+  int ntn, ntm;
+  int rounds, halves;   // whole rounds of 256 tiles; tiles behind them that two workgroups share (else: workgroups with one more)
   Divisor band, panel, panel_end, width, width_end;   // tiles of a band, of a panel (and in the last band), columns of a panel (and of the last)
   int tiles() const { return ntn * ntm; }
+  // half tiles: id (r & 7) + 16 (r >> 3) + 8 half takes half of tile r
+  int workgroups() const { return rounds ? std::min(std::max(tiles(), 1), kStreamGroups) : (halves + 7) / 8 * 16; }
 };
 inline StreamOrder stream_order(int ntn, int ntm) {
   StreamOrder o;
   o.ntn = ntn; o.ntm = ntm;
   const int np = ntn <= StreamOrder::kPanel + 1 ? 1 : (ntn + StreamOrder::kPanel - 1) / StreamOrder::kPanel;
-  o.w = (ntn + np - 1) / np;
-  const int end = ntm % StreamOrder::kBand ? ntm % StreamOrder::kBand : StreamOrder::kBand, last = ntn - (ntn - 1) / o.w * o.w;
+  const int w = (ntn + np - 1) / np;
+  const int end = ntm % StreamOrder::kBand ? ntm % StreamOrder::kBand : StreamOrder::kBand, last = ntn - (ntn - 1) / w * w;
   o.band = divisor(StreamOrder::kBand * ntn);
-  o.panel = divisor(StreamOrder::kBand * o.w);
-  o.panel_end = divisor(end * o.w);
-  o.width = divisor(o.w);
+  o.panel = divisor(StreamOrder::kBand * w);
+  o.panel_end = divisor(end * w);
+  o.width = divisor(w);
   o.width_end = divisor(last);
+  const int rem = o.tiles() % kStreamGroups;
+  o.halves = rem <= kStreamGroups / 2 ? rem : 0;
+  o.rounds = o.tiles() / kStreamGroups + (rem > o.halves ? 1 : 0);
   return o;
 }
-struct TileAt { int m, n; };
-__device__ __forceinline__ TileAt tile_at(const StreamOrder &o, int id) {
+struct TileAt { int m0, nt; };   // first row, column tile
+__device__ __forceinline__ TileAt tile_at(const StreamOrder &order, int id) {
+  const StreamOrder o = order;   // one round of scalar loads, no branches
   const int nblk = o.ntn * o.ntm, per = nblk >> 3;
   const int pos = id < per * 8 ? (id & 7) * per + (id >> 3) : id;   // the last nblk % 8 tiles keep their place
   const int band = quotient(pos, o.band), row0 = band * StreamOrder::kBand;
-  int rem = pos - band * o.band.d;
   const bool end = o.ntm - row0 < StreamOrder::kBand;
-  const int panel = end ? quotient(rem, o.panel_end) : quotient(rem, o.panel), col0 = panel * o.w;
-  rem -= panel * (end ? o.panel_end.d : o.panel.d);
-  const bool narrow = o.ntn - col0 < o.w;
-  const int row = narrow ? quotient(rem, o.width_end) : quotient(rem, o.width);
-  return TileAt{row0 + row, col0 + rem - row * (narrow ? o.width_end.d : o.w)};
+  const Divisor pd{end ? o.panel_end.magic : o.panel.magic, end ? o.panel_end.d : o.panel.d};
+  int rem = pos - band * o.band.d;
+  const int panel = quotient(rem, pd), col0 = panel * o.width.d;
+  const bool narrow = o.ntn - col0 < o.width.d;
+  const Divisor wd{narrow ? o.width_end.magic : o.width.magic, narrow ? o.width_end.d : o.width.d};
+  rem -= panel * pd.d;
+  const int row = quotient(rem, wd);
+  return TileAt{(row0 + row) * 256, col0 + rem - row * wd.d};
+}
+
+// The kernel's only argument, read again where this is called: what a tile needs once would, held over the main loop, take
+// more scalar registers than there are.
+template <class A>
+__device__ __forceinline__ const A &kernel_args() {
+  typedef const __attribute__((address_space(4))) A Const;
+  Const *args = (Const *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  return *(const A *)args;
 }
 
 // ---- main loop over a stream of tiles ----------------------------------------------------------
@@ -325,7 +348,8 @@ __device__ __forceinline__ TileAt tile_at(const StreamOrder &o, int id) {
 // Bound: power.  Without loads a half step takes 0.73 us on such data and 0.54 on zeros, the loads alone 0.38; together 0.8 and
 // 0.6 (0.87 and 0.77 in the loop above), of which the matrix instructions are 0.43 at 2.4 GHz.  Against a workgroup per tile on that
 // loop (kernels inside the calls): projection 65536 x 1280 x 1792 334 -> 293 us, W_O 65536 x 1280 x 1280 234 -> 195,
-// projection 16384 x 2048 x 3584 243 -> 221, 6500 x 2048 x 3584 114 -> 110, 121600 x 4096 x 7168 6.10 -> 5.96 ms.
+// projection 16384 x 2048 x 3584 243 -> 221, 6500 x 2048 x 3584 114 -> 110, 121600 x 4096 x 7168 6.10 -> 5.96 ms (5.51 on a
+// day when that took 5.67, with a tile's place worked out in one round of scalar loads and no branches).
 struct StreamTile { const bf16 *A; int rows; WeightTile B; };   // row m0 of the row operand, rows from there, weight columns
 
 struct StreamLoop {
@@ -336,13 +360,14 @@ __device__ __forceinline__ int xs_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); 
 
 // acc[tn][tm][r]:  n = wn*128 + tn*32 + 8*(r/4) + 4*(lane/32) + r%4,  m = wm*64 + tm*32 + lane%32, wn = wave % 2, wm = wave / 2.
 // K a multiple of 128, at least 256.
-template <class Src, class Epi>
-__device__ __forceinline__ void gemm_stream(const StreamOrder &order, int64_t lda, int K, char *smem, const Src &src, const Epi &epi) {
+// Args: the kernel's argument, with the order; src(args, tile), epi(args, blocks of 32 rows of a wave, tile, acc, scratch).
+template <class Args, class Src, class Epi>
+__device__ __forceinline__ void gemm_stream(int64_t lda, int K, char *smem, const Src &src, const Epi &epi) {
   typedef StreamLoop T;
-  constexpr int TM = T::TM, TN = T::TN, kSet = 4;   // load instructions of a wave per half step
+  constexpr int TN = T::TN, kSet = 4;   // load instructions of a wave per half step
   const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % T::WGN, wm = wave / T::WGN;
-  const int nk = K / 64, ntiles = order.ntn * order.ntm;
+  const int nk = K / 64;
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
   // what is requested next.  Rows past the last valid one read as 0, and so does everything behind the last tile.
   // This wave's loads: rows 32 wave + 8 j + lane/8 of an X stage, k-rows 4 wave + 2 j + lane/32 of a weight stage.
@@ -355,18 +380,33 @@ __device__ __forceinline__ void gemm_stream(const StreamOrder &order, int64_t ld
     xv[j] = (unsigned)(r * lda * 2) + ((lane & 7) ^ xs_swz(r)) * 16;
   }
   TileAt now{}, next{};   // the tile that is worked on and the one that is requested
-  auto request_x = [&](int id) {
+  bool any = false;       // is there one?
+  // tile `round` of this workgroup, or half a tile behind the rounds
+  auto request_x = [&](int round) {
+    const Args &args = kernel_args<Args>();
+    const StreamOrder &order = args.order;
     xbytes = 0;
-    if (id >= ntiles) return;
+    int id = blockIdx.x + round * kStreamGroups, half = 0;
+    if (round < order.rounds) any = id < order.ntn * order.ntm;
+    else {
+      const int r = (blockIdx.x & 7) + (blockIdx.x >> 4) * 8;
+      half = (blockIdx.x >> 3) & 1;
+      id = order.rounds * kStreamGroups + r;
+      any = round == order.rounds && r < order.halves;
+    }
+    if (!any) return;
     next = tile_at(order, id);
-    const StreamTile s = src(next);
+    next.m0 += half * (T::BM / 2);
+    const StreamTile s = src(args, next);
+    any = s.rows > 0;
+    if (!any) return;
     xbase = reinterpret_cast<const char *>(s.A);
-    xbytes = (unsigned)((min(s.rows, T::BM) - 1) * lda * 2) + 128u;
+    xbytes = (unsigned)((min(s.rows, round < order.rounds ? T::BM : T::BM / 2) - 1) * lda * 2) + 128u;
   };
-  auto request_w = [&](int id) {
+  auto request_w = [&]() {
     wbytes = 0;
-    if (id >= ntiles) return;
-    const StreamTile s = src(next);
+    if (!any) return;
+    const StreamTile s = src(kernel_args<Args>(), next);
     wbase = reinterpret_cast<const char *>(s.B.base);
     wbytes = s.B.bytes;
     wstep = (int64_t)32 * s.B.ld * 2;
@@ -384,50 +424,45 @@ __device__ __forceinline__ void gemm_stream(const StreamOrder &order, int64_t ld
   auto load_w = [&](int at, int j) { load_to_lds(buffer_of(wbase, wbytes), wv[j], lds0 + at + (wave * 2 + j) * 1024); };
   // fragment addresses: X chunk 2 kk + h of row ln (+ 32 tm), weight rows 8 h + (lane%16)/4 (+ 16 kk, + 4)
   const int wr = (lane & 15) >> 2;
-  const int xo = (wm * T::WM + ln) * 128 + ((h ^ xs_swz(ln)) << 4);
   const int wo = (h * 8 + wr) * 512 + (wn * 16 + (wr << 2) + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) * 16 + (lane & 1) * 8;
-  struct Frags { bf16x8 x[TM]; s16x4 lo[TN], hi[TN]; };
-  constexpr int NR = TM + 2 * TN, NM = TM * TN;   // fragment reads and MFMAs of a k-step
-  // fragment read i, in the order the MFMAs of the step need them: k-step xkk of the X stage at xat, wkk of the weights at wat
-  auto read_frag = [&](Frags &f, int xat, int xkk, int wat, int wkk, int i) {
-    if (i >= 2 && i < 2 + TM) {
-      f.x[i - 2] = *reinterpret_cast<const bf16x8 *>(smem + ((xat + xo) ^ (xkk << 5)) + (i - 2) * 4096);
-      return;
-    }
-    const int w = i < 2 ? i : i - TM, tn = w / 2;
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + ((wat + wo) ^ (tn << 6)) + wkk * 8192 + (w & 1) * 2048));
-    if (w & 1) f.hi[tn] = v; else f.lo[tn] = v;
-  };
-  // the reads of MFMA step i of NM: all of them within the first NM - 2 steps
-  auto read_frags = [&](Frags &f, int xat, int xkk, int wat, int wkk, int i) {
-    constexpr int S = NM - 3;
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-      if (r * S / NR == i) read_frag(f, xat, xkk, wat, wkk, r);
-  };
-  f32x16 acc[TN][TM];
-  auto mma = [&](const Frags &f, int i) {
-    const int tn = i / TM, tm = i % TM;
-    const s16x8 w8 = __builtin_shufflevector(f.lo[tn], f.hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
-    acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), f.x[tm], acc[tn][tm], 0, 0, 0);
-  };
-  int id = blockIdx.x;
-  request_x(id);
-  request_w(id);
-  load_x(xs[0], 0); load_x(xs[0], 1);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {   // X 0b W 0 | X 1a W 1 | X 1b W 2 | X 2a W 3
-    if (i & 1) xbase += 128;
-    load_x(xs[(i + 1) / 2], i & 1 ? 0 : 2); load_x(xs[(i + 1) / 2], i & 1 ? 1 : 3);
-    load_w(ws[i], 0); load_w(ws[i], 1);
-    wbase += wstep;
-  }
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kSet) : "memory");
+  struct Frags { bf16x8 x[T::TM]; s16x4 lo[TN], hi[TN]; };
   Frags f0, f1;
+  f32x16 acc[TN][T::TM];
+  // a tile of TM x 128 rows, whose first fragments are in f0; `loose`: half steps that wait for loads older than the stores of
+  // the tile before
+  auto fragments = [&](auto tm_tag) {   // reads of a k-step: (f, X stage at, its k-step, weights at, their k-step, i)
+    constexpr int TM = decltype(tm_tag)::value;
+    const int xo = (wm * TM * 32 + ln) * 128 + ((h ^ xs_swz(ln)) << 4);
+    return [=](Frags &f, int xat, int xkk, int wat, int wkk, int i) {   // read i, in the order the MFMAs of the step need them
+      if (i >= 2 && i < 2 + TM) {
+        f.x[i - 2] = *reinterpret_cast<const bf16x8 *>(smem + ((xat + xo) ^ (xkk << 5)) + (i - 2) * 4096);
+        return;
+      }
+      const int w = i < 2 ? i : i - TM, tn = w / 2;
+      const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + ((wat + wo) ^ (tn << 6)) + wkk * 8192 + (w & 1) * 2048));
+      if (w & 1) f.hi[tn] = v; else f.lo[tn] = v;
+    };
+  };
+  auto first_fragments = [&](auto tm_tag) {
+    const auto read_frag = fragments(tm_tag);
 #pragma unroll
-  for (int i = 0; i < NR; ++i) read_frag(f0, xs[0], 0, ws[0], 0, i);
-  int loose = 0;   // half steps of this tile that wait for loads older than the stores of the tile before
-  for (;;) {
+    for (int i = 0; i < decltype(tm_tag)::value + 2 * TN; ++i) read_frag(f0, xs[0], 0, ws[0], 0, i);
+  };
+  auto work_tile = [&](auto tm_tag, int round, int loose) {
+    constexpr int TM = decltype(tm_tag)::value;
+    constexpr int NR = TM + 2 * TN, NM = TM * TN;         // fragment reads and MFMAs of a k-step
+    constexpr int READS = NM - 3, MEET = TM == 1 ? 2 : NM - 3;   // the reads go out under the first READS MFMAs; the barrier's place
+    const auto read_frag = fragments(tm_tag);
+    auto read_frags = [&](Frags &f, int xat, int xkk, int wat, int wkk, int i) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        if (r * READS / NR == i) read_frag(f, xat, xkk, wat, wkk, r);
+    };
+    auto mma = [&](const Frags &f, int i) {
+      const int tn = i / TM, tm = i % TM;
+      const s16x8 w8 = __builtin_shufflevector(f.lo[tn], f.hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
+      acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), f.x[tm], acc[tn][tm], 0, 0, 0);
+    };
     now = next;
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
@@ -443,24 +478,25 @@ __device__ __forceinline__ void gemm_stream(const StreamOrder &order, int64_t ld
         for (int i = 0; i < NM; ++i) {
           read_frags(f1, xs[0], 2 * p + 1, ws[0], 1, i);
           mma(f0, i);
-          if (i == NM - 3) {
+          if (i == MEET) {
             if (2 * s + p < loose) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * kSet + Epi::kStores) : "memory");
             else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * kSet) : "memory");
           }
           __builtin_amdgcn_sched_barrier(0);
         }
-        if (p == 0) { if (s == nk - 2) request_w(id + gridDim.x); }
-        else if (s == nk - 3) request_x(id + gridDim.x);
+        if (p == 0) { if (s == nk - 2) request_w(); }
+        else if (s == nk - 3) request_x(round + 1);
         else xbase += 128;
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
           read_frags(f0, p ? xs[1] : xs[0], p ? 0 : 2, ws[1], 0, i);
-          if (i % 2 == 1) {
-            const int l = i / 2;
-            if (l >= 2) load_w(ws[0], l - 2);
-            else if (p == 0) load_x(xs[2], 2 + l);
-            else if (s + 1 < nk) load_x(xs[0], l);   // the last one: behind the epilogue
-          }
+#pragma unroll
+          for (int l = 0; l < 4; ++l)
+            if ((NM == 8 ? 2 * l + 1 : l) == i) {
+              if (l >= 2) load_w(ws[0], l - 2);
+              else if (p == 0) load_x(xs[2], 2 + l);
+              else if (s + 1 < nk) load_x(xs[0], l);   // the last one: behind the epilogue
+            }
           mma(f1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -472,16 +508,37 @@ __device__ __forceinline__ void gemm_stream(const StreamOrder &order, int64_t ld
       xs[0] = xs[1]; xs[1] = xs[2]; xs[2] = x0;
     }
     asm volatile("" ::: "memory");
-    epi(now, acc, smem + xs[2] + wave * 4096);
-    id += gridDim.x;
-    if (id >= ntiles) break;
+    epi(kernel_args<Args>(), tm_tag, now, acc, smem + xs[2] + wave * 4096);
+  };
+  typedef std::integral_constant<int, T::TM> Whole;
+  typedef std::integral_constant<int, T::TM / 2> Half;
+
+  request_x(0);
+  request_w();
+  if (!any) return;
+  load_x(xs[0], 0); load_x(xs[0], 1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {   // X 0b W 0 | X 1a W 1 | X 1b W 2 | X 2a W 3
+    if (i & 1) xbase += 128;
+    load_x(xs[(i + 1) / 2], i & 1 ? 0 : 2); load_x(xs[(i + 1) / 2], i & 1 ? 1 : 3);
+    load_w(ws[i], 0); load_w(ws[i], 1);
+    wbase += wstep;
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kSet) : "memory");
+  const int rounds = kernel_args<Args>().order.rounds;
+  if (rounds) first_fragments(Whole{});
+  else first_fragments(Half{});
+  for (int round = 0;;) {
+    const int loose = round ? 3 : 0;
+    if (round == rounds) { work_tile(Half{}, round, loose); break; }
+    work_tile(Whole{}, round, loose);
+    if (!any) break;
+    ++round;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     load_x(xs[2], 0); load_x(xs[2], 1);
-    loose = 3;
-    if constexpr (Epi::kReread) {   // the fragments that the last half step has read gave their registers to the epilogue
-#pragma unroll
-      for (int i = 0; i < NR; ++i) read_frag(f0, xs[0], 0, ws[0], 0, i);
-    }
+    // the fragments that the last half step has read were those of a whole tile, or gave their registers to the epilogue
+    if (round == rounds) first_fragments(Half{});
+    else if constexpr (Epi::kReread) first_fragments(Whole{});
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // what was requested behind the last tile still writes LDS
 }
@@ -536,16 +593,16 @@ __device__ __forceinline__ int epilogue_lane() {
   return lane;
 }
 // columns 64 tp .. of the wave to `base` (row 0 of the tile, first of the 64 columns); also(r, v) gets row r of the tile's wave
-template <class Also>
+template <int TM, class Also>
 __device__ __forceinline__ void store_columns(const f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], int tp, char *st, bf16 *base, unsigned bytes,
                                               int ld, const Also &also) {
   typedef StreamLoop T;
   const int lane = epilogue_lane(), ln = lane & 31, h = lane >> 5;
   const int wm = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / T::WGN;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
-  const unsigned voff = (unsigned)((wm * T::WM + (lane >> 3)) * ld + (lane & 7) * 8) * 2;
+  const unsigned voff = (unsigned)((wm * TM * 32 + (lane >> 3)) * ld + (lane & 7) * 8) * 2;
 #pragma unroll
-  for (int tm = 0; tm < T::TM; ++tm) {
+  for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -707,28 +764,28 @@ __global__ void pack_weights_kernel(ProjArgs a, int wtot, int wpad, bf16 *dst) {
 // ---- both projections as streams of tiles --------------------------------------------------------
 // PACKED: weights from wpack (rows of wpad columns), else from the four matrices (widths multiples of 256).  A group of 64
 // columns lies in one of Q | K | C | gate, whole heads in a wave's 128 columns.
+struct ProjStream { StreamOrder order; ProjArgs a; const bf16 *wpack; int wpad; };
+
 template <int DH, bool PACKED>
 struct ProjStreamEpi {
   static constexpr int kStores = kStreamStores;
   static constexpr bool kReread = true;
-  __device__ __forceinline__ void operator()(TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
+  template <class Rows>
+  __device__ __forceinline__ void operator()(const ProjStream &args, Rows, TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
     typedef StreamLoop T;
-    // the kernel's first argument, read where it is used: held over the main loop it takes more scalar registers than there are
-    typedef const __attribute__((address_space(4))) ProjArgs KernelArgs;
-    KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args));
-    const KernelArgs &a = *args;
+    const ProjArgs &a = args.a;
     const int lane = epilogue_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % T::WGN, wm = wave / T::WGN;
-    const int m0 = t.m * T::BM, n0 = t.n * T::BN + wn * T::WN;   // first row of the tile, first column of the wave
+    constexpr int TM = Rows::value;
+    const int m0 = t.m0, mw = m0 + wm * TM * 32, n0 = t.nt * T::BN + wn * T::WN;   // first row of the tile and of the wave, first column of the wave
     const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2], wtot = b3 + a.width[3];
     if (a.rope && n0 < b2) {   // q or k columns: column j of a head pairs with j + DH/2
       constexpr int half = DH / 2, tiles_half = DH / 64, tiles_head = DH / 32, heads = T::WN / DH;
-      constexpr int G = T::TM * tiles_half * 4, AHEAD = 2;   // groups of 4 columns; table values asked for AHEAD groups early
-      bool rot[T::TM];
-      const float2 *trow[T::TM];
+      constexpr int G = TM * tiles_half * 4, AHEAD = 2;   // groups of 4 columns; table values asked for AHEAD groups early
+      bool rot[TM];
+      const float2 *trow[TM];
 #pragma unroll
-      for (int tm = 0; tm < T::TM; ++tm) {
-        const int m = m0 + wm * T::WM + tm * 32 + (lane & 31), mc = min(m, a.M - 1);
+      for (int tm = 0; tm < TM; ++tm) {
+        const int mc = min(mw + tm * 32 + (lane & 31), a.M - 1);
         const int p = a.rope_by_token ? mc : a.pos[mc];
         // a row that does not rotate takes row 0 of the table and keeps its values
         rot[tm] = PACKED || a.rope_by_token || p < a.max_len;
@@ -762,12 +819,12 @@ struct ProjStreamEpi {
         __builtin_amdgcn_sched_barrier(0);   // else the values of all groups are asked for at once: spills
       }
     }
-    // cache rows of the wave's 64 rows, one per lane
+    // cache rows of the wave's rows, one per lane
     const bool caches = a.kcache && n0 < b3 && n0 + T::WN > b1;
     int64_t crow = -1;
     if (caches) {
-      const int m = m0 + wm * T::WM + lane;
-      if (m < a.M) {
+      const int m = mw + lane;
+      if (m < a.M && lane < TM * 32) {
         const int p = a.pos[m], b = a.seq_id[m];
         const int slot = a.slots ? a.slots[b] : b;
         if (slot >= 0 && slot < a.max_batch && p >= 0 && p < a.max_seq) crow = cache_row(PageMap{a.pm.table, a.pm.page_size, a.pm.pages_per_slot, a.pm.num_pages}, a.max_seq, slot, p);
@@ -779,31 +836,33 @@ struct ProjStreamEpi {
       const bool s1 = col >= b1, s2 = col >= b2, s3 = col >= b3;
       const int lcol = col - (s3 ? b3 : s2 ? b2 : s1 ? b1 : 0), width = s3 ? a.width[3] : s2 ? a.width[2] : s1 ? a.width[1] : a.width[0];
       bf16 *dst = (s3 ? a.dst[3] : s2 ? a.dst[2] : s1 ? a.dst[1] : a.dst[0]) + (int64_t)m0 * width + lcol;
-      const unsigned bytes = PACKED && col >= wtot ? 0u : (unsigned)((min(a.M - m0, T::BM) - 1) * width * 2) + 128u;   // padding: none
+      const unsigned bytes = PACKED && col >= wtot ? 0u : (unsigned)((min(a.M - m0, TM * 128) - 1) * width * 2) + 128u;   // padding: none
       if (caches && s1 && !s3) {
         bf16 *cache = (s2 ? a.ccache : a.kcache) + lcol + (lane & 7) * 8;
-        store_columns(acc, tp, st, dst, bytes, width, [&](int r, u32x4 v) {
+        store_columns<TM>(acc, tp, st, dst, bytes, width, [&](int r, u32x4 v) {
           const int64_t cr = ((int64_t)__shfl((int)(crow >> 32), r) << 32) | (unsigned)__shfl((int)crow, r);
           if (cr >= 0) *reinterpret_cast<u32x4 *>(cache + cr * width) = v;
         });
       } else {
-        store_columns(acc, tp, st, dst, bytes, width, [](int, u32x4) {});
+        store_columns<TM>(acc, tp, st, dst, bytes, width, [](int, u32x4) {});
       }
     }
   }
 };
 
 template <int DH, bool PACKED>
-__global__ __launch_bounds__(StreamLoop::NT) void proj_stream_kernel(ProjArgs a, const bf16 *wpack, int wpad, StreamOrder order) {
+__global__ __launch_bounds__(StreamLoop::NT) void proj_stream_kernel(ProjStream args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   typedef StreamLoop T;
-  gemm_stream(order, a.lda, a.K, smem, [&](TileAt t) {
-    const int m0 = t.m * T::BM, n0 = t.n * T::BN;
-    if constexpr (PACKED) return StreamTile{a.x + (int64_t)m0 * a.lda, a.M - m0, weight_tile(wpack + n0, wpad)};
+  gemm_stream<ProjStream>(args.a.lda, args.a.K, smem, [](const ProjStream &g, TileAt t) {
+    const ProjArgs &a = g.a;
+    const int n0 = t.nt * T::BN;
+    const bf16 *x = a.x + (int64_t)t.m0 * a.lda;
+    if constexpr (PACKED) return StreamTile{x, a.M - t.m0, weight_tile(g.wpack + n0, g.wpad)};
     const int b1 = a.width[0], b2 = b1 + a.width[1], b3 = b2 + a.width[2];
     const bool s1 = n0 >= b1, s2 = n0 >= b2, s3 = n0 >= b3;
     const int lcol = n0 - (s3 ? b3 : s2 ? b2 : s1 ? b1 : 0), width = s3 ? a.width[3] : s2 ? a.width[2] : s1 ? a.width[1] : a.width[0];
-    return StreamTile{a.x + (int64_t)m0 * a.lda, a.M - m0, weight_tile((s3 ? a.w[3] : s2 ? a.w[2] : s1 ? a.w[1] : a.w[0]) + lcol, width)};
+    return StreamTile{x, a.M - t.m0, weight_tile((s3 ? a.w[3] : s2 ? a.w[2] : s1 ? a.w[1] : a.w[0]) + lcol, width)};
   }, ProjStreamEpi<DH, PACKED>{});
 }
 
@@ -1024,26 +1083,29 @@ __global__ __launch_bounds__(T::NT) void plain_gemm_kernel(PlainArgs a) {
   }
 }
 
+struct PlainStream { StreamOrder order; PlainArgs a; };
+
 struct PlainStreamEpi {
   static constexpr int kStores = kStreamStores;
   static constexpr bool kReread = false;
-  const PlainArgs &a;
-  __device__ __forceinline__ void operator()(TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
+  template <class Rows>
+  __device__ __forceinline__ void operator()(const PlainStream &args, Rows, TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
     typedef StreamLoop T;
+    constexpr int TM = Rows::value;
+    const PlainArgs &a = args.a;
     const int wn = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % T::WGN;
-    bf16 *base = a.C + (int64_t)t.m * T::BM * a.N + t.n * T::BN + wn * T::WN;
-    const unsigned bytes = (unsigned)((min(a.M - t.m * T::BM, T::BM) - 1) * a.N * 2) + 128u;
-    store_columns(acc, 0, st, base, bytes, a.N, [](int, u32x4) {});
-    store_columns(acc, 1, st, base + 64, bytes, a.N, [](int, u32x4) {});
+    bf16 *base = a.C + (int64_t)t.m0 * a.N + t.nt * T::BN + wn * T::WN;
+    const unsigned bytes = (unsigned)((min(a.M - t.m0, TM * 128) - 1) * a.N * 2) + 128u;
+    store_columns<TM>(acc, 0, st, base, bytes, a.N, [](int, u32x4) {});
+    store_columns<TM>(acc, 1, st, base + 64, bytes, a.N, [](int, u32x4) {});
   }
 };
 
-__global__ __launch_bounds__(StreamLoop::NT) void plain_stream_kernel(PlainArgs a, StreamOrder order) {
+__global__ __launch_bounds__(StreamLoop::NT) void plain_stream_kernel(PlainStream args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  typedef StreamLoop T;
-  gemm_stream(order, a.lda, a.K, smem, [&](TileAt t) {
-    return StreamTile{a.A + (int64_t)t.m * T::BM * a.lda, a.M - t.m * T::BM, weight_tile(a.B + t.n * T::BN, a.N)};
-  }, PlainStreamEpi{a});
+  gemm_stream<PlainStream>(args.a.lda, args.a.K, smem, [](const PlainStream &g, TileAt t) {
+    return StreamTile{g.a.A + (int64_t)t.m0 * g.a.lda, g.a.M - t.m0, weight_tile(g.a.B + t.nt * StreamLoop::BN, g.a.N)};
+  }, PlainStreamEpi{});
 }
 
 // ------------------------------------------------------------------------------ decode projection
@@ -1097,12 +1159,11 @@ typedef GemmTile<256, 256, 64, 2, 2> TileBig4;   // four waves of 128 x 128 (pla
 typedef GemmTile<256, 128, 64, 4, 1> TileHead;   // one 128-wide head per workgroup, wave tile 64(m) x 128(n)
 typedef GemmTile<256, 64, 64, 4, 1> TileHead64;  // one 64-wide head per workgroup, wave tile 64(m) x 64(n)
 
-// one workgroup per CU, or per tile where there are fewer
-template <class K, class... Args>
-void launch_stream(K kernel, int M, int N, hipStream_t st, const Args &...args) {
-  const StreamOrder o = stream_order(N / StreamLoop::BN, (M + StreamLoop::BM - 1) / StreamLoop::BM);
+template <class Args>
+void launch_stream(void (*kernel)(Args), Args args, int M, int N, hipStream_t st) {
+  args.order = stream_order(N / StreamLoop::BN, (M + StreamLoop::BM - 1) / StreamLoop::BM);
   allow_dynamic_lds((const void *)kernel, StreamLoop::SMEM);
-  kernel<<<std::min(o.tiles(), 256), StreamLoop::NT, StreamLoop::SMEM, st>>>(args..., o);
+  kernel<<<args.order.workgroups(), StreamLoop::NT, StreamLoop::SMEM, st>>>(args);
 }
 
 template <class T, class K, class Args>
@@ -1178,14 +1239,14 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
   }
   if (short_gemm_ok(M, d.wtot)) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
   if (proj_direct_big(d)) {
-    launch_stream(proj_stream_kernel<128, false>, M, d.wtot, st, a, (const bf16 *)nullptr, 0);
+    launch_stream(proj_stream_kernel<128, false>, ProjStream{{}, a, nullptr, 0}, M, d.wtot, st);
   } else if (proj_packed_ok(d)) {
     bf16 *wpack = (bf16 *)ws.wpack;
     const int wpad = proj_packed_width(d);
     const int64_t chunks = (int64_t)d.H * (wpad / 8);
     pack_weights_kernel<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(a, d.wtot, wpad, wpack);
-    if (d.dh == 64) launch_stream(proj_stream_kernel<64, true>, M, wpad, st, a, (const bf16 *)wpack, wpad);
-    else launch_stream(proj_stream_kernel<128, true>, M, wpad, st, a, (const bf16 *)wpack, wpad);
+    if (d.dh == 64) launch_stream(proj_stream_kernel<64, true>, ProjStream{{}, a, wpack, wpad}, M, wpad, st);
+    else launch_stream(proj_stream_kernel<128, true>, ProjStream{{}, a, wpack, wpad}, M, wpad, st);
   } else {
     const int nt = (d.wtot / 128) * ((M + 255) / 256);
     launch<TileHead>(proj_gemm_kernel<TileHead>, a, nt, st);
@@ -1257,7 +1318,7 @@ void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const vo
   }
   if (short_gemm_ok(M, N)) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
   if (N % 256 == 0 && K % 128 == 0 && K >= 256) {
-    launch_stream(plain_stream_kernel, M, N, st, a);
+    launch_stream(plain_stream_kernel, PlainStream{{}, a}, M, N, st);
   }
   else launch<TileHead>(plain_gemm_kernel<TileHead>, a, (N / 128) * ((M + 255) / 256), st);
 }

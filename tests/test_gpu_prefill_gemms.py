@@ -1,6 +1,6 @@
 """The prefill's GEMMs at the edges of their tiles: the few-row kernel, the 64-row tiles that split K over their waves
 (three stages of 64: contractions of one, two and more) and the 256 x 256 tiles (operands loaded straight into LDS, eight
-waves, four stages of 32).  One valid row in the last row tile and full row tiles, contractions that leave the stages at
+waves; the decoder's in four stages of 32).  One valid row in the last row tile and full row tiles, contractions that leave the stages at
 each phase, two heads side by side in a weight tile, several heads and one, the packed weights, every gate.
 
 Reference: float64 on the same bf16 inputs.  Bounds: the bf16 tolerances of the parity gate, the max-abs one scaled by
@@ -52,6 +52,15 @@ def test_other_gates(layer, rows, gate):
 def test_second_tile_on_a_cu(layer, rows):
     """252 and 280 tiles of 64 x 64, 250 and 260 of 64 x 128 in the projection: two stages a step or one."""
     _check(LAYERS[layer], rows, True)
+
+
+@pytest.mark.parametrize("layer,rows", [("k256", 4993), ("k256", 13057), ("k256", 19457), ("packed", 9345), ("packed", 13825),
+                                        ("ten", 11137)])
+def test_rounds_of_tiles(layer, rows):
+    """256 x 256 tiles on 256 CUs.  100: less than a round, every tile shared by two workgroups; 260: a round and four to
+    share, of the last strip's one row only the first half exists; 385: 129 behind the round are too many to share; 7 columns
+    in panels of 4 and 3, 259 and 385 tiles; 10 columns in panels of 4, 4 and 2, a last band of 4 strips, 440 tiles."""
+    _check(dict(LAYERS, ten=_wl(n_heads=12, latent_dim=512))[layer], rows, True)
 
 
 def _check(wl, rows, gate):
