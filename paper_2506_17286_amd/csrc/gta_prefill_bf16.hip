@@ -9,7 +9,10 @@
 // one, and the steps in which it waits at its barrier, are filled by the other; measured against one workgroup of
 // eight waves and 256 queries: fused kernel of 4 x 4096 tokens with heads of 64 300 -> 270 us, ragged batch of 112 K
 // tokens 18.9 -> 17.95 ms, 4 x 4096 tokens of the 1B shape 231 -> 225 us (whole calls 780 -> 760, 25.1 -> 24.0 ms, 509
-// -> 503).  Wider latents are covered by several workgroups that each recompute the scores.
+// -> 503).  Heads of 64 and latent tiles of 128 take 168 registers, and three workgroups share a CU: with the fused decoder
+// below, 32 x 2048 tokens of 5 maps 316 -> 238 us (two, decoder operands through registers and L through LDS: its epilogue alone took
+// 105), 8 x 800 34 -> 26, 768 wide layer 16 x 1000 42 -> 33.  Wider latents are covered by several workgroups that each
+// recompute the scores.
 // Both products are computed transposed:
 //   S^T[key][query] = K . Q^T      (row operand: K tile from LDS, column operand: the wave's queries,
 //                                   held in 32 registers for the whole kernel)
@@ -26,8 +29,8 @@
 // pair of a query is reduced with v_permlane32_swap, P is packed with v_cvt_pk_bf16_f32 and summed with
 // v_dot2_f32_bf16 (so the row sum is the sum of the rounded values the MFMA sees).
 //
-// Key/latent tiles of 32 rows go from memory straight into LDS (buffer_load_dwordx4 .. lds) through five stages (heads of
-// 128 and latent tiles of 64: three), all but one of them ahead of their use, one barrier per step;
+// Key/latent tiles of 32 rows go from memory straight into LDS (buffer_load_dwordx4 .. lds) through three stages, two of
+// them ahead of their use, one barrier per step;
 // measured against staging through registers and LDS writes: 7 % of the kernel at latents of 1024 and 3 % at 512 (ragged
 // batch of 112 K tokens 19.6 -> 18.6 ms, 4 x 4096 tokens 238 -> 230 us).  Bound: MFMA issue, the LDS reads of the fragments (1 KiB per MFMA) and the softmax arithmetic share the cycles
 // (matrix pipes busy about half of them); latents wider than a tile recompute the scores.  The finished tile is rounded
@@ -75,9 +78,10 @@ struct AttnTile {
   static constexpr int K_INSTR = BK * K_ROW / 1024, C_INSTR = BK * C_ROW / 1024, C_RPI = 1024 / C_ROW;
   static constexpr int K_PITCH = 1024 + 16, C_PITCH = 1024 + 64, C_GROUP = 4 * C_PITCH;
   static constexpr int K_BYTES = K_INSTR * K_PITCH, C_BYTES = C_INSTR / 4 * C_GROUP, TILE = K_BYTES + C_BYTES, STAGE = KS * TILE;
-  // as many stages as leave room for the workgroups the registers allow on a CU: two (five stages), with latent tiles of
-  // 64 four (three: 32 x 2048 tokens, 20 maps, heads and latents of 64: 509 us with five stages, 482 with three)
-  static constexpr int NSTAGE = DH == 64 && DLW == 128 && KS == 1 ? 5 : 3;
+  // as many stages as leave room for the workgroups the registers allow on a CU: two, with latent tiles of 128 and heads of 64
+  // three (32 x 2048 tokens, 5 maps, decoder fused: 246 us with four stages, 238 with three), with latent tiles of 64 four (32 x
+  // 2048 tokens, 20 maps: 509 us with five stages, 482 with three)
+  static constexpr int NSTAGE = 3;
   static constexpr int OUT_PITCH = DLW * 2 + 16;
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int MERGE = KS == 1 ? 0 : QW * (NDLB * 16 + 2) * 256;   // the odd half's accumulators and statistics
@@ -121,18 +125,17 @@ struct AttnArgs {
 // us, 4 x 40 60.2 -> 57.2, 40 behind 1100 of 8192 52.2 -> 50.1, 200 behind 900 of 2048 64.1 -> 62.1)
 __device__ __forceinline__ int splits_of(const AttnArgs &a, int keys) { return max(min((keys + (32 << a.split_shift) - 1) >> (5 + a.split_shift), a.splits), 1); }
 
-// LDS of the fused value decoder: the normalised BQ x DLW tile (row operand) and the DLW x 256 decoder matrices of the
-// group's heads side by side, in halves where two workgroups share a CU; afterwards the BQ x 256 gate / output tile.
+// The fused value decoder: the group's four heads of 64 columns one after the other (two key halves: two each).  The normalised
+// tile stays in registers: its accumulators, rounded, are the column operand as they stand, with k in the order of
+// decoder_frag.  A head's matrix [128, 64] goes straight into LDS, two ahead (two key halves: all four), and a wave's 32 x 64 gate
+// values through 4 KiB of its own, which then take the gated heads on their way to 16-byte stores.
 template <class T>
 struct FusedDecoder {
-  static constexpr int N = 256;                         // heads per group x d_h
-  static constexpr int W_PITCH = N * 2 + 64;            // == 64 mod 256 for the transpose reads
-  static constexpr int W_OFF = T::BQ * T::OUT_PITCH;    // behind the L tile
-  static constexpr int NTN = N / 32 / T::KS;            // 32-column tiles per wave: KS waves share 32 queries
-  static constexpr int G_PITCH = N * 2 + 16;
-  static constexpr int KH = T::KS == 1 ? 2 : 1, KROWS = T::DLW / KH;   // the matrices pass through LDS in KH parts
-  static constexpr int SMEM_LW = W_OFF + KROWS * W_PITCH, SMEM_G = T::BQ * G_PITCH;
-  static constexpr int SMEM = SMEM_LW > SMEM_G ? (SMEM_LW > T::SMEM ? SMEM_LW : T::SMEM) : (SMEM_G > T::SMEM ? SMEM_G : T::SMEM);
+  static constexpr int HEADS = 4, HPW = HEADS / T::KS;          // heads of a group, of a wave
+  static constexpr int W_BYTES = 128 * 128, WBUF = T::KS == 1 ? 2 : HEADS;
+  static constexpr int IO_OFF = WBUF * W_BYTES, L_OFF = IO_OFF + T::NW * 4096;   // two key halves: L of the waves that merged it
+  static constexpr int USED = L_OFF + (T::KS == 1 ? 0 : T::QW * 8192);
+  static constexpr int SMEM = USED > T::SMEM ? USED : T::SMEM;
   static_assert(SMEM <= 160 * 1024, "LDS budget");
 };
 
@@ -284,7 +287,7 @@ __device__ __forceinline__ void commit_chunk(const AttnArgs &a, int b) {
 // CHUNK: keys and latents in the caches.  Fresh prompts have a kernel without that code: in one for both they paid for it (calls of
 // the paper's layers, both and now, 7 x 41..331 tokens 41.8 / 40.1 us, 32 x 20..100 68.6 / 66.0, 19 x 295 101.6 / 99.0).
 template <class T, bool FUSE, bool CHUNK>
-__global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
+__global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ? 3 : 2) void attn_prefill_kernel(AttnArgs a) {
   if constexpr (!CHUNK) { a.prefix = nullptr; a.slots = nullptr; a.pm.table = nullptr; }
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
@@ -687,6 +690,130 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
     return;
   }
 
+  if constexpr (FUSE) {
+    // ---- value decoder on the tile (Sec. 3.2): the workgroup holds the whole latent width of its
+    // group, so the heads of the group are finished here and L never goes to memory
+    typedef FusedDecoder<T> F;
+    const int head0 = g * a.hpq;
+    const unsigned ldo = (unsigned)(a.nh * a.dh * 2);
+    // this wave's heads; its rows of the gate and of the output, 8 lanes a row; rows past the sequence are beyond the buffers
+    auto head_of = [&](int i) { return head0 + kh * F::HPW + i; };
+    const int rows = min(Tb - qw0, 32);
+    const unsigned row_bytes = rows > 0 ? (rows - 1) * ldo + 128u : 0u, io_off = (lane >> 3) * ldo + (lane & 7) * 16;
+    auto rows_of = [&](const bf16 *p, int i) {
+      return __builtin_amdgcn_make_buffer_rsrc((void *)(p + (start + qw0) * (int64_t)(a.nh * a.dh) + head_of(i) * 64), 0, row_bytes, 0x00020000);
+    };
+    u32x4 gt[2][4];
+    auto ask_gate = [&](int i) {
+      const __amdgpu_buffer_rsrc_t r = rows_of(a.gate, i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) gt[i % 2][j] = __builtin_amdgcn_raw_buffer_load_b128(r, io_off + j * 8 * ldo, 0, 0);
+    };
+    // matrix of head w of the group: 16 loads of 8 rows; 64-byte halves of a row swapped where bit 1 of the row is set, so that the
+    // four rows of a transpose read lie in different 64-byte columns of 256 bytes
+    const unsigned wv = (lane >> 3) * 128 + ((((lane & 7) >> 2) ^ ((lane >> 4) & 1)) * 4 + (lane & 3)) * 16;
+    auto load_w = [&](int w) {
+      const u32x4 r = uniform_buffer_of(a.wp + (int64_t)(head0 + w) * 128 * 64, F::W_BYTES);
+#pragma unroll
+      for (int j = 0; j < 16 / T::NW; ++j)
+        load_to_lds(r, wv + (wave * (16 / T::NW) + j) * 1024, lds0 + w % F::WBUF * F::W_BYTES + (wave * (16 / T::NW) + j) * 1024);
+    };
+    constexpr int GATE = 4, STORES = 4;   // instructions of a wave and head
+    auto request = [&](int w, bool gate) {   // in this order: the waits below count what is younger than a matrix
+      load_w(w);
+      asm volatile("" ::: "memory");
+      if (gate && a.gate) ask_gate(w);
+      asm volatile("" ::: "memory");
+    };
+#pragma unroll
+    for (int w = 0; w < F::WBUF; ++w) request(w, w < 2);
+    bf16x8 lf[8];
+    if (kh == 0) {
+      const float inv = 1.0f / l_all;
+#pragma unroll
+      for (int mm = 0; mm < 8; ++mm)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) lf[mm][i] = (bf16)(acc[mm / 2][mm % 2 * 8 + i] * inv);
+    }
+    if constexpr (T::KS == 2) {
+      bf16x8 *lx = reinterpret_cast<bf16x8 *>(smem + F::L_OFF + qw * 8192) + lane;
+      if (kh == 0) {
+#pragma unroll
+        for (int mm = 0; mm < 8; ++mm) lx[mm * 64] = lf[mm];
+      }
+      __syncthreads();
+      if (kh == 1) {
+#pragma unroll
+        for (int mm = 0; mm < 8; ++mm) lf[mm] = lx[mm * 64];
+      }
+    }
+    const int wrow = (lane & 15) >> 2;
+    const int wfr = (4 * h + wrow) * 128 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8, wsw = (wrow >> 1) * 64;
+    char *io = smem + F::IO_OFF + wave * 4096;
+#pragma unroll
+    for (int i = 0; i < F::HPW; ++i) {
+      // this head's matrix has landed (younger than it: gate values of one head and the stores of the last; before the first head
+      // the next one's matrix and the gates of both); everyone has read the one before it
+      if constexpr (T::KS == 2) {
+        if (i == 0) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+      } else if (i == 0) {
+        if (a.gate) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * GATE + 16 / T::NW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(16 / T::NW) : "memory");
+      } else {
+        if (a.gate) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(GATE + STORES) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(STORES) : "memory");
+      }
+      if (T::KS == 1 && i > 0 && i + 1 < F::HPW) request(i + 1, true);
+      f32x16 z[2];
+#pragma unroll
+      for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[tn][r] = 0.f;
+      const char *wb = smem + (T::KS == 1 ? i % F::WBUF : kh * F::HPW + i) * F::W_BYTES + wfr;
+#pragma unroll
+      for (int mm = 0; mm < 8; ++mm)
+#pragma unroll
+        for (int tn = 0; tn < 2; ++tn) {
+          const char *wp = wb + mm * 16 * 128 + (tn * 64 ^ wsw);
+          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp));
+          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 8 * 128));
+          const s16x8 w8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          z[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), lf[mm], z[tn], 0, 0, 0);
+        }
+      // chunk c of row r in slot c ^ (r % 8); lane: row ln, columns tn*32 + rq*8 + 4h .. +3
+      if (a.gate) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = j * 8 + (lane >> 3);
+          *reinterpret_cast<u32x4 *>(io + r * 128 + (((lane & 7) ^ (r & 7)) << 4)) = gt[i % 2][j];
+        }
+      }
+      auto finish = [&](auto factor) {
+#pragma unroll
+        for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+          for (int rq = 0; rq < 4; ++rq) {
+            bf16x4 *slot = reinterpret_cast<bf16x4 *>(io + ln * 128 + (((tn * 4 + rq) ^ (ln & 7)) << 4) + h * 8);
+            const bf16x4 gz = *slot;
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)(z[tn][rq * 4 + e] * factor((float)gz[e]));
+            *slot = o;
+          }
+      };
+      if (!a.gate) finish([](float) { return 1.f; });
+      else if (a.gate_kind == kGateSigmoid) finish([](float x) { return gate_factor(kGateSigmoid, x); });
+      else finish([&](float x) { return gate_factor(a.gate_kind, x); });
+      const __amdgpu_buffer_rsrc_t ro = rows_of(a.out, i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = j * 8 + (lane >> 3);
+        __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(io + r * 128 + (((lane & 7) ^ (r & 7)) << 4)), ro, io_off + j * 8 * ldo, 0, 0);
+      }
+    }
+    return;
+  }
+
   // ---- normalise, park the tile in LDS in output layout, write row-contiguous 16-byte chunks
   if (kh == 0) {
     const float inv = 1.0f / l_all;
@@ -700,104 +827,6 @@ __global__ __launch_bounds__(T::NT, 2) void attn_prefill_kernel(AttnArgs a) {
         for (int i = 0; i < 4; ++i) v[i] = (bf16)(acc[dlb][rq * 4 + i] * inv);
         *reinterpret_cast<bf16x4 *>(smem + row * T::OUT_PITCH + (dlb * 32 + rq * 8 + 4 * h) * 2) = v;
       }
-  }
-  if constexpr (FUSE) {
-    // ---- value decoder on the tile (Sec. 3.2): the workgroup holds the whole latent width of its
-    // group, so the heads of the group are finished here and L never goes to memory
-    typedef FusedDecoder<T> F;
-    constexpr int WCH = F::KROWS * (F::N / 8) / T::NT;   // 16-byte chunks of the decoder matrices per thread and part
-    constexpr int GCH = T::BQ * (F::N / 8) / T::NT;      // chunks of the gate / output tile per thread
-    const int head0 = g * a.hpq;
-    const int64_t ldo = (int64_t)a.nh * a.dh;
-    u32x4 wr[WCH];
-    auto w_load = [&](int part) {
-#pragma unroll
-      for (int i = 0; i < WCH; ++i) {
-        const int c = tid + i * T::NT, k = part * F::KROWS + c / (F::N / 8), col = (c % (F::N / 8)) * 8;
-        wr[i] = *reinterpret_cast<const u32x4 *>(a.wp + ((int64_t)(head0 + col / a.dh) * a.dl + k) * a.dh + col % a.dh);
-      }
-    };
-    auto w_store = [&]() {
-#pragma unroll
-      for (int i = 0; i < WCH; ++i) {
-        const int c = tid + i * T::NT, k = c / (F::N / 8), col = (c % (F::N / 8)) * 8;
-        *reinterpret_cast<u32x4 *>(smem + F::W_OFF + k * F::W_PITCH + col * 2) = wr[i];
-      }
-    };
-    w_load(0);
-    w_store();
-    if constexpr (F::KH > 1) w_load(1);
-    // gate tile: requested now, parked in LDS once the operands are dead (rows past the sequence
-    // re-read its last row; they are not stored)
-    const int gr0 = tid / (F::N / 8), gch = tid % (F::N / 8);
-    constexpr int GRPP = T::NT / (F::N / 8);
-    u32x4 gt[GCH];
-    if (a.gate) {
-      const bf16 *gp = a.gate + head0 * a.dh + gch * 8;
-#pragma unroll
-      for (int i = 0; i < GCH; ++i)
-        gt[i] = *reinterpret_cast<const u32x4 *>(gp + (start + min(q0 + i * GRPP + gr0, Tb - 1)) * ldo);
-    }
-    __syncthreads();
-    f32x16 z[F::NTN];   // this wave's columns: 32 (kh * NTN + tn) ..
-#pragma unroll
-    for (int tn = 0; tn < F::NTN; ++tn)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) z[tn][r] = 0.f;
-    const char *lrow = smem + (qw * 32 + ln) * T::OUT_PITCH + h * 16;
-    const char *wfr = smem + F::W_OFF + (h * 8 + ((lane & 15) >> 2)) * F::W_PITCH + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2 + kh * F::NTN * 64;
-#pragma unroll
-    for (int ks = 0; ks < T::DLW / 16; ++ks) {
-      constexpr int KSP = F::KROWS / 16;   // k-steps per part
-      if (F::KH > 1 && ks == KSP) {
-        __syncthreads();
-        w_store();
-        __syncthreads();
-      }
-      const bf16x8 xf = *reinterpret_cast<const bf16x8 *>(lrow + ks * 32);
-#pragma unroll
-      for (int tn = 0; tn < F::NTN; ++tn) {
-        const char *wp = wfr + ks % KSP * 16 * F::W_PITCH + tn * 64;
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 4 * F::W_PITCH));
-        s16x8 w8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        z[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), xf, z[tn], 0, 0, 0);
-      }
-    }
-    __syncthreads();   // operands dead: the same LDS now takes the gate tile in output layout
-    if (a.gate) {
-#pragma unroll
-      for (int i = 0; i < GCH; ++i)
-        *reinterpret_cast<u32x4 *>(smem + (i * GRPP + gr0) * F::G_PITCH + gch * 16) = gt[i];
-      __syncthreads();
-    }
-    // lane: row qw*32 + ln, columns (kh*NTN + tn)*32 + rq*8 + 4h .. +3
-    char *orow = smem + (qw * 32 + ln) * F::G_PITCH + 4 * h * 2 + kh * F::NTN * 64;
-#pragma unroll
-    for (int tn = 0; tn < F::NTN; ++tn)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        bf16x4 *slot = reinterpret_cast<bf16x4 *>(orow + (tn * 32 + rq * 8) * 2);
-        float v[4] = {z[tn][rq * 4], z[tn][rq * 4 + 1], z[tn][rq * 4 + 2], z[tn][rq * 4 + 3]};
-        if (a.gate) {
-          const bf16x4 gz = *slot;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] *= gate_factor(a.gate_kind, (float)gz[i]);
-        }
-        bf16x4 o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = (bf16)v[i];
-        *slot = o;
-      }
-    __syncthreads();
-    bf16 *Ob = a.out + (start + q0) * ldo + head0 * a.dh + gch * 8;
-#pragma unroll 4
-    for (int i = 0; i < GCH; ++i) {
-      const int r = i * GRPP + gr0;
-      if (q0 + r < Tb)
-        *reinterpret_cast<u32x4 *>(Ob + (int64_t)r * ldo) = *reinterpret_cast<const u32x4 *>(smem + r * F::G_PITCH + gch * 16);
-    }
-    return;
   }
   __syncthreads();
   bf16 *Lb = a.L + (start + q0) * (int64_t)(a.nq * a.dl) + g * a.dl + dlc * T::DLW;
