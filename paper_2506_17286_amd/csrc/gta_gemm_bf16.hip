@@ -11,10 +11,9 @@
 // a plain 16-byte LDS read of an X row.  Each lane then owns 4 consecutive output columns of one
 // output row, which makes the RoPE pairing (j, j + d_h/2) lane-local.
 //
-// Workgroup tile BM x BN x BK with WGM x WGN waves of 32x32x16 MFMA tiles.  Projection and output projection of many rows
-// run as a stream of 256 x 256 tiles through one workgroup per CU (gemm_stream), the value decoder as one such tile per
-// workgroup (gemm_mainloop_big): operands straight into LDS, results rounded to bf16, passed through LDS and written with
-// 16-byte row-contiguous stores.
+// Workgroup tile BM x BN x BK with WGM x WGN waves of 32x32x16 MFMA tiles.  Many rows run as a stream of 256 x 256 tiles
+// through one workgroup per CU (gemm_stream): operands straight into LDS, results rounded to bf16, passed through LDS and
+// written with 16-byte row-contiguous stores.
 // The small tiles (split-K projection of the decode step) take the plain two-stage loop and store straight from the
 // accumulator layout.  Short prefills take the kernels for few rows (short_gemm_ok).
 #include <math.h>
@@ -120,37 +119,7 @@ __device__ __forceinline__ void gemm_mainloop(const bf16 *__restrict__ A, int64_
   }
 }
 
-// ---- software-pipelined main loop for the big tiles --------------------------------------------
-// 256 x 256 tile, eight waves (two per SIMD) of 64 x 128, k-tiles of 32.  Both operand tiles go from memory straight
-// into LDS (buffer_load_dwordx4 .. lds: no staging registers, no LDS writes by the waves) through four stages, so a
-// k-tile is requested three tiles ahead of its use.  The loop is laid out in steps of one MFMA:
-//   * the fragment reads of k-step kk+1 go out under the MFMAs of step kk (two fragment sets);
-//   * the barrier of tile t sits in its first k-step, behind that step's fragment reads: every wave has then read all
-//     of stage t, and (each wave having waited for its own loads) tile t+1 is complete;
-//   * behind it, under the MFMAs of the second k-step, go the reads of tile t+1's first step and the wave's loads of
-//     tile t+4 into the stage just left.
-// LDS layout: a load instruction fills 1 KiB in lane order, so there is no padding; instead each lane fetches the
-// 16-byte chunk that belongs in its slot.  X rows are 4 chunks, chunk c of row r in slot c ^ x_swz(r): any 8 (16)
-// consecutive rows read one logical chunk from 8 (16) different 16-byte columns of 128 (256) bytes.  Weight rows are
-// 32 chunks, chunk c of k-row k in slot c ^ 4 (k % 4): the four k-rows of a transpose read lie in different 64-byte
-// columns.
-// Measured against four waves of 128 x 128 that staged through registers (one wave per SIMD, 512 registers and spills):
-// decoder of 16384 rows 76 -> 69.  The same loop with four waves was no faster than the staged one; wave priorities, the
-// barrier's place and free scheduling changed nothing.
-__device__ __forceinline__ int x_swz(int r) { return ((r >> 2) & 3) ^ (r & 2); }
-
-struct BigLoop {
-  static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, X_BYTES = BM * BK * 2, STAGE = X_BYTES + BK * BN * 2;
-  static constexpr int SMEM = NSTAGE * STAGE;
-};
-
-// What the last four tiles fetch instead of operands: load j (0..7) of stage `s` of this wave.
-struct NoTail {
-  static constexpr bool active = false;
-  __device__ void load(int, int, unsigned) const {}
-};
-
-// Weight operand of a big tile: `base` points at its first k-row, rows are ld elements apart; column chunk c (8
+// Weight operand of a 256 x 256 tile: `base` points at its first k-row, rows are ld elements apart; column chunk c (8
 // columns) sits chunk_bytes(c) behind the start of a row; `bytes` covers 32 rows.
 struct WeightTile {
   const bf16 *base; int64_t ld; unsigned bytes;
@@ -159,105 +128,6 @@ struct WeightTile {
 };
 __device__ __forceinline__ WeightTile weight_tile(const bf16 *base, int64_t ld, unsigned head_bytes = 0) {
   return WeightTile{base, ld, (unsigned)(31 * ld * 2) + (head_bytes ? head_bytes + 256u : 512u), head_bytes};
-}
-
-// acc[tn][tm][r]:  n = wn*128 + tn*32 + 8*(r/4) + 4*(lane/32) + r%4,  m = wm*64 + tm*32 + lane%32, wn = wave % 2, wm = wave / 2.
-// `Abase` points at row m0 of the row operand.  K a multiple of 32, at least 128.  All loads have landed on return and
-// every wave has passed a barrier behind its last LDS read.
-template <class G, class Tail>
-__device__ __forceinline__ void gemm_mainloop_big(const bf16 *__restrict__ Abase, int64_t lda, int rows_valid, WeightTile B, int K,
-                                                  char *smem, f32x16 (&acc)[G::TN][G::TM], const Tail &tail) {
-  typedef BigLoop T;
-  constexpr int TM = G::TM, TN = G::TN, NW = G::NT / 64, LPW = 16 / NW;   // LPW: load instructions per wave and operand
-  const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % G::WGN, wm = wave / G::WGN;
-  const int nk = K / T::BK;
-  const int rv = min(rows_valid, T::BM);
-  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
-  // this wave's loads of a tile: rows 32 wave + 16 j + lane/4 of X (rows past the last valid one re-read it), k-rows
-  // 4 wave + 2 j + lane/32 of the weights
-  unsigned xv[LPW], wv[LPW];
-#pragma unroll
-  for (int j = 0; j < LPW; ++j) {
-    const int r = (wave * LPW + j) * 16 + (lane >> 2), k = (wave * LPW + j) * 2 + h;
-    xv[j] = (unsigned)(min(r, rv - 1) * lda * 2) + ((lane & 3) ^ x_swz(lane >> 2)) * 16;
-    wv[j] = (unsigned)(k * B.ld * 2) + B.chunk_bytes(ln ^ ((k & 3) << 2));
-  }
-  const u32x4 xr = buffer_of(Abase, (unsigned)((rv - 1) * lda * 2) + (unsigned)K * 2u);
-  const int64_t wstep = (int64_t)T::BK * B.ld * 2;
-  const char *wbase = reinterpret_cast<const char *>(B.base);   // of the tile that is requested next
-  auto load_x = [&](int t, int j) { load_to_lds(xr, xv[j], (unsigned)(t * T::BK * 2), lds0 + (t & 3) * T::STAGE + (wave * LPW + j) * 1024); };
-  auto load_w = [&](int t, int j) {
-    load_to_lds(buffer_of(wbase, B.bytes), wv[j], 0u, lds0 + (t & 3) * T::STAGE + T::X_BYTES + (wave * LPW + j) * 1024);
-  };
-  // fragment addresses: X chunk 2 kk + h of row ln (+ 32 tm), weight rows 8 h + (lane%16)/4 (+ 16 kk, + 4)
-  int xo[2], wo[TN];
-  const int wr = (lane & 15) >> 2;
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) xo[kk] = (wm * G::WM + ln) * 64 + (((kk * 2 + h) ^ x_swz(ln & 15)) * 16);
-#pragma unroll
-  for (int tn = 0; tn < TN; ++tn)
-    wo[tn] = T::X_BYTES + (h * 8 + wr) * 512 + (wn * (G::WN / 8) + ((tn ^ wr) << 2) + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) * 16 + (lane & 1) * 8;
-  struct Frags { bf16x8 x[TM]; s16x4 lo[TN], hi[TN]; };
-  constexpr int NR = TM + 2 * TN, NM = TM * TN;   // fragment reads and MFMAs of a k-step
-  // fragment read i, in the order the MFMAs of the step need them
-  auto read_frag = [&](Frags &f, const char *st, int kk, int i) {
-    if (i >= 2 && i < 2 + TM) { f.x[i - 2] = *reinterpret_cast<const bf16x8 *>(st + xo[kk] + (i - 2) * 2048); return; }
-    const int w = i < 2 ? i : i - TM, tn = w / 2;
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(st + wo[tn] + kk * 8192 + (w & 1) * 2048));
-    if (w & 1) f.hi[tn] = v; else f.lo[tn] = v;
-  };
-  // the reads of step i of NM: all of them within the first NM - 2 steps
-  auto read_frags = [&](Frags &f, const char *st, int kk, int i) {
-    constexpr int S = NM - 3;
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-      if (r * S / NR == i) read_frag(f, st, kk, r);
-  };
-  auto mma = [&](const Frags &f, int i) {
-    const int tn = i / TM, tm = i % TM;
-    const s16x8 w8 = __builtin_shufflevector(f.lo[tn], f.hi[tn], 0, 1, 2, 3, 4, 5, 6, 7);
-    acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), f.x[tm], acc[tn][tm], 0, 0, 0);
-  };
-  constexpr int PER_TILE = 2 * LPW;   // loads of a wave per tile
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-#pragma unroll
-    for (int j = 0; j < LPW; ++j) { load_x(t, j); load_w(t, j); }
-    wbase += wstep;
-  }
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * PER_TILE) : "memory");
-  Frags f0, f1;
-#pragma unroll
-  for (int i = 0; i < NR; ++i) read_frag(f0, smem, 0, i);
-#pragma unroll 1
-  for (int t = 0; t < nk; ++t) {
-    const char *cur = smem + (t & 3) * T::STAGE, *nxt = smem + ((t + 1) & 3) * T::STAGE;
-    const bool more = t + 4 < nk;
-#pragma unroll
-    for (int i = 0; i < NM; ++i) {
-      read_frags(f1, cur, 1, i);
-      mma(f0, i);
-      if (i == NM - 3) {   // three tiles in flight (t+1 .. t+3); at the end there may be fewer
-        if (Tail::active || t < nk - 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * PER_TILE) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int i = 0; i < NM; ++i) {
-      read_frags(f0, nxt, 0, i);
-      if (i % 2 == 1) {
-        const int l = i / 2;   // NM / 2 = PER_TILE
-        if (more) { if (l % 2 == 0) load_x(t + 4, l / 2); else load_w(t + 4, l / 2); }
-        else if (Tail::active) tail.load(t & 3, l, lds0 + (t & 3) * T::STAGE);
-      }
-      mma(f1, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    wbase += wstep;
-  }
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // Order of a stream's tiles, of which XCD x (workgroup ids x mod 8) takes the x-th eighth: bands of 8 row strips, a band in
@@ -344,10 +214,11 @@ __device__ __forceinline__ const A &kernel_args() {
 // that the first half steps of the next tile can wait for loads that are older.
 // LDS layout: a load instruction fills 1 KiB in lane order, so there is no padding; each lane fetches the 16-byte chunk that
 // belongs in its slot.  X rows are 8 chunks, chunk c of row r in slot c ^ xs_swz(r): any 8 (16) consecutive rows read one
-// logical chunk from 8 (16) different 16-byte columns of 128 (256) bytes.  Weights as in the loop above.
+// logical chunk from 8 (16) different 16-byte columns of 128 (256) bytes.  Weight rows are 32 chunks, chunk c of k-row k in
+// slot c ^ 4 (k % 4): the four k-rows of a transpose read lie in different 64-byte columns.
 // Bound: power.  Without loads a half step takes 0.73 us on such data and 0.54 on zeros, the loads alone 0.38; together 0.8 and
-// 0.6 (0.87 and 0.77 in the loop above), of which the matrix instructions are 0.43 at 2.4 GHz.  Against a workgroup per tile on that
-// loop (kernels inside the calls): projection 65536 x 1280 x 1792 334 -> 293 us, W_O 65536 x 1280 x 1280 234 -> 195,
+// 0.6, of which the matrix instructions are 0.43 at 2.4 GHz.  Against a workgroup per tile, four stages of 32 k for both operands
+// (0.87 and 0.77; kernels inside the calls): projection 65536 x 1280 x 1792 334 -> 293 us, W_O 65536 x 1280 x 1280 234 -> 195,
 // projection 16384 x 2048 x 3584 243 -> 221, 6500 x 2048 x 3584 114 -> 110, 121600 x 4096 x 7168 6.10 -> 5.96 ms (5.51 on a
 // day when that took 5.67, with a tile's place worked out in one round of scalar loads and no branches).
 struct StreamTile { const bf16 *A; int rows; WeightTile B; };   // row m0 of the row operand, rows from there, weight columns
@@ -911,78 +782,92 @@ __global__ __launch_bounds__(T::NT) void decoder_gemm_kernel(DecoderArgs a) {
   }
 }
 
-// The decoder's gate tile (256 rows x 512 bytes) fills the four stages as the last four k-tiles leave them, in output
-// layout: stage s takes rows 64 s .. 64 s + 63, two per load (rows past the end of the matrix re-read the last valid
-// one).
-template <int NW>
-struct GateTail {
-  static constexpr bool active = true;
-  u32x4 rsrc; unsigned ld_bytes; int last;   // last valid row of the tile
-  __device__ __forceinline__ void load(int s, int j, unsigned lds) const {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = (wave * (32 / NW) + j) * 2 + (lane >> 5);
-    load_to_lds(rsrc, (unsigned)min(s * 64 + r, last) * ld_bytes + ((lane & 31) ^ (r & 15)) * 16, 0u, lds + (wave * (32 / NW) + j) * 1024);
+// Two heads of one map group per 256-wide tile (they share the row operand L_g), as a stream of tiles.  The gate is applied to
+// the fp32 accumulators: the wave asks for its 64 x 128 pre-activations at the start of the epilogue (64 registers, the
+// fragments' and more), and they pass through its scratch into accumulator layout, 32 rows x 64 columns at a time.
+// Bound: 201 MB for 16384 rows of the 1B shape (40 us of a large copy).  Measured against a workgroup per tile whose gate tile
+// took the place of the last four k-tiles' operands, with X in rows of 64 bytes: 16384 rows of the 1B shape 72 -> 64 us, 4000 rows (125 tiles,
+// shared) 23 -> 18, 16384 rows of the 8 x 128 + 1024 shape 182 -> 163.
+struct DecoderStream { StreamOrder order; DecoderArgs a; };
+
+// KIND: kGateOff, kGateSigmoid (the method's, the short path) or -1, any other.  A kernel each: with both nonlinearities behind a branch
+// in one the compiler sees a way around both, on which the gate values are still in flight, and waits for them in the main loop.
+template <int KIND>
+struct DecoderStreamEpi {
+  static constexpr bool GATE = KIND != kGateOff;
+  static constexpr int kStores = kStreamStores;
+  static constexpr bool kReread = true;
+  template <class Rows>
+  __device__ __forceinline__ void operator()(const DecoderStream &args, Rows, TileAt t, f32x16 (&acc)[StreamLoop::TN][StreamLoop::TM], char *st) const {
+    typedef StreamLoop T;
+    constexpr int TM = Rows::value;
+    const DecoderArgs &a = args.a;
+    const int lane = epilogue_lane(), ln = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave % T::WGN, wm = wave / T::WGN;
+    const int ldo = a.nh * a.dh;
+    const int64_t at = (int64_t)t.m0 * ldo + t.nt * T::BN + wn * T::WN;
+    const unsigned bytes = (unsigned)((min(a.M - t.m0, TM * 128) - 1) * ldo * 2) + 256u;
+    const unsigned voff = (unsigned)((wm * TM * 32 + (lane >> 3)) * ldo + (lane & 7) * 8) * 2;
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(a.out + at, 0, bytes, 0x00020000);
+    u32x4 gt[TM][2][4];
+    auto ask = [&](int tm) {
+      const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void *)(a.g + at), 0, bytes, 0x00020000);
+#pragma unroll
+      for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gt[tm][tp][i] = __builtin_amdgcn_raw_buffer_load_b128(rg, voff + (tm * 32 + i * 8) * ldo * 2 + tp * 128, 0, 0);
+    };
+    if constexpr (GATE) {
+#pragma unroll
+      for (int tm = 0; tm < (KIND < 0 ? 1 : TM); ++tm) ask(tm);   // the other nonlinearities need the registers
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int tp = 0; tp < 2; ++tp) {
+        if (KIND < 0 && tm > 0 && tp == 0) ask(tm);
+        if constexpr (GATE) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int r = i * 8 + (lane >> 3);
+            *reinterpret_cast<u32x4 *>(st + r * 128 + (((lane & 7) ^ (r & 7)) << 4)) = gt[tm][tp][i];
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int rq = 0; rq < 4; ++rq) {
+            bf16x4 *slot = reinterpret_cast<bf16x4 *>(st + ln * 128 + (((q * 4 + rq) ^ (ln & 7)) << 4) + h * 8);
+            const f32x16 &v = acc[tp * 2 + q][tm];
+            float f[4] = {1.f, 1.f, 1.f, 1.f};
+            if constexpr (GATE) {
+              const bf16x4 gz = *slot;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) f[e] = gate_factor(KIND < 0 ? a.gate : KIND, (float)gz[e]);
+            }
+            *slot = pack4(v[rq * 4] * f[0], v[rq * 4 + 1] * f[1], v[rq * 4 + 2] * f[2], v[rq * 4 + 3] * f[3]);
+          }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = i * 8 + (lane >> 3);
+          const u32x4 v = *reinterpret_cast<const u32x4 *>(st + r * 128 + (((lane & 7) ^ (r & 7)) << 4));
+          __builtin_amdgcn_raw_buffer_store_b128(v, ro, voff + (tm * 32 + i * 8) * ldo * 2 + tp * 128, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
   }
 };
 
-// Two heads of one map group per 256-wide tile (they share the row operand L_g), pipelined main
-// loop.  The gate is applied to the fp32 accumulators: the gate tile is fetched into LDS in output layout, every
-// lane reads the pre-activations of its own elements from there and puts the gated, rounded result back in the
-// same place.
-template <class T, bool GATE>
-__global__ __launch_bounds__(T::NT) void decoder_pair_kernel(DecoderArgs a) {
+template <int KIND>
+__global__ __launch_bounds__(StreamLoop::NT) void decoder_stream_kernel(DecoderStream args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  int mt, nt;
-  tile_of_block(a.nh / 2, (a.M + T::BM - 1) / T::BM, mt, nt);
-  const int head = nt * 2, m0 = mt * T::BM;
-  f32x16 acc[T::TN][T::TM];
-  zero_acc<T>(acc);
-  const int64_t ldo = (int64_t)a.nh * a.dh;
-  const int col0 = head * a.dh;
-  const int rv = min(a.M - m0, T::BM);
-  {
-    const bf16 *Ab = a.L + (int64_t)m0 * a.ldl + (head / a.hpq) * a.dl;
-    const WeightTile wt = weight_tile(a.wp + (int64_t)head * a.dl * a.dh, a.dh, (unsigned)(a.dl * a.dh * 2));
-    if constexpr (GATE) {
-      const GateTail<T::NT / 64> gate{buffer_of(a.g + (int64_t)m0 * ldo + col0, (unsigned)((rv - 1) * ldo * 2) + 512u), (unsigned)(ldo * 2), rv - 1};
-      gemm_mainloop_big<T>(Ab, a.ldl, rv, wt, a.dl, smem, acc, gate);
-    } else {
-      gemm_mainloop_big<T>(Ab, a.ldl, rv, wt, a.dl, smem, acc, NoTail{});
-    }
-  }
-  // one row block (tm) at a time: all 16 gate reads of the block are issued before the first is used
-  // the Sigmoid of the method takes the short path; the other nonlinearities a general one
-  auto gate_rows = [&](auto sig_tag) {
-    constexpr bool SIG = decltype(sig_tag)::value;
-  #pragma unroll
-    for (int tm = 0; tm < T::TM; ++tm) {
-      bf16x4 gz[T::TN][4];
-      if constexpr (GATE) {
-  #pragma unroll
-        for (int tn = 0; tn < T::TN; ++tn)
-  #pragma unroll
-          for (int rq = 0; rq < 4; ++rq) gz[tn][rq] = *reinterpret_cast<const bf16x4 *>(smem + out_lds_offset<T>(tm, tn, rq));
-      }
-  #pragma unroll
-      for (int tn = 0; tn < T::TN; ++tn)
-  #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-          float v[4] = {acc[tn][tm][rq * 4], acc[tn][tm][rq * 4 + 1], acc[tn][tm][rq * 4 + 2], acc[tn][tm][rq * 4 + 3]};
-          if constexpr (GATE) {
-  #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              v[i] *= SIG ? __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * (float)gz[tn][rq][i]))
-                          : gate_factor(a.gate, (float)gz[tn][rq][i]);
-          }
-          *reinterpret_cast<bf16x4 *>(smem + out_lds_offset<T>(tm, tn, rq)) = pack4(v[0], v[1], v[2], v[3]);
-        }
-    }
-  };
-  if (!GATE || a.gate == kGateSigmoid) gate_rows(std::true_type{});
-  else gate_rows(std::false_type{});
-  __syncthreads();
-  for_each_out_chunk<T::NT>(smem, [&](int r, int ch, u32x4 v) {
-    if (m0 + r < a.M) *reinterpret_cast<u32x4 *>(a.out + (int64_t)(m0 + r) * ldo + col0 + ch * 8) = v;
-  });
+  gemm_stream<DecoderStream>(args.a.ldl, args.a.dl, smem, [](const DecoderStream &g, TileAt t) {
+    const DecoderArgs &a = g.a;
+    const int head = t.nt * 2;
+    return StreamTile{a.L + (int64_t)t.m0 * a.ldl + (head / a.hpq) * a.dl, a.M - t.m0,
+                      weight_tile(a.wp + (int64_t)head * a.dl * a.dh, a.dh, (unsigned)(a.dl * a.dh * 2))};
+  }, DecoderStreamEpi<KIND>{});
 }
 
 // All 256 / d_h heads of one 256-wide tile share the row operand L_g (they lie in one map group);
@@ -1154,7 +1039,6 @@ typedef GemmTile<64, 128, 64, 1, 4> TileSkinny64;
 typedef GemmTile<32, 64, 64, 1, 2> TileSkinny32N64;   // 64-wide tiles for widths that are not multiples of 128
 typedef GemmTile<64, 64, 64, 2, 2> TileSkinny64N64;
 
-typedef GemmTile<256, 256, 64, 4, 2> TileBig;    // eight waves, wave tile 64(m) x 128(n)
 typedef GemmTile<256, 256, 64, 2, 2> TileBig4;   // four waves of 128 x 128 (plain main loop)
 typedef GemmTile<256, 128, 64, 4, 1> TileHead;   // one 128-wide head per workgroup, wave tile 64(m) x 128(n)
 typedef GemmTile<256, 64, 64, 4, 1> TileHead64;  // one 64-wide head per workgroup, wave tile 64(m) x 64(n)
@@ -1293,8 +1177,8 @@ void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const voi
   a.g = (const bf16 *)g; a.gate = d.gate; a.out = (bf16 *)out;
   if (short_gemm_ok(M, d.nh * d.dh)) { launch_short_decoder(d, L, wp, g, out, M, st); return; }
   if (d.dh == 128 && d.hpq % 2 == 0 && d.dl % 128 == 0 && d.dl >= 256) {
-    if (d.gate) launch<TileBig>(decoder_pair_kernel<TileBig, true>, a, (d.nh / 2) * ((M + 255) / 256), st);
-    else launch<TileBig>(decoder_pair_kernel<TileBig, false>, a, (d.nh / 2) * ((M + 255) / 256), st);
+    launch_stream(d.gate == kGateOff ? decoder_stream_kernel<kGateOff> : d.gate == kGateSigmoid ? decoder_stream_kernel<kGateSigmoid>
+                  : decoder_stream_kernel<-1>, DecoderStream{{}, a}, M, d.nh * 128, st);
     return;
   }
   if ((d.dh == 64 || d.dh == 128) && d.hpq % (256 / d.dh) == 0) {
