@@ -548,12 +548,16 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
         for (int r = 0; r < 16; ++r) acc[i][r] *= corr;
     }
   };
-  // main part: this wave's blocks of steps t and t+1 both lie entirely below its diagonal
+  // Main part: steps whose next block lies below the wave's diagonal (up to t_main), and with latent tiles of 128 (DIAG) also those
+  // where it touches the diagonal.  (256: the branch costs the longest chains what the diagonal gains; 16 prompts of 525..15071 tokens,
+  // 8 x 128 + 1024 shape, 19.09 -> 19.18 ms; with 128 columns 1 x 500 tokens of the 1B shape 42.95 -> 42.39 us, 2 chunks of
+  // 100..200 57.4 -> 56.6, 32 x 2048 tokens of the paper's layer 670 -> 662.)
+  constexpr bool DIAG = T::PIPELINED && T::NDLB == 4;
   int t = 0;
   if constexpr (T::PIPELINED) {
-  const int lim = min(nb_w, qa0 >> 5) - 1 - tile0 - kh, t_main = lim < 0 ? 0 : lim / T::KS;   // steps 0 .. t_main-1
+  const int lim = min(nb_w, qa0 >> 5) - 1 - tile0 - kh, t_main = lim < 0 ? 0 : lim / T::KS;
 #pragma unroll 1
-  for (; t < t_main; ++t) {
+  for (; DIAG ? blk(t + 1) < nb_w : t < t_main; ++t) {
     // The fragment reads of the first score MFMAs and of the first two map-times-latent MFMAs go out
     // before anything else, so that the MFMAs below do not each wait for an LDS round trip; the second
     // half of the key fragments follows behind the first two score MFMAs.
@@ -577,6 +581,7 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (DIAG && t >= t_main) mask(s, blk(t + 1) * 32);
     // 2 * NDLB steps, each one MFMA of block t (latent fragment i, read two steps earlier), the
     // transpose reads of fragment i+2 and a slice of the softmax arithmetic of block t+1 (16 slices
     // dealt evenly over the steps); the scheduling barrier after every step pins this order, so each
@@ -625,24 +630,29 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
     rotate();
   }
   }
-  // the blocks around the diagonal, then idle steps that only keep staging for the other waves
+  // the blocks that the loop above leaves (the last one has no next), then idle steps that only keep staging for the other waves
 #pragma unroll 1
   for (; t < nsteps; ++t) {
     if (t > 0) issue();
     if (blk(t) < nb_w) {
       rescale();
-      f32x16 s;
-      bf16x8 pn[2];
-      if (blk(t + 1) < nb_w) {
-        scores(nxt, s);
-        if (blk(t + 1) * 32 + 31 > qa0) mask(s, blk(t + 1) * 32);
-      } else {   // no further block: all-masked scores leave the statistics unchanged and give P = 0
+      if constexpr (DIAG) {
+        pv(cur, pf);
+        corr = 1.f;
+      } else {
+        f32x16 s;
+        bf16x8 pn[2];
+        if (blk(t + 1) < nb_w) {
+          scores(nxt, s);
+          if (blk(t + 1) * 32 + 31 > qa0) mask(s, blk(t + 1) * 32);
+        } else {   // no further block: all-masked scores leave the statistics unchanged and give P = 0
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = -INFINITY;
+          for (int r = 0; r < 16; ++r) s[r] = -INFINITY;
+        }
+        softmax(s, pn, corr);
+        pv(cur, pf);
+        pf[0] = pn[0]; pf[1] = pn[1];
       }
-      softmax(s, pn, corr);
-      pv(cur, pf);
-      pf[0] = pn[0]; pf[1] = pn[1];
     }
     wait_meet(std::integral_constant<int, T::NSTAGE - 3>{});
     rotate();
