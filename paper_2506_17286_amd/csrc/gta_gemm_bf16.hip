@@ -1091,17 +1091,20 @@ size_t proj_packed_bytes(const Dims &d) {
   return d.dtype == GTA_BF16 && !proj_direct_big(d) && proj_packed_ok(d) ? (size_t)d.H * proj_packed_width(d) * 2 : 0;
 }
 
-
-// Up to one and a half rounds of 64 x 128 tiles (512 are on the chip at once) the tiles that split K over their waves
-// are ahead of the 256 x 256 ones, which would be too few; measured whole calls, 64-row against 256-row tiles:
-// projection of the 1B shape 1700 tokens 94 against 104 us (756 tiles), 1900 109 / 110 (840), 2300 126 / 124 (1008); the
-// 8 x 128 + 1024 shape 800 tokens 104 / 125 (728), 1000 127 / 130 (896); the paper's layer 3200 tokens 78 / 81 (700),
-// 4000 97 / 90 (882).  Value decoder of the 1B shape 3000 tokens 137.7 / 138.8 (752), 4000 169.8 / 167.4 (1008).  W_O of
-// the paper's layer 4000 tokens 97 / 101 (630), 5600 100.6 / 97.7 (880).
-static bool short_gemm_ok(int M, int N) { return (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= 768; }
+// 512 tiles of 64 x 128 are on the chip at once; up to there the tiles that split K over their waves are ahead of the stream of 256 x
+// 256 tiles, of which there would be too few.  Whole calls, 64-row tiles / stream: 1B shape 1200 tokens (532 tiles in the
+// projection) 76.3 / 75.7 us, 1700 (756) 90.3 / 88.1, 2200 (560 in the decoder) 106.1 / 100.9, 3000 (752) 131.8 / 126.8; paper's layer 2400
+// tokens (532) 90.3 / 86.9, 3200 (700) 108.3 / 98.4, 4 x 1000 (630 in W_O) 80.5 / 77.4; 768 wide layer 4 x 1000 62.6 / 59.3.  Alone the
+// projections are level at 1200 (38.4 / 38.5) and 2000 tokens (paper, 448 tiles: 31.3 / 32.1).  Contractions beyond 2048 and shapes
+// that no stream takes keep one and a half rounds: 8 x 128 + 1024 shape 600 tokens (560) 97.9 / 98.7, 700 (616) 102.5 / 103.1.
+static bool short_gemm_ok(int M, int N, int K, bool stream) {
+  return (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= (stream && K <= 2048 ? 512 : 768);
+}
+static bool proj_streams(const Dims &d) { return proj_direct_big(d) || proj_packed_ok(d); }
+static bool decoder_streams(const Dims &d) { return d.dh == 128 && d.hpq % 2 == 0 && d.dl % 128 == 0 && d.dl >= 256; }
 
 bool proj_folds(const Dims &d, int batch, int64_t M) {
-  return batch <= kFoldBatch && short_gemm_ok((int)M, d.wtot) && short_proj_folds(d, M);
+  return batch <= kFoldBatch && short_gemm_ok((int)M, d.wtot, d.H, proj_streams(d)) && short_proj_folds(d, M);
 }
 
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
@@ -1121,7 +1124,7 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
     a.max_batch = cache->max_batch; a.max_seq = cache->max_seq;
     a.pm = page_map_of(*cache);
   }
-  if (short_gemm_ok(M, d.wtot)) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
+  if (short_gemm_ok(M, d.wtot, d.H, proj_streams(d))) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
   if (proj_direct_big(d)) {
     launch_stream(proj_stream_kernel<128, false>, ProjStream{{}, a, nullptr, 0}, M, d.wtot, st);
   } else if (proj_packed_ok(d)) {
@@ -1175,8 +1178,8 @@ void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const voi
   a.L = (const bf16 *)L; a.ldl = (int64_t)d.nq * d.dl; a.M = M;
   a.wp = (const bf16 *)wp; a.dl = d.dl; a.dh = d.dh; a.hpq = d.hpq; a.nh = d.nh;
   a.g = (const bf16 *)g; a.gate = d.gate; a.out = (bf16 *)out;
-  if (short_gemm_ok(M, d.nh * d.dh)) { launch_short_decoder(d, L, wp, g, out, M, st); return; }
-  if (d.dh == 128 && d.hpq % 2 == 0 && d.dl % 128 == 0 && d.dl >= 256) {
+  if (short_gemm_ok(M, d.nh * d.dh, d.dl, decoder_streams(d))) { launch_short_decoder(d, L, wp, g, out, M, st); return; }
+  if (decoder_streams(d)) {
     launch_stream(d.gate == kGateOff ? decoder_stream_kernel<kGateOff> : d.gate == kGateSigmoid ? decoder_stream_kernel<kGateSigmoid>
                   : decoder_stream_kernel<-1>, DecoderStream{{}, a}, M, d.nh * 128, st);
     return;
@@ -1200,10 +1203,9 @@ void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const vo
     launch_rows_plain(A, lda, M, N, K, B, C, st);
     return;
   }
-  if (short_gemm_ok(M, N)) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
-  if (N % 256 == 0 && K % 128 == 0 && K >= 256) {
-    launch_stream(plain_stream_kernel, PlainStream{{}, a}, M, N, st);
-  }
+  const bool stream = N % 256 == 0 && K % 128 == 0 && K >= 256;
+  if (short_gemm_ok(M, N, K, stream)) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
+  if (stream) launch_stream(plain_stream_kernel, PlainStream{{}, a}, M, N, st);
   else launch<TileHead>(plain_gemm_kernel<TileHead>, a, (N / 128) * ((M + 255) / 256), st);
 }
 

@@ -54,10 +54,11 @@ def test_second_tile_on_a_cu(layer, rows):
     _check(LAYERS[layer], rows, True)
 
 
-@pytest.mark.parametrize("layer,rows", [("k256", 4993), ("k256", 13057), ("k256", 19457), ("packed", 9345), ("packed", 13825),
-                                        ("ten", 11137)])
+@pytest.mark.parametrize("layer,rows", [("k256", 3264), ("k256", 3265), ("k256", 4993), ("k256", 13057), ("k256", 19457), ("packed", 9345),
+                                        ("packed", 13825), ("ten", 11137)])
 def test_rounds_of_tiles(layer, rows):
-    """256 x 256 tiles on 256 CUs.  100: less than a round, every tile shared by two workgroups; 260: a round and four to
+    """510 and 520 tiles of 64 x 128 in the projection: the last on those, the first on 256 x 256 tiles.  256 x 256 tiles on 256 CUs:
+    100: less than a round, every tile shared by two workgroups; 260: a round and four to
     share, of the last strip's one row only the first half exists; 385: 129 behind the round are too many to share; 7 columns
     in panels of 4 and 3, 259 and 385 tiles; 10 columns in panels of 4, 4 and 2, a last band of 4 strips, 440 tiles."""
     _check(dict(LAYERS, ten=_wl(n_heads=12, latent_dim=512))[layer], rows, True)
