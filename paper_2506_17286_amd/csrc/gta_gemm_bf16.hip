@@ -612,26 +612,13 @@ __global__ __launch_bounds__(T::NT) void proj_gemm_kernel(ProjArgs a) {
 }
 
 // ---- projection against packed weights -----------------------------------------------------------
-// The four weight matrices are first copied side by side into one [H, Wtot] matrix, so that a
+// The setup launch copies the four weight matrices side by side into one [H, Wtot] matrix (pack_of), so that a
 // 256-column tile may straddle Q | K | C | gate: this serves output widths that are multiples of 64
 // but not of 256 (heads of 64, a single shared key).  Columns are routed to their outputs per
 // 64-column group (a head never straddles one).
 // The packed row is padded with zero columns to a multiple of 256 (wpad); the last tile computes
 // them and stores nothing for them.
-__global__ void pack_weights_kernel(ProjArgs a, int wtot, int wpad, bf16 *dst) {
-  const int cpr = wpad / 8;   // 16-byte chunks per packed row
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= (int64_t)a.K * cpr) return;
-  const int k = (int)(i / cpr);
-  int col = (int)(i % cpr) * 8, seg = 0;
-  u32x4 v = {0u, 0u, 0u, 0u};
-  if (col < wtot) {
-    while (col >= a.width[seg]) { col -= a.width[seg]; ++seg; }
-    v = *reinterpret_cast<const u32x4 *>(a.w[seg] + (int64_t)k * a.width[seg] + col);
-  }
-  *reinterpret_cast<u32x4 *>(dst + i * 8) = v;
-}
-
+//
 // ---- both projections as streams of tiles --------------------------------------------------------
 // PACKED: weights from wpack (rows of wpad columns), else from the four matrices (widths multiples of 256).  A group of 64
 // columns lies in one of Q | K | C | gate, whole heads in a wave's 128 columns.
@@ -1107,6 +1094,16 @@ bool proj_folds(const Dims &d, int batch, int64_t M) {
   return batch <= kFoldBatch && short_gemm_ok((int)M, d.wtot, d.H, proj_streams(d)) && short_proj_folds(d, M);
 }
 
+PackWeights pack_of(const Dims &d, const gta_weights &w, int64_t M, const PrefillWs &ws) {
+  PackWeights p{};
+  if (proj_direct_big(d) || !proj_packed_ok(d) || short_gemm_ok((int)M, d.wtot, d.H, true)) return p;
+  p.w[0] = w.wq; p.w[1] = w.wk; p.w[2] = w.wc; p.w[3] = w.wg;
+  p.width[0] = d.wq_w; p.width[1] = d.wk_w; p.width[2] = d.wc_w; p.width[3] = d.wg_w;
+  p.K = d.H; p.wtot = d.wtot; p.wpad = proj_packed_width(d); p.dst = ws.wpack;
+  p.blocks = (int)(((int64_t)p.K * (p.wpad / 8) + 255) / 256);
+  return p;
+}
+
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
                       const gta_cache *cache, const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold,
                       hipStream_t st) {
@@ -1128,10 +1125,8 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
   if (proj_direct_big(d)) {
     launch_stream(proj_stream_kernel<128, false>, ProjStream{{}, a, nullptr, 0}, M, d.wtot, st);
   } else if (proj_packed_ok(d)) {
-    bf16 *wpack = (bf16 *)ws.wpack;
+    const bf16 *wpack = (const bf16 *)ws.wpack;   // filled by the setup launch (pack_of)
     const int wpad = proj_packed_width(d);
-    const int64_t chunks = (int64_t)d.H * (wpad / 8);
-    pack_weights_kernel<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(a, d.wtot, wpad, wpack);
     if (d.dh == 64) launch_stream(proj_stream_kernel<64, true>, ProjStream{{}, a, wpack, wpad}, M, wpad, st);
     else launch_stream(proj_stream_kernel<128, true>, ProjStream{{}, a, wpack, wpad}, M, wpad, st);
   } else {

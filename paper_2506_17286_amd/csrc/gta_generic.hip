@@ -180,12 +180,27 @@ __global__ void finalize_prefill_kernel(Dims d, const float *praw, const int32_t
   }
 }
 
-// Everything a prefill call derives from the sequence offsets alone, in one launch: blocks
-// [0, nb_row) fill the row -> (sequence, position) map, the next nb_rope blocks the RoPE table, the
-// rest set the cached lengths (nothing below reads the lengths back during the call).
+// One 16-byte chunk of the packed weights per thread.
+__device__ __forceinline__ void pack_weights(const PackWeights &a, int blk) {
+  const int cpr = a.wpad / 8;   // chunks per packed row
+  const int64_t i = blk * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= (int64_t)a.K * cpr) return;
+  const int k = (int)(i / cpr);
+  int col = (int)(i % cpr) * 8, seg = 0;
+  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  if (col < a.wtot) {
+    while (col >= a.width[seg]) { col -= a.width[seg]; ++seg; }
+    v = *reinterpret_cast<const uint4 *>((const bf16 *)a.w[seg] + (int64_t)k * a.width[seg] + col);
+  }
+  reinterpret_cast<uint4 *>(a.dst)[i] = v;
+}
+
+// Everything a prefill call derives from the sequence offsets and the weights alone, in one launch: blocks
+// [0, nb_row) fill the row -> (sequence, position) map, the next nb_rope blocks the RoPE table, the next
+// pack.blocks the packed weights, the rest set the cached lengths (nothing below reads the lengths back during the call).
 __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total, int per_seq, int32_t *seq_id,
                                      int32_t *pos, int nb_row, float2 *tab, int max_pos, int half, int dh,
-                                     double base, int nb_rope, int rope_rows, CacheView cv) {
+                                     double base, int nb_rope, int rope_rows, CacheView cv, PackWeights pack) {
   int blk = blockIdx.x;
   if (blk < nb_row) {
     int64_t t = blk * (int64_t)blockDim.x + threadIdx.x;
@@ -201,6 +216,8 @@ __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total
     return;
   }
   blk -= nb_rope;
+  if (blk < pack.blocks) { pack_weights(pack, blk); return; }
+  blk -= pack.blocks;
   int b = blk * 4 + (threadIdx.x >> 6);
   if (b < batch) prefill_commit_seq(cv, cu, per_seq, b);
 }
@@ -210,7 +227,7 @@ __global__ void prefill_setup_kernel(const int32_t *cu, int batch, int64_t total
 // the chunk does not fit (the sequence is then skipped: nothing stored, zero output, status flagged at
 // commit).  Token t of sequence b gets position prefix[b] + (t - cu[b]); the RoPE table is per packed
 // token here (row t), since positions of different sequences no longer coincide.  Blocks [0, nb_row):
-// row map and RoPE rows, tpw tokens per wave; last blocks: prefix[], a wave per sequence.  Nothing
+// row map and RoPE rows, tpw tokens per wave; then the packed weights; last blocks: prefix[], a wave per sequence.  Nothing
 // in this launch writes the cached lengths, so every wave may read them.  Against a power and a walk of
 // the page table per entry (whole calls): 4 x 1200..2048 behind 3000 on pages of 64 346 -> 337 us, 4 x 900
 // 144.7 -> 140.7; fresh 1 x 8000 on pages of 64 357 -> 345.
@@ -223,7 +240,7 @@ __device__ __forceinline__ int chunk_prefix(const CacheView &cv, const int32_t *
 
 __global__ void prefill_chunk_setup_kernel(const int32_t *cu, int batch, int64_t total, int per_seq, int32_t *seq_id,
                                            int32_t *pos, int nb_row, int tpw, float2 *tab, int half, int dh,
-                                           double base, CacheView cv, int32_t *prefix) {
+                                           double base, CacheView cv, int32_t *prefix, PackWeights pack) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int blk = blockIdx.x;
   if (blk < nb_row) {
@@ -239,7 +256,9 @@ __global__ void prefill_chunk_setup_kernel(const int32_t *cu, int batch, int64_t
     }
     return;
   }
-  const int b = (blk - nb_row) * 4 + wave;
+  blk -= nb_row;
+  if (blk < pack.blocks) { pack_weights(pack, blk); return; }
+  const int b = (blk - pack.blocks) * 4 + wave;
   if (b >= batch) return;
   const int pre = chunk_prefix(cv, cu, per_seq, b);
   if (lane == 0) prefix[b] = pre;
@@ -653,7 +672,7 @@ int prefill_impl(const Dims &d, const gta_weights &w, const T *x, const int32_t 
   const bool mfma = F32 && f32_gemms_ok(d, total);
   Fold fold{};
   if (mfma && f32_proj_folds(d, batch, total)) fold = Fold{cu, batch, per_seq};
-  else launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
+  else launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, PackWeights{}, st);
   // Sec. 3.2 projections, RoPE, cache rows: [Q | K | C | gate pre-activation]
   if (mfma) launch_proj_f32(d, w, x, M, ws, cache, slots, max_len, false, fold, st);
   else project_raw<T>(d, w, x, M, ws, cache, slots, total, max_len, 0, st);
@@ -678,7 +697,7 @@ int prefill_chunk_impl(const Dims &d, const gta_weights &w, const T *x, const in
                        hipStream_t st) {
   const int per_seq = (int)(total / batch);
   const int M = (int)total;
-  launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, st);
+  launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, PackWeights{}, st);
   if (std::is_same<T, float>::value && f32_gemms_ok(d, total)) launch_proj_f32(d, w, x, M, ws, &cache, slots, max_chunk, true, Fold{}, st);
   else project_raw<T>(d, w, x, M, ws, &cache, slots, total, max_chunk, 1, st);
   CacheView cv = view_of(&cache, slots);
@@ -732,7 +751,8 @@ int decode_impl(const Dims &d, const gta_weights &w, const T *x, int batch, cons
 
 // ------------------------------------------------------------------------------ exported helpers
 void launch_prefill_setup(const Dims &d, const int32_t *cu, int batch, int64_t total, int max_len, int32_t *seq_id,
-                          int32_t *pos, float2 *tab, const gta_cache *cache, const int32_t *slots, hipStream_t st) {
+                          int32_t *pos, float2 *tab, const gta_cache *cache, const int32_t *slots, const PackWeights &pack,
+                          hipStream_t st) {
   if (total <= 0) return;
   const int half = d.dh / 2;
   const int nb_row = (int)((total + 255) / 256);
@@ -742,19 +762,19 @@ void launch_prefill_setup(const Dims &d, const int32_t *cu, int batch, int64_t t
   const int per_row = half > 256 || !rope ? 1 : 256 / half, rows = per_row * ((int64_t)max_len > 256 * per_row ? 4 : 1);
   const int nb_rope = rope ? (int)(((int64_t)max_len + rows - 1) / rows) : 0;
   const int nb_commit = cache ? (batch + 3) / 4 : 0;
-  prefill_setup_kernel<<<nb_row + nb_rope + nb_commit, 256, nb_rope ? half * sizeof(double) : 0, st>>>(
+  prefill_setup_kernel<<<nb_row + nb_rope + pack.blocks + nb_commit, 256, nb_rope ? half * sizeof(double) : 0, st>>>(
       cu, batch, total, (int)(total / batch), seq_id, pos, nb_row, tab, max_len, half, d.dh, d.rope_base, nb_rope, rows,
-      cache ? view_of(cache, slots) : CacheView{});
+      cache ? view_of(cache, slots) : CacheView{}, pack);
 }
 
 void launch_prefill_chunk_setup(const Dims &d, const int32_t *cu, int batch, int64_t total, int32_t *seq_id,
                                 int32_t *pos, float2 *tab, int32_t *prefix, const gta_cache &cache,
-                                const int32_t *slots, hipStream_t st) {
+                                const int32_t *slots, const PackWeights &pack, hipStream_t st) {
   if (total <= 0) return;
   const int half = d.rope ? d.dh / 2 : 0, tpw = total > 4096 ? 4 : 1, nb_row = (int)((total + 4 * tpw - 1) / (4 * tpw));
-  prefill_chunk_setup_kernel<<<nb_row + (batch + 3) / 4, 256, half * sizeof(double), st>>>(
+  prefill_chunk_setup_kernel<<<nb_row + pack.blocks + (batch + 3) / 4, 256, half * sizeof(double), st>>>(
       cu, batch, total, (int)(total / batch), seq_id, pos, nb_row, tpw, tab, half, d.dh, d.rope_base, view_of(&cache, slots),
-      prefix);
+      prefix, pack);
 }
 
 void launch_prefill_chunk_commit(const gta_cache &cache, const int32_t *slots, const int32_t *cu, int batch,

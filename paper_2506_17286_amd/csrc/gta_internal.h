@@ -142,6 +142,10 @@ __device__ __forceinline__ void prefill_commit_seq(const CacheView &cv, const in
 constexpr int kFoldBatch = 16;
 struct Fold { const int32_t *cu; int batch, per_seq; };
 
+// Weight matrices that the projection of a call wants side by side: [K, wpad], columns from wtot on zero.  Done by workgroups of the
+// setup launch (blocks 0: nothing to do); a launch of its own took 5 us.
+struct PackWeights { const void *w[4]; int width[4], K, wtot, wpad; void *dst; int blocks; };
+
 // ---- workspace carve-up (one function per mode so sizing and use cannot disagree) ----------
 struct PrefillWs {
   int32_t *seq_id, *pos;   // [total] sequence index and position of each packed token
@@ -206,13 +210,13 @@ int launch_calibration_mfma(int workgroups, int iters, bool random_operands, voi
 // chunked prefill: row map with positions behind the cached rows, per-token RoPE rows, prefix[]; commit
 void launch_prefill_chunk_setup(const Dims &d, const int32_t *cu, int batch, int64_t total, int32_t *seq_id,
                                 int32_t *pos, float2 *tab, int32_t *prefix, const gta_cache &cache,
-                                const int32_t *slots, hipStream_t st);
+                                const int32_t *slots, const PackWeights &pack, hipStream_t st);
 void launch_prefill_chunk_commit(const gta_cache &cache, const int32_t *slots, const int32_t *cu, int batch,
                                  int64_t total, const int32_t *prefix, hipStream_t st);
 // row map, RoPE table (if d.rope) and cached lengths (if cache) of one prefill call in one launch
 void launch_prefill_setup(const Dims &d, const int32_t *cu, int batch, int64_t total, int max_len,
                           int32_t *seq_id, int32_t *pos, float2 *tab, const gta_cache *cache,
-                          const int32_t *slots, hipStream_t st);
+                          const int32_t *slots, const PackWeights &pack, hipStream_t st);
 
 // hipGetLastError after the launches of a call; with GTA_DEBUG set in the environment the HIP error
 // string goes to stderr (the only thing the library ever prints).

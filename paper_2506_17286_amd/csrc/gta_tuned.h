@@ -34,6 +34,7 @@ void tuned_decode_combine(const Dims &d, const float *part, const int32_t *oldle
 // bf16 MFMA GEMMs (gta_gemm_bf16.hip)
 bool gemm_shapes_supported(const Dims &d);
 size_t proj_packed_bytes(const Dims &d);   // workspace for the packed [H, Wtot] weights, 0 if not used
+PackWeights pack_of(const Dims &d, const gta_weights &w, int64_t M, const PrefillWs &ws);   // what launch_proj_gemm wants packed before it
 void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M, const PrefillWs &ws,
                       const gta_cache *cache, const int32_t *slots, int max_len, bool rope_by_token, const Fold &fold,
                       hipStream_t st);

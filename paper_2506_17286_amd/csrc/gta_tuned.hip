@@ -9,7 +9,7 @@ void tuned_project(const Dims &d, const gta_weights &w, const void *x, const int
                    const gta_cache *cache, const int32_t *slots, const PrefillWs &ws, hipStream_t st) {
   Fold fold{};
   if (proj_folds(d, batch, total)) fold = Fold{cu, batch, (int)(total / batch)};
-  else launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, st);
+  else launch_prefill_setup(d, cu, batch, total, max_len, ws.seq_id, ws.pos, ws.rope, cache, slots, pack_of(d, w, total, ws), st);
   launch_proj_gemm(d, w, x, (int)total, ws, cache, slots, max_len, false, fold, st);
 }
 
@@ -51,7 +51,7 @@ int tuned_prefill_chunk(const Dims &d, const gta_weights &w, const void *x, cons
                         int64_t total, int max_chunk, const gta_cache &cache, const int32_t *slots, void *out,
                         const PrefillWs &ws, hipStream_t st) {
   const int M = (int)total;
-  launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, st);
+  launch_prefill_chunk_setup(d, cu, batch, total, ws.seq_id, ws.pos, ws.rope, ws.prefix, cache, slots, pack_of(d, w, total, ws), st);
   launch_proj_gemm(d, w, x, M, ws, &cache, slots, max_chunk, true, Fold{}, st);
   void *heads = w.wo ? ws.o : out;
   const bool fuse = attn_decoder_fusable(d, cache.max_seq);
