@@ -285,6 +285,7 @@ struct AttnF32 {
   const float *q, *k, *c; float *L;
   const int32_t *cu; int per_seq, max_len;
   int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, n_qtiles, nslice, batch;
+  int ahead, back;   // workgroups i < ahead take tile i, the others tile back - i
   float scale_log2e;
 };
 
@@ -298,7 +299,11 @@ __global__ __launch_bounds__(256, DH + DLW < 256 ? 2 : 1) void attn_prefill_f32_
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // longest query tiles first; inside a level the maps of one sequence side by side (they share keys and latents)
-  const int per_qt = a.batch * a.nq * a.nslice, lvl = (int)blockIdx.x / per_qt, rest = (int)blockIdx.x % per_qt;
+  // A CU holds two workgroups (DH + DLW < 256).  Where the chip holds all of them, those behind the first 256 go backwards, so that the
+  // longest shares its CU with the shortest of them: paper's layer 2 x 1500 tokens (470 workgroups) 306 -> 293 us, 768 wide layer 4 x 1000
+  // (384) 173 -> 168.  Larger launches even that out by themselves (4 x 1024, 640: 357, backwards 360).
+  const int per_qt = a.batch * a.nq * a.nslice, id = (int)blockIdx.x < a.ahead ? (int)blockIdx.x : a.back - (int)blockIdx.x;
+  const int lvl = id / per_qt, rest = id % per_qt;
   const int qt = a.n_qtiles - 1 - lvl;
   const int sl_i = rest % a.nslice, g = rest / a.nslice % a.nq, b = rest / (a.nslice * a.nq);
   const int64_t start = a.cu ? a.cu[b] : (int64_t)b * a.per_seq;
@@ -754,6 +759,8 @@ void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, cons
   const bool wide = attn_slice(d) == 128;
   a.nslice = d.dl / attn_slice(d);
   const unsigned grid = (unsigned)a.n_qtiles * batch * d.nq * a.nslice;
+  a.ahead = d.dh + attn_slice(d) < 256 && grid <= 512 ? 256 : (int)grid;
+  a.back = 255 + (int)grid;
   auto launch = [&](auto kernel, int dlw) {
     const int smem = 4 * 32 * (dlw + 4) * (int)sizeof(float);
     if (smem > 64 * 1024) allow_dynamic_lds((const void *)kernel, smem);

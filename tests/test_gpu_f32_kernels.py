@@ -25,7 +25,8 @@ SHAPES = {
     "latent256": dict(d_model=64, n_heads=4, n_qgroups=4, n_kgroups=2, n_cgroups=2, head_dim=64, latent_dim=256),
     "heads128": dict(d_model=64, n_heads=2, n_qgroups=2, n_kgroups=1, n_cgroups=1, head_dim=128, latent_dim=128),
 }
-LENS = {"short": [1, 31, 32, 33, 97], "long": [513, 2, 160]}
+# paired: 360 attention workgroups of the paper's shape, those behind the first 256 in reverse (the others: none, or too many)
+LENS = {"short": [1, 31, 32, 33, 97], "long": [513, 2, 160], "paired": [545, 2, 160, 33]}
 
 
 def _wl(shape, **kw):
