@@ -88,6 +88,7 @@ struct AttnTile {
   static constexpr int SMEM = cmax(cmax(BQ * OUT_PITCH, NSTAGE * STAGE), MERGE);
   // the hand-scheduled main loop deals 16 softmax slices over 2 * NDLB steps; others take the plain loop
   static constexpr bool PIPELINED = NDLB == 8 || NDLB == 4;
+  static constexpr bool PAIRED = KS == 1 && DLW == 256;   // which workgroups share a CU is chosen (launch_tile)
   static_assert((DH == 64 || DH == 128) && (DLW == 64 || DLW == 128 || DLW == 256) && (KS == 1 || KS == 2), "tile");
   static_assert((K_INSTR >= NW && C_INSTR >= NW) || (KS == 2 && NW == 8), "load instructions of a step divide over the waves");
   static_assert(SMEM <= 160 * 1024, "LDS budget");
@@ -105,6 +106,7 @@ struct AttnArgs {
   int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, ndlc, batch;
   // query tiles of the longest sequence; bound of the levels (tile_of_rank); how workgroups get theirs (launch_tile)
   int n_qtiles, levels, numbering, spread, eighth;
+  int ahead, back;           // workgroups i < ahead work as number i, the others as number back - i
   float scale_log2e;
   // fused value decoder (kernel template flag): O_i = (L_g W_{P,i}) * Sigmoid(gate) for the heads of g
   const bf16 *wp, *gate;     // [n_h, d_l, d_h]; gate pre-activations [total, n_h*d_h] or NULL (gate off)
@@ -296,13 +298,13 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
     if ((int)blockIdx.x >= a.workgroups) { commit_chunk(a, ((int)blockIdx.x - a.workgroups) * T::NT + tid); return; }
   const int per = FUSE ? a.nq : a.nq * a.ndlc * a.splits;    // workgroups of a query tile
   int u, r;                                                  // rank of the tile, workgroup of the tile
+  int id = !T::PAIRED || (int)blockIdx.x < a.ahead ? (int)blockIdx.x : a.back - (int)blockIdx.x;
   if (a.spread) {
-    int id = (int)blockIdx.x;
     if (a.eighth && id < 8 * a.eighth) id = (id & 7) * a.eighth + (id >> 3);
     u = id / per; r = id % per;
   }
   else {   // eight tiles at a time, one per XCD, in turn from either end
-    const int x = (int)blockIdx.x & 7, at = (int)blockIdx.x >> 3, round = at / per;
+    const int x = id & 7, at = id >> 3, round = at / per;
     r = at % per;
     u = round * 8 + (round & 1 ? 7 - x : x);
   }
@@ -931,6 +933,12 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   int smem = T::SMEM;
   if constexpr (FUSE) smem = FusedDecoder<T>::SMEM;
   a.workgroups = (int)(tiles * a.ndlc * d.nq * a.splits);
+  // Two workgroups of four waves share a CU: where the chip holds all of them, those behind the first 256 go backwards, so that the
+  // longest shares its CU with the shortest of them (a tile's workgroups stay on one XCD): 1B shape 6 x 1100 172 -> 164 us, 7 x
+  // 200..1000 113 -> 109, 8 x 1000 183 -> 180.  Not with narrower latent tiles (16 x 700 of the paper's layer 121.7 / 121.0, 8 x 100,
+  // which has too few for it, 39.7 / 39.9).
+  a.ahead = a.workgroups <= 512 ? 256 : a.workgroups;
+  a.back = 255 + a.workgroups;
   auto launch = [&](auto kernel, int more) {
     allow_dynamic_lds((const void *)kernel, smem);
     kernel<<<(unsigned)(a.workgroups + more), T::NT, smem, st>>>(a);
@@ -961,7 +969,12 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
   // paper 16 x 700 154 / 160 (384), but 2 x 1000 99 / 91 (64); up to 256 keys it is never worth it: 1 x 128 40.7 / 42.2.
   const int64_t half = half_workgroups(d, batch, max_len, DLW);
   a.splits = 1;
-  if (half > 512 || max_keys <= 256 || (half > 256 && max_keys <= 1024)) {
+  // Fresh prompts of one length whose workgroups nearly fill the chip keep one half, the longest paired with the shortest on a CU
+  // (launch_tile): 1B shape 4 x 2000 203 / 197 (two halves first), 5 x 1500 188 / 179 (480), 6 x 1100 164 / 156 (432), but 3 x 1500 129 /
+  // 131 (288), 2 x 3500 215 / 219 (448), 1 x 8000 352 / 358.  Chunks of one length gain as much behind equal caches (8 x 600
+  // behind 4000 315 / 271) and lose behind unequal ones, which the host does not see (behind 200..4000 226 / 246).
+  const bool alike = DLW == 256 && !a.prefix && batch > 2 && a.total == (int64_t)batch * max_len && half > 384;
+  if (half > 512 || max_keys <= 256 || (half > 256 && max_keys <= 1024) || alike) {
     launch_tile<AttnTile<DH, DLW, 1>, FUSE>(a, d, batch, max_len, st);
     return;
   }

@@ -59,6 +59,20 @@ def test_fresh(shape, lens, bound):
             _check(wl, w, x[cu[b]:cu[b + 1]], none, none, 0, out[cu[b]:cu[b + 1]], f"{shape} {lens} sequence {b}")
 
 
+@pytest.mark.parametrize("lens", [[1000, 300, 129, 1, 700, 640, 900], [1030] * 6], ids=["ragged", "alike"])
+def test_paired_workgroups(lens):
+    """257 to 512 workgroups of four waves: those behind the first 256 go backwards.  Short ragged prompts (280 workgroups), and
+    prompts of one length, which stay with four waves beyond 1024 keys (432)."""
+    wl, w, x, _ = _setup("1b", sum(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = U.f64(U.run_prefill(wl, U.upload_weights(w, "bf16"), x, cu))
+    none = np.zeros((0, 1))
+    for b in range(len(lens)) if len(set(lens)) > 1 else (0, 3):
+        _check(wl, w, x[cu[b]:cu[b + 1]], none, none, 0, out[cu[b]:cu[b + 1]], f"{lens} sequence {b}")
+    if len(set(lens)) == 1:   # every row is written
+        assert (np.abs(out).max(axis=1) > 0).all()
+
+
 @pytest.mark.parametrize("chunk", [False, True])
 @pytest.mark.parametrize("batch", [3, 63, 64, 65, 130])
 @pytest.mark.parametrize("shape", ["1b", "paper"])
