@@ -42,12 +42,12 @@ TRAFFIC_SOURCE = {
     ("decode_b64_8k_bf16", "decode_attn_kernel"): ("bench_decode8k.txt", "decode_attn_kernel"),
     ("decode_b512_2k_bf16", "decode_attn_kernel"): ("bench_decode512.txt", "decode_attn_kernel"),
     ("prefill_1b_bf16", "attn_prefill_kernel"): ("bench_prefill.txt", "attn_prefill_kernel"),
-    ("prefill_1b_bf16", "projection"): ("bench_prefill.txt", "proj_gemm_kernel"),
-    ("prefill_1b_bf16", "decoder"): ("bench_prefill.txt", "decoder_pair_kernel"),
-    ("prefill_1b_bf16", "output_projection"): ("bench_prefill.txt", "plain_gemm_kernel"),
+    ("prefill_1b_bf16", "projection"): ("bench_prefill.txt", "proj_stream_kernel"),
+    ("prefill_1b_bf16", "decoder"): ("bench_prefill.txt", "decoder_stream_kernel"),
+    ("prefill_1b_bf16", "output_projection"): ("bench_prefill.txt", "plain_stream_kernel"),
     ("varlen_prefill_bf16", "attn_prefill_kernel"): ("bench_varlen.txt", "attn_prefill_kernel"),
-    ("varlen_prefill_bf16", "projection"): ("bench_varlen.txt", "proj_gemm_kernel"),
-    ("varlen_prefill_bf16", "decoder"): ("bench_varlen.txt", "decoder_pair_kernel"),
+    ("varlen_prefill_bf16", "projection"): ("bench_varlen.txt", "proj_stream_kernel"),
+    ("varlen_prefill_bf16", "decoder"): ("bench_varlen.txt", "decoder_stream_kernel"),
     ("gta1b_prefill_b32_t2048", "attn_prefill_kernel"): ("bench_paper.txt", "AttnTile<64, 128, 1> plain"),
     ("gta1b_decode_b64_t2048", "decode_attn_kernel"): ("bench_paper.txt", "decode_narrow_kernel"),
 }
