@@ -285,11 +285,11 @@ struct AttnF32 {
   const float *q, *k, *c; float *L;
   const int32_t *cu; int per_seq, max_len;
   int nq, qpk, qpc, wq_w, wk_w, wc_w, dl, n_qtiles, nslice, batch;
-  int ahead, back;   // workgroups i < ahead take tile i, the others tile back - i
+  int back;   // PAIR: workgroups i < 256 take tile i, the others tile back - i
   float scale_log2e;
 };
 
-template <int DH, int DLW>
+template <int DH, int DLW, bool PAIR>
 __global__ __launch_bounds__(256, DH + DLW < 256 ? 2 : 1) void attn_prefill_f32_kernel(AttnF32 a) {
   constexpr int NT = DLW / 32, OP = DLW + 4;
   typedef float cvec __attribute__((ext_vector_type(NT)));
@@ -301,8 +301,9 @@ __global__ __launch_bounds__(256, DH + DLW < 256 ? 2 : 1) void attn_prefill_f32_
   // longest query tiles first; inside a level the maps of one sequence side by side (they share keys and latents)
   // A CU holds two workgroups (DH + DLW < 256).  Where the chip holds all of them, those behind the first 256 go backwards, so that the
   // longest shares its CU with the shortest of them: paper's layer 2 x 1500 tokens (470 workgroups) 306 -> 293 us, 768 wide layer 4 x 1000
-  // (384) 173 -> 168.  Larger launches even that out by themselves (4 x 1024, 640: 357, backwards 360).
-  const int per_qt = a.batch * a.nq * a.nslice, id = (int)blockIdx.x < a.ahead ? (int)blockIdx.x : a.back - (int)blockIdx.x;
+  // (384) 173 -> 168.  Larger launches even that out by themselves (4 x 1024, 640: 357, backwards 360) and
+  // are kernels of their own: the choice alone, made at run time, took 0.6 of their 360 us.
+  const int per_qt = a.batch * a.nq * a.nslice, id = !PAIR || blockIdx.x < 256 ? (int)blockIdx.x : a.back - (int)blockIdx.x;
   const int lvl = id / per_qt, rest = id % per_qt;
   const int qt = a.n_qtiles - 1 - lvl;
   const int sl_i = rest % a.nslice, g = rest / a.nslice % a.nq, b = rest / (a.nslice * a.nq);
@@ -759,18 +760,20 @@ void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, cons
   const bool wide = attn_slice(d) == 128;
   a.nslice = d.dl / attn_slice(d);
   const unsigned grid = (unsigned)a.n_qtiles * batch * d.nq * a.nslice;
-  a.ahead = d.dh + attn_slice(d) < 256 && grid <= 512 ? 256 : (int)grid;
+  const bool pair = grid > 256 && grid <= 512;
   a.back = 255 + (int)grid;
   auto launch = [&](auto kernel, int dlw) {
     const int smem = 4 * 32 * (dlw + 4) * (int)sizeof(float);
     if (smem > 64 * 1024) allow_dynamic_lds((const void *)kernel, smem);
     kernel<<<grid, 256, smem, st>>>(a);
   };
-#define GTA_ATTN(DH) if (wide) launch(attn_prefill_f32_kernel<DH, 128>, 128); else launch(attn_prefill_f32_kernel<DH, 64>, 64)
+#define GTA_ATTN_OF(DH, DLW) if (pair && DH + DLW < 256) launch(attn_prefill_f32_kernel<DH, DLW, DH + DLW < 256>, DLW); else launch(attn_prefill_f32_kernel<DH, DLW, false>, DLW)
+#define GTA_ATTN(DH) if (wide) { GTA_ATTN_OF(DH, 128); } else { GTA_ATTN_OF(DH, 64); }
   if (d.dh == 32) { GTA_ATTN(32); }
   else if (d.dh == 64) { GTA_ATTN(64); }
   else { GTA_ATTN(128); }
 #undef GTA_ATTN
+#undef GTA_ATTN_OF
 }
 
 void launch_decode_attn_f32(const Dims &d, const float *q, const int32_t *oldlen, const gta_cache &cache, const int32_t *slots,
