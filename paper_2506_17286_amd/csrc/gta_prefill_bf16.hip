@@ -746,6 +746,18 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
       for (int mm = 0; mm < 8; ++mm)
 #pragma unroll
         for (int i = 0; i < 8; ++i) lf[mm][i] = (bf16)(acc[mm / 2][mm % 2 * 8 + i] * inv);
+      // i holds column 16 mm + 8 (i/4) + 4 h + i%4 so far.  Swapped across the lane halves it is column 16 mm + 8 h + i, the order in
+      // which the decoder's own kernels add up, and the results are theirs bit for bit.
+#pragma unroll
+      for (int mm = 0; mm < 8; ++mm) {
+        u32x4 v = __builtin_bit_cast(u32x4, lf[mm]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const u32x2 r = __builtin_amdgcn_permlane32_swap(v[i], v[i + 2], false, false);
+          v[i] = r[0]; v[i + 2] = r[1];
+        }
+        lf[mm] = __builtin_bit_cast(bf16x8, u32x4{v[0], v[1], v[2], v[3]});
+      }
     }
     if constexpr (T::KS == 2) {
       bf16x8 *lx = reinterpret_cast<bf16x8 *>(smem + F::L_OFF + qw * 8192) + lane;
@@ -760,7 +772,7 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
       }
     }
     const int wrow = (lane & 15) >> 2;
-    const int wfr = (4 * h + wrow) * 128 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8, wsw = (wrow >> 1) * 64;
+    const int wfr = (8 * h + wrow) * 128 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8, wsw = (wrow >> 1) * 64;
     char *io = smem + F::IO_OFF + wave * 4096;
 #pragma unroll
     for (int i = 0; i < F::HPW; ++i) {
@@ -788,7 +800,7 @@ __global__ __launch_bounds__(T::NT, T::KS == 1 && T::DH == 64 && T::DLW == 128 ?
         for (int tn = 0; tn < 2; ++tn) {
           const char *wp = wb + mm * 16 * 128 + (tn * 64 ^ wsw);
           const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp));
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 8 * 128));
+          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(wp + 4 * 128));
           const s16x8 w8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
           z[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w8), lf[mm], z[tn], 0, 0, 0);
         }

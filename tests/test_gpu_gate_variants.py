@@ -37,6 +37,32 @@ def test_fused_decoder(longest, gate):
     _prefill("paper", gate, [longest, 129, 97, 32, 1])
 
 
+@pytest.mark.parametrize("lens", [[5000], [2048, 1500, 900, 480, 33, 1]], ids=["key halves", "four waves"])
+def test_fused_decoder_is_the_stages_bit_for_bit(lens):
+    """The decoder fused into the attention rounds L as the attention stage does and adds up its products in the order of the decoder
+    stage's 256-row tiles, so without a gate (whose exponentials differ) the heads of the whole call are those of the three stages."""
+    wl = W.scaled(SHAPES["paper"], d_model=256, batch=len(lens), seqlen=max(lens), min_seqlen=None)
+    cfg = B.config_of(wl)
+    cfg.gate = B.GATE_CODES[False]
+    rng = W.make_rng(wl)
+    wdev = U.upload_weights(W.draw_weights(wl, rng, std=0.15), wl.dtype)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(cu[-1])
+    x = W.draw_hidden(wl, rng, total)
+    got = U.run_prefill(wl, wdev, x, cu, gate=False)
+    xd, cud, gw = B.to_device(x, wl.dtype), torch.from_numpy(cu).cuda(), B.make_weights(wdev)
+    kw, cw = wl.kv_width
+    q, k, c, g, l, heads = (torch.full((total, n), float("nan"), dtype=torch.bfloat16, device="cuda") for n in
+                            (wl.n_qgroups * wl.head_dim, kw, cw, wl.n_heads * wl.head_dim, wl.n_qgroups * wl.latent_dim, wl.n_heads * wl.head_dim))
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_PREFILL, len(lens), total, max(lens)))
+    B.gta_prefill_projection(cfg, gw, xd, cud, len(lens), total, max(lens), q, k, c, g, ws)
+    B.gta_prefill_attention(cfg, q, k, c, cud, len(lens), total, max(lens), l)
+    B.gta_prefill_decoder(cfg, gw, l, g, total, heads)
+    torch.cuda.synchronize()
+    assert torch.isfinite(heads.float()).all()
+    assert torch.equal(got, heads), f"{int((got != heads).sum())} of {heads.numel()} differ"
+
+
 def _prefill(shape, gate, lens):
     wl = W.scaled(SHAPES[shape], batch=len(lens), seqlen=max(lens), min_seqlen=None)
     rng = W.make_rng(wl)
