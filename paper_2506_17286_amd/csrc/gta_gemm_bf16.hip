@@ -670,8 +670,9 @@ struct ProjStreamEpi {
           for (int i = 0; i < 4; ++i) {
             const float c = turn ? cs[i] : 1.f, sv = turn ? sn[i] : 0.f;
             const float lo = acc[tn][tm][rq * 4 + i], hi = acc[tn_hi][tm][rq * 4 + i];
-            acc[tn][tm][rq * 4 + i] = lo * c - hi * sv;
-            acc[tn_hi][tm][rq * 4 + i] = hi * c + lo * sv;
+            // spelled out, as the product that is rounded by itself decides the last bit: against packed weights hi cos, else lo sin
+            acc[tn][tm][rq * 4 + i] = fmaf(lo, c, -(hi * sv));
+            acc[tn_hi][tm][rq * 4 + i] = PACKED ? fmaf(lo, sv, hi * c) : fmaf(hi, c, lo * sv);
           }
         }
         __builtin_amdgcn_sched_barrier(0);   // else the values of all groups are asked for at once: spills

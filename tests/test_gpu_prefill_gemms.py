@@ -64,6 +64,43 @@ def test_rounds_of_tiles(layer, rows):
     _check(dict(LAYERS, ten=_wl(n_heads=12, latent_dim=512))[layer], rows, True)
 
 
+ROTATED = {"packed64": _wl(head_dim=64, n_heads=20, n_qgroups=5, n_kgroups=1, latent_dim=128), "packed128": _wl(n_heads=10, n_qgroups=5, n_kgroups=1),
+           "matrices": _wl()}
+
+
+@pytest.mark.parametrize("layer", list(ROTATED))
+def test_rotation_bits(layer):
+    """Rows of X with a single one give weights as values before the rotation, exactly, and the rotation is one product rounded to fp32
+    and one fused multiply-add.  Which product comes first is part of the result's last fp32 bit: hi cos first against packed
+    weights, lo sin first against the four matrices."""
+    wl, rows = ROTATED[layer], 9000
+    H, dh, nq, nk, nh, dl = wl.d_model, wl.head_dim, wl.n_qgroups, wl.n_kgroups, wl.n_heads, wl.latent_dim
+    g = torch.Generator(device="cuda")
+    g.manual_seed(wl.seed)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    w = {"wq": rand(H, nq * dh), "wk": rand(H, nk * dh), "wc": rand(H, dl), "wg": rand(H, nh * dh), "wp": rand(nh, dl, dh), "wo": None}
+    at = torch.arange(rows, device="cuda") % H
+    x = torch.zeros((rows, H), dtype=torch.bfloat16, device="cuda")
+    x[torch.arange(rows, device="cuda"), at] = 1.
+    mk = lambda n: torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    out = {"q": mk(nq * dh), "k": mk(nk * dh), "c": mk(dl), "g": mk(nh * dh)}
+    cfg = B.config_of(wl)
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_PREFILL, 1, rows, rows))
+    B.gta_prefill_projection(cfg, B.make_weights(w), x, None, 1, rows, rows, out["q"], out["k"], out["c"], out["g"], ws)
+    ang = torch.arange(rows, device="cuda", dtype=torch.float64)[:, None] * \
+        wl.rope_base ** (-torch.arange(dh // 2, device="cuda", dtype=torch.float64) * 2 / dh)
+    c, s = ang.cos().float()[:, None], ang.sin().float()[:, None]
+    fma = lambda a, b, z: (a.double() * b.double() + z.double()).float()   # the product is exact
+    for name, groups in (("q", nq), ("k", nk)):
+        lo, hi = w["w" + name][at].float().view(rows, groups, dh).split(dh // 2, dim=-1)
+        ref = torch.cat([fma(lo, c, -(hi * s)), fma(hi, c, lo * s) if layer == "matrices" else fma(lo, s, hi * c)], dim=-1)
+        ref = ref.bfloat16().view(rows, -1)
+        # a cosine or sine may lie next to a tie of its own rounding to fp32 (2^-29 of them, as its 64-bit error), and so may a result
+        assert int((out[name] != ref).sum()) <= 2, f"{name}: {int((out[name] != ref).sum())} of {ref.numel()} differ"
+    for name in ("c", "g"):
+        assert torch.equal(out[name], w["w" + name][at])
+
+
 def _check(wl, rows, gate):
     cfg = B.config_of(wl)
     cfg.gate = B.GATE_CODES[gate]
