@@ -665,14 +665,14 @@ struct ProjStreamEpi {
 #pragma unroll
         for (int hd = 0; hd < heads; ++hd) {
           const int tn = hd * tiles_head + (g / 4) % tiles_half, tn_hi = tn + tiles_half;
-          const bool turn = n0 + hd * DH < b2 && rot[tm];   // columns behind q and k take the identity
+          const bool turn = n0 + hd * DH < b2 && rot[tm];   // columns behind q and k stay as they are, infinities and all
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float c = turn ? cs[i] : 1.f, sv = turn ? sn[i] : 0.f;
             const float lo = acc[tn][tm][rq * 4 + i], hi = acc[tn_hi][tm][rq * 4 + i];
             // spelled out, as the product that is rounded by itself decides the last bit: against packed weights hi cos, else lo sin
-            acc[tn][tm][rq * 4 + i] = fmaf(lo, c, -(hi * sv));
-            acc[tn_hi][tm][rq * 4 + i] = PACKED ? fmaf(lo, sv, hi * c) : fmaf(hi, c, lo * sv);
+            const float tl = fmaf(lo, cs[i], -(hi * sn[i])), th = PACKED ? fmaf(lo, sn[i], hi * cs[i]) : fmaf(hi, cs[i], lo * sn[i]);
+            acc[tn][tm][rq * 4 + i] = turn ? tl : lo;
+            acc[tn_hi][tm][rq * 4 + i] = turn ? th : hi;
           }
         }
         __builtin_amdgcn_sched_barrier(0);   // else the values of all groups are asked for at once: spills

@@ -101,6 +101,34 @@ def test_rotation_bits(layer):
         assert torch.equal(out[name], w["w" + name][at])
 
 
+@pytest.mark.parametrize("rows", [100, 1400, 2700, 9000])
+def test_infinite_weights_stay_in_their_columns(rows):
+    """Q and K end in the middle of a wave's 128 columns (320 of 256 + 64), so that latent columns go through the rotation's
+    epilogue: a column of infinities must not reach the one that would be its partner.  24, 264, 516 and 1692 tiles of 64 x 128."""
+    wl = _wl(head_dim=64, n_heads=16, n_qgroups=4, n_kgroups=1, latent_dim=128)
+    H, dh, nq, nk, nh, dl = wl.d_model, wl.head_dim, wl.n_qgroups, wl.n_kgroups, wl.n_heads, wl.latent_dim
+    g = torch.Generator(device="cuda")
+    g.manual_seed(wl.seed + rows)
+    rand = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).bfloat16()
+    w = {"wq": rand(H, nq * dh, std=H ** -0.5), "wk": rand(H, nk * dh, std=H ** -0.5), "wc": rand(H, dl, std=H ** -0.5),
+         "wg": rand(H, nh * dh, std=H ** -0.5), "wp": rand(nh, dl, dh), "wo": None}
+    x = rand(rows, H).abs() + 1.
+    w["wc"][3, 5] = w["wc"][7, 40] = float("inf")
+    w["wg"][9, 70] = float("-inf")
+    mk = lambda n: torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    out = {"q": mk(nq * dh), "k": mk(nk * dh), "c": mk(dl), "g": mk(nh * dh)}
+    cfg = B.config_of(wl)
+    ws = B.alloc_workspace(B.gta_workspace_bytes(cfg, B.GTA_MODE_PREFILL, 1, rows, rows))
+    B.gta_prefill_projection(cfg, B.make_weights(w), x, None, 1, rows, rows, out["q"], out["k"], out["c"], out["g"], ws)
+    inf = {"q": {}, "k": {}, "c": {5: float("inf"), 40: float("inf")}, "g": {70: float("-inf")}}
+    for name in ("c", "g"):
+        for col, v in inf[name].items():
+            assert bool((out[name][:, col] == v).all()), f"{name} column {col}"
+        rest = [i for i in range(out[name].shape[1]) if i not in inf[name]]
+        _close(out[name][:, rest], x.double() @ w["w" + name][:, rest].double(), name)
+    assert torch.isfinite(out["q"].float()).all() and torch.isfinite(out["k"].float()).all()
+
+
 def _check(wl, rows, gate):
     cfg = B.config_of(wl)
     cfg.gate = B.GATE_CODES[gate]
