@@ -1085,19 +1085,26 @@ size_t proj_packed_bytes(const Dims &d) {
 // tokens (532) 90.3 / 86.9, 3200 (700) 108.3 / 98.4, 4 x 1000 (630 in W_O) 80.5 / 77.4; 768 wide layer 4 x 1000 62.6 / 59.3.  Alone the
 // projections are level at 1200 (38.4 / 38.5) and 2000 tokens (paper, 448 tiles: 31.3 / 32.1).  Contractions beyond 2048 and shapes
 // that no stream takes keep one and a half rounds: 8 x 128 + 1024 shape 600 tokens (560) 97.9 / 98.7, 700 (616) 102.5 / 103.1.
-static bool short_gemm_ok(int M, int N, int K, bool stream) {
-  return (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= (stream && K <= 2048 ? 512 : 768);
+static int short_tiles(int K, bool stream) { return stream && K <= 2048 ? 512 : 768; }
+static bool short_gemm_ok(int M, int N, int tiles) { return (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= tiles; }
+// Packed weights have to be laid out first: with heads of 128 (those of 64 have 64-row tiles of only 64 columns) and long contractions
+// the 64-row tiles stay ahead for longer.  Whole calls, 64-row tiles / stream: 2048 -> 3456 513 tiles 72.4 / 76.3 us, 567 75.8 / 78.6, 675
+// 82.4 / 83.6, 729 85.3 / 84.3; 2048 -> 3200 525 74.4 / 77.0, 600 78.6 / 80.2, 675 83.0 / 83.9; 1792 -> 3072 528 75.0 / 76.6, 648 81.1 / 81.8;
+// but 1536 -> 2688 525 73.6 / 73.9, 609 78.8 / 78.2, 672 87.4 / 81.2; 1024 -> 3456 675 70.0 / 68.7; 1280 -> 2304 630 81.0 / 79.8.  Heads of
+// 64: 2048 -> 2752 528 67.6 / 67.9, 550 69.5 / 68.9, 638 75.0 / 72.3.
+static int proj_short_tiles(const Dims &d) {
+  if (!proj_direct_big(d) && proj_packed_ok(d) && d.dh == 128 && d.H > 1536) return std::max(704, short_tiles(d.H, true));
+  return short_tiles(d.H, proj_direct_big(d) || proj_packed_ok(d));
 }
-static bool proj_streams(const Dims &d) { return proj_direct_big(d) || proj_packed_ok(d); }
 static bool decoder_streams(const Dims &d) { return d.dh == 128 && d.hpq % 2 == 0 && d.dl % 128 == 0 && d.dl >= 256; }
 
 bool proj_folds(const Dims &d, int batch, int64_t M) {
-  return batch <= kFoldBatch && short_gemm_ok((int)M, d.wtot, d.H, proj_streams(d)) && short_proj_folds(d, M);
+  return batch <= kFoldBatch && short_gemm_ok((int)M, d.wtot, proj_short_tiles(d)) && short_proj_folds(d, M);
 }
 
 PackWeights pack_of(const Dims &d, const gta_weights &w, int64_t M, const PrefillWs &ws) {
   PackWeights p{};
-  if (proj_direct_big(d) || !proj_packed_ok(d) || short_gemm_ok((int)M, d.wtot, d.H, true)) return p;
+  if (proj_direct_big(d) || !proj_packed_ok(d) || short_gemm_ok((int)M, d.wtot, proj_short_tiles(d))) return p;
   p.w[0] = w.wq; p.w[1] = w.wk; p.w[2] = w.wc; p.w[3] = w.wg;
   p.width[0] = d.wq_w; p.width[1] = d.wk_w; p.width[2] = d.wc_w; p.width[3] = d.wg_w;
   p.K = d.H; p.wtot = d.wtot; p.wpad = proj_packed_width(d); p.dst = ws.wpack;
@@ -1122,7 +1129,7 @@ void launch_proj_gemm(const Dims &d, const gta_weights &w, const void *x, int M,
     a.max_batch = cache->max_batch; a.max_seq = cache->max_seq;
     a.pm = page_map_of(*cache);
   }
-  if (short_gemm_ok(M, d.wtot, d.H, proj_streams(d))) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
+  if (short_gemm_ok(M, d.wtot, proj_short_tiles(d))) { launch_short_proj(d, w, x, M, ws, cache, slots, max_len, rope_by_token, fold, st); return; }
   if (proj_direct_big(d)) {
     launch_stream(proj_stream_kernel<128, false>, ProjStream{{}, a, nullptr, 0}, M, d.wtot, st);
   } else if (proj_packed_ok(d)) {
@@ -1174,7 +1181,7 @@ void launch_decoder_gemm(const Dims &d, const void *L, const void *wp, const voi
   a.L = (const bf16 *)L; a.ldl = (int64_t)d.nq * d.dl; a.M = M;
   a.wp = (const bf16 *)wp; a.dl = d.dl; a.dh = d.dh; a.hpq = d.hpq; a.nh = d.nh;
   a.g = (const bf16 *)g; a.gate = d.gate; a.out = (bf16 *)out;
-  if (short_gemm_ok(M, d.nh * d.dh, d.dl, decoder_streams(d))) { launch_short_decoder(d, L, wp, g, out, M, st); return; }
+  if (short_gemm_ok(M, d.nh * d.dh, short_tiles(d.dl, decoder_streams(d)))) { launch_short_decoder(d, L, wp, g, out, M, st); return; }
   if (decoder_streams(d)) {
     launch_stream(d.gate == kGateOff ? decoder_stream_kernel<kGateOff> : d.gate == kGateSigmoid ? decoder_stream_kernel<kGateSigmoid>
                   : decoder_stream_kernel<-1>, DecoderStream{{}, a}, M, d.nh * 128, st);
@@ -1200,7 +1207,7 @@ void launch_plain_gemm(const void *A, int64_t lda, int M, int N, int K, const vo
     return;
   }
   const bool stream = N % 256 == 0 && K % 128 == 0 && K >= 256;
-  if (short_gemm_ok(M, N, K, stream)) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
+  if (short_gemm_ok(M, N, short_tiles(K, stream))) { launch_short_plain(A, lda, M, N, K, B, C, st); return; }
   if (stream) launch_stream(plain_stream_kernel, PlainStream{{}, a}, M, N, st);
   else launch<TileHead>(plain_gemm_kernel<TileHead>, a, (N / 128) * ((M + 255) / 256), st);
 }

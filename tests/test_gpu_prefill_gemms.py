@@ -54,6 +54,12 @@ def test_second_tile_on_a_cu(layer, rows):
     _check(LAYERS[layer], rows, True)
 
 
+@pytest.mark.parametrize("rows", [3200, 3201])
+def test_packed_weights_of_long_contractions(rows):
+    """Heads of 128, 2048 rows of packed weights: 700 tiles of 64 x 128, the last on those, and 714, the first on 256 x 256 tiles."""
+    _check(_wl(d_model=2048, n_heads=8, n_qgroups=4, n_kgroups=1, latent_dim=128), rows, True)
+
+
 @pytest.mark.parametrize("layer,rows", [("k256", 3264), ("k256", 3265), ("k256", 4993), ("k256", 13057), ("k256", 19457), ("packed", 9345),
                                         ("packed", 13825), ("ten", 11137)])
 def test_rounds_of_tiles(layer, rows):
