@@ -299,10 +299,13 @@ __global__ __launch_bounds__(256, DH + DLW < 256 ? 2 : 1) void attn_prefill_f32_
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ln = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // longest query tiles first; inside a level the maps of one sequence side by side (they share keys and latents)
-  // A CU holds two workgroups (DH + DLW < 256).  Where the chip holds all of them, those behind the first 256 go backwards, so that the
-  // longest shares its CU with the shortest of them: paper's layer 2 x 1500 tokens (470 workgroups) 306 -> 293 us, 768 wide layer 4 x 1000
-  // (384) 173 -> 168.  Larger launches even that out by themselves (4 x 1024, 640: 357, backwards 360) and
-  // are kernels of their own: the choice alone, made at run time, took 0.6 of their 360 us.
+  // A CU holds two workgroups (DH + DLW < 256; heads of 32 and latent tiles of 64: three, but is given a second one only when all have
+  // one).  Where the chip holds all of them, those behind the first 256 go backwards, so that the longest shares its CU with the
+  // shortest of them: paper's layer 2 x 1500 tokens (470 workgroups) 306 -> 293 us, 768 wide layer 4 x 1000 (384) 173 -> 168, 16 heads of
+  // 32, 4 maps, 9 x 400 (468) 61.2 -> 59.3.  A few behind the first 256 lose more than they gain: 768 wide layer 3 x 1000 (288) 149.9 -> 150.7,
+  // 5 x 600 (285) 112.7 -> 113.1, paper's layer 2 x 896 (280) 200.9 -> 201.5, but 2 x 928 (290) 206.8 -> 204.3.  Larger launches even
+  // it out by themselves (4 x 1024, 640: 357, backwards 360) and are kernels of their own: the choice alone, made at run time, took
+  // 0.6 of their 360 us.
   const int per_qt = a.batch * a.nq * a.nslice, id = !PAIR || blockIdx.x < 256 ? (int)blockIdx.x : a.back - (int)blockIdx.x;
   const int lvl = id / per_qt, rest = id % per_qt;
   const int qt = a.n_qtiles - 1 - lvl;
@@ -760,7 +763,7 @@ void launch_attn_prefill_f32(const Dims &d, const float *q, const float *k, cons
   const bool wide = attn_slice(d) == 128;
   a.nslice = d.dl / attn_slice(d);
   const unsigned grid = (unsigned)a.n_qtiles * batch * d.nq * a.nslice;
-  const bool pair = grid > 256 && grid <= 512;
+  const bool pair = grid > 288 && grid <= 512;
   a.back = 255 + (int)grid;
   auto launch = [&](auto kernel, int dlw) {
     const int smem = 4 * 32 * (dlw + 4) * (int)sizeof(float);
