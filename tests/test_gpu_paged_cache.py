@@ -147,6 +147,67 @@ def test_prefill_writes_paged_caches(shape, page_size):
         U.assert_close(cc[s, :lens[b]], Cref[cu[b]:cu[b + 1]], wl.dtype, "C cache")
 
 
+@pytest.mark.parametrize("mode,page_size", [("fresh", 16), ("fresh", 64), ("chunk", 64)])
+@pytest.mark.parametrize("shape,tokens", [("1b", 1300), ("1b", 6500), ("1b", 7000), ("paper", 2400), ("paper", 9400), ("paper", 14000)])
+def test_many_tokens_on_paged_caches(shape, tokens, mode, page_size):
+    """The projection as a stream of 256 x 256 tiles, from the four matrices (1b) and from packed weights (paper): tiles that two
+    workgroups share (84, 70), a whole round and tiles to share behind it (364, 259), two rounds (392, 385).  Prompts, and chunks
+    behind cached rows whose sines come per token; one sequence's first row has no page.  Outputs and rows bit for bit those of
+    the contiguous caches; all key and latent rows against the definition in 64 bits, two sequences' outputs against the oracle."""
+    lens = [tokens // 2, 1, tokens // 5, 64]
+    lens.append(tokens - sum(lens))
+    prefix = [37, 500, 0, 200, 129] if mode == "chunk" else [0] * 5
+    slots, lost = [4, 0, 5, 2, 1], 3
+    pps = (max(n + p for n, p in zip(lens, prefix)) + page_size) // page_size
+    cap = pps * page_size
+    wl = W.scaled(_base(shape, "prefill"), d_model=256, batch=5, seqlen=max(lens), min_seqlen=None)
+    rng = W.make_rng(wl)
+    w = W.draw_weights(wl, rng, std=wl.d_model ** -0.5)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    x = W.draw_hidden(wl, rng, tokens)
+    wdev = U.upload_weights(w, wl.dtype)
+    gen = torch.Generator(device="cuda").manual_seed(tokens)
+    kd, cd = (torch.randn((6, cap, n), generator=gen, device="cuda").bfloat16() for n in wl.kv_width)
+    flat = U.DeviceCache(wl, 6, cap, k=kd.clone(), c=cd.clone())
+    paged = U.PagedDeviceCache(wl, 6, page_size, pps, seed=17, fill=FILL, missing=[(slots[lost], prefix[lost] // page_size)])
+    paged.store(kd, cd)
+    outs = []
+    for cache in (flat, paged):
+        for s, n in zip(slots, prefix):
+            cache.seq_lens[s] = n
+        run = U.run_prefill_chunk if mode == "chunk" else U.run_prefill
+        outs.append(run(wl, wdev, x, cu, cache=cache, slots=slots))
+    for b, s in enumerate(slots):
+        full = b == lost
+        assert int(paged.seq_lens[s]) == prefix[b] + (0 if full else lens[b]) and int(paged.status[s]) == (B.GTA_ERR_CACHE_FULL if full else 0)
+        got, want = outs[1][cu[b]:cu[b + 1]], outs[0][cu[b]:cu[b + 1]]
+        assert bool((got == 0).all()) if full and mode == "chunk" else _same_bits(got, want), f"output of sequence {b}"
+    kl, cl = paged.logical()
+    others = [s for s in range(6) if s != slots[lost]]
+    assert _same_bits(kl[others], flat.k[others]) and _same_bits(cl[others], flat.c[others])
+    assert paged.spare_untouched(FILL)
+    xd, dh = B.to_device(x, wl.dtype).double(), wl.head_dim
+    wk, wc = wdev["wk"].double(), wdev["wc"].double()
+    for b, s in enumerate(slots):
+        xb, at = xd[cu[b]:cu[b + 1]], slice(prefix[b], prefix[b] + lens[b])
+        ang = torch.arange(at.start, at.stop, device="cuda", dtype=torch.float64)[:, None] * \
+            wl.rope_base ** (-torch.arange(dh // 2, device="cuda", dtype=torch.float64) * 2 / dh)
+        lo, hi = (xb @ wk).view(lens[b], -1, dh).split(dh // 2, dim=-1)
+        c, sn = ang.cos()[:, None], ang.sin()[:, None]
+        for name, got, ref in (("K", flat.k, torch.cat([lo * c - hi * sn, hi * c + lo * sn], dim=-1).reshape(lens[b], -1)), ("C", flat.c, xb @ wc)):
+            U.assert_close(U.f64(got[s, at]), ref.cpu().numpy(), wl.dtype, f"{name} rows of sequence {b}", max(1.0, float(ref.abs().max())))
+        assert _same_bits(flat.k[s, :at.start], kd[s, :at.start]) and _same_bits(flat.k[s, at.stop:], kd[s, at.stop:])
+    cfg, ow = U.oracle_config(wl), U.oracle_weights(w)
+    for b in (1, 3):
+        pos = np.arange(prefix[b], prefix[b] + lens[b])
+        Q, K, C, G = orc.project_tokens(cfg, ow, x[cu[b]:cu[b + 1]], pos)
+        K = np.concatenate([U.f64(kd[slots[b], :prefix[b]]).reshape(prefix[b], wl.n_kgroups, dh), K])
+        C = np.concatenate([U.f64(cd[slots[b], :prefix[b]]).reshape(prefix[b], wl.n_cgroups, wl.latent_dim), C])
+        L = np.stack([orc.attention_map_rows(cfg, Q[:, g], pos, K[:, cfg.k_of_group(g)]) @ C[:, cfg.c_of_group(g)] for g in range(wl.n_qgroups)], axis=1)
+        ref = orc.decode_heads(cfg, ow, L, G)
+        U.assert_close(U.f64(outs[0][cu[b]:cu[b + 1]]), ref, wl.dtype, f"sequence {b}", max(1.0, float(np.abs(ref).max())))
+
+
 def test_prefill_into_missing_pages_flags_the_slot():
     """A sequence whose rows reach a table entry without a page keeps its old length and is flagged; its
     output rows do not depend on the cache and are still right; the other sequence is stored."""
