@@ -61,8 +61,8 @@ def test_fresh(shape, lens, bound):
 
 @pytest.mark.parametrize("lens", [[1000, 300, 129, 1, 700, 640, 900], [1030] * 6], ids=["ragged", "alike"])
 def test_paired_workgroups(lens):
-    """257 to 512 workgroups of four waves: those behind the first 256 go backwards.  Short ragged prompts (280 workgroups), and
-    prompts of one length, which stay with four waves beyond 1024 keys (432)."""
+    """257 to 512 workgroups of four waves: those behind the first 256 go backwards.  All (level, sequence) pairs on the chip at once:
+    short ragged prompts (448 workgroups), and prompts of one length, which stay with four waves beyond 1024 keys (432)."""
     wl, w, x, _ = _setup("1b", sum(lens))
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     out = U.f64(U.run_prefill(wl, U.upload_weights(w, "bf16"), x, cu))
@@ -71,6 +71,28 @@ def test_paired_workgroups(lens):
         _check(wl, w, x[cu[b]:cu[b + 1]], none, none, 0, out[cu[b]:cu[b + 1]], f"{lens} sequence {b}")
     if len(set(lens)) == 1:   # every row is written
         assert (np.abs(out).max(axis=1) > 0).all()
+
+
+@pytest.mark.parametrize("chunk", [False, True])
+@pytest.mark.parametrize("lens", [[1000, 129, 300, 1, 640, 0, 257, 128, 400, 145], [1000, 900, 1, 640, 1000, 128, 897, 600, 1000, 774]],
+                         ids=["in turn", "dealt"])
+def test_paired_workgroups_of_ranked_tiles(lens, chunk):
+    """More pairs than the chip holds (640 workgroups), so that tiles are ranked, and a bound of 33 tiles (264 workgroups, to the XCDs
+    in turn) and of 64 (512, eight tiles at a time), more than there are tiles; chunks with the workgroups that set the lengths behind
+    them."""
+    wl, w, x, r2 = _setup("1b", sum(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    prefix, cap = [0, 40, 500, 300, 127, 9, 128, 0, 33, 470] if chunk else [0] * 10, 1408
+    k, c = W.draw_cache(wl, r2, 10, cap)
+    cache = U.DeviceCache(wl, 10, cap, B.to_device(k, "bf16"), B.to_device(c, "bf16"))
+    cache.seq_lens.copy_(torch.tensor(prefix, dtype=torch.int32))
+    run = U.run_prefill_chunk if chunk else U.run_prefill
+    out = U.f64(run(wl, U.upload_weights(w, "bf16"), x, cu, cache=cache))
+    assert cache.seq_lens.tolist() == [p + n for p, n in zip(prefix, lens)]
+    for b in range(10):
+        if lens[b]:
+            _check(wl, w, x[cu[b]:cu[b + 1]], k[b].astype(np.float64), c[b].astype(np.float64), prefix[b], out[cu[b]:cu[b + 1]],
+                   f"sequence {b}: {lens[b]} behind {prefix[b]}")
 
 
 @pytest.mark.parametrize("chunk", [False, True])
