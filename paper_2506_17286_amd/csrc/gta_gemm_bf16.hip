@@ -201,8 +201,8 @@ __device__ __forceinline__ const A &kernel_args() {
 // A workgroup works through the tiles blockIdx.x, + gridDim.x, .. of a launch of one workgroup per CU; the loads of a tile
 // start under the last k-steps of the tile before it, and what is behind its epilogue's stores does not wait for them.
 // 256 x 256 tile, eight waves (two per SIMD) of 64 x 128.  X comes in rows of 64 k (128 bytes: with 64 bytes of a row per
-// load, the L2 moved every line twice and the loads alone took longer than the matrix instructions, 0.52 against 0.38 us
-// per 32 k at K = 1280), three stages of 32 KiB; weights in four stages of 32 k, 16 KiB each.  The unit of the loop is a
+// load, the L2 moved every line twice and the loads alone took longer than the matrix instructions, 0.52 against 0.43 us
+// per 32 k at K = 1280; now 0.38), three stages of 32 KiB; weights in four stages of 32 k, 16 KiB each.  The unit of the loop is a
 // half step of 32 k (two k-steps of eight MFMAs per wave); half step u
 //   * reads the fragments of its second k-step under the MFMAs of the first;
 //   * waits at a barrier: every wave has then read all of weight stage u (u odd: and of X stage u / 2), and the loads of
@@ -437,9 +437,9 @@ __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d) {
 // the x-th eighth of that order: the 32 workgroups that run together on an XCD then form one block,
 // share 8 X strips and 4 weight strips (every operand slice fetched into the L2 is used 4 or 8 times),
 // whatever the numbers of row strips and column tiles are.  Edge blocks are simply smaller.
-__device__ __forceinline__ void tile_of_id(int id, int ntn, int ntm, int &mt, int &nt) {
+__device__ __forceinline__ void tile_of_block(int ntn, int ntm, int &mt, int &nt) {
   constexpr int RB = 8, PW = 4;
-  const int nblk = ntn * ntm, per = nblk / 8;
+  const int id = blockIdx.x, nblk = ntn * ntm, per = nblk / 8;
   const int pos = id < per * 8 ? (id % 8) * per + id / 8 : id;   // the last nblk % 8 tiles keep their place
   const int band = pos / (RB * ntn);
   int rem = pos - band * RB * ntn;
@@ -449,7 +449,6 @@ __device__ __forceinline__ void tile_of_id(int id, int ntn, int ntm, int &mt, in
   mt = band * RB + rem % h;
   nt = panel * PW + rem / h;
 }
-__device__ __forceinline__ void tile_of_block(int ntn, int ntm, int &mt, int &nt) { tile_of_id(blockIdx.x, ntn, ntm, mt, nt); }
 
 // ---- epilogue of a stream's tile ----------------------------------------------------------------
 // A wave rounds its 64 x 128 part to bf16 and writes it through its 4 KiB of scratch, 32 rows x 64 columns at a time (in the
@@ -1046,8 +1045,8 @@ void launch(K kernel, const Args &a, int ntiles, hipStream_t st) {
 
 }  // namespace
 
-// The pipelined 256 x 256 tile against packed weights: widths in units of a 64-column group that
-// holds whole heads, at least four k-tiles of 32 (H in units of 128 like everything on this path).
+// The stream of 256 x 256 tiles against packed weights: widths in units of a 64-column group that
+// holds whole heads, H a multiple of 128, at least 256 (gemm_stream).
 static bool proj_packed_ok(const Dims &d) {
   if (d.dh != 64 && d.dh != 128) return false;
   if (d.wq_w % d.dh || d.wk_w % d.dh || d.wc_w % 64 || d.wg_w % 64 || d.wq_w % 64 || d.wk_w % 64) return false;
@@ -1061,7 +1060,7 @@ static bool proj_direct_ok(const Dims &d) {
   return !(d.H % 64 || d.dl % 64 || d.wq_w % 128 || d.wk_w % 128 || d.wc_w % 128 || d.wg_w % 128);
 }
 static bool proj_direct_big(const Dims &d) {
-  // the pipelined loop takes at least four k-tiles of 32
+  // the stream takes whole tiles of columns from one matrix and multiples of 128 in K, at least 256
   return proj_direct_ok(d) && !(d.wq_w % 256 || d.wk_w % 256 || d.wc_w % 256 || d.wg_w % 256) && d.H % 128 == 0 && d.H >= 256;
 }
 

@@ -128,11 +128,12 @@ struct AttnArgs {
 __device__ __forceinline__ int splits_of(const AttnArgs &a, int keys) { return max(min((keys + (32 << a.split_shift) - 1) >> (5 + a.split_shift), a.splits), 1); }
 
 // The fused value decoder: the group's four heads of 64 columns one after the other (two key halves: two each).  The normalised
-// tile stays in registers: its accumulators, rounded, are the column operand as they stand, with k in the order of
-// decoder_frag.  A head's matrix [128, 64] goes straight into LDS, two ahead (two key halves: all four), and a wave's 32 x 64 gate
-// values through 4 KiB of its own, which then take the gated heads on their way to 16-byte stores.
+// tile stays in registers: its accumulators, rounded, are the column operand once the lane halves have swapped two words of
+// each fragment.  A head's matrix [128, 64] goes straight into LDS, one ahead of its use (two key halves: all four at once), and a wave's
+// 32 x 64 gate values through 4 KiB of its own, which then take the gated heads on their way to 16-byte stores.
 template <class T>
 struct FusedDecoder {
+  static_assert(T::DH == 64 && T::DLW == 128, "four heads of 64 on a latent of 128 (attn_decoder_fusable)");
   static constexpr int HEADS = 4, HPW = HEADS / T::KS;          // heads of a group, of a wave
   static constexpr int W_BYTES = 128 * 128, WBUF = T::KS == 1 ? 2 : HEADS;
   static constexpr int IO_OFF = WBUF * W_BYTES, L_OFF = IO_OFF + T::NW * 4096;   // two key halves: L of the waves that merged it
@@ -918,9 +919,11 @@ void launch_tile(AttnArgs a, const Dims &d, int batch, int max_len, hipStream_t 
   // ids for every (level, sequence), and no more than this many query tiles whatever the lengths are
   const int64_t every = (int64_t)a.n_qtiles * batch;
   int64_t tiles = std::min(every, a.total / T::BQ + batch);
-  // Where the chip holds every (level, sequence) at once the order means nothing and tiles need no ranks (two workgroups
-  // of four waves on a CU, one of eight): ragged calls, with and without ranks, paper's layers 7 x 41..331 tokens 41.4 / 40.8
-  // us, 8 x 10..80 42.2 / 41.5, 32 x 20..100 67.7 / 66.8, 1B shape 4 x 10..40 behind 6000 70.0 / 68.8.
+  // Where the chip holds every (level, sequence) at once, two workgroups of four waves or one of eight on a CU, the order means nothing
+  // and tiles need no ranks: ragged calls, with and without ranks, paper's layer 7 x 41..331 tokens 53.4 / 53.1 us, 8 x 10..80
+  // 32.7 / 32.6, 1B shape 4 x 10..40 behind 6000 67.3 / 66.5.  Heads of 64 with latent tiles of 128 have three workgroups of four waves on
+  // a CU, but there the missing tiles of 513 to 768 ids cost more than the ranks (60 x 25..250 91.9 / 95.7, 20 x 80..800 102.3 /
+  // 105.2, 18 x 100..1000 behind 3000 202 / 218, one length level).
   const bool fits = every * a.nq * a.ndlc * a.splits <= 512 / T::KS, at_once = batch > 1 && fits;
   // Nor do fresh prompts of one tile each or of one length: 4096 x 32 tokens of the 1B shape 4.46 -> 2.57 ms, 4096 x 2..16 behind 100
   // rows, paper's layer, 2.57 -> 1.12 (ranked with a walk over all offsets).  With offsets the lengths show in ids that are no more than
@@ -971,14 +974,16 @@ int64_t half_workgroups(const Dims &d, int batch, int max_len, int dlw) { return
 // max_keys: host bound of a sequence's keys.  part: scratch for key splits (attn_split_bytes) or NULL.
 template <int DH, int DLW, bool FUSE>
 void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys, float *part, hipStream_t st) {
-  // Workgroups of 128 queries, all keys walked by four waves, two workgroups per CU.  Launches whose workgroups would
-  // all be on the chip at once (512) only wait for the longest chain of key tiles; there eight waves share a workgroup's
+  // Workgroups of 128 queries, all keys walked by four waves, two workgroups per CU (heads of 64 and latent tiles of 128: three, for
+  // which the lines lie in the same places).  Launches whose workgroups would all be on the chip at once (512) only wait for the longest chain of key tiles; there eight waves share a workgroup's
   // queries in two key halves: half the chain, at 2 us of merge and one workgroup per CU.  Measured whole calls, one
   // half against two, 1B shape: fresh 1 x 2000 127 against 122 us, 1 x 8192 404 / 360 (512 workgroups), 2 x 4096 281 /
   // 267 (512), 2 x 3000 ragged 213 / 197 (384), 3 x 4000 373 / 398 (768); chunks 8 x 300 behind 4000 189 / 172 (192),
-  // 8 x 600 behind 4000 290 / 291 (320), 5 x 2000 ragged behind 5000 389 / 421 (640); paper shape 4 x 2048 138 / 125
-  // (256).  Up to 1024 keys the chain is too short for more than one round of the two halves: 8 x 1000 191 / 196 (512),
-  // paper 16 x 700 154 / 160 (384), but 2 x 1000 99 / 91 (64); up to 256 keys it is never worth it: 1 x 128 40.7 / 42.2.
+  // 8 x 600 behind 4000 290 / 291 (320), 5 x 2000 ragged behind 5000 389 / 421 (640); paper's layer 1 x 8000 224 / 182 (320), 4 x 2048
+  // 120 / 109 (320), 5 x 2000 143 / 138 (400), 6 x 2000 151 / 151 (480), of 200..2000 119 / 108, chunks 20 x 30..300 behind 2000 109 / 101
+  // (300), of one length 125 / 145.  Up to 1024 keys the chain is too short for more than one round of the two halves: 8 x 1000
+  // 191 / 196 (512), paper's layer 10 x 1000 126 / 130 (400), 16 x 700 128 / 136 (480), but 2 x 1000 75 / 70 (80); up to 256 keys it
+  // gains little or nothing: paper's layer 1 x 128 26.4 / 26.4, 1 x 256 36.0 / 35.1, 1B shape 1 x 128 40.7 / 42.2.
   const int64_t half = half_workgroups(d, batch, max_len, DLW);
   a.splits = 1;
   // Fresh prompts of one length whose workgroups nearly fill the chip keep one half, the longest paired with the shortest on a CU

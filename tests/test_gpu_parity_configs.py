@@ -269,10 +269,10 @@ def test_tuned_prefill_ragged_small(shape, with_wo, tokens):
         base = W.scaled(W.WORKLOADS[1], **WIDE_ROW_GROUPINGS[shape])
     else:
         base = W.WORKLOADS[1] if shape == "1b" else W.WORKLOADS[4]
-    # calls of few tokens take the kernels for few rows and the 64-row tiles that split K (up to 768 tiles of 64 x
-    # 128), longer ones the 256-row tiles, on a ragged mix: with many tokens the projections of at least 1472 columns
-    # (1b, wide, paper, paper_nc2, packed128_pad, q8k4c2, c4) take the latter.  Every GEMM of every shape on its 256-row
-    # tiles is checked stage by stage in test_gpu_prefill_gemms.py
+    # calls of few tokens take the kernels for few rows and the 64-row tiles that split K (up to 512 tiles of 64 x 128, at the
+    # 8 x 128 + 1024 shape, with its contraction of 4096, 768), longer ones the 256-row tiles, on a ragged mix: 4204 tokens are 66 rows of
+    # such tiles, so that every projection here (8 to 56 of them wide) takes the latter.  Every GEMM of every shape on
+    # its 256-row tiles is checked stage by stage in test_gpu_prefill_gemms.py
     lens = [1, 37, 256, 300, 129, 64]
     slots = [5, 0, 3, 1, 6, 2]
     if tokens == "many":

@@ -64,9 +64,9 @@ def test_prefix_then_chunk_equals_one_pass(shape, with_wo):
 
 @pytest.mark.parametrize("shape", ["1b", "paper"])
 def test_chunk_beyond_the_short_prefill_limit(shape):
-    """A chunk call with more tokens than the short-prefill projection takes (1728 at the 1B shape, 3456 at the
-    paper's): 256-row projection tiles with per-token RoPE rows.  A long and a short chunk behind 100 and
-    650 cached rows."""
+    """A chunk call with more tokens than the short-prefill projection takes (1152 at the 1B shape, 2304 at the paper's): 256 x 256
+    projection tiles, shared by two workgroups each (112 and 126), with per-token RoPE rows.  (Whole rounds of them: the calls of many
+    tokens in test_gpu_paged_cache.py.)  A long and a short chunk behind 100 and 650 cached rows."""
     long_len = 1900 if shape == "1b" else 4500
     lens, pre = [long_len, 700], [100, 650]
     wl = W.scaled(_base(shape), batch=2, seqlen=long_len, min_seqlen=None)

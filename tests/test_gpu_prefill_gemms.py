@@ -1,7 +1,6 @@
 """The prefill's GEMMs at the edges of their tiles: the few-row kernel, the 64-row tiles that split K over their waves
-(three stages of 64: contractions of one, two and more) and the 256 x 256 tiles (operands loaded straight into LDS, eight
-waves; the decoder's in four stages of 32).  One valid row in the last row tile and full row tiles, contractions that leave the stages at
-each phase, two heads side by side in a weight tile, several heads and one, the packed weights, every gate.
+(three stages of 64: contractions of one, two and more) and the stream of 256 x 256 tiles (eight waves; X in three stages of 64, weights in
+four of 32).  One valid row in the last row tile and full row tiles, contractions that leave the stages at each phase, two heads side by side in a weight tile, several heads and one, the packed weights, every gate.
 
 Reference: float64 on the same bf16 inputs.  Bounds: the bf16 tolerances of the parity gate, the max-abs one scaled by
 the largest reference value (the outputs carry one bf16 rounding, 2^-9 of their size)."""
