@@ -987,8 +987,10 @@ void launch_attn(AttnArgs a, const Dims &d, int batch, int max_len, int max_keys
   const int64_t half = half_workgroups(d, batch, max_len, DLW);
   a.splits = 1;
   // Fresh prompts of one length whose workgroups nearly fill the chip keep one half, the longest paired with the shortest on a CU
-  // (launch_tile): 1B shape 4 x 2000 203 / 197 (two halves first), 5 x 1500 188 / 179 (480), 6 x 1100 164 / 156 (432), but 3 x 1500 129 /
-  // 131 (288), 2 x 3500 215 / 219 (448), 1 x 8000 352 / 358.  Chunks of one length gain as much behind equal caches (8 x 600
+  // (launch_tile): 1B shape, two halves / one, 3 prompts 3 x 1900 173.2 / 177.0 us (360 workgroups), 3 x 2000 183.1 / 183.5 (384), 3 x
+  // 2300 199.1 / 198.1 (432), 3 x 2600 226.5 / 220.9 (504); 4 x 1400 162.2 / 164.5 (352), 4 x 1600 180.3 / 177.9 (416), 4 x 2000 212.6 /
+  // 203.9 (512); 5 x 1500 197.2 / 187.5 (480); 6 x 1100 174.8 / 165.6 (432).  Two prompts are ahead only from 480 on (2 x 3500 230.4 /
+  // 233.5, 448; 2 x 4000 261.5 / 258.1), one never (1 x 8000 353.6 / 361.3).  Chunks of one length gain as much behind equal caches (8 x 600
   // behind 4000 315 / 271) and lose behind unequal ones, which the host does not see (behind 200..4000 226 / 246).
   const bool alike = DLW == 256 && !a.prefix && batch > 2 && a.total == (int64_t)batch * max_len && half > 384;
   if (half > 512 || max_keys <= 256 || (half > 256 && max_keys <= 1024) || alike) {
